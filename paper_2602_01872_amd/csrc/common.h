@@ -242,8 +242,7 @@ struct GemmTNArgs {
     void* workspace = nullptr;
     size_t workspace_bytes = 0;
     const int32_t* a_rows = nullptr; // row i of A is stored at row a_rows[i] (null: i)
-    float* colsum_out = nullptr;     // optional [N]: column sums of B (each row times colsum_scale[m] if set)
-    const float* colsum_scale = nullptr;
+    float* colsum_out = nullptr;     // optional [N]: column sums of B
     // A second product from the same launch (at most one of the two):
     const float* A2 = nullptr;       // C2[K x N] = A2[M x K]^T B   (fp32, rows not gathered)
     int64_t lda2 = 0;

@@ -1,4 +1,4 @@
-// Dense feature transforms on the gfx950 matrix cores (fp32 MFMA, fp32 accumulate).
+// Dense feature transforms on the gfx950 matrix cores, in fp32 precision.
 //
 //   gemm_nn:  C[M x N] = epilogue(A[M x K] B[K x N] + A2[M x K2] B2[K2 x N])   (X W, dY W^T)
 //   gemm_tn:  C[K x N] = A[M x K]^T B[M x N]                                   (X^T dY)
@@ -8,16 +8,21 @@
 // slice of the node dimension (tn, partial sums reduced afterwards in a fixed order, so
 // the result does not depend on scheduling).
 //
-// Tiling: 256 threads = 4 wavefronts laid out WM x WN; a wavefront owns TM x TN tiles of
-// 32x32 computed with v_mfma_f32_32x32x2_f32.  Operand layout of that instruction on a
-// 64-lane wavefront: lane l supplies A[i = l%32][k = l/32] and B[k = l/32][j = l%32]; of
-// the 16 accumulator registers, register r of lane l holds D[8*(r/4) + 4*(l/32) + r%4][l%32].
-// Both operands are staged in LDS k-major (the 32 lanes of a half-wave read 32 consecutive
-// floats: no bank conflicts).  The next k-tile is requested from HBM into raw registers
-// before the current one is multiplied and is only touched (converted, masked, written to
-// LDS) after the multiply, so the loads overlap the matrix instructions; addresses are
-// clamped into the operand instead of branching, and out-of-range elements are zeroed when
-// they are written to LDS.
+// Arithmetic.  The bf16 matrix instructions run at 16 times the rate of the fp32 ones, and an fp32 number is
+// exactly the sum of three bf16 numbers: x = hi + mid + lo, hi = the top 16 bits of x, mid = bf16(x - hi) and
+// lo = x - hi - mid, which has at most 8 significant bits (both differences are exact).  A product of two fp32
+// numbers is then nine bf16 products, each exact in fp32; six of them are computed (hi.hi, hi.mid, mid.hi, mid.mid,
+// hi.lo, lo.hi) and added in the fp32 accumulators, the small ones first.  The three left out (mid.lo, lo.mid, lo.lo)
+// are below 2^-22 of |a||b| and of random sign: together less than the rounding of the fp32 sums they would enter.
+// Measured against fp64 (normal deviates) the error is smaller than that of the fp32 instructions at every length, because
+// an accumulator is rounded 6 times per 32 terms and not 16 times: rms 2.3e-7 against 2.9e-7 of the result at K = 256,
+// 4.8e-7 against 5.7e-7 at K = 1024, and X^T dY over 10^6 rows 9.5e-7 against 1.12e-6.  An operand stored in bf16 is its own hi: three
+// products.  The split is done by the thread that stages an element (5.5 instructions per element).
+//
+// Loads and arithmetic overlap the same way everywhere: the next k-tile is requested from HBM into raw registers before
+// the current one is multiplied and is only touched (split, masked, written to LDS) afterwards; addresses are clamped into the
+// operand instead of branching.  The layouts are described at the kernels.  Products whose operands are not 16-byte
+// friendly, or whose B is not given transposed, take gemm_nn_kernel, which uses the fp32 instructions.
 #include "common.h"
 
 #include <algorithm>
@@ -29,6 +34,7 @@ namespace grp {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 32;      // k-tile depth
+constexpr int NT_WGS = 3;   // resident workgroups per CU that the 128-wide tiles are built for (48 KB of LDS and 168 registers each)
 constexpr int NXCD = 8;     // L2 domains; consecutive workgroup ids go round them
 
 template <typename T> __device__ __forceinline__ float to_f(T v);
@@ -72,6 +78,78 @@ __device__ __forceinline__ uint4 ldg_safe4(const T* __restrict__ row, bool row_o
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 __device__ __forceinline__ int64_t lmin(int64_t a, int64_t b) { return a < b ? a : b; }
 
+// ------------------------------------------------------------------------------- fp32 as three bf16 planes
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// a, b -> packed pairs hi, mid, lo with a = hi.x + mid.x + lo.x exactly (hi truncates, so it cannot overflow).
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    hi = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    const floatx2 r = {a - __uint_as_float(ua & 0xFFFF0000u), b - __uint_as_float(ub & 0xFFFF0000u)};
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+    const float la = r.x - __uint_as_float(mid << 16), lb = r.y - __uint_as_float(mid & 0xFFFF0000u);
+    lo = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+}
+__device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& mid, uint4& lo) {
+    split2(v[0], v[1], hi.x, mid.x, lo.x);
+    split2(v[2], v[3], hi.y, mid.y, lo.y);
+    split2(v[4], v[5], hi.z, mid.z, lo.z);
+    split2(v[6], v[7], hi.w, mid.w, lo.w);
+}
+// Eight k values of one row into the three planes of a tile; `at` is their place in the first.
+template <int PLANE>
+__device__ __forceinline__ void put_split8(unsigned char* at, const float (&v)[8]) {
+    uint4 hi, mid, lo;
+    split8(v, hi, mid, lo);
+    *reinterpret_cast<uint4*>(at) = hi;
+    *reinterpret_cast<uint4*>(at + PLANE) = mid;
+    *reinterpret_cast<uint4*>(at + 2 * PLANE) = lo;
+}
+
+__device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// One 16-deep step of a wavefront's TM x TN block of 32x32 tiles.  ap / bp: this lane's eight k of its first tile row in the
+// first plane.  MAYBE_ONE and one: A is a single plane (an operand stored in bf16).
+template <int TM, int TN, int PLANE_A, int PLANE_B, bool MAYBE_ONE>
+__device__ __forceinline__ void mma32(const unsigned char* ap, const unsigned char* bp, bool one, floatx16 (&acc)[TM][TN]) {
+    auto at = [](const unsigned char* p) { return *reinterpret_cast<const bf16x8*>(p); };
+    auto mul = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+    bf16x8 ah[TM], am[TM], al[TM], bh[TN], bm[TN], bl[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) ah[i] = at(ap + i * 32 * 64);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        bh[j] = at(bp + j * 32 * 64);
+        bm[j] = at(bp + PLANE_B + j * 32 * 64);
+        bl[j] = at(bp + 2 * PLANE_B + j * 32 * 64);
+    }
+    auto more_of_a = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            am[i] = at(ap + PLANE_A + i * 32 * 64);
+            al[i] = at(ap + 2 * PLANE_A + i * 32 * 64);
+        }
+    };
+    if (!MAYBE_ONE) more_of_a();
+    mul(ah, bl);                                      // small products first
+    if (!MAYBE_ONE || !one) {
+        if (MAYBE_ONE) more_of_a();
+        mul(al, bh);
+        mul(am, bm);
+        mul(am, bh);
+    }
+    mul(ah, bm);
+    mul(ah, bh);
+}
+
 // One BKT-deep step of the wavefront's TM x TN block from k-major LDS tiles.  The operands of
 // the next k-pair are read from LDS before the matrix instructions of the current one are
 // issued, so the LDS latency hides behind them.
@@ -97,41 +175,6 @@ __device__ __forceinline__ void mma_step(const float* __restrict__ As, const flo
             for (int j = 0; j < TN; ++j) b[nxt][j] = bp[(k + 2) * PB + 32 * j];
         }
         __builtin_amdgcn_sched_barrier(0);    // keep the next operands' LDS reads ahead of these MFMAs
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// Variant for the tn kernel, whose LDS tiles keep the output dimension contiguous: tile t of
-// a wavefront's TM (or TN) tiles takes the interleaved columns TM*l + t of its 32*TM-wide
-// block, so that one 4*TM-byte LDS read per lane feeds all TM tiles.  Accumulator register r
-// of tile (i, j) then holds row TM*(8*(r/4) + 4*(lane/32) + r%4) + i, column TN*(lane%32) + j
-// of the wavefront's block.
-template <int TM, int TN, int PA, int PB, int BKT>
-__device__ __forceinline__ void mma_step_interleaved(const float* __restrict__ As, const float* __restrict__ Bs, int a_off,
-                                                     int b_off, floatx16 (&acc)[TM][TN]) {
-    static_assert((TM == 1 || TM == 2) && (TN == 1 || TN == 2), "one LDS read of at most 8 bytes per operand");
-    const int lane = threadIdx.x & 63;
-    const int li = lane & 31, lk = lane >> 5;
-    const float* ap = As + lk * PA + a_off + TM * li;
-    const float* bp = Bs + lk * PB + b_off + TN * li;
-    float a[2][TM], b[2][TN];
-    auto rd = [&](int k, int buf) {
-        if constexpr (TM == 2) { const float2 t = *reinterpret_cast<const float2*>(ap + k * PA); a[buf][0] = t.x; a[buf][1] = t.y; }
-        else a[buf][0] = ap[k * PA];
-        if constexpr (TN == 2) { const float2 t = *reinterpret_cast<const float2*>(bp + k * PB); b[buf][0] = t.x; b[buf][1] = t.y; }
-        else b[buf][0] = bp[k * PB];
-    };
-    rd(0, 0);
-#pragma unroll
-    for (int k = 0; k < BKT; k += 2) {
-        const int cur = (k >> 1) & 1, nxt = cur ^ 1;
-        if (k + 2 < BKT) rd(k + 2, nxt);
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -393,297 +436,310 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 }
 
 // ------------------------------------------------------------------------------- NT (fast path of nn)
-// Epilogue of an interior tile (all 128 rows < M, all columns < N, bias and row scale either
-// cover the whole tile or none of it, every pointer and pitch 16-byte friendly).  A waiting
-// wavefront issues an instruction only every few cycles while another one feeds the matrix
-// pipe, so what counts here is the instruction count: uniform bases, 32-bit per-thread
-// offsets, immediate LDS offsets, the options applied without branches (neutral operands),
-// and all loads of a pass issued before its first store.
-template <int WM, int WN, int TM, int TN>
-__device__ __forceinline__ void nn_epilogue_interior(const GemmNNArgs& g, floatx16 (&acc)[TM][TN], float* lds, int64_t m0,
-                                                     int n0, bool use_bias, bool use_rs) {
-    constexpr int BN = WN * TN * 32;
-    constexpr int PC = BN + 4;
-    constexpr int C4 = BN / 4;                        // 16-byte columns per tile row
-    // tile rows covered by one pass of the workgroup: a power of two (a pass must not straddle
-    // two 32-row blocks); with BN = 96 only 192 of the 256 threads take part
-    constexpr int RPI = 256 / C4 >= 32 ? 32 : 256 / C4 >= 16 ? 16 : 256 / C4 >= 8 ? 8 : 4;
-    constexpr int ITS = WM * 32 / RPI;
-    constexpr int ITB = ITS < 8 ? ITS : 8;            // passes whose loads are in flight together
-    static_assert(32 % RPI == 0 && ITS % ITB == 0, "a pass must not straddle two 32-row blocks");
-    const int tid = threadIdx.x;
-    const bool active = tid < RPI * C4;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave / WN, wn = wave % WN;
-    const int li = lane & 31, lk = lane >> 5;
-    const uint32_t c4 = tid % C4, r0 = tid / C4;
-    const float* const rd = lds + r0 * PC + 4 * c4;
-    float* const wr = lds + (wm * 32 + 4 * lk) * PC + wn * TN * 32 + li;
-    float4 b4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (use_bias && active) b4 = *reinterpret_cast<const float4*>(g.bias + (n0 - g.bias_col0) + 4 * c4);
-    const float floor_v = g.relu ? 0.f : -INFINITY;
-    float* const Cb = g.C + m0 * g.ldc + n0;
-    float* const Rb = g.C_raw ? g.C_raw + m0 * g.ld_raw + n0 : nullptr;
-    const float* const Ab = g.addend ? g.addend + m0 * g.ld_add + n0 : nullptr;
-    const float* const Mb = g.mask ? g.mask + m0 * g.ld_mask + n0 : nullptr;
-    const float* const Sb = use_rs ? g.rowscale + m0 : nullptr;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        if (i > 0) __syncthreads();                   // the previous pass has been read out
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) wr[(8 * (r / 4) + (r % 4)) * PC + 32 * j] = acc[i][j][r];
-        __syncthreads();
-        if (!active) continue;                        // (uniform barriers above: nothing below synchronises)
-#pragma unroll
-        for (int it0 = 0; it0 < ITS; it0 += ITB) {
-            float4 av[ITB], mv[ITB];
-            float rs[ITB];
-#pragma unroll
-            for (int u = 0; u < ITB; ++u) {
-                const int it = it0 + u;
-                const uint32_t row = ((RPI * it) / 32 * TM + i) * 32 + (RPI * it) % 32 + r0;
-                av[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                mv[u] = make_float4(1.f, 1.f, 1.f, 1.f);
-                rs[u] = 1.f;
-                if (Ab) av[u] = *reinterpret_cast<const float4*>(Ab + (row * (uint32_t)g.ld_add + 4 * c4));
-                if (Mb) mv[u] = *reinterpret_cast<const float4*>(Mb + (row * (uint32_t)g.ld_mask + 4 * c4));
-                if (Sb) rs[u] = Sb[row];
-            }
-#pragma unroll
-            for (int u = 0; u < ITB; ++u) {
-                const int it = it0 + u;
-                const uint32_t row = ((RPI * it) / 32 * TM + i) * 32 + (RPI * it) % 32 + r0;
-                float4 v = *reinterpret_cast<const float4*>(rd + RPI * it * PC);
-                v.x += av[u].x + b4.x; v.y += av[u].y + b4.y; v.z += av[u].z + b4.z; v.w += av[u].w + b4.w;
-                if (Rb) *reinterpret_cast<float4*>(Rb + (row * (uint32_t)g.ld_raw + 4 * c4)) = v;
-                v.x = fmaxf(v.x * rs[u], floor_v); v.y = fmaxf(v.y * rs[u], floor_v);
-                v.z = fmaxf(v.z * rs[u], floor_v); v.w = fmaxf(v.w * rs[u], floor_v);
-                v.x = mv[u].x > 0.f ? v.x : 0.f; v.y = mv[u].y > 0.f ? v.y : 0.f;
-                v.z = mv[u].z > 0.f ? v.z : 0.f; v.w = mv[u].w > 0.f ? v.w : 0.f;
-                *reinterpret_cast<float4*>(Cb + (row * (uint32_t)g.ldc + 4 * c4)) = v;
-            }
-        }
-    }
-}
-
 // Same product as gemm_nn with B supplied transposed (Bt[N x K], k contiguous), which is how
-// the step keeps its weight matrices.  Both operands are then loaded along k as 16-byte
-// vectors and written to LDS unchanged (row-major [row][k], pitch 36 floats: the 16-byte
-// writes and reads of eight consecutive lanes fall in distinct banks).  A lane of the MFMA
-// reads its four consecutive k values with one 16-byte LDS read and uses them in four
-// consecutive MFMAs: within a k-tile, step (s, t) multiplies k = 8s + 4*(lane/32) + t from
-// both operands, a permutation of the tile's 32 k values.  Loads use a uniform base that
-// advances along k plus 32-bit per-thread offsets fixed before the loop; rows past the end of
-// an operand are clamped to its last row (their products land in rows or columns the epilogue
-// does not store, or zero-fills); only the last, ragged k-tile of a product is masked.
+// the step keeps its weight matrices.
+//
+// A wavefront owns 16*TM rows of C and all BN = 16*TN columns of the workgroup's tile.  Its rows of A go from memory to
+// its registers and are split there: no other wavefront needs them, so they never pass through LDS.  Only B does (three
+// planes, double-buffered, one barrier per 32-deep k-tile).  v_mfma_f32_16x16x32_bf16 is used with B as its first operand:
+// lane l supplies eight k of column n = l%16 of the tile (B) and of row m = l%16 (A), and its four accumulator registers
+// are C[m = l%16][n = 4*(l/16) .. +3], so that results leave as 16-byte vectors along rows and the epilogue reads its operands the
+// same way, without LDS.  Which eight k a lane takes is free as long as both operands agree: lane group q = l/16 takes
+// the four from 4*q and the four from 16 + 4*q, so that one load instruction covers 64 consecutive bytes of a row.
+// LDS rows hold 32 k (64 bytes, 4 places of 16); group q of row r sits at place q ^ ((r >> 1) & 3): the reads of eight
+// consecutive rows fall in distinct banks.
+// Loads use a uniform base that advances along k plus 32-bit per-thread offsets fixed before the loop; rows past the end of
+// an operand are clamped to its last row (their products are not stored); only the last, ragged k-tile of a product
+// is masked.
 // IRREG selects the variant with gathered (a_rows) or limited (a_valid_rows) A rows.
-template <typename AT, int WM, int WN, int TM, int TN, bool IRREG, int BKT, int NBUF>
-__global__ __launch_bounds__(256) void gemm_nt_kernel(GemmNNArgs g) {
+template <typename AT, int TM, int TN, bool IRREG>
+__global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     if (g.M_dev) {                                    // the launch was sized by upper bounds
         g.M = *g.M_dev;
         if (g.a_valid_rows_dev) g.a_valid_rows = *g.a_valid_rows_dev;
     }
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
-    constexpr int PK = BKT + 4;
-    constexpr int KQ = BKT / 4;                       // 16-byte slots per tile row
-    constexpr int RSTEP = 256 / KQ;                   // tile rows covered by one pass of the workgroup
-    constexpr int A_REPS = BM * BKT / 4 / 256, B_REPS = (BN * BKT / 4 + 255) / 256;
-    constexpr bool B_FULL = BN * BKT / 4 % 256 == 0;  // else the last pass over the B tile is partial (BN = 96, BKT = 16)
+    constexpr int BM = 4 * TM * 16, BN = TN * 16;
+    constexpr int PLANE = BN * 64;
+    constexpr int B_REPS = (BN + 63) / 64;            // a pass of the workgroup covers 64 rows of Bt
     constexpr bool A_BF16 = sizeof(AT) == 2;
-    static_assert(BM * BKT / 4 % 256 == 0 && BKT % 8 == 0, "the A tile must fill the workgroup");
-    constexpr int PC = BN + 4;
-    constexpr int MAIN_FLOATS = NBUF * (BM + BN) * PK;
-    constexpr int EPI_FLOATS = WM * 32 * PC;
-    constexpr int LDS_FLOATS = MAIN_FLOATS > EPI_FLOATS ? MAIN_FLOATS : EPI_FLOATS;
-    __shared__ __attribute__((aligned(16))) float lds[LDS_FLOATS];
-    float* const As0 = lds;
-    float* const Bs0 = lds + NBUF * BM * PK;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * 3 * PLANE];
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave / WN, wn = wave % WN;
-    const int li = lane & 31, lk = lane >> 5;
+    const int li = lane & 15, lq = lane >> 4;
     const int n_store = g.zero_pad_to > g.N ? g.zero_pad_to : g.N;
     const int n_tiles = (n_store + BN - 1) / BN;
+    // Workgroup ids go round the NXCD L2 domains; the column tiles of one row slab get ids
+    // that differ by NXCD, so they run on the same domain and the slab's second read hits L2.
     const int64_t hq = blockIdx.x / NXCD;
     const int64_t slab = (hq / n_tiles) * NXCD + blockIdx.x % NXCD;
     const int64_t m0 = slab * BM;
     const int n0 = (int)(hq % n_tiles) * BN;
     if (m0 >= g.M) return;
 
-    floatx16 acc[TM][TN];
+    floatx4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // Per-thread offsets of its 16-byte slots (k offset 4*kq included).  Regular variant: 32-bit
-    // offsets from the slab's first row; irregular variant: 64-bit offsets from the operand base.
-    const int kq4 = 4 * (tid % KQ);
-    const int trow = tid / KQ;
+    // Offsets of this lane's A rows (its first four k included).  Regular variant: 32-bit offsets from the slab's
+    // first row; irregular variant: 64-bit offsets from the operand base.
     const int rows_here = (int)lmin((int64_t)BM, g.M - m0);
     using aoff_t = typename std::conditional<IRREG, int64_t, uint32_t>::type;
-    aoff_t aoff[A_REPS];
-    uint32_t aoff2[A_REPS], boff[B_REPS], boff2[B_REPS];
-    bool a_zero[A_REPS];
+    aoff_t aoff[TM];
+    uint32_t aoff2[TM];
+    bool a_zero[TM];
     const AT* a_base = (const AT*)g.A;
     if (!IRREG) a_base += m0 * g.lda;
+    const float* const a2_base = g.A2 + m0 * g.lda2;
 #pragma unroll
-    for (int r = 0; r < A_REPS; ++r) {
-        const int lr = imin(trow + RSTEP * r, rows_here - 1);
+    for (int i = 0; i < TM; ++i) {
+        const int lr = imin(wave * 16 * TM + 16 * i + li, rows_here - 1);
         if (IRREG) {
             const int64_t a_valid = g.a_valid_rows > 0 ? g.a_valid_rows : g.M;
             const int64_t r1 = lmin(m0 + lr, a_valid - 1);
-            aoff[r] = (aoff_t)((g.a_rows ? (int64_t)g.a_rows[r1] : r1) * g.lda + kq4);
-            a_zero[r] = m0 + lr >= a_valid;
+            aoff[i] = (aoff_t)((g.a_rows ? (int64_t)g.a_rows[r1] : r1) * g.lda + 4 * lq);
+            a_zero[i] = m0 + lr >= a_valid;
         } else {
-            aoff[r] = (aoff_t)((uint32_t)lr * (uint32_t)g.lda + kq4);
-            a_zero[r] = false;
+            aoff[i] = (aoff_t)((uint32_t)lr * (uint32_t)g.lda + 4 * lq);
+            a_zero[i] = false;
         }
-        aoff2[r] = (uint32_t)lr * (uint32_t)g.lda2 + kq4;
+        aoff2[i] = (uint32_t)lr * (uint32_t)g.lda2 + 4 * lq;
     }
+    // This thread's part of the B tile: k group tq of rows trow, trow + 64.
+    const int tq = tid & 3, trow = tid >> 2;
+    uint32_t boff[B_REPS], boff2[B_REPS];
 #pragma unroll
     for (int r = 0; r < B_REPS; ++r) {
-        const uint32_t nc = imin(n0 + trow + RSTEP * r, g.N - 1);
-        boff[r] = nc * (uint32_t)g.ldbt + kq4;
-        boff2[r] = nc * (uint32_t)g.ldbt2 + kq4;
+        const uint32_t nc = imin(n0 + trow + 64 * r, g.N - 1);
+        boff[r] = nc * (uint32_t)g.ldbt + 4 * tq;
+        boff2[r] = nc * (uint32_t)g.ldbt2 + 4 * tq;
     }
-    const float* const a2_base = g.A2 + m0 * g.lda2;
+    const int nk1 = (g.K + BK - 1) / BK;
+    const int nk = nk1 + (g.K2 + BK - 1) / BK;
+    uint4 ra[TM][2], rb[B_REPS][2];
 
-    const int nk1 = (g.K + BKT - 1) / BKT;
-    const int nk2 = (g.K2 + BKT - 1) / BKT;
-    const int nk = nk1 + nk2;
-    uint4 ra[A_REPS], rb[B_REPS];
-
+    // a ragged last tile reads the operand's last whole four-element group again (masked afterwards)
+    auto clamp = [&](int k0, int Kc, int q, int& d0, int& d1) {
+        d0 = 0; d1 = 16;
+        if (k0 + BK > Kc) {
+            const int last = ((Kc + 3) & ~3) - 4 - k0 - 4 * q;
+            d0 = imin(0, last);
+            d1 = imin(16, last);
+        }
+    };
     auto fetch = [&](int kt) {
         const bool second = kt >= nk1;
-        const int k0 = (second ? kt - nk1 : kt) * BKT;
+        const int k0 = (second ? kt - nk1 : kt) * BK;
         const int Kc = second ? g.K2 : g.K;
-        // a ragged last tile reads the operand's last whole 16-byte slot again (masked when staged)
-        const int d = k0 + BKT > Kc ? imin(0, ((Kc + 3) & ~3) - 4 - k0 - kq4) : 0;
+        int d0, d1, e0, e1;
+        clamp(k0, Kc, lq, d0, d1);
+        clamp(k0, Kc, tq, e0, e1);
         if (second) {
             const float* pa = a2_base + k0;
             const float* pb = g.Bt2 + k0;
 #pragma unroll
-            for (int r = 0; r < A_REPS; ++r) ra[r] = ldg_raw4<float>(pa + (aoff2[r] + d));
+            for (int i = 0; i < TM; ++i) {
+                ra[i][0] = ldg_raw4<float>(pa + (aoff2[i] + d0));
+                ra[i][1] = ldg_raw4<float>(pa + (aoff2[i] + d1));
+            }
 #pragma unroll
-            for (int r = 0; r < B_REPS; ++r) rb[r] = ldg_raw4<float>(pb + (boff2[r] + d));
+            for (int r = 0; r < B_REPS; ++r) {
+                rb[r][0] = ldg_raw4<float>(pb + (boff2[r] + e0));
+                rb[r][1] = ldg_raw4<float>(pb + (boff2[r] + e1));
+            }
         } else {
             const AT* pa = a_base + k0;
             const float* pb = g.Bt + k0;
 #pragma unroll
-            for (int r = 0; r < A_REPS; ++r) ra[r] = ldg_raw4<AT>(pa + (aoff[r] + d));
+            for (int i = 0; i < TM; ++i) {
+                ra[i][0] = ldg_raw4<AT>(pa + (aoff[i] + d0));
+                ra[i][1] = ldg_raw4<AT>(pa + (aoff[i] + d1));
+            }
 #pragma unroll
-            for (int r = 0; r < B_REPS; ++r) rb[r] = ldg_raw4<float>(pb + (boff[r] + d));
+            for (int r = 0; r < B_REPS; ++r) {
+                rb[r][0] = ldg_raw4<float>(pb + (boff[r] + e0));
+                rb[r][1] = ldg_raw4<float>(pb + (boff[r] + e1));
+            }
         }
     };
-    float* const as_w = As0 + trow * PK + kq4;
-    float* const bs_w = Bs0 + trow * PK + kq4;
-    auto stage = [&](int kt) {
-        const bool second = kt >= nk1;
-        const int k0 = (second ? kt - nk1 : kt) * BKT;
-        const int Kc = second ? g.K2 : g.K;
-        const bool ragged = k0 + BKT > Kc;                // uniform: only the last k-tile of a product
-        const int kbase = k0 + kq4;
-        const int buf = NBUF == 1 ? 0 : (kt & 1);
-        float* As = as_w + buf * BM * PK;
-        float* Bs = bs_w + buf * BN * PK;
-        if (!ragged && !(A_BF16 && !second) && !IRREG) {  // common case: registers go to LDS as loaded
+    // eight values of k group q as floats, zero where the k does not exist
+    auto floats = [&](const uint4 (&r)[2], int left /*k values of the tile that exist*/, int q, float (&v)[8]) {
+        unpack4(r[0], false, *reinterpret_cast<float(*)[4]>(&v[0]));
+        unpack4(r[1], false, *reinterpret_cast<float(*)[4]>(&v[4]));
+        if (left < BK) {
 #pragma unroll
-            for (int r = 0; r < A_REPS; ++r) *reinterpret_cast<uint4*>(As + RSTEP * r * PK) = ra[r];
-#pragma unroll
-            for (int r = 0; r < B_REPS; ++r)
-                if (B_FULL || trow + RSTEP * r < BN) *reinterpret_cast<uint4*>(Bs + RSTEP * r * PK) = rb[r];
-            return;
+            for (int t = 0; t < 8; ++t) v[t] = 4 * q + (t & 3) + (t >= 4 ? 16 : 0) < left ? v[t] : 0.f;
         }
-#pragma unroll
-        for (int r = 0; r < A_REPS; ++r) {
-            float v[4];
-            unpack4(ra[r], A_BF16 && !second, v);
-            if (ragged) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = kbase + q < Kc ? v[q] : 0.f;
-            }
-            if (IRREG && !second && a_zero[r]) { v[0] = v[1] = v[2] = v[3] = 0.f; }
-            *reinterpret_cast<float4*>(As + RSTEP * r * PK) = make_float4(v[0], v[1], v[2], v[3]);
-        }
+    };
+    auto left_of = [&](int kt) { return kt >= nk1 ? g.K2 - (kt - nk1) * BK : g.K - kt * BK; };
+    unsigned char* const bput = lds + 64 * trow + 16 * (tq ^ ((trow >> 1) & 3));
+    auto stage_b = [&](int kt) {
+        const int left = left_of(kt);
 #pragma unroll
         for (int r = 0; r < B_REPS; ++r) {
-            float v[4];
-            unpack4(rb[r], false, v);
-            if (ragged) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = kbase + q < Kc ? v[q] : 0.f;
-            }
-            if (B_FULL || trow + RSTEP * r < BN)
-                *reinterpret_cast<float4*>(Bs + RSTEP * r * PK) = make_float4(v[0], v[1], v[2], v[3]);
+            float v[8];
+            floats(rb[r], left, tq, v);
+            if (BN % 64 == 0 || trow + 64 * r < BN) put_split8<PLANE>(bput + (kt & 1) * 3 * PLANE + 64 * 64 * r, v);
         }
     };
-
-    const float* const ap0 = As0 + (wm * TM * 32 + li) * PK + 4 * lk;
-    const float* const bp0 = Bs0 + (wn * TN * 32 + li) * PK + 4 * lk;
+    bf16x8 a[TM][3];
+    auto split_a = [&](int kt) {
+        const int left = left_of(kt);
+        const bool second = kt >= nk1;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const bool zero = IRREG && !second && a_zero[i];
+            if (A_BF16 && !second) {
+                uint4 w = make_uint4(ra[i][0].x, ra[i][0].y, ra[i][1].x, ra[i][1].y);
+                if (left < BK || zero) {
+                    const int have = zero ? -64 : left - 4 * lq;
+                    auto keep = [&](uint32_t x, int q) { return have >= q + 2 ? x : have == q + 1 ? x & 0xFFFFu : 0u; };
+                    w = make_uint4(keep(w.x, 0), keep(w.y, 2), keep(w.z, 16), keep(w.w, 18));
+                }
+                a[i][0] = a[i][1] = a[i][2] = __builtin_bit_cast(bf16x8, w);
+            } else {
+                float v[8];
+                floats(ra[i], left, lq, v);
+                if (zero) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) v[t] = 0.f;
+                }
+                uint4 hi, mid, lo;
+                split8(v, hi, mid, lo);
+                a[i][0] = __builtin_bit_cast(bf16x8, hi);
+                a[i][1] = __builtin_bit_cast(bf16x8, mid);
+                a[i][2] = __builtin_bit_cast(bf16x8, lo);
+            }
+        }
+    };
+    const unsigned char* const bget = lds + 64 * li + 16 * (lq ^ ((li >> 1) & 3));
     auto mma = [&](int kt) {
-        const float* ap = ap0 + (NBUF == 1 ? 0 : (kt & 1)) * BM * PK;
-        const float* bp = bp0 + (NBUF == 1 ? 0 : (kt & 1)) * BN * PK;
-        float4 a4[2][TM], b4[2][TN];
+        const unsigned char* const bp = bget + (kt & 1) * 3 * PLANE;
+        const bool one = A_BF16 && kt < nk1;
+        bf16x8 b[2][3];
+        auto get = [&](int j) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) a4[0][i] = *reinterpret_cast<const float4*>(ap + 32 * i * PK);
+            for (int p = 0; p < 3; ++p) b[j & 1][p] = *reinterpret_cast<const bf16x8*>(bp + p * PLANE + j * 16 * 64);
+        };
+        get(0);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) b4[0][j] = *reinterpret_cast<const float4*>(bp + 32 * j * PK);
-#pragma unroll
-        for (int s = 0; s < BKT / 8; ++s) {
-            const int cur = s & 1, nxt = cur ^ 1;
-            if (s + 1 < BKT / 8) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) a4[nxt][i] = *reinterpret_cast<const float4*>(ap + 32 * i * PK + 8 * (s + 1));
-#pragma unroll
-                for (int j = 0; j < TN; ++j) b4[nxt][j] = *reinterpret_cast<const float4*>(bp + 32 * j * PK + 8 * (s + 1));
-            }
+        for (int j = 0; j < TN; ++j) {
+            if (j + 1 < TN) get(j + 1);               // a column tile ahead: the LDS latency hides behind the products
             __builtin_amdgcn_sched_barrier(0);
+            const bf16x8 bh = b[j & 1][0], bm = b[j & 1][1], bl = b[j & 1][2];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bl, a[i][0], acc[i][j]);      // small products first
+            if (!one) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bh, a[i][2], acc[i][j]);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const float av = t == 0 ? a4[cur][i].x : t == 1 ? a4[cur][i].y : t == 2 ? a4[cur][i].z : a4[cur][i].w;
-                        const float bv = t == 0 ? b4[cur][j].x : t == 1 ? b4[cur][j].y : t == 2 ? b4[cur][j].z : b4[cur][j].w;
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
-                    }
+                for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bm, a[i][1], acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bh, a[i][1], acc[i][j]);
             }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bm, a[i][0], acc[i][j]);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[i][j] = mfma16(bh, a[i][0], acc[i][j]);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
 
     fetch(0);
-    stage(0);
-    __syncthreads();
+    stage_b(0);
     for (int kt = 0; kt < nk; ++kt) {
+        split_a(kt);
         if (kt + 1 < nk) fetch(kt + 1);
+        __syncthreads();                              // tile kt is written; everybody is done with tile kt - 1
         mma(kt);
-        if (NBUF == 1) __syncthreads();
-        if (kt + 1 < nk) stage(kt + 1);
-        __syncthreads();
+        if (kt + 1 < nk) stage_b(kt + 1);
     }
-    // interior tiles take the lean epilogue; edge tiles and awkward operands the general one
+
+    // ---- epilogue: (+ addend) (+ bias) -> C_raw; (* rowscale) (ReLU) (mask) -> C
     const int bias_n = g.bias_n > 0 ? g.bias_n : g.N - g.bias_col0;
     const int rs_cols = g.rowscale_cols > 0 ? g.rowscale_cols : g.N;
-    const bool bias_in = g.bias && n0 >= g.bias_col0 && n0 + BN <= g.bias_col0 + bias_n;
+    const bool vec = n_store % 4 == 0 && g.ldc % 4 == 0 && ((uintptr_t)g.C % 16) == 0 &&
+                     (!g.addend || (g.ld_add % 4 == 0 && ((uintptr_t)g.addend % 16) == 0)) &&
+                     (!g.mask || (g.ld_mask % 4 == 0 && ((uintptr_t)g.mask % 16) == 0)) &&
+                     (!g.C_raw || (g.ld_raw % 4 == 0 && ((uintptr_t)g.C_raw % 16) == 0));
+    // columns [n0, n0 + BN) all exist and lie on one side of the bias' and the row scale's ranges
+    const bool bias_in = g.bias && n0 >= g.bias_col0 && n0 + BN <= g.bias_col0 + bias_n && g.bias_col0 % 4 == 0 && ((uintptr_t)g.bias % 16) == 0;
     const bool bias_out = !g.bias || n0 + BN <= g.bias_col0 || n0 >= g.bias_col0 + bias_n;
     const bool rs_in = g.rowscale && n0 + BN <= rs_cols;
     const bool rs_out = !g.rowscale || n0 >= rs_cols;
-    const bool interior = m0 + BM <= g.M && n0 + BN <= g.N && (bias_in || bias_out) && (rs_in || rs_out) &&
-                          g.ldc % 4 == 0 && ((uintptr_t)g.C % 16) == 0 &&
-                          (!g.addend || (g.ld_add % 4 == 0 && ((uintptr_t)g.addend % 16) == 0)) &&
-                          (!g.mask || (g.ld_mask % 4 == 0 && ((uintptr_t)g.mask % 16) == 0)) &&
-                          (!g.C_raw || (g.ld_raw % 4 == 0 && ((uintptr_t)g.C_raw % 16) == 0)) &&
-                          (!bias_in || (g.bias_col0 % 4 == 0 && ((uintptr_t)g.bias % 16) == 0));
-    if (interior) nn_epilogue_interior<WM, WN, TM, TN>(g, acc, lds, m0, n0, bias_in, rs_in);
-    else nn_epilogue<true, WM, WN, TM, TN>(g, acc, lds, m0, n0, n_store);
+    const bool lean = vec && n0 + BN <= g.N && (bias_in || bias_out) && (rs_in || rs_out);
+    const float floor_v = g.relu ? 0.f : -INFINITY;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int lr = wave * 16 * TM + 16 * i + li;
+        if (lr >= rows_here) continue;
+        const int64_t m = m0 + lr;
+        const int nl = n0 + 4 * lq;
+        const float rs = g.rowscale ? g.rowscale[m] : 1.f;
+        float* const Cr = g.C + m * g.ldc + nl;
+        if (lean) {
+            const float s = rs_in ? rs : 1.f;
+            float4 av[TN], mv[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                av[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                mv[j] = make_float4(1.f, 1.f, 1.f, 1.f);
+                if (g.addend) av[j] = *reinterpret_cast<const float4*>(g.addend + m * g.ld_add + nl + 16 * j);
+                if (g.mask) mv[j] = *reinterpret_cast<const float4*>(g.mask + m * g.ld_mask + nl + 16 * j);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                float4 v = make_float4(acc[i][j][0] + av[j].x, acc[i][j][1] + av[j].y, acc[i][j][2] + av[j].z, acc[i][j][3] + av[j].w);
+                if (bias_in) {
+                    const float4 b4 = *reinterpret_cast<const float4*>(g.bias + (nl - g.bias_col0) + 16 * j);
+                    v.x += b4.x; v.y += b4.y; v.z += b4.z; v.w += b4.w;
+                }
+                if (g.C_raw) *reinterpret_cast<float4*>(g.C_raw + m * g.ld_raw + nl + 16 * j) = v;
+                v.x = fmaxf(v.x * s, floor_v); v.y = fmaxf(v.y * s, floor_v);
+                v.z = fmaxf(v.z * s, floor_v); v.w = fmaxf(v.w * s, floor_v);
+                v.x = mv[j].x > 0.f ? v.x : 0.f; v.y = mv[j].y > 0.f ? v.y : 0.f;
+                v.z = mv[j].z > 0.f ? v.z : 0.f; v.w = mv[j].w > 0.f ? v.w : 0.f;
+                *reinterpret_cast<float4*>(Cr + 16 * j) = v;
+            }
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int nb = nl + 16 * j;
+            float v[4], raw[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = nb + q, cb = n - g.bias_col0;
+                float t = acc[i][j][q];
+                if (n < g.N) {
+                    if (g.addend) t += g.addend[m * g.ld_add + n];
+                    if (g.bias && cb >= 0 && cb < bias_n) t += g.bias[cb];
+                    raw[q] = t;
+                    if (n < rs_cols) t *= rs;
+                    if (g.relu) t = t > 0.f ? t : 0.f;
+                    if (g.mask) t = g.mask[m * g.ld_mask + n] > 0.f ? t : 0.f;
+                } else {
+                    t = 0.f;
+                    raw[q] = 0.f;
+                }
+                v[q] = t;
+            }
+            if (vec) {
+                if (nb >= n_store) continue;
+                if (g.C_raw) *reinterpret_cast<float4*>(g.C_raw + m * g.ld_raw + nb) = make_float4(raw[0], raw[1], raw[2], raw[3]);
+                *reinterpret_cast<float4*>(Cr + 16 * j) = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (nb + q >= n_store) break;
+                    if (g.C_raw) g.C_raw[m * g.ld_raw + nb + q] = raw[q];
+                    Cr[16 * j + q] = v[q];
+                }
+            }
+        }
+    }
 }
 
 // Tile choice (measured on MI355X at M = 3e5; the nt path adds a 128 x 96 tile for 64 < N <= 96,
@@ -727,14 +783,12 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const bool ok = small && veca && a.ldbt % 4 == 0 && a.ldbt >= round_up(a.K, 4) && (uintptr_t)a.Bt % 16 == 0 &&
                         (a.K2 == 0 || (a.Bt2 && a.ldbt2 % 4 == 0 && a.ldbt2 >= round_up(a.K2, 4) && (uintptr_t)a.Bt2 % 16 == 0));
         const int n_eff = a.zero_pad_to > a.N ? a.zero_pad_to : a.N;
-        const bool short_k = a.K <= 128 || (a.K2 > 0 && a.K2 <= 128);
         // one profiling name per kernel variant, so that the names line up with a kernel trace
         char pname[64];
-        snprintf(pname, sizeof pname, "gemm_%s_%s_%s%s", ok ? "nt" : "nn", a.a_bf16 ? "bf16a" : "f32",
+        snprintf(pname, sizeof pname, "gemm_%s_%s_%s", ok ? "nt" : "nn", a.a_bf16 ? "bf16a" : "f32",
                  ok ? (a.M > 0 && n_eff > 32 && (cdiv(a.M_dev ? (a.M + 1) / 2 : a.M, 128) * cdiv(n_eff, n_eff > 96 ? 128 : n_eff > 64 ? 96 : 64) < 384 || a.K + a.K2 <= 64)
                            ? "64x64" : n_eff > 96 ? "128x128" : n_eff > 64 ? "128x96" : "128x64")
-                    : (n_eff > 64 ? "128x128" : n_eff > 32 ? "128x64" : "128x32"),
-                 short_k ? "_k16" : "_k32");
+                    : (n_eff > 64 ? "128x128" : n_eff > 32 ? "128x64" : "128x32"));
         ProfScope ps(pname, st, nn_flops, nn_bytes);
         if (!ok) {                                       // slow, always-safe kernel
             if (a.a_bf16) nn_pick<__hip_bfloat16, false>(a, st); else nn_pick<float, false>(a, st);
@@ -742,7 +796,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
             return GRP_OK;
         }
         const bool rowlimit = a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
-        int tile_n = n_eff > 96 ? 128 : n_eff > 64 ? 96 : 64;
+        int tile_n = n_eff > 96 ? 128 : n_eff > 64 ? 96 : n_eff > 32 ? 64 : 32;
         // A product whose 128-row tiles would leave half the chip idle (mini-batch blocks) is cut into
         // 64 x 64 tiles instead: four times the workgroups, each a quarter of the work.
         // (an upper bound of M that the device will cut down counts half: sampled blocks fill about that much)
@@ -753,27 +807,22 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         if (small_tiles) tile_n = 64;
         const int64_t slabs = round_up(cdiv(a.M, small_tiles ? 64 : 128), NXCD);
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, tile_n));
-#define GRP_NT_LAUNCH2(AT, WM_, WN_, TM_, TN_, RL)                                                                        \
-    do {                                                                                                                  \
-        if (short_k) hipLaunchKernelGGL((gemm_nt_kernel<AT, WM_, WN_, TM_, TN_, RL, 16, 2>), dim3(blocks), dim3(256), 0, st, a); \
-        else hipLaunchKernelGGL((gemm_nt_kernel<AT, WM_, WN_, TM_, TN_, RL, 32, 1>), dim3(blocks), dim3(256), 0, st, a);         \
+#define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
+    do {                                                                                                                   \
+        if (rowlimit) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, a);         \
+        else hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false>), dim3(blocks), dim3(256), 0, st, a);                 \
     } while (0)
-#define GRP_NT_LAUNCH(AT, WM_, WN_, TM_, TN_)                                                                       \
-    do {                                                                                                            \
-        if (rowlimit) GRP_NT_LAUNCH2(AT, WM_, WN_, TM_, TN_, true);                                                 \
-        else GRP_NT_LAUNCH2(AT, WM_, WN_, TM_, TN_, false);                                                         \
+#define GRP_NT_LAUNCH(TM_, TN_)                                                                                            \
+    do {                                                                                                                   \
+        if (a.a_bf16) GRP_NT_LAUNCH2(__hip_bfloat16, TM_, TN_); else GRP_NT_LAUNCH2(float, TM_, TN_);                      \
     } while (0)
-        if (small_tiles) {
-            if (a.a_bf16) GRP_NT_LAUNCH(__hip_bfloat16, 2, 2, 1, 1); else GRP_NT_LAUNCH(float, 2, 2, 1, 1);
-        } else if (n_eff > 96) {
-            if (a.a_bf16) GRP_NT_LAUNCH(__hip_bfloat16, 2, 2, 2, 2); else GRP_NT_LAUNCH(float, 2, 2, 2, 2);
-        } else if (n_eff > 64) {
-            if (a.a_bf16) GRP_NT_LAUNCH(__hip_bfloat16, 4, 1, 1, 3); else GRP_NT_LAUNCH(float, 4, 1, 1, 3);
-        } else {
-            if (a.a_bf16) GRP_NT_LAUNCH(__hip_bfloat16, 4, 1, 1, 2); else GRP_NT_LAUNCH(float, 4, 1, 1, 2);
-        }
-#undef GRP_NT_LAUNCH
+        if (small_tiles) GRP_NT_LAUNCH(1, 4);
+        else if (tile_n == 128) GRP_NT_LAUNCH(2, 8);
+        else if (tile_n == 96) GRP_NT_LAUNCH(2, 6);
+        else if (tile_n == 64) GRP_NT_LAUNCH(2, 4);
+        else GRP_NT_LAUNCH(2, 2);
 #undef GRP_NT_LAUNCH2
+#undef GRP_NT_LAUNCH
         GRP_LAUNCH_CHECK();
         return GRP_OK;
     }
@@ -836,13 +885,25 @@ size_t gemm_tn_workspace_bytes(int64_t M, int32_t K, int32_t N) {
 
 // Grid: x = NXCD * tiles * ceil(splits / NXCD).  Workgroup ids are mapped so that the output
 // tiles of one slice of the node dimension run on the same L2 domain (they read the same rows).
-// Whole 32-row steps (all but the last of a slice) load through a uniform base plus 32-bit
-// per-thread offsets and go to LDS as loaded; columns past K or N are read from clamped
+// The matrix instruction wants eight consecutive k per lane, and k is the node dimension here: a staging thread loads
+// four columns of eight consecutive rows, which in its registers are four runs of eight k values.  Column 4*g + q of a
+// tile W columns wide is kept in tile row q*(W/4) + g, so that the lanes of a wavefront (consecutive g) write consecutive
+// rows.  The first threads stage A, the next ones B.  LDS rows hold 32 k values (64 bytes, 4 places of 16); the eight k
+// from 8*c of a row sit at place c ^ tn_turn(row).
+// Whole 32-row steps load as they are; columns past K or N are read from clamped
 // addresses and never masked, since they only reach output rows / columns that are not stored.
 // GATHER: rows of A are taken through g.a_rows.  cs_out (optional): the workgroups of the
-// first row of output tiles also add up the columns of B they stream (times colsum_scale).
+// first row of output tiles also add up the columns of B they stream.
+
+// Chosen so that neither side meets a bank conflict (counted: none): a 16-byte write serves eight consecutive lanes, here rows, per
+// cycle over 32 banks, a 16-byte read sixteen lanes over 64 banks (lanes 0-3, 12-15, 20-27; 4-11, 16-19, 28-31; ...).
+__device__ __forceinline__ int tn_turn(int row) {
+    const int y = row >> 3;
+    return ((row >> 1) ^ (2 * (y & 1)) ^ ((y ^ (y >> 1)) & 1)) & 3;
+}
+
 template <typename AT, bool VEC, bool GATHER, int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTNArgs g, int tiles_k, int tiles_n, int dual, int splits, int64_t chunk,
+__global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int tiles_k, int tiles_n, int dual, int splits, int64_t chunk,
                                                       float* __restrict__ out, float* __restrict__ out2, int64_t out_ld,
                                                       int64_t out_split_stride, float* __restrict__ cs_out,
                                                       int64_t cs_split_stride) {
@@ -853,14 +914,13 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTNArgs g, int tiles_k,
         if (chunk < BK) chunk = BK;
     }
     constexpr int BKA = WM * TM * 32, BN = WN * TN * 32;   // output tile: BKA (rows of C) x BN
-    constexpr int PA = BKA + 4, PB = BN + 4;
-    constexpr int QA = BKA / 4, QB = BN / 4;               // 16-byte slots per tile row
-    constexpr int RA = 256 / QA, RB = 256 / QB;            // tile rows per pass of the workgroup
-    constexpr int A_REPS = BK / RA, B_REPS = BK / RB;
-    constexpr bool A_BF16 = sizeof(AT) == 2;
-    static_assert(BK % RA == 0 && BK % RB == 0 && B_REPS >= 1, "tiles must fill the workgroup");
-    __shared__ __attribute__((aligned(16))) float As[BK * PA];
-    __shared__ __attribute__((aligned(16))) float Bs[BK * PB];
+    constexpr int PLANE_A = BKA * 64, PLANE_B = BN * 64;
+    constexpr int QA = BKA / 4, QB = BN / 4;               // column groups of a tile
+    constexpr int TA = QA * (BK / 8), TB = QB * (BK / 8);  // staging threads of each operand
+    static_assert(TA % 64 == 0 && TA + TB <= 256 && QA % 8 == 0 && QB % 8 == 0, "an operand is staged by whole wavefronts");
+    __shared__ __attribute__((aligned(16))) unsigned char lds[3 * (PLANE_A + PLANE_B)];
+    unsigned char* const As = lds;
+    unsigned char* const Bs = lds + 3 * PLANE_A;
 
     // dual = 1: the second half of the tiles multiplies A2 instead of A; dual = 2: B2 instead of B
     const int tiles1 = tiles_k * tiles_n;
@@ -872,23 +932,32 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTNArgs g, int tiles_k,
     const int split = (hq / tiles) * NXCD + blockIdx.x % NXCD;
     if (split >= splits) return;
     const bool a2 = op2 && dual == 1, b2 = op2 && dual == 2;
-    const void* const Aop = a2 ? (const void*)g.A2 : g.A;
-    const int64_t lda = a2 ? g.lda2 : g.lda;
-    const int32_t* const a_rows = a2 ? nullptr : g.a_rows;
-    const float* const Bop = b2 ? g.B2 : g.B;
-    const int64_t ldb = b2 ? g.ldb2 : g.ldb;
-    const bool a_is_bf16 = sizeof(AT) == 2 && !a2;
-
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave / WN, wn = wave % WN;
+    const bool a_one = sizeof(AT) == 2 && !a2;             // A is stored in bf16: one plane
     const int ka0 = (tile / tiles_n) * BKA;
     const int n0 = (tile % tiles_n) * BN;
     const int64_t m_begin = (int64_t)split * chunk;
     const int64_t m_end = m_begin + chunk < g.M ? m_begin + chunk : g.M;
-    const int kpad = (g.K + 3) & ~3, npad = (g.N + 3) & ~3;
+
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int wm = wave / WN, wn = wave % WN;
+    const bool is_a = tid < TA, is_b = !is_a && tid < TA + TB;
+    const int q_n = is_a ? QA : QB;                        // the operand this thread stages:
+    const int lt = is_a ? tid : tid - TA;
+    const int grp = lt % q_n, mb = lt / q_n;               // four columns from 4 * grp, eight rows from 8 * mb
+    const void* const op = is_a ? (a2 ? (const void*)g.A2 : g.A) : (const void*)(b2 ? g.B2 : g.B);
+    const int64_t ld = is_a ? (a2 ? g.lda2 : g.lda) : (b2 ? g.ldb2 : g.ldb);
+    const int width = is_a ? g.K : g.N;
+    const int c_first = (is_a ? ka0 : n0) + 4 * grp;
+    const int col = imin(c_first, ((width + 3) & ~3) - 4);
+    const bool bf16 = is_a && a_one;
+    const int32_t* const rows = (GATHER && is_a && !a2) ? g.a_rows : nullptr;
     const bool do_cs = cs_out != nullptr && ka0 == 0 && !op2;
-    const float* const cs_scale = do_cs ? g.colsum_scale : nullptr;
+    // The matrix unit cuts the aligned terms of a sum off below its last bit, towards minus infinity: a bias of a few
+    // thousandths of a unit in the last place per instruction, the same sign everywhere.  It is nothing beside the rounding
+    // of one accumulator, but it would add up over the slices of a long reduction (10^6 rows: 3 times the error of plain
+    // fp32).  Every other slice therefore sums -A^T B and stores the negative of that, so that the biases cancel.
+    const uint32_t flip = (split & 1) ? 0x80000000u : 0u;
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -897,141 +966,142 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(GemmTNArgs g, int tiles_k,
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int cqa = tid % QA, ma = tid / QA, cqb = tid % QB, mb = tid / QB;
-    const int ca = imin(ka0 + 4 * cqa, kpad - 4), cb = imin(n0 + 4 * cqb, npad - 4);
-    uint32_t aoff[A_REPS], boff[B_REPS];
-#pragma unroll
-    for (int r = 0; r < A_REPS; ++r) aoff[r] = (uint32_t)(ma + RA * r) * (uint32_t)lda + ca;
-#pragma unroll
-    for (int r = 0; r < B_REPS; ++r) boff[r] = (uint32_t)(mb + RB * r) * (uint32_t)ldb + cb;
-    float* const as_w = As + ma * PA + 4 * cqa;
-    float* const bs_w = Bs + mb * PB + 4 * cqb;
     float csum[4] = {0.f, 0.f, 0.f, 0.f};
+    uint4 raw[8];
 
-    uint4 ra[A_REPS], rb[B_REPS];
-    float rsc[B_REPS];
     auto fetch = [&](int64_t mt) {
-        const bool full = mt + BK <= m_end;
-        if (cs_scale) {
+        if (!is_a && !is_b) return;
+        const int64_t mr = mt + 8 * mb;
+        if (VEC && !rows && mt + BK <= m_end) {
+            if (sizeof(AT) == 2 && bf16) {
+                const __hip_bfloat16* p = (const __hip_bfloat16*)op + mr * ld + col;
 #pragma unroll
-            for (int r = 0; r < B_REPS; ++r) rsc[r] = cs_scale[lmin(mt + mb + RB * r, g.M - 1)];
-        }
-        if (VEC && (!GATHER || !a_rows) && full) {
-            const float* pb = Bop + mt * ldb;
-            if (A_BF16 && !a_is_bf16) {               // the second operand of a bf16 launch is fp32
-                const float* pa = (const float*)Aop + mt * lda;
-#pragma unroll
-                for (int r = 0; r < A_REPS; ++r) ra[r] = ldg_raw4<float>(pa + aoff[r]);
+                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<__hip_bfloat16>(p + r * ld);
             } else {
-                const AT* pa = (const AT*)Aop + mt * lda;
+                const float* p = (const float*)op + mr * ld + col;
 #pragma unroll
-                for (int r = 0; r < A_REPS; ++r) ra[r] = ldg_raw4<AT>(pa + aoff[r]);
+                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<float>(p + r * ld);
             }
-#pragma unroll
-            for (int r = 0; r < B_REPS; ++r) rb[r] = ldg_raw4<float>(pb + boff[r]);
             return;
         }
 #pragma unroll
-        for (int r = 0; r < A_REPS; ++r) {
-            const int m = ma + RA * r;
+        for (int r = 0; r < 8; ++r) {
+            const bool ok = mr + r < m_end;
+            const int64_t gm = lmin(mr + r, g.M - 1);
+            const int64_t row = rows ? (int64_t)rows[gm] : gm;
             if constexpr (VEC) {
-                const int64_t gm = lmin(mt + m, g.M - 1);
-                const int64_t row = a_rows ? (int64_t)a_rows[gm] : gm;
-                if (A_BF16 && !a_is_bf16) ra[r] = ldg_raw4<float>((const float*)Aop + row * lda + ca);
-                else ra[r] = ldg_raw4<AT>((const AT*)Aop + row * lda + ca);
+                if (sizeof(AT) == 2 && bf16) raw[r] = ldg_raw4<__hip_bfloat16>((const __hip_bfloat16*)op + row * ld + col);
+                else raw[r] = ldg_raw4<float>((const float*)op + row * ld + col);
+                if (!ok) raw[r] = make_uint4(0u, 0u, 0u, 0u);
+            } else if (sizeof(AT) == 2 && bf16) {          // back to packed halves
+                const uint4 f = ldg_safe4((const __hip_bfloat16*)op + row * ld, ok, c_first, width);
+                raw[r] = make_uint4((f.x >> 16) | (f.y & 0xFFFF0000u), (f.z >> 16) | (f.w & 0xFFFF0000u), 0u, 0u);
             } else {
-                const bool ok = mt + m < m_end;
-                const int64_t gm = ok ? mt + m : 0;
-                const int64_t row = (a_rows && ok) ? (int64_t)a_rows[gm] : gm;
-                if (A_BF16 && !a_is_bf16) ra[r] = ldg_safe4<float>((const float*)Aop + row * lda, ok, ka0 + 4 * cqa, g.K);
-                else ra[r] = ldg_safe4<AT>((const AT*)Aop + row * lda, ok, ka0 + 4 * cqa, g.K);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < B_REPS; ++r) {
-            const int m = mb + RB * r;
-            if constexpr (VEC) {
-                rb[r] = ldg_raw4<float>(Bop + lmin(mt + m, g.M - 1) * ldb + cb);
-            } else {
-                const bool ok = mt + m < m_end;
-                rb[r] = ldg_safe4<float>(Bop + (ok ? mt + m : 0) * ldb, ok, n0 + 4 * cqb, g.N);
+                raw[r] = ldg_safe4((const float*)op + row * ld, ok, c_first, width);
             }
         }
     };
-    auto stage = [&](int64_t mt) {
-        const bool full = mt + BK <= m_end;
-        if (VEC && full && !a_is_bf16) {
+    unsigned char* put[4];                                 // where the eight rows of column 4 * grp + q go: tile row q * q_n + grp
 #pragma unroll
-            for (int r = 0; r < A_REPS; ++r) *reinterpret_cast<uint4*>(as_w + RA * r * PA) = ra[r];
-        } else {
+    for (int q = 0; q < 4; ++q) {
+        const int row = q * q_n + grp;
+        put[q] = (is_a ? As : Bs) + 64 * row + 16 * (mb ^ tn_turn(row));
+    }
+    auto stage = [&]() {
+        if (sizeof(AT) == 2 && bf16) {
 #pragma unroll
-            for (int r = 0; r < A_REPS; ++r) {
-                float v[4];
-                unpack4(ra[r], VEC && a_is_bf16, v);
-                if (VEC && mt + ma + RA * r >= m_end) { v[0] = v[1] = v[2] = v[3] = 0.f; }
-                *reinterpret_cast<float4*>(as_w + RA * r * PA) = make_float4(v[0], v[1], v[2], v[3]);
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t sel = (q & 1) ? 0x07060302u : 0x05040100u;
+                auto w = [&](int r) { return __builtin_amdgcn_perm(q < 2 ? raw[r + 1].x : raw[r + 1].y, q < 2 ? raw[r].x : raw[r].y, sel); };
+                const uint32_t fl = flip | (flip >> 16);
+                *reinterpret_cast<uint4*>(put[q]) = make_uint4(w(0) ^ fl, w(2) ^ fl, w(4) ^ fl, w(6) ^ fl);
             }
+            return;
         }
+        if (!is_a && !is_b) return;
 #pragma unroll
-        for (int r = 0; r < B_REPS; ++r) {
-            float v[4];
-            unpack4(rb[r], false, v);
-            if (VEC && !full && mt + mb + RB * r >= m_end) { v[0] = v[1] = v[2] = v[3] = 0.f; }
-            *reinterpret_cast<float4*>(bs_w + RB * r * PB) = make_float4(v[0], v[1], v[2], v[3]);
-            if (do_cs) {
-                const float sc = cs_scale ? rsc[r] : 1.f;
+        for (int q = 0; q < 4; ++q) {
+            float v[8];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) csum[q] += v[q] * sc;
+            for (int r = 0; r < 8; ++r) {
+                const uint4 t = raw[r];
+                v[r] = __uint_as_float(q == 0 ? t.x : q == 1 ? t.y : q == 2 ? t.z : t.w);
+            }
+            if (is_a) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) v[r] = __uint_as_float(__float_as_uint(v[r]) ^ flip);
+                put_split8<PLANE_A>(put[q], v);
+            } else {
+                put_split8<PLANE_B>(put[q], v);
+                if (do_cs) csum[q] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
             }
         }
     };
+    const int li = lane & 31, lk = lane >> 5;
+    const unsigned char* const ap0 = As + 64 * (wm * TM * 32 + li);
+    const unsigned char* const bp0 = Bs + 64 * (wn * TN * 32 + li);
+    const int c0 = 16 * (lk ^ tn_turn(li));
 
     if (m_begin < m_end) {
         fetch(m_begin);
-        stage(m_begin);
+        stage();
         __syncthreads();
         for (int64_t mt = m_begin; mt < m_end; mt += BK) {
             const bool more = mt + BK < m_end;
             if (more) fetch(mt + BK);
-            mma_step_interleaved<TM, TN, PA, PB, BK>(As, Bs, wm * TM * 32, wn * TN * 32, acc);
+            mma32<TM, TN, PLANE_A, PLANE_B, sizeof(AT) == 2>(ap0 + c0, bp0 + c0, a_one, acc);
+            mma32<TM, TN, PLANE_A, PLANE_B, sizeof(AT) == 2>(ap0 + (c0 ^ 32), bp0 + (c0 ^ 32), a_one, acc);
             __syncthreads();
             if (more) {
-                stage(mt + BK);
+                stage();
                 __syncthreads();
             }
         }
     }
 
-    const int li = lane & 31, lk = lane >> 5;
     // Partial tiles (out2 null): the second product's rows follow the first's K rows (dual = 1) or its
     // columns follow the first's N columns (dual = 2).  Direct output: out2 is the second matrix.
     float* o = (op2 && out2 ? out2 : out) + (int64_t)split * out_split_stride;
     if (op2 && !out2) o += a2 ? (int64_t)g.K * out_ld : (int64_t)g.N;
-    const int colb = n0 + wn * TN * 32 + TN * li;     // first of this lane's TN interleaved columns
-    const bool pair = TN == 2 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && colb + 1 < g.N;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = __uint_as_float(__float_as_uint(acc[i][j][r]) ^ flip);
+    int cols[TN];                                     // this lane's output columns
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int row = wn * TN * 32 + 32 * j + li;
+        cols[j] = n0 + 4 * (row % QB) + row / QB;
+    }
+    const bool pair = TN == 2 && BN == 128 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && cols[TN - 1] < g.N;   // neighbours
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int ka = ka0 + wm * TM * 32 + TM * (8 * (r / 4) + 4 * lk + (r % 4)) + i;
+            const int row = wm * TM * 32 + 32 * i + 8 * (r / 4) + 4 * lk + (r % 4);
+            const int ka = ka0 + 4 * (row % QA) + row / QA;
             if (ka >= g.K) continue;
-            float* orow = o + (int64_t)ka * out_ld + colb;
+            float* orow = o + (int64_t)ka * out_ld;
             if constexpr (TN == 2) {
-                if (pair) { *reinterpret_cast<float2*>(orow) = make_float2(acc[i][0][r], acc[i][1][r]); continue; }
+                if (pair) { *reinterpret_cast<float2*>(orow + cols[0]) = make_float2(acc[i][0][r], acc[i][1][r]); continue; }
             }
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                if (colb + j < g.N) orow[j] = acc[i][j][r];
+                if (cols[j] < g.N) orow[cols[j]] = acc[i][j][r];
         }
-    if (do_cs) {                                      // the main loop ended on a barrier: As is free
-        float* red = As;
+    if (do_cs) {                                      // the main loop ended on a barrier: the tiles are free
+        float* red = reinterpret_cast<float*>(lds);
+        if (is_b) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) red[mb * BN + 4 * cqb + q] = csum[q];
+            for (int q = 0; q < 4; ++q) red[mb * BN + 4 * grp + q] = csum[q];
+        }
         __syncthreads();
         if (tid < BN) {
             float t = 0.f;
-            for (int u = 0; u < RB; ++u) t += red[u * BN + tid];
+#pragma unroll
+            for (int u = 0; u < BK / 8; ++u) t += red[u * BN + tid];
             if (n0 + tid < g.N) cs_out[(int64_t)split * cs_split_stride + n0 + tid] = t;
         }
     }
