@@ -191,9 +191,9 @@ __global__ __launch_bounds__(256) void adopt_finish_kernel(const int64_t* __rest
 
 struct Owned {
     void* p = nullptr;
-    ~Owned() { if (p) (void)hipFree(p); }
+    ~Owned() { if (p) pool_free(p); }
     grp_status alloc(size_t bytes) {
-        if (hipMalloc(&p, bytes ? bytes : 4) != hipSuccess) {
+        if (pool_alloc(&p, bytes ? bytes : 4) != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
             return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", bytes);
@@ -241,7 +241,7 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
         return b.total();
     };
     h->slab_bytes = carve(nullptr, 0);
-    if (hipMalloc(&h->slab, h->slab_bytes) != hipSuccess) {
+    if (pool_alloc(&h->slab, h->slab_bytes) != hipSuccess) {
         (void)hipGetLastError();
         h->slab = nullptr;
         return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", h->slab_bytes);
@@ -316,7 +316,7 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
                                                  bits, st));
                 if (need > sort_bytes) {
                     GRP_HIP(hipStreamSynchronize(st));
-                    (void)hipFree(tmp.p);
+                    pool_free(tmp.p);
                     tmp.p = nullptr;
                     GRP_TRY(tmp.alloc(need));
                     sort_bytes = need;

@@ -60,6 +60,11 @@ struct ProfScope {
                              hipGetErrorString(e_), __FILE__, __LINE__);                \
     } while (0)
 
+// ---------------------------------------------------------------- device memory of the builders (runtime.hip)
+// As hipMalloc / hipFree, from a bounded cache of freed blocks.
+hipError_t pool_alloc(void** p, size_t bytes);
+void pool_free(void* p);
+
 // ---------------------------------------------------------------- partition handle
 }  // namespace grp
 

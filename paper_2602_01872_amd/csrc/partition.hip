@@ -534,9 +534,9 @@ static unsigned grid_for(int64_t work) {
 
 struct DevBuf {
     void* p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
+    ~DevBuf() { if (p) pool_free(p); }
     grp_status alloc(size_t bytes) {
-        if (hipMalloc(&p, bytes ? bytes : 4) != hipSuccess) {
+        if (pool_alloc(&p, bytes ? bytes : 4) != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
             return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", bytes);
@@ -560,8 +560,8 @@ static void free_partition(grp_partition_t* h) {
                     h->base_mask, h->csr_long.tasks, h->csr_long.row_task, h->csc_long.tasks, h->csc_long.row_task, h->csr_w, h->csc_w, h->w_local_in, h->w_global_in};
     const char* lo = (const char*)h->slab;
     for (void* q : ptrs)
-        if (q && !(lo && (const char*)q >= lo && (const char*)q < lo + h->slab_bytes)) (void)hipFree(q);
-    if (h->slab) (void)hipFree(h->slab);
+        if (q && !(lo && (const char*)q >= lo && (const char*)q < lo + h->slab_bytes)) pool_free(q);
+    if (h->slab) pool_free(h->slab);
     delete h;
 }
 
@@ -569,7 +569,7 @@ template <typename T>
 static grp_status halloc(T** out, int64_t count) {
     void* p = nullptr;
     const size_t bytes = (size_t)(count > 0 ? count : 1) * sizeof(T);
-    if (hipMalloc(&p, bytes) != hipSuccess) {
+    if (pool_alloc(&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", bytes);
     }
@@ -634,7 +634,7 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
     const int64_t cap_chunks = cap_long ? nnz / SPMM_CHUNK + cap_long + 1 : 0;
     if (cap_chunks >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "more than 2^31 row chunks");
     h->slab_bytes = carve_csr_csc(h, vals != nullptr, cap_long, cap_chunks, nullptr, 0);
-    if (hipMalloc(&h->slab, h->slab_bytes) != hipSuccess) {
+    if (pool_alloc(&h->slab, h->slab_bytes) != hipSuccess) {
         (void)hipGetLastError();
         h->slab = nullptr;
         return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", h->slab_bytes);
@@ -1118,7 +1118,7 @@ __global__ __launch_bounds__(256) void bucket_keys_kernel(const int64_t* __restr
 static void free_chunks(grp_chunks_t* h) {
     if (!h) return;
     for (void* q : {(void*)h->src, (void*)h->dst, (void*)h->d_global_all, (void*)h->assign})
-        if (q) (void)hipFree(q);
+        if (q) pool_free(q);
     delete h;
 }
 

@@ -66,6 +66,100 @@ void prof_end(hipStream_t st) {
     g_open_end = nullptr;
 }
 
+// ---------------------------------------------------------------- device memory of the builders
+// A builder makes a dozen allocations and its handle is freed when the next one exists; hipMalloc and hipFree cost a few
+// microseconds when the runtime has the pages at hand and up to a millisecond each when it has to map them (a partition of 3e5 nodes
+// out of 6.2e7 edges: 1.5 ms of kernels and transfers inside 10 ms).  Freed blocks are therefore kept and handed out again.
+//   - hipFree waits for the device; a freed block waits in `pending` instead, and the first request that one of those
+//     could serve waits for the device once and makes all of them ready.  So a block never changes hands while work that
+//     was queued before its release, on any stream, can still use it.
+//   - A request takes the smallest ready block of at most 1.25 times its size.
+//   - At most 1/64 of the device's memory is kept; the block that was freed longest ago goes first.  A block that 64 later
+//     requests have passed over is given back, and so is everything kept when an allocation fails.
+//   - One cache per device, one lock.
+namespace {
+struct PoolBlock { void* p; size_t bytes; uint64_t freed_at; bool pending; };
+struct Pool {
+    std::vector<PoolBlock> kept;                 // in the order they were freed
+    size_t kept_bytes = 0, bound = 0;
+    uint64_t clock = 0;                          // requests so far
+};
+std::mutex g_pool_mu;
+std::map<int, Pool> g_pools;
+std::map<void*, std::pair<int, size_t>> g_pool_live;      // blocks handed out: device and size
+
+void pool_drop(Pool& pool, size_t i) {           // give a kept block back to the runtime
+    (void)hipFree(pool.kept[i].p);
+    pool.kept_bytes -= pool.kept[i].bytes;
+    pool.kept.erase(pool.kept.begin() + (long)i);
+}
+}  // namespace
+
+hipError_t pool_alloc(void** out, size_t bytes) {
+    *out = nullptr;
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    size_t unit = 256;                           // sizes are rounded up to eighths of a power of two, so that similar builds fit each other's blocks
+    while (unit * 16 <= bytes) unit *= 2;
+    const size_t want = (bytes + unit - 1) / unit * unit;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    Pool& pool = g_pools[dev];
+    ++pool.clock;
+    for (int pass = 0; pass < 2; ++pass) {       // ready blocks first, then, after one wait, the pending ones
+        size_t best = pool.kept.size();
+        bool waits = false;
+        for (size_t i = 0; i < pool.kept.size(); ++i) {
+            const PoolBlock& b = pool.kept[i];
+            if (b.bytes < want || b.bytes > want + want / 4) continue;
+            if (b.pending) { waits = true; continue; }
+            if (best == pool.kept.size() || b.bytes < pool.kept[best].bytes) best = i;
+        }
+        if (best < pool.kept.size()) {
+            *out = pool.kept[best].p;
+            g_pool_live[*out] = {dev, pool.kept[best].bytes};
+            pool.kept_bytes -= pool.kept[best].bytes;
+            pool.kept.erase(pool.kept.begin() + (long)best);
+            break;
+        }
+        if (!waits) break;
+        if (hipDeviceSynchronize() != hipSuccess) {            // (another thread may be capturing a graph)
+            (void)hipGetLastError();
+            break;
+        }
+        for (PoolBlock& b : pool.kept) b.pending = false;
+    }
+    while (!pool.kept.empty() && pool.clock - pool.kept.front().freed_at > 64) pool_drop(pool, 0);
+    if (*out) return hipSuccess;
+    hipError_t r = hipMalloc(out, want ? want : 256);
+    if (r != hipSuccess && !pool.kept.empty()) {
+        (void)hipGetLastError();
+        while (!pool.kept.empty()) pool_drop(pool, 0);
+        r = hipMalloc(out, want ? want : 256);
+    }
+    if (r != hipSuccess) { *out = nullptr; return r; }
+    g_pool_live[*out] = {dev, want ? want : 256};
+    return hipSuccess;
+}
+
+void pool_free(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    const auto it = g_pool_live.find(p);
+    if (it == g_pool_live.end()) { (void)hipFree(p); return; }
+    const int dev = it->second.first;
+    const size_t bytes = it->second.second;
+    g_pool_live.erase(it);
+    Pool& pool = g_pools[dev];
+    if (pool.bound == 0) {
+        size_t free_b = 0, total = 0;
+        pool.bound = hipMemGetInfo(&free_b, &total) == hipSuccess && total ? total / 64 : 1;
+    }
+    pool.kept.push_back({p, bytes, pool.clock, true});
+    pool.kept_bytes += bytes;
+    while (pool.kept_bytes > pool.bound) pool_drop(pool, 0);
+}
+
 // One helper stream (default priority, not synchronising with the legacy stream) and its events per caller
 // stream and device, created at the first request and kept until the process ends.
 SideLane* side_lane(hipStream_t main) {

@@ -112,8 +112,8 @@ grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, 
     const int64_t n_long = lr->n_long;
     const int min_piece = SLICE_MIN_PIECE;
     int64_t* row_task = nullptr;
-    GRP_HIP(hipMalloc((void**)&row_task, (size_t)(n_long + 1) * sizeof(int64_t)));
-    auto fail_free = [&](grp_status s) { (void)hipFree(row_task); return s; };
+    GRP_HIP(pool_alloc((void**)&row_task, (size_t)(n_long + 1) * sizeof(int64_t)));
+    auto fail_free = [&](grp_status s) { pool_free(row_task); return s; };
     GRP_HIP(hipMemsetAsync(row_task + n_long, 0, sizeof(int64_t), st));
     {   // the long rows' share of the edges decides whether the schedule pays
         hipLaunchKernelGGL(long_edges_kernel, dim3((unsigned)cdiv(n_long, 256)), dim3(256), 0, st, ptr, lr->long_row, n_long,
@@ -123,7 +123,7 @@ grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, 
             hipStreamSynchronize(st) != hipSuccess)
             return fail_free(fail(GRP_EHIP, "slice schedule: the long rows' edge count did not reach the host"));
         if (long_edges * 100 < nnz * (int64_t)g_slice_min_percent.load()) {
-            (void)hipFree(row_task);
+            pool_free(row_task);
             return GRP_OK;
         }
         if (hipMemsetAsync(row_task + n_long, 0, sizeof(int64_t), st) != hipSuccess)
@@ -137,28 +137,28 @@ grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, 
         if (rocprim::exclusive_scan(nullptr, need, row_task, row_task, (int64_t)0, (size_t)(n_long + 1), rocprim::plus<int64_t>(), st) != hipSuccess)
             return fail_free(fail(GRP_EHIP, "slice schedule: scan size query failed"));
         void* tmp = nullptr;
-        if (hipMalloc(&tmp, need ? need : 4) != hipSuccess) { (void)hipGetLastError(); return fail_free(fail(GRP_ENOMEM, "slice schedule: scan scratch")); }
+        if (pool_alloc(&tmp, need ? need : 4) != hipSuccess) { (void)hipGetLastError(); return fail_free(fail(GRP_ENOMEM, "slice schedule: scan scratch")); }
         const hipError_t e = rocprim::exclusive_scan(tmp, need, row_task, row_task, (int64_t)0, (size_t)(n_long + 1), rocprim::plus<int64_t>(), st);
         (void)hipStreamSynchronize(st);
-        (void)hipFree(tmp);
+        pool_free(tmp);
         if (e != hipSuccess) return fail_free(fail(GRP_EHIP, "slice schedule: scan failed"));
     }
     int64_t n_tasks = 0;
     if (hipMemcpy(&n_tasks, row_task + n_long, sizeof n_tasks, hipMemcpyDeviceToHost) != hipSuccess)
         return fail_free(fail(GRP_EHIP, "slice schedule: task count did not reach the host"));
     if (n_tasks <= 0 || n_tasks >= ((int64_t)1 << 32)) {       // nothing to do, or more tasks than a 32-bit id holds
-        (void)hipFree(row_task);
+        pool_free(row_task);
         return GRP_OK;
     }
     SliceTask *recs = nullptr, *sorted = nullptr;
     uint8_t *keys = nullptr, *keys_out = nullptr;
     void* tmp = nullptr;
-    auto cleanup = [&]() { (void)hipFree(recs); (void)hipFree(keys); (void)hipFree(keys_out); (void)hipFree(tmp); };
+    auto cleanup = [&]() { pool_free(recs); pool_free(keys); pool_free(keys_out); pool_free(tmp); };
     grp_status status = GRP_OK;
     do {
-        if (hipMalloc((void**)&recs, (size_t)n_tasks * sizeof(SliceTask)) != hipSuccess ||
-            hipMalloc((void**)&sorted, (size_t)n_tasks * sizeof(SliceTask)) != hipSuccess ||
-            hipMalloc((void**)&keys, (size_t)n_tasks) != hipSuccess || hipMalloc((void**)&keys_out, (size_t)n_tasks) != hipSuccess) {
+        if (pool_alloc((void**)&recs, (size_t)n_tasks * sizeof(SliceTask)) != hipSuccess ||
+            pool_alloc((void**)&sorted, (size_t)n_tasks * sizeof(SliceTask)) != hipSuccess ||
+            pool_alloc((void**)&keys, (size_t)n_tasks) != hipSuccess || pool_alloc((void**)&keys_out, (size_t)n_tasks) != hipSuccess) {
             (void)hipGetLastError();
             status = fail(GRP_ENOMEM, "slice schedule: %lld task records", (long long)n_tasks);
             break;
@@ -167,7 +167,7 @@ grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, 
                            row_task, recs, keys);
         size_t need = 0;
         if (rocprim::radix_sort_pairs(nullptr, need, keys, keys_out, recs, sorted, (size_t)n_tasks, 0u, SLICE_KEY_BITS, st) != hipSuccess ||
-            hipMalloc(&tmp, need ? need : 4) != hipSuccess) {
+            pool_alloc(&tmp, need ? need : 4) != hipSuccess) {
             (void)hipGetLastError();
             status = fail(GRP_ENOMEM, "slice schedule: sort scratch");
             break;
@@ -180,8 +180,8 @@ grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, 
     } while (false);
     cleanup();
     if (status != GRP_OK) {
-        (void)hipFree(sorted);
-        (void)hipFree(row_task);
+        pool_free(sorted);
+        pool_free(row_task);
         return status;
     }
     lr->n_tasks = n_tasks;
