@@ -144,6 +144,13 @@ struct grp_chunks_s {
 
 namespace grp {
 
+__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+
+// 16 and 8 bytes at any element boundary (global loads of these need no alignment beyond the element's, and are as fast as
+// aligned ones when the address is a multiple of their size)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline int64_t round_up(int64_t a, int64_t b) { return cdiv(a, b) * b; }
 
@@ -221,6 +228,7 @@ struct GemmNNArgs {
     int32_t rowscale_cols = 0;      // rowscale applies to columns < this only (0: all columns)
     int32_t bias_col0 = 0;          // bias[c - bias_col0] is added to columns c in [bias_col0, bias_col0 + bias_n)
     int32_t bias_n = 0;             // (0: N - bias_col0)
+    int32_t a_tight = 0;            // set by the launch: rows of A end at column K or are not 16-byte friendly
     const float* Bt = nullptr;      // when set: B given transposed, Bt[N x K] (pitch ldbt), fast path
     int64_t ldbt = 0;
     const float* Bt2 = nullptr;     // same for the second product
@@ -255,6 +263,7 @@ struct GemmTNArgs {
     int64_t ldb2 = 0;
     float* C2 = nullptr;             // pitch ldc
     const int64_t* M_dev = nullptr;  // when set: the real number of rows (on the device); M above is an upper bound
+    int32_t a_tight = 0, b_tight = 0;    // set by the launch: rows of A / B end at their last column or are not 16-byte friendly
 };
 grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st);
 

@@ -117,6 +117,7 @@ __global__ __launch_bounds__(256) void gat_stats_kernel(const int64_t* __restric
 // FWD and DST, of the CSC for SRC) and accumulates a feature row `acc` and a scalar `scal`:
 //   FWD  acc += alpha_uv T[u,:]                                           (row v, edges u -> v)
 //   DST  scal += alpha_uv (dOut_v . T[u,:] - c_v) LeakyReLU'(pre_uv)      (row v; acc unused)
+//        (the slope LeakyReLU' here less that of the self edge: see gat_walk_edges)
 //   SRC  acc += alpha_uv dOut[v,:];  scal += alpha_uv (T_u . dOut[v,:] - c_v) LeakyReLU'(pre_uv)   (row u, edges u -> v)
 // Short rows are walked by one group of G lanes.  Rows longer than `long_thr` edges use the
 // partition's split schedule: the first workgroups of the launch each walk one chunk (their
@@ -194,6 +195,10 @@ __device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t
 template <int PASS, int G, int NJ>
 __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G, NJ>& R, int64_t b, int64_t e, int t,
                                                const bool (&live)[NJ], float4 (&acc)[NJ], float& scal) {
+    // DST adds up alpha_uv (dOut_v . t_u - c_v) LeakyReLU'(pre_uv) over a row.  Without the last factor that sum is zero, so the
+    // self edge's slope is taken off every factor: what is left are the edges on the other side of the kink, instead of
+    // terms of both signs that cancel to rounding noise (the self edge itself then adds nothing).
+    const float slope0 = PASS == GAT_DST ? leaky_d(R.p + R.q) : 0.f;
     for (int64_t base = b; base < e; base += G) {
         const int cnt = (int)(e - base < G ? e - base : G);
         int mine = 0;
@@ -209,7 +214,7 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
                 pre = A.pq[mine].x + R.q; mx = R.mx; inv = R.inv;
             }
             mya = __expf(leaky(pre) - mx) * inv;
-            mw = mya * leaky_d(pre);
+            mw = mya * (leaky_d(pre) - slope0);
         }
         for (int k = 0; k < cnt; k += 4) {
             const bool p1 = k + 1 < cnt, p2 = k + 2 < cnt, p3 = k + 3 < cnt;
@@ -277,7 +282,7 @@ __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G,
         const float ds_self = __expf(leaky(pre_s) - R.mx) * R.inv * (dself - R.c) * leaky_d(pre_s);
         if (t == 0) {
             A.cvec[r] = R.c;
-            A.dqs[r] = make_float2(scal + ds_self, ds_self);
+            A.dqs[r] = make_float2(scal, ds_self);
         }
     } else {
         const float2 st = A.rowstat[r], dq = A.dqs[r];

@@ -45,9 +45,10 @@ template <> __device__ __forceinline__ float to_f<__hip_bfloat16>(__hip_bfloat16
 template <typename T>
 __device__ __forceinline__ uint4 ldg_raw4(const T* __restrict__ p) {
     if constexpr (sizeof(T) == 4) {
-        return *reinterpret_cast<const uint4*>(p);
+        const u32x4_any r = *reinterpret_cast<const u32x4_any*>(p);
+        return make_uint4(r.x, r.y, r.z, r.w);
     } else {
-        const uint2 r = *reinterpret_cast<const uint2*>(p);
+        const u32x2_any r = *reinterpret_cast<const u32x2_any*>(p);
         return make_uint4(r.x, r.y, 0u, 0u);
     }
 }
@@ -63,7 +64,7 @@ __device__ __forceinline__ void unpack4(const uint4& r, bool bf16, float o[4]) {
     }
 }
 
-// Slow, always-safe element loads for operands whose pitch or base is not 16-byte friendly.
+// Slow, always-safe element loads (rows of fewer than four columns without padding, B not given transposed).
 template <typename T>
 __device__ __forceinline__ uint4 ldg_safe4(const T* __restrict__ row, bool row_ok, int k, int K) {
     float o[4] = {0.f, 0.f, 0.f, 0.f};
@@ -75,7 +76,6 @@ __device__ __forceinline__ uint4 ldg_safe4(const T* __restrict__ row, bool row_o
     return make_uint4(__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3]));
 }
 
-__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 __device__ __forceinline__ int64_t lmin(int64_t a, int64_t b) { return a < b ? a : b; }
 
 // ------------------------------------------------------------------------------- fp32 as three bf16 planes
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // Loads use a uniform base that advances along k plus 32-bit per-thread offsets fixed before the loop; rows past the end of
 // an operand are clamped to its last row (their products are not stored); only the last, ragged k-tile of a product
 // is masked.
-// IRREG selects the variant with gathered (a_rows) or limited (a_valid_rows) A rows.
+// IRREG selects the variant with gathered (a_rows), limited (a_valid_rows) or tightly packed (a_tight) A rows.
 template <typename AT, int TM, int TN, bool IRREG>
 __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     if (g.M_dev) {                                    // the launch was sized by upper bounds
@@ -490,7 +490,11 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     aoff_t aoff[TM];
     uint32_t aoff2[TM];
     bool a_zero[TM];
-    const AT* a_base = (const AT*)g.A;
+    // Rows of A without room for a whole last group are read up to their last element instead: that group is read a_turn
+    // elements early and turned into place before it is masked.  (The base is moved back and the offsets forward by as much:
+    // the early group may start before the k-tile, and an unsigned offset from the tile's start could not say so.)
+    const int a_turn = IRREG && g.a_tight ? -g.K & 3 : 0;
+    const AT* a_base = (const AT*)g.A - a_turn;
     if (!IRREG) a_base += m0 * g.lda;
     const float* const a2_base = g.A2 + m0 * g.lda2;
 #pragma unroll
@@ -499,7 +503,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
         if (IRREG) {
             const int64_t a_valid = g.a_valid_rows > 0 ? g.a_valid_rows : g.M;
             const int64_t r1 = lmin(m0 + lr, a_valid - 1);
-            aoff[i] = (aoff_t)((g.a_rows ? (int64_t)g.a_rows[r1] : r1) * g.lda + 4 * lq);
+            aoff[i] = (aoff_t)((g.a_rows ? (int64_t)g.a_rows[r1] : r1) * g.lda + 4 * lq + a_turn);
             a_zero[i] = m0 + lr >= a_valid;
         } else {
             aoff[i] = (aoff_t)((uint32_t)lr * (uint32_t)g.lda + 4 * lq);
@@ -520,11 +524,12 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     const int nk = nk1 + (g.K2 + BK - 1) / BK;
     uint4 ra[TM][2], rb[B_REPS][2];
 
-    // a ragged last tile reads the operand's last whole four-element group again (masked afterwards)
-    auto clamp = [&](int k0, int Kc, int q, int& d0, int& d1) {
+    // a ragged last tile reads the operand's last four-element group again (masked afterwards); in A that group may lie a_turn
+    // elements early (below)
+    auto clamp = [&](int k0, int Kc, int q, int turn, int& d0, int& d1) {
         d0 = 0; d1 = 16;
         if (k0 + BK > Kc) {
-            const int last = ((Kc + 3) & ~3) - 4 - k0 - 4 * q;
+            const int last = ((Kc + 3) & ~3) - 4 - turn - k0 - 4 * q;
             d0 = imin(0, last);
             d1 = imin(16, last);
         }
@@ -534,8 +539,8 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
         const int k0 = (second ? kt - nk1 : kt) * BK;
         const int Kc = second ? g.K2 : g.K;
         int d0, d1, e0, e1;
-        clamp(k0, Kc, lq, d0, d1);
-        clamp(k0, Kc, tq, e0, e1);
+        clamp(k0, Kc, lq, second ? 0 : a_turn, d0, d1);
+        clamp(k0, Kc, tq, 0, e0, e1);
         if (second) {
             const float* pa = a2_base + k0;
             const float* pb = g.Bt2 + k0;
@@ -565,10 +570,21 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
         }
     };
     // eight values of k group q as floats, zero where the k does not exist
-    auto floats = [&](const uint4 (&r)[2], int left /*k values of the tile that exist*/, int q, float (&v)[8]) {
+    auto floats = [&](const uint4 (&r)[2], int left /*k values of the tile that exist*/, int q, int turn, float (&v)[8]) {
         unpack4(r[0], false, *reinterpret_cast<float(*)[4]>(&v[0]));
         unpack4(r[1], false, *reinterpret_cast<float(*)[4]>(&v[4]));
         if (left < BK) {
+            if (turn) {                               // (uniform) only the group that `left` cuts is kept in part
+                const int at = left & ~3;             // its first k within the tile
+#pragma unroll
+                for (int h = 0; h < 8; h += 4) {
+                    if (4 * q + (h ? 16 : 0) != at) continue;
+                    const float x = v[h + 1], y = v[h + 2], z = v[h + 3];
+                    v[h] = turn == 1 ? x : turn == 2 ? y : z;
+                    v[h + 1] = turn == 1 ? y : z;
+                    v[h + 2] = z;
+                }
+            }
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = 4 * q + (t & 3) + (t >= 4 ? 16 : 0) < left ? v[t] : 0.f;
         }
@@ -580,7 +596,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
 #pragma unroll
         for (int r = 0; r < B_REPS; ++r) {
             float v[8];
-            floats(rb[r], left, tq, v);
+            floats(rb[r], left, tq, 0, v);
             if (BN % 64 == 0 || trow + 64 * r < BN) put_split8<PLANE>(bput + (kt & 1) * 3 * PLANE + 64 * 64 * r, v);
         }
     };
@@ -593,6 +609,12 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
             const bool zero = IRREG && !second && a_zero[i];
             if (A_BF16 && !second) {
                 uint4 w = make_uint4(ra[i][0].x, ra[i][0].y, ra[i][1].x, ra[i][1].y);
+                if (left < BK && a_turn) {            // two packed pairs: shifted as one 64-bit word
+                    auto turned = [&](uint32_t lo, uint32_t hi) { return (((uint64_t)hi << 32) | lo) >> (16 * a_turn); };
+                    const uint64_t t0 = turned(w.x, w.y), t1 = turned(w.z, w.w);
+                    if (4 * lq == (left & ~3)) { w.x = (uint32_t)t0; w.y = (uint32_t)(t0 >> 32); }
+                    if (4 * lq + 16 == (left & ~3)) { w.z = (uint32_t)t1; w.w = (uint32_t)(t1 >> 32); }
+                }
                 if (left < BK || zero) {
                     const int have = zero ? -64 : left - 4 * lq;
                     auto keep = [&](uint32_t x, int q) { return have >= q + 2 ? x : have == q + 1 ? x & 0xFFFFu : 0u; };
@@ -601,7 +623,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
                 a[i][0] = a[i][1] = a[i][2] = __builtin_bit_cast(bf16x8, w);
             } else {
                 float v[8];
-                floats(ra[i], left, lq, v);
+                floats(ra[i], left, lq, second ? 0 : a_turn, v);
                 if (zero) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) v[t] = 0.f;
@@ -780,7 +802,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         // 32-bit element offsets inside a slab and inside Bt
         const bool small = a.lda < (1 << 23) && a.lda2 < (1 << 23) && (int64_t)a.N * a.ldbt < (1ll << 31) &&
                            (int64_t)a.N * a.ldbt2 < (1ll << 31);
-        const bool ok = small && veca && a.ldbt % 4 == 0 && a.ldbt >= round_up(a.K, 4) && (uintptr_t)a.Bt % 16 == 0 &&
+        const bool ok = small && (veca || a.K >= 4) && a.ldbt % 4 == 0 && a.ldbt >= round_up(a.K, 4) && (uintptr_t)a.Bt % 16 == 0 &&
                         (a.K2 == 0 || (a.Bt2 && a.ldbt2 % 4 == 0 && a.ldbt2 >= round_up(a.K2, 4) && (uintptr_t)a.Bt2 % 16 == 0));
         const int n_eff = a.zero_pad_to > a.N ? a.zero_pad_to : a.N;
         // one profiling name per kernel variant, so that the names line up with a kernel trace
@@ -795,7 +817,9 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
             GRP_LAUNCH_CHECK();
             return GRP_OK;
         }
-        const bool rowlimit = a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
+        GemmNNArgs t = a;
+        t.a_tight = veca ? 0 : 1;
+        const bool irreg = t.a_tight || a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
         int tile_n = n_eff > 96 ? 128 : n_eff > 64 ? 96 : n_eff > 32 ? 64 : 32;
         // A product whose 128-row tiles would leave half the chip idle (mini-batch blocks) is cut into
         // 64 x 64 tiles instead: four times the workgroups, each a quarter of the work.
@@ -809,8 +833,8 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, tile_n));
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
-        if (rowlimit) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, a);         \
-        else hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false>), dim3(blocks), dim3(256), 0, st, a);                 \
+        if (irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, t);         \
+        else hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false>), dim3(blocks), dim3(256), 0, st, t);                 \
     } while (0)
 #define GRP_NT_LAUNCH(TM_, TN_)                                                                                            \
     do {                                                                                                                   \
@@ -949,7 +973,11 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
     const int64_t ld = is_a ? (a2 ? g.lda2 : g.lda) : (b2 ? g.ldb2 : g.ldb);
     const int width = is_a ? g.K : g.N;
     const int c_first = (is_a ? ka0 : n0) + 4 * grp;
-    const int col = imin(c_first, ((width + 3) & ~3) - 4);
+    // the first column of an operand's last group: rows without room for all of it end it at their last element, and its
+    // columns then repeat some of the group before
+    const int last_a = (g.a_tight && !a2) ? g.K - 4 : ((g.K + 3) & ~3) - 4;
+    const int last_b = g.b_tight ? g.N - 4 : ((g.N + 3) & ~3) - 4;
+    const int col = imin(c_first, is_a ? last_a : last_b);
     const bool bf16 = is_a && a_one;
     const int32_t* const rows = (GATHER && is_a && !a2) ? g.a_rows : nullptr;
     const bool do_cs = cs_out != nullptr && ka0 == 0 && !op2;
@@ -1073,16 +1101,18 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int row = wn * TN * 32 + 32 * j + li;
-        cols[j] = n0 + 4 * (row % QB) + row / QB;
+        const int c = n0 + 4 * (row % QB), cr = imin(c, last_b) + row / QB;
+        cols[j] = cr >= c ? cr : g.N;                 // (repeated: not stored)
     }
-    const bool pair = TN == 2 && BN == 128 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && cols[TN - 1] < g.N;   // neighbours
+    const bool pair = TN == 2 && BN == 128 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && cols[TN - 1] < g.N &&
+                      cols[0] < g.N && cols[0] % 2 == 0;       // neighbours
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int row = wm * TM * 32 + 32 * i + 8 * (r / 4) + 4 * lk + (r % 4);
-            const int ka = ka0 + 4 * (row % QA) + row / QA;
-            if (ka >= g.K) continue;
+            const int kc = ka0 + 4 * (row % QA), ka = imin(kc, last_a) + row / QA;
+            if (ka >= g.K || ka < kc) continue;
             float* orow = o + (int64_t)ka * out_ld;
             if constexpr (TN == 2) {
                 if (pair) { *reinterpret_cast<float2*>(orow + cols[0]) = make_float2(acc[i][0][r], acc[i][1][r]); continue; }
@@ -1102,7 +1132,8 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
             float t = 0.f;
 #pragma unroll
             for (int u = 0; u < BK / 8; ++u) t += red[u * BN + tid];
-            if (n0 + tid < g.N) cs_out[(int64_t)split * cs_split_stride + n0 + tid] = t;
+            const int c = n0 + (tid & ~3), cr = imin(c, last_b) + (tid & 3);
+            if (cr < g.N && cr >= c) cs_out[(int64_t)split * cs_split_stride + cr] = t;
         }
     }
 }
@@ -1269,15 +1300,19 @@ grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st) {
         const double prods = dual ? 2.0 : 1.0;
         ProfScope ps(a.a_bf16 ? "gemm_tn_bf16a" : "gemm_tn_f32", st, 2.0 * prods * a.M * a.K * a.N,
                      (double)a.M * a.K * (elem + (dual == 1 ? 4 : 0)) + 4.0 * a.M * a.N * (dual == 2 ? 2 : 1) + 4.0 * prods * a.K * a.N);
-        const bool vec = veca && vecb && veca2 && vecb2;
+        // A2 and B2 come from the step's own arrays; A and B may have any pitch and alignment (see last_a, last_b)
+        const bool vec = (veca || (a.K >= 4 && a.lda < (1 << 25))) && (vecb || (a.N >= 4 && a.ldb < (1 << 25) && !a.B2)) && veca2 && vecb2 && a.M > 0;
+        GemmTNArgs t = a;
+        t.a_tight = vec && !veca;
+        t.b_tight = vec && !vecb;
         if (a.a_bf16) {
-            if (vec && !a.a_rows) tn_pick<__hip_bfloat16, true, false>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
-            else if (vec) tn_pick<__hip_bfloat16, true, true>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
-            else tn_pick<__hip_bfloat16, false, true>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
+            if (vec && !a.a_rows) tn_pick<__hip_bfloat16, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            else if (vec) tn_pick<__hip_bfloat16, true, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            else tn_pick<__hip_bfloat16, false, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
         } else {
-            if (vec && !a.a_rows) tn_pick<float, true, false>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
-            else if (vec) tn_pick<float, true, true>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
-            else tn_pick<float, false, true>(a, p, dual, out, out2, out_ld, stride, cs_out, st);
+            if (vec && !a.a_rows) tn_pick<float, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            else if (vec) tn_pick<float, true, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            else tn_pick<float, false, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
         }
         GRP_LAUNCH_CHECK();
     }

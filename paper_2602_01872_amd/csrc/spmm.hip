@@ -26,13 +26,23 @@
 
 namespace grp {
 
+// Rows of X may start at any element: the vector loads below ask for no more than the element's own alignment (the hardware takes
+// them at the full rate when the address happens to be 16-byte friendly, which it is for every pitch of whole vectors).
+// A row of F columns whose pitch leaves no room for its last, partial vector is read with that vector moved back to end at the
+// row's last element (SpmmEpilogue::last_x): the lane that owns it sums columns F-4 .. F-1 and turns them into place when
+// the row is finished.
+// (1e5 rows of 75 fp32 columns packed without padding, 1.5e6 edges: 1090 us a sweep with one lane per column, 55 us this way.)
+
 template <typename T> struct Vec4Load;
 template <> struct Vec4Load<float> {
-    static __device__ __forceinline__ float4 ld(const float* p) { return *reinterpret_cast<const float4*>(p); }
+    static __device__ __forceinline__ float4 ld(const float* p) {
+        const u32x4_any r = *reinterpret_cast<const u32x4_any*>(p);
+        return make_float4(__uint_as_float(r.x), __uint_as_float(r.y), __uint_as_float(r.z), __uint_as_float(r.w));
+    }
 };
 template <> struct Vec4Load<__hip_bfloat16> {
     static __device__ __forceinline__ float4 ld(const __hip_bfloat16* p) {
-        uint2 r = *reinterpret_cast<const uint2*>(p);
+        const u32x2_any r = *reinterpret_cast<const u32x2_any*>(p);
         float4 v;
         v.x = __uint_as_float(r.x << 16);
         v.y = __uint_as_float(r.x & 0xFFFF0000u);
@@ -78,7 +88,7 @@ template <typename XT, int G, int NJ, bool EV, bool WIDE = false>
 __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t b,
                                             int64_t e, const XT* __restrict__ X, int64_t ldx,
                                             const float* __restrict__ colscale, int t, const bool (&live)[NJ],
-                                            float4 (&acc)[NJ]) {
+                                            const int (&colx)[NJ], float4 (&acc)[NJ]) {
     constexpr int U = (G == SPMM_DEEP_G && NJ == 1) ? 8 : 4;       // a batch holds G indices, so U <= G
     for (int64_t base = b; base < e; base += G) {
         const int cnt = (int)((e - base) < (int64_t)G ? (e - base) : (int64_t)G);
@@ -113,10 +123,9 @@ __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, con
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 if (!live[j]) continue;
-                const int col = 4 * (t + G * j);
                 float4 v[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = Vec4Load<XT>::ld(X + c[u] * ldx + col);
+                for (int u = 0; u < U; ++u) v[u] = Vec4Load<XT>::ld(X + c[u] * ldx + colx[j]);
                 if (EV || colscale) {
 #pragma unroll
                     for (int u = 0; u < U; ++u) axpy4(acc[j], sc[u], v[u]);
@@ -140,7 +149,7 @@ __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, con
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 if (!live[j]) continue;
-                const float4 v0 = Vec4Load<XT>::ld(X + c0 * ldx + 4 * (t + G * j));
+                const float4 v0 = Vec4Load<XT>::ld(X + c0 * ldx + colx[j]);
                 axpy4(acc[j], s0, v0);
             }
         }
@@ -164,13 +173,32 @@ struct SpmmEpilogue {
     const float* rowscale;    // a_i given explicitly; null: from `scale` and the row length
     const int64_t* n_rows_dev;       // when set: the real row count and the real addend_rows (device values;
     const int64_t* addend_rows_dev;  //           the launch and addend_rows above are upper bounds)
+    int last_x;               // no vector of an X row starts past this column
+    int vec_out;              // Y and the addend take 16-byte vectors
 };
 
 template <typename XT>
 __device__ __forceinline__ void finish_row(const SpmmEpilogue& ep, int64_t i, int64_t deg, int col, float4 r,
                                            const XT* __restrict__ X, int64_t ldx) {
     const float a = ep.rowscale ? ep.rowscale[i] : row_scale(ep.scale, deg, ep.self_term);
-    if (ep.self_term) add4(r, Vec4Load<XT>::ld(X + i * ldx + col));
+    if (ep.self_term) add4(r, Vec4Load<XT>::ld(X + i * ldx + imin(col, ep.last_x)));
+    if (col > ep.last_x) {                                  // the row's last vector was moved back: turn it into place
+        const int by = col - ep.last_x;
+        r = by == 1 ? make_float4(r.y, r.z, r.w, 0.f) : by == 2 ? make_float4(r.z, r.w, 0.f, 0.f) : make_float4(r.w, 0.f, 0.f, 0.f);
+    }
+    if (!ep.vec_out) {
+        float o[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (col + q >= ep.F) break;
+            float y = o[q] * a;
+            if (ep.addend) y += ep.addend[i * ep.ld_add + col + q];
+            if (ep.bias) y += ep.bias[col + q];
+            if (ep.relu) y = y > 0.f ? y : 0.f;
+            ep.Y[i * ep.ldy + col + q] = y;
+        }
+        return;
+    }
     r.x *= a; r.y *= a; r.z *= a; r.w *= a;
     if (ep.addend && i < (ep.addend_rows_dev ? *ep.addend_rows_dev : ep.addend_rows)) add4(r, *reinterpret_cast<const float4*>(ep.addend + i * ep.ld_add + col));
     float o[4] = {r.x, r.y, r.z, r.w};
@@ -202,7 +230,7 @@ __device__ __forceinline__ void finish_row(const SpmmEpilogue& ep, int64_t i, in
 // One workgroup per chunk of a long row -> one partial row.
 template <typename XT, int G, int NJ, bool EV, bool WIDE = false>
 __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t* __restrict__ idx,
-                                           const float* __restrict__ val, int F,
+                                           const float* __restrict__ val, int F, int last_x,
                                            const XT* __restrict__ X, int64_t ldx, const float* __restrict__ colscale,
                                            float* __restrict__ part_row, float* red) {
     constexpr int NG = 256 / G;
@@ -214,12 +242,14 @@ __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t
     if (e > ce) e = ce;
     float4 acc[NJ];
     bool live[NJ];
+    int colx[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         live[j] = slab_col<G, WIDE>(t, j) < F;
+        colx[j] = imin(slab_col<G, WIDE>(t, j), last_x);
     }
-    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, acc);
+    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, colx, acc);
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
         *reinterpret_cast<float4*>(&red[gi * W + slab_col<G, WIDE>(t, j)]) = acc[j];
@@ -249,7 +279,7 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restric
     constexpr int ROWS = 256 / G;
     __shared__ __attribute__((aligned(16))) float red[ROWS * 4 * G * NJ];
     if ((int)blockIdx.x < n_chunks) {              // uniform per workgroup
-        chunk_body<XT, G, NJ, EV, WIDE>(chunk_begin[blockIdx.x], chunk_end[blockIdx.x], idx, val, ep.F, X, ldx, colscale,
+        chunk_body<XT, G, NJ, EV, WIDE>(chunk_begin[blockIdx.x], chunk_end[blockIdx.x], idx, val, ep.F, ep.last_x, X, ldx, colscale,
                               partials + (int64_t)blockIdx.x * ld_part, red);
         return;
     }
@@ -260,12 +290,14 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restric
     if (e - b > long_thr) return;     // its chunks are reduced above, the row is finished by the combine kernel
     float4 acc[NJ];
     bool live[NJ];
+    int colx[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         live[j] = slab_col<G, WIDE>(t, j) < ep.F;
+        colx[j] = imin(slab_col<G, WIDE>(t, j), ep.last_x);
     }
-    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, acc);
+    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, colx, acc);
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
         if (live[j]) finish_row<XT>(ep, i, e - b, slab_col<G, WIDE>(t, j), acc[j], X, ldx);
@@ -305,13 +337,13 @@ __global__ __launch_bounds__(256) void spmm_combine_kernel(const int32_t* __rest
 template <typename XT, int VW> struct LaneVec;
 template <> struct LaneVec<float, 4> {
     static __device__ __forceinline__ void ld(const float* p, float (&f)[4]) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
+        const float4 v = Vec4Load<float>::ld(p);
         f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
     }
 };
 template <> struct LaneVec<__hip_bfloat16, 4> {
     static __device__ __forceinline__ void ld(const __hip_bfloat16* p, float (&f)[4]) {
-        const uint2 r = *reinterpret_cast<const uint2*>(p);
+        const u32x2_any r = *reinterpret_cast<const u32x2_any*>(p);
         f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xFFFF0000u);
         f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xFFFF0000u);
     }
@@ -334,7 +366,7 @@ template <> struct LaneVec<__hip_bfloat16, 8> {
 // and a gathered row is added with one multiply-add per element (times 1, or 0 past the task's end).
 template <typename XT, int G, int NJ, int VW, bool EV, bool CS, bool SHIFT32 = false>
 __global__ __launch_bounds__(256) void spmm_tasks_kernel(const SliceTask* __restrict__ tasks, int64_t n_tasks, int64_t per_wave,
-                                                         const int32_t* __restrict__ idx, const float* __restrict__ val, int F,
+                                                         const int32_t* __restrict__ idx, const float* __restrict__ val, int F, int last_x,
                                                          const XT* __restrict__ X, int64_t ldx,
                                                          const float* __restrict__ colscale, float* __restrict__ partials,
                                                          int64_t ld_part, int row_shift) {
@@ -374,12 +406,12 @@ __global__ __launch_bounds__(256) void spmm_tasks_kernel(const SliceTask* __rest
 #pragma unroll
     for (int q = 0; q < IPL; ++q) wx[q] = 1.f;
     load_indices(cur.begin, pass_len(cur, 0), ix, wx);
-    int col[NJ];                                           // first column of the lane's unit in slab j (a dead unit reads column 0)
+    int col[NJ];                                           // first column the lane reads in slab j (a dead unit reads column 0)
     bool live[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         live[j] = VW * (t + G * j) < F;
-        col[j] = live[j] ? VW * (t + G * j) : 0;
+        col[j] = live[j] ? (VW == 4 ? imin(VW * (t + G * j), last_x) : VW * t) : 0;
     }
     float acc[NJ][VW];
 #pragma unroll
@@ -471,7 +503,7 @@ __global__ __launch_bounds__(256) void spmm_tasks_kernel(const SliceTask* __rest
 #pragma unroll
                     for (int q = 0; q < VW; ++q) acc[j][q] += __shfl_xor(acc[j][q], o, 64);
                 if (gi == 0 && live[j]) {
-                    float* out = partials + (int64_t)cur.id * ld_part + col[j];
+                    float* out = partials + (int64_t)cur.id * ld_part + VW * (t + G * j);
 #pragma unroll
                     for (int q = 0; q < VW; q += 4)
                         *reinterpret_cast<float4*>(out + q) = make_float4(acc[j][q], acc[j][q + 1], acc[j][q + 2], acc[j][q + 3]);
@@ -534,7 +566,7 @@ __global__ __launch_bounds__(256) void spmm_combine_tasks_kernel(const int32_t* 
     }
 }
 
-// Fallback for pitches or pointers that are not 16-byte friendly: one wavefront per row,
+// Rows of fewer than four columns without room for one vector: one wavefront per row,
 // one lane per column (handles rows of any length itself).
 template <typename XT>
 __global__ __launch_bounds__(256) void spmm_rows_scalar_kernel(
@@ -588,7 +620,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             }
         }
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F,
+            hipLaunchKernelGGL(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F, ep.last_x,
                                (const XT*)a.X, a.ldx, a.colscale, a.partials, ld_part, row_shift);
         };
         // bf16 rows of whole 16-byte units: eight elements per lane, half the lanes per row
@@ -685,9 +717,13 @@ grp_status launch_spmm(const SpmmArgs& a, hipStream_t st) {
         return fail(GRP_EINVAL, "spmm: bad arguments");
     const int elem = a.x_bf16 ? 2 : 4;
     const int64_t fpad = round_up(a.F, 4);
-    const bool vec_ok = a.ldx >= fpad && a.ldy >= fpad && a.ldx % 4 == 0 && a.ldy % 4 == 0 &&
-                        ((uintptr_t)a.X % (4 * elem)) == 0 && ((uintptr_t)a.Y % 16) == 0 &&
-                        (!a.addend || (a.ld_add % 4 == 0 && a.ld_add >= fpad && ((uintptr_t)a.addend % 16) == 0));
+    // X rows of any pitch and alignment are read as vectors; only a row of fewer than four columns packed without padding is not.
+    // (Rows of whole vectors that are also aligned keep the last vector where it is and may read pad columns.)
+    const bool roomy = a.ldx >= fpad && a.ldx % 4 == 0 && ((uintptr_t)a.X % (4 * elem)) == 0;
+    const bool vec_out = a.ldy >= fpad && a.ldy % 4 == 0 && ((uintptr_t)a.Y % 16) == 0 &&
+                         (!a.addend || (a.ld_add % 4 == 0 && a.ld_add >= fpad && ((uintptr_t)a.addend % 16) == 0));
+    const bool plain = !a.residual && !a.Y2 && !a.mask && a.addend_rows <= 0 && !a.addend_rows_dev;
+    const bool vec_ok = (roomy || a.F >= 4) && (vec_out || plain);
     // compulsory traffic: the index stream, the row pointers, every source row once, every
     // output row once (+ addend rows)
     const int64_t n_src = a.n_src > 0 ? a.n_src : a.n_rows;
@@ -707,10 +743,10 @@ grp_status launch_spmm(const SpmmArgs& a, hipStream_t st) {
             return fail(GRP_EINVAL, "spmm: mask must be 16-byte aligned with a pitch multiple of 4");
         SpmmEpilogue ep{a.scale, a.self_term, a.relu, a.F, a.addend, a.ld_add, a.bias, a.Y, a.ldy,
                         a.residual, a.ld_res, a.Y2, a.ldy2, a.addend_rows > 0 ? a.addend_rows : a.n_rows, a.mask, a.ld_mask,
-                        a.rowscale, a.n_rows_dev, a.addend_rows_dev};
+                        a.rowscale, a.n_rows_dev, a.addend_rows_dev, (int)(roomy ? fpad : a.F) - 4, vec_out ? 1 : 0};
         GRP_TRY(a.x_bf16 ? dispatch<__hip_bfloat16>(a, ep, st) : dispatch<float>(a, ep, st));
     } else {
-        if (a.residual || a.Y2 || a.mask || a.addend_rows > 0 || a.addend_rows_dev)
+        if (!plain)
             return fail(GRP_EUNSUPPORTED, "spmm: this epilogue needs 16-byte friendly operands");
         const int64_t blocks = cdiv(a.n_rows, 4);
         if (a.x_bf16)
