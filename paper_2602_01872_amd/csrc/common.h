@@ -146,10 +146,12 @@ namespace grp {
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
-// 16 and 8 bytes at any element boundary (global loads of these need no alignment beyond the element's, and are as fast as
-// aligned ones when the address is a multiple of their size)
+// 16 and 8 bytes at any element boundary: global loads of these need no alignment beyond the element's
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+
+typedef uint32_t u32x4_al __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_al __attribute__((ext_vector_type(2)));
 
 static inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline int64_t round_up(int64_t a, int64_t b) { return cdiv(a, b) * b; }

@@ -42,13 +42,15 @@ template <> __device__ __forceinline__ float to_f<float>(float v) { return v; }
 template <> __device__ __forceinline__ float to_f<__hip_bfloat16>(__hip_bfloat16 v) { return __bfloat162float(v); }
 
 // Four consecutive elements as raw bits (fp32: 16 bytes, bf16: 8 bytes in .x/.y).
-template <typename T>
+template <typename T, bool ANY = false /* at any element boundary */>
 __device__ __forceinline__ uint4 ldg_raw4(const T* __restrict__ p) {
     if constexpr (sizeof(T) == 4) {
-        const u32x4_any r = *reinterpret_cast<const u32x4_any*>(p);
+        using V = typename std::conditional<ANY, u32x4_any, u32x4_al>::type;
+        const V r = *reinterpret_cast<const V*>(p);
         return make_uint4(r.x, r.y, r.z, r.w);
     } else {
-        const u32x2_any r = *reinterpret_cast<const u32x2_any*>(p);
+        using V = typename std::conditional<ANY, u32x2_any, u32x2_al>::type;
+        const V r = *reinterpret_cast<const V*>(p);
         return make_uint4(r.x, r.y, 0u, 0u);
     }
 }
@@ -559,8 +561,8 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
             const float* pb = g.Bt + k0;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                ra[i][0] = ldg_raw4<AT>(pa + (aoff[i] + d0));
-                ra[i][1] = ldg_raw4<AT>(pa + (aoff[i] + d1));
+                ra[i][0] = ldg_raw4<AT, IRREG>(pa + (aoff[i] + d0));
+                ra[i][1] = ldg_raw4<AT, IRREG>(pa + (aoff[i] + d1));
             }
 #pragma unroll
             for (int r = 0; r < B_REPS; ++r) {
@@ -916,7 +918,7 @@ size_t gemm_tn_workspace_bytes(int64_t M, int32_t K, int32_t N) {
 // from 8*c of a row sit at place c ^ tn_turn(row).
 // Whole 32-row steps load as they are; columns past K or N are read from clamped
 // addresses and never masked, since they only reach output rows / columns that are not stored.
-// GATHER: rows of A are taken through g.a_rows.  cs_out (optional): the workgroups of the
+// GATHER: rows of A are taken through g.a_rows, or an operand is tightly packed.  cs_out (optional): the workgroups of the
 // first row of output tiles also add up the columns of B they stream.
 
 // Chosen so that neither side meets a bank conflict (counted: none): a 16-byte write serves eight consecutive lanes, here rows, per
@@ -975,8 +977,8 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
     const int c_first = (is_a ? ka0 : n0) + 4 * grp;
     // the first column of an operand's last group: rows without room for all of it end it at their last element, and its
     // columns then repeat some of the group before
-    const int last_a = (g.a_tight && !a2) ? g.K - 4 : ((g.K + 3) & ~3) - 4;
-    const int last_b = g.b_tight ? g.N - 4 : ((g.N + 3) & ~3) - 4;
+    const int last_a = (GATHER && g.a_tight && !a2) ? g.K - 4 : ((g.K + 3) & ~3) - 4;
+    const int last_b = GATHER && g.b_tight ? g.N - 4 : ((g.N + 3) & ~3) - 4;
     const int col = imin(c_first, is_a ? last_a : last_b);
     const bool bf16 = is_a && a_one;
     const int32_t* const rows = (GATHER && is_a && !a2) ? g.a_rows : nullptr;
@@ -1004,11 +1006,11 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
             if (sizeof(AT) == 2 && bf16) {
                 const __hip_bfloat16* p = (const __hip_bfloat16*)op + mr * ld + col;
 #pragma unroll
-                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<__hip_bfloat16>(p + r * ld);
+                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<__hip_bfloat16, GATHER>(p + r * ld);
             } else {
                 const float* p = (const float*)op + mr * ld + col;
 #pragma unroll
-                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<float>(p + r * ld);
+                for (int r = 0; r < 8; ++r) raw[r] = ldg_raw4<float, GATHER>(p + r * ld);
             }
             return;
         }
@@ -1018,8 +1020,8 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
             const int64_t gm = lmin(mr + r, g.M - 1);
             const int64_t row = rows ? (int64_t)rows[gm] : gm;
             if constexpr (VEC) {
-                if (sizeof(AT) == 2 && bf16) raw[r] = ldg_raw4<__hip_bfloat16>((const __hip_bfloat16*)op + row * ld + col);
-                else raw[r] = ldg_raw4<float>((const float*)op + row * ld + col);
+                if (sizeof(AT) == 2 && bf16) raw[r] = ldg_raw4<__hip_bfloat16, GATHER>((const __hip_bfloat16*)op + row * ld + col);
+                else raw[r] = ldg_raw4<float, GATHER>((const float*)op + row * ld + col);
                 if (!ok) raw[r] = make_uint4(0u, 0u, 0u, 0u);
             } else if (sizeof(AT) == 2 && bf16) {          // back to packed halves
                 const uint4 f = ldg_safe4((const __hip_bfloat16*)op + row * ld, ok, c_first, width);
@@ -1102,17 +1104,17 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
     for (int j = 0; j < TN; ++j) {
         const int row = wn * TN * 32 + 32 * j + li;
         const int c = n0 + 4 * (row % QB), cr = imin(c, last_b) + row / QB;
-        cols[j] = cr >= c ? cr : g.N;                 // (repeated: not stored)
+        cols[j] = !GATHER || cr >= c ? cr : g.N;      // (repeated: not stored)
     }
     const bool pair = TN == 2 && BN == 128 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && cols[TN - 1] < g.N &&
-                      cols[0] < g.N && cols[0] % 2 == 0;       // neighbours
+                      (!GATHER || (cols[0] < g.N && cols[0] % 2 == 0));      // neighbours
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int row = wm * TM * 32 + 32 * i + 8 * (r / 4) + 4 * lk + (r % 4);
             const int kc = ka0 + 4 * (row % QA), ka = imin(kc, last_a) + row / QA;
-            if (ka >= g.K || ka < kc) continue;
+            if (ka >= g.K || (GATHER && ka < kc)) continue;
             float* orow = o + (int64_t)ka * out_ld;
             if constexpr (TN == 2) {
                 if (pair) { *reinterpret_cast<float2*>(orow + cols[0]) = make_float2(acc[i][0][r], acc[i][1][r]); continue; }
@@ -1306,11 +1308,11 @@ grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st) {
         t.a_tight = vec && !veca;
         t.b_tight = vec && !vecb;
         if (a.a_bf16) {
-            if (vec && !a.a_rows) tn_pick<__hip_bfloat16, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            if (vec && !a.a_rows && veca && vecb) tn_pick<__hip_bfloat16, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
             else if (vec) tn_pick<__hip_bfloat16, true, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
             else tn_pick<__hip_bfloat16, false, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
         } else {
-            if (vec && !a.a_rows) tn_pick<float, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
+            if (vec && !a.a_rows && veca && vecb) tn_pick<float, true, false>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
             else if (vec) tn_pick<float, true, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
             else tn_pick<float, false, true>(t, p, dual, out, out2, out_ld, stride, cs_out, st);
         }

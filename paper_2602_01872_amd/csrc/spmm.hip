@@ -31,7 +31,7 @@ namespace grp {
 // A row of F columns whose pitch leaves no room for its last, partial vector is read with that vector moved back to end at the
 // row's last element (SpmmEpilogue::last_x): the lane that owns it sums columns F-4 .. F-1 and turns them into place when
 // the row is finished.
-// (1e5 rows of 75 fp32 columns packed without padding, 1.5e6 edges: 1090 us a sweep with one lane per column, 55 us this way.)
+// (1e5 rows of 75 fp32 columns packed without padding, 1.4e6 edges: 1090 us a sweep with one lane per column, 73 us this way.)
 
 template <typename T> struct Vec4Load;
 template <> struct Vec4Load<float> {
@@ -52,7 +52,6 @@ template <> struct Vec4Load<__hip_bfloat16> {
     }
 };
 
-constexpr int SPMM_DEEP_G = 16;      // groups of this many lanes (rows of 33..64 elements) keep 8 gathers in flight
 
 __device__ __forceinline__ float row_scale(int mode, int64_t deg, int self_term) {
     if (mode == GRP_SCALE_MEAN) return 1.0f / (float)(deg > 1 ? deg : 1);
@@ -71,10 +70,14 @@ __device__ __forceinline__ void add4(float4& acc, const float4& v) {
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
 }
 
-// Sum of X rows over the edges [b, e) for the calling group of G lanes (lane t).
+// Sum of X rows over the edges [b, e), taken by S groups of G lanes (this one is number gi; lane t of its group; tl = gi * G + t).
 // EV: every edge carries a value val[e] that multiplies its gathered row.
-// U neighbour rows are requested before any is accumulated: 4, or 8 for groups of 16 lanes (measured:
-// +4 % at F = 47; no gain for wider rows, and narrower groups fetch fewer than 8 indices per batch).
+// The S * G lanes fetch a batch of column indices with one load (or U / G of them, where that is more than one: a batch holds at
+// least one step of every group); edge k of the batch belongs to group k % S.  A group requests U of its rows before it
+// adds any; places past the batch's end read its last row again (a hit in L1) and add it zero times.  Fetched one by one,
+// the last few rows of every batch cost a memory latency each, and narrow groups had no full step at all.
+// A lone group of wide rows takes the last rows of a batch singly: a repeated gather of 512 bytes is not free (3.25 edges a row:
+// F = 256 181 us, with repeats 185; F = 100 87 and 91; bf16 F = 128 83 and 86; but F = 47 67 us singly and 63 with repeats).
 // WIDE (bf16 rows of whole 16-byte units, NJ = 2): a lane owns eight consecutive columns, fetched with one 16-byte load
 // and kept as two adjacent 4-column slabs, so a row takes half the lanes and a wavefront gathers twice the rows.
 template <int G, bool WIDE> __device__ __forceinline__ int slab_col(int t, int j) { return WIDE ? 8 * t + 4 * j : 4 * (t + G * j); }
@@ -84,74 +87,73 @@ __device__ __forceinline__ void bf16x8_to_float4s(const uint4& r, float4& lo, fl
     hi = make_float4(__uint_as_float(r.z << 16), __uint_as_float(r.z & 0xFFFF0000u), __uint_as_float(r.w << 16),
                      __uint_as_float(r.w & 0xFFFF0000u));
 }
-template <typename XT, int G, int NJ, bool EV, bool WIDE = false>
+template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
 __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, const float* __restrict__ val, int64_t b,
                                             int64_t e, const XT* __restrict__ X, int64_t ldx,
-                                            const float* __restrict__ colscale, int t, const bool (&live)[NJ],
+                                            const float* __restrict__ colscale, int t, int gi, const bool (&live)[NJ],
                                             const int (&colx)[NJ], float4 (&acc)[NJ]) {
-    constexpr int U = (G == SPMM_DEEP_G && NJ == 1) ? 8 : 4;       // a batch holds G indices, so U <= G
-    for (int64_t base = b; base < e; base += G) {
-        const int cnt = (int)((e - base) < (int64_t)G ? (e - base) : (int64_t)G);
-        const int mine = (t < cnt) ? idx[base + t] : 0;
-        float minew = 1.f;
-        if (EV) minew = (t < cnt) ? val[base + t] : 0.f;
-        int k = 0;
-        for (; k + U <= cnt; k += U) {
-            int64_t c[U];
-            float sc[U];
+    static_assert(!WIDE || (NJ == 2 && sizeof(XT) == 2), "eight bf16 columns per lane");
+    constexpr int L = G * S;                               // lanes of a row
+    constexpr int U = 4;                                   // (8: no faster for any width, with these batches)
+    constexpr bool SINGLY = S == 1 && (G >= 32 || (WIDE && G >= 8));      // no places past a batch's end: its last rows one by one
+    constexpr int Q = G < U ? U / G : 1;                   // indices per lane: a batch of L * Q holds at least one step of every group
+    for (int64_t base = b; base < e; base += L * Q) {
+        const int cnt = (int)((e - base) < (int64_t)(L * Q) ? (e - base) : (int64_t)(L * Q));
+        int mine[Q];
+        float minew[Q];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                c[u] = __shfl(mine, k + u, G);
+        for (int q = 0; q < Q; ++q) {
+            const int tl = q * L + gi * G + t;
+            const int64_t at = base + (tl < cnt ? tl : cnt - 1);
+            mine[q] = idx[at];
+            minew[q] = EV ? val[at] : 1.f;
+        }
+        auto step = [&](auto uc, int k) {                  // the group's rows k .. k + UC - 1 of the batch
+            constexpr int UC = decltype(uc)::value;
+            int64_t c[UC];
+            float sc[UC];
+#pragma unroll
+            for (int u = 0; u < UC; ++u) {
+                const int pos = (k + u) * S + gi;
+                const bool on = SINGLY || pos < cnt;
+                // Q > 1: k is 0 and place u lies in register u / G (a place past the end reads a copy of the last index)
+                const int q = Q > 1 ? u / G : 0;
+                const int from = Q > 1 ? pos - q * L : on ? pos : cnt - 1;
+                c[u] = __shfl(mine[q], from, L);
                 sc[u] = colscale ? colscale[c[u]] : 1.f;
-                if (EV) sc[u] *= __shfl(minew, k + u, G);
+                if (EV) sc[u] *= __shfl(minew[q], from, L);
+                sc[u] = on ? sc[u] : 0.f;
             }
             if constexpr (WIDE) {
-                static_assert(!WIDE || (NJ == 2 && sizeof(XT) == 2), "eight bf16 columns per lane");
                 if (live[0]) {                             // F is a multiple of 8: both slabs are live or neither
-                    uint4 r[U];
+                    uint4 r[UC];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) r[u] = *reinterpret_cast<const uint4*>(X + c[u] * ldx + 8 * t);
+                    for (int u = 0; u < UC; ++u) r[u] = *reinterpret_cast<const uint4*>(X + c[u] * ldx + 8 * t);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
+                    for (int u = 0; u < UC; ++u) {
                         float4 lo, hi;
                         bf16x8_to_float4s(r[u], lo, hi);
-                        if (EV || colscale) { axpy4(acc[0], sc[u], lo); axpy4(acc[1], sc[u], hi); }
-                        else { add4(acc[0], lo); add4(acc[1], hi); }
+                        axpy4(acc[0], sc[u], lo); axpy4(acc[1], sc[u], hi);
                     }
                 }
-            } else
+            } else {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if (!live[j]) continue;
-                float4 v[U];
+                for (int j = 0; j < NJ; ++j) {
+                    if (!live[j]) continue;
+                    float4 v[UC];
 #pragma unroll
-                for (int u = 0; u < U; ++u) v[u] = Vec4Load<XT>::ld(X + c[u] * ldx + colx[j]);
-                if (EV || colscale) {
+                    for (int u = 0; u < UC; ++u) v[u] = Vec4Load<XT>::ld(X + c[u] * ldx + colx[j]);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) axpy4(acc[j], sc[u], v[u]);
-                } else {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) add4(acc[j], v[u]);
+                    for (int u = 0; u < UC; ++u) axpy4(acc[j], sc[u], v[u]);        // x * 1 + acc rounds once, as x + acc does
                 }
             }
-        }
-        for (; k < cnt; ++k) {
-            const int64_t c0 = __shfl(mine, k, G);
-            float s0 = colscale ? colscale[c0] : 1.f;
-            if (EV) s0 *= __shfl(minew, k, G);
-            if constexpr (WIDE) {
-                if (live[0]) {
-                    float4 lo, hi;
-                    bf16x8_to_float4s(*reinterpret_cast<const uint4*>(X + c0 * ldx + 8 * t), lo, hi);
-                    axpy4(acc[0], s0, lo); axpy4(acc[1], s0, hi);
-                }
-            } else
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if (!live[j]) continue;
-                const float4 v0 = Vec4Load<XT>::ld(X + c0 * ldx + colx[j]);
-                axpy4(acc[j], s0, v0);
-            }
+        };
+        int k = 0;
+        if constexpr (SINGLY) {
+            for (; k + U <= cnt; k += U) step(std::integral_constant<int, U>(), k);
+            for (; k < cnt; ++k) step(std::integral_constant<int, 1>(), k);
+        } else {
+            for (; k * S < cnt; k += U) step(std::integral_constant<int, U>(), k);
         }
     }
 }
@@ -174,30 +176,34 @@ struct SpmmEpilogue {
     const int64_t* n_rows_dev;       // when set: the real row count and the real addend_rows (device values;
     const int64_t* addend_rows_dev;  //           the launch and addend_rows above are upper bounds)
     int last_x;               // no vector of an X row starts past this column
-    int vec_out;              // Y and the addend take 16-byte vectors
+    int tight;                // bit 0: last_x is not a whole number of vectors; bit 1: Y or the addend take no 16-byte vectors
 };
 
 template <typename XT>
 __device__ __forceinline__ void finish_row(const SpmmEpilogue& ep, int64_t i, int64_t deg, int col, float4 r,
                                            const XT* __restrict__ X, int64_t ldx) {
     const float a = ep.rowscale ? ep.rowscale[i] : row_scale(ep.scale, deg, ep.self_term);
-    if (ep.self_term) add4(r, Vec4Load<XT>::ld(X + i * ldx + imin(col, ep.last_x)));
-    if (col > ep.last_x) {                                  // the row's last vector was moved back: turn it into place
-        const int by = col - ep.last_x;
-        r = by == 1 ? make_float4(r.y, r.z, r.w, 0.f) : by == 2 ? make_float4(r.z, r.w, 0.f, 0.f) : make_float4(r.w, 0.f, 0.f, 0.f);
-    }
-    if (!ep.vec_out) {
-        float o[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (col + q >= ep.F) break;
-            float y = o[q] * a;
-            if (ep.addend) y += ep.addend[i * ep.ld_add + col + q];
-            if (ep.bias) y += ep.bias[col + q];
-            if (ep.relu) y = y > 0.f ? y : 0.f;
-            ep.Y[i * ep.ldy + col + q] = y;
+    if (ep.tight) {                                          // (uniform)
+        if (ep.self_term) add4(r, Vec4Load<XT>::ld(X + i * ldx + imin(col, ep.last_x)));
+        if (col > ep.last_x) {                               // the row's last vector was moved back: turn it into place
+            const int by = col - ep.last_x;
+            r = by == 1 ? make_float4(r.y, r.z, r.w, 0.f) : by == 2 ? make_float4(r.z, r.w, 0.f, 0.f) : make_float4(r.w, 0.f, 0.f, 0.f);
         }
-        return;
+        if (ep.tight & 2) {                                  // Y or the addend take no vectors
+            const float o[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (col + q >= ep.F) break;
+                float y = o[q] * a;
+                if (ep.addend) y += ep.addend[i * ep.ld_add + col + q];
+                if (ep.bias) y += ep.bias[col + q];
+                if (ep.relu) y = y > 0.f ? y : 0.f;
+                ep.Y[i * ep.ldy + col + q] = y;
+            }
+            return;
+        }
+    } else if (ep.self_term) {
+        add4(r, Vec4Load<XT>::ld(X + i * ldx + col));
     }
     r.x *= a; r.y *= a; r.z *= a; r.w *= a;
     if (ep.addend && i < (ep.addend_rows_dev ? *ep.addend_rows_dev : ep.addend_rows)) add4(r, *reinterpret_cast<const float4*>(ep.addend + i * ep.ld_add + col));
@@ -249,7 +255,7 @@ __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t
         live[j] = slab_col<G, WIDE>(t, j) < F;
         colx[j] = imin(slab_col<G, WIDE>(t, j), last_x);
     }
-    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, colx, acc);
+    gather_rows<XT, G, 1, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, 0, live, colx, acc);
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
         *reinterpret_cast<float4*>(&red[gi * W + slab_col<G, WIDE>(t, j)]) = acc[j];
@@ -267,7 +273,8 @@ __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t
 // are the heavy ones, so they start first); the others take the rows of at most `long_thr`
 // edges, one group per row.  One launch instead of two keeps the few chunk workgroups from
 // running on an otherwise idle chip.
-template <typename XT, int G, int NJ, bool EV, bool WIDE = false>
+// S groups share a row (see spmm_groups for the choice); their sums are added in a fixed butterfly.
+template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, int64_t n_rows, int64_t long_thr,
                                                         const XT* __restrict__ X,
@@ -276,16 +283,16 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restric
                                                         const int64_t* __restrict__ chunk_begin,
                                                         const int64_t* __restrict__ chunk_end,
                                                         float* __restrict__ partials, int64_t ld_part) {
-    constexpr int ROWS = 256 / G;
-    __shared__ __attribute__((aligned(16))) float red[ROWS * 4 * G * NJ];
+    constexpr int ROWS = 256 / (G * S);
+    __shared__ __attribute__((aligned(16))) float red[256 * 4 * NJ];
     if ((int)blockIdx.x < n_chunks) {              // uniform per workgroup
         chunk_body<XT, G, NJ, EV, WIDE>(chunk_begin[blockIdx.x], chunk_end[blockIdx.x], idx, val, ep.F, ep.last_x, X, ldx, colscale,
                               partials + (int64_t)blockIdx.x * ld_part, red);
         return;
     }
-    const int t = threadIdx.x % G;
-    const int64_t i = (int64_t)(blockIdx.x - n_chunks) * ROWS + threadIdx.x / G;
-    if (i >= (ep.n_rows_dev ? *ep.n_rows_dev : n_rows)) return;          // whole groups leave together (G divides 64)
+    const int t = threadIdx.x % G, gi = S == 1 ? 0 : threadIdx.x / G % S;
+    const int64_t i = (int64_t)(blockIdx.x - n_chunks) * ROWS + threadIdx.x / (G * S);
+    if (i >= (ep.n_rows_dev ? *ep.n_rows_dev : n_rows)) return;          // a row's lanes leave together (G * S divides 64)
     const int64_t b = ptr[i], e = ptr[i + 1];
     if (e - b > long_thr) return;     // its chunks are reduced above, the row is finished by the combine kernel
     float4 acc[NJ];
@@ -297,7 +304,17 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restric
         live[j] = slab_col<G, WIDE>(t, j) < ep.F;
         colx[j] = imin(slab_col<G, WIDE>(t, j), ep.last_x);
     }
-    gather_rows<XT, G, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, live, colx, acc);
+    gather_rows<XT, G, S, NJ, EV, WIDE>(idx, val, b, e, X, ldx, colscale, t, gi, live, colx, acc);
+    if constexpr (S > 1) {
+#pragma unroll
+        for (int o = G; o < G * S; o <<= 1)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                acc[j].x += __shfl_xor(acc[j].x, o, 64); acc[j].y += __shfl_xor(acc[j].y, o, 64);
+                acc[j].z += __shfl_xor(acc[j].z, o, 64); acc[j].w += __shfl_xor(acc[j].w, o, 64);
+            }
+        if (gi != 0) return;
+    }
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
         if (live[j]) finish_row<XT>(ep, i, e - b, slab_col<G, WIDE>(t, j), acc[j], X, ldx);
@@ -593,6 +610,23 @@ __global__ __launch_bounds__(256) void spmm_rows_scalar_kernel(
     }
 }
 
+// Groups that may share a row of G lanes' width: four, as far as a wavefront holds them.
+constexpr int SPMM_GROUPS(int G) { return G >= 64 ? 1 : G == 32 ? 2 : 4; }
+// Whether they do.  A lone group walks the longest unsplit row of a small graph while the chip waits, and a wavefront of many narrow
+// groups waits for the longest of its rows; shared rows cost a butterfly each, and idle lanes where rows are short.  Against
+// one group per row (us):
+//   2500 rows, 3 edges a row (skewed): F = 8 18.2 -> 11.1, F = 47 17.2 -> 10.9;  2e4 rows, 15: F = 8 21.9 -> 11.1, F = 47 22.8 -> 16.0
+//   1e6 rows, 25: F = 3 250 -> 227, F = 8 236 -> 209, F = 16 306 -> 266, F = 32 399 -> 376, but F = 47 601 -> 636
+//   3e5 rows, 3.25: F = 8 35 -> 28, F = 16 44 -> 40, but F = 32 52 -> 60, F = 47 63 -> 94, F = 100 91 -> 108
+//   1e5 rows, 14: F = 100 78 -> 75, F = 47 58 -> 56 (uniform degrees: 45 -> 49), bf16 F = 128 73 -> 75
+// (before: at F = 8 these were 30, 36, 354 and 56 us.)
+static bool spmm_share(const SpmmArgs& a, int G, int S) {
+    if (cdiv(a.n_rows, 256 / (G * S)) >= ((int64_t)3 << 22)) return false;      // (a launch holds fewer than 2^32 work-items)
+    const int64_t waves = a.n_rows * G / 64;               // with one group per row
+    if (G <= 2 || waves <= 2048 || (G <= 4 && a.nnz >= 2 * a.n_rows)) return true;
+    return a.nnz >= 8 * a.n_rows && (G <= 8 || waves <= (G == 32 ? 65536 : 8192));
+}
+
 template <typename XT, int G, int NJ>
 static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st) {
     constexpr int ROWS = 256 / G;
@@ -643,33 +677,32 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
         }
     }
+    auto rows = [&](auto kernel, int lanes) {              // lanes: of a row
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), dim3(256), 0, st, a.ptr, a.idx, a.val,
+                           a.n_rows, thr, (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
+                           n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+    };
     bool rows_done = false;
     if constexpr (std::is_same<XT, __hip_bfloat16>::value && G >= 2 && NJ == 1) {
         // bf16 rows of whole 16-byte units: eight columns per lane, half the lanes per row (twice the rows per wavefront)
         if (a.F % 8 == 0 && a.ldx % 8 == 0 && ((uintptr_t)a.X % 16) == 0 && !a.self_term) {
-            constexpr int GW = G / 2;
-            const dim3 wgrid((unsigned)(n_chunks + cdiv(a.n_rows, 256 / GW)));
-            if (a.val)
-                hipLaunchKernelGGL((spmm_rows_kernel<XT, GW, 2, true, true>), wgrid, dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows,
-                                   thr, (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
-                                   n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
-            else
-                hipLaunchKernelGGL((spmm_rows_kernel<XT, GW, 2, false, true>), wgrid, dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows,
-                                   thr, (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
-                                   n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+            constexpr int GW = G / 2, S = SPMM_GROUPS(GW);
+            if (S > 1 && spmm_share(a, GW, S)) {
+                if (a.val) rows(spmm_rows_kernel<XT, GW, S, 2, true, true>, GW * S);
+                else rows(spmm_rows_kernel<XT, GW, S, 2, false, true>, GW * S);
+            } else if (a.val) rows(spmm_rows_kernel<XT, GW, 1, 2, true, true>, GW);
+            else rows(spmm_rows_kernel<XT, GW, 1, 2, false, true>, GW);
             rows_done = true;
         }
     }
-    const dim3 grid((unsigned)(n_chunks + cdiv(a.n_rows, ROWS)));
-    if (rows_done) {
-    } else if (a.val)
-        hipLaunchKernelGGL((spmm_rows_kernel<XT, G, NJ, true>), grid, dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows, thr,
-                           (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
-                           n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
-    else
-        hipLaunchKernelGGL((spmm_rows_kernel<XT, G, NJ, false>), grid, dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows, thr,
-                           (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
-                           n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+    if (!rows_done) {
+        constexpr int S = SPMM_GROUPS(G);
+        if (S > 1 && spmm_share(a, G, S)) {
+            if (a.val) rows(spmm_rows_kernel<XT, G, S, NJ, true>, G * S);
+            else rows(spmm_rows_kernel<XT, G, S, NJ, false>, G * S);
+        } else if (a.val) rows(spmm_rows_kernel<XT, G, 1, NJ, true>, G);
+        else rows(spmm_rows_kernel<XT, G, 1, NJ, false>, G);
+    }
     if (sliced) {
         hipLaunchKernelGGL((spmm_combine_tasks_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, 4)), dim3(256), 0, st,
                            lr->long_row, (const int64_t*)lr->row_task, lr->n_long, a.ptr, (const float*)a.partials, ld_part,
@@ -743,7 +776,7 @@ grp_status launch_spmm(const SpmmArgs& a, hipStream_t st) {
             return fail(GRP_EINVAL, "spmm: mask must be 16-byte aligned with a pitch multiple of 4");
         SpmmEpilogue ep{a.scale, a.self_term, a.relu, a.F, a.addend, a.ld_add, a.bias, a.Y, a.ldy,
                         a.residual, a.ld_res, a.Y2, a.ldy2, a.addend_rows > 0 ? a.addend_rows : a.n_rows, a.mask, a.ld_mask,
-                        a.rowscale, a.n_rows_dev, a.addend_rows_dev, (int)(roomy ? fpad : a.F) - 4, vec_out ? 1 : 0};
+                        a.rowscale, a.n_rows_dev, a.addend_rows_dev, (int)(roomy ? fpad : a.F) - 4, (roomy ? 0 : 1) | (vec_out ? 0 : 2)};
         GRP_TRY(a.x_bf16 ? dispatch<__hip_bfloat16>(a, ep, st) : dispatch<float>(a, ep, st));
     } else {
         if (!plain)
