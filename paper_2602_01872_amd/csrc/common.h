@@ -235,11 +235,14 @@ struct GemmNNArgs {
     int64_t ldbt = 0;
     const float* Bt2 = nullptr;     // same for the second product
     int64_t ldbt2 = 0;
+    unsigned char* planes = nullptr;  // scratch of gemm_planes_bytes for B split once per launch (null: split in the kernel)
+    size_t planes_bytes = 0;
     // Row counts known on the device only: when set, M (and a_valid_rows) above are upper bounds that
     // size the launch, and the kernels read the real values here.
     const int64_t* M_dev = nullptr;
     const int64_t* a_valid_rows_dev = nullptr;
 };
+size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K);      // K: of both products together
 grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st);
 
 // C[K x N] = A[M x K]^T B[M x N], fixed-order split over M.

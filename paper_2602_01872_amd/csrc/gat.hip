@@ -20,6 +20,8 @@
 // longer than SPMM_LONG_ROW edges are walked in the partition's chunks by whole workgroups.
 #include "common.h"
 
+#include <algorithm>
+
 namespace grp {
 
 constexpr float GAT_SLOPE = 0.2f;
@@ -460,6 +462,8 @@ struct GatPlan {
     float2* dqs;
     void *tn_ws, *colsum_ws, *stats_ws;
     size_t tn_ws_bytes, total;
+    unsigned char* planes = nullptr;   // the weights of the product at hand, split (GemmNNArgs::planes)
+    size_t planes_bytes = 0;
 };
 
 static inline int64_t ldp4(int64_t f) { return round_up(f, 4); }
@@ -471,7 +475,7 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
     const int k = m->n_layers;
     p.L.resize(k);
     int64_t off = 0, ldmax = 4, ldxmax = 8, wxmax = 1;
-    size_t tn_bytes = 0, cs_bytes = 0;
+    size_t tn_bytes = 0, cs_bytes = 0, pl_bytes = 0;
     for (int l = 0; l < k; ++l) {
         GatLayer& L = p.L[l];
         L.fin = m->dims[l]; L.fout = m->dims[l + 1];
@@ -493,6 +497,7 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
         if (t > tn_bytes) tn_bytes = t;
         const size_t c = colsum_workspace_bytes(n, L.fout);
         if (c > cs_bytes) cs_bytes = c;
+        pl_bytes = std::max({pl_bytes, gemm_planes_bytes(n, (int32_t)L.ldx, L.fin), gemm_planes_bytes(n, L.fin, (int32_t)L.ldx)});
     }
     p.dZa = b.take<float>((size_t)n * ldmax);
     p.dZb = b.take<float>((size_t)n * ldmax);
@@ -505,6 +510,8 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
     p.tn_ws = b.take<char>(tn_bytes);
     p.tn_ws_bytes = tn_bytes;
     p.colsum_ws = b.take<char>(cs_bytes);
+    if (pl_bytes > 0) p.planes = b.take<unsigned char>(pl_bytes);
+    p.planes_bytes = pl_bytes;
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
     p.total = b.total();
     return p;
@@ -584,6 +591,7 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
     for (int l = 0; l < k; ++l) {
         const GatLayer& L = p.L[l];
         GemmNNArgs a;          // T_ext = H [W | 0 | W a_src | W a_dst | 0 0]
+        a.planes = p.planes; a.planes_bytes = p.planes_bytes;
         a.M = n; a.N = (int)L.ldx; a.K = L.fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16; a.Bt = L.Wt; a.ldbt = L.ldin_pad;
         a.C = L.Tx; a.ldc = L.ldx;
         GRP_TRY(launch_gemm_nn(a, st));
@@ -639,6 +647,7 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
         }
         if (l > 0) {
             GemmNNArgs c;      // dZ_prev = (H_in > 0) * (dT_ext W_ext^T)
+            c.planes = p.planes; c.planes_bytes = p.planes_bytes;
             c.M = n; c.N = L.fin; c.K = (int)L.ldx; c.A = p.dTx; c.lda = L.ldx; c.Bt = L.Wp; c.ldbt = L.ldx;
             c.mask = p.L[l - 1].Hout; c.ld_mask = p.L[l - 1].ldh;
             c.C = dZ_other; c.ldc = p.L[l - 1].ldh; c.zero_pad_to = (int)p.L[l - 1].ldh;

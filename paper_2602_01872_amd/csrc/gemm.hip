@@ -35,6 +35,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 32;      // k-tile depth
 constexpr int NT_WGS = 3;   // resident workgroups per CU that the 128-wide tiles are built for (48 KB of LDS and 168 registers each)
+constexpr int NT_PRE_SLABS = 512;      // products over fewer slabs of 128 rows split B in the kernel (a launch for the planes costs 3 us)
 constexpr int NXCD = 8;     // L2 domains; consecutive workgroup ids go round them
 
 template <typename T> __device__ __forceinline__ float to_f(T v);
@@ -454,7 +455,13 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // an operand are clamped to its last row (their products are not stored); only the last, ragged k-tile of a product
 // is masked.
 // IRREG selects the variant with gathered (a_rows), limited (a_valid_rows) or tightly packed (a_tight) A rows.
-template <typename AT, int TM, int TN, bool IRREG>
+// PRE: B comes as planes (g.planes, split_b_kernel below) whose 1 KB runs are copied from memory to LDS without passing
+// through registers.  The loop is bound by issue: matrix and vector instructions of a SIMD's wavefronts add up (96 of the
+// former and about 330 of the latter per k-tile: 1536 + 1320 cycles, 2870 measured), and the split of B, which every slab of
+// 128 rows did again, was a third of the vector instructions.  SAGE step on 3e5 rows (five such products) 3184 -> 3044 us, residual
+// GCN-8 step on 2^20 rows 61.0 -> 59.5 ms, attention step 4282 -> 4180 us (with the 96-column tiles), bf16 share of 8.4e6 rows
+// 41.3 -> 41.0 ms.
+template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
 __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     if (g.M_dev) {                                    // the launch was sized by upper bounds
         g.M = *g.M_dev;
@@ -536,13 +543,28 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
             d1 = imin(16, last);
         }
     };
+    // PRE: tile kt of B into its half of the LDS; a wavefront's copy is 64 consecutive units of 16 bytes on both sides
+    const uint32_t lds_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+    const int swave = __builtin_amdgcn_readfirstlane(wave);
+    auto copy_b = [&](int kt) {
+        constexpr int RUNS = 3 * BN / 16, PER_PLANE = BN / 16;
+        const int64_t n_all = (int64_t)n_tiles * BN;
+#pragma unroll
+        for (int r = 0; r < (RUNS + 3) / 4; ++r) {
+            const int c = swave + 4 * r;
+            if (RUNS % 4 != 0 && c >= RUNS) break;
+            const unsigned char* const from = g.planes + (((int64_t)kt * 3 + c / PER_PLANE) * n_all + n0 + 16 * (c % PER_PLANE)) * 64;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(lds_at + (kt & 1) * 3 * PLANE + c * 1024), "v"(lane * 16), "s"(from) : "memory");
+        }
+    };
     auto fetch = [&](int kt) {
         const bool second = kt >= nk1;
         const int k0 = (second ? kt - nk1 : kt) * BK;
         const int Kc = second ? g.K2 : g.K;
         int d0, d1, e0, e1;
         clamp(k0, Kc, lq, second ? 0 : a_turn, d0, d1);
-        clamp(k0, Kc, tq, 0, e0, e1);
+        if (!PRE) clamp(k0, Kc, tq, 0, e0, e1);
         if (second) {
             const float* pa = a2_base + k0;
             const float* pb = g.Bt2 + k0;
@@ -552,7 +574,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
                 ra[i][1] = ldg_raw4<float>(pa + (aoff2[i] + d1));
             }
 #pragma unroll
-            for (int r = 0; r < B_REPS; ++r) {
+            for (int r = 0; !PRE && r < B_REPS; ++r) {
                 rb[r][0] = ldg_raw4<float>(pb + (boff2[r] + e0));
                 rb[r][1] = ldg_raw4<float>(pb + (boff2[r] + e1));
             }
@@ -565,7 +587,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
                 ra[i][1] = ldg_raw4<AT, IRREG>(pa + (aoff[i] + d1));
             }
 #pragma unroll
-            for (int r = 0; r < B_REPS; ++r) {
+            for (int r = 0; !PRE && r < B_REPS; ++r) {
                 rb[r][0] = ldg_raw4<float>(pb + (boff[r] + e0));
                 rb[r][1] = ldg_raw4<float>(pb + (boff[r] + e1));
             }
@@ -672,13 +694,25 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     };
 
     fetch(0);
-    stage_b(0);
-    for (int kt = 0; kt < nk; ++kt) {
-        split_a(kt);
-        if (kt + 1 < nk) fetch(kt + 1);
-        __syncthreads();                              // tile kt is written; everybody is done with tile kt - 1
-        mma(kt);
-        if (kt + 1 < nk) stage_b(kt + 1);
+    if constexpr (PRE) {
+        copy_b(0);
+        for (int kt = 0; kt < nk; ++kt) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's part of tile kt is in LDS (and its rows of A here)
+            split_a(kt);
+            if (kt + 1 < nk) fetch(kt + 1);
+            __syncthreads();                          // so is everybody's; everybody is done with tile kt - 1
+            if (kt + 1 < nk) copy_b(kt + 1);
+            mma(kt);
+        }
+    } else {
+        stage_b(0);
+        for (int kt = 0; kt < nk; ++kt) {
+            split_a(kt);
+            if (kt + 1 < nk) fetch(kt + 1);
+            __syncthreads();                          // tile kt is written; everybody is done with tile kt - 1
+            mma(kt);
+            if (kt + 1 < nk) stage_b(kt + 1);
+        }
     }
 
     // ---- epilogue: (+ addend) (+ bias) -> C_raw; (* rowscale) (ReLU) (mask) -> C
@@ -766,6 +800,35 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     }
 }
 
+// The operand(s) B of a product as the planes that the PRE kernels copy: tile kt of 32 k (those of the second product follow the
+// first's), plane, row n < n_all, 64 bytes laid out as the kernel's LDS rows are.  Rows and k that do not exist are zero.
+__global__ __launch_bounds__(256) void split_b_kernel(const float* __restrict__ Bt, int64_t ldbt, int K, const float* __restrict__ Bt2,
+                                                      int64_t ldbt2, int K2, int N, int n_all, unsigned char* __restrict__ planes) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int nk1 = (K + BK - 1) / BK, nk = nk1 + (K2 + BK - 1) / BK;
+    if (e >= nk * n_all * 4) return;
+    const int q = e & 3, n = (e >> 2) % n_all, kt = (e >> 2) / n_all;
+    const bool second = kt >= nk1;
+    const int k0 = (second ? kt - nk1 : kt) * BK + 4 * q, Kc = second ? K2 : K;
+    const float* const row = second ? Bt2 + (int64_t)n * ldbt2 : Bt + (int64_t)n * ldbt;
+    float v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int k = k0 + (t & 3) + (t >= 4 ? 16 : 0);
+        v[t] = n < N && k < Kc ? row[k] : 0.f;
+    }
+    uint4 part[3];
+    split8(v, part[0], part[1], part[2]);
+    unsigned char* const out = planes + ((int64_t)kt * 3 * n_all + n) * 64 + 16 * (q ^ ((n >> 1) & 3));
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(out + (int64_t)p * n_all * 64) = part[p];
+}
+
+size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K) {
+    if (cdiv(M, 128) < NT_PRE_SLABS) return 0;
+    return (size_t)(cdiv(K, BK) + 1) * 3 * round_up(N, 128) * 64;      // (two products round their k up one by one)
+}
+
 // Tile choice (measured on MI355X at M = 3e5; the nt path adds a 128 x 96 tile for 64 < N <= 96,
 // e.g. two stacked 47-wide weight blocks): 128 x 128 output tiles at three workgroups per
 // CU beat 128 x 256 at one; a 32-deep single-buffered k-tile is best for long reductions, a
@@ -831,11 +894,23 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         // overlap their loads and stores better than three of 128 x 128 (K = 16 + 16, N = 128 over 1.7e7 rows: 3.73 -> 3.32 ms).
         const bool small_tiles = n_eff > 32 && (cdiv(m_plan, 128) * cdiv(n_eff, tile_n) < 384 || a.K + a.K2 <= 64);
         if (small_tiles) tile_n = 64;
+        // (W + the attention columns: 260 columns are three tiles of 96 with 28 to spare, of 128 with 124)
+        else if (n_eff > 128 && round_up(n_eff, 96) < round_up(n_eff, 128)) tile_n = 96;
         const int64_t slabs = round_up(cdiv(a.M, small_tiles ? 64 : 128), NXCD);
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, tile_n));
+        // Both k tilings and the padding fit what gemm_planes_bytes reserved for this N and K + K2.
+        const int n_all = (int)cdiv(n_eff, tile_n) * tile_n;
+        const size_t planes_need = (size_t)(cdiv(a.K, BK) + cdiv(a.K2, BK)) * 3 * n_all * 64;
+        const bool pre = !small_tiles && tile_n >= 64 && a.planes && cdiv(m_plan, 128) >= NT_PRE_SLABS && planes_need <= a.planes_bytes;
+        if (pre)
+            hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)cdiv((int64_t)planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
+                               a.ldbt2, a.K2, a.N, n_all, a.planes);
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
-        if (irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, t);         \
+        constexpr bool P_ = TM_ == 2 && TN_ >= 4;                                                                          \
+        if (P_ && pre && irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (P_ && pre) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, t);       \
         else hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false>), dim3(blocks), dim3(256), 0, st, t);                 \
     } while (0)
 #define GRP_NT_LAUNCH(TM_, TN_)                                                                                            \

@@ -10,6 +10,7 @@
 // linear map commute): "aggregate first" when Fin <= Fout, "transform first" otherwise.
 #include "common.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace grp {
@@ -40,6 +41,8 @@ struct StepPlan {
     void *tn_ws = nullptr, *colsum_ws = nullptr, *stats_ws = nullptr, *sampler_ws = nullptr;
     float* partials = nullptr;   // partial rows of the split long rows (SpMM)
     size_t tn_ws_bytes = 0, sampler_bytes = 0;
+    unsigned char* planes = nullptr;   // the weights of the product at hand, split (GemmNNArgs::planes)
+    size_t planes_bytes = 0;
     size_t total = 0;
 };
 
@@ -91,7 +94,7 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
     }
     p.L.resize(k);
     int64_t off = 0, fmax = 0, max_rows = 1;
-    size_t tn_bytes = 0, cs_bytes = 0;
+    size_t tn_bytes = 0, cs_bytes = 0, pl_bytes = 0;
     for (int l = 0; l < k; ++l) {
         LayerBufs& L = p.L[l];
         const int fin = m->dims[l], fout = m->dims[l + 1];
@@ -128,6 +131,9 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         if (t > tn_bytes) tn_bytes = t;
         const size_t c = colsum_workspace_bytes(rows, fout);
         if (c > cs_bytes) cs_bytes = c;
+        const int32_t w = (int32_t)std::max(ldp(fin), ldp(fout));      // one operand of a product may be two matrices side by side
+        const int64_t m_rows = std::max(rows, rows_in);
+        pl_bytes = std::max({pl_bytes, gemm_planes_bytes(m_rows, 2 * w, w), gemm_planes_bytes(m_rows, w, 2 * w)});
     }
     if (!mb) p.inv_in = b.take<float>((size_t)n);
     if (!sage) {
@@ -148,6 +154,8 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
     p.tn_ws = b.take<char>(tn_bytes);
     p.tn_ws_bytes = tn_bytes;
     p.colsum_ws = b.take<char>(cs_bytes);
+    if (pl_bytes > 0) p.planes = b.take<unsigned char>(pl_bytes);
+    p.planes_bytes = pl_bytes;
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
     {
         int64_t fsp = 0;                                   // the widest aggregation of the step
@@ -248,6 +256,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             s.F = fin; s.X = H; s.ldx = ldh; s.x_bf16 = h_bf16; set_mean(s, B); s.Y = L.M; s.ldy = ldp(fin);
             GRP_TRY(launch_spmm(s, st));
             GemmNNArgs a;
+            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
             a.a_rows = B.self_rows; a.Bt = L.Wt_s; a.ldbt = L.ldwt;
             a.K2 = fin; a.A2 = L.M; a.lda2 = ldp(fin); a.Bt2 = L.Wt_n; a.ldbt2 = L.ldwt;
@@ -258,6 +267,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             // H' = ReLU(mean-aggregate(T) + Z0)
             const int64_t w2 = 2 * ldp(fout);
             GemmNNArgs a;
+            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_dst; a.N = (int)(ldp(fout) + fout); a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
             a.Bt = L.Wt_n; a.ldbt = L.ldwt; a.bias = theta + L.off_b; a.bias_col0 = (int)ldp(fout); a.bias_n = fout;
             a.C = p.tmpA; a.ldc = w2; a.zero_pad_to = (int)w2;
@@ -269,6 +279,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             GRP_TRY(launch_spmm(s, st));
         } else {
             GemmNNArgs a;      // T = H Wn over every input row, Z0 = H_self Ws + b
+            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_in; a.M_dev = B.n_in_dev; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
             a.Bt = L.Wt_n; a.ldbt = L.ldwt;
             a.C = p.tmpA; a.ldc = ldp(fout); a.zero_pad_to = (int)ldp(fout);
@@ -323,6 +334,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
                 const int64_t w2 = 2 * ldp(fin);
                 if (B.n_dst > 0) {
                     GemmNNArgs a;
+                    a.planes = p.planes; a.planes_bytes = p.planes_bytes;
                     a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.N = (int)(ldp(fin) + fin); a.K = fout; a.A = dZ; a.lda = ldp(fout);
                     a.Bt = L.Wp_n; a.ldbt = L.ldwp; a.rowscale = B.inv_in; a.rowscale_cols = (int)ldp(fin);
                     a.C = p.tmpA; a.ldc = w2; a.zero_pad_to = (int)w2;
@@ -356,6 +368,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             GRP_TRY(launch_gemm_tn(t, st));
             if (l > 0 && B.n_in > 0) {
                 GemmNNArgs c;      // dZ_prev = mask * ([dZ Ws^T ; 0] + dT Wn^T)
+                c.planes = p.planes; c.planes_bytes = p.planes_bytes;
                 c.M = B.n_in; c.M_dev = B.n_in_dev; c.N = fin; c.K = fout; c.A = dZ; c.lda = ldp(fout);
                 c.a_valid_rows = B.n_dst; c.a_valid_rows_dev = B.n_dst_dev;
                 c.Bt = L.Wp_s; c.ldbt = L.ldwp;
@@ -405,6 +418,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
             ldh = ldp(fin);
         }
         GemmNNArgs a;
+        a.planes = p.planes; a.planes_bytes = p.planes_bytes;
         a.M = n; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16; a.Bt = L.Wt_s; a.ldbt = L.ldwt;
         a.rowscale = p.gs; a.C = p.tmpA; a.ldc = ldp(fout); a.zero_pad_to = (int)ldp(fout);
         GRP_TRY(launch_gemm_nn(a, st));
@@ -446,6 +460,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         if (l > 0 && n > 0) {
             const LayerBufs& Lp = p.L[l - 1];
             GemmNNArgs c;      // G_in = dT W^T (+ G);  dZ'_prev = diag(r) (A_prev > 0) G_in
+            c.planes = p.planes; c.planes_bytes = p.planes_bytes;
             c.M = n; c.N = fin; c.K = fout; c.A = p.tmpA; c.lda = ldp(fout); c.Bt = L.Wp_s; c.ldbt = L.ldwp;
             if (L.skip) { c.addend = G; c.ld_add = ldp(fout); }
             if (Lp.skip) { c.C_raw = G_other; c.ld_raw = ldp(fin); }
