@@ -122,13 +122,19 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
 // New source nodes are collected in a bitmap over the partition's nodes (one bit each): the words'
 // population counts are prefix-summed and every non-empty word then numbers its own nodes, which
 // yields them in ascending local id while touching n / 8 bytes instead of per-node flag arrays.
+// mark[u] - 1 is the place of a node that the block has; for any other node it is whatever the memory held, so a place counts
+// only if it exists and names the node.  (Clearing the map first and after each layer cost the step of a 7e6-node store a fill of
+// 28 MB and a launch per layer: 10.4 of 450 us for the fill and 2.5 for each of the launches.)
 __global__ __launch_bounds__(256) void flag_new_kernel(const int32_t* __restrict__ idx_local,
                                                        const int64_t* __restrict__ nnz_dev,
-                                                       const int32_t* __restrict__ mark, uint32_t* __restrict__ bits) {
-    const int64_t nnz = *nnz_dev;
+                                                       const int32_t* __restrict__ mark, const int32_t* __restrict__ dst_nodes,
+                                                       const int64_t* __restrict__ n_dst_dev, uint32_t* __restrict__ bits) {
+    const int64_t nnz = *nnz_dev, n_dst = *n_dst_dev;
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * 256) {
         const int32_t u = idx_local[e];
-        if (mark[u] == 0) atomicOr(&bits[u >> 5], 1u << (u & 31));
+        const int32_t at = mark[u];
+        const bool known = at > 0 && at <= n_dst && dst_nodes[at - 1] == u;
+        if (!known) atomicOr(&bits[u >> 5], 1u << (u & 31));
     }
 }
 
@@ -179,13 +185,6 @@ __global__ __launch_bounds__(256) void relabel_kernel(const int64_t* __restrict_
     }
 }
 
-__global__ __launch_bounds__(256) void clear_marks_kernel(const int32_t* __restrict__ src_nodes,
-                                                          const int64_t* __restrict__ n_src_dev, int32_t* __restrict__ mark) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= *n_src_dev) return;
-    mark[src_nodes[i]] = 0;
-}
-
 void sampler_bounds(int64_t n, int64_t n_seeds, const int32_t* fanouts, int k, SamplerBounds* out) {
     int64_t nd = n_seeds;
     for (int l = k - 1; l >= 0; --l) {
@@ -219,8 +218,8 @@ struct SamplerBufs {
     SamplerLayerBufs L[GRP_MAX_LAYERS];
     int32_t* seeds;                     // [n_seeds] the caller's seeds, range-checked
     int64_t* sizes;                     // [SZ_PER_LAYER * GRP_MAX_LAYERS] the blocks' real sizes (see the enum)
-    int64_t* bad;                       // [2] seeds outside the partition (carved just before `mark`: one fill clears all)
-    int32_t* mark;                      // [n] block-local index + 1 of the current layer's nodes, else 0
+    int64_t* bad;                       // [2] seeds outside the partition (carved just before `bits`: one fill clears both)
+    int32_t* mark;                      // [n] block-local index + 1 of the current layer's nodes, anything elsewhere
     uint32_t* bits;                     // [n_words + 1] bitmap of newly reached nodes (the last word stays 0)
     int32_t* wpos;                      // [n_words + 1] set bits in the words before each word
     int64_t n_words;
@@ -266,9 +265,9 @@ static SamplerBufs carve_sampler(int64_t n, const SamplerBounds& b, int k, void*
             L.lr_cap_long = L.lr_cap_chunks = 0;
         }
     }
-    s.bad = bump.take<int64_t>(2);
     s.mark = bump.take<int32_t>((size_t)n);
     s.n_words = cdiv(n, 32);
+    s.bad = bump.take<int64_t>(2);
     s.bits = bump.take<uint32_t>((size_t)s.n_words + 1);
     s.wpos = bump.take<int32_t>((size_t)s.n_words + 1);
     s.scan_bytes = scan_temp_bytes(s.n_words + 1 > max_dst + 1 ? s.n_words + 1 : max_dst + 1);
@@ -301,7 +300,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
     SamplerBufs s = carve_sampler(n, bd, k, ws, ws_bytes);
     if (s.total > ws_bytes) return fail(GRP_EWORKSPACE, "mini-batch: sampler workspace %zu < %zu", ws_bytes, s.total);
 
-    {   // the bad-seed counter and, with more than one layer, the node map and the bitmap start at zero
+    {   // the bad-seed counter and, with more than one layer, the bitmap start at zero
         // (carved back to back: one fill covers them)
         char* const lo = (char*)s.bad;
         char* const hi = k > 1 ? (char*)(s.bits + s.n_words + 1) : (char*)(s.bad + 2);
@@ -353,7 +352,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         // new source nodes in ascending local id, block-local relabelling, transposed block
         const int64_t src_bound = bd.src[l], nnz_bound = bd.nnz[l];
         hipLaunchKernelGGL(flag_new_kernel, dim3(blocks_for(nnz_bound)), dim3(256), 0, st, (const int32_t*)L.idx_local,
-                           (const int64_t*)(D + SZ_NNZ), (const int32_t*)s.mark, s.bits);
+                           (const int64_t*)(D + SZ_NNZ), (const int32_t*)s.mark, dst_nodes, (const int64_t*)(D + SZ_DST), s.bits);
         GRP_LAUNCH_CHECK();
         GRP_TRY(exclusive_scan_popcount(s.scan_tmp, s.scan_bytes, s.bits, s.wpos, s.n_words + 1, st));
         hipLaunchKernelGGL(assign_new_kernel, dim3(blocks_for(s.n_words)), dim3(256), 0, st, s.n_words, s.bits,
@@ -377,9 +376,6 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
             bst = lane->stream;
             scan_tmp_t = s.scan_tmp_side;
         }
-        hipLaunchKernelGGL(clear_marks_kernel, dim3(blocks_for(src_bound)), dim3(256), 0, st, (const int32_t*)L.src_nodes,
-                           (const int64_t*)(D + SZ_SRC), s.mark);
-        GRP_LAUNCH_CHECK();
         GRP_TRY(sort_keys_u64(s.sort_tmp, s.sort_bytes, L.keys, L.keys_sorted, nnz_bound, 32u + (unsigned)bits, bst));
         // Over src_bound rows: those past the real sources come out empty (their pointer is the real number
         // of edges, where the sentinels begin), and the entries of idxT past that number are never read.
