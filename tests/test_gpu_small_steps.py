@@ -1,0 +1,66 @@
+"""The loss kernels at the class counts where they change (registers for up to 192 classes, memory above) and at row counts of
+one and a few workgroups, against the oracle; and a mini-batch step on workspaces that hold anything at all: the sampler's node map is
+never cleared, so what it held before must not show in a single bit."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import graph as ograph
+from oracle import step as ostep
+from tests._cases import TOL_FP32, assert_step_grads_close
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def g():
+    import paper_2602_01872_amd as lib
+    lib.load()
+    return lib
+
+
+@pytest.mark.parametrize("N,C", [(1, 65), (15, 128), (17, 129), (255, 172), (257, 192), (400, 193), (4097, 100)])
+def test_loss_at_class_and_row_edges(g, N, C):
+    dims, seed = [6, C], 5
+    s, d = synth.uniform_graph(N, 4 * N, seed=seed)
+    part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, seed, 0)
+    op = ograph.partition(s.numpy(), d.numpy(), N, 1, seed, 0)
+    x, y, theta = synth.normal_matrix(N, 6, seed), synth.labels(N, C, seed), synth.model_weights("sage", dims, seed)
+    model, opts = g.model_desc(g.ARCH_SAGE_MEAN, dims), g.step_opts(full_graph=True)
+    ws = torch.empty(g.grp_step_workspace_bytes(part, model, opts), dtype=torch.uint8, device=DEV)
+    grad, stats = torch.full((g.grp_param_count(model),), float("nan"), device=DEV), g.new_stats(1)
+    g.grp_train_step(part, model, opts, x.to(DEV), y.to(DEV), None, theta.to(DEV), ws, grad, stats)
+    torch.cuda.synchronize()
+
+    def oracle(**kw):
+        return ostep.train_step(op, "sage", dims, theta.double().numpy(), x.double().numpy(), y.numpy(), **kw)
+    _, want = assert_step_grads_close(grad.cpu().numpy(), oracle, "sage", dims, TOL_FP32)
+    got = g.read_stats(stats)[0]
+    assert int(got["S"]) == want["S"] and float(got["R"]) == want["R"]
+    assert abs(float(got["loss"]) - want["loss"]) <= TOL_FP32 * abs(want["loss"])
+    assert np.isclose(float(got["sum_ratio"]), want["sum_ratio"], rtol=1e-12)
+
+
+@pytest.mark.parametrize("fill", [1, 7, -1, 2_000_000_000])
+def test_minibatch_step_on_a_used_workspace(g, fill):
+    N, E, dims, seed = 5000, 60_000, [12, 16, 16, 5], 3
+    s, d = synth.rmat_graph(13, E, seed=seed, n_nodes=N)
+    part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, seed, 0)
+    x, y, theta = synth.normal_matrix(N, 12, seed).to(DEV), synth.labels(N, 5, seed).to(DEV), synth.model_weights("sage", dims, seed).to(DEV)
+    seeds = torch.randperm(N, generator=torch.Generator().manual_seed(1))[:300].to(torch.int32)
+    seeds[7] = seeds[3]                                    # a seed may be given twice
+    model = g.model_desc(g.ARCH_SAGE_MEAN, dims)
+    opts = g.step_opts(full_graph=False, seeds=seeds.to(DEV), fanouts=[4, 4, 4], sampler_seed=9)
+    bytes_ = g.grp_step_workspace_bytes(part, model, opts)
+    out = []
+    for value in (0, fill):
+        ws = torch.full(((bytes_ + 3) // 4,), value, dtype=torch.int32, device=DEV).view(torch.uint8)
+        grad, stats = torch.zeros(g.grp_param_count(model), device=DEV), g.new_stats(1)
+        for _ in range(2):                                 # the second pass finds the first one's map
+            g.grp_train_step(part, model, opts, x, y, None, theta, ws, grad, stats)
+            out.append((grad.clone(), stats.clone()))
+    torch.cuda.synchronize()
+    for grad, stats in out[1:]:
+        assert torch.equal(grad, out[0][0]) and torch.equal(stats, out[0][1])
