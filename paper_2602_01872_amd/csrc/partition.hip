@@ -337,7 +337,9 @@ __global__ __launch_bounds__(256) void edge_keys_kernel(const int64_t* __restric
 // Both passes in one (unweighted builds): range check, global in-degrees of owned destinations and the keys of
 // the kept edges, written into a buffer of `cap` keys.  counters: [1] += bad ids, [2] += kept edges (the
 // slot cursor).  If the cursor ends above cap the keys are incomplete and the caller runs edge_keys_kernel
-// with a buffer of the exact size (the in-degrees and the count are complete either way).
+// with a buffer of the exact size (the in-degrees and the count are complete either way).  N >= 1 (the set has a word 0).
+// One edge after another, every lookup waited for the one before it: 62e6 edges, an eighth of the nodes 663 us; in stages
+// of eight 532 us (1.9 TB/s of edges; the read alone would take 190).
 __global__ __launch_bounds__(256) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
                                                              int64_t E, int64_t N, NodeSet own,
                                                              unsigned long long* __restrict__ dg,
@@ -357,27 +359,54 @@ __global__ __launch_bounds__(256) void edge_scan_keys_kernel(const int64_t* __re
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const int64_t e0 = tile * (256 * PER) + 2 * tid;
         int64_t us[PER], vs[PER];
+        if (vec && (tile + 1) * (256 * PER) <= E) {          // (uniform)
 #pragma unroll
-        for (int i = 0; i < PER; i += 2) {
-            const int64_t e = e0 + (int64_t)i * 256;
-            load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-            load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);     // -2: past the end, neither counted nor an error
+            for (int i = 0; i < PER; i += 2) {
+                const i64x2 a = *reinterpret_cast<const i64x2*>(src + e0 + (int64_t)i * 256);
+                const i64x2 b = *reinterpret_cast<const i64x2*>(dst + e0 + (int64_t)i * 256);
+                us[i] = a.x; us[i + 1] = a.y;
+                vs[i] = b.x; vs[i + 1] = b.y;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < PER; i += 2) {
+                const int64_t e = e0 + (int64_t)i * 256;
+                load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
+                load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]); // -2: past the end, neither counted nor an error
+            }
         }
+        // Eight edges' lookups are requested together, stage by stage; a lane that has no need of one reads word 0 (one line for
+        // all of them).
+        uint32_t word[PER], has = 0, both = 0;               // bit i: the destination, and also the source, of edge i is in the set
+        int32_t rv[PER], ru[PER];
         uint64_t key[PER];
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int64_t u = us[i], v = vs[i];
-            key[i] = ~0ull;
-            if (v == -2) continue;
-            if (u < 0 || v < 0 || u >= N || v >= N) { bad++; continue; }
-            if (!set_has(own, v)) continue;
-            const int32_t rv = set_rank(own, v);
-            dg_table_add(slot_key, slot_count, dg, rv);
-            if (set_has(own, u)) {
-                key[i] = ((uint64_t)(uint32_t)rv << 32) | (uint64_t)(uint32_t)set_rank(own, u);
-                ++mine;
-            }
+            const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
+            bad += !ok && vs[i] != -2;
+            if (!ok) us[i] = vs[i] = 0;
+            word[i] = own.bits[vs[i] >> 5];
+            has |= (ok ? 1u : 0u) << i;
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (!((word[i] >> (vs[i] & 31)) & 1u)) has &= ~(1u << i);
+            const bool in = (has >> i) & 1u;
+            rv[i] = own.before[in ? vs[i] >> 5 : 0] + __popc(word[i] & ((1u << (vs[i] & 31)) - 1u));
+            word[i] = own.bits[in ? us[i] >> 5 : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if ((has >> i) & (word[i] >> (us[i] & 31)) & 1u) both |= 1u << i;
+            ru[i] = own.before[(both >> i) & 1u ? us[i] >> 5 : 0] + __popc(word[i] & ((1u << (us[i] & 31)) - 1u));
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if ((has >> i) & 1u) dg_table_add(slot_key, slot_count, dg, rv[i]);
+            const bool kept = (both >> i) & 1u;
+            key[i] = kept ? ((uint64_t)(uint32_t)rv[i] << 32) | (uint64_t)(uint32_t)ru[i] : ~0ull;
+            mine += kept;
         }
         int incl = mine;
 #pragma unroll
@@ -425,20 +454,16 @@ __global__ __launch_bounds__(256) void local_keys_kernel(const int64_t* __restri
     }
 }
 
-__global__ __launch_bounds__(256) void swap_halves_kernel(const uint64_t* __restrict__ in, int64_t nnz,
-                                                          uint64_t* __restrict__ out) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256)
-        out[i] = (in[i] << 32) | (in[i] >> 32);
-}
-
-// From sorted keys: idx[i] = low half; ptr[r] = first position whose high half is >= r.
+// From sorted keys: idx[i] = low half; ptr[r] = first position whose high half is >= r.  SWAPPED: the halves change places.
+template <bool SWAPPED>
 __global__ __launch_bounds__(256) void csr_from_keys_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int64_t n,
                                                             int64_t* __restrict__ ptr, int32_t* __restrict__ idx) {
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i <= nnz; i += (int64_t)gridDim.x * 256) {
-        const int64_t hi = i < nnz ? (int64_t)(keys[i] >> 32) : n;
-        const int64_t prev = i > 0 ? (int64_t)(keys[i - 1] >> 32) : -1;
+        auto row = [&](int64_t k) { return (int64_t)(SWAPPED ? keys[k] & 0xFFFFFFFFull : keys[k] >> 32); };
+        const int64_t hi = i < nnz ? row(i) : n;
+        const int64_t prev = i > 0 ? row(i - 1) : -1;
         for (int64_t r = prev + 1; r <= hi; ++r) ptr[r] = i;
-        if (i < nnz) idx[i] = (int32_t)(keys[i] & 0xFFFFFFFFull);
+        if (i < nnz) idx[i] = (int32_t)(SWAPPED ? keys[i] >> 32 : keys[i] & 0xFFFFFFFFull);
     }
 }
 
@@ -624,6 +649,23 @@ static size_t carve_csr_csc(grp_partition_t* h, bool weighted, int64_t cap_long,
     return b.total();
 }
 
+// Sorts of the bits [begin, end) of 64-bit keys, with a value each if vals is given (temp null: sizes only).  The library merges
+// below 2^20 keys, in two launches per doubling; its digit passes are already faster from SORT_BY_DIGITS_FROM on.
+// Builds from n nodes and E local edges (us): 2e4, 1.6e5 272 -> 265 and 3e4, 2.5e5 330 -> 332 (merged as before); 4e4, 3e5 368 -> 293;
+// 1e5, 7e5 466 -> 364; 1.2e5, 1e6 505 -> 396; 3e5, 3e6 693 -> 544; 1e6, 2e7 2218 -> 1687 (the last two: the transpose's shorter sort).
+template <unsigned long LIMIT>
+static hipError_t sort_bits_as(void* temp, size_t& bytes, uint64_t* in, uint64_t* out, float* vin, float* vout, int64_t count, unsigned begin,
+                               unsigned end, hipStream_t st) {
+    using Config = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config, rocprim::default_config, LIMIT>;
+    if (vin) return rocprim::radix_sort_pairs<Config>(temp, bytes, in, out, vin, vout, (size_t)count, begin, end, st);
+    return rocprim::radix_sort_keys<Config>(temp, bytes, in, out, (size_t)count, begin, end, st);
+}
+constexpr unsigned long SORT_BY_DIGITS_FROM = 1ul << 18;
+static hipError_t sort_bits(void* temp, size_t& bytes, uint64_t* in, uint64_t* out, float* vin, float* vout, int64_t count, unsigned begin,
+                            unsigned end, hipStream_t st) {
+    return sort_bits_as<SORT_BY_DIGITS_FROM>(temp, bytes, in, out, vin, vout, count, begin, end, st);
+}
+
 // keys (unsorted, nnz of them; clobbered) -> h->rowptr/col/d_local_in and h->colptr/row/d_local_out.
 // vals / vals_alt (optional, nnz floats each; clobbered): a value per key that travels through the
 // (stable) sorts into h->csr_w and h->csc_w.
@@ -640,37 +682,32 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
         return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", h->slab_bytes);
     }
     (void)carve_csr_csc(h, vals != nullptr, cap_long, cap_chunks, h->slab, h->slab_bytes);
-    const unsigned end_bit = 32 + bits_for(n > 1 ? n : 2);
+    const unsigned id_bits = bits_for(n > 1 ? n : 2);
     // one scratch allocation: the sorts' temporary storage, later the long-row pass's prefix sums
-    size_t sort_bytes = 0;
-    if (nnz > 0 && !vals)
-        GRP_HIP(rocprim::radix_sort_keys(nullptr, sort_bytes, keys, keys_alt, (size_t)nnz, 0u, end_bit, st));
-    else if (nnz > 0)
-        GRP_HIP(rocprim::radix_sort_pairs(nullptr, sort_bytes, keys, keys_alt, vals, vals_alt, (size_t)nnz, 0u, end_bit, st));
+    size_t sort_bytes = 0, transpose_bytes = 0;
+    if (nnz > 0) {
+        GRP_HIP(sort_bits(nullptr, sort_bytes, keys, keys_alt, vals, vals_alt, nnz, 0u, 32u + id_bits, st));
+        GRP_HIP(sort_bits(nullptr, transpose_bytes, keys_alt, keys, vals_alt, vals, nnz, 0u, id_bits, st));
+        sort_bytes = std::max(sort_bytes, transpose_bytes);
+    }
     const size_t scan_bytes = cap_long ? scan_temp_bytes(n + 1) : 0;
     const size_t scanned_bytes = cap_long ? (((size_t)n + 1) * sizeof(int64_t) + 255) & ~(size_t)255 : 0;
     size_t tmp_bytes = sort_bytes > scanned_bytes + scan_bytes ? sort_bytes : scanned_bytes + scan_bytes;
     DevBuf tmp;
     GRP_TRY(tmp.alloc(tmp_bytes));
-    if (nnz > 0 && !vals) {
-        GRP_HIP(rocprim::radix_sort_keys(tmp.p, sort_bytes, keys, keys_alt, (size_t)nnz, 0u, end_bit, st));
-    } else if (nnz > 0) {
-        GRP_HIP(rocprim::radix_sort_pairs(tmp.p, sort_bytes, keys, keys_alt, vals, vals_alt, (size_t)nnz, 0u, end_bit, st));
-        GRP_HIP(hipMemcpyAsync(h->csr_w, vals_alt, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
-    }
-    hipLaunchKernelGGL(csr_from_keys_kernel, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys_alt, nnz, n, h->rowptr, h->col);
-    GRP_LAUNCH_CHECK();
     if (nnz > 0) {
-        hipLaunchKernelGGL(swap_halves_kernel, dim3(grid_for(nnz)), dim3(256), 0, st, keys_alt, nnz, keys);
-        GRP_LAUNCH_CHECK();
-        if (!vals) {
-            GRP_HIP(rocprim::radix_sort_keys(tmp.p, sort_bytes, keys, keys_alt, (size_t)nnz, 0u, end_bit, st));
-        } else {      // from CSR order (vals_alt) to CSC order (vals)
-            GRP_HIP(rocprim::radix_sort_pairs(tmp.p, sort_bytes, keys, keys_alt, vals_alt, vals, (size_t)nnz, 0u, end_bit, st));
-            GRP_HIP(hipMemcpyAsync(h->csc_w, vals, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
-        }
+        GRP_HIP(sort_bits(tmp.p, sort_bytes, keys, keys_alt, vals, vals_alt, nnz, 0u, 32u + id_bits, st));
+        if (vals) GRP_HIP(hipMemcpyAsync(h->csr_w, vals_alt, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
     }
-    hipLaunchKernelGGL(csr_from_keys_kernel, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys_alt, nnz, n, h->colptr, h->row);
+    hipLaunchKernelGGL(csr_from_keys_kernel<false>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys_alt, nnz, n, h->rowptr, h->col);
+    GRP_LAUNCH_CHECK();
+    // The transpose: the keys are in order of (destination, source), so that a stable sort by source alone gives the order of
+    // (source, destination): half the digits.
+    if (nnz > 0) {
+        GRP_HIP(sort_bits(tmp.p, sort_bytes, keys_alt, keys, vals_alt, vals, nnz, 0u, id_bits, st));
+        if (vals) GRP_HIP(hipMemcpyAsync(h->csc_w, vals, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
+    }
+    hipLaunchKernelGGL(csr_from_keys_kernel<true>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys, nnz, n, h->colptr, h->row);
     GRP_LAUNCH_CHECK();
     if (n > 0) {
         hipLaunchKernelGGL(degree_from_ptr_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, h->rowptr, n, h->d_local_in);
@@ -768,6 +805,7 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
             GRP_LAUNCH_CHECK();
         } else {
             ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
+            if (N == 0) own = NodeSet{counters.as<uint32_t>(), counters.as<int32_t>()};      // every id is out of range: any word 0 will do
             hipLaunchKernelGGL(edge_scan_keys_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
                                (unsigned long long*)h->d_global_in, counters.as<unsigned long long>(), keybuf.as<uint64_t>(),
                                (unsigned long long)cap);
