@@ -29,7 +29,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0          # MI355X published HBM3E bandwidth
-PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X published dense fp32 matrix rate
+PEAK_FP32_TFLOPS = 2500.0 / 6  # dense fp32 products: six products at the published dense bf16 matrix rate
 
 # HBM bytes per launch of a kernel in a workload come from rocprofv3 --pmc runs of this script (FETCH_SIZE,
 # then WRITE_SIZE, scaled by what the same counter reads for a plain copy); their summaries under profiles/
@@ -111,8 +111,8 @@ def _roofline(kernels, traffic_table):
     dom = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
     k = kernels[dom]
     if dom.startswith("gemm") and "reduce" not in dom:
-        r = dict(kernel=dom, bound="mfma", achieved=k["gflops"] / 1e3, peak=PEAK_FP32_MFMA_TFLOPS, unit="TFLOP/s",
-                 frac=k["gflops"] / 1e3 / PEAK_FP32_MFMA_TFLOPS)
+        r = dict(kernel=dom, bound="mfma", achieved=k["gflops"] / 1e3, peak=PEAK_FP32_TFLOPS, unit="TFLOP/s",
+                 frac=k["gflops"] / 1e3 / PEAK_FP32_TFLOPS)
     else:
         r = dict(kernel=dom, bound="hbm", achieved=k["gbs"], peak=PEAK_HBM_GBS, unit="GB/s", frac=k["gbs"] / PEAK_HBM_GBS)
     t = traffic_table.get(dom.split("[")[0])
