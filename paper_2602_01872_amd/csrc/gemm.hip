@@ -555,7 +555,7 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
             if (RUNS % 4 != 0 && c >= RUNS) break;
             const unsigned char* const from = g.planes + (((int64_t)kt * 3 + c / PER_PLANE) * n_all + n0 + 16 * (c % PER_PLANE)) * 64;
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(lds_at + (kt & 1) * 3 * PLANE + c * 1024), "v"(lane * 16), "s"(from) : "memory");
+                         :: "s"(lds_at + (kt & 1) * 3 * PLANE + c * 1024), "v"(lane * 16), "s"(from) : "memory", "m0");
         }
     };
     auto fetch = [&](int kt) {
