@@ -74,8 +74,9 @@ __device__ __forceinline__ void add4(float4& acc, const float4& v) {
 // EV: every edge carries a value val[e] that multiplies its gathered row.
 // The S * G lanes fetch a batch of column indices with one load (or U / G of them, where that is more than one: a batch holds at
 // least one step of every group); edge k of the batch belongs to group k % S.  A group requests U of its rows before it
-// adds any; places past the batch's end read its last row again (a hit in L1) and add it zero times.  Fetched one by one,
-// the last few rows of every batch cost a memory latency each, and narrow groups had no full step at all.
+// adds any; places past the batch's end read its last row again (a hit in L1) and add zeros in its place (a select: 0 times an
+// infinity would be NaN).  Fetched one by one, the last few rows of every batch cost a memory latency each, and narrow groups
+// had no full step at all.
 // A lone group of wide rows takes the last rows of a batch singly: a repeated gather of 512 bytes is not free (3.25 edges a row:
 // F = 256 181 us, with repeats 185; F = 100 87 and 91; bf16 F = 128 83 and 86; but F = 47 67 us singly and 63 with repeats).
 // WIDE (bf16 rows of whole 16-byte units, NJ = 2): a lane owns eight consecutive columns, fetched with one 16-byte load
@@ -112,17 +113,18 @@ __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, con
             constexpr int UC = decltype(uc)::value;
             int64_t c[UC];
             float sc[UC];
+            bool on[UC];
 #pragma unroll
             for (int u = 0; u < UC; ++u) {
                 const int pos = (k + u) * S + gi;
-                const bool on = SINGLY || pos < cnt;
+                on[u] = SINGLY || pos < cnt;
                 // Q > 1: k is 0 and place u lies in register u / G (a place past the end reads a copy of the last index)
                 const int q = Q > 1 ? u / G : 0;
-                const int from = Q > 1 ? pos - q * L : on ? pos : cnt - 1;
+                const int from = Q > 1 ? pos - q * L : on[u] ? pos : cnt - 1;
                 c[u] = __shfl(mine[q], from, L);
                 sc[u] = colscale ? colscale[c[u]] : 1.f;
                 if (EV) sc[u] *= __shfl(minew[q], from, L);
-                sc[u] = on ? sc[u] : 0.f;
+                sc[u] = on[u] ? sc[u] : 0.f;
             }
             if constexpr (WIDE) {
                 if (live[0]) {                             // F is a multiple of 8: both slabs are live or neither
@@ -131,6 +133,7 @@ __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, con
                     for (int u = 0; u < UC; ++u) r[u] = *reinterpret_cast<const uint4*>(X + c[u] * ldx + 8 * t);
 #pragma unroll
                     for (int u = 0; u < UC; ++u) {
+                        if (!SINGLY) r[u] = on[u] ? r[u] : make_uint4(0u, 0u, 0u, 0u);
                         float4 lo, hi;
                         bf16x8_to_float4s(r[u], lo, hi);
                         axpy4(acc[0], sc[u], lo); axpy4(acc[1], sc[u], hi);
@@ -144,7 +147,10 @@ __device__ __forceinline__ void gather_rows(const int32_t* __restrict__ idx, con
 #pragma unroll
                     for (int u = 0; u < UC; ++u) v[u] = Vec4Load<XT>::ld(X + c[u] * ldx + colx[j]);
 #pragma unroll
-                    for (int u = 0; u < UC; ++u) axpy4(acc[j], sc[u], v[u]);        // x * 1 + acc rounds once, as x + acc does
+                    for (int u = 0; u < UC; ++u) {
+                        if (!SINGLY) v[u] = make_float4(on[u] ? v[u].x : 0.f, on[u] ? v[u].y : 0.f, on[u] ? v[u].z : 0.f, on[u] ? v[u].w : 0.f);
+                        axpy4(acc[j], sc[u], v[u]);        // x * 1 + acc rounds once, as x + acc does
+                    }
                 }
             }
         };
