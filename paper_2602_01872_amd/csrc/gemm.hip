@@ -461,6 +461,20 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // 128 rows did again, was a third of the vector instructions.  SAGE step on 3e5 rows (five such products) 3184 -> 3044 us, residual
 // GCN-8 step on 2^20 rows 61.0 -> 59.5 ms, attention step 4282 -> 4180 us (with the 96-column tiles), bf16 share of 8.4e6 rows
 // 41.3 -> 41.0 ms.
+// One element of the product, added up in plain fp32 along k.
+template <typename AT>
+__device__ __forceinline__ float nt_plain(const GemmNNArgs& g, int64_t m, int n) {
+    const bool zero = g.a_valid_rows > 0 && m >= g.a_valid_rows;       // (such rows of the first A read as zero)
+    const AT* const a = (const AT*)g.A + (zero ? 0 : (g.a_rows ? (int64_t)g.a_rows[m] : m) * g.lda);
+    const float* const b = g.Bt + (int64_t)n * g.ldbt;
+    float s = 0.f;
+    for (int k = 0; k < g.K; ++k) s = fmaf(zero ? 0.f : to_f<AT>(a[k]), b[k], s);
+    const float* const a2 = g.A2 + m * g.lda2;
+    const float* const b2 = g.Bt2 + (int64_t)n * g.ldbt2;
+    for (int k = 0; k < g.K2; ++k) s = fmaf(a2[k], b2[k], s);
+    return s;
+}
+
 template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
 __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     if (g.M_dev) {                                    // the launch was sized by upper bounds
@@ -715,6 +729,35 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
         }
     }
 
+    // An infinity has no planes (x - hi is NaN), and a sum of planes may pass the largest float where the sum of the
+    // products does not.  Both show as results that are not finite: those are added up again in plain fp32.
+    float odd[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) odd[q] = fmaf(acc[i][j][q], 0.f, odd[q]);
+    if (!((odd[0] + odd[1]) + (odd[2] + odd[3]) == 0.f)) {
+#pragma unroll 1
+        for (int e = 0; e < TM * TN * 4; ++e) {
+            const int m_at = wave * 16 * TM + 16 * (e / (4 * TN)) + li, n_at = n0 + 16 * (e / 4 % TN) + 4 * lq + e % 4;
+            auto each = [&](auto f) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[i][j][q] = f((i * TN + j) * 4 + q, acc[i][j][q]);
+            };
+            float v = 0.f;
+            each([&](int at, float x) { v = at == e ? x : v; return x; });
+            if (isfinite(v) || m_at >= rows_here || n_at >= g.N) continue;
+            v = nt_plain<AT>(g, m0 + m_at, n_at);
+            each([&](int at, float x) { return at == e ? v : x; });
+        }
+    }
+
     // ---- epilogue: (+ addend) (+ bias) -> C_raw; (* rowscale) (ReLU) (mask) -> C
     const int bias_n = g.bias_n > 0 ? g.bias_n : g.N - g.bias_col0;
     const int rs_cols = g.rowscale_cols > 0 ? g.rowscale_cols : g.N;
@@ -728,7 +771,6 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
     const bool rs_in = g.rowscale && n0 + BN <= rs_cols;
     const bool rs_out = !g.rowscale || n0 >= rs_cols;
     const bool lean = vec && n0 + BN <= g.N && (bias_in || bias_out) && (rs_in || rs_out);
-    const float floor_v = g.relu ? 0.f : -INFINITY;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int lr = wave * 16 * TM + 16 * i + li;
@@ -755,8 +797,11 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_nt_kernel(GemmNNArgs g) {
                     v.x += b4.x; v.y += b4.y; v.z += b4.z; v.w += b4.w;
                 }
                 if (g.C_raw) *reinterpret_cast<float4*>(g.C_raw + m * g.ld_raw + nl + 16 * j) = v;
-                v.x = fmaxf(v.x * s, floor_v); v.y = fmaxf(v.y * s, floor_v);
-                v.z = fmaxf(v.z * s, floor_v); v.w = fmaxf(v.w * s, floor_v);
+                v.x *= s; v.y *= s; v.z *= s; v.w *= s;
+                if (g.relu) {
+                    v.x = v.x > 0.f ? v.x : 0.f; v.y = v.y > 0.f ? v.y : 0.f;
+                    v.z = v.z > 0.f ? v.z : 0.f; v.w = v.w > 0.f ? v.w : 0.f;
+                }
                 v.x = mv[j].x > 0.f ? v.x : 0.f; v.y = mv[j].y > 0.f ? v.y : 0.f;
                 v.z = mv[j].z > 0.f ? v.z : 0.f; v.w = mv[j].w > 0.f ? v.w : 0.f;
                 *reinterpret_cast<float4*>(Cr + 16 * j) = v;
@@ -1174,22 +1219,62 @@ __global__ __launch_bounds__(256, NT_WGS) void gemm_tn_kernel(GemmTNArgs g, int 
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = __uint_as_float(__float_as_uint(acc[i][j][r]) ^ flip);
-    int cols[TN];                                     // this lane's output columns
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int row = wn * TN * 32 + 32 * j + li;
+    // (an own copy of the thread's number: what is derived from it here need not be kept in registers during the loop above)
+    int tid_e = tid;
+    asm volatile("" : "+v"(tid_e));
+    const int li_e = tid_e & 31, lk_e = (tid_e >> 5) & 1, wm_e = (tid_e >> 6) / WN, wn_e = (tid_e >> 6) % WN;
+    auto col_of = [&](int j) {                        // the output column of this lane's accumulators [.][j] (g.N: none)
+        const int row = wn_e * TN * 32 + 32 * j + li_e;
         const int c = n0 + 4 * (row % QB), cr = imin(c, last_b) + row / QB;
-        cols[j] = !GATHER || cr >= c ? cr : g.N;      // (repeated: not stored)
+        return cr < g.N && (!GATHER || cr >= c) ? cr : g.N;      // (repeated: not stored)
+    };
+    auto row_of = [&](int i, int r) {                 // and the output row of accumulator [i][.][r] (g.K: none)
+        const int row = wm_e * TM * 32 + 32 * i + 8 * (r / 4) + 4 * lk_e + (r % 4);
+        const int kc = ka0 + 4 * (row % QA), ka = imin(kc, last_a) + row / QA;
+        return ka < g.K && (!GATHER || ka >= kc) ? ka : g.K;
+    };
+    // Results that are not finite are added up again in plain fp32, as in gemm_nt_kernel.
+    float odd[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) odd[r & 3] = fmaf(acc[i][j][r], 0.f, odd[r & 3]);
+    if (!((odd[0] + odd[1]) + (odd[2] + odd[3]) == 0.f)) {
+#pragma unroll 1
+        for (int e = 0; e < TM * TN * 16; ++e) {
+            auto each = [&](auto f) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] = f((i * TN + j) * 16 + r, acc[i][j][r]);
+            };
+            float v = 0.f;
+            each([&](int at, float x) { v = at == e ? x : v; return x; });
+            const int ka = row_of(e / (16 * TN), e % 16), c = col_of(e / 16 % TN);
+            if (isfinite(v) || ka >= g.K || c >= g.N) continue;
+            v = 0.f;
+            for (int64_t m = m_begin; m < m_end; ++m) {
+                const float x = a2 ? g.A2[m * g.lda2 + ka] : to_f<AT>(((const AT*)g.A)[(g.a_rows ? (int64_t)g.a_rows[m] : m) * g.lda + ka]);
+                v = fmaf(x, b2 ? g.B2[m * g.ldb2 + c] : g.B[m * g.ldb + c], v);
+            }
+            each([&](int at, float x) { return at == e ? v : x; });
+        }
     }
+    int cols[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cols[j] = col_of(j);
     const bool pair = TN == 2 && BN == 128 && out_ld % 2 == 0 && ((uintptr_t)o % 8) == 0 && cols[TN - 1] < g.N &&
                       (!GATHER || (cols[0] < g.N && cols[0] % 2 == 0));      // neighbours
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int row = wm * TM * 32 + 32 * i + 8 * (r / 4) + 4 * lk + (r % 4);
-            const int kc = ka0 + 4 * (row % QA), ka = imin(kc, last_a) + row / QA;
-            if (ka >= g.K || (GATHER && ka < kc)) continue;
+            const int ka = row_of(i, r);
+            if (ka >= g.K) continue;
             float* orow = o + (int64_t)ka * out_ld;
             if constexpr (TN == 2) {
                 if (pair) { *reinterpret_cast<float2*>(orow + cols[0]) = make_float2(acc[i][0][r], acc[i][1][r]); continue; }
