@@ -128,9 +128,10 @@ __device__ __forceinline__ floatx4 mfma16(bf16x8 a, bf16x8 b, floatx4 c) { retur
 template <typename V> __device__ __forceinline__ void pin(V& v) { asm volatile("" : "+v"(v)); }
 
 // One 32-deep step of a wavefront's TM x TN block of 32x32 tiles.  as / bs + c0: this lane's eight of the first 16 k of its first
-// tile row in the first plane; its eight of the other 16 k lie at c0 ^ 32.  MAYBE_ONE and one: A is a single plane (an operand stored in bf16).
+// tile row in the first plane; its eight of the other 16 k lie at c0 ^ 32.  sign: +1 or -1, of the tile.  MAYBE_ONE and one: A is a single
+// plane (an operand stored in bf16).
 template <int TM, int TN, int PLANE_A, int PLANE_B, bool MAYBE_ONE>
-__device__ __forceinline__ void mma32(const unsigned char* as, const unsigned char* bs, int c0, bool one, floatx16 (&acc)[TM][TN]) {
+__device__ __forceinline__ void mma32(const unsigned char* as, const unsigned char* bs, int c0, bool one, float sign, floatx16 (&acc)[TM][TN]) {
     auto mul = [](bf16x8 a, bf16x8 b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); };
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -173,7 +174,7 @@ __device__ __forceinline__ void mma32(const unsigned char* as, const unsigned ch
 #pragma unroll
             for (int h = 0; h < 2; ++h) top = mul(a[0][h], b[0][h], top);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] += t[r] + top[r];
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = fmaf(t[r] + top[r], sign, acc[i][j][r]);
             pin(acc[i][j]);
         }
     }
@@ -664,6 +665,9 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
             if (BN % 64 == 0 || trow + 64 * r < BN) put_split8<PLANE>(bput + (kt & 1) * 3 * PLANE + 64 * 64 * r, v);
         }
     };
+    // What the matrix unit cuts off has always the same sign.  It is nothing beside the rounding of one result, but a bias gradient adds
+    // up the results of 10^5..10^7 rows: every other 16 rows are multiplied as -A, and their sums subtracted.
+    auto odd_rows = [&](int i) { return ((wave * TM + i) & 1) != 0; };
     bf16x8 a[TM][3];
     auto split_a = [&](int kt) {
         const int left = left_of(kt);
@@ -684,6 +688,7 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
                     auto keep = [&](uint32_t x, int q) { return have >= q + 2 ? x : have == q + 1 ? x & 0xFFFFu : 0u; };
                     w = make_uint4(keep(w.x, 0), keep(w.y, 2), keep(w.z, 16), keep(w.w, 18));
                 }
+                if (odd_rows(i)) w = make_uint4(w.x ^ 0x80008000u, w.y ^ 0x80008000u, w.z ^ 0x80008000u, w.w ^ 0x80008000u);
                 a[i][0] = a[i][1] = a[i][2] = __builtin_bit_cast(bf16x8, w);
             } else {
                 float v[8];
@@ -691,6 +696,10 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
                 if (zero) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) v[t] = 0.f;
+                }
+                if (odd_rows(i)) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) v[t] = -v[t];
                 }
                 uint4 hi, mid, lo;
                 split8(v, hi, mid, lo);
@@ -735,7 +744,8 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
             }
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-                acc[i][j] += t[i] + mfma16(b[j & 1][0], a[i][0], floatx4{0.f, 0.f, 0.f, 0.f});
+                const floatx4 sum = t[i] + mfma16(b[j & 1][0], a[i][0], floatx4{0.f, 0.f, 0.f, 0.f});
+                acc[i][j] = odd_rows(i) ? acc[i][j] - sum : acc[i][j] + sum;
                 pin(acc[i][j]);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1139,12 +1149,9 @@ __global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArg
     const bool bf16 = is_a && a_one;
     const int32_t* const rows = (GATHER && is_a && !a2) ? g.a_rows : nullptr;
     const bool do_cs = cs_out != nullptr && ka0 == 0 && !op2;
-    // The matrix unit cuts the aligned terms of a sum off below its last bit, towards minus infinity: a bias of a few
-    // thousandths of a unit in the last place per instruction, the same sign everywhere.  It is nothing beside the rounding
-    // of one accumulator, but it would add up over the slices of a long reduction (10^6 rows: 3 times the error of plain
-    // fp32).  Every other slice therefore sums -A^T B and stores the negative of that, so that the biases cancel.
-    const uint32_t flip = (split & 1) ? 0x80000000u : 0u;
-
+    // What the matrix unit cuts off has always the same sign, which would add up over the tiles of a long reduction: every other tile is
+    // multiplied as -A^T B and subtracted.
+    uint32_t flip = 0;                                     // of the staged tile
     floatx16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -1235,9 +1242,10 @@ __global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArg
         for (int64_t mt = m_begin; mt < m_end; mt += BK) {
             const bool more = mt + BK < m_end;
             if (more) fetch(mt + BK);
-            mma32<TM, TN, PLANE_A, PLANE_B, sizeof(AT) == 2>(ap0, bp0, c0, a_one, acc);
+            mma32<TM, TN, PLANE_A, PLANE_B, sizeof(AT) == 2>(ap0, bp0, c0, a_one, flip ? -1.f : 1.f, acc);
             __syncthreads();
             if (more) {
+                flip ^= 0x80000000u;
                 stage();
                 __syncthreads();
             }
@@ -1248,12 +1256,6 @@ __global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArg
     // columns follow the first's N columns (dual = 2).  Direct output: out2 is the second matrix.
     float* o = (op2 && out2 ? out2 : out) + (int64_t)split * out_split_stride;
     if (op2 && !out2) o += a2 ? (int64_t)g.K * out_ld : (int64_t)g.N;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = __uint_as_float(__float_as_uint(acc[i][j][r]) ^ flip);
     // (an own copy of the thread's number: what is derived from it here need not be kept in registers during the loop above)
     int tid_e = tid;
     asm volatile("" : "+v"(tid_e));

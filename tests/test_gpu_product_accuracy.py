@@ -94,3 +94,25 @@ def test_many_rows(g, kind):
     got, want = tn(g, A, B)
     n = 123 / 3 / 256 + 16 / 3 / 16 + 16 / 3 if kind == "uniform" else 3 + 123 / 2 + 16 / 2 + 16 / 2
     assert rms(got - want) <= 1.25 * ROUND * math.sqrt(n) * rms(want)
+
+
+@pytest.mark.parametrize("way,M,K,N", [("nt", 1_000_000, 256, 16), ("nt", 400_000, 32, 64), ("tn", 128, 1024, 1024), ("tn", 96, 1000, 1024)])
+def test_errors_have_no_sign(g, way, M, K, N):
+    """Column sums over many rows (bias gradients) add up the errors of the results: their mean has to vanish, to five times what the
+    mean of that many independent errors has by chance, and 1/2000 of half a unit for the pairing of rows and tiles with opposite signs."""
+    A, B = values("normal", M, K, 7), values("normal", *((N, K) if way == "nt" else (M, N)), 8)
+    err, total = torch.zeros((), device=DEV, dtype=torch.float64), 0.0
+    squares = torch.zeros((), device=DEV, dtype=torch.float64)
+    if way == "nt":
+        got = torch.empty(M, N, device=DEV)
+        g.grp_gemm_nt(M, N, K, A, K, g.DTYPE_FP32, B, K, got, N)
+        for lo in range(0, M, 100_000):
+            want = A[lo:lo + 100_000].double() @ B.double().T
+            e = got[lo:lo + 100_000].double() - want
+            err, squares, total = err + e.sum(), squares + e.pow(2).sum(), total + float(want.pow(2).sum())
+    else:
+        got, want = tn(g, A, B)
+        err, squares, total = (got - want).sum(), (got - want).pow(2).sum(), float(want.pow(2).sum())
+    n = got.numel()
+    size = math.sqrt(total / n)
+    assert abs(float(err)) / n <= 5 * math.sqrt(float(squares) / n / n) + U / 2000 * size
