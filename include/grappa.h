@@ -14,7 +14,9 @@
  * General conventions
  *   - Pointers marked DEV are device (HBM) addresses, HOST are host addresses.  The
  *     caller owns every buffer it passes; the library owns only the opaque handles it
- *     returns and frees them in *_destroy.
+ *     returns and frees them in *_destroy.  Device memory that destroyed handles and finished builds leave is kept for
+ *     the next builds while another handle lives on that GPU: at most 1/64 of its memory.  It goes back to the runtime with the
+ *     GPU's last handle, when 64 later allocations had no use for it, when an allocation fails, or by grp_release_memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls are
  *     asynchronous on that stream and do not synchronise it unless stated otherwise
  *     (the builders grp_partition*, grp_chunks_build*, grp_epoch_seeds and the inspection calls do;
@@ -202,6 +204,10 @@ grp_status grp_partition_from_csr(const int64_t* rowptr, const int32_t* col, int
 
 grp_status grp_partition_view(const grp_partition_t* part, grp_partition_view_t* view /*HOST*/);
 grp_status grp_partition_destroy(grp_partition_t* part);   /* NULL is a no-op */
+
+/* Gives the memory that the library keeps for later builds on the current GPU (see the conventions above) back to the
+ * runtime now.  Waits for the device; not while a stream is being captured.  Errors: GRP_EHIP.            */
+grp_status grp_release_memory(void);
 
 /* ------------------------------------------------------------------ model */
 

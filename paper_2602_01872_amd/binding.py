@@ -92,6 +92,7 @@ def load() -> C.CDLL:
         "grp_partition_from_chunks": [vp, i32, i32, vp, C.POINTER(vp)],
         "grp_partition_base_mask": [vp, C.POINTER(vp)],
         "grp_partition_destroy": [vp],
+        "grp_release_memory": [],
         "grp_step_workspace_bytes": [vp, C.POINTER(ModelDesc), C.POINTER(StepOpts), C.POINTER(sz)],
         "grp_step_activation": [vp, C.POINTER(ModelDesc), C.POINTER(StepOpts), vp, sz, i32, C.POINTER(vp), C.POINTER(i64)],
         "grp_step_block": [vp, C.POINTER(ModelDesc), C.POINTER(StepOpts), vp, sz, i32, C.POINTER(BlockView)],
@@ -522,6 +523,11 @@ def grp_gemm_tn(M, K, N, A, lda, a_dtype, B, ldb, Cm, ldc, workspace, stream=Non
                               _stream(stream)))
 
 
+def grp_release_memory():
+    """Gives back the device memory that the library keeps for later builds on the current GPU."""
+    _check(load().grp_release_memory())
+
+
 def grp_set_slice_policy(min_nodes: int = 1 << 19, min_long_edge_percent: int = 25):
     _check(load().grp_set_slice_policy(min_nodes, min_long_edge_percent))
 
@@ -552,7 +558,7 @@ def read_stats(stats: torch.Tensor) -> np.ndarray:
 
 def exported_symbols():
     return ["grp_last_error", "grp_partition", "grp_node_owners", "grp_epoch_seeds", "grp_gather_rows", "grp_partition_weighted", "grp_partition_weights", "grp_partition_from_local_coo", "grp_partition_from_csr", "grp_partition_view",
-            "grp_partition_destroy", "grp_chunks_build", "grp_chunks_build_assigned", "grp_chunks_destroy", "grp_partition_from_chunks",
+            "grp_partition_destroy", "grp_release_memory", "grp_chunks_build", "grp_chunks_build_assigned", "grp_chunks_destroy", "grp_partition_from_chunks",
             "grp_partition_base_mask", "grp_partition_halo", "grp_param_count", "grp_step_workspace_bytes", "grp_step_activation", "grp_step_block", "grp_train_step",
             "grp_aggregate", "grp_aggregate_ptrs", "grp_optimizer_step", "grp_spmm", "grp_spmm_workspace_bytes", "grp_spmm_static", "grp_gemm_nn", "grp_gemm_nt", "grp_gemm_tn_workspace_bytes", "grp_gemm_tn",
             "grp_set_slice_policy", "grp_sweep_chunk", "grp_super_epoch_epochs", "grp_controller_create", "grp_controller_observe", "grp_controller_observe_stats", "grp_controller_end_epoch", "grp_controller_state", "grp_controller_destroy", "grp_profile_enable", "grp_profile_report"]

@@ -64,6 +64,7 @@ struct ProfScope {
 // As hipMalloc / hipFree, from a bounded cache of freed blocks.
 hipError_t pool_alloc(void** p, size_t bytes);
 void pool_free(void* p);
+hipError_t pool_release();         // gives back what is kept on the current device
 
 // ---------------------------------------------------------------- partition handle
 }  // namespace grp

@@ -75,13 +75,15 @@ void prof_end(hipStream_t st) {
 //     was queued before its release, on any stream, can still use it.
 //   - A request takes the smallest ready block of at most 1.25 times its size.
 //   - At most 1/64 of the device's memory is kept; the block that was freed longest ago goes first.  A block that 64 later
-//     requests have passed over is given back, and so is everything kept when an allocation fails.
+//     requests have passed over is given back.  Everything kept is given back when an allocation fails, when the last block in use on
+//     the device is freed (no handle is left there), and by grp_release_memory.
 //   - One cache per device, one lock.
 namespace {
 struct PoolBlock { void* p; size_t bytes; uint64_t freed_at; bool pending; };
 struct Pool {
     std::vector<PoolBlock> kept;                 // in the order they were freed
     size_t kept_bytes = 0, bound = 0;
+    int64_t live = 0;                            // blocks in use
     uint64_t clock = 0;                          // requests so far
 };
 std::mutex g_pool_mu;
@@ -92,6 +94,9 @@ void pool_drop(Pool& pool, size_t i) {           // give a kept block back to th
     (void)hipFree(pool.kept[i].p);
     pool.kept_bytes -= pool.kept[i].bytes;
     pool.kept.erase(pool.kept.begin() + (long)i);
+}
+void pool_drop_all(Pool& pool) {
+    while (!pool.kept.empty()) pool_drop(pool, pool.kept.size() - 1);
 }
 }  // namespace
 
@@ -130,15 +135,16 @@ hipError_t pool_alloc(void** out, size_t bytes) {
         for (PoolBlock& b : pool.kept) b.pending = false;
     }
     while (!pool.kept.empty() && pool.clock - pool.kept.front().freed_at > 64) pool_drop(pool, 0);
-    if (*out) return hipSuccess;
+    if (*out) { ++pool.live; return hipSuccess; }
     hipError_t r = hipMalloc(out, want ? want : 256);
     if (r != hipSuccess && !pool.kept.empty()) {
         (void)hipGetLastError();
-        while (!pool.kept.empty()) pool_drop(pool, 0);
+        pool_drop_all(pool);
         r = hipMalloc(out, want ? want : 256);
     }
     if (r != hipSuccess) { *out = nullptr; return r; }
     g_pool_live[*out] = {dev, want ? want : 256};
+    ++pool.live;
     return hipSuccess;
 }
 
@@ -151,6 +157,11 @@ void pool_free(void* p) {
     const size_t bytes = it->second.second;
     g_pool_live.erase(it);
     Pool& pool = g_pools[dev];
+    if (--pool.live == 0) {
+        (void)hipFree(p);
+        pool_drop_all(pool);
+        return;
+    }
     if (pool.bound == 0) {
         size_t free_b = 0, total = 0;
         pool.bound = hipMemGetInfo(&free_b, &total) == hipSuccess && total ? total / 64 : 1;
@@ -158,6 +169,15 @@ void pool_free(void* p) {
     pool.kept.push_back({p, bytes, pool.clock, true});
     pool.kept_bytes += bytes;
     while (pool.kept_bytes > pool.bound) pool_drop(pool, 0);
+}
+
+hipError_t pool_release() {
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(g_pool_mu);
+    pool_drop_all(g_pools[dev]);
+    return hipSuccess;
 }
 
 // One helper stream (default priority, not synchronising with the legacy stream) and its events per caller
@@ -193,6 +213,11 @@ SideLane* side_lane(hipStream_t main) {
 }  // namespace grp
 
 extern "C" const char* grp_last_error(void) { return grp::g_err.c_str(); }
+
+extern "C" grp_status grp_release_memory(void) {
+    GRP_HIP(grp::pool_release());
+    return GRP_OK;
+}
 
 extern "C" grp_status grp_profile_enable(int32_t on) {
     std::lock_guard<std::mutex> lk(grp::g_prof_mu);
