@@ -279,7 +279,7 @@ __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t
 // are the heavy ones, so they start first); the others take the rows of at most `long_thr`
 // edges, one group per row.  One launch instead of two keeps the few chunk workgroups from
 // running on an otherwise idle chip.
-// S groups share a row (see spmm_groups for the choice); their sums are added in a fixed butterfly.
+// S groups share a row (see spmm_share for the choice); their sums are added in a fixed butterfly.
 template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, int64_t n_rows, int64_t long_thr,
@@ -616,6 +616,9 @@ __global__ __launch_bounds__(256) void spmm_rows_scalar_kernel(
     }
 }
 
+// Whether a launch of n_chunks workgroups and of rows with so many lanes each holds fewer than 2^32 work-items, which is the limit.
+static bool spmm_fits(int64_t n_rows, int64_t n_chunks, int lanes) { return (n_chunks + cdiv(n_rows, 256 / lanes)) * 256 < ((int64_t)1 << 32); }
+
 // Groups that may share a row of G lanes' width: four, as far as a wavefront holds them.
 constexpr int SPMM_GROUPS(int G) { return G >= 64 ? 1 : G == 32 ? 2 : 4; }
 // Whether they do.  A lone group walks the longest unsplit row of a small graph while the chip waits, and a wavefront of many narrow
@@ -626,11 +629,12 @@ constexpr int SPMM_GROUPS(int G) { return G >= 64 ? 1 : G == 32 ? 2 : 4; }
 //   3e5 rows, 3.25: F = 8 35 -> 28, F = 16 44 -> 40, but F = 32 52 -> 60, F = 47 63 -> 94, F = 100 91 -> 108
 //   1e5 rows, 14: F = 100 78 -> 75, F = 47 58 -> 56 (uniform degrees: 45 -> 49), bf16 F = 128 73 -> 75
 // (before: at F = 8 these were 30, 36, 354 and 56 us.)
-static bool spmm_share(const SpmmArgs& a, int G, int S) {
-    if (cdiv(a.n_rows, 256 / (G * S)) >= ((int64_t)3 << 22)) return false;      // (a launch holds fewer than 2^32 work-items)
-    const int64_t waves = a.n_rows * G / 64;               // with one group per row
-    if (G <= 2 || waves <= 2048 || (G <= 4 && a.nnz >= 2 * a.n_rows)) return true;
-    return a.nnz >= 8 * a.n_rows && (G <= 8 || waves <= (G == 32 ? 65536 : 8192));
+// n_chunks: workgroups that the launch holds besides those of its rows.
+bool spmm_share(int64_t n_rows, int64_t nnz, int64_t n_chunks, int G, int S) {
+    if (!spmm_fits(n_rows, n_chunks, G * S)) return false;
+    const int64_t waves = n_rows * G / 64;                 // with one group per row
+    if (G <= 2 || waves <= 2048 || (G <= 4 && nnz >= 2 * n_rows)) return true;
+    return nnz >= 8 * n_rows && (G <= 8 || waves <= (G == 32 ? 65536 : 8192));
 }
 
 template <typename XT, int G, int NJ>
@@ -693,7 +697,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         // bf16 rows of whole 16-byte units: eight columns per lane, half the lanes per row (twice the rows per wavefront)
         if (a.F % 8 == 0 && a.ldx % 8 == 0 && ((uintptr_t)a.X % 16) == 0 && !a.self_term) {
             constexpr int GW = G / 2, S = SPMM_GROUPS(GW);
-            if (S > 1 && spmm_share(a, GW, S)) {
+            if (S > 1 && spmm_share(a.n_rows, a.nnz, n_chunks, GW, S)) {
                 if (a.val) rows(spmm_rows_kernel<XT, GW, S, 2, true, true>, GW * S);
                 else rows(spmm_rows_kernel<XT, GW, S, 2, false, true>, GW * S);
             } else if (a.val) rows(spmm_rows_kernel<XT, GW, 1, 2, true, true>, GW);
@@ -703,7 +707,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
     }
     if (!rows_done) {
         constexpr int S = SPMM_GROUPS(G);
-        if (S > 1 && spmm_share(a, G, S)) {
+        if (S > 1 && spmm_share(a.n_rows, a.nnz, n_chunks, G, S)) {
             if (a.val) rows(spmm_rows_kernel<XT, G, S, NJ, true>, G * S);
             else rows(spmm_rows_kernel<XT, G, S, NJ, false>, G * S);
         } else if (a.val) rows(spmm_rows_kernel<XT, G, 1, NJ, true>, G);
@@ -728,7 +732,7 @@ static grp_status dispatch(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_
         while (g < f4 && g < 64) g <<= 1;
         const LongRows* lr = a.long_rows;
         const int64_t chunks = lr && lr->n_long > 0 && lr->n_tasks == 0 ? lr->n_chunks : 0;
-        if ((chunks + cdiv(a.n_rows, 256 / g)) * 256 >= ((int64_t)1 << 32))
+        if (!spmm_fits(a.n_rows, chunks, g))
             return fail(GRP_EUNSUPPORTED, "spmm: %lld rows of %d columns exceed one launch", (long long)a.n_rows, a.F);
     }
     if (f4 <= 1) launch_one<XT, 1, 1>(a, ep, st);
