@@ -919,10 +919,35 @@ size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K) {
     return (size_t)(cdiv(K, BK) + 1) * 3 * round_up(N, 128) * 64;      // (two products round their k up one by one)
 }
 
-// Tile choice (measured on MI355X at M = 3e5; the nt path adds a 128 x 96 tile for 64 < N <= 96,
-// e.g. two stacked 47-wide weight blocks): 128 x 128 output tiles at three workgroups per
-// CU beat 128 x 256 at one; a 32-deep single-buffered k-tile is best for long reductions, a
-// 16-deep double-buffered one wastes less on short or ragged K.
+// Output tiles of an NT product: 128 rows by 128, 96, 64 or 32 columns, whichever covers the columns with the least to spare, or 64 x 64.
+struct NtPlan {
+    int tile_m, tile_n;
+    int n_all;               // columns that the tiles cover
+    size_t planes_need;
+    bool pre;                // B is split once, into a.planes
+};
+static NtPlan nt_plan(const GemmNNArgs& a, int n_eff) {
+    NtPlan p;
+    p.tile_m = 128;
+    p.tile_n = n_eff > 96 ? 128 : n_eff > 64 ? 96 : n_eff > 32 ? 64 : 32;
+    // A product whose 128-row tiles would leave half the chip idle (mini-batch blocks) is cut into
+    // 64 x 64 tiles instead: four times the workgroups, each a quarter of the work.
+    // (an upper bound of M that the device will cut down counts half: sampled blocks fill about that much)
+    const int64_t m_plan = a.M_dev ? (a.M + 1) / 2 : a.M;
+    // A product with almost no reduction (K + K2 <= 64) is its epilogue: eight resident 64 x 64 workgroups per CU
+    // overlap their loads and stores better than three of 128 x 128 (K = 16 + 16, N = 128 over 1.7e7 rows: 3.73 -> 3.32 ms).
+    if (n_eff > 32 && (cdiv(m_plan, 128) * cdiv(n_eff, p.tile_n) < 384 || a.K + a.K2 <= 64)) p.tile_m = p.tile_n = 64;
+    // (W + the attention columns: 260 columns are three tiles of 96 with 28 to spare, of 128 with 124)
+    else if (n_eff > 128 && round_up(n_eff, 96) < round_up(n_eff, 128)) p.tile_n = 96;
+    // Both k tilings and the padding fit what gemm_planes_bytes reserved for this N and K + K2.
+    p.n_all = (int)cdiv(n_eff, p.tile_n) * p.tile_n;
+    p.planes_need = (size_t)(cdiv(a.K, BK) + cdiv(a.K2, BK)) * 3 * p.n_all * 64;
+    p.pre = p.tile_m == 128 && p.tile_n >= 64 && a.planes && cdiv(m_plan, 128) >= NT_PRE_SLABS && p.planes_need <= a.planes_bytes;
+    return p;
+}
+
+// The fp32 kernel's tiles (measured at M = 3e5): 128 x 128 output tiles at three workgroups per CU beat 128 x 256 at one; a 32-deep
+// single-buffered k-tile is best for long reductions, a 16-deep double-buffered one wastes less on short or ragged K.
 template <typename AT, bool VEC>
 static void nn_pick(const GemmNNArgs& a, hipStream_t st) {
     const int n_eff = a.zero_pad_to > a.N ? a.zero_pad_to : a.N;
@@ -960,12 +985,12 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const bool ok = small && (veca || a.K >= 4) && a.ldbt % 4 == 0 && a.ldbt >= round_up(a.K, 4) && (uintptr_t)a.Bt % 16 == 0 &&
                         (a.K2 == 0 || (a.Bt2 && a.ldbt2 % 4 == 0 && a.ldbt2 >= round_up(a.K2, 4) && (uintptr_t)a.Bt2 % 16 == 0));
         const int n_eff = a.zero_pad_to > a.N ? a.zero_pad_to : a.N;
-        // one profiling name per kernel variant, so that the names line up with a kernel trace
+        const NtPlan p = nt_plan(a, n_eff);
+        // One profiling name per tile shape and element type of the kernels, and per place where B is split, as in a kernel trace (a
+        // product with planes includes the launch that makes them).
         char pname[64];
-        snprintf(pname, sizeof pname, "gemm_%s_%s_%s", ok ? "nt" : "nn", a.a_bf16 ? "bf16a" : "f32",
-                 ok ? (a.M > 0 && n_eff > 32 && (cdiv(a.M_dev ? (a.M + 1) / 2 : a.M, 128) * cdiv(n_eff, n_eff > 96 ? 128 : n_eff > 64 ? 96 : 64) < 384 || a.K + a.K2 <= 64)
-                           ? "64x64" : n_eff > 96 ? "128x128" : n_eff > 64 ? "128x96" : "128x64")
-                    : (n_eff > 64 ? "128x128" : n_eff > 32 ? "128x64" : "128x32"));
+        snprintf(pname, sizeof pname, "gemm_%s_%s_%dx%d%s", ok ? "nt" : "nn", a.a_bf16 ? "bf16a" : "f32", ok ? p.tile_m : 128,
+                 ok ? p.tile_n : n_eff > 64 ? 128 : n_eff > 32 ? 64 : 32, ok && p.pre ? "_planes" : "");
         ProfScope ps(pname, st, nn_flops, nn_bytes);
         if (!ok) {                                       // slow, always-safe kernel
             if (a.a_bf16) nn_pick<__hip_bfloat16, false>(a, st); else nn_pick<float, false>(a, st);
@@ -975,26 +1000,12 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         GemmNNArgs t = a;
         t.a_tight = veca ? 0 : 1;
         const bool irreg = t.a_tight || a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
-        int tile_n = n_eff > 96 ? 128 : n_eff > 64 ? 96 : n_eff > 32 ? 64 : 32;
-        // A product whose 128-row tiles would leave half the chip idle (mini-batch blocks) is cut into
-        // 64 x 64 tiles instead: four times the workgroups, each a quarter of the work.
-        // (an upper bound of M that the device will cut down counts half: sampled blocks fill about that much)
-        const int64_t m_plan = a.M_dev ? (a.M + 1) / 2 : a.M;
-        // A product with almost no reduction (K + K2 <= 64) is its epilogue: eight resident 64 x 64 workgroups per CU
-        // overlap their loads and stores better than three of 128 x 128 (K = 16 + 16, N = 128 over 1.7e7 rows: 3.73 -> 3.32 ms).
-        const bool small_tiles = n_eff > 32 && (cdiv(m_plan, 128) * cdiv(n_eff, tile_n) < 384 || a.K + a.K2 <= 64);
-        if (small_tiles) tile_n = 64;
-        // (W + the attention columns: 260 columns are three tiles of 96 with 28 to spare, of 128 with 124)
-        else if (n_eff > 128 && round_up(n_eff, 96) < round_up(n_eff, 128)) tile_n = 96;
-        const int64_t slabs = round_up(cdiv(a.M, small_tiles ? 64 : 128), NXCD);
-        const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, tile_n));
-        // Both k tilings and the padding fit what gemm_planes_bytes reserved for this N and K + K2.
-        const int n_all = (int)cdiv(n_eff, tile_n) * tile_n;
-        const size_t planes_need = (size_t)(cdiv(a.K, BK) + cdiv(a.K2, BK)) * 3 * n_all * 64;
-        const bool pre = !small_tiles && tile_n >= 64 && a.planes && cdiv(m_plan, 128) >= NT_PRE_SLABS && planes_need <= a.planes_bytes;
+        const int64_t slabs = round_up(cdiv(a.M, p.tile_m), NXCD);
+        const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, p.tile_n));
+        const bool pre = p.pre;
         if (pre)
-            hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)cdiv((int64_t)planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
-                               a.ldbt2, a.K2, a.N, n_all, a.planes);
+            hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
+                               a.ldbt2, a.K2, a.N, p.n_all, a.planes);
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
         constexpr bool P_ = TM_ == 2 && TN_ >= 4;                                                                          \
@@ -1007,10 +1018,10 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
     do {                                                                                                                   \
         if (a.a_bf16) GRP_NT_LAUNCH2(__hip_bfloat16, TM_, TN_); else GRP_NT_LAUNCH2(float, TM_, TN_);                      \
     } while (0)
-        if (small_tiles) GRP_NT_LAUNCH(1, 4);
-        else if (tile_n == 128) GRP_NT_LAUNCH(2, 8);
-        else if (tile_n == 96) GRP_NT_LAUNCH(2, 6);
-        else if (tile_n == 64) GRP_NT_LAUNCH(2, 4);
+        if (p.tile_m == 64) GRP_NT_LAUNCH(1, 4);
+        else if (p.tile_n == 128) GRP_NT_LAUNCH(2, 8);
+        else if (p.tile_n == 96) GRP_NT_LAUNCH(2, 6);
+        else if (p.tile_n == 64) GRP_NT_LAUNCH(2, 4);
         else GRP_NT_LAUNCH(2, 2);
 #undef GRP_NT_LAUNCH2
 #undef GRP_NT_LAUNCH

@@ -1,0 +1,31 @@
+"""The profiler names a dense product after the kernel variant that ran."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("M,N,K,bf16,name", [
+    (70_000, 256, 96, False, "gemm_nt_f32_128x128"),
+    (70_000, 260, 96, False, "gemm_nt_f32_128x96"),       # three tiles of 96 columns, not of 128
+    (70_000, 150, 96, True, "gemm_nt_bf16a_128x96"),
+    (70_000, 95, 96, False, "gemm_nt_f32_128x96"),
+    (70_000, 64, 96, False, "gemm_nt_f32_128x64"),
+    (70_000, 20, 96, False, "gemm_nt_f32_128x32"),
+    (70_000, 256, 64, False, "gemm_nt_f32_64x64"),        # almost no reduction
+    (2_000, 256, 96, False, "gemm_nt_f32_64x64"),         # too few rows to fill the chip
+    (2_000, 256, 3, False, "gemm_nt_f32_64x64"),
+])
+def test_dense_product_names(M, N, K, bf16, name):
+    import paper_2602_01872_amd as g
+    ld = (K + 3) // 4 * 4
+    A = torch.ones(M, ld, device=DEV, dtype=torch.bfloat16 if bf16 else torch.float32)
+    B, C = torch.ones(N, ld, device=DEV), torch.empty(M, N, device=DEV)
+    g.grp_profile_enable(1)
+    try:
+        g.grp_gemm_nt(M, N, K, A, ld, g.DTYPE_BF16 if bf16 else g.DTYPE_FP32, B, ld, C, N)
+        torch.cuda.synchronize()
+        assert list(g.grp_profile_report()) == [name]
+    finally:
+        g.grp_profile_enable(0)
