@@ -104,3 +104,25 @@ def test_activations_over_many_rows(g, dims):
     cc = torch.arange(dims[1]).repeat(odd.numel()).numpy()
     got = torch.as_tensor(g.read_activation(part, model, opts, ws, 0, rr, cc)).view(odd.numel(), dims[1])
     assert torch.equal(got, want.expand_as(got).to(got.dtype))
+
+
+@pytest.mark.parametrize("K", [1, 40])
+def test_largest_floats(g, K):
+    """Numbers whose first bf16 would round up to infinity, and sums of planes that pass the largest float, keep their finite products."""
+    M, N, big = 70, 24, torch.finfo(torch.float32).max
+    A = torch.zeros(M, (K + 3) // 4 * 4, device=DEV)
+    A[:, 0] = torch.tensor([big, -big, big * (1 - 2.0 ** -20), 1.0, 1e30, -1e-30, 2.0 ** 127], device=DEV).repeat(10)
+    W = torch.zeros(N, A.shape[1], device=DEV)
+    W[:, 0] = torch.tensor([1.0, -1.0, 0.5, 1 / 3], device=DEV).repeat(6)
+    want = A[:, :1].double() * W[:, 0].double()[None, :]
+    C = torch.full((M, N), 7.0, device=DEV)
+    g.grp_gemm_nt(M, N, K, A, A.shape[1], g.DTYPE_FP32, W, W.shape[1], C, N)
+    assert float(((C.double() - want) / want).abs().max()) <= 2.0 ** -23
+    B = torch.zeros(4, N, device=DEV)                        # A^T B over four rows, one of them not zero
+    B[2] = W[:, 0]
+    X = torch.zeros(4, M, device=DEV)
+    X[2] = A[:, 0]
+    ws = torch.empty(max(g.grp_gemm_tn_workspace_bytes(4, M, N), 16), dtype=torch.uint8, device=DEV)
+    C = torch.full((M, N), 7.0, device=DEV)
+    g.grp_gemm_tn(4, M, N, X, M, g.DTYPE_FP32, B, N, C, N, ws)
+    assert float(((C.double() - want) / want).abs().max()) <= 2.0 ** -23
