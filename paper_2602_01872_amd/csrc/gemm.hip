@@ -934,9 +934,14 @@ static NtPlan nt_plan(const GemmNNArgs& a, int n_eff) {
     // 64 x 64 tiles instead: four times the workgroups, each a quarter of the work.
     // (an upper bound of M that the device will cut down counts half: sampled blocks fill about that much)
     const int64_t m_plan = a.M_dev ? (a.M + 1) / 2 : a.M;
-    // A product with almost no reduction (K + K2 <= 64) is its epilogue: eight resident 64 x 64 workgroups per CU
-    // overlap their loads and stores better than three of 128 x 128 (K = 16 + 16, N = 128 over 1.7e7 rows: 3.73 -> 3.32 ms).
-    if (n_eff > 32 && (cdiv(m_plan, 128) * cdiv(n_eff, p.tile_n) < 384 || a.K + a.K2 <= 64)) p.tile_m = p.tile_n = 64;
+    const int64_t wide_tiles = cdiv(m_plan, 128) * cdiv(n_eff, p.tile_n);
+    // A product with almost no reduction (K + K2 <= 64) is its epilogue: eight resident 64 x 64 workgroups per CU overlap their loads
+    // and stores better than three wide ones (K = 32, N = 128 over 3e5 rows: 41 against 46 us; N = 100, 200: 47 against 70, 81 against 119),
+    // until the wide ones, with half the splits of A and no column to spare, come in large numbers (K = 64, N = 128 over
+    // 2e6 rows: 460 against 421 us, masked over 8.4e6 2.55 against 2.26 ms; N = 256 over 1e6 459 against 419 us), or waste the least
+    // (N = 96 over 3e5 rows 43 against 34 us).
+    const bool short_k = a.K + a.K2 <= 64 && !(n_eff % p.tile_n == 0 && (p.tile_n == 96 || (p.tile_n == 128 && wide_tiles >= 4096)));
+    if (n_eff > 32 && (wide_tiles < 384 || short_k)) p.tile_m = p.tile_n = 64;
     // (W + the attention columns: 260 columns are three tiles of 96 with 28 to spare, of 128 with 124)
     else if (n_eff > 128 && round_up(n_eff, 96) < round_up(n_eff, 128)) p.tile_n = 96;
     // Both k tilings and the padding fit what gemm_planes_bytes reserved for this N and K + K2.

@@ -13,7 +13,10 @@ DEV = "cuda"
     (70_000, 95, 96, False, "gemm_nt_f32_128x96"),
     (70_000, 64, 96, False, "gemm_nt_f32_128x64"),
     (70_000, 20, 96, False, "gemm_nt_f32_128x32"),
-    (70_000, 256, 64, False, "gemm_nt_f32_64x64"),        # almost no reduction
+    (70_000, 256, 64, False, "gemm_nt_f32_64x64"),        # almost no reduction,
+    (262_144, 256, 64, False, "gemm_nt_f32_128x128"),     # but tiles in large numbers without a column to spare
+    (262_143, 252, 64, False, "gemm_nt_f32_64x64"),
+    (70_000, 96, 64, False, "gemm_nt_f32_128x96"),
     (2_000, 256, 96, False, "gemm_nt_f32_64x64"),         # too few rows to fill the chip
     (2_000, 256, 3, False, "gemm_nt_f32_64x64"),
 ])
