@@ -29,7 +29,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0          # MI355X published HBM3E bandwidth
-PEAK_FP32_TFLOPS = 2500.0 / 6  # dense fp32 products: six products at the published dense bf16 matrix rate
+PEAK_FP32_TFLOPS = 2500.0 / 8  # dense fp32 products: eight products at the published dense bf16 matrix rate
 
 # HBM bytes per launch of a kernel in a workload come from rocprofv3 --pmc runs of this script (FETCH_SIZE,
 # then WRITE_SIZE, scaled by what the same counter reads for a plain copy); their summaries under profiles/

@@ -517,7 +517,8 @@ grp_status grp_spmm_static(const grp_partition_t* part, int32_t transposed, int3
                            int32_t self_term, int32_t F, const void* X, int64_t ldx, int32_t x_dtype,
                            float* Y, int64_t ldy, void* stream);
 
-/* Dense transforms on the matrix cores (fp32 accumulate; nt and tn take fp32 operands as exact sums of three bf16 numbers):
+/* Dense transforms on the matrix cores (fp32 accumulate; nt and tn take fp32 operands as exact sums of three bf16 numbers, with errors
+ * no larger than fp32 arithmetic has; operands below 2^-110 in size lose what lies below 2^-133):
  *   grp_gemm_nn:  C[M x N] = A[M x K] B[K x N]            (X W, dY W^T with B given transposed)
  *   grp_gemm_tn:  C[K x N] = A[M x K]^T B[M x N]          (X^T dY), reduction over M in a
  *                 fixed order; `workspace` DEV of grp_gemm_tn_workspace_bytes(M,K,N).   */

@@ -483,11 +483,11 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // is masked.
 // IRREG selects the variant with gathered (a_rows), limited (a_valid_rows) or tightly packed (a_tight) A rows.
 // PRE: B comes as planes (g.planes, split_b_kernel below) whose 1 KB runs are copied from memory to LDS without passing
-// through registers.  The loop is bound by issue: matrix and vector instructions of a SIMD's wavefronts add up (96 of the
-// former and about 330 of the latter per k-tile: 1536 + 1320 cycles, 2870 measured), and the split of B, which every slab of
-// 128 rows did again, was a third of the vector instructions.  SAGE step on 3e5 rows (five such products) 3184 -> 3044 us, residual
-// GCN-8 step on 2^20 rows 61.0 -> 59.5 ms, attention step 4282 -> 4180 us (with the 96-column tiles), bf16 share of 8.4e6 rows
-// 41.3 -> 41.0 ms.
+// through registers.  The loop is bound by issue: matrix and vector instructions of a SIMD's wavefronts add up (N = 512, K = 256: per
+// k-tile 128 of the former of 16 cycles and 350 of the latter of 4, 2048 + 1400 cycles; 3360 measured), and the split of B, which
+// every slab of 128 rows does again otherwise, would add to the latter and to the registers.  With and without, in us: the four 128-wide
+// products of a SAGE step on 3e5 rows 1652 and 1997, those of a residual GCN-8 step on 2^20 rows 14.1 and 16.5 ms, a bf16 one over
+// 8.4e6 rows (K = 64 + 64) 2.74 and 3.30 ms.
 // One element of the product, added up in plain fp32 along k.
 template <typename AT>
 __device__ __forceinline__ float nt_plain(const GemmNNArgs& g, int64_t m, int n) {
@@ -1062,10 +1062,10 @@ static TnPlan tn_plan(int64_t M, int K, int N, int products = 1) {
     p.bk_tile = (K <= 64 && p.bn_tile >= 64) ? 64 : 128;      // a short K fills a 64-row tile
     p.tiles_k = (int)cdiv(K, p.bk_tile);
     p.tiles_n = (int)cdiv(N, p.bn_tile);
-    // Products over very many rows are streams (a few output tiles, each workgroup a long run of rows): they want more
-    // loads in flight than one round of workgroups holds, and the partial tiles cost nothing beside 10^7 rows
-    // (K = 128, N = 16 over 1.7e7 rows: 3.84 -> 2.88 ms; bf16 K = 64 + 64, N = 128: 5.9 -> 5.2 ms; at 3e5 rows four times
-    // the slices cost 4 %).
+    // Products over very many rows are cut into up to eight times the slices: the chains of partial sums get that much shorter (at 256
+    // slices of 1.7e7 rows an accumulator is rounded 2000 times), and the partial tiles cost nothing beside 10^7 rows (bf16 K = 64,
+    // N = 128 over 1.7e7 rows 2.34 ms in one round of workgroups, 2.38 in four; K = 128, N = 16 1.95 and 1.94; at 3e5 rows four times the
+    // slices cost 4 %).
     const bool stream = M >= ((int64_t)1 << 23);
     const int target = N_CU * tn_wgs(p.bk_tile * p.bn_tile / 4096);      // (tiles of 32 x 32 per wavefront)
     int64_t s = (stream ? 4 * target : target) / (p.tiles_k * p.tiles_n * products);
