@@ -488,17 +488,17 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // every slab of 128 rows does again otherwise, would add to the latter and to the registers.  With and without, in us: the four 128-wide
 // products of a SAGE step on 3e5 rows 1652 and 1997, those of a residual GCN-8 step on 2^20 rows 14.1 and 16.5 ms, a bf16 one over
 // 8.4e6 rows (K = 64 + 64) 2.74 and 3.30 ms.
-// One element of the product, added up in plain fp32 along k.
+// One element of the product, added up in plain fp32 along k (up to the first NaN: a diverged step has them everywhere).
 template <typename AT>
 __device__ __forceinline__ float nt_plain(const GemmNNArgs& g, int64_t m, int n) {
     const bool zero = g.a_valid_rows > 0 && m >= g.a_valid_rows;       // (such rows of the first A read as zero)
     const AT* const a = (const AT*)g.A + (zero ? 0 : (g.a_rows ? (int64_t)g.a_rows[m] : m) * g.lda);
     const float* const b = g.Bt + (int64_t)n * g.ldbt;
     float s = 0.f;
-    for (int k = 0; k < g.K; ++k) s = fmaf(zero ? 0.f : to_f<AT>(a[k]), b[k], s);
+    for (int k = 0; k < g.K && !isnan(s); ++k) s = fmaf(zero ? 0.f : to_f<AT>(a[k]), b[k], s);
     const float* const a2 = g.A2 + m * g.lda2;
     const float* const b2 = g.Bt2 + (int64_t)n * g.ldbt2;
-    for (int k = 0; k < g.K2; ++k) s = fmaf(a2[k], b2[k], s);
+    for (int k = 0; k < g.K2 && !isnan(s); ++k) s = fmaf(a2[k], b2[k], s);
     return s;
 }
 
@@ -1310,7 +1310,7 @@ __global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArg
             const int ka = row_of(e / (16 * TN), e % 16), c = col_of(e / 16 % TN);
             if (isfinite(v) || ka >= g.K || c >= g.N) continue;
             v = 0.f;
-            for (int64_t m = m_begin; m < m_end; ++m) {
+            for (int64_t m = m_begin; m < m_end && !isnan(v); ++m) {
                 const float x = a2 ? g.A2[m * g.lda2 + ka] : to_f<AT>(((const AT*)g.A)[(g.a_rows ? (int64_t)g.a_rows[m] : m) * g.lda + ka]);
                 v = fmaf(x, b2 ? g.B2[m * g.ldb2 + c] : g.B[m * g.ldb + c], v);
             }
