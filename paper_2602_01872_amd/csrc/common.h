@@ -101,8 +101,6 @@ struct LongRows {
     SliceTask* tasks = nullptr;      // [n_tasks] in processing order (slice-major, rows ascending inside a slice)
     int64_t* row_task = nullptr;     // [n_long+1] first task id of each long row
 };
-// Structures with fewer rows than this keep the chunk schedule (their gathered rows fit the caches anyway).
-grp_status build_slice_tasks(const int64_t* ptr, const int32_t* idx, int64_t n, int64_t nnz, LongRows* lr, hipStream_t st);
 }  // namespace grp
 
 struct grp_partition_s {
@@ -144,6 +142,32 @@ struct grp_chunks_s {
 };
 
 namespace grp {
+
+// The sliced schedules of the handle's long rows, where they pay (slices.hip).  long_edges: the edges of each direction's long rows
+// (negative: counted there).
+grp_status build_slice_tasks(grp_partition_t* h, const int64_t (&long_edges)[2], hipStream_t st);
+
+// Exclusive prefix sum over a workgroup of WAVES full wavefronts; total: of all.  Starts on a barrier.
+template <int WAVES, typename T> __device__ __forceinline__ T block_scan(T v, T* wave_sum /*[WAVES], LDS*/, T& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    T incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+    }
+    __syncthreads();
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        if (w < wave) before += wave_sum[w];
+        all += wave_sum[w];
+    }
+    total = all;
+    return before + incl - v;
+}
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
@@ -387,6 +411,16 @@ grp_status launch_csr_from_sorted_keys(const uint64_t* keys, int64_t nnz, int64_
 // cap_chunks >= nnz / SPMM_CHUNK + cap_long.  scanned: [n + 1] int64 scratch.
 grp_status build_long_rows_device(const int64_t* ptr_dev, int64_t n, LongRows* out, int64_t cap_long, int64_t cap_chunks,
                                   int64_t* scanned, void* scan_tmp, size_t scan_bytes, hipStream_t st);
+
+// ---- CSR and CSC from unordered keys (buckets.hip)
+struct BucketPlan {
+    int row_bits, id_bits;               // of a packed key: row within its bucket, other end
+    int n_buckets;                       // of a direction
+};
+bool bucket_plan(int64_t n, int64_t nnz, BucketPlan* p);      // false: sizes that are not built this way
+size_t bucket_scratch_bytes(const BucketPlan& p, int64_t nnz);
+grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys, uint64_t* packed, void* scratch, int64_t (&long_edges)[2],
+                        hipStream_t st);
 
 // M(x): the SplitMix64 finaliser of x + 0x9E3779B97F4A7C15 (the sampler's and the seed order's hash step)
 __host__ __device__ __forceinline__ uint64_t mixM(uint64_t x) {

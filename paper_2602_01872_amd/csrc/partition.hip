@@ -3,8 +3,9 @@
 // owner(v) = SplitMix64_output(seed, v) mod K.  A partition keeps the edges whose two
 // endpoints it owns, renumbers nodes by ascending global id and stores the edge multiset
 // twice in canonical order: CSR by destination (sources ascending) and CSC by source
-// (destinations ascending).  Canonical order comes from a radix sort of the 64-bit keys
-// (row << 32 | column); equal keys are indistinguishable, so the arrays are unique and can
+// (destinations ascending).  Canonical order comes from a sort of the 64-bit keys (row << 32 | column): by buckets of rows
+// (buckets.hip), or a device-wide radix sort where weights travel with the keys or there are more than 2^22 nodes or 2^26
+// edges.  Equal keys are indistinguishable, so the arrays are unique and can
 // be compared bit for bit.  Everything is integer work: counters use integer atomics only.
 //
 // The device-wide radix sort and prefix sum are rocPRIM's; the hashing, filtering,
@@ -649,10 +650,10 @@ static size_t carve_csr_csc(grp_partition_t* h, bool weighted, int64_t cap_long,
     return b.total();
 }
 
-// Sorts of the bits [begin, end) of 64-bit keys, with a value each if vals is given (temp null: sizes only).  The library merges
-// below 2^20 keys, in two launches per doubling; its digit passes are already faster from SORT_BY_DIGITS_FROM on.
-// Builds from n nodes and E local edges (us): 2e4, 1.6e5 272 -> 265 and 3e4, 2.5e5 330 -> 332 (merged as before); 4e4, 3e5 368 -> 293;
-// 1e5, 7e5 466 -> 364; 1.2e5, 1e6 505 -> 396; 3e5, 3e6 693 -> 544; 1e6, 2e7 2218 -> 1687 (the last two: the transpose's shorter sort).
+// Sorts of the bits [begin, end) of 64-bit keys, with a value each if vals is given (temp null: sizes only), for the builds that
+// buckets.hip does not take.  The library merges below 2^20 keys, in two launches per doubling; its digit passes are already faster
+// from SORT_BY_DIGITS_FROM on (unweighted builds that once came here, us: 3e4, 2.5e5 edges 330 and 332; 4e4, 3e5 368 -> 293; 1e5,
+// 7e5 466 -> 364; 1.2e5, 1e6 505 -> 396).
 template <unsigned long LIMIT>
 static hipError_t sort_bits_as(void* temp, size_t& bytes, uint64_t* in, uint64_t* out, float* vin, float* vout, int64_t count, unsigned begin,
                                unsigned end, hipStream_t st) {
@@ -682,6 +683,14 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
         return fail(GRP_ENOMEM, "device allocation of %zu bytes failed", h->slab_bytes);
     }
     (void)carve_csr_csc(h, vals != nullptr, cap_long, cap_chunks, h->slab, h->slab_bytes);
+    BucketPlan plan;
+    if (!vals && bucket_plan(n, nnz, &plan)) {
+        DevBuf scratch;
+        int64_t long_edges[2];
+        GRP_TRY(scratch.alloc(bucket_scratch_bytes(plan, nnz)));
+        GRP_TRY(bucket_build(h, plan, keys, keys_alt, scratch.p, long_edges, st));
+        return build_slice_tasks(h, long_edges, st);
+    }
     const unsigned id_bits = bits_for(n > 1 ? n : 2);
     // one scratch allocation: the sorts' temporary storage, later the long-row pass's prefix sums
     size_t sort_bytes = 0, transpose_bytes = 0;
@@ -720,11 +729,7 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
     GRP_TRY(build_long_rows(h->rowptr, n, &h->csr_long, cap_long, cap_chunks, scanned, scan_tmp, scan_bytes, st));
     GRP_TRY(build_long_rows(h->colptr, n, &h->csc_long, cap_long, cap_chunks, scanned, scan_tmp, scan_bytes, st));
     GRP_HIP(hipStreamSynchronize(st));
-    if (!vals) {                                          // weighted partitions keep the chunk schedule
-        GRP_TRY(build_slice_tasks(h->rowptr, h->col, n, h->nnz, &h->csr_long, st));
-        GRP_TRY(build_slice_tasks(h->colptr, h->row, n, h->nnz, &h->csc_long, st));
-    }
-    return GRP_OK;
+    return vals ? GRP_OK : build_slice_tasks(h, {-1, -1}, st);      // weighted partitions keep the chunk schedule
 }
 
 static grp_status weighted_build(const int64_t* src, const int64_t* dst, const float* w, int64_t E, NodeSet own,
