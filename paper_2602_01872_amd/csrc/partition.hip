@@ -27,10 +27,31 @@ __device__ __forceinline__ uint64_t splitmix64_output(uint64_t seed, uint64_t in
     return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(256) void owner_flag_kernel(int64_t N, uint32_t K, uint64_t seed, uint32_t part,
-                                                         int32_t* __restrict__ flag) {
+// splitmix64_output(seed, v) mod K == part, without a division: K = 2^rot * odd divides z - part exactly if the product with the
+// inverse of odd (mod 2^64), rotated right by rot, does not exceed (2^64 - 1) / K (Granlund and Montgomery, "Division by invariant
+// integers using multiplication", 1994, section 9).
+struct OwnerTest {
+    uint64_t seed, inv, limit;
+    uint32_t part;
+    int rot;
+    __device__ __forceinline__ bool operator()(int64_t v) const {
+        const uint64_t z = splitmix64_output(seed, (uint64_t)v);
+        uint64_t q = (z - part) * inv;
+        q = (q >> rot) | (q << ((64 - rot) & 63));
+        return z >= part && q <= limit;
+    }
+};
+static OwnerTest owner_test(uint64_t seed, uint32_t K, uint32_t part) {
+    OwnerTest t{seed, 1, ~0ull / K, part, 0};
+    uint64_t odd = K;
+    while ((odd & 1) == 0) { odd >>= 1; ++t.rot; }
+    for (int i = 0; i < 6; ++i) t.inv *= 2 - odd * t.inv;       // Newton: twice the bits each time
+    return t;
+}
+
+__global__ __launch_bounds__(256) void owner_flag_kernel(int64_t N, OwnerTest owned, int32_t* __restrict__ flag) {
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N) flag[v] = (splitmix64_output(seed, (uint64_t)v) % K) == part ? 1 : 0;
+    if (v < N) flag[v] = owned(v) ? 1 : 0;
 }
 
 // owner[v] for every node and (optionally) the number of nodes per partition.
@@ -56,12 +77,6 @@ __global__ __launch_bounds__(256) void node_owners_kernel(int64_t N, uint32_t K,
     }
 }
 
-__global__ __launch_bounds__(256) void scatter_l2g_kernel(int64_t N, const int32_t* __restrict__ flag,
-                                                          const int64_t* __restrict__ pos, int64_t* __restrict__ l2g) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N && flag[v]) l2g[pos[v]] = v;
-}
-
 // Edges e and e + 1 (e even) of an id array with one 16-byte load when the array allows it; `fill` past the end.
 typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void load_edge_pair(const int64_t* __restrict__ p, int64_t e, int64_t E, bool vec, int64_t fill,
@@ -76,16 +91,45 @@ __device__ __forceinline__ void load_edge_pair(const int64_t* __restrict__ p, in
     }
 }
 
-// A node set as a bitmap plus the number of members before each 32-node word: membership and the
-// member's rank (its local id) from two small arrays that stay in the L2 caches (N / 4 bytes in all),
-// where per-node flag and position arrays (12 bytes per node) cost a cache line from HBM per lookup.
+// A node set as a bitmap, every 32-node word beside the number of members before it: membership and the
+// member's rank (its local id) from one small array that stays in the L2 caches (N / 4 bytes in all),
+// where per-node flag and position arrays (12 bytes per node) cost a cache line from HBM per lookup.  What a lookup costs is its line's
+// way from the L2, so a word and its count lie together.
 struct NodeSet {
-    const uint32_t* bits;
-    const int32_t* before;
+    const uint2* words;                  // bits, members before
 };
-__device__ __forceinline__ bool set_has(const NodeSet& s, int64_t v) { return (s.bits[v >> 5] >> (v & 31)) & 1u; }
-__device__ __forceinline__ int32_t set_rank(const NodeSet& s, int64_t v) {
-    return s.before[v >> 5] + __popc(s.bits[v >> 5] & ((1u << (v & 31)) - 1u));
+// The words of the set of the nodes v < N that member(v) holds for, and one empty word after the last; the grid covers their nodes.
+template <typename Member>
+__global__ __launch_bounds__(256) void node_bits_kernel(int64_t N, int64_t n_words, Member member, uint32_t* __restrict__ bits) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const unsigned long long m = __ballot(v < N && member(v));
+    const int64_t w = v >> 5;
+    if ((threadIdx.x & 31) == 0 && w <= n_words) bits[w] = (uint32_t)(m >> (threadIdx.x & 32));
+}
+__global__ __launch_bounds__(256) void count_bits_kernel(const uint32_t* __restrict__ bits, int64_t n_words, unsigned long long* __restrict__ count) {
+    unsigned long long c = 0;
+    for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < n_words; w += (int64_t)gridDim.x * 256) c += __popc(bits[w]);
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
+    if ((threadIdx.x & 63) == 0 && c) atomicAdd(count, c);
+}
+__device__ __forceinline__ bool word_has(const uint2& w, int64_t v) { return (w.x >> (v & 31)) & 1u; }
+__device__ __forceinline__ int32_t word_rank(const uint2& w, int64_t v) { return (int32_t)w.y + __popc(w.x & ((1u << (v & 31)) - 1u)); }
+__device__ __forceinline__ bool set_has(const NodeSet& s, int64_t v) { return word_has(s.words[v >> 5], v); }
+__device__ __forceinline__ int32_t set_rank(const NodeSet& s, int64_t v) { return word_rank(s.words[v >> 5], v); }
+
+// Node v's word, which its first node also puts into the set.
+__device__ __forceinline__ uint2 set_word(const uint32_t* __restrict__ bits, const int32_t* __restrict__ before, int64_t v,
+                                          uint2* __restrict__ words) {
+    const uint2 w = make_uint2(bits[v >> 5], (uint32_t)before[v >> 5]);
+    if ((v & 31) == 0) words[v >> 5] = w;
+    return w;
+}
+__global__ __launch_bounds__(256) void set_nodes_kernel(int64_t N, const uint32_t* __restrict__ bits, const int32_t* __restrict__ before,
+                                                        uint2* __restrict__ words, int64_t* __restrict__ l2g) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v >= N) return;
+    const uint2 w = set_word(bits, before, v, words);
+    if (word_has(w, v)) l2g[word_rank(w, v)] = v;
 }
 
 // ---- weighted partitions: the selected edges are compacted in edge-list order, so that equal
@@ -171,18 +215,6 @@ __global__ __launch_bounds__(256) void ordered_emit_kernel(const int64_t* __rest
             ++slot;
         }
         __syncthreads();                                 // wave_count is reused by the next tile
-    }
-}
-
-// bits[w] = flags of nodes 32w .. 32w+31; the grid covers n_words * 32 nodes
-__global__ __launch_bounds__(256) void pack_bits_kernel(const int32_t* __restrict__ flag, int64_t N, int64_t n_words,
-                                                        uint32_t* __restrict__ bits) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const unsigned long long m = __ballot(v < N && flag[v] != 0);
-    const int64_t w = v >> 5;
-    if ((threadIdx.x & 63) == 0 && w < n_words) {
-        bits[w] = (uint32_t)m;
-        if (w + 1 < n_words) bits[w + 1] = (uint32_t)(m >> 32);
     }
 }
 
@@ -335,109 +367,186 @@ __global__ __launch_bounds__(256) void edge_keys_kernel(const int64_t* __restric
     }
 }
 
-// Both passes in one (unweighted builds): range check, global in-degrees of owned destinations and the keys of
-// the kept edges, written into a buffer of `cap` keys.  counters: [1] += bad ids, [2] += kept edges (the
-// slot cursor).  If the cursor ends above cap the keys are incomplete and the caller runs edge_keys_kernel
-// with a buffer of the exact size (the in-degrees and the count are complete either way).  N >= 1 (the set has a word 0).
-// One edge after another, every lookup waited for the one before it: 62e6 edges, an eighth of the nodes 663 us; in stages
-// of eight 532 us (1.9 TB/s of edges; the read alone would take 190).
-__global__ __launch_bounds__(256) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
-                                                             int64_t E, int64_t N, NodeSet own,
-                                                             unsigned long long* __restrict__ dg,
-                                                             unsigned long long* __restrict__ counters,
-                                                             uint64_t* __restrict__ keys, unsigned long long cap) {
-    constexpr int PER = 8;
+// Both passes in one (unweighted builds): range check, the keys of the kept edges, written into a buffer of `cap` keys, and the local
+// ids of all owned destinations, from which rank_count_kernel counts the global in-degrees.  counters: [1] += bad ids, [2] += kept
+// edges, [3] += local ids (the cursors).  If the kept edges end above cap the keys are incomplete and the caller runs
+// edge_keys_kernel with a buffer of the exact size; local ids past id_cap are counted here, one by one.
+// What sets the time is what is asked of the L2 beside the edges: a membership lookup per edge (a bitmap larger than the L1: a line
+// each) and, worst, the in-degrees' additions, scattered words that are a request each even after a table in LDS (62e6
+// edges, an eighth of the nodes: 547 us with either of a lookup and a computed membership).  So membership is computed (about
+// 290 cycles a wavefront), and a tile's ids leave in ranges of SPAN ids, as neighbouring words; counting a range takes LDS only.
+// (286 us, and 49 for the counts; the read alone would take 190.)
+constexpr int SPAN_BITS = 14;            // 64 KB of counters
+constexpr int SPANS_MAX = 256;           // ranges: partitions of up to 2^22 nodes
+constexpr int SCAN_THREADS = 512;
+constexpr int SCAN_PER = 8;              // edges per thread and tile: their loads are in flight together
+constexpr int SCAN_TILE = SCAN_THREADS * SCAN_PER;
+constexpr int SCAN_GRID = 2048;
+__global__ __launch_bounds__(SCAN_THREADS) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, int64_t E,
+                                                                      int64_t N, NodeSet own, OwnerTest owned, int spans,
+                                                                      unsigned long long* __restrict__ dg, unsigned long long* __restrict__ counters,
+                                                                      uint64_t* __restrict__ keys, unsigned long long cap,
+                                                                      uint32_t* __restrict__ ids, unsigned long long id_cap,
+                                                                      uint32_t* __restrict__ heads /*[tiles][spans + 1]*/) {
+    __shared__ uint32_t buf[SCAN_TILE];
+    __shared__ uint32_t first[SPANS_MAX + 1];
+    __shared__ uint32_t kept, id_total;
+    __shared__ unsigned long long base[2];
     const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
-    __shared__ int32_t slot_key[DG_SLOTS];
-    __shared__ uint32_t slot_count[DG_SLOTS];
-    __shared__ int wave_count[4];
-    __shared__ unsigned long long tile_base;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < DG_SLOTS; i += 256) { slot_key[i] = -1; slot_count[i] = 0u; }
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
     unsigned long long bad = 0;
-    const int64_t n_tiles = (E + 256 * PER - 1) / (256 * PER);
+    const int64_t n_tiles = (E + SCAN_TILE - 1) / SCAN_TILE;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t e0 = tile * (256 * PER) + 2 * tid;
-        int64_t us[PER], vs[PER];
-        if (vec && (tile + 1) * (256 * PER) <= E) {          // (uniform)
+        for (int i = tid; i < spans; i += SCAN_THREADS) first[i] = 0u;
+        if (tid == 0) kept = 0u;
+        const int64_t e0 = tile * SCAN_TILE + 2 * tid;
+        uint32_t u[SCAN_PER], v[SCAN_PER], has = 0;          // bit i: the destination of edge i is owned
+        {
+            int64_t us[SCAN_PER], vs[SCAN_PER];
+            if (vec && (tile + 1) * SCAN_TILE <= E) {        // (uniform)
 #pragma unroll
-            for (int i = 0; i < PER; i += 2) {
-                const i64x2 a = *reinterpret_cast<const i64x2*>(src + e0 + (int64_t)i * 256);
-                const i64x2 b = *reinterpret_cast<const i64x2*>(dst + e0 + (int64_t)i * 256);
-                us[i] = a.x; us[i + 1] = a.y;
-                vs[i] = b.x; vs[i + 1] = b.y;
+                for (int i = 0; i < SCAN_PER; i += 2) {
+                    const i64x2 a = *reinterpret_cast<const i64x2*>(src + e0 + (int64_t)i * SCAN_THREADS);
+                    const i64x2 b = *reinterpret_cast<const i64x2*>(dst + e0 + (int64_t)i * SCAN_THREADS);
+                    us[i] = a.x; us[i + 1] = a.y;
+                    vs[i] = b.x; vs[i + 1] = b.y;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < SCAN_PER; i += 2) {
+                    const int64_t e = e0 + (int64_t)i * SCAN_THREADS;
+                    load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
+                    load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);      // -2: past the end, neither counted nor an error
+                }
             }
-        } else {
 #pragma unroll
-            for (int i = 0; i < PER; i += 2) {
-                const int64_t e = e0 + (int64_t)i * 256;
-                load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-                load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]); // -2: past the end, neither counted nor an error
+            for (int i = 0; i < SCAN_PER; ++i) {
+                const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
+                bad += !ok && vs[i] != -2;
+                u[i] = ok ? (uint32_t)us[i] : 0u;
+                v[i] = ok ? (uint32_t)vs[i] : 0u;
+                has |= (ok && owned(v[i]) ? 1u : 0u) << i;
             }
         }
-        // Eight edges' lookups are requested together, stage by stage; a lane that has no need of one reads word 0 (one line for
-        // all of them).
-        uint32_t word[PER], has = 0, both = 0;               // bit i: the destination, and also the source, of edge i is in the set
-        int32_t rv[PER], ru[PER];
-        uint64_t key[PER];
-        int mine = 0;
+        // The lookups of eight edges are requested together, in two stages; a lane that has no need of one reads word 0 (one line for all
+        // of them).
+        uint2 wv[SCAN_PER], wu[SCAN_PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-            bad += !ok && vs[i] != -2;
-            if (!ok) us[i] = vs[i] = 0;
-            word[i] = own.bits[vs[i] >> 5];
-            has |= (ok ? 1u : 0u) << i;
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if (!((word[i] >> (vs[i] & 31)) & 1u)) has &= ~(1u << i);
+        for (int i = 0; i < SCAN_PER; ++i) {
             const bool in = (has >> i) & 1u;
-            rv[i] = own.before[in ? vs[i] >> 5 : 0] + __popc(word[i] & ((1u << (vs[i] & 31)) - 1u));
-            word[i] = own.bits[in ? us[i] >> 5 : 0];
+            wv[i] = own.words[in ? v[i] >> 5 : 0u];
+            wu[i] = own.words[in ? u[i] >> 5 : 0u];
         }
+        __syncthreads();                                     // the counters are clear
+        uint32_t at[SCAN_PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if ((has >> i) & (word[i] >> (us[i] & 31)) & 1u) both |= 1u << i;
-            ru[i] = own.before[(both >> i) & 1u ? us[i] >> 5 : 0] + __popc(word[i] & ((1u << (us[i] & 31)) - 1u));
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if ((has >> i) & 1u) dg_table_add(slot_key, slot_count, dg, rv[i]);
-            const bool kept = (both >> i) & 1u;
-            key[i] = kept ? ((uint64_t)(uint32_t)rv[i] << 32) | (uint64_t)(uint32_t)ru[i] : ~0ull;
-            mine += kept;
-        }
-        int incl = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += t;
-        }
-        if (lane == 63) wave_count[wave] = incl;
-        __syncthreads();
-        int before = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            if (w < wave) before += wave_count[w];
-            total += wave_count[w];
-        }
-        if (tid == 0) tile_base = total ? atomicAdd(&counters[2], (unsigned long long)total) : 0ull;
-        __syncthreads();
-        unsigned long long slot = tile_base + (unsigned long long)(before + incl - mine);
-#pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (key[i] != ~0ull) {
-                if (slot < cap) keys[slot] = key[i];
-                ++slot;
+        for (int i = 0; i < SCAN_PER; ++i) {
+            if (!((has >> i) & 1u)) continue;
+            v[i] = (uint32_t)word_rank(wv[i], v[i]);
+            at[i] = atomicAdd(&first[v[i] >> SPAN_BITS], 1u);
+            if (word_has(wu[i], u[i])) {
+                u[i] = (uint32_t)word_rank(wu[i], u[i]);
+                has |= (1u << SCAN_PER) << i;                // kept
+                at[i] |= atomicAdd(&kept, 1u) << 16;
             }
-        __syncthreads();                                 // wave_count / tile_base are reused by the next tile
+        }
+        __syncthreads();
+        if (tid < 64) {                                      // the ranges' places in the tile, and the tile's in the arrays
+            constexpr int PER = SPANS_MAX / 64;
+            uint32_t c[PER], sum = 0;
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                c[q] = PER * lane + q < spans ? first[PER * lane + q] : 0u;
+                sum += c[q];
+            }
+            uint32_t incl = sum;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t t = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += t;
+            }
+            const uint32_t total = __shfl(incl, 63, 64);
+            unsigned long long b = 0;
+            if (lane < 2) {
+                const uint32_t want = lane == 0 ? total : kept;
+                if (want) b = atomicAdd(&counters[3 - lane], (unsigned long long)want);
+                base[lane] = b;
+            }
+            if (lane == 0) id_total = total;
+            b = __shfl(b, 0, 64);
+            uint32_t place = incl - sum;
+            auto head = [&](uint32_t x) { return (uint32_t)(b + x < id_cap ? b + x : id_cap); };
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                if (PER * lane + q < spans) {
+                    first[PER * lane + q] = place;
+                    heads[tile * (spans + 1) + PER * lane + q] = head(place);
+                }
+                place += c[q];
+            }
+            if (lane == 0) heads[tile * (spans + 1) + spans] = head(total);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SCAN_PER; ++i) {
+            if ((has >> i) & 1u) buf[first[v[i] >> SPAN_BITS] + (at[i] & 0xFFFFu)] = v[i];
+            if ((has >> (SCAN_PER + i)) & 1u) {
+                const unsigned long long slot = base[1] + (at[i] >> 16);
+                if (slot < cap) keys[slot] = ((uint64_t)v[i] << 32) | (uint64_t)u[i];
+            }
+        }
+        __syncthreads();
+        for (uint32_t x = tid; x < id_total; x += SCAN_THREADS) {
+            if (base[0] + x < id_cap) ids[base[0] + x] = buf[x];
+            else atomicAdd(&dg[buf[x]], 1ull);
+        }
+        __syncthreads();                                     // the arrays in LDS are used anew
     }
-    for (int i = tid; i < DG_SLOTS; i += 256)
-        if (slot_key[i] >= 0) atomicAdd(&dg[slot_key[i]], (unsigned long long)slot_count[i]);
     for (int o = 32; o > 0; o >>= 1) bad += __shfl_down(bad, o, 64);
     if (lane == 0 && bad) atomicAdd(&counters[1], bad);
+}
+
+// dg[i] += how often i is among the tiles' local ids.  A workgroup counts a part of the tiles (blockIdx.y) for one range of ids
+// (blockIdx.x) in LDS and adds its counts to memory as neighbouring words.  A wavefront takes the runs of `at_once` tiles together,
+// whatever their lengths: id j of them lies in the run that a search over the runs' prefix sum finds.
+__global__ __launch_bounds__(1024) void rank_count_kernel(const uint32_t* __restrict__ ids, const uint32_t* __restrict__ heads, int64_t n_tiles,
+                                                          int spans, int at_once, int64_t n, unsigned long long* __restrict__ dg) {
+    __shared__ uint32_t count[1 << SPAN_BITS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < (1 << SPAN_BITS); i += 1024) count[i] = 0u;
+    __syncthreads();
+    for (int64_t t0 = ((int64_t)blockIdx.y * 16 + wave) * at_once; t0 < n_tiles; t0 += (int64_t)gridDim.y * 16 * at_once) {
+        const bool mine = lane < at_once && t0 + lane < n_tiles;
+        const int64_t t = mine ? t0 + lane : t0;
+        const uint32_t b = heads[t * (spans + 1) + blockIdx.x], e = heads[t * (spans + 1) + blockIdx.x + 1];
+        uint32_t end = mine ? e - b : 0u;                    // of the lane's run, in the runs laid end to end
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t x = __shfl_up(end, o, 64);
+            if (lane >= o) end += x;
+        }
+        const uint32_t total = __shfl(end, 63, 64), from = e - end;      // id j of this run is ids[from + j]
+        constexpr int U = 8;
+        for (uint32_t j0 = 0; j0 < total; j0 += 64 * U) {
+            uint32_t id[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const uint32_t j = j0 + q * 64 + lane < total ? j0 + q * 64 + lane : total - 1;
+                int run = 0;                                 // runs that end at or before j
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1)
+                    if (__shfl(end, run + o - 1, 64) <= j) run += o;
+                id[q] = ids[__shfl(from, run, 64) + j];
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (j0 + q * 64 + lane < total) atomicAdd(&count[id[q] & ((1u << SPAN_BITS) - 1u)], 1u);
+        }
+    }
+    __syncthreads();
+    const int64_t id0 = (int64_t)blockIdx.x << SPAN_BITS;
+    for (int i = tid; i < (1 << SPAN_BITS); i += 1024)
+        if (count[i] && id0 + i < n) atomicAdd(&dg[id0 + i], (unsigned long long)count[i]);
 }
 
 // Local edge list: range check + keys in place order.
@@ -569,11 +678,6 @@ struct DevBuf {
         }
         return GRP_OK;
     }
-    template <typename T> T* as() { return (T*)p; }
-};
-
-struct DevView {                          // a typed look at part of an allocation (same accessors as DevBuf)
-    void* p;
     template <typename T> T* as() { return (T*)p; }
 };
 
@@ -735,93 +839,116 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
 static grp_status weighted_build(const int64_t* src, const int64_t* dst, const float* w, int64_t E, NodeSet own,
                                  hipStream_t st, grp_partition_t* h);
 
+// A node set and what building it needs, from one allocation.
+struct SetScratch {
+    unsigned long long* counters;        // [4]; the last: members
+    uint32_t* bits;                      // [n_words + 1]
+    int32_t* before;                     // [n_words + 1]
+    uint2* words;                        // [n_words]
+    char* scan;
+    int64_t n_words;
+    size_t scan_bytes;
+    grp_status alloc(int64_t N, DevBuf& slab) {
+        n_words = cdiv(N > 0 ? N : 1, 32);
+        scan_bytes = scan_temp_bytes(n_words + 1);
+        for (int pass = 0; pass < 2; ++pass) {
+            Bump b(slab.p, 0);
+            counters = b.take<unsigned long long>(4);
+            bits = b.take<uint32_t>((size_t)n_words + 1);
+            before = b.take<int32_t>((size_t)n_words + 1);
+            words = b.take<uint2>((size_t)n_words);
+            scan = b.take<char>(scan_bytes);
+            if (pass == 0) GRP_TRY(slab.alloc(b.total()));
+        }
+        return GRP_OK;
+    }
+};
+// bits and before of the nodes that member(v) holds for, and their number n (waits for it).
+template <typename Member>
+static grp_status build_node_set(int64_t N, Member member, const SetScratch& t, int64_t* n, hipStream_t st) {
+    *n = 0;
+    if (N <= 0) return GRP_OK;
+    hipLaunchKernelGGL(node_bits_kernel<Member>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words, member, t.bits);
+    GRP_LAUNCH_CHECK();
+    GRP_TRY(exclusive_scan_popcount(t.scan, t.scan_bytes, t.bits, t.before, t.n_words + 1, st));
+    if (N >= ((int64_t)1 << 31)) {       // more than 32 bits may be needed to see that there are too many
+        hipLaunchKernelGGL(count_bits_kernel, dim3(4096), dim3(256), 0, st, (const uint32_t*)t.bits, t.n_words, t.counters + 3);
+        GRP_LAUNCH_CHECK();
+        GRP_HIP(hipMemcpyAsync(n, t.counters + 3, sizeof *n, hipMemcpyDeviceToHost, st));
+        GRP_HIP(hipStreamSynchronize(st));
+        return GRP_OK;
+    }
+    int32_t count = 0;
+    GRP_HIP(hipMemcpyAsync(&count, t.before + t.n_words, sizeof count, hipMemcpyDeviceToHost, st));
+    GRP_HIP(hipStreamSynchronize(st));
+    *n = count;
+    return GRP_OK;
+}
+
 static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t E, int64_t N, int32_t K, uint64_t seed,
                                  int32_t part_id, hipStream_t st, grp_partition_t* h, const float* w = nullptr,
                                  bool weighted = false) {
-    // every N-sized temporary from one allocation: flags, positions, the node set, counters, scan scratch
-    const int64_t n_words = cdiv(N > 0 ? N : 1, 32);
-    size_t pos_scan_bytes = 0;
-    if (N > 0)
-        GRP_HIP(rocprim::exclusive_scan(nullptr, pos_scan_bytes, (const int32_t*)nullptr, (int64_t*)nullptr, (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-    const size_t set_scan_bytes = scan_temp_bytes(n_words + 1);
-    const size_t scratch_bytes = pos_scan_bytes > set_scan_bytes ? pos_scan_bytes : set_scan_bytes;
+    // every N-sized temporary from one allocation: the node set, counters, scan scratch
+    SetScratch t;
     DevBuf slab;
-    struct { int32_t* flag; int64_t* pos; unsigned long long* counters; uint32_t* bits; int32_t* before; char* scratch; } t{};
-    for (int pass = 0; pass < 2; ++pass) {
-        Bump b(slab.p, 0);
-        t.counters = b.take<unsigned long long>(4);
-        t.flag = b.take<int32_t>((size_t)(N > 0 ? N : 1));
-        t.pos = b.take<int64_t>((size_t)(N > 0 ? N : 1));
-        t.bits = b.take<uint32_t>((size_t)n_words + 1);
-        t.before = b.take<int32_t>((size_t)n_words + 1);
-        t.scratch = b.take<char>(scratch_bytes);
-        if (pass == 0) GRP_TRY(slab.alloc(b.total()));
-    }
-    DevView flag{t.flag}, pos{t.pos}, counters{t.counters};
-    GRP_HIP(hipMemsetAsync(counters.p, 0, 3 * sizeof(unsigned long long), st));
-
+    GRP_TRY(t.alloc(N, slab));
+    GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
+    const OwnerTest owned = owner_test(seed, (uint32_t)K, (uint32_t)part_id);
     int64_t n = 0;
-    if (N > 0) {
-        hipLaunchKernelGGL(owner_flag_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, (uint32_t)K, seed,
-                           (uint32_t)part_id, flag.as<int32_t>());
-        GRP_LAUNCH_CHECK();
-        GRP_HIP(rocprim::exclusive_scan(t.scratch, pos_scan_bytes, flag.as<int32_t>(), pos.as<int64_t>(), (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-        int64_t last_pos = 0;
-        int32_t last_flag = 0;
-        GRP_HIP(hipMemcpyAsync(&last_pos, pos.as<int64_t>() + (N - 1), sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipMemcpyAsync(&last_flag, flag.as<int32_t>() + (N - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipStreamSynchronize(st));
-        n = last_pos + last_flag;
-    }
+    GRP_TRY(build_node_set(N, owned, t, &n, st));
     if (n >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "partition has %lld >= 2^31 local nodes", (long long)n);
     h->n = n;
     GRP_TRY(halloc(&h->l2g, n));
     GRP_TRY(halloc(&h->d_global_in, n));
     GRP_HIP(hipMemsetAsync(h->d_global_in, 0, (size_t)(n > 0 ? n : 1) * sizeof(int64_t), st));
+    const NodeSet own{t.words};
     if (N > 0) {
-        hipLaunchKernelGGL(scatter_l2g_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, flag.as<int32_t>(),
-                           pos.as<int64_t>(), h->l2g);
+        hipLaunchKernelGGL(set_nodes_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, (const uint32_t*)t.bits, (const int32_t*)t.before,
+                           t.words, h->l2g);
         GRP_LAUNCH_CHECK();
     }
     unsigned long long host_counters[3] = {0, 0, 0};
-    NodeSet own{nullptr, nullptr};
-    if (E > 0 && N > 0) {
-        hipLaunchKernelGGL(pack_bits_kernel, dim3((unsigned)cdiv(n_words * 32, 256)), dim3(256), 0, st,
-                           (const int32_t*)flag.as<int32_t>(), N, n_words, t.bits);
-        GRP_LAUNCH_CHECK();
-        GRP_HIP(hipMemsetAsync(t.bits + n_words, 0, sizeof(uint32_t), st));
-        GRP_TRY(exclusive_scan_popcount(t.scratch, set_scan_bytes, t.bits, t.before, n_words + 1, st));
-        own = NodeSet{t.bits, t.before};
-    }
     const unsigned scan_grid = grid_for(E) < (unsigned)EDGE_SCAN_GRID ? grid_for(E) : (unsigned)EDGE_SCAN_GRID;
-    // unweighted: one pass writes the keys too, into a buffer sized for twice the expected E / K^2 kept edges
-    int64_t cap = weighted ? 0 : 2 * (E / K / K) + (1 << 20);
+    // Unweighted: one pass writes the keys too, into a buffer sized for twice the expected E / K^2 kept edges, and the local ids of twice
+    // the expected E / K edges that end in the partition.  Ids beyond 32 bits and more ranges of local ids than that pass
+    // orders take two passes and an addition per edge instead.
+    const int64_t spans = cdiv(n > 0 ? n : 1, (int64_t)1 << SPAN_BITS), scan_tiles = cdiv(E, SCAN_TILE);
+    const bool one_pass = !weighted && N < ((int64_t)1 << 31) && spans <= SPANS_MAX;
+    int64_t cap = one_pass ? 2 * (E / K / K) + (1 << 20) : 0, id_cap = one_pass ? 2 * (E / K) + (1 << 20) : 0;
     if (cap > E) cap = E;
-    DevBuf keybuf;                                       // both key arrays
+    if (id_cap > E) id_cap = E;
+    if (id_cap > (int64_t)0xFFFFFFF0) id_cap = 0xFFFFFFF0;
+    DevBuf keybuf, idbuf;                                // both key arrays; the local ids and where the tiles' runs begin
     size_t key_pitch = (((size_t)(cap > 0 ? cap : 1) * sizeof(uint64_t)) + 255) & ~(size_t)255;
+    const size_t id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
     if (!weighted) GRP_TRY(keybuf.alloc(2 * key_pitch));
+    if (one_pass && E > 0) GRP_TRY(idbuf.alloc(id_pitch + (size_t)scan_tiles * (size_t)(spans + 1) * sizeof(uint32_t)));
     if (E > 0) {
-        if (weighted) {
+        if (!one_pass) {
             ProfScope ps("partition_edge_scan", st, 0.0, 16.0 * (double)E);
             hipLaunchKernelGGL(edge_scan_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
-                               (unsigned long long*)h->d_global_in, counters.as<unsigned long long>());
+                               (unsigned long long*)h->d_global_in, t.counters);
             GRP_LAUNCH_CHECK();
         } else {
             ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
-            if (N == 0) own = NodeSet{counters.as<uint32_t>(), counters.as<int32_t>()};      // every id is out of range: any word 0 will do
-            hipLaunchKernelGGL(edge_scan_keys_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
-                               (unsigned long long*)h->d_global_in, counters.as<unsigned long long>(), keybuf.as<uint64_t>(),
-                               (unsigned long long)cap);
+            uint32_t* const heads = (uint32_t*)((char*)idbuf.p + id_pitch);
+            hipLaunchKernelGGL(edge_scan_keys_kernel, dim3((unsigned)(scan_tiles < SCAN_GRID ? scan_tiles : SCAN_GRID)), dim3(SCAN_THREADS), 0, st, src,
+                               dst, E, N, own, owned, (int)spans, (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(),
+                               (unsigned long long)cap, idbuf.as<uint32_t>(), (unsigned long long)id_cap, heads);
+            int64_t parts = cdiv(256, spans);            // a workgroup per CU, a tile at least for each of its wavefronts
+            if (parts > cdiv(scan_tiles, 16)) parts = cdiv(scan_tiles, 16);
+            int at_once = 64;
+            while (at_once > 1 && parts * 16 * at_once > scan_tiles) at_once /= 2;
+            hipLaunchKernelGGL(rank_count_kernel, dim3((unsigned)spans, (unsigned)parts), dim3(1024), 0, st, (const uint32_t*)idbuf.as<uint32_t>(),
+                               (const uint32_t*)heads, scan_tiles, (int)spans, at_once, n, (unsigned long long*)h->d_global_in);
             GRP_LAUNCH_CHECK();
         }
-        GRP_HIP(hipMemcpyAsync(host_counters, counters.p, sizeof host_counters, hipMemcpyDeviceToHost, st));
+        GRP_HIP(hipMemcpyAsync(host_counters, t.counters, sizeof host_counters, hipMemcpyDeviceToHost, st));
         GRP_HIP(hipStreamSynchronize(st));
     }
     if (host_counters[1] != 0)
         return fail(GRP_ERANGE, "%llu edges have an endpoint outside [0, %lld)", host_counters[1], (long long)N);
-    const int64_t nnz = (int64_t)(weighted ? host_counters[0] : host_counters[2]);
+    const int64_t nnz = (int64_t)(one_pass ? host_counters[2] : host_counters[0]);
     h->nnz = nnz;
     if (weighted) return weighted_build(src, dst, w, E, own, st, h);
     DevBuf exact;                                        // only if the first buffer was too small
@@ -830,10 +957,10 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
         key_pitch = (((size_t)nnz * sizeof(uint64_t)) + 255) & ~(size_t)255;
         GRP_TRY(exact.alloc(2 * key_pitch));
         keys = exact.as<uint64_t>();
-        GRP_HIP(hipMemsetAsync(counters.as<unsigned long long>() + 2, 0, sizeof(unsigned long long), st));
+        GRP_HIP(hipMemsetAsync(t.counters + 2, 0, sizeof(unsigned long long), st));
         ProfScope ps("partition_edge_keys", st, 0.0, 16.0 * (double)E + 8.0 * (double)nnz);
         hipLaunchKernelGGL(edge_keys_kernel<SetSelect>, dim3(grid_for(E)), dim3(256), 0, st, src, dst, E, SetSelect{own},
-                           counters.as<unsigned long long>() + 2, keys);
+                           t.counters + 2, keys);
         GRP_LAUNCH_CHECK();
     }
     uint64_t* const keys_alt = (uint64_t*)((char*)keys + key_pitch);
@@ -990,8 +1117,8 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     GRP_HIP(hipMemsetAsync(counters.p, 0, 3 * sizeof(unsigned long long), st));
     int64_t n = 0;
     if (N > 0) {
-        hipLaunchKernelGGL(owner_flag_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, (uint32_t)K, seed,
-                           (uint32_t)part_id, owned.as<int32_t>());
+        hipLaunchKernelGGL(owner_flag_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, owner_test(seed, (uint32_t)K, (uint32_t)part_id),
+                           owned.as<int32_t>());
         GRP_LAUNCH_CHECK();
         GRP_HIP(hipMemcpyAsync(member.p, owned.p, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
         for (int hop = 0; hop < hops; ++hop) {
@@ -1128,34 +1255,54 @@ __global__ __launch_bounds__(256) void chunk_scatter_kernel(const int64_t* __res
     }
 }
 
-__global__ __launch_bounds__(256) void pair_flag_kernel(int64_t N, ChunkMap cm, uint32_t base, uint32_t swept,
-                                                        int32_t* __restrict__ flag) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N) {
+struct PairMember {
+    ChunkMap cm;
+    uint32_t base, swept;
+    __device__ __forceinline__ bool operator()(int64_t v) const {
         const uint32_t ch = chunk_of(cm, v);
-        flag[v] = (ch == base || ch == swept) ? 1 : 0;
+        return ch == base || ch == swept;
     }
-}
+};
 
-__global__ __launch_bounds__(256) void pair_nodes_kernel(int64_t N, ChunkMap cm, uint32_t base,
-                                                         const int32_t* __restrict__ flag, const int64_t* __restrict__ pos,
-                                                         const int64_t* __restrict__ dg_all, int64_t* __restrict__ l2g,
-                                                         int64_t* __restrict__ dg, uint8_t* __restrict__ base_mask) {
+__global__ __launch_bounds__(256) void pair_nodes_kernel(int64_t N, ChunkMap cm, uint32_t base, const uint32_t* __restrict__ bits,
+                                                         const int32_t* __restrict__ before, uint2* __restrict__ words,
+                                                         const int64_t* __restrict__ dg_all, int64_t* __restrict__ l2g, int64_t* __restrict__ dg,
+                                                         uint8_t* __restrict__ base_mask) {
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N && flag[v]) {
-        const int64_t i = pos[v];
+    if (v >= N) return;
+    const uint2 w = set_word(bits, before, v, words);
+    if (word_has(w, v)) {
+        const int64_t i = word_rank(w, v);
         l2g[i] = v;
         dg[i] = dg_all[v];
         base_mask[i] = chunk_of(cm, v) == base ? 1 : 0;
     }
 }
 
-// Keys of one bucket's edges (both endpoints are members by construction).
-__global__ __launch_bounds__(256) void bucket_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
-                                                          int64_t count, const int64_t* __restrict__ pos,
-                                                          uint64_t* __restrict__ keys) {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256)
-        keys[e] = ((uint64_t)pos[dst[e]] << 32) | (uint64_t)pos[src[e]];
+// Keys of the edges of up to four buckets (blockIdx.y; both endpoints are members by construction).  Four edges a thread: their
+// lookups are in flight together (3.9e6 edges in four launches of one edge a thread, ids looked up in an 8-byte array over all nodes, 71
+// us; this way 60).
+struct PairBuckets { int64_t from[4], count[4], to[4]; };
+__global__ __launch_bounds__(256) void bucket_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, PairBuckets b,
+                                                          NodeSet set, uint64_t* __restrict__ keys) {
+    constexpr int PER = 4;
+    const int64_t count = b.count[blockIdx.y];
+    const int64_t* const s = src + b.from[blockIdx.y];
+    const int64_t* const d = dst + b.from[blockIdx.y];
+    for (int64_t e0 = (int64_t)blockIdx.x * (256 * PER) + threadIdx.x; e0 < count; e0 += (int64_t)gridDim.x * (256 * PER)) {
+        int64_t u[PER], v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t e = e0 + i * 256 < count ? e0 + i * 256 : count - 1;
+            u[i] = s[e];
+            v[i] = d[e];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t key = ((uint64_t)(uint32_t)set_rank(set, v[i]) << 32) | (uint64_t)(uint32_t)set_rank(set, u[i]);
+            if (e0 + i * 256 < count) keys[b.to[blockIdx.y] + e0 + i * 256] = key;
+        }
+    }
 }
 
 static void free_chunks(grp_chunks_t* h) {
@@ -1220,63 +1367,47 @@ static grp_status pair_partition_impl(const grp_chunks_t* ck, int32_t base, int3
                                       grp_partition_t* h) {
     const int64_t N = ck->N;
     const int c = ck->n_chunks;
-    DevBuf flag, pos, scan_tmp;
-    GRP_TRY(flag.alloc((size_t)N * sizeof(int32_t)));
-    GRP_TRY(pos.alloc((size_t)N * sizeof(int64_t)));
+    const ChunkMap cm{ck->seed, (uint32_t)c, ck->assign};
+    SetScratch t;
+    DevBuf slab;
+    GRP_TRY(t.alloc(N, slab));
+    if (N >= ((int64_t)1 << 31)) GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
     int64_t n = 0;
-    if (N > 0) {
-        hipLaunchKernelGGL(pair_flag_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, ChunkMap{ck->seed, (uint32_t)c, ck->assign},
-                           (uint32_t)base, (uint32_t)swept, flag.as<int32_t>());
-        GRP_LAUNCH_CHECK();
-        size_t bytes = 0;
-        GRP_HIP(rocprim::exclusive_scan(nullptr, bytes, flag.as<int32_t>(), pos.as<int64_t>(), (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-        GRP_TRY(scan_tmp.alloc(bytes));
-        GRP_HIP(rocprim::exclusive_scan(scan_tmp.p, bytes, flag.as<int32_t>(), pos.as<int64_t>(), (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-        int64_t last_pos = 0;
-        int32_t last_flag = 0;
-        GRP_HIP(hipMemcpyAsync(&last_pos, pos.as<int64_t>() + (N - 1), sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipMemcpyAsync(&last_flag, flag.as<int32_t>() + (N - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipStreamSynchronize(st));
-        n = last_pos + last_flag;
-    }
+    GRP_TRY(build_node_set(N, PairMember{cm, (uint32_t)base, (uint32_t)swept}, t, &n, st));
     if (n >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "partition has %lld >= 2^31 local nodes", (long long)n);
     h->n = n;
     GRP_TRY(halloc(&h->l2g, n));
     GRP_TRY(halloc(&h->d_global_in, n));
     GRP_TRY(halloc(&h->base_mask, n));
+    const NodeSet set{t.words};
     if (N > 0) {
-        hipLaunchKernelGGL(pair_nodes_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, ChunkMap{ck->seed, (uint32_t)c, ck->assign},
-                           (uint32_t)base, flag.as<int32_t>(), pos.as<int64_t>(), ck->d_global_all, h->l2g, h->d_global_in,
-                           h->base_mask);
+        hipLaunchKernelGGL(pair_nodes_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, cm, (uint32_t)base, (const uint32_t*)t.bits,
+                           (const int32_t*)t.before, t.words, ck->d_global_all, h->l2g, h->d_global_in, h->base_mask);
         GRP_LAUNCH_CHECK();
     }
     // the partition's edges are exactly the buckets (x, y) with x, y in {base, swept}
     int chunks2[2] = {base, swept};
     const int nc = base == swept ? 1 : 2;
-    int64_t nnz = 0;
+    PairBuckets buckets{};
+    int64_t nnz = 0, most = 0;
     for (int a = 0; a < nc; ++a)
         for (int b = 0; b < nc; ++b) {
-            const int bk = chunks2[a] * c + chunks2[b];
-            nnz += ck->bucket_ptr[bk + 1] - ck->bucket_ptr[bk];
+            const int bk = chunks2[a] * c + chunks2[b], i = a * nc + b;
+            buckets.from[i] = ck->bucket_ptr[bk];
+            buckets.count[i] = ck->bucket_ptr[bk + 1] - ck->bucket_ptr[bk];
+            buckets.to[i] = nnz;
+            nnz += buckets.count[i];
+            most = buckets.count[i] > most ? buckets.count[i] : most;
         }
     h->nnz = nnz;
     DevBuf keys, keys_alt;
     GRP_TRY(keys.alloc((size_t)nnz * sizeof(uint64_t)));
     GRP_TRY(keys_alt.alloc((size_t)nnz * sizeof(uint64_t)));
-    int64_t off = 0;
-    for (int a = 0; a < nc; ++a)
-        for (int b = 0; b < nc; ++b) {
-            const int bk = chunks2[a] * c + chunks2[b];
-            const int64_t lo = ck->bucket_ptr[bk], cnt = ck->bucket_ptr[bk + 1] - lo;
-            if (cnt > 0) {
-                hipLaunchKernelGGL(bucket_keys_kernel, dim3(grid_for(cnt)), dim3(256), 0, st, ck->src + lo, ck->dst + lo, cnt,
-                                   pos.as<int64_t>(), keys.as<uint64_t>() + off);
-                GRP_LAUNCH_CHECK();
-            }
-            off += cnt;
-        }
+    if (nnz > 0) {
+        hipLaunchKernelGGL(bucket_keys_kernel, dim3(grid_for(cdiv(most, 4)), nc * nc), dim3(256), 0, st, ck->src, ck->dst, buckets, set,
+                           keys.as<uint64_t>());
+        GRP_LAUNCH_CHECK();
+    }
     return build_csr_csc(h, keys.as<uint64_t>(), keys_alt.as<uint64_t>(), st);
 }
 

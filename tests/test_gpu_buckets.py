@@ -51,3 +51,19 @@ def test_local_edges_bit_exact(kind, n, E):
         y = torch.empty(n, 4, device=DEV)
         g.grp_spmm(part, transposed, g.SCALE_NONE, False, 4, x, 4, g.DTYPE_FP32, y, 4)
         assert torch.equal(y, torch.zeros(n, 4, device=DEV).index_add_(0, b, x[a])), transposed
+
+
+@pytest.mark.parametrize("N,K", [(1, 1), (31, 2), (64, 3), (70001, 1), (70001, 6), (70001, 7), (70000, 48), (70000, 1 << 20), (70000, (1 << 31) - 1)])
+def test_hash_split_bit_exact(N, K):
+    import paper_2602_01872_amd as g
+    rng = np.random.default_rng(N + K)
+    s, d = rng.integers(0, N, 200001), rng.integers(0, N, 200001)
+    owner = torch.empty(N, dtype=torch.int32, device=DEV)
+    g.grp_node_owners(N, K, 5, owner)
+    for p in sorted({0, K - 1, int(owner[N // 2])}):
+        print(f"[case] hash N={N} K={K} part {p}", flush=True)
+        want = ograph.partition(s, d, N, K, 5, p)
+        part = g.grp_partition(torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV), N, K, 5, p)
+        assert part.n == want["n"]
+        for k in KEYS:
+            assert np.array_equal(part.array(k), want[k]), k
