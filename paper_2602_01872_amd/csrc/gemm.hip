@@ -668,6 +668,7 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
     // What the matrix unit cuts off has always the same sign.  It is nothing beside the rounding of one result, but a bias gradient adds
     // up the results of 10^5..10^7 rows: every other 16 rows are multiplied as -A, and their sums subtracted.
     auto odd_rows = [&](int i) { return ((wave * TM + i) & 1) != 0; };
+    const float turned = (wave & 1) ? -1.f : 1.f;     // (TM = 1)
     bf16x8 a[TM][3];
     auto split_a = [&](int kt) {
         const int left = left_of(kt);
@@ -697,7 +698,11 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
 #pragma unroll
                     for (int t = 0; t < 8; ++t) v[t] = 0.f;
                 }
-                if (odd_rows(i)) {
+                if (TM % 2 != 0) {
+                    const uint32_t sign = (uint32_t)(wave & 1) << 31;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) v[t] = __uint_as_float(__float_as_uint(v[t]) ^ sign);
+                } else if (odd_rows(i)) {
 #pragma unroll
                     for (int t = 0; t < 8; ++t) v[t] = -v[t];
                 }
@@ -713,22 +718,35 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
     auto mma = [&](int kt) {
         const unsigned char* const bp = bget + (kt & 1) * 3 * PLANE;
         const bool one = A_BF16 && kt < nk1;
-        bf16x8 b[2][3];
-        auto get = [&](int j) {
+        // A wavefront of two row tiles multiplies a column tile at a time: two chains of dependent instructions.  Of one row tile it takes
+        // all its column tiles together, since such products run with one wavefront per SIMD, that waits for its chains alone: what bounds
+        // them is the instructions of an iteration (64 rows, N = 64: a k-tile 1.02 -> 0.91 us, most of it the one sign per wavefront that
+        // took both branches before; requesting k-tiles further ahead changed nothing).
+        constexpr int J = TM == 1 ? TN : 1;
+        bf16x8 b[J == 1 ? 2 : 1][J][3];
+        auto get = [&](int j0) {
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[j & 1][p] = *reinterpret_cast<const bf16x8*>(bp + p * PLANE + j * 16 * 64);
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    b[J == 1 ? j0 & 1 : 0][j][p] = *reinterpret_cast<const bf16x8*>(bp + p * PLANE + (j0 + j) * 16 * 64);
         };
         get(0);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            if (j + 1 < TN) get(j + 1);               // a column tile ahead: the LDS latency hides behind the products
+        for (int j0 = 0; j0 < TN; j0 += J) {
+            if (j0 + J < TN) get(j0 + J);             // a column tile ahead: the LDS latency hides behind the products
             __builtin_amdgcn_sched_barrier(0);
-            floatx4 t[TM];
+            auto& bj = b[J == 1 ? j0 & 1 : 0];
+            floatx4 t[TM][J], top[TM][J];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) t[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < J; ++j) t[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
             auto mul = [&](int pb, int pa) {
 #pragma unroll
-                for (int i = 0; i < TM; ++i) t[i] = mfma16(b[j & 1][pb], a[i][pa], t[i]);
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < J; ++j) t[i][j] = mfma16(bj[j][pb], a[i][pa], t[i][j]);
             };
             if (!one) {                               // small products first
                 mul(2, 1);
@@ -743,11 +761,21 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
                 mul(1, 0);
             }
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const floatx4 sum = t[i] + mfma16(b[j & 1][0], a[i][0], floatx4{0.f, 0.f, 0.f, 0.f});
-                acc[i][j] = odd_rows(i) ? acc[i][j] - sum : acc[i][j] + sum;
-                pin(acc[i][j]);
-            }
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < J; ++j) top[i][j] = mfma16(bj[j][0], a[i][0], floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const floatx4 sum = t[i][j] + top[i][j];
+                    if (TM % 2 == 0) acc[i][j0 + j] = odd_rows(i) ? acc[i][j0 + j] - sum : acc[i][j0 + j] + sum;
+                    else {                            // (not known when compiled; a sum times +1 or -1 is added with one rounding as well)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[i][j0 + j][q] = fmaf(sum[q], turned, acc[i][j0 + j][q]);
+                    }
+                    pin(acc[i][j0 + j]);
+                }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -1046,7 +1074,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------------------- TN
-constexpr int TN_ROWS_PER_SPLIT_MIN = 128;    // node rows per split (multiple of BK): a lone workgroup spends ~3 us per 32 rows
+constexpr int TN_IDLE = 128;                  // a launch of fewer workgroups leaves half the chip idle
 constexpr int TN_MAX_SPLITS = 256;
 constexpr int N_CU = 256;                     // a product is cut into one full round of resident workgroups (768 slices at two per CU: 6-8 % slower)
 
@@ -1069,7 +1097,12 @@ static TnPlan tn_plan(int64_t M, int K, int N, int products = 1) {
     const bool stream = M >= ((int64_t)1 << 23);
     const int target = N_CU * tn_wgs(p.bk_tile * p.bn_tile / 4096);      // (tiles of 32 x 32 per wavefront)
     int64_t s = (stream ? 4 * target : target) / (p.tiles_k * p.tiles_n * products);
-    if (s > cdiv(M, TN_ROWS_PER_SPLIT_MIN)) s = cdiv(M, TN_ROWS_PER_SPLIT_MIN);
+    // A lone workgroup spends over a microsecond on 32 rows: slices of 128, of fewer where that leaves most of the chip idle (with the
+    // sum over the slices, us: K = N = 64 over 2500 rows 11.9 -> 9.7; K = N = 256 over 256 18.4 -> 11.9, 1024 19.1 -> 15.4, 2500 21.2 -> 19.2;
+    // K = 128, N = 256 over 1024 18.4 -> 14.0).
+    const int64_t tiles = (int64_t)p.tiles_k * p.tiles_n * products;
+    const int rows_min = tiles * cdiv(M, 128) > TN_IDLE ? 128 : tiles * cdiv(M, 64) > TN_IDLE ? 64 : 32;
+    if (s > cdiv(M, rows_min)) s = cdiv(M, rows_min);
     if (s > (stream ? 8 * TN_MAX_SPLITS : TN_MAX_SPLITS)) s = stream ? 8 * TN_MAX_SPLITS : TN_MAX_SPLITS;
     if (s < 1) s = 1;
     p.chunk = round_up(cdiv(M, s), BK);
