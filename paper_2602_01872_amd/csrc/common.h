@@ -390,9 +390,6 @@ grp_status launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // ---------------------------------------------------------------- device primitives (partition.hip)
 namespace grp {
 // rocPRIM wrappers with caller-provided temporary storage (sizes from the *_temp_bytes calls).
-size_t sort_keys_temp_bytes(int64_t count);
-grp_status sort_keys_u64(void* temp, size_t temp_bytes, const uint64_t* in, uint64_t* out, int64_t count,
-                         unsigned end_bit, hipStream_t st);
 size_t scan_temp_bytes(int64_t count);
 grp_status exclusive_scan_i64(void* temp, size_t temp_bytes, const int64_t* in, int64_t* out, int64_t count,
                               hipStream_t st);
@@ -401,9 +398,6 @@ grp_status exclusive_scan_i32(void* temp, size_t temp_bytes, const int32_t* in, 
 // out[i] = number of set bits in words[0 .. i), i in [0, count): reads `count` words
 grp_status exclusive_scan_popcount(void* temp, size_t temp_bytes, const uint32_t* words, int32_t* out, int64_t count,
                                    hipStream_t st);
-// From sorted keys (row << 32 | col): idx[i] = low half, ptr[r] = first position with high half >= r.
-grp_status launch_csr_from_sorted_keys(const uint64_t* keys, int64_t nnz, int64_t n, int64_t* ptr, int32_t* idx,
-                                       hipStream_t st);
 // The split schedule of the long rows of a device pointer array, written into caller-provided device
 // arrays without a host pass: out->n_long / n_chunks are set to the capacities (the launches cover
 // them) and the slots beyond the real counts are filled so that they do nothing (row -1, empty

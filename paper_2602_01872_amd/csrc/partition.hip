@@ -1715,23 +1715,6 @@ extern "C" grp_status grp_partition_destroy(grp_partition_t* part) {
 // ------------------------------------------------------------------ shared device primitives
 namespace grp {
 
-size_t sort_keys_temp_bytes(int64_t count) {
-    size_t bytes = 0;
-    (void)rocprim::radix_sort_keys(nullptr, bytes, (const uint64_t*)nullptr, (uint64_t*)nullptr,
-                                   (size_t)(count > 0 ? count : 1), 0u, 64u, (hipStream_t)0);
-    return bytes + 256;
-}
-
-grp_status sort_keys_u64(void* temp, size_t temp_bytes, const uint64_t* in, uint64_t* out, int64_t count,
-                         unsigned end_bit, hipStream_t st) {
-    if (count <= 0) return GRP_OK;
-    size_t need = 0;
-    GRP_HIP(rocprim::radix_sort_keys(nullptr, need, in, out, (size_t)count, 0u, end_bit, st));
-    if (need > temp_bytes) return fail(GRP_EWORKSPACE, "sort temp %zu < %zu", temp_bytes, need);
-    GRP_HIP(rocprim::radix_sort_keys(temp, need, in, out, (size_t)count, 0u, end_bit, st));
-    return GRP_OK;
-}
-
 size_t scan_temp_bytes(int64_t count) {
     size_t bytes = 0;
     (void)rocprim::exclusive_scan(nullptr, bytes, (const int64_t*)nullptr, (int64_t*)nullptr, (int64_t)0,
@@ -1778,31 +1761,6 @@ grp_status exclusive_scan_popcount(void* temp, size_t temp_bytes, const uint32_t
     GRP_HIP(rocprim::exclusive_scan(nullptr, need, in, out, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), st));
     if (need > temp_bytes) return fail(GRP_EWORKSPACE, "scan temp %zu < %zu", temp_bytes, need);
     GRP_HIP(rocprim::exclusive_scan(temp, need, in, out, (int32_t)0, (size_t)count, rocprim::plus<int32_t>(), st));
-    return GRP_OK;
-}
-
-// Same result as csr_from_keys_kernel for matrices with many empty rows (a sampled block has more
-// rows than most of them have entries): every row pointer is found by binary search instead of by
-// the thread at the end of the previous row walking over the gap.
-__global__ __launch_bounds__(256) void csr_from_keys_search_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int64_t n,
-                                                                   int64_t* __restrict__ ptr, int32_t* __restrict__ idx) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < nnz) idx[i] = (int32_t)(keys[i] & 0xFFFFFFFFull);
-    if (i <= n) {
-        int64_t lo = 0, hi = nnz;                        // first position whose row is >= i
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if ((int64_t)(keys[mid] >> 32) < i) lo = mid + 1; else hi = mid;
-        }
-        ptr[i] = lo;
-    }
-}
-
-grp_status launch_csr_from_sorted_keys(const uint64_t* keys, int64_t nnz, int64_t n, int64_t* ptr, int32_t* idx,
-                                       hipStream_t st) {
-    const int64_t work = nnz > n + 1 ? nnz : n + 1;
-    hipLaunchKernelGGL(csr_from_keys_search_kernel, dim3((unsigned)cdiv(work, 256)), dim3(256), 0, st, keys, nnz, n, ptr, idx);
-    GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
 

@@ -13,9 +13,16 @@
 //
 // Layers are built from the seeds inwards.  Above the input layer, new source nodes are
 // found with a node bitmap and a prefix sum over its words (ascending local id), sources are
-// relabelled to block-local indices and the block is also stored transposed (by radix
-// sort) for the backward pass.  The input layer keeps partition-local ids: they index the
-// feature matrix directly, so no feature rows are copied.
+// relabelled to block-local indices and the block is also stored transposed for the backward pass.  The input layer keeps
+// partition-local ids: they index the feature matrix directly, so no feature rows are copied.
+//
+// Every launch costs the device about 3.6 us, whatever its stream (a captured step of 70 launches replayed alone 450 us, on two streams
+// 508 for two, on four 1030 for four), so the work is cut into as few as its dependences allow: a layer is (1) the counts of its rows with
+// their prefix sum, beside the relabelling of the layer before, (2) the choice of its edges, which marks the nodes they
+// reach, (3) the prefix sum over the marks' words, which numbers them.  The transposed blocks of all layers take three more together.
+// The prefix sums look back over the workgroups before theirs instead of taking launches of their own.  (23 launches
+// on the caller's stream and 20 beside it became 9 and 3: a step of 1024 seeds, fanouts 15, 10, 5 on a 7e6-node store 415 -> 391 us, an epoch of
+// 24 steps on four streams 6.2 -> 5.2 ms.)
 //
 // The host never learns a block's sizes.  They depend on the draws, so they exist on the device only
 // (`sizes`, four numbers per layer); every launch is sized by the upper bounds that follow from the seeds
@@ -24,6 +31,7 @@
 // the device, and can be captured in a graph.
 #include "common.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace grp {
@@ -33,50 +41,167 @@ constexpr int SAMPLE_MAX_FANOUT = 64;         // one lane of a wavefront per cho
 // edges, newly reached nodes.
 enum { SZ_DST = 0, SZ_SRC = 1, SZ_NNZ = 2, SZ_NEW = 3, SZ_PER_LAYER = 4 };
 
-// Per destination row: the number of edges it keeps and 1 / max(that, 1); above the input layer also
-// the row's place in the block's source list (destinations come first, in order) and in the node -> block
-// index map.  The elements of `cnt` from n_dst to the bound are zero and close the prefix sum.
-__global__ __launch_bounds__(256) void sample_count_kernel(const int64_t* __restrict__ rowptr,
-                                                           const int32_t* __restrict__ dst_nodes,
-                                                           const int64_t* __restrict__ n_dst_dev, int64_t bound,
-                                                           int fanout, int64_t* __restrict__ cnt /*[bound+1]*/,
-                                                           int32_t* __restrict__ cnt32 /*[n_dst] or null*/,
-                                                           float* __restrict__ inv /*[n_dst]*/,
-                                                           int32_t* __restrict__ mark /*[n] or null*/,
-                                                           int32_t* __restrict__ src_nodes /*[>= n_dst] or null*/) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i > bound) return;
-    if (i >= *n_dst_dev) { cnt[i] = 0; return; }          // rows between the real count and the bound are empty
-    const int32_t v = dst_nodes[i];
-    const int64_t d = rowptr[v + 1] - rowptr[v];
-    const int64_t c = d < fanout ? d : fanout;
-    cnt[i] = c;
-    if (cnt32) cnt32[i] = (int32_t)c;
-    inv[i] = 1.0f / (float)(c > 1 ? c : 1);
-    if (mark) {
-        mark[v] = (int32_t)i + 1;
-        src_nodes[i] = v;
+// ---- prefix sums across the workgroups of one launch.  A workgroup posts the sum of its part, then adds up what those before it have
+// posted, 64 at a time, until it meets one that has posted its whole prefix, and posts its own.  Flag and value share a 64-bit word,
+// cleared before the launch.  Workgroups wait for lower-numbered ones only, and there are at most PARTS of them, which the chip
+// holds many times over: launches that run side by side cannot keep each other's waiting.
+constexpr int PARTS = 128;
+constexpr unsigned long long POSTED_SUM = 1ull << 62, POSTED_PREFIX = 2ull << 62, POSTED_VALUE = (1ull << 62) - 1;
+
+// The sum before part `part`, for the lanes of one wavefront; `own`: this part's sum.
+__device__ __forceinline__ unsigned long long look_back(unsigned long long* __restrict__ posted, int part, unsigned long long own) {
+    const int lane = threadIdx.x & 63;
+    auto post = [&](unsigned long long v) {
+        if (lane == 0) __hip_atomic_store(&posted[part], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    post((part == 0 ? POSTED_PREFIX : POSTED_SUM) | own);
+    unsigned long long before = 0;
+    for (int at = part - 1; at >= 0; at -= 64) {
+        unsigned long long v = POSTED_PREFIX;
+        do {
+            if (at - lane >= 0) v = __hip_atomic_load(&posted[at - lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } while (__ballot((v >> 62) == 0));
+        const unsigned long long whole = __ballot((v >> 62) == 2);       // (lanes past part 0 count as whole, with nothing)
+        const int last = whole ? __ffsll(whole) - 1 : 63;
+        unsigned long long sum = lane <= last ? v & POSTED_VALUE : 0ull;
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        before += sum;
+        if (whole) break;
     }
+    if (part > 0) post(POSTED_PREFIX | (before + own));
+    return before;
 }
 
-// Seeds outside [0, n) are counted (`bad`, zero on entry; the step's statistics report it) and replaced by
-// node 0 in the copy the sampler works on, so that no kernel reads outside the partition.  Also states the
-// seed-side block's number of destinations.
-__global__ __launch_bounds__(256) void check_seeds_kernel(const int32_t* __restrict__ seeds, int64_t n_seeds, int64_t n,
-                                                          int32_t* __restrict__ safe, int64_t* __restrict__ bad,
-                                                          int64_t* __restrict__ n_dst_out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) *n_dst_out = n_seeds;
-    if (i >= n_seeds) return;
-    const int32_t v = seeds[i];
-    const bool ok = v >= 0 && (int64_t)v < n;
-    safe[i] = ok ? v : 0;
-    if (!ok) atomicAdd((unsigned long long*)bad, 1ull);
+constexpr int CS_THREADS = 256;
+constexpr int CS_PER = 4;
+constexpr int CS_ROUND = CS_THREADS * CS_PER;                // rows of a part, taken that many at a time
+// Rounds of a part and number of parts for `items` rows.
+struct ScanPlan { int rounds, parts; };
+static ScanPlan scan_plan(int64_t items, int64_t round) {
+    const int64_t rounds = cdiv(items, round * PARTS);
+    return {(int)rounds, (int)cdiv(items, round * rounds)};
+}
+
+// Rows of a layer, counted: the number of edges row i keeps (CSR pointer ptr[0 .. bound], the rows between the real count and the bound
+// empty), 1 / max(that, 1) and, above the input layer, its place at the head of the block's source list.  The seeds' layer reads
+// the caller's list: seeds outside [0, n) are counted (`bad`; the step's statistics report it) and replaced by node 0 in the
+// copy the sampler works on, so that no kernel reads outside the partition.
+struct CountJob {
+    const int64_t* rowptr;
+    const int32_t* dst_nodes;
+    const int32_t* raw_seeds;            // the seeds' layer only: the caller's list (dst_nodes receives the checked copy)
+    int64_t n, n_seeds;
+    int64_t* sizes;                      // of this layer
+    int64_t bound;
+    int fanout, rounds, parts;
+    unsigned long long* posted;
+    int64_t* ptr;
+    int32_t* cnt32;
+    float* inv;
+    int32_t* mark;                       // the seeds' layer only (and above the input layer)
+    int32_t* src_nodes;                  // above the input layer
+    unsigned long long* bad;
+};
+// idx_blk[e] = block-local index of the source of edge e; arrival[e] = how many edges of that source came before it, in any order.
+struct RelabelJob {
+    const int64_t* ptr;                  // null: nothing to relabel
+    const int64_t* sizes;
+    int64_t dst_bound;
+    const int32_t* idx_local;
+    const int32_t* mark;
+    int32_t* idx_blk;
+    int32_t* arrival;
+    uint32_t* count_t;                   // [sources] edges of each (cleared)
+};
+
+__global__ __launch_bounds__(CS_THREADS) void count_rows_kernel(CountJob c, RelabelJob r) {
+    __shared__ unsigned long long wave_sum[CS_THREADS / 64];
+    __shared__ unsigned long long before_s;
+    const int tid = threadIdx.x, lane = tid & 63;
+    if ((int)blockIdx.x >= c.parts) {                        // relabelling: a wavefront per destination row
+        const int64_t i = (int64_t)((int)blockIdx.x - c.parts) * 4 + tid / 64;
+        if (i >= r.sizes[SZ_DST]) return;
+        for (int64_t e = r.ptr[i] + lane; e < r.ptr[i + 1]; e += 64) {
+            const int32_t s = r.mark[r.idx_local[e]] - 1;
+            r.idx_blk[e] = s;
+            r.arrival[e] = (int32_t)atomicAdd(&r.count_t[s], 1u);
+        }
+        return;
+    }
+    const int part = (int)blockIdx.x;
+    const int64_t n_dst = c.raw_seeds ? c.n_seeds : c.sizes[SZ_DST];
+    if (c.raw_seeds && part == 0 && tid == 0) c.sizes[SZ_DST] = n_dst;
+    const int64_t part0 = (int64_t)part * c.rounds * CS_ROUND;
+    int32_t cnt[CS_PER];
+    auto count = [&](int round, bool first) {                // the counts of one round, in cnt
+        unsigned long long sum = 0;
+        int32_t v[CS_PER];
+#pragma unroll
+        for (int q = 0; q < CS_PER; ++q) {
+            const int64_t i = part0 + (int64_t)round * CS_ROUND + CS_PER * tid + q;
+            v[q] = 0;
+            if (i < n_dst) {
+                if (c.raw_seeds) {
+                    v[q] = c.raw_seeds[i];
+                    const bool ok = v[q] >= 0 && (int64_t)v[q] < c.n;
+                    if (!ok) v[q] = 0;
+                    if (first && !ok) atomicAdd(c.bad, 1ull);
+                    if (first) const_cast<int32_t*>(c.dst_nodes)[i] = v[q];
+                } else {
+                    v[q] = c.dst_nodes[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < CS_PER; ++q) {
+            const int64_t i = part0 + (int64_t)round * CS_ROUND + CS_PER * tid + q;
+            cnt[q] = 0;
+            if (i < n_dst) {
+                const int64_t d = c.rowptr[v[q] + 1] - c.rowptr[v[q]];
+                cnt[q] = (int32_t)(d < c.fanout ? d : c.fanout);
+                if (first) {
+                    if (c.cnt32) c.cnt32[i] = cnt[q];
+                    c.inv[i] = 1.0f / (float)(cnt[q] > 1 ? cnt[q] : 1);
+                    // (a lower layer's destinations are the sources of the layer above: the map holds the same places already)
+                    if (c.mark) c.mark[v[q]] = (int32_t)i + 1;
+                    if (c.src_nodes) c.src_nodes[i] = v[q];
+                }
+            }
+            sum += (unsigned long long)cnt[q];
+        }
+        return sum;
+    };
+    unsigned long long mine = 0, total;
+    for (int round = 0; round < c.rounds; ++round) mine += count(round, true);
+    (void)block_scan<CS_THREADS / 64>(mine, wave_sum, total);
+    if (tid < 64) {
+        const unsigned long long b = look_back(c.posted, part, total);
+        if (lane == 0) before_s = b;
+    }
+    __syncthreads();
+    unsigned long long at0 = before_s;
+    for (int round = 0; round < c.rounds; ++round) {
+        const unsigned long long sum = c.rounds == 1 ? mine : count(round, false);
+        unsigned long long at = at0 + block_scan<CS_THREADS / 64>(sum, wave_sum, total);
+        at0 += total;
+#pragma unroll
+        for (int q = 0; q < CS_PER; ++q) {
+            const int64_t i = part0 + (int64_t)round * CS_ROUND + CS_PER * tid + q;
+            if (i <= c.bound) c.ptr[i] = (int64_t)at;
+            at += (unsigned long long)cnt[q];
+        }
+    }
 }
 
 // One wavefront per destination row.  Lane t computes draw t; the subset is grown in `fanout`
 // wave-uniform steps with lane t keeping the t-th element; each lane then finds the rank of its
 // element (they are distinct) and writes the edge to that output slot.
+// Above the input layer the sources that the block does not have yet are marked in a bitmap over the partition's nodes (one bit each):
+// the words' population counts are prefix-summed and every non-empty word then numbers its own nodes, which
+// yields them in ascending local id while touching n / 8 bytes instead of per-node flag arrays.
+// mark[u] - 1 is the place of a node that the block has; for any other node it is whatever the memory held, so a place counts
+// only if it exists and names the node.  (Clearing the map first and after each layer cost the step of a 7e6-node store a fill of
+// 28 MB and a launch per layer: 10.4 of 450 us for the fill and 2.5 for each of the launches.)
 constexpr int SAMPLE_ROWS_PER_WG = 4;
 
 __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(const int64_t* __restrict__ rowptr,
@@ -89,7 +214,9 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
                                                                                 const uint64_t* __restrict__ batch_id_dev,
                                                                                 int layer,
                                                                                 const int64_t* __restrict__ out_ptr,
-                                                                                int32_t* __restrict__ out_idx) {
+                                                                                int32_t* __restrict__ out_idx,
+                                                                                const int32_t* __restrict__ mark,
+                                                                                uint32_t* __restrict__ bits /*null: input layer*/) {
     const int lane = threadIdx.x & 63;
     const int64_t i = (int64_t)blockIdx.x * SAMPLE_ROWS_PER_WG + (threadIdx.x >> 6);
     const int64_t n_dst = sizes[SZ_DST];
@@ -99,8 +226,15 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
     const int64_t b = rowptr[v];
     const int64_t d = rowptr[v + 1] - b;
     const int64_t o = out_ptr[i];
+    auto take = [&](int64_t slot, int32_t u) {
+        out_idx[slot] = u;
+        if (!bits) return;
+        const int32_t at = mark[u];
+        const bool known = at > 0 && at <= n_dst && dst_nodes[at - 1] == u;
+        if (!known) atomicOr(&bits[u >> 5], 1u << (u & 31));
+    };
     if (d <= fanout) {
-        for (int64_t j = lane; j < d; j += 64) out_idx[o + j] = col[b + j];
+        for (int64_t j = lane; j < d; j += 64) take(o + j, col[b + j]);
         return;
     }
     const uint64_t h2 = mixM(mixM(h0 ^ (batch_id_dev ? *batch_id_dev : batch_id)) ^ (uint64_t)layer);
@@ -116,72 +250,270 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
     }
     int rank = 0;
     for (int t = 0; t < fanout; ++t) rank += __shfl(mine, t, 64) < mine ? 1 : 0;
-    if (lane < fanout) out_idx[o + rank] = col[b + mine];
+    if (lane < fanout) take(o + rank, col[b + mine]);
 }
 
-// New source nodes are collected in a bitmap over the partition's nodes (one bit each): the words'
-// population counts are prefix-summed and every non-empty word then numbers its own nodes, which
-// yields them in ascending local id while touching n / 8 bytes instead of per-node flag arrays.
-// mark[u] - 1 is the place of a node that the block has; for any other node it is whatever the memory held, so a place counts
-// only if it exists and names the node.  (Clearing the map first and after each layer cost the step of a 7e6-node store a fill of
-// 28 MB and a launch per layer: 10.4 of 450 us for the fill and 2.5 for each of the launches.)
-__global__ __launch_bounds__(256) void flag_new_kernel(const int32_t* __restrict__ idx_local,
-                                                       const int64_t* __restrict__ nnz_dev,
-                                                       const int32_t* __restrict__ mark, const int32_t* __restrict__ dst_nodes,
-                                                       const int64_t* __restrict__ n_dst_dev, uint32_t* __restrict__ bits) {
-    const int64_t nnz = *nnz_dev, n_dst = *n_dst_dev;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * 256) {
-        const int32_t u = idx_local[e];
-        const int32_t at = mark[u];
-        const bool known = at > 0 && at <= n_dst && dst_nodes[at - 1] == u;
-        if (!known) atomicOr(&bits[u >> 5], 1u << (u & 31));
-    }
-}
-
-// Also clears the bitmap for the next layer.
-__global__ __launch_bounds__(256) void assign_new_kernel(int64_t n_words, uint32_t* __restrict__ bits,
-                                                         const int32_t* __restrict__ wpos,
-                                                         const int64_t* __restrict__ n_dst_dev,
-                                                         int32_t* __restrict__ mark, int32_t* __restrict__ src_nodes) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_words) return;
-    uint32_t w = bits[i];
-    if (!w) return;
-    bits[i] = 0;
-    int32_t p = (int32_t)*n_dst_dev + wpos[i];
-    while (w) {
-        const int32_t u = (int32_t)(i * 32) + (__ffs(w) - 1);
-        src_nodes[p] = u;
-        mark[u] = ++p;
-        w &= w - 1;
-    }
-}
-
-// idx_blk[e] = block-local index of the source; keyT[e] = (source index << 32) | destination index.  The key
-// slots from the real number of edges to the bound receive `sentinel` (a source index above every real
-// one), so that the sort of the whole bound leaves them at the end.  Also completes the layer's sizes and
-// states the next layer's number of destinations (this layer's sources).
-__global__ __launch_bounds__(256) void relabel_kernel(const int64_t* __restrict__ ptr, int64_t* __restrict__ sizes,
-                                                      int64_t* __restrict__ next_n_dst, const int32_t* __restrict__ idx_local,
-                                                      const int32_t* __restrict__ mark, int32_t* __restrict__ idx_blk,
-                                                      uint64_t* __restrict__ keyT, int64_t nnz_bound, uint64_t sentinel,
-                                                      const int32_t* __restrict__ n_new) {
+// The bitmap's words: the new nodes of every word are numbered after the destinations and the new nodes of the words before it.
+// Also clears the bitmap for the next layer, completes the layer's sizes and states the next layer's number of destinations (this
+// layer's sources).  Parts of `rounds` rounds, a thread WD_PER consecutive words of each.
+constexpr int WD_THREADS = 256;
+constexpr int WD_PER = 16;
+constexpr int WD_ROUND = WD_THREADS * WD_PER;
+__global__ __launch_bounds__(WD_THREADS) void number_new_kernel(int64_t n_words /*rounded up to WD_PER, the words past the last empty*/, int rounds,
+                                                                unsigned long long* __restrict__ posted, uint32_t* __restrict__ bits,
+                                                                int64_t* __restrict__ sizes, int64_t* __restrict__ next_n_dst,
+                                                                int32_t* __restrict__ mark, int32_t* __restrict__ src_nodes) {
+    __shared__ unsigned long long wave_sum[WD_THREADS / 64];
+    __shared__ unsigned long long before_s;
+    const int tid = threadIdx.x;
     const int64_t n_dst = sizes[SZ_DST];
-    const int64_t nnz = sizes[SZ_NNZ];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        sizes[SZ_NEW] = *n_new;
-        sizes[SZ_SRC] = n_dst + *n_new;
-        *next_n_dst = n_dst + *n_new;
+    const int64_t part0 = (int64_t)blockIdx.x * rounds * WD_ROUND;
+    uint4 w[WD_PER / 4];
+    auto load = [&](int round) {
+        const int64_t i = part0 + (int64_t)round * WD_ROUND + WD_PER * tid;
+        unsigned long long sum = 0;
+#pragma unroll
+        for (int q = 0; q < WD_PER / 4; ++q) {
+            w[q] = i < n_words ? reinterpret_cast<const uint4*>(bits + i)[q] : make_uint4(0u, 0u, 0u, 0u);
+            sum += (unsigned long long)(__popc(w[q].x) + __popc(w[q].y) + __popc(w[q].z) + __popc(w[q].w));
+        }
+        return sum;
+    };
+    unsigned long long mine = 0, total, part_total;
+    for (int round = 0; round < rounds; ++round) mine += load(round);
+    (void)block_scan<WD_THREADS / 64>(mine, wave_sum, part_total);
+    if (tid < 64) {
+        const unsigned long long b = look_back(posted, (int)blockIdx.x, part_total);
+        if (tid == 0) before_s = b;
     }
-    for (int64_t e = nnz + (int64_t)blockIdx.x * 256 + threadIdx.x; e < nnz_bound; e += (int64_t)gridDim.x * 256)
-        keyT[e] = sentinel;
-    const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
-    if (i >= n_dst) return;
-    const int lane = threadIdx.x & 63;
-    for (int64_t e = ptr[i] + lane; e < ptr[i + 1]; e += 64) {
-        const int32_t s = mark[idx_local[e]] - 1;
-        idx_blk[e] = s;
-        keyT[e] = ((uint64_t)(uint32_t)s << 32) | (uint64_t)i;
+    __syncthreads();
+    unsigned long long at0 = before_s;
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        const int64_t n_new = (int64_t)(at0 + part_total);
+        sizes[SZ_NEW] = n_new;
+        sizes[SZ_SRC] = n_dst + n_new;
+        *next_n_dst = n_dst + n_new;
+    }
+    for (int round = 0; round < rounds; ++round) {
+        const unsigned long long sum = rounds == 1 ? mine : load(round);
+        unsigned long long at = at0 + block_scan<WD_THREADS / 64>(sum, wave_sum, total);
+        at0 += total;
+        if (sum == 0) continue;
+        const int64_t i = part0 + (int64_t)round * WD_ROUND + WD_PER * tid;
+        int32_t p = (int32_t)(n_dst + (int64_t)at);
+#pragma unroll
+        for (int q = 0; q < WD_PER / 4; ++q) {
+            const uint32_t word[4] = {w[q].x, w[q].y, w[q].z, w[q].w};
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                for (uint32_t left = word[h]; left; left &= left - 1) {
+                    const int32_t u = (int32_t)((i + 4 * q + h) * 32) + (__ffs(left) - 1);
+                    src_nodes[p] = u;
+                    mark[u] = ++p;
+                }
+            reinterpret_cast<uint4*>(bits + i)[q] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+}
+
+// ---- the transposed blocks, of all layers above the input layer in three launches (blockIdx.y: the layer).
+struct TransposeJob {
+    const int64_t* sizes;
+    const int64_t* ptr;                  // the block
+    const int32_t* idx_blk;
+    const int32_t* arrival;
+    const uint32_t* count_t;
+    int64_t src_bound;
+    int64_t* ptr_t;                      // [src_bound + 1]; the rows past the real sources are empty
+    int32_t* loose;                      // the rows' edges in order of arrival
+    int32_t* idx_t;
+    int rounds, parts;                   // of the sources
+    unsigned long long* posted;          // [2 PARTS] edges; long rows and their chunks
+    int32_t *long_row, *long_first;      // the split schedule of the long rows, up to its capacities
+    int64_t *chunk_begin, *chunk_end;
+    int64_t cap_long, cap_chunks;
+};
+struct TransposeJobs { TransposeJob d[GRP_MAX_LAYERS - 1]; };
+
+// Row pointers and the schedule of the long rows (as long_rows_emit_kernel makes it; places past the real ones do nothing).
+__global__ __launch_bounds__(CS_THREADS) void transpose_rows_kernel(TransposeJobs jobs) {
+    __shared__ unsigned long long wave_sum[CS_THREADS / 64];
+    __shared__ unsigned long long before_s[2];
+    const TransposeJob& t = jobs.d[blockIdx.y];
+    if ((int)blockIdx.x >= t.parts) return;
+    const int part = (int)blockIdx.x, tid = threadIdx.x;
+    const int64_t part0 = (int64_t)part * t.rounds * CS_ROUND;
+    uint32_t c[CS_PER];
+    auto load = [&](int round, unsigned long long& longs) {
+        unsigned long long sum = 0;
+        longs = 0;
+#pragma unroll
+        for (int q = 0; q < CS_PER; ++q) {
+            const int64_t i = part0 + (int64_t)round * CS_ROUND + CS_PER * tid + q;
+            c[q] = i < t.src_bound ? t.count_t[i] : 0u;
+            sum += c[q];
+            if (c[q] > (uint32_t)SPMM_LONG_ROW) longs += (1ull << 31) + (c[q] + SPMM_CHUNK - 1) / SPMM_CHUNK;
+        }
+        return sum;
+    };
+    unsigned long long mine = 0, mine_long = 0, total[2], round_total, l;
+    for (int round = 0; round < t.rounds; ++round) {
+        mine += load(round, l);
+        mine_long += l;
+    }
+    (void)block_scan<CS_THREADS / 64>(mine, wave_sum, total[0]);
+    (void)block_scan<CS_THREADS / 64>(mine_long, wave_sum, total[1]);
+    if (tid < 128) {                                         // a wavefront each
+        const unsigned long long b = look_back(t.posted + (tid / 64) * PARTS, part, tid < 64 ? total[0] : total[1]);
+        if ((tid & 63) == 0) before_s[tid / 64] = b;
+    }
+    __syncthreads();
+    unsigned long long at0 = before_s[0], long0 = before_s[1];
+    for (int round = 0; round < t.rounds; ++round) {
+        const unsigned long long sum = t.rounds == 1 ? mine : load(round, l);
+        if (t.rounds == 1) l = mine_long;
+        unsigned long long at = at0 + block_scan<CS_THREADS / 64>(sum, wave_sum, round_total);
+        at0 += round_total;
+        unsigned long long slot = long0 + block_scan<CS_THREADS / 64>(l, wave_sum, round_total);
+        long0 += round_total;
+#pragma unroll
+        for (int q = 0; q < CS_PER; ++q) {
+            const int64_t i = part0 + (int64_t)round * CS_ROUND + CS_PER * tid + q;
+            if (i <= t.src_bound) t.ptr_t[i] = (int64_t)at;
+            if (c[q] > (uint32_t)SPMM_LONG_ROW) {
+                const int64_t j = (int64_t)(slot >> 31);
+                int64_t k = (int64_t)(slot & 0x7FFFFFFFull);
+                slot += (1ull << 31) + (c[q] + SPMM_CHUNK - 1) / SPMM_CHUNK;
+                if (j < t.cap_long) {
+                    t.long_row[j] = (int32_t)i;
+                    t.long_first[j] = (int32_t)k;
+                }
+                const int64_t end = (int64_t)(at + c[q]);
+                for (int64_t e = (int64_t)at; e < end && k < t.cap_chunks; e += SPMM_CHUNK, ++k) {
+                    t.chunk_begin[k] = e;
+                    t.chunk_end[k] = e + SPMM_CHUNK < end ? e + SPMM_CHUNK : end;
+                }
+            }
+            at += c[q];
+        }
+    }
+    if (part == t.parts - 1) {                               // (long0 is the sum of all)
+        const int64_t n_long = (int64_t)(long0 >> 31), n_chunks = (int64_t)(long0 & 0x7FFFFFFFull);
+        for (int64_t j = n_long + tid; j <= t.cap_long; j += CS_THREADS) {
+            if (j < t.cap_long) t.long_row[j] = -1;
+            t.long_first[j] = (int32_t)(n_chunks < t.cap_chunks ? n_chunks : t.cap_chunks);
+        }
+        for (int64_t k = n_chunks + tid; k < t.cap_chunks; k += CS_THREADS) { t.chunk_begin[k] = 0; t.chunk_end[k] = 0; }
+    }
+}
+
+// Every edge to its source's row, in order of arrival.
+__global__ __launch_bounds__(256) void transpose_scatter_kernel(TransposeJobs jobs) {
+    const TransposeJob& t = jobs.d[blockIdx.y];
+    const int64_t n_dst = t.sizes[SZ_DST];
+    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n_dst; i += (int64_t)gridDim.x * 4)
+        for (int64_t e = t.ptr[i] + (threadIdx.x & 63); e < t.ptr[i + 1]; e += 64) t.loose[t.ptr_t[t.idx_blk[e]] + t.arrival[e]] = (int32_t)i;
+}
+
+// Every source's row in ascending order, whatever the order of arrival was.  A workgroup owns TS_ROWS rows: as many of them as fit
+// are taken into LDS, where an edge's place is the number of smaller ones in its row (of equal ones, by where they lie); a row of more
+// than TS_RANK edges is counted id by id instead, TS_CAP destinations at a time.  (7.5 us for two blocks of 6e3 and 7e4 places; walking the
+// rows one by one to see which fit took 27 us more.)
+constexpr int TS_THREADS = 256;
+constexpr int TS_ROWS = 256;
+constexpr int TS_CAP = 8192;
+constexpr int TS_RANK = 128;
+__global__ __launch_bounds__(TS_THREADS) void transpose_sort_kernel(TransposeJobs jobs) {
+    __shared__ uint32_t buf[TS_CAP];
+    __shared__ uint32_t off[TS_ROWS + 1];
+    __shared__ unsigned long long long_rows[TS_ROWS / 64];   // the rows that are too long to be ranked
+    __shared__ uint32_t wave_sum[TS_THREADS / 64];
+    static_assert(TS_ROWS == TS_THREADS, "a thread per row");
+    const TransposeJob& t = jobs.d[blockIdx.y];
+    const int64_t n_src = t.sizes[SZ_SRC], n_dst = t.sizes[SZ_DST];
+    const int tid = threadIdx.x;
+    for (int64_t row0 = (int64_t)blockIdx.x * TS_ROWS; row0 < n_src; row0 += (int64_t)gridDim.x * TS_ROWS) {
+        const int rows = (int)(n_src - row0 < TS_ROWS ? n_src - row0 : TS_ROWS);
+        const int64_t e0 = t.ptr_t[row0];
+        const uint32_t mine = (uint32_t)(t.ptr_t[row0 + (tid < rows ? tid : rows)] - e0), next = (uint32_t)(t.ptr_t[row0 + (tid < rows ? tid + 1 : rows)] - e0);
+        off[tid] = mine;
+        if (tid == TS_ROWS - 1) off[TS_ROWS] = next;         // (rows past the last are empty)
+        const unsigned long long too_long = __ballot(next - mine > (uint32_t)TS_RANK);
+        if ((tid & 63) == 0) long_rows[tid / 64] = too_long;
+        __syncthreads();
+        const int32_t* const in = t.loose + e0;
+        int32_t* const out = t.idx_t + e0;
+        for (int ra = 0; ra < rows;) {                           // (uniform)
+            const uint32_t base = off[ra];
+            int rb = rows;                                       // rows ra .. rb - 1 fit, and none of them is too long to be ranked
+            for (int q = TS_ROWS / 64 - 1; q >= ra / 64; --q) {
+                const unsigned long long l = q == ra / 64 ? long_rows[q] & (~0ull << (ra & 63)) : long_rows[q];
+                if (l) rb = 64 * q + __ffsll(l) - 1;
+            }
+            if (off[rb] - base > (uint32_t)TS_CAP) {
+                int x = ra, y = rb;                              // off[x] - base <= TS_CAP < off[y] - base
+                while (y - x > 1) {
+                    const int mid = (x + y) >> 1;
+                    if (off[mid] - base <= (uint32_t)TS_CAP) x = mid; else y = mid;
+                }
+                rb = x;
+            }
+            if (rb > ra) {
+                const uint32_t m = off[rb] - base;
+                for (uint32_t e = tid; e < m; e += TS_THREADS) buf[e] = (uint32_t)in[base + e];
+                __syncthreads();
+                for (uint32_t e = tid; e < m; e += TS_THREADS) {
+                    int lo = ra, hi = rb;                        // the row of e: off[lo] <= base + e < off[lo + 1]
+                    while (hi - lo > 1) {
+                        const int mid = (lo + hi) >> 1;
+                        if (off[mid] <= base + e) lo = mid; else hi = mid;
+                    }
+                    const uint32_t b = off[lo] - base, z = off[lo + 1] - base, key = buf[e];
+                    uint32_t rank = 0;
+                    for (uint32_t j = b; j < z; j += 8) {    // (eight reads in flight)
+                        uint32_t other[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) other[q] = buf[j + q < z ? j + q : e];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) rank += j + q < z && (other[q] < key || (other[q] == key && j + q < e)) ? 1u : 0u;
+                    }
+                    out[base + b + rank] = (int32_t)key;
+                }
+                __syncthreads();
+                ra = rb;
+                continue;
+            }
+            const uint32_t m = off[ra + 1] - base;               // one long row
+            int32_t* o = out + base;
+            for (int64_t d0 = 0; d0 < n_dst; d0 += TS_CAP) {
+                for (int i = tid; i < TS_CAP; i += TS_THREADS) buf[i] = 0u;
+                __syncthreads();
+                constexpr int U = 8;
+                for (uint32_t j0 = 0; j0 < m; j0 += U * TS_THREADS) {
+                    int64_t d[U];
+    #pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t j = j0 + u * TS_THREADS + tid;
+                        d[u] = (int64_t)in[base + (j < m ? j : m - 1)] - d0;
+                        if (j >= m) d[u] = -1;
+                    }
+    #pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (d[u] >= 0 && d[u] < TS_CAP) atomicAdd(&buf[d[u]], 1u);
+                }
+                __syncthreads();
+                constexpr int PER = TS_CAP / TS_THREADS;
+                uint32_t sum = 0, total;
+                for (int i = 0; i < PER; ++i) sum += buf[tid * PER + i];
+                uint32_t at = block_scan<TS_THREADS / 64>(sum, wave_sum, total);
+                for (int i = 0; i < PER; ++i)
+                    for (uint32_t c = buf[tid * PER + i]; c > 0; --c) o[at++] = (int32_t)(d0 + tid * PER + i);
+                o += total;
+                __syncthreads();
+            }
+            ra = ra + 1;
+        }
+        __syncthreads();                                     // off is filled anew
     }
 }
 
@@ -198,56 +530,52 @@ void sampler_bounds(int64_t n, int64_t n_seeds, const int32_t* fanouts, int k, S
 }
 
 struct SamplerLayerBufs {
-    int64_t* cnt;        // [dst+1] counts, then in place the block row pointer
     int64_t* ptr;        // [dst+1]
-    int32_t* cnt32;      // [dst]
+    int32_t* cnt32;      // [dst] (the seeds' layer)
     int32_t* idx_local;  // [nnz] partition-local source ids
     int32_t* idx_blk;    // [nnz] block-local (layers >= 1)
     int32_t* src_nodes;  // [src] (layers >= 1)
-    uint64_t *keys, *keys_sorted;  // [nnz] (layers >= 1)
+    int32_t *arrival, *loose;      // [nnz] (layers >= 1) scratch of the transposed block
+    uint32_t* count_t;             // [src] (layers >= 1)
     int64_t* ptrT;       // [src+1]
     int32_t* idxT;       // [nnz]
     float* inv_in;       // [dst]
     int32_t *lr_row, *lr_first;    // long rows of the transposed block
     int64_t *lr_cb, *lr_ce;
-    int64_t* lr_scan;              // [src+1] scratch of the schedule's construction
     int64_t lr_cap_long, lr_cap_chunks;
+    unsigned long long* posted;    // [4 PARTS] of the rows' counts, the new nodes and the transposed rows (two)
 };
 
 struct SamplerBufs {
     SamplerLayerBufs L[GRP_MAX_LAYERS];
     int32_t* seeds;                     // [n_seeds] the caller's seeds, range-checked
     int64_t* sizes;                     // [SZ_PER_LAYER * GRP_MAX_LAYERS] the blocks' real sizes (see the enum)
-    int64_t* bad;                       // [2] seeds outside the partition (carved just before `bits`: one fill clears both)
     int32_t* mark;                      // [n] block-local index + 1 of the current layer's nodes, anything elsewhere
-    uint32_t* bits;                     // [n_words + 1] bitmap of newly reached nodes (the last word stays 0)
-    int32_t* wpos;                      // [n_words + 1] set bits in the words before each word
-    int64_t n_words;
-    void *scan_tmp, *sort_tmp;
-    void* scan_tmp_side;                // the prefix sums of the transposed blocks (built on a helper stream)
-    size_t scan_bytes, sort_bytes;
+    // what starts at zero, carved back to back: one fill clears it
+    int64_t* bad;                       // [2] seeds outside the partition
+    uint32_t* bits;                     // [n_words] bitmap of newly reached nodes
+    int64_t n_words;                    // rounded up to what a thread of number_new_kernel takes
+    char *clear_from, *clear_to;
     size_t total;
 };
 
 static SamplerBufs carve_sampler(int64_t n, const SamplerBounds& b, int k, void* ws, size_t ws_bytes) {
     SamplerBufs s;
     Bump bump(ws, ws_bytes);
-    int64_t max_nnz = 1, max_dst = 1;
     s.sizes = bump.take<int64_t>(SZ_PER_LAYER * GRP_MAX_LAYERS);
     s.seeds = bump.take<int32_t>((size_t)b.dst[k - 1]);
     for (int l = 0; l < k; ++l) {
         SamplerLayerBufs& L = s.L[l];
-        L.cnt = bump.take<int64_t>((size_t)b.dst[l] + 1);
+        L = SamplerLayerBufs{};
         L.ptr = bump.take<int64_t>((size_t)b.dst[l] + 1);
-        L.cnt32 = bump.take<int32_t>((size_t)b.dst[l]);
+        if (l == k - 1) L.cnt32 = bump.take<int32_t>((size_t)b.dst[l]);
         L.idx_local = bump.take<int32_t>((size_t)b.nnz[l]);
         L.inv_in = bump.take<float>((size_t)b.dst[l]);
-        if (b.dst[l] > max_dst) max_dst = b.dst[l];
         if (l > 0) {
             L.idx_blk = bump.take<int32_t>((size_t)b.nnz[l]);
             L.src_nodes = bump.take<int32_t>((size_t)b.src[l]);
-            L.keys = bump.take<uint64_t>((size_t)b.nnz[l]);
-            L.keys_sorted = bump.take<uint64_t>((size_t)b.nnz[l]);
+            L.arrival = bump.take<int32_t>((size_t)b.nnz[l]);
+            L.loose = bump.take<int32_t>((size_t)b.nnz[l]);
             L.ptrT = bump.take<int64_t>((size_t)b.src[l] + 1);
             L.idxT = bump.take<int32_t>((size_t)b.nnz[l]);
             L.lr_cap_long = b.nnz[l] / SPMM_LONG_ROW + 1;
@@ -256,33 +584,23 @@ static SamplerBufs carve_sampler(int64_t n, const SamplerBounds& b, int k, void*
             L.lr_first = bump.take<int32_t>((size_t)L.lr_cap_long + 1);
             L.lr_cb = bump.take<int64_t>((size_t)L.lr_cap_chunks);
             L.lr_ce = bump.take<int64_t>((size_t)L.lr_cap_chunks);
-            L.lr_scan = bump.take<int64_t>((size_t)b.src[l] + 1);
-            if (b.nnz[l] > max_nnz) max_nnz = b.nnz[l];
-        } else {
-            L.idx_blk = nullptr; L.src_nodes = nullptr; L.keys = L.keys_sorted = nullptr;
-            L.ptrT = nullptr; L.idxT = nullptr; L.lr_row = L.lr_first = nullptr; L.lr_cb = L.lr_ce = nullptr;
-            L.lr_scan = nullptr;
-            L.lr_cap_long = L.lr_cap_chunks = 0;
         }
     }
     s.mark = bump.take<int32_t>((size_t)n);
-    s.n_words = cdiv(n, 32);
+    s.n_words = round_up(cdiv(n, 32), WD_PER);
     s.bad = bump.take<int64_t>(2);
-    s.bits = bump.take<uint32_t>((size_t)s.n_words + 1);
-    s.wpos = bump.take<int32_t>((size_t)s.n_words + 1);
-    s.scan_bytes = scan_temp_bytes(s.n_words + 1 > max_dst + 1 ? s.n_words + 1 : max_dst + 1);
-    s.scan_tmp = bump.take<char>(s.scan_bytes);
-    s.scan_tmp_side = k > 1 ? bump.take<char>(s.scan_bytes) : nullptr;
-    s.sort_bytes = k > 1 ? sort_keys_temp_bytes(max_nnz) : 0;
-    s.sort_tmp = bump.take<char>(s.sort_bytes);
+    for (int l = 0; l < k; ++l) {
+        s.L[l].posted = bump.take<unsigned long long>(4 * PARTS);
+        if (l > 0) s.L[l].count_t = bump.take<uint32_t>((size_t)b.src[l]);
+    }
+    s.bits = bump.take<uint32_t>(k > 1 ? (size_t)s.n_words : 1);
+    s.clear_from = (char*)s.bad;
+    s.clear_to = (char*)(s.bits + (k > 1 ? s.n_words : 1));
     s.total = bump.total();
     return s;
 }
 
 size_t sampler_workspace_bytes(int64_t n, const SamplerBounds& b, int k) { return carve_sampler(n, b, k, nullptr, 0).total; }
-
-// One thread per item (item counts here stay below 2^31, so the grid fits).
-static unsigned blocks_for(int64_t work) { return (unsigned)cdiv(work > 0 ? work : 1, 256); }
 
 grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, int k, void* ws, size_t ws_bytes,
                          Block* blocks, LongRows* long_bwd_store, const int64_t** nnz_parts_dev,
@@ -300,34 +618,53 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
     SamplerBufs s = carve_sampler(n, bd, k, ws, ws_bytes);
     if (s.total > ws_bytes) return fail(GRP_EWORKSPACE, "mini-batch: sampler workspace %zu < %zu", ws_bytes, s.total);
 
-    {   // the bad-seed counter and, with more than one layer, the bitmap start at zero
-        // (carved back to back: one fill covers them)
-        char* const lo = (char*)s.bad;
-        char* const hi = k > 1 ? (char*)(s.bits + s.n_words + 1) : (char*)(s.bad + 2);
-        GRP_TRY(launch_fill_zero(lo, (size_t)(hi - lo), st));
-    }
-    hipLaunchKernelGGL(check_seeds_kernel, dim3(blocks_for(o->n_seeds)), dim3(256), 0, st, o->seeds, (int64_t)o->n_seeds, n,
-                       s.seeds, s.bad, s.sizes + SZ_PER_LAYER * (k - 1) + SZ_DST);
-    GRP_LAUNCH_CHECK();
+    GRP_TRY(launch_fill_zero(s.clear_from, (size_t)(s.clear_to - s.clear_from), st));
     *bad_seeds_dev = s.bad;
-    SideLane* const lane = (k > 1 && !(o->flags & GRP_STEP_ONE_STREAM)) ? side_lane(st) : nullptr;
     const uint64_t h0 = mixM(o->sampler_seed);
     const int32_t* dst_nodes = s.seeds;
+    RelabelJob relabel{};                                // of the layer before
+    TransposeJobs jobs{};
     for (int l = k - 1; l >= 0; --l) {
         SamplerLayerBufs& L = s.L[l];
         int64_t* const D = s.sizes + SZ_PER_LAYER * l;   // this layer's sizes; D[SZ_DST] is already there
         const int64_t dst_bound = bd.dst[l];
         const int f = o->fanouts[l];
-        hipLaunchKernelGGL(sample_count_kernel, dim3(blocks_for(dst_bound + 1)), dim3(256), 0, st, part->rowptr, dst_nodes,
-                           (const int64_t*)(D + SZ_DST), dst_bound, f, L.cnt, L.cnt32, L.inv_in, l > 0 ? s.mark : nullptr,
-                           l > 0 ? L.src_nodes : nullptr);
+        const bool top = l == k - 1;
+        const ScanPlan cp = scan_plan(dst_bound + 1, CS_ROUND);
+        const CountJob count{part->rowptr, dst_nodes, top ? o->seeds : nullptr, n, (int64_t)o->n_seeds, D, dst_bound, f, cp.rounds, cp.parts, L.posted,
+                             L.ptr, L.cnt32, L.inv_in, top && l > 0 ? s.mark : nullptr, L.src_nodes, (unsigned long long*)s.bad};
+        hipLaunchKernelGGL(count_rows_kernel, dim3((unsigned)(cp.parts + (relabel.ptr ? cdiv(relabel.dst_bound, 4) : 0))), dim3(CS_THREADS), 0, st, count,
+                           relabel);
         GRP_LAUNCH_CHECK();
-        GRP_TRY(exclusive_scan_i64(s.scan_tmp, s.scan_bytes, L.cnt, L.ptr, dst_bound + 1, st));
+        if (l == 0 && k > 1) {
+            // The transposed blocks are read by the backward pass only: they are built on a helper stream, beside the choice of the input
+            // layer's edges and the forward pass.
+            SideLane* const lane = !(o->flags & GRP_STEP_ONE_STREAM) ? side_lane(st) : nullptr;
+            hipStream_t bst = st;
+            if (lane) {
+                GRP_HIP(hipEventRecord(lane->fork[0], st));
+                GRP_HIP(hipStreamWaitEvent(lane->stream, lane->fork[0], 0));
+                bst = lane->stream;
+            }
+            int parts = 0;
+            for (int q = 1; q < k; ++q) parts = std::max(parts, jobs.d[q - 1].parts);
+            const int64_t dst_groups = std::min(cdiv(bd.dst[1], 4), (int64_t)1 << 18);             // (layer 1 is the largest)
+            const int64_t src_groups = std::min(cdiv(bd.src[1], TS_ROWS), (int64_t)1 << 18);
+            hipLaunchKernelGGL(transpose_rows_kernel, dim3((unsigned)parts, (unsigned)(k - 1)), dim3(CS_THREADS), 0, bst, jobs);
+            hipLaunchKernelGGL(transpose_scatter_kernel, dim3((unsigned)dst_groups, (unsigned)(k - 1)), dim3(256), 0, bst, jobs);
+            hipLaunchKernelGGL(transpose_sort_kernel, dim3((unsigned)src_groups, (unsigned)(k - 1)), dim3(TS_THREADS), 0, bst, jobs);
+            GRP_LAUNCH_CHECK();
+            if (lane) {
+                GRP_HIP(hipEventRecord(lane->join, lane->stream));
+                *transposed_ready = lane->join;
+            }
+        }
         {
             ProfScope ps("sample_select", st);
             hipLaunchKernelGGL(sample_select_kernel, dim3((unsigned)cdiv(dst_bound, SAMPLE_ROWS_PER_WG)),
                                dim3(64 * SAMPLE_ROWS_PER_WG), 0, st, part->rowptr, part->col, part->l2g, dst_nodes, D, f,
-                               h0, (uint64_t)o->batch_id, o->batch_id_dev, l, (const int64_t*)L.ptr, L.idx_local);
+                               h0, (uint64_t)o->batch_id, o->batch_id_dev, l, (const int64_t*)L.ptr, L.idx_local, (const int32_t*)s.mark,
+                               l > 0 ? s.bits : nullptr);
             GRP_LAUNCH_CHECK();
         }
 
@@ -340,7 +677,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         B.inv_in = L.inv_in;
         B.long_fwd = nullptr;                            // rows hold at most `fanout` edges
         nnz_parts_dev[l] = D + SZ_NNZ;
-        if (l == k - 1) *seed_counts_dev = L.cnt32;
+        if (top) *seed_counts_dev = L.cnt32;
         if (l == 0) {
             B.idx = L.idx_local;
             B.n_in = n;
@@ -349,41 +686,20 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
             B.ptrT = nullptr; B.idxT = nullptr; B.long_bwd = nullptr;
             break;
         }
-        // new source nodes in ascending local id, block-local relabelling, transposed block
-        const int64_t src_bound = bd.src[l], nnz_bound = bd.nnz[l];
-        hipLaunchKernelGGL(flag_new_kernel, dim3(blocks_for(nnz_bound)), dim3(256), 0, st, (const int32_t*)L.idx_local,
-                           (const int64_t*)(D + SZ_NNZ), (const int32_t*)s.mark, dst_nodes, (const int64_t*)(D + SZ_DST), s.bits);
+        // new source nodes in ascending local id
+        const int64_t src_bound = bd.src[l];
+        const ScanPlan wp = scan_plan(s.n_words, WD_ROUND);
+        hipLaunchKernelGGL(number_new_kernel, dim3((unsigned)wp.parts), dim3(WD_THREADS), 0, st, s.n_words, wp.rounds, L.posted + PARTS, s.bits, D,
+                           s.sizes + SZ_PER_LAYER * (l - 1) + SZ_DST, s.mark, L.src_nodes);
         GRP_LAUNCH_CHECK();
-        GRP_TRY(exclusive_scan_popcount(s.scan_tmp, s.scan_bytes, s.bits, s.wpos, s.n_words + 1, st));
-        hipLaunchKernelGGL(assign_new_kernel, dim3(blocks_for(s.n_words)), dim3(256), 0, st, s.n_words, s.bits,
-                           (const int32_t*)s.wpos, (const int64_t*)(D + SZ_DST), s.mark, L.src_nodes);
-        GRP_LAUNCH_CHECK();
-        // Keys are (source << 32 | destination); the unused slots up to the bound get the source index
-        // src_bound, which no real source reaches, and the sort covers the bits of that value.
-        int bits = 1;
-        while (bits < 32 && ((int64_t)1 << bits) <= src_bound) ++bits;
-        hipLaunchKernelGGL(relabel_kernel, dim3((unsigned)cdiv(dst_bound, 4)), dim3(256), 0, st, (const int64_t*)L.ptr, D,
-                           s.sizes + SZ_PER_LAYER * (l - 1) + SZ_DST, (const int32_t*)L.idx_local, (const int32_t*)s.mark,
-                           L.idx_blk, L.keys, nnz_bound, (uint64_t)src_bound << 32, (const int32_t*)(s.wpos + s.n_words));
-        GRP_LAUNCH_CHECK();
-        // The transposed block is read by the backward pass only: it is built on the helper stream, beside the
-        // sampling of the next layers and the forward pass.
-        hipStream_t bst = st;
-        void* scan_tmp_t = s.scan_tmp;
-        if (lane) {
-            GRP_HIP(hipEventRecord(lane->fork[l], st));
-            GRP_HIP(hipStreamWaitEvent(lane->stream, lane->fork[l], 0));
-            bst = lane->stream;
-            scan_tmp_t = s.scan_tmp_side;
-        }
-        GRP_TRY(sort_keys_u64(s.sort_tmp, s.sort_bytes, L.keys, L.keys_sorted, nnz_bound, 32u + (unsigned)bits, bst));
-        // Over src_bound rows: those past the real sources come out empty (their pointer is the real number
-        // of edges, where the sentinels begin), and the entries of idxT past that number are never read.
-        GRP_TRY(launch_csr_from_sorted_keys(L.keys_sorted, nnz_bound, src_bound, L.ptrT, L.idxT, bst));
+        relabel = RelabelJob{L.ptr, D, dst_bound, L.idx_local, s.mark, L.idx_blk, L.arrival, L.count_t};
+        const ScanPlan tp = scan_plan(src_bound + 1, CS_ROUND);
+        jobs.d[l - 1] = TransposeJob{D, L.ptr, L.idx_blk, L.arrival, L.count_t, src_bound, L.ptrT, L.loose, L.idxT, tp.rounds, tp.parts,
+                                     L.posted + 2 * PARTS, L.lr_row, L.lr_first, L.lr_cb, L.lr_ce, L.lr_cap_long, L.lr_cap_chunks};
         LongRows& lr = long_bwd_store[l];
         lr.long_row = L.lr_row; lr.long_first = L.lr_first; lr.chunk_begin = L.lr_cb; lr.chunk_end = L.lr_ce;
-        GRP_TRY(build_long_rows_device(L.ptrT, src_bound, &lr, L.lr_cap_long, L.lr_cap_chunks, L.lr_scan, scan_tmp_t,
-                                       s.scan_bytes, bst));
+        lr.n_long = (int32_t)L.lr_cap_long;              // (the launches cover the capacities)
+        lr.n_chunks = (int32_t)L.lr_cap_chunks;
         B.idx = L.idx_blk;
         B.n_in = src_bound;
         B.n_in_dev = D + SZ_SRC;
@@ -392,10 +708,6 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         B.idxT = L.idxT;
         B.long_bwd = &lr;
         dst_nodes = L.src_nodes;
-    }
-    if (lane) {
-        GRP_HIP(hipEventRecord(lane->join, lane->stream));
-        *transposed_ready = lane->join;
     }
     return GRP_OK;
 }
