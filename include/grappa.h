@@ -348,6 +348,19 @@ grp_status grp_train_step(const grp_partition_t* part, const grp_model_desc* mod
                           const float* weights, void* workspace, size_t workspace_bytes,
                           void* stream, float* grad_out, grp_step_stats* stats_out);
 
+/* `count` train steps of one model and one set of weights, as that many calls of grp_train_step in turn: the same results, bit
+ * for bit, but the steps' launches are merged where they are the same kernel (small partitions and mini-batches are bound by their
+ * number).  HOST arrays of `count` device pointers each: features, labels, train_masks (the array or any entry may be
+ * null), workspaces (workspace_bytes each), grads_out and stats_out must not overlap; opts: HOST array of `count` options.
+ * Steps that cannot be merged (attention models, weighted partitions, partitions with the sliced schedule, wide products over many
+ * rows, profiling switched on) run one after another.  Capturable like grp_train_step.  Errors: as there; of
+ * merged steps none has been started when an argument of any is refused. */
+grp_status grp_train_steps(int32_t count, const grp_partition_t* const* parts, const grp_model_desc* model,
+                           const grp_step_opts* opts, const void* const* features,
+                           const int32_t* const* labels, const uint8_t* const* train_masks,
+                           const float* weights, void* const* workspaces, size_t workspace_bytes,
+                           void* stream, float* const* grads_out, grp_step_stats* const* stats_out);
+
 /* Seed order of an epoch in mini-batch mode (the per-worker loop over batches of the phase-parallel
  * algorithm; the paper lets every worker visit all of its training nodes once per epoch and fixes no
  * order): the partition's training nodes (train_mask[v] != 0; NULL = every node; DEV uint8[n]) sorted

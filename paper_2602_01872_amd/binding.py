@@ -102,6 +102,7 @@ def load() -> C.CDLL:
         "grp_optimizer_step": [C.POINTER(OptimizerDesc), i64, i64, vp, vp, vp, vp, vp],
         "grp_spmm_workspace_bytes": [vp, i32, i32, C.POINTER(sz)],
         "grp_spmm": [vp, i32, i32, i32, i32, vp, i64, i32, vp, i64, vp, sz, vp],
+        "grp_train_steps": [i32, vp, C.POINTER(ModelDesc), vp, vp, vp, vp, vp, vp, sz, vp, vp, vp],
         "grp_spmm_static": [vp, i32, i32, i32, i32, vp, i64, i32, vp, i64, vp],
         "grp_gemm_nn": [i64, i32, i32, vp, i64, i32, vp, i64, vp, i64, vp],
         "grp_gemm_nt": [i64, i32, i32, vp, i64, i32, vp, i64, vp, i64, vp],
@@ -453,6 +454,16 @@ def grp_train_step(part: Partition, model: ModelDesc, opts: StepOpts, features, 
                                  _ptr(grad_out), _ptr(stats_out)))
 
 
+def grp_train_steps(parts, model: ModelDesc, opts, features, labels, train_masks, weights, workspaces, grads_out, stats_out, stream=None):
+    """Lists of one entry per step (``train_masks``: a list or None); the steps' launches are merged, the results are those of
+    ``grp_train_step`` for each in turn.  Workspaces, gradients and records must be distinct."""
+    n = len(parts)
+    ptrs = lambda ts: (C.c_void_p * n)(*[_ptr(t) for t in ts])
+    _check(load().grp_train_steps(n, (C.c_void_p * n)(*[p.handle for p in parts]), C.byref(model), (StepOpts * n)(*opts), ptrs(features),
+                                  ptrs(labels), None if train_masks is None else ptrs(train_masks), _ptr(weights), ptrs(workspaces),
+                                  min(w.numel() * w.element_size() for w in workspaces), _stream(stream), ptrs(grads_out), ptrs(stats_out)))
+
+
 def grp_aggregate(grads, ld_grads: int, stats, K: int, P: int, variant: int, update, c_out=None, stream=None):
     _check(load().grp_aggregate(_ptr(grads), ld_grads, _ptr(stats), K, P, variant, _stream(stream), _ptr(update),
                                 _ptr(c_out)))
@@ -559,6 +570,6 @@ def read_stats(stats: torch.Tensor) -> np.ndarray:
 def exported_symbols():
     return ["grp_last_error", "grp_partition", "grp_node_owners", "grp_epoch_seeds", "grp_gather_rows", "grp_partition_weighted", "grp_partition_weights", "grp_partition_from_local_coo", "grp_partition_from_csr", "grp_partition_view",
             "grp_partition_destroy", "grp_release_memory", "grp_chunks_build", "grp_chunks_build_assigned", "grp_chunks_destroy", "grp_partition_from_chunks",
-            "grp_partition_base_mask", "grp_partition_halo", "grp_param_count", "grp_step_workspace_bytes", "grp_step_activation", "grp_step_block", "grp_train_step",
+            "grp_partition_base_mask", "grp_partition_halo", "grp_param_count", "grp_step_workspace_bytes", "grp_step_activation", "grp_step_block", "grp_train_step", "grp_train_steps",
             "grp_aggregate", "grp_aggregate_ptrs", "grp_optimizer_step", "grp_spmm", "grp_spmm_workspace_bytes", "grp_spmm_static", "grp_gemm_nn", "grp_gemm_nt", "grp_gemm_tn_workspace_bytes", "grp_gemm_tn",
             "grp_set_slice_policy", "grp_sweep_chunk", "grp_super_epoch_epochs", "grp_controller_create", "grp_controller_observe", "grp_controller_observe_stats", "grp_controller_end_epoch", "grp_controller_state", "grp_controller_destroy", "grp_profile_enable", "grp_profile_report"]

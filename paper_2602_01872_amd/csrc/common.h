@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 #include <hip/hip_bf16.h>
 
@@ -60,6 +61,98 @@ struct ProfScope {
                              hipGetErrorString(e_), __FILE__, __LINE__);                \
     } while (0)
 
+}  // namespace grp
+
+// ---------------------------------------------------------------- launches of several steps merged
+// A launch costs the device about 3.6 us whatever it does, and the steps of a phase's partitions are the same launches on other data.
+// (Four steps of 2 500 nodes, GCN 64-64-8: some 100 launches and 427 us one after another, 28 and 145 us merged; separate streams do not help:
+// launches of different queues cost the same 3.6 us each.)
+// grp_train_steps lets every step record its launches instead of making them, and then makes one launch of those that are the same
+// kernel at the same point of their steps: blockIdx.z says whose arguments a workgroup takes.
+//
+// A kernel takes part through three things: its body as a device function whose first parameter is the step's own gridDim.x, the kernel
+// around it, and an Op that names the body:  struct Op { static constexpr int THREADS, WGS; template <class... A> static
+// __device__ void run(unsigned gx, const A&... a) { body(gx, a...); } }.  launch(kernel, Op(), ...) then does either.
+namespace grp {
+
+template <class... P> struct Pack {};
+template <class H, class... T> struct Pack<H, T...> { H head; Pack<T...> tail; };
+template <class... P> struct Packer { static Pack<> make() { return {}; } };
+template <class H, class... T> struct Packer<H, T...> {
+    static Pack<H, T...> make(H h, T... t) { return Pack<H, T...>{h, Packer<T...>::make(t...)}; }
+};
+template <class Op, class... A> __device__ __forceinline__ void unpack(unsigned gx, const Pack<>&, const A&... a) { Op::run(gx, a...); }
+template <class Op, class H, class... T, class... A>
+__device__ __forceinline__ void unpack(unsigned gx, const Pack<H, T...>& p, const A&... a) { unpack<Op>(gx, p.tail, a..., p.head); }
+
+constexpr size_t MANY_ARG_BYTES = 3584;            // of the 4 KB that a launch's arguments may take
+constexpr int MANY_MOST = 8;
+template <class P> constexpr int many_of() {
+    return MANY_ARG_BYTES / (sizeof(P) + 4) >= MANY_MOST ? MANY_MOST : (int)(MANY_ARG_BYTES / (sizeof(P) + 4));
+}
+template <class P> struct Many {
+    P at[many_of<P>() > 0 ? many_of<P>() : 1];
+    uint32_t gx[many_of<P>() > 0 ? many_of<P>() : 1];
+};
+template <class Op, class P> __global__ __launch_bounds__(Op::THREADS, Op::WGS) void many_kernel(Many<P> m) {
+    const uint32_t gx = m.gx[blockIdx.z];
+    if (blockIdx.x < gx) unpack<Op>(gx, m.at[blockIdx.z]);
+}
+
+struct LaunchRecord {
+    void (*go)(const LaunchRecord* const* recs, int count, hipStream_t st);     // launches `count` records of this kind (the same go)
+    dim3 grid;
+    std::vector<unsigned char> args;               // a Pack
+};
+struct LaunchRecorder {
+    std::vector<LaunchRecord> list;
+    bool unsupported = false;                      // a launch that cannot be merged was asked for (and not made)
+};
+extern thread_local LaunchRecorder* g_recorder;    // null: launches are made at once
+
+template <class Op, class P> void launch_many(const LaunchRecord* const* recs, int count, hipStream_t st) {
+    constexpr int N = many_of<P>();
+    static_assert(N > 0, "the arguments of one step must fit a launch");
+    for (int i0 = 0; i0 < count; i0 += N) {
+        const int n = count - i0 < N ? count - i0 : N;
+        Many<P> m;
+        memset((void*)&m, 0, sizeof m);
+        dim3 grid(1, 1, (unsigned)n);
+        for (int i = 0; i < n; ++i) {
+            const LaunchRecord& r = *recs[i0 + i];
+            memcpy((void*)&m.at[i], r.args.data(), sizeof(P));
+            m.gx[i] = r.grid.x;
+            grid.x = std::max(grid.x, r.grid.x);
+            grid.y = r.grid.y;                     // (alike: launch_merged)
+        }
+        hipLaunchKernelGGL((many_kernel<Op, P>), grid, dim3(Op::THREADS), 0, st, m);
+    }
+}
+
+// One launch, made or recorded (no dynamic LDS, one thread count: Op::THREADS).
+template <class Op, class... P, class... A> void launch(void (*kernel)(P...), Op, dim3 grid, hipStream_t st, A... a) {
+    if (!g_recorder) {
+        hipLaunchKernelGGL(kernel, grid, dim3(Op::THREADS), 0, st, P(a)...);
+        return;
+    }
+    const Pack<P...> p = Packer<P...>::make(P(a)...);
+    g_recorder->list.emplace_back();
+    LaunchRecord& r = g_recorder->list.back();
+    r.go = &launch_many<Op, Pack<P...>>;
+    r.grid = grid;
+    r.args.assign((const unsigned char*)&p, (const unsigned char*)&p + sizeof p);
+}
+// In front of a launch that has no Op: false if it must not be made, because launches are being recorded (the steps are then made one by
+// one).
+inline bool may_launch() {
+    if (g_recorder) g_recorder->unsupported = true;
+    return !g_recorder;
+}
+#define GRP_PLAIN_LAUNCH(...) do { if (grp::may_launch()) hipLaunchKernelGGL(__VA_ARGS__); } while (0)
+
+}  // namespace grp
+
+namespace grp {
 // ---------------------------------------------------------------- device memory of the builders (runtime.hip)
 // As hipMalloc / hipFree, from a bounded cache of freed blocks.
 hipError_t pool_alloc(void** p, size_t bytes);
@@ -316,11 +409,12 @@ struct PackJob {
     int64_t ld_out;
     float scale;             // every element is multiplied by this
 };
-struct PackJobs {
+template <int MOST> struct PackJobsOf {
     int32_t n = 0;
-    PackJob job[4 * GRP_MAX_LAYERS];
-    int64_t begin[4 * GRP_MAX_LAYERS + 1] = {0};
+    PackJob job[MOST];
+    int64_t begin[MOST + 1] = {0};
 };
+using PackJobs = PackJobsOf<4 * GRP_MAX_LAYERS>;
 // Appends a job: the output is written with its columns zero-padded to a multiple of 4 and its
 // rows zero-padded to out_rows_pad.
 void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, bool transpose, int32_t out_rows_pad,

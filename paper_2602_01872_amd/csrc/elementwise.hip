@@ -13,11 +13,18 @@
 namespace grp {
 
 // ------------------------------------------------------------------ small utilities
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ p, size_t words) {
+__device__ __forceinline__ void fill_zero_kernel_body(unsigned gx, uint32_t* __restrict__ p, size_t words) {
     size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * 256;
+    const size_t stride = (size_t)gx * 256;
     for (; i < words; i += stride) p[i] = 0u;
 }
+__global__ __launch_bounds__(256) void fill_zero_kernel(uint32_t* __restrict__ p, size_t words) {
+    fill_zero_kernel_body(gridDim.x, p, words);
+}
+struct fill_zero_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { fill_zero_kernel_body(gx, a...); }
+};
 
 grp_status launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
     if (bytes == 0) return GRP_OK;
@@ -26,14 +33,15 @@ grp_status launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
     size_t blocks = (words + 255) / 256;
     if (blocks > 65536) blocks = 65536;
     ProfScope ps("fill_zero", st);
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (uint32_t*)p, words);
+    launch(fill_zero_kernel, fill_zero_kernel_op(), dim3((unsigned)blocks), st, (uint32_t*)p, words);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
 
 // All weight re-packing jobs of a step in one launch: job j owns the flat element range
 // [begin_j, begin_{j+1}) of the grid and is either a zero-padded copy or a zero-padded transpose.
-__global__ __launch_bounds__(256) void pack_weights_kernel(PackJobs jobs) {
+template <int MOST>
+__device__ __forceinline__ void pack_weights_kernel_body(unsigned gx, const PackJobsOf<MOST>& jobs) {
     const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e0 >= jobs.begin[jobs.n]) return;
     int j = 0;
@@ -50,6 +58,15 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(PackJobs jobs) {
         J.out[(int64_t)r * J.ld_out + c] = (r < J.rows && c < J.cols) ? J.in[(int64_t)r * J.cols + c] * J.scale : 0.f;
     }
 }
+template <int MOST>
+__global__ __launch_bounds__(256) void pack_weights_kernel(PackJobsOf<MOST> jobs) {
+    pack_weights_kernel_body<MOST>(gridDim.x, jobs);
+}
+template <int MOST>
+struct pack_weights_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { pack_weights_kernel_body<MOST>(gx, a...); }
+};
 
 void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, bool transpose, int32_t out_rows_pad,
                    float* out, int64_t ld_out, float scale) {
@@ -66,7 +83,17 @@ void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, 
 grp_status launch_pack_weights(const PackJobs& jobs, hipStream_t st) {
     if (jobs.n == 0 || jobs.begin[jobs.n] == 0) return GRP_OK;
     ProfScope ps("pack_weights", st);
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)cdiv(jobs.begin[jobs.n], 256)), dim3(256), 0, st, jobs);
+    const dim3 grid((unsigned)cdiv(jobs.begin[jobs.n], 256));
+    constexpr int FEW = 12;                            // three layers: arguments of several steps fit one launch
+    if (jobs.n <= FEW) {
+        PackJobsOf<FEW> few;
+        few.n = jobs.n;
+        for (int j = 0; j < jobs.n; ++j) few.job[j] = jobs.job[j];
+        for (int j = 0; j <= jobs.n; ++j) few.begin[j] = jobs.begin[j];
+        launch(pack_weights_kernel<FEW>, pack_weights_kernel_op<FEW>(), grid, st, few);
+    } else {
+        GRP_PLAIN_LAUNCH(pack_weights_kernel<4 * GRP_MAX_LAYERS>, grid, dim3(256), 0, st, jobs);
+    }
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -100,7 +127,7 @@ uint64_t dropout_layer_key(const DropoutPlan& d, int layer) {
 // One thread per 4 columns of a row.  VEC: every pitch is a multiple of 4 and every base 16-byte
 // aligned, so the 4 columns (pad columns included, which stay zero) move as one float4.
 template <bool VEC>
-__global__ __launch_bounds__(256) void dropout_kernel(const int64_t* __restrict__ l2g, int64_t n, int F, uint64_t key,
+__device__ __forceinline__ void dropout_kernel_body(unsigned gx, const int64_t* __restrict__ l2g, int64_t n, int F, uint64_t key,
                                                       uint32_t thresh, float scale, float* __restrict__ H, int64_t ldh,
                                                       float* __restrict__ act, int64_t ld_act,
                                                       const float* __restrict__ res, int64_t ld_res,
@@ -141,6 +168,21 @@ __global__ __launch_bounds__(256) void dropout_kernel(const int64_t* __restrict_
         }
     }
 }
+template <bool VEC>
+__global__ __launch_bounds__(256) void dropout_kernel(const int64_t* __restrict__ l2g, int64_t n, int F, uint64_t key,
+                                                      uint32_t thresh, float scale, float* __restrict__ H, int64_t ldh,
+                                                      float* __restrict__ act, int64_t ld_act,
+                                                      const float* __restrict__ res, int64_t ld_res,
+                                                      const int32_t* __restrict__ node_of_row,
+                                                      const int64_t* __restrict__ n_dev, uint64_t seed, int layer,
+                                                      const uint64_t* __restrict__ batch_id_dev) {
+    dropout_kernel_body<VEC>(gridDim.x, l2g, n, F, key, thresh, scale, H, ldh, act, ld_act, res, ld_res, node_of_row, n_dev, seed, layer, batch_id_dev);
+}
+template <bool VEC>
+struct dropout_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { dropout_kernel_body<VEC>(gx, a...); }
+};
 
 grp_status launch_dropout(const DropoutPlan& d, int layer, const int64_t* l2g, int64_t n, int32_t F, float* H, int64_t ldh,
                           float* act, int64_t ld_act, const float* res, int64_t ld_res, hipStream_t st,
@@ -154,10 +196,10 @@ grp_status launch_dropout(const DropoutPlan& d, int layer, const int64_t* l2g, i
                                ld_res >= round_up(F, 4) && (uintptr_t)res % 16 == 0));
     const uint64_t key = dropout_layer_key(d, layer);
     if (vec)
-        hipLaunchKernelGGL(dropout_kernel<true>, dim3((unsigned)cdiv(work, 256)), dim3(256), 0, st, l2g, n, (int)F, key,
+        launch(dropout_kernel<true>, dropout_kernel_op<true>(), dim3((unsigned)cdiv(work, 256)), st, l2g, n, (int)F, key,
                            d.thresh, d.scale, H, ldh, act, ld_act, res, ld_res, node_of_row, n_dev, d.seed, layer, d.batch_id_dev);
     else
-        hipLaunchKernelGGL(dropout_kernel<false>, dim3((unsigned)cdiv(work, 256)), dim3(256), 0, st, l2g, n, (int)F, key,
+        launch(dropout_kernel<false>, dropout_kernel_op<false>(), dim3((unsigned)cdiv(work, 256)), st, l2g, n, (int)F, key,
                            d.thresh, d.scale, H, ldh, act, ld_act, res, ld_res, node_of_row, n_dev, d.seed, layer, d.batch_id_dev);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
@@ -170,7 +212,7 @@ __global__ __launch_bounds__(256) void scale_copy_kernel(const float* __restrict
 }
 
 // Y[i, :] = rowscale[i] * X[i, :] over c4 float4 columns (pitches multiples of 4, 16-byte aligned bases).
-__global__ __launch_bounds__(256) void scale_rows_kernel(const float* __restrict__ X, int64_t ldx,
+__device__ __forceinline__ void scale_rows_kernel_body(unsigned gx, const float* __restrict__ X, int64_t ldx,
                                                          const float* __restrict__ rowscale, int64_t n, int c4,
                                                          float* __restrict__ Y, int64_t ldy,
                                                          const int64_t* __restrict__ n_dev) {
@@ -184,6 +226,16 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const float* __restrict
     v.x *= a; v.y *= a; v.z *= a; v.w *= a;
     *reinterpret_cast<float4*>(Y + i * ldy + c) = v;
 }
+__global__ __launch_bounds__(256) void scale_rows_kernel(const float* __restrict__ X, int64_t ldx,
+                                                         const float* __restrict__ rowscale, int64_t n, int c4,
+                                                         float* __restrict__ Y, int64_t ldy,
+                                                         const int64_t* __restrict__ n_dev) {
+    scale_rows_kernel_body(gridDim.x, X, ldx, rowscale, n, c4, Y, ldy, n_dev);
+}
+struct scale_rows_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { scale_rows_kernel_body(gx, a...); }
+};
 
 grp_status launch_scale_rows(const float* X, int64_t ldx, const float* rowscale, int64_t n, int32_t F, float* Y, int64_t ldy,
                              hipStream_t st, const int64_t* n_dev) {
@@ -192,7 +244,7 @@ grp_status launch_scale_rows(const float* X, int64_t ldx, const float* rowscale,
     if (ldx % 4 || ldy % 4 || ldx < 4 * c4 || ldy < 4 * c4 || (uintptr_t)X % 16 || (uintptr_t)Y % 16)
         return fail(GRP_EINVAL, "scale_rows: operands must be 16-byte friendly");
     ProfScope ps("scale_rows", st, 0.0, 8.0 * n * F);
-    hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)cdiv(n * c4, 256)), dim3(256), 0, st, X, ldx, rowscale, n, c4, Y, ldy, n_dev);
+    launch(scale_rows_kernel, scale_rows_kernel_op(), dim3((unsigned)cdiv(n * c4, 256)), st, X, ldx, rowscale, n, c4, Y, ldy, n_dev);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -209,14 +261,14 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const float* __restrict__
 
 grp_status launch_pad_rows(const float* X, int64_t ldx, int64_t n, int32_t F, float* Y, int64_t ldy, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    hipLaunchKernelGGL(pad_rows_kernel, dim3((unsigned)cdiv(n * ldy, 256)), dim3(256), 0, st, X, ldx, n, (int)F, Y, ldy);
+    GRP_PLAIN_LAUNCH(pad_rows_kernel, dim3((unsigned)cdiv(n * ldy, 256)), dim3(256), 0, st, X, ldx, n, (int)F, Y, ldy);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
 
 grp_status launch_scale_copy(const float* in, float s, float* out, int64_t n, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    hipLaunchKernelGGL(scale_copy_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, in, s, out, n);
+    GRP_PLAIN_LAUNCH(scale_copy_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, in, s, out, n);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -258,7 +310,7 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
 
 // out[c] = sum_b part[b][c]: 8 columns per workgroup, 32 lanes per column take the blocks
 // b = j, j + 32, ... and are added in lane order.
-__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, int64_t blocks, int N,
+__device__ __forceinline__ void colsum_final_kernel_body(unsigned gx, const float* __restrict__ part, int64_t blocks, int N,
                                                            float* __restrict__ out) {
     __shared__ float red[32][8];
     const int cl = threadIdx.x & 7, j = threadIdx.x >> 3;
@@ -284,11 +336,19 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restri
         out[c] = t;
     }
 }
+__global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, int64_t blocks, int N,
+                                                           float* __restrict__ out) {
+    colsum_final_kernel_body(gridDim.x, part, blocks, N, out);
+}
+struct colsum_final_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { colsum_final_kernel_body(gx, a...); }
+};
 
 // Same partial sums with 16-byte loads: thread t owns the float4 column t % C4 and the rows
 // t / C4, t / C4 + R, ... of the block's slab (R = 256 / C4 row lanes); the row lanes are then
 // added through LDS in lane order.  Needs N <= 1024, lda % 4 == 0 and a 16-byte aligned A.
-__global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const float* __restrict__ A, int64_t M, int N,
+__device__ __forceinline__ void colsum_partial_vec_kernel_body(unsigned gx, const float* __restrict__ A, int64_t M, int N,
                                                                  int64_t lda, const float* __restrict__ rowmul,
                                                                  float* __restrict__ part) {
     __shared__ float red[256 * 4];
@@ -329,6 +389,15 @@ __global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const float* __
         part[(int64_t)blockIdx.x * N + c] = acc;
     }
 }
+__global__ __launch_bounds__(256) void colsum_partial_vec_kernel(const float* __restrict__ A, int64_t M, int N,
+                                                                 int64_t lda, const float* __restrict__ rowmul,
+                                                                 float* __restrict__ part) {
+    colsum_partial_vec_kernel_body(gridDim.x, A, M, N, lda, rowmul, part);
+}
+struct colsum_partial_vec_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { colsum_partial_vec_kernel_body(gx, a...); }
+};
 
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul, float* out,
                                 void* scratch, hipStream_t st) {
@@ -336,14 +405,12 @@ grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t ld
     ProfScope ps("colsum", st, 0.0, 4.0 * M * N);
     const bool vec = N <= 1024 && lda % 4 == 0 && lda >= round_up(N, 4) && (uintptr_t)A % 16 == 0;
     if (vec)
-        hipLaunchKernelGGL(colsum_partial_vec_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
-                           (float*)scratch);
+        launch(colsum_partial_vec_kernel, colsum_partial_vec_kernel_op(), dim3((unsigned)blocks), st, A, M, N, lda, rowmul, (float*)scratch);
     else
-        hipLaunchKernelGGL(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
+        GRP_PLAIN_LAUNCH(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
                            (float*)scratch);
     GRP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)cdiv(N, 8)), dim3(256), 0, st, (const float*)scratch,
-                       blocks, N, out);
+    launch(colsum_final_kernel, colsum_final_kernel_op(), dim3((unsigned)cdiv(N, 8)), st, (const float*)scratch, blocks, N, out);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -355,7 +422,7 @@ grp_status launch_colsum(const float* A, int64_t M, int32_t N, int64_t lda, floa
 // ------------------------------------------------------------------ degree scales
 // inv_in[v] = 1/max(d_in,1); r[v] = 1/sqrt(max(d_in+sl,1)); s[v] = 1/sqrt(max(d_out+sl,1));
 // rinv[v] = sqrt(max(d_in+sl,1)).  Null outputs are skipped.
-__global__ __launch_bounds__(256) void degree_scales_kernel(const int32_t* __restrict__ d_in,
+__device__ __forceinline__ void degree_scales_kernel_body(unsigned gx, const int32_t* __restrict__ d_in,
                                                             const int32_t* __restrict__ d_out, int64_t n, int sl,
                                                             float* __restrict__ inv_in, float* __restrict__ r,
                                                             float* __restrict__ s, float* __restrict__ rinv) {
@@ -368,13 +435,22 @@ __global__ __launch_bounds__(256) void degree_scales_kernel(const int32_t* __res
     if (rinv) rinv[v] = sqrtf(a);
     if (s) s[v] = 1.0f / sqrtf(b);
 }
+__global__ __launch_bounds__(256) void degree_scales_kernel(const int32_t* __restrict__ d_in,
+                                                            const int32_t* __restrict__ d_out, int64_t n, int sl,
+                                                            float* __restrict__ inv_in, float* __restrict__ r,
+                                                            float* __restrict__ s, float* __restrict__ rinv) {
+    degree_scales_kernel_body(gridDim.x, d_in, d_out, n, sl, inv_in, r, s, rinv);
+}
+struct degree_scales_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { degree_scales_kernel_body(gx, a...); }
+};
 
 grp_status launch_degree_scales(const int32_t* d_in, const int32_t* d_out, int64_t n, int sl, float* inv_in, float* r,
                                 float* s, float* rinv, hipStream_t st) {
     if (n == 0) return GRP_OK;
     ProfScope ps("degree_scales", st);
-    hipLaunchKernelGGL(degree_scales_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, d_in, d_out, n, sl, inv_in,
-                       r, s, rinv);
+    launch(degree_scales_kernel, degree_scales_kernel_op(), dim3((unsigned)cdiv(n, 256)), st, d_in, d_out, n, sl, inv_in, r, s, rinv);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -408,7 +484,7 @@ __device__ __forceinline__ double coverage_ratio(const CoverageIn& c, int64_t v)
 }
 
 // Rows are loss candidates: node = nodes ? nodes[i] : i; kept if !mask || mask[node].
-__global__ __launch_bounds__(256) void stats_partial_kernel(int64_t n_rows, const int32_t* __restrict__ nodes,
+__device__ __forceinline__ void stats_partial_kernel_body(unsigned gx, int64_t n_rows, const int32_t* __restrict__ nodes,
                                                             const uint8_t* __restrict__ mask, CoverageIn cv,
                                                             const int32_t* __restrict__ sampled,
                                                             StatsPartial* __restrict__ part) {
@@ -416,7 +492,7 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(int64_t n_rows, cons
     __shared__ int64_t smi[4];
     double ratio = 0.0, rd = 0.0;
     int64_t s = 0, ri = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_rows; i += (int64_t)gridDim.x * 256) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_rows; i += (int64_t)gx * 256) {
         const int64_t v = nodes ? nodes[i] : i;
         if (mask && !mask[v]) continue;
         const int64_t dl = cv.d_local[v], dg = cv.d_global[v];
@@ -437,6 +513,16 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(int64_t n_rows, cons
     ri = block_sum<int64_t>(ri, smi);
     if (threadIdx.x == 0) part[blockIdx.x] = StatsPartial{ratio, rd, s, ri};
 }
+__global__ __launch_bounds__(256) void stats_partial_kernel(int64_t n_rows, const int32_t* __restrict__ nodes,
+                                                            const uint8_t* __restrict__ mask, CoverageIn cv,
+                                                            const int32_t* __restrict__ sampled,
+                                                            StatsPartial* __restrict__ part) {
+    stats_partial_kernel_body(gridDim.x, n_rows, nodes, mask, cv, sampled, part);
+}
+struct stats_partial_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { stats_partial_kernel_body(gx, a...); }
+};
 
 struct NnzParts {
     const int64_t* p[GRP_MAX_LAYERS];
@@ -444,8 +530,8 @@ struct NnzParts {
     const int64_t* bad_seeds;      // null, or the number of seeds that were outside the partition
 };
 
-__global__ __launch_bounds__(256) void stats_final_kernel(const StatsPartial* __restrict__ part, int blocks,
-                                                          int full_graph, int64_t nnz_const, NnzParts np,
+__device__ __forceinline__ void stats_final_kernel_body(unsigned gx, const StatsPartial* __restrict__ part, int blocks,
+                                                          int full_graph, int64_t nnz_const, const NnzParts& np,
                                                           grp_step_stats* __restrict__ out) {
     __shared__ double smd[4];
     __shared__ int64_t smi[4];
@@ -469,6 +555,15 @@ __global__ __launch_bounds__(256) void stats_final_kernel(const StatsPartial* __
         out->nnz_used = nnz_used;
     }
 }
+__global__ __launch_bounds__(256) void stats_final_kernel(const StatsPartial* __restrict__ part, int blocks,
+                                                          int full_graph, int64_t nnz_const, NnzParts np,
+                                                          grp_step_stats* __restrict__ out) {
+    stats_final_kernel_body(gridDim.x, part, blocks, full_graph, nnz_const, np, out);
+}
+struct stats_final_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { stats_final_kernel_body(gx, a...); }
+};
 
 grp_status launch_stats(int64_t n_rows, const int32_t* nodes, const uint8_t* mask, const int32_t* d_local,
                         const int64_t* d_global, const int32_t* sampled_count, int64_t nnz_const,
@@ -483,11 +578,10 @@ grp_status launch_stats(int64_t n_rows, const int32_t* nodes, const uint8_t* mas
     if (w_local && sampled_count) return fail(GRP_EUNSUPPORTED, "coverage statistics: weight masses in mini-batch mode");
     const CoverageIn cv{d_local, d_global, w_local, w_global};
     const int blocks = stats_blocks(n_rows, 256);
-    hipLaunchKernelGGL(stats_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, n_rows, nodes, mask, cv, sampled_count,
-                       part);
+    launch(stats_partial_kernel, stats_partial_kernel_op(), dim3((unsigned)blocks), st, n_rows, nodes, mask, cv, sampled_count, part);
     GRP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(256), 0, st, (const StatsPartial*)part, blocks,
-                       (sampled_count || w_local) ? 0 : 1, nnz_const, np, out);
+    launch(stats_final_kernel, stats_final_kernel_op(), dim3(1), st, (const StatsPartial*)part, blocks, (sampled_count || w_local) ? 0 : 1, nnz_const,
+           np, out);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -544,7 +638,7 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(int64_t n_rows, int C
 // element) and the logits of the group's next row are requested before the current row is
 // reduced, so the load latency overlaps the shuffles and exponentials.
 template <int NV>
-__global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, int C, const float* __restrict__ Z,
+__device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_t n_rows, int C, const float* __restrict__ Z,
                                                                int64_t ldz, const int32_t* __restrict__ labels,
                                                                const int32_t* __restrict__ nodes,
                                                                const uint8_t* __restrict__ mask, int node_level,
@@ -557,7 +651,7 @@ __global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, i
     const int t = threadIdx.x & 15;
     const int64_t S = stats->S;
     const float inv_s = S > 0 ? 1.0f / (float)S : 0.f;
-    const int64_t stride = (int64_t)gridDim.x * 16;
+    const int64_t stride = (int64_t)gx * 16;
     double loss = 0.0;
     int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     float cur[NV], nxt[NV];
@@ -608,8 +702,25 @@ __global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, i
     loss = block_sum<double>(loss, smd);
     if (threadIdx.x == 0) loss_part[blockIdx.x] = loss;
 }
+template <int NV>
+__global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, int C, const float* __restrict__ Z,
+                                                               int64_t ldz, const int32_t* __restrict__ labels,
+                                                               const int32_t* __restrict__ nodes,
+                                                               const uint8_t* __restrict__ mask, int node_level,
+                                                               CoverageIn cv,
+                                                               const float* __restrict__ rowscale,
+                                                               float* __restrict__ dZ, int64_t lddz, int c_store,
+                                                               const grp_step_stats* __restrict__ stats,
+                                                               double* __restrict__ loss_part) {
+    softmax_xent_reg_kernel_body<NV>(gridDim.x, n_rows, C, Z, ldz, labels, nodes, mask, node_level, cv, rowscale, dZ, lddz, c_store, stats, loss_part);
+}
+template <int NV>
+struct softmax_xent_reg_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { softmax_xent_reg_kernel_body<NV>(gx, a...); }
+};
 
-__global__ __launch_bounds__(256) void loss_final_kernel(const double* __restrict__ part, int blocks,
+__device__ __forceinline__ void loss_final_kernel_body(unsigned gx, const double* __restrict__ part, int blocks,
                                                          grp_step_stats* __restrict__ stats) {
     __shared__ double smd[4];
     double s = 0.0;
@@ -617,6 +728,14 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const double* __restric
     s = block_sum<double>(s, smd);
     if (threadIdx.x == 0) stats->loss = stats->S > 0 ? s / (double)stats->S : 0.0;
 }
+__global__ __launch_bounds__(256) void loss_final_kernel(const double* __restrict__ part, int blocks,
+                                                         grp_step_stats* __restrict__ stats) {
+    loss_final_kernel_body(gridDim.x, part, blocks, stats);
+}
+struct loss_final_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { loss_final_kernel_body(gx, a...); }
+};
 
 grp_status launch_softmax_xent(int64_t n_rows, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
                                const int32_t* node_of_row, const uint8_t* mask, int32_t node_level,
@@ -632,16 +751,16 @@ grp_status launch_softmax_xent(int64_t n_rows, int32_t C, const float* Z, int64_
     n_rows, C, Z, ldz, labels, node_of_row, mask, node_level, cv, rowscale, dZ, lddz, c_store,               \
         (const grp_step_stats*)stats, loss_part
     const int blocks = stats_blocks(n_rows, 16);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS); };
-    if (c_store <= 16) go(softmax_xent_reg_kernel<1>);
-    else if (c_store <= 32) go(softmax_xent_reg_kernel<2>);
-    else if (c_store <= 64) go(softmax_xent_reg_kernel<4>);
-    else if (c_store <= 128) go(softmax_xent_reg_kernel<8>);
-    else if (c_store <= 192) go(softmax_xent_reg_kernel<12>);       // (1024 rows of 172 columns: 11 -> 5.5 us)
-    else go(softmax_xent_kernel);
+    auto go = [&](auto kernel, auto op) { launch(kernel, op, dim3((unsigned)blocks), st, GRP_SOFTMAX_ARGS); };
+    if (c_store <= 16) go(softmax_xent_reg_kernel<1>, softmax_xent_reg_kernel_op<1>());
+    else if (c_store <= 32) go(softmax_xent_reg_kernel<2>, softmax_xent_reg_kernel_op<2>());
+    else if (c_store <= 64) go(softmax_xent_reg_kernel<4>, softmax_xent_reg_kernel_op<4>());
+    else if (c_store <= 128) go(softmax_xent_reg_kernel<8>, softmax_xent_reg_kernel_op<8>());
+    else if (c_store <= 192) go(softmax_xent_reg_kernel<12>, softmax_xent_reg_kernel_op<12>());       // (1024 rows of 172 columns: 11 -> 5.5 us)
+    else GRP_PLAIN_LAUNCH(softmax_xent_kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS);
 #undef GRP_SOFTMAX_ARGS
     GRP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, (const double*)loss_part, blocks, stats);
+    launch(loss_final_kernel, loss_final_kernel_op(), dim3(1), st, (const double*)loss_part, blocks, stats);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -654,7 +773,7 @@ __global__ __launch_bounds__(256) void inverse_mass_kernel(const double* __restr
 
 grp_status launch_inverse_mass(const double* mass, int64_t n, float* inv, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    hipLaunchKernelGGL(inverse_mass_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, mass, n, inv);
+    GRP_PLAIN_LAUNCH(inverse_mass_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, mass, n, inv);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }

@@ -502,8 +502,8 @@ __device__ __forceinline__ float nt_plain(const GemmNNArgs& g, int64_t m, int n)
     return s;
 }
 
-template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
-__global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArgs g) {
+template <typename AT, int TM, int TN, bool IRREG, bool PRE>
+__device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
     if (g.M_dev) {                                    // the launch was sized by upper bounds
         g.M = *g.M_dev;
         if (g.a_valid_rows_dev) g.a_valid_rows = *g.a_valid_rows_dev;
@@ -917,6 +917,15 @@ __global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArg
         }
     }
 }
+template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
+__global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArgs g) {
+    gemm_nt_kernel_body<AT, TM, TN, IRREG, PRE>(gridDim.x, g);
+}
+template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
+struct gemm_nt_kernel_op {
+    static constexpr int THREADS = 256, WGS = nt_wgs(TN, PRE);
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { gemm_nt_kernel_body<AT, TM, TN, IRREG, PRE>(gx, a...); }
+};
 
 // The operand(s) B of a product as the planes that the PRE kernels copy: tile kt of 32 k (those of the second product follow the
 // first's), plane, row n < n_all, 64 bytes laid out as the kernel's LDS rows are.  Rows and k that do not exist are zero.
@@ -988,12 +997,12 @@ static void nn_pick(const GemmNNArgs& a, hipStream_t st) {
     const int64_t slabs = round_up(cdiv(a.M, 128), NXCD);
     if (n_eff > 64) {
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, 128));
-        if (short_k) hipLaunchKernelGGL((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 16, 2>), dim3(blocks), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 32, 1>), dim3(blocks), dim3(256), 0, st, a);
+        if (short_k) GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 16, 2>), dim3(blocks), dim3(256), 0, st, a);
+        else GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 32, 1>), dim3(blocks), dim3(256), 0, st, a);
     } else if (n_eff > 32) {
-        hipLaunchKernelGGL((gemm_nn_kernel<AT, VEC, 4, 1, 1, 2, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
+        GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 4, 1, 1, 2, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
     } else {
-        hipLaunchKernelGGL((gemm_nn_kernel<AT, VEC, 4, 1, 1, 1, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
+        GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 4, 1, 1, 1, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
     }
 }
 
@@ -1037,15 +1046,15 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, p.tile_n));
         const bool pre = p.pre;
         if (pre)
-            hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
+            GRP_PLAIN_LAUNCH(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
                                a.ldbt2, a.K2, a.N, p.n_all, a.planes);
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
         constexpr bool P_ = TM_ == 2 && TN_ >= 4;                                                                          \
-        if (P_ && pre && irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
-        else if (P_ && pre) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
-        else if (irreg) hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, true>), dim3(blocks), dim3(256), 0, st, t);       \
-        else hipLaunchKernelGGL((gemm_nt_kernel<AT, TM_, TN_, false>), dim3(blocks), dim3(256), 0, st, t);                 \
+        if (P_ && pre && irreg) GRP_PLAIN_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (P_ && pre) GRP_PLAIN_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (irreg) launch(gemm_nt_kernel<AT, TM_, TN_, true>, gemm_nt_kernel_op<AT, TM_, TN_, true>(), dim3(blocks), st, t);       \
+        else launch(gemm_nt_kernel<AT, TM_, TN_, false>, gemm_nt_kernel_op<AT, TM_, TN_, false>(), dim3(blocks), st, t);                 \
     } while (0)
 #define GRP_NT_LAUNCH(TM_, TN_)                                                                                            \
     do {                                                                                                                   \
@@ -1144,7 +1153,7 @@ __device__ __forceinline__ int tn_turn(int row) {
 }
 
 template <typename AT, bool VEC, bool GATHER, int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArgs g, int tiles_k, int tiles_n, int dual, int splits, int64_t chunk,
+__device__ __forceinline__ void gemm_tn_kernel_body(unsigned gx, GemmTNArgs g, int tiles_k, int tiles_n, int dual, int splits, int64_t chunk,
                                                       float* __restrict__ out, float* __restrict__ out2, int64_t out_ld,
                                                       int64_t out_split_stride, float* __restrict__ cs_out,
                                                       int64_t cs_split_stride) {
@@ -1385,6 +1394,18 @@ __global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArg
         }
     }
 }
+template <typename AT, bool VEC, bool GATHER, int WM, int WN, int TM, int TN>
+__global__ __launch_bounds__(256, tn_wgs(TM * TN)) void gemm_tn_kernel(GemmTNArgs g, int tiles_k, int tiles_n, int dual, int splits, int64_t chunk,
+                                                      float* __restrict__ out, float* __restrict__ out2, int64_t out_ld,
+                                                      int64_t out_split_stride, float* __restrict__ cs_out,
+                                                      int64_t cs_split_stride) {
+    gemm_tn_kernel_body<AT, VEC, GATHER, WM, WN, TM, TN>(gridDim.x, g, tiles_k, tiles_n, dual, splits, chunk, out, out2, out_ld, out_split_stride, cs_out, cs_split_stride);
+}
+template <typename AT, bool VEC, bool GATHER, int WM, int WN, int TM, int TN>
+struct gemm_tn_kernel_op {
+    static constexpr int THREADS = 256, WGS = tn_wgs(TM * TN);
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { gemm_tn_kernel_body<AT, VEC, GATHER, WM, WN, TM, TN>(gx, a...); }
+};
 
 // Where element (row, col) of the reduced partials goes: rows [0, K) x cols [0, N) -> C; with two
 // products the second one's rows [K, 2K) (dual = 1) or columns [N, 2N) (dual = 2) -> C2; the last row
@@ -1408,7 +1429,7 @@ __device__ __forceinline__ void tn_store(int64_t e, float val, int K, int N, int
 
 // C[e] = sum_p part[p][e], p ascending.  Four partial tiles are requested before the first is
 // added (the adds stay in split order, so the result is the plain sequential sum).
-__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ part, int splits, int K, int N,
+__device__ __forceinline__ void tn_reduce_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
                                                         int64_t part_stride, float* __restrict__ C, int64_t ldc,
                                                         float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
                                                         int64_t total) {
@@ -1425,11 +1446,21 @@ __global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict_
     for (; p < splits; ++p) s += p0[(int64_t)p * part_stride];
     tn_store(e, s, K, N, dual, C, C2, ldc, colsum_out);
 }
+__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ part, int splits, int K, int N,
+                                                        int64_t part_stride, float* __restrict__ C, int64_t ldc,
+                                                        float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
+                                                        int64_t total) {
+    tn_reduce_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
+}
+struct tn_reduce_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_kernel_body(gx, a...); }
+};
 
 // The same sum for partials whose stride allows 16-byte loads: a workgroup owns 64 elements,
 // 16 groups of threads each add a contiguous range of splits in ascending order, and the 16
 // group sums are then added in ascending order: a fixed association, so still deterministic.
-__global__ __launch_bounds__(256) void tn_reduce_vec_kernel(const float* __restrict__ part, int splits, int K, int N,
+__device__ __forceinline__ void tn_reduce_vec_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
                                                             int64_t part_stride, float* __restrict__ C, int64_t ldc,
                                                             float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
                                                             int64_t total) {           // total: a multiple of 4
@@ -1467,11 +1498,21 @@ __global__ __launch_bounds__(256) void tn_reduce_vec_kernel(const float* __restr
         for (int q = 0; q < 4; ++q) tn_store(e + q, tv[q], K, N, dual, C, C2, ldc, colsum_out);
     }
 }
+__global__ __launch_bounds__(256) void tn_reduce_vec_kernel(const float* __restrict__ part, int splits, int K, int N,
+                                                            int64_t part_stride, float* __restrict__ C, int64_t ldc,
+                                                            float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
+                                                            int64_t total) {
+    tn_reduce_vec_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
+}
+struct tn_reduce_vec_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_vec_kernel_body(gx, a...); }
+};
 
 // Scalar variant of the same scheme for strides that rule out 16-byte loads: a workgroup owns
 // 64 elements, 4 groups of threads each add a contiguous quarter of the splits in ascending
 // order, the 4 group sums are added in ascending order.
-__global__ __launch_bounds__(256) void tn_reduce_4way_kernel(const float* __restrict__ part, int splits, int K, int N,
+__device__ __forceinline__ void tn_reduce_4way_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
                                                              int64_t part_stride, float* __restrict__ C, int64_t ldc,
                                                              float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
                                                              int64_t total) {
@@ -1498,6 +1539,16 @@ __global__ __launch_bounds__(256) void tn_reduce_4way_kernel(const float* __rest
         tn_store(e, t, K, N, dual, C, C2, ldc, colsum_out);
     }
 }
+__global__ __launch_bounds__(256) void tn_reduce_4way_kernel(const float* __restrict__ part, int splits, int K, int N,
+                                                             int64_t part_stride, float* __restrict__ C, int64_t ldc,
+                                                             float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
+                                                             int64_t total) {
+    tn_reduce_4way_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
+}
+struct tn_reduce_4way_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_4way_kernel_body(gx, a...); }
+};
 
 template <typename AT, bool VEC, bool GATHER>
 static void tn_pick(const GemmTNArgs& a, const TnPlan& p, int dual, float* out, float* out2, int64_t out_ld, int64_t stride,
@@ -1505,8 +1556,14 @@ static void tn_pick(const GemmTNArgs& a, const TnPlan& p, int dual, float* out, 
     const unsigned blocks = (unsigned)(NXCD * p.tiles_k * p.tiles_n * (dual ? 2 : 1) * cdiv(p.splits, NXCD));
     dim3 grid(blocks);
 #define GRP_TN_LAUNCH(WM_, WN_, TM_, TN_)                                                                              \
-    hipLaunchKernelGGL((gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>), grid, dim3(256), 0, st, a, p.tiles_k,     \
-                       p.tiles_n, dual, p.splits, p.chunk, out, out2, out_ld, stride, cs_out, stride)
+    do {                                                                                                               \
+        if constexpr (VEC)                                                                                             \
+            launch(gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>, gemm_tn_kernel_op<AT, VEC, GATHER, WM_, WN_, TM_, TN_>(), grid, st, a, \
+                   p.tiles_k, p.tiles_n, dual, p.splits, p.chunk, out, out2, out_ld, stride, cs_out, stride);           \
+        else                                                                                                           \
+            GRP_PLAIN_LAUNCH((gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>), grid, dim3(256), 0, st, a, p.tiles_k, \
+                             p.tiles_n, dual, p.splits, p.chunk, out, out2, out_ld, stride, cs_out, stride);            \
+    } while (0)
     if (p.bk_tile == 64 && p.bn_tile == 128) GRP_TN_LAUNCH(2, 2, 1, 2);
     else if (p.bk_tile == 64) GRP_TN_LAUNCH(2, 2, 1, 1);
     else if (p.bn_tile == 128) GRP_TN_LAUNCH(2, 2, 2, 2);
@@ -1569,13 +1626,13 @@ grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st) {
         ProfScope ps("gemm_tn_reduce", st, 0.0, 4.0 * total * (p.splits + 1.0));
         const float* part = (const float*)a.workspace;
         if (stride % 4 == 0 && total % 4 == 0 && (uintptr_t)a.workspace % 16 == 0 && p.splits >= 16) {
-            hipLaunchKernelGGL(tn_reduce_vec_kernel, dim3((unsigned)cdiv(total, 64)), dim3(256), 0, st, part, p.splits, a.K,
+            launch(tn_reduce_vec_kernel, tn_reduce_vec_kernel_op(), dim3((unsigned)cdiv(total, 64)), st, part, p.splits, a.K,
                                a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
         } else if (p.splits >= 16) {
-            hipLaunchKernelGGL(tn_reduce_4way_kernel, dim3((unsigned)cdiv(total, 64)), dim3(256), 0, st, part, p.splits, a.K,
+            launch(tn_reduce_4way_kernel, tn_reduce_4way_kernel_op(), dim3((unsigned)cdiv(total, 64)), st, part, p.splits, a.K,
                                a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
         } else {
-            hipLaunchKernelGGL(tn_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, st, part, p.splits, a.K,
+            launch(tn_reduce_kernel, tn_reduce_kernel_op(), dim3((unsigned)cdiv(total, 256)), st, part, p.splits, a.K,
                                a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
         }
         GRP_LAUNCH_CHECK();

@@ -48,6 +48,7 @@ void prof_detail(const char* fmt, ...) {
     va_end(ap);
 }
 
+bool prof_enabled() { return g_prof_on; }
 void prof_begin(const char* name, hipStream_t st, double flops, double bytes) {
     if (!g_prof_on) return;
     ProfRec r{name, nullptr, nullptr, flops, bytes};

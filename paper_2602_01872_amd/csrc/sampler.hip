@@ -114,7 +114,7 @@ struct RelabelJob {
     uint32_t* count_t;                   // [sources] edges of each (cleared)
 };
 
-__global__ __launch_bounds__(CS_THREADS) void count_rows_kernel(CountJob c, RelabelJob r) {
+__device__ __forceinline__ void count_rows_kernel_body(unsigned gx, CountJob c, RelabelJob r) {
     __shared__ unsigned long long wave_sum[CS_THREADS / 64];
     __shared__ unsigned long long before_s;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -192,6 +192,13 @@ __global__ __launch_bounds__(CS_THREADS) void count_rows_kernel(CountJob c, Rela
         }
     }
 }
+__global__ __launch_bounds__(CS_THREADS) void count_rows_kernel(CountJob c, RelabelJob r) {
+    count_rows_kernel_body(gridDim.x, c, r);
+}
+struct count_rows_kernel_op {
+    static constexpr int THREADS = CS_THREADS, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { count_rows_kernel_body(gx, a...); }
+};
 
 // One wavefront per destination row.  Lane t computes draw t; the subset is grown in `fanout`
 // wave-uniform steps with lane t keeping the t-th element; each lane then finds the rank of its
@@ -203,8 +210,9 @@ __global__ __launch_bounds__(CS_THREADS) void count_rows_kernel(CountJob c, Rela
 // only if it exists and names the node.  (Clearing the map first and after each layer cost the step of a 7e6-node store a fill of
 // 28 MB and a launch per layer: 10.4 of 450 us for the fill and 2.5 for each of the launches.)
 constexpr int SAMPLE_ROWS_PER_WG = 4;
+constexpr int SAMPLE_THREADS = 64 * SAMPLE_ROWS_PER_WG;
 
-__global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(const int64_t* __restrict__ rowptr,
+__device__ __forceinline__ void sample_select_kernel_body(unsigned gx, const int64_t* __restrict__ rowptr,
                                                                                 const int32_t* __restrict__ col,
                                                                                 const int64_t* __restrict__ l2g,
                                                                                 const int32_t* __restrict__ dst_nodes,
@@ -252,6 +260,25 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
     for (int t = 0; t < fanout; ++t) rank += __shfl(mine, t, 64) < mine ? 1 : 0;
     if (lane < fanout) take(o + rank, col[b + mine]);
 }
+__global__ __launch_bounds__(SAMPLE_THREADS) void sample_select_kernel(const int64_t* __restrict__ rowptr,
+                                                                                const int32_t* __restrict__ col,
+                                                                                const int64_t* __restrict__ l2g,
+                                                                                const int32_t* __restrict__ dst_nodes,
+                                                                                int64_t* __restrict__ sizes /*of this layer*/,
+                                                                                int fanout, uint64_t h0 /*M(sampler_seed)*/,
+                                                                                uint64_t batch_id,
+                                                                                const uint64_t* __restrict__ batch_id_dev,
+                                                                                int layer,
+                                                                                const int64_t* __restrict__ out_ptr,
+                                                                                int32_t* __restrict__ out_idx,
+                                                                                const int32_t* __restrict__ mark,
+                                                                                uint32_t* __restrict__ bits /*null: input layer*/) {
+    sample_select_kernel_body(gridDim.x, rowptr, col, l2g, dst_nodes, sizes, fanout, h0, batch_id, batch_id_dev, layer, out_ptr, out_idx, mark, bits);
+}
+struct sample_select_kernel_op {
+    static constexpr int THREADS = SAMPLE_THREADS, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { sample_select_kernel_body(gx, a...); }
+};
 
 // The bitmap's words: the new nodes of every word are numbered after the destinations and the new nodes of the words before it.
 // Also clears the bitmap for the next layer, completes the layer's sizes and states the next layer's number of destinations (this
@@ -259,7 +286,7 @@ __global__ __launch_bounds__(64 * SAMPLE_ROWS_PER_WG) void sample_select_kernel(
 constexpr int WD_THREADS = 256;
 constexpr int WD_PER = 16;
 constexpr int WD_ROUND = WD_THREADS * WD_PER;
-__global__ __launch_bounds__(WD_THREADS) void number_new_kernel(int64_t n_words /*rounded up to WD_PER, the words past the last empty*/, int rounds,
+__device__ __forceinline__ void number_new_kernel_body(unsigned gx, int64_t n_words /*rounded up to WD_PER, the words past the last empty*/, int rounds,
                                                                 unsigned long long* __restrict__ posted, uint32_t* __restrict__ bits,
                                                                 int64_t* __restrict__ sizes, int64_t* __restrict__ next_n_dst,
                                                                 int32_t* __restrict__ mark, int32_t* __restrict__ src_nodes) {
@@ -288,7 +315,7 @@ __global__ __launch_bounds__(WD_THREADS) void number_new_kernel(int64_t n_words 
     }
     __syncthreads();
     unsigned long long at0 = before_s;
-    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+    if (blockIdx.x == gx - 1 && tid == 0) {
         const int64_t n_new = (int64_t)(at0 + part_total);
         sizes[SZ_NEW] = n_new;
         sizes[SZ_SRC] = n_dst + n_new;
@@ -315,6 +342,16 @@ __global__ __launch_bounds__(WD_THREADS) void number_new_kernel(int64_t n_words 
         }
     }
 }
+__global__ __launch_bounds__(WD_THREADS) void number_new_kernel(int64_t n_words /*rounded up to WD_PER, the words past the last empty*/, int rounds,
+                                                                unsigned long long* __restrict__ posted, uint32_t* __restrict__ bits,
+                                                                int64_t* __restrict__ sizes, int64_t* __restrict__ next_n_dst,
+                                                                int32_t* __restrict__ mark, int32_t* __restrict__ src_nodes) {
+    number_new_kernel_body(gridDim.x, n_words, rounds, posted, bits, sizes, next_n_dst, mark, src_nodes);
+}
+struct number_new_kernel_op {
+    static constexpr int THREADS = WD_THREADS, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { number_new_kernel_body(gx, a...); }
+};
 
 // ---- the transposed blocks, of all layers above the input layer in three launches (blockIdx.y: the layer).
 struct TransposeJob {
@@ -333,10 +370,12 @@ struct TransposeJob {
     int64_t *chunk_begin, *chunk_end;
     int64_t cap_long, cap_chunks;
 };
-struct TransposeJobs { TransposeJob d[GRP_MAX_LAYERS - 1]; };
+template <int MOST> struct TransposeJobsOf { TransposeJob d[MOST]; };
+using TransposeJobs = TransposeJobsOf<GRP_MAX_LAYERS - 1>;
 
 // Row pointers and the schedule of the long rows (as long_rows_emit_kernel makes it; places past the real ones do nothing).
-__global__ __launch_bounds__(CS_THREADS) void transpose_rows_kernel(TransposeJobs jobs) {
+template <int MOST>
+__device__ __forceinline__ void transpose_rows_kernel_body(unsigned gx, const TransposeJobsOf<MOST>& jobs) {
     __shared__ unsigned long long wave_sum[CS_THREADS / 64];
     __shared__ unsigned long long before_s[2];
     const TransposeJob& t = jobs.d[blockIdx.y];
@@ -406,14 +445,33 @@ __global__ __launch_bounds__(CS_THREADS) void transpose_rows_kernel(TransposeJob
         for (int64_t k = n_chunks + tid; k < t.cap_chunks; k += CS_THREADS) { t.chunk_begin[k] = 0; t.chunk_end[k] = 0; }
     }
 }
+template <int MOST>
+__global__ __launch_bounds__(CS_THREADS) void transpose_rows_kernel(TransposeJobsOf<MOST> jobs) {
+    transpose_rows_kernel_body<MOST>(gridDim.x, jobs);
+}
+template <int MOST>
+struct transpose_rows_kernel_op {
+    static constexpr int THREADS = CS_THREADS, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { transpose_rows_kernel_body<MOST>(gx, a...); }
+};
 
 // Every edge to its source's row, in order of arrival.
-__global__ __launch_bounds__(256) void transpose_scatter_kernel(TransposeJobs jobs) {
+template <int MOST>
+__device__ __forceinline__ void transpose_scatter_kernel_body(unsigned gx, const TransposeJobsOf<MOST>& jobs) {
     const TransposeJob& t = jobs.d[blockIdx.y];
     const int64_t n_dst = t.sizes[SZ_DST];
-    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n_dst; i += (int64_t)gridDim.x * 4)
+    for (int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / 64; i < n_dst; i += (int64_t)gx * 4)
         for (int64_t e = t.ptr[i] + (threadIdx.x & 63); e < t.ptr[i + 1]; e += 64) t.loose[t.ptr_t[t.idx_blk[e]] + t.arrival[e]] = (int32_t)i;
 }
+template <int MOST>
+__global__ __launch_bounds__(256) void transpose_scatter_kernel(TransposeJobsOf<MOST> jobs) {
+    transpose_scatter_kernel_body<MOST>(gridDim.x, jobs);
+}
+template <int MOST>
+struct transpose_scatter_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { transpose_scatter_kernel_body<MOST>(gx, a...); }
+};
 
 // Every source's row in ascending order, whatever the order of arrival was.  A workgroup owns TS_ROWS rows: as many of them as fit
 // are taken into LDS, where an edge's place is the number of smaller ones in its row (of equal ones, by where they lie); a row of more
@@ -423,7 +481,8 @@ constexpr int TS_THREADS = 256;
 constexpr int TS_ROWS = 256;
 constexpr int TS_CAP = 8192;
 constexpr int TS_RANK = 128;
-__global__ __launch_bounds__(TS_THREADS) void transpose_sort_kernel(TransposeJobs jobs) {
+template <int MOST>
+__device__ __forceinline__ void transpose_sort_kernel_body(unsigned gx, const TransposeJobsOf<MOST>& jobs) {
     __shared__ uint32_t buf[TS_CAP];
     __shared__ uint32_t off[TS_ROWS + 1];
     __shared__ unsigned long long long_rows[TS_ROWS / 64];   // the rows that are too long to be ranked
@@ -432,7 +491,7 @@ __global__ __launch_bounds__(TS_THREADS) void transpose_sort_kernel(TransposeJob
     const TransposeJob& t = jobs.d[blockIdx.y];
     const int64_t n_src = t.sizes[SZ_SRC], n_dst = t.sizes[SZ_DST];
     const int tid = threadIdx.x;
-    for (int64_t row0 = (int64_t)blockIdx.x * TS_ROWS; row0 < n_src; row0 += (int64_t)gridDim.x * TS_ROWS) {
+    for (int64_t row0 = (int64_t)blockIdx.x * TS_ROWS; row0 < n_src; row0 += (int64_t)gx * TS_ROWS) {
         const int rows = (int)(n_src - row0 < TS_ROWS ? n_src - row0 : TS_ROWS);
         const int64_t e0 = t.ptr_t[row0];
         const uint32_t mine = (uint32_t)(t.ptr_t[row0 + (tid < rows ? tid : rows)] - e0), next = (uint32_t)(t.ptr_t[row0 + (tid < rows ? tid + 1 : rows)] - e0);
@@ -516,6 +575,15 @@ __global__ __launch_bounds__(TS_THREADS) void transpose_sort_kernel(TransposeJob
         __syncthreads();                                     // off is filled anew
     }
 }
+template <int MOST>
+__global__ __launch_bounds__(TS_THREADS) void transpose_sort_kernel(TransposeJobsOf<MOST> jobs) {
+    transpose_sort_kernel_body<MOST>(gridDim.x, jobs);
+}
+template <int MOST>
+struct transpose_sort_kernel_op {
+    static constexpr int THREADS = TS_THREADS, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { transpose_sort_kernel_body<MOST>(gx, a...); }
+};
 
 void sampler_bounds(int64_t n, int64_t n_seeds, const int32_t* fanouts, int k, SamplerBounds* out) {
     int64_t nd = n_seeds;
@@ -633,8 +701,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         const ScanPlan cp = scan_plan(dst_bound + 1, CS_ROUND);
         const CountJob count{part->rowptr, dst_nodes, top ? o->seeds : nullptr, n, (int64_t)o->n_seeds, D, dst_bound, f, cp.rounds, cp.parts, L.posted,
                              L.ptr, L.cnt32, L.inv_in, top && l > 0 ? s.mark : nullptr, L.src_nodes, (unsigned long long*)s.bad};
-        hipLaunchKernelGGL(count_rows_kernel, dim3((unsigned)(cp.parts + (relabel.ptr ? cdiv(relabel.dst_bound, 4) : 0))), dim3(CS_THREADS), 0, st, count,
-                           relabel);
+        launch(count_rows_kernel, count_rows_kernel_op(), dim3((unsigned)(cp.parts + (relabel.ptr ? cdiv(relabel.dst_bound, 4) : 0))), st, count, relabel);
         GRP_LAUNCH_CHECK();
         if (l == 0 && k > 1) {
             // The transposed blocks are read by the backward pass only: they are built on a helper stream, beside the choice of the input
@@ -650,9 +717,19 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
             for (int q = 1; q < k; ++q) parts = std::max(parts, jobs.d[q - 1].parts);
             const int64_t dst_groups = std::min(cdiv(bd.dst[1], 4), (int64_t)1 << 18);             // (layer 1 is the largest)
             const int64_t src_groups = std::min(cdiv(bd.src[1], TS_ROWS), (int64_t)1 << 18);
-            hipLaunchKernelGGL(transpose_rows_kernel, dim3((unsigned)parts, (unsigned)(k - 1)), dim3(CS_THREADS), 0, bst, jobs);
-            hipLaunchKernelGGL(transpose_scatter_kernel, dim3((unsigned)dst_groups, (unsigned)(k - 1)), dim3(256), 0, bst, jobs);
-            hipLaunchKernelGGL(transpose_sort_kernel, dim3((unsigned)src_groups, (unsigned)(k - 1)), dim3(TS_THREADS), 0, bst, jobs);
+            constexpr int FEW = 3;                       // arguments of several steps fit one launch
+            if (k - 1 <= FEW) {
+                TransposeJobsOf<FEW> few{};
+                for (int q = 0; q < k - 1; ++q) few.d[q] = jobs.d[q];
+                launch(transpose_rows_kernel<FEW>, transpose_rows_kernel_op<FEW>(), dim3((unsigned)parts, (unsigned)(k - 1)), bst, few);
+                launch(transpose_scatter_kernel<FEW>, transpose_scatter_kernel_op<FEW>(), dim3((unsigned)dst_groups, (unsigned)(k - 1)), bst, few);
+                launch(transpose_sort_kernel<FEW>, transpose_sort_kernel_op<FEW>(), dim3((unsigned)src_groups, (unsigned)(k - 1)), bst, few);
+            } else {
+                constexpr int ALL = GRP_MAX_LAYERS - 1;
+                GRP_PLAIN_LAUNCH(transpose_rows_kernel<ALL>, dim3((unsigned)parts, (unsigned)(k - 1)), dim3(CS_THREADS), 0, bst, jobs);
+                GRP_PLAIN_LAUNCH(transpose_scatter_kernel<ALL>, dim3((unsigned)dst_groups, (unsigned)(k - 1)), dim3(256), 0, bst, jobs);
+                GRP_PLAIN_LAUNCH(transpose_sort_kernel<ALL>, dim3((unsigned)src_groups, (unsigned)(k - 1)), dim3(TS_THREADS), 0, bst, jobs);
+            }
             GRP_LAUNCH_CHECK();
             if (lane) {
                 GRP_HIP(hipEventRecord(lane->join, lane->stream));
@@ -661,8 +738,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         }
         {
             ProfScope ps("sample_select", st);
-            hipLaunchKernelGGL(sample_select_kernel, dim3((unsigned)cdiv(dst_bound, SAMPLE_ROWS_PER_WG)),
-                               dim3(64 * SAMPLE_ROWS_PER_WG), 0, st, part->rowptr, part->col, part->l2g, dst_nodes, D, f,
+            launch(sample_select_kernel, sample_select_kernel_op(), dim3((unsigned)cdiv(dst_bound, SAMPLE_ROWS_PER_WG)), st, part->rowptr, part->col, part->l2g, dst_nodes, D, f,
                                h0, (uint64_t)o->batch_id, o->batch_id_dev, l, (const int64_t*)L.ptr, L.idx_local, (const int32_t*)s.mark,
                                l > 0 ? s.bits : nullptr);
             GRP_LAUNCH_CHECK();
@@ -689,7 +765,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         // new source nodes in ascending local id
         const int64_t src_bound = bd.src[l];
         const ScanPlan wp = scan_plan(s.n_words, WD_ROUND);
-        hipLaunchKernelGGL(number_new_kernel, dim3((unsigned)wp.parts), dim3(WD_THREADS), 0, st, s.n_words, wp.rounds, L.posted + PARTS, s.bits, D,
+        launch(number_new_kernel, number_new_kernel_op(), dim3((unsigned)wp.parts), st, s.n_words, wp.rounds, L.posted + PARTS, s.bits, D,
                            s.sizes + SZ_PER_LAYER * (l - 1) + SZ_DST, s.mark, L.src_nodes);
         GRP_LAUNCH_CHECK();
         relabel = RelabelJob{L.ptr, D, dst_bound, L.idx_local, s.mark, L.idx_blk, L.arrival, L.count_t};

@@ -280,8 +280,8 @@ __device__ __forceinline__ void chunk_body(int64_t cb, int64_t ce, const int32_t
 // edges, one group per row.  One launch instead of two keeps the few chunk workgroups from
 // running on an otherwise idle chip.
 // S groups share a row (see spmm_share for the choice); their sums are added in a fixed butterfly.
-template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
-__global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
+template <typename XT, int G, int S, int NJ, bool EV, bool WIDE>
+__device__ __forceinline__ void spmm_rows_kernel_body(unsigned gx, const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, int64_t n_rows, int64_t long_thr,
                                                         const XT* __restrict__ X,
                                                         int64_t ldx, const float* __restrict__ colscale,
@@ -325,10 +325,26 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restric
     for (int j = 0; j < NJ; ++j)
         if (live[j]) finish_row<XT>(ep, i, e - b, slab_col<G, WIDE>(t, j), acc[j], X, ldx);
 }
+template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
+__global__ __launch_bounds__(256) void spmm_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
+                                                        const float* __restrict__ val, int64_t n_rows, int64_t long_thr,
+                                                        const XT* __restrict__ X,
+                                                        int64_t ldx, const float* __restrict__ colscale,
+                                                        SpmmEpilogue ep, int n_chunks,
+                                                        const int64_t* __restrict__ chunk_begin,
+                                                        const int64_t* __restrict__ chunk_end,
+                                                        float* __restrict__ partials, int64_t ld_part) {
+    spmm_rows_kernel_body<XT, G, S, NJ, EV, WIDE>(gridDim.x, ptr, idx, val, n_rows, long_thr, X, ldx, colscale, ep, n_chunks, chunk_begin, chunk_end, partials, ld_part);
+}
+template <typename XT, int G, int S, int NJ, bool EV, bool WIDE = false>
+struct spmm_rows_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { spmm_rows_kernel_body<XT, G, S, NJ, EV, WIDE>(gx, a...); }
+};
 
 // One group per long row: partial rows added in chunk order, then the epilogue.
 template <typename XT, int G, int NJ>
-__global__ __launch_bounds__(256) void spmm_combine_kernel(const int32_t* __restrict__ long_row,
+__device__ __forceinline__ void spmm_combine_kernel_body(unsigned gx, const int32_t* __restrict__ long_row,
                                                            const int32_t* __restrict__ long_first, int n_long,
                                                            const int64_t* __restrict__ ptr,
                                                            const float* __restrict__ partials, int64_t ld_part,
@@ -350,6 +366,19 @@ __global__ __launch_bounds__(256) void spmm_combine_kernel(const int32_t* __rest
         finish_row<XT>(ep, i, deg, col, acc, X, ldx);
     }
 }
+template <typename XT, int G, int NJ>
+__global__ __launch_bounds__(256) void spmm_combine_kernel(const int32_t* __restrict__ long_row,
+                                                           const int32_t* __restrict__ long_first, int n_long,
+                                                           const int64_t* __restrict__ ptr,
+                                                           const float* __restrict__ partials, int64_t ld_part,
+                                                           const XT* __restrict__ X, int64_t ldx, SpmmEpilogue ep) {
+    spmm_combine_kernel_body<XT, G, NJ>(gridDim.x, long_row, long_first, n_long, ptr, partials, ld_part, X, ldx, ep);
+}
+template <typename XT, int G, int NJ>
+struct spmm_combine_kernel_op {
+    static constexpr int THREADS = 256, WGS = 1;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { spmm_combine_kernel_body<XT, G, NJ>(gx, a...); }
+};
 
 // ---- the source-sliced schedule of the long rows (slices.hip): one wavefront per task.
 // A task is at most SLICE_TASK_MAX consecutive edges of one long row whose sources lie in one slice of the
@@ -664,7 +693,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             }
         }
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F, ep.last_x,
+            GRP_PLAIN_LAUNCH(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F, ep.last_x,
                                (const XT*)a.X, a.ldx, a.colscale, a.partials, ld_part, row_shift);
         };
         // bf16 rows of whole 16-byte units: eight elements per lane, half the lanes per row
@@ -687,10 +716,14 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
         }
     }
-    auto rows = [&](auto kernel, int lanes) {              // lanes: of a row
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), dim3(256), 0, st, a.ptr, a.idx, a.val,
-                           a.n_rows, thr, (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr,
-                           n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+    auto rows = [&](auto kernel, auto op, int lanes) {     // lanes: of a row
+        launch(kernel, op, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), st, a.ptr, a.idx, a.val, a.n_rows, thr, (const XT*)a.X, a.ldx,
+               a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+    };
+    auto rows_val = [&](auto kernel, int lanes) {          // with edge values
+        GRP_PLAIN_LAUNCH(kernel, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows, thr,
+                         (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr,
+                         a.partials, ld_part);
     };
     bool rows_done = false;
     if constexpr (std::is_same<XT, __hip_bfloat16>::value && G >= 2 && NJ == 1) {
@@ -698,27 +731,27 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         if (a.F % 8 == 0 && a.ldx % 8 == 0 && ((uintptr_t)a.X % 16) == 0 && !a.self_term) {
             constexpr int GW = G / 2, S = SPMM_GROUPS(GW);
             if (S > 1 && spmm_share(a.n_rows, a.nnz, n_chunks, GW, S)) {
-                if (a.val) rows(spmm_rows_kernel<XT, GW, S, 2, true, true>, GW * S);
-                else rows(spmm_rows_kernel<XT, GW, S, 2, false, true>, GW * S);
-            } else if (a.val) rows(spmm_rows_kernel<XT, GW, 1, 2, true, true>, GW);
-            else rows(spmm_rows_kernel<XT, GW, 1, 2, false, true>, GW);
+                if (a.val) rows_val(spmm_rows_kernel<XT, GW, S, 2, true, true>, GW * S);
+                else rows(spmm_rows_kernel<XT, GW, S, 2, false, true>, spmm_rows_kernel_op<XT, GW, S, 2, false, true>(), GW * S);
+            } else if (a.val) rows_val(spmm_rows_kernel<XT, GW, 1, 2, true, true>, GW);
+            else rows(spmm_rows_kernel<XT, GW, 1, 2, false, true>, spmm_rows_kernel_op<XT, GW, 1, 2, false, true>(), GW);
             rows_done = true;
         }
     }
     if (!rows_done) {
         constexpr int S = SPMM_GROUPS(G);
         if (S > 1 && spmm_share(a.n_rows, a.nnz, n_chunks, G, S)) {
-            if (a.val) rows(spmm_rows_kernel<XT, G, S, NJ, true>, G * S);
-            else rows(spmm_rows_kernel<XT, G, S, NJ, false>, G * S);
-        } else if (a.val) rows(spmm_rows_kernel<XT, G, 1, NJ, true>, G);
-        else rows(spmm_rows_kernel<XT, G, 1, NJ, false>, G);
+            if (a.val) rows_val(spmm_rows_kernel<XT, G, S, NJ, true>, G * S);
+            else rows(spmm_rows_kernel<XT, G, S, NJ, false>, spmm_rows_kernel_op<XT, G, S, NJ, false>(), G * S);
+        } else if (a.val) rows_val(spmm_rows_kernel<XT, G, 1, NJ, true>, G);
+        else rows(spmm_rows_kernel<XT, G, 1, NJ, false>, spmm_rows_kernel_op<XT, G, 1, NJ, false>(), G);
     }
     if (sliced) {
-        hipLaunchKernelGGL((spmm_combine_tasks_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, 4)), dim3(256), 0, st,
+        GRP_PLAIN_LAUNCH((spmm_combine_tasks_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, 4)), dim3(256), 0, st,
                            lr->long_row, (const int64_t*)lr->row_task, lr->n_long, a.ptr, (const float*)a.partials, ld_part,
                            (const XT*)a.X, a.ldx, ep);
     } else if (split) {
-        hipLaunchKernelGGL((spmm_combine_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, ROWS)), dim3(256), 0, st,
+        launch(spmm_combine_kernel<XT, G, NJ>, spmm_combine_kernel_op<XT, G, NJ>(), dim3((unsigned)cdiv(lr->n_long, ROWS)), st,
                            lr->long_row, lr->long_first, lr->n_long, a.ptr, (const float*)a.partials, ld_part,
                            (const XT*)a.X, a.ldx, ep);
     }
@@ -793,11 +826,11 @@ grp_status launch_spmm(const SpmmArgs& a, hipStream_t st) {
             return fail(GRP_EUNSUPPORTED, "spmm: this epilogue needs 16-byte friendly operands");
         const int64_t blocks = cdiv(a.n_rows, 4);
         if (a.x_bf16)
-            hipLaunchKernelGGL((spmm_rows_scalar_kernel<__hip_bfloat16>), dim3((unsigned)blocks), dim3(256), 0, st,
+            GRP_PLAIN_LAUNCH((spmm_rows_scalar_kernel<__hip_bfloat16>), dim3((unsigned)blocks), dim3(256), 0, st,
                                a.ptr, a.idx, a.n_rows, a.F, (const __hip_bfloat16*)a.X, a.ldx, a.scale,
                                a.self_term, a.colscale, a.addend, a.ld_add, a.bias, a.relu, a.Y, a.ldy, a.val, a.rowscale, a.n_rows_dev);
         else
-            hipLaunchKernelGGL((spmm_rows_scalar_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, st, a.ptr,
+            GRP_PLAIN_LAUNCH((spmm_rows_scalar_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, st, a.ptr,
                                a.idx, a.n_rows, a.F, (const float*)a.X, a.ldx, a.scale, a.self_term, a.colscale, a.addend,
                                a.ld_add, a.bias, a.relu, a.Y, a.ldy, a.val, a.rowscale, a.n_rows_dev);
     }

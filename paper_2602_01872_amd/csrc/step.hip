@@ -11,6 +11,7 @@
 #include "common.h"
 
 #include <algorithm>
+#include <new>
 #include <vector>
 
 namespace grp {
@@ -475,6 +476,78 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
 }
 
 }  // namespace grp
+
+namespace grp {
+thread_local LaunchRecorder* g_recorder = nullptr;
+
+// The launches of several steps, each step's in its own order: what stands at the front of a step is launched together with every other
+// front of the same kernel, the step with the most launches left first (so that steps that differ by a launch or two fall in again).
+static void launch_merged(const std::vector<LaunchRecorder>& steps, hipStream_t st) {
+    std::vector<size_t> at(steps.size(), 0);
+    std::vector<const LaunchRecord*> recs;
+    for (;;) {
+        size_t lead = steps.size(), left = 0;
+        for (size_t p = 0; p < steps.size(); ++p)
+            if (steps[p].list.size() - at[p] > left) {
+                left = steps[p].list.size() - at[p];
+                lead = p;
+            }
+        if (left == 0) return;
+        const auto go = steps[lead].list[at[lead]].go;
+        const unsigned layers = steps[lead].list[at[lead]].grid.y;
+        recs.clear();
+        for (size_t p = 0; p < steps.size(); ++p)
+            if (at[p] < steps[p].list.size() && steps[p].list[at[p]].go == go && steps[p].list[at[p]].grid.y == layers)
+                recs.push_back(&steps[p].list[at[p]++]);
+        go(recs.data(), (int)recs.size(), st);
+    }
+}
+
+struct Recording {                       // for the lifetime of one step's recording
+    explicit Recording(LaunchRecorder* r) { g_recorder = r; }
+    ~Recording() { g_recorder = nullptr; }
+};
+bool prof_enabled();
+}  // namespace grp
+
+extern "C" grp_status grp_train_steps(int32_t count, const grp_partition_t* const* parts, const grp_model_desc* model, const grp_step_opts* opts,
+                                      const void* const* features, const int32_t* const* labels, const uint8_t* const* train_masks,
+                                      const float* weights, void* const* workspaces, size_t workspace_bytes, void* stream,
+                                      float* const* grads_out, grp_step_stats* const* stats_out) {
+    using namespace grp;
+    if (count < 0) return fail(GRP_EINVAL, "train_steps: count = %d", count);
+    if (count == 0) return GRP_OK;
+    if (!parts || !model || !opts || !features || !labels || !workspaces || !grads_out || !stats_out) return fail(GRP_EINVAL, "train_steps: null array");
+    auto step = [&](int p, const grp_step_opts& o) {
+        return grp_train_step(parts[p], model, &o, features[p], labels[p], train_masks ? train_masks[p] : nullptr, weights, workspaces[p],
+                              workspace_bytes, stream, grads_out[p], stats_out[p]);
+    };
+    // (an attention model's launches are not recorded, nor are any while they are timed one by one)
+    bool merge = count > 1 && model->arch != GRP_ARCH_GAT && !prof_enabled() && !g_recorder;
+    for (int p = 0; p < count && merge; ++p)
+        for (int q = 0; q < p; ++q) merge = merge && workspaces[p] != workspaces[q];
+    if (merge) {
+        try {
+            std::vector<LaunchRecorder> steps((size_t)count);
+            for (int p = 0; p < count && merge; ++p) {
+                grp_step_opts o = opts[p];
+                o.flags |= GRP_STEP_ONE_STREAM;
+                Recording r(&steps[(size_t)p]);
+                GRP_TRY(step(p, o));
+                merge = !steps[(size_t)p].unsupported;
+            }
+            if (merge) {
+                launch_merged(steps, (hipStream_t)stream);
+                GRP_LAUNCH_CHECK();
+                return GRP_OK;
+            }
+        } catch (const std::bad_alloc&) {
+            return fail(GRP_ENOMEM, "train_steps: out of host memory");
+        }
+    }
+    for (int p = 0; p < count; ++p) GRP_TRY(step(p, opts[p]));
+    return GRP_OK;
+}
 
 extern "C" int64_t grp_param_count(const grp_model_desc* model) {
     if (!grp::valid_model(model)) return -1;

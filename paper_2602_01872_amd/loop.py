@@ -2,17 +2,29 @@
 
 Sequencing only: every partition step, the scale-and-reduce and the optimizer step are
 library calls; the partitions of a phase are independent of each other, so they are processed
-in turn on the one GPU or, with ``streams`` > 1, side by side on that many HIP streams (small
-partitions leave most of the chip idle); their gradients are kept resident for the reduction.
+in turn on the one GPU, on several HIP streams (``streams`` > 1), or, where they are small enough to be bound by the number of
+their launches, in merged launches; their gradients are kept resident for the reduction.
 """
 from __future__ import annotations
-
-from concurrent.futures import ThreadPoolExecutor
 
 import torch
 
 from . import binding as g
 from .controller import Controller
+
+
+# Full-graph steps are merged, at most MERGE_STEPS at a time, while a step's workspace is at most this large (each merged step needs one of
+# its own, so this also bounds the memory).  Eight steps one by one / merged by two / four / eight, us, workspace of one step:
+#   GraphSAGE 100-256-256-47   26 MiB 1661/917/526/355   117 MiB 2703/1927/1552/1389   369 MiB 5750/4873/4485/4332   706 MiB 8827/8842/8832/8828
+#   GCN 64-128-16               5 MiB 959/527/303/185     70 MiB 1409/885/605/498      136 MiB 1771/1188/980/915     498 MiB 3917/3458/3370/3182
+MERGE_WORKSPACE_BYTES = 512 << 20
+MERGE_STEPS = 8
+
+
+def _groups(active, most):
+    """(slot, partition) of a phase, in runs of at most ``most``."""
+    slots = list(enumerate(active))
+    return [slots[lo:lo + most] for lo in range(0, len(slots), most)]
 
 
 class PhaseParallelTrainer:
@@ -24,7 +36,7 @@ class PhaseParallelTrainer:
     ``dropout_rate`` / ``dropout_seed``: hidden-layer dropout; the masks of a phase are drawn with
     batch_id = the number of optimizer steps taken so far.
     ``streams``: number of streams (default priority) the steps of a phase are spread over, each with a
-    workspace of its own; 1 = everything on the current stream.  The result does not depend on it.
+    workspace of its own; 1 = everything on the current stream, small steps in merged launches.  The result does not depend on it.
     """
 
     def __init__(self, parts, model, xs, ys, masks, theta0, estimator, max_active, optimizer=None,
@@ -45,8 +57,10 @@ class PhaseParallelTrainer:
         self.stats = g.new_stats(max_active, device=dev)
         ws_bytes = max(g.grp_step_workspace_bytes(p, model, self.opts) for p in parts)
         n_lanes = max(1, min(int(streams), max_active))
-        self.ws = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev) for _ in range(n_lanes)]
         self.side = [torch.cuda.Stream(device=dev) for _ in range(n_lanes)] if n_lanes > 1 else []
+        if not self.side and ws_bytes <= MERGE_WORKSPACE_BYTES:
+            n_lanes = min(MERGE_STEPS, max_active)
+        self.ws = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev) for _ in range(n_lanes)]
         self.step_count = 0
         self.history = []          # per optimizer step: device tensor views are copied lazily
 
@@ -56,19 +70,23 @@ class PhaseParallelTrainer:
 
     def run_phase(self, active):
         self.opts.batch_id = self.step_count
-        main = torch.cuda.current_stream()
-        if self.side:                 # the side streams start once theta (and everything before) is ready
+        record = lambda slot: self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES]
+        if self.side:
+            main = torch.cuda.current_stream()
             ready = main.record_event()
-            for st in self.side:
+            for st in self.side:      # the side streams start once theta (and everything before) is ready
                 st.wait_event(ready)
-        for slot, p in enumerate(active):
-            lane = slot % len(self.ws)
-            g.grp_train_step(self.parts[p], self.model, self.opts, self.xs[p], self.ys[p], self.masks[p],
-                             self.theta, self.ws[lane], self.grads[slot],
-                             self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES],
-                             stream=self.side[lane] if self.side else None)
-        for st in self.side:          # the reduction waits for every step
-            main.wait_stream(st)
+            for slot, p in enumerate(active):
+                lane = slot % len(self.ws)
+                g.grp_train_step(self.parts[p], self.model, self.opts, self.xs[p], self.ys[p], self.masks[p], self.theta, self.ws[lane],
+                                 self.grads[slot], record(slot), stream=self.side[lane])
+            for st in self.side:      # the reduction waits for every step
+                main.wait_stream(st)
+        else:
+            for group in _groups(active, len(self.ws)):
+                g.grp_train_steps([self.parts[p] for _, p in group], self.model, [self.opts] * len(group), [self.xs[p] for _, p in group],
+                                  [self.ys[p] for _, p in group], [self.masks[p] for _, p in group], self.theta, self.ws[:len(group)],
+                                  [self.grads[slot] for slot, _ in group], [record(slot) for slot, _ in group])
         g.grp_aggregate(self.grads, self.ld, self.stats, len(active), self.P, self.estimator, self.update)
         self.step_count += 1
         g.grp_optimizer_step(self.opt, self.P, self.step_count, self.theta, self.update, self.m, self.v)
@@ -91,14 +109,13 @@ class MiniBatchTrainer:
     batch_id is the number of iterations done so far (``iteration``).  Within an iteration the phases run as
     in ``PhaseParallelTrainer``.  Sequencing only: the seed order, sampling, steps, reduction and update
     are library calls.
-    ``lanes``: the steps of a phase are independent, and a mini-batch step is a chain of ~60 small launches
-    that leaves most of the chip idle; with ``lanes`` > 1 that many host threads each queue their share of
-    the phase's steps on a stream (default priority) with a workspace of their own, so the steps overlap
-    on the GPU.  The result does not depend on it.
-    ``graphs``: the step of every partition is captured once in a HIP graph (a full batch; the seeds and the
+    ``lanes``: the steps of a phase are independent, and a mini-batch step is a chain of ~40 small launches
+    that leaves most of the chip idle; that many steps (each with a workspace of its own) are made with merged launches.
+    The result does not depend on it.
+    ``graphs``: the steps of every such group of partitions are captured once in a HIP graph (full batches; the seeds and the
     batch id are read from device buffers that are rewritten before each replay), so an iteration costs the
-    host three launches per partition instead of ~60: one thread then keeps ``lanes`` streams busy.  Batches
-    shorter than ``batch_size`` (the last of an epoch) run uncaptured.  Same bits as without.
+    host three launches instead of ~40.  Batches shorter than ``batch_size`` (the last of an epoch) run uncaptured.  Same bits
+    as without.
     """
 
     def __init__(self, parts, model, xs, ys, masks, theta0, estimator, max_active, batch_size, fanouts,
@@ -117,7 +134,9 @@ class MiniBatchTrainer:
         self.update = torch.zeros(self.P, device=dev)
         self.grads = torch.zeros(max_active, self.ld, device=dev)
         self.stats = g.new_stats(max_active, device=dev)
-        self.seeds = [torch.zeros(max(p.n, 1), dtype=torch.int32, device=dev) for p in parts]
+        width = (max(max(p.n for p in parts), 1) + 63) // 64 * 64
+        self.all_seeds = torch.zeros(len(parts), width, dtype=torch.int32, device=dev)
+        self.seeds = [self.all_seeds[i, :max(p.n, 1)] for i, p in enumerate(parts)]
         self.n_train = [g.grp_epoch_seeds(p, mk, sampler_seed, 0, sd) for p, mk, sd in zip(parts, masks, self.seeds)]
         self.iters = max(1, max(-(-c // self.batch_size) for c in self.n_train))
         probe = g.step_opts(estimator=estimator, full_graph=False, seeds=self.seeds[0][:1], fanouts=self.fanouts)
@@ -128,11 +147,10 @@ class MiniBatchTrainer:
         n_lanes = max(1, min(int(lanes), max_active))
         self.ws = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev) for _ in range(n_lanes)]
         self.graphs = bool(graphs)
-        self.side = [torch.cuda.Stream(device=dev) for _ in range(n_lanes)] if (n_lanes > 1 or self.graphs) else []
-        self.pool = ThreadPoolExecutor(max_workers=n_lanes) if (n_lanes > 1 and not self.graphs) else None
+        self.side = torch.cuda.Stream(device=dev) if self.graphs else None     # where steps are captured
         self.bid_dev = torch.zeros(1, dtype=torch.int64, device=dev)          # the batch id of the captured steps
-        self.batch_seeds = [torch.zeros(self.batch_size, dtype=torch.int32, device=dev) for _ in parts] if self.graphs else []
-        self.captured = {}                                                     # partition -> its step's graph
+        self.batch_seeds = torch.zeros(len(parts), self.batch_size, dtype=torch.int32, device=dev) if self.graphs else None
+        self.captured = {}                                                     # partition -> the graph of its group's steps
         self.step_count = 0
         self.epoch = 0
         self.iteration = 0
@@ -147,77 +165,59 @@ class MiniBatchTrainer:
         counts = [g.grp_epoch_seeds(p, mk, self.sampler_seed, self.epoch, sd)
                   for p, mk, sd in zip(self.parts, self.masks, self.seeds)]
         assert counts == self.n_train
-        def one_step(slot, p, it, lane, stream):
-            lo, hi = it * B, min((it + 1) * B, counts[p])
-            st = self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES]
-            if hi <= lo:                               # no seeds left: a zero gradient and an empty record
-                self.grads[slot].zero_()
-                st.zero_()
-                return
-            opts = g.step_opts(estimator=self.estimator, full_graph=False, seeds=self.seeds[p][lo:hi],
-                               fanouts=self.fanouts, sampler_seed=self.sampler_seed, batch_id=self.iteration,
-                               dropout_rate=self.dropout_rate, dropout_seed=self.dropout_seed)
-            g.grp_train_step(self.parts[p], self.model, opts, self.xs[p], self.ys[p], None, self.theta,
-                             self.ws[lane], self.grads[slot], st, stream=stream)
 
-        def lane_job(lane, active, it):                # one host thread: its share of the phase, in order
-            with torch.cuda.stream(self.side[lane]):
-                for slot, p in enumerate(active):
-                    if slot % len(self.side) == lane:
-                        one_step(slot, p, it, lane, self.side[lane])
+        def steps(group, opts):                        # the steps of a group, in merged launches
+            g.grp_train_steps([self.parts[p] for _, p in group], self.model, opts, [self.xs[p] for _, p in group],
+                              [self.ys[p] for _, p in group], None, self.theta, self.ws[:len(group)], [self.grads[slot] for slot, _ in group],
+                              [self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES] for slot, _ in group])
 
-        def graph_step(slot, p, it):                    # replay (capturing at first use) the partition's full-batch step
-            lane = slot % len(self.side)
-            lo = it * B
-            with torch.cuda.stream(self.side[lane]):
-                self.batch_seeds[p].copy_(self.seeds[p][lo:lo + B])
-                if p not in self.captured:
-                    st = self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES]
-                    opts = g.step_opts(estimator=self.estimator, full_graph=False, seeds=self.batch_seeds[p],
-                                       fanouts=self.fanouts, sampler_seed=self.sampler_seed, batch_id_dev=self.bid_dev,
-                                       dropout_rate=self.dropout_rate, dropout_seed=self.dropout_seed,
-                                       flags=g.STEP_ONE_STREAM if len(self.side) > 1 else 0)   # the lanes fill the GPU
-                    # once uncaptured on this stream first: nothing lazy (a kernel's first load) is left for the capture
-                    g.grp_train_step(self.parts[p], self.model, opts, self.xs[p], self.ys[p], None, self.theta,
-                                     self.ws[lane], self.grads[slot], st)
-                    graph = torch.cuda.CUDAGraph()
-                    torch.cuda.synchronize()
-                    with torch.cuda.graph(graph, stream=self.side[lane]):
-                        g.grp_train_step(self.parts[p], self.model, opts, self.xs[p], self.ys[p], None, self.theta,
-                                         self.ws[lane], self.grads[slot], st)
+        def uncaptured(group, it):
+            live, opts = [], []
+            for slot, p in group:
+                lo, hi = it * B, min((it + 1) * B, counts[p])
+                if hi <= lo:                               # no seeds left: a zero gradient and an empty record
+                    self.grads[slot].zero_()
+                    self.stats[slot * g.STATS_BYTES:(slot + 1) * g.STATS_BYTES].zero_()
+                    continue
+                live.append((slot, p))
+                opts.append(g.step_opts(estimator=self.estimator, full_graph=False, seeds=self.seeds[p][lo:hi], fanouts=self.fanouts,
+                                        sampler_seed=self.sampler_seed, batch_id=self.iteration, dropout_rate=self.dropout_rate,
+                                        dropout_seed=self.dropout_seed))
+            if live:
+                steps(live, opts)
+
+        def replay(group):                                 # (captured at first use)
+            first = group[0][1]
+            if first not in self.captured:
+                opts = [g.step_opts(estimator=self.estimator, full_graph=False, seeds=self.batch_seeds[p], fanouts=self.fanouts,
+                                    sampler_seed=self.sampler_seed, batch_id_dev=self.bid_dev, dropout_rate=self.dropout_rate,
+                                    dropout_seed=self.dropout_seed) for _, p in group]
+                main = torch.cuda.current_stream()
+                self.side.wait_stream(main)
+                with torch.cuda.stream(self.side):         # once uncaptured first: nothing lazy (a kernel's first load) is left for the capture
+                    steps(group, opts)
+                main.wait_stream(self.side)
+                graph = torch.cuda.CUDAGraph()
+                torch.cuda.synchronize()
+                with torch.cuda.graph(graph, stream=self.side):
+                    steps(group, opts)
+                for _, p in group:
                     self.captured[p] = (graph, opts)
-                self.captured[p][0].replay()
+            self.captured[first][0].replay()
 
         for it in range(self.iters):
+            lo, hi = it * B, (it + 1) * B
             if self.graphs:
                 self.bid_dev.fill_(self.iteration)
             for active in self.phases():
-                if self.graphs:
-                    main = torch.cuda.current_stream()
-                    ready = main.record_event()
-                    for sd in self.side:
-                        sd.wait_event(ready)
-                    for slot, p in enumerate(active):
-                        if min((it + 1) * B, counts[p]) - it * B == B:
-                            graph_step(slot, p, it)
-                        else:
-                            lane = slot % len(self.side)
-                            with torch.cuda.stream(self.side[lane]):
-                                one_step(slot, p, it, lane, self.side[lane])
-                    for sd in self.side:
-                        main.wait_stream(sd)
-                elif self.pool is None:
-                    for slot, p in enumerate(active):
-                        one_step(slot, p, it, 0, None)
-                else:
-                    main = torch.cuda.current_stream()
-                    ready = main.record_event()        # theta and everything before
-                    for sd in self.side:
-                        sd.wait_event(ready)
-                    for job in [self.pool.submit(lane_job, lane, active, it) for lane in range(len(self.side))]:
-                        job.result()
-                    for sd in self.side:               # the reduction waits for every step
-                        main.wait_stream(sd)
+                groups = _groups(active, len(self.ws))
+                full = [self.graphs and all(hi <= counts[p] for _, p in group) for group in groups]
+                if any(full):                              # the phase's seeds in one copy (rows without a full batch are not read)
+                    a, z = active[0], active[-1] + 1
+                    width = min(hi, self.all_seeds.shape[1]) - lo
+                    self.batch_seeds[a:z, :width].copy_(self.all_seeds[a:z, lo:lo + width])
+                for group, whole in zip(groups, full):
+                    replay(group) if whole else uncaptured(group, it)
                 g.grp_aggregate(self.grads, self.ld, self.stats, len(active), self.P, self.estimator, self.update)
                 self.step_count += 1
                 g.grp_optimizer_step(self.opt, self.P, self.step_count, self.theta, self.update, self.m, self.v)

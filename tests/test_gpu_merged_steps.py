@@ -1,0 +1,78 @@
+"""Steps whose launches are merged give the bits that the same steps give one after another: partitions of very different sizes (other tiles, more
+or fewer launches: long rows, slices of the sums), more steps than one launch takes, steps that cannot be merged."""
+import pytest
+import torch
+
+import synth
+from tests._cases import make_inputs
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _graph(n, E, seed):
+    s, d = synth.rmat_graph(max(2, (n - 1).bit_length()), E, seed=seed, n_nodes=n)
+    return s.to(DEV), d.to(DEV)
+
+
+@pytest.mark.parametrize("arch,dims,sizes,dropout", [
+    ("gcn", [64, 64, 8], [(2500, 6000), (2400, 40000), (1, 0), (9000, 20000)], 0.0),
+    ("gcn", [17, 33, 5], [(300, 900)] * 11, 0.25),
+    ("gcn_res", [32, 32, 32, 6], [(700, 5000), (4100, 9000)], 0.5),
+    ("sage", [30, 100, 70, 200], [(5000, 60000), (64, 100), (40000, 90000)], 0.5),
+    ("gat", [12, 16, 4], [(500, 3000), (600, 3000)], 0.0),
+])
+def test_full_graph_steps(arch, dims, sizes, dropout):
+    import paper_2602_01872_amd as g
+    print(f"[case] merged {arch} {dims} {sizes}", flush=True)
+    code = {"sage": g.ARCH_SAGE_MEAN, "gcn": g.ARCH_GCN, "gcn_res": g.ARCH_GCN_RESIDUAL, "gat": g.ARCH_GAT}[arch]
+    model = g.model_desc(code, dims)
+    P = g.grp_param_count(model)
+    parts, xs, ys, masks, opts = [], [], [], [], []
+    for i, (n, E) in enumerate(sizes):
+        s, d = _graph(n, E, 50 + i) if E else (torch.zeros(0, dtype=torch.int64, device=DEV),) * 2
+        parts.append(g.grp_partition_from_local_coo(s, d, n))
+        x, y, theta = make_inputs(n, dims, arch, 7)
+        xs.append(x.to(DEV))
+        ys.append(y.to(DEV))
+        masks.append((torch.arange(n, device=DEV) % 3 != i % 3).to(torch.uint8) if i % 2 else None)
+        opts.append(g.step_opts(estimator=g.EST_SHRINKAGE, full_graph=True, dropout_rate=dropout, dropout_seed=3, batch_id=i))
+    _compare(g, parts, model, opts, xs, ys, masks, theta.to(DEV), P)
+
+
+@pytest.mark.parametrize("fanouts,batches,dropout", [((5, 4, 3), [100, 7, 300], 0.5), ((2, 2, 2, 2, 2), [50, 60], 0.0), ((6,), [1, 64, 65, 200, 31], 0.0)])
+def test_minibatch_steps(fanouts, batches, dropout):
+    import paper_2602_01872_amd as g
+    print(f"[case] merged mini-batch {fanouts} {batches}", flush=True)
+    dims = [20] + [32] * (len(fanouts) - 1) + [6]
+    model = g.model_desc(g.ARCH_SAGE_MEAN, dims)
+    P = g.grp_param_count(model)
+    parts, xs, ys, opts = [], [], [], []
+    for i, b in enumerate(batches):
+        n = 900 + 1700 * i
+        s, d = _graph(n, 12 * n, 70 + i)
+        parts.append(g.grp_partition_from_local_coo(s, d, n))
+        x, y, theta = make_inputs(n, dims, "sage", 8)
+        xs.append(x.to(DEV))
+        ys.append(y.to(DEV))
+        seeds = torch.randperm(n, generator=torch.Generator().manual_seed(i))[:b].to(torch.int32).to(DEV)
+        opts.append(g.step_opts(estimator=g.EST_BATCH_MIN_DIST, full_graph=False, seeds=seeds, fanouts=fanouts, sampler_seed=4, batch_id=9,
+                                dropout_rate=dropout, dropout_seed=3))
+    _compare(g, parts, model, opts, xs, ys, None, theta.to(DEV), P)
+
+
+def _compare(g, parts, model, opts, xs, ys, masks, theta, P):
+    K = len(parts)
+    size = max(g.grp_step_workspace_bytes(p, model, o) for p, o in zip(parts, opts))
+    ws = [torch.full((size,), 3 + i, dtype=torch.uint8, device=DEV) for i in range(K)]
+    ld = (P + 3) // 4 * 4
+    one, many = torch.full((K, ld), 9.0, device=DEV), torch.full((K, ld), 9.0, device=DEV)
+    st1, stm = g.new_stats(K), g.new_stats(K)
+    cut = lambda t, i: t[i * g.STATS_BYTES:(i + 1) * g.STATS_BYTES]
+    for i in range(K):
+        g.grp_train_step(parts[i], model, opts[i], xs[i], ys[i], masks[i] if masks else None, theta, ws[0], one[i], cut(st1, i))
+    for _ in range(2):
+        g.grp_train_steps(parts, model, opts, xs, ys, masks, theta, ws, list(many), [cut(stm, i) for i in range(K)])
+    torch.cuda.synchronize()
+    assert torch.equal(st1, stm)
+    assert torch.equal(one, many)
