@@ -618,6 +618,269 @@ __global__ __launch_bounds__(256) void spmm_combine_tasks_kernel(const int32_t* 
     }
 }
 
+// ---- plain sums in slabs of columns: G lanes own an edge's part of a row, 16 bytes each (a slab: 64 columns of fp32 or 128 of bf16 with G =
+// 16), and a launch walks the whole structure slab by slab, so that an L2 holds four times as many (quarter) rows of X at F = 256.
+// The lanes of a group fetch the indices of SLAB_BATCH edges of its run and turn them into byte offsets; a lane's offset is handed to its
+// group by DPP, which folds into the addition of the column (G = 8 needs two): no LDS, no 64-bit products.  X is read through a buffer
+// descriptor: a place past the end of a run has an offset beyond it and reads as zeros, without a request to memory and without a select.
+// What bounds them: the lines that miss the L2 (2^20 rows of 256 columns, 25 edges a row: 88 million, a quarter at 6 TB/s in each pass) and,
+// below that, requests in flight.  Sum over the rows of a direction, us, before (spmm_rows_kernel, spmm_tasks_kernel) -> now:
+//   2^20 rows, 25 edges, fp32: F = 16 292 -> 210, 32 446 -> 271, 64 679 -> 514, 128 1146 -> 996, 256 2314 -> 1927 (tasks 1240 -> 936, rows
+//   1030 -> 950), 512 5099 -> 3747;  2^20 rows, 4 edges: F = 16 131 -> 74, 64 246 -> 183, 256 767 -> 714;  3e5 rows, 20 edges: F = 16 89 ->
+//   73, 64 196 -> 165, 256 682 -> 553
+//   bf16: 2^20 rows, 25 edges: F = 32 405 -> 271, 64 600 -> 368, 128 882 -> 679, 256 1467 -> 1289;  3e5 rows, 20 edges: F = 64 165 -> 100
+// (Slabs of 32 columns for wide rows: 79 million lines, but 2350 us: a quarter of the bytes in flight for each index fetched.)
+constexpr int SLAB_BATCH = 16;
+constexpr uint32_t SLAB_NOWHERE = 0xFFFF0000u;             // (a column's bytes may be added to it)
+constexpr uint32_t SLAB_X_BYTES = 0xFFFF0000u;             // X ends before
+
+template <int G, int N> __device__ __forceinline__ uint32_t group_lane(uint32_t v) {      // lane N of the G lanes around this one
+    static_assert(G == 4 || G == 8 || G == 16, "a quad, half a DPP row, a DPP row");
+    if constexpr (G == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, N * 0x55, 0xF, 0xF, false);        // quad_perm
+    int r = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xF, 0xF, false);            // row_newbcast
+    if constexpr (G == 8) r = __builtin_amdgcn_update_dpp(r, (int)v, 0x158 + N, 0xF, 0xC, false);      // (banks 2 and 3: the upper half)
+    return (uint32_t)r;
+}
+template <typename XT, int G> struct Slab {
+    static constexpr int VW = 16 / (int)sizeof(XT);        // columns of a lane
+    static constexpr int COLS = G * VW;                    // of a slab
+    static constexpr int NG = 64 / G;                      // groups of a wavefront
+    static constexpr int Q = SLAB_BATCH / G;               // offsets of a batch that a lane holds: edge q * G + t of the batch in place q
+    __amdgpu_buffer_rsrc_t x;
+    uint32_t pitch, colx;
+    int t, col;                                            // lane of the group, its first column
+    __device__ __forceinline__ Slab(const XT* X, uint32_t x_bytes, int64_t ldx, uint32_t slab, int F) {
+        x = __builtin_amdgcn_make_buffer_rsrc(const_cast<XT*>(X), 0, (int)x_bytes, 0x00020000);
+        pitch = (uint32_t)ldx * (uint32_t)sizeof(XT);
+        t = (int)threadIdx.x % G;
+        col = (int)slab * COLS + VW * t;
+        colx = (uint32_t)(col < F ? col : (int)slab * COLS) * (uint32_t)sizeof(XT);      // (a lane without columns reads what its first one does)
+    }
+    template <int N0, int... U> __device__ __forceinline__ void step(const uint32_t (&off)[Q], float (&acc)[VW], std::integer_sequence<int, U...>) const {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 v[sizeof...(U)];
+        ((v[U] = __builtin_amdgcn_raw_buffer_load_b128(x, (int)(group_lane<G, (N0 + U) % G>(off[(N0 + U) / G]) + colx), 0, 0)), ...);
+#pragma unroll
+        for (int u = 0; u < (int)sizeof...(U); ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (sizeof(XT) == 4) {
+                    acc[q] += __uint_as_float(v[u][q]);
+                } else {
+                    acc[2 * q] += __uint_as_float(v[u][q] << 16);
+                    acc[2 * q + 1] += __uint_as_float(v[u][q] & 0xFFFF0000u);
+                }
+            }
+    }
+    // The first cnt edges of a batch (cnt: the same in every group; a group with fewer has offsets nowhere).
+    __device__ __forceinline__ void gather(const uint32_t (&off)[Q], int cnt, float (&acc)[VW]) const {
+        if (cnt > 4) step<0>(off, acc, std::make_integer_sequence<int, 8>());
+        else step<0>(off, acc, std::make_integer_sequence<int, 4>());
+        if (cnt > 12) step<8>(off, acc, std::make_integer_sequence<int, 8>());
+        else if (cnt > 8) step<8>(off, acc, std::make_integer_sequence<int, 4>());
+    }
+    // Indices of the edges k .. k + SLAB_BATCH - 1 of a run that ends at `end` (edge `some` exists and is read where there are none), and
+    // the offsets of their rows.
+    __device__ __forceinline__ void fetch(const int32_t* __restrict__ idx, int64_t some, uint32_t k, uint32_t end, int32_t (&ix)[Q]) const {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ix[q] = idx[some + (k + q * G + t < end ? (int64_t)(k + q * G + t) : 0)];
+    }
+    __device__ __forceinline__ void place(const int32_t (&ix)[Q], uint32_t k, uint32_t end, uint32_t (&off)[Q]) const {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) off[q] = k + q * G + t < end ? (uint32_t)ix[q] * pitch : SLAB_NOWHERE;
+    }
+    __device__ __forceinline__ void store(float* row, const float (&acc)[VW]) const {      // a partial row
+#pragma unroll
+        for (int q = 0; q < VW; q += 4) *reinterpret_cast<float4*>(row + col + q) = make_float4(acc[q], acc[q + 1], acc[q + 2], acc[q + 3]);
+    }
+};
+
+// The chunks of long rows (n_chunks workgroups of every slab: the groups take a run of the chunk each, their sums are added through
+// LDS in ascending order) and the rows of at most long_thr edges.  A workgroup takes SLAB_ROWS consecutive rows, puts them in order of
+// their lengths (longest first) and deals them to its wavefronts, a row a group, so that the groups of a wavefront end together.
+// While a batch of a row is gathered, the indices of its next batch, or of the next row, are on their way.
+constexpr int SLAB_ROWS = 256;
+constexpr int64_t SLAB_MANY = (int64_t)1 << 17;
+template <typename XT, int G>
+__device__ __forceinline__ void spmm_slab_rows_kernel_body(unsigned gx, const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, int64_t n_rows,
+                                                           int64_t long_thr, const XT* __restrict__ X, int64_t ldx, uint32_t x_bytes,
+                                                           const SpmmEpilogue& ep, uint32_t slab_blocks, int n_chunks,
+                                                           const int64_t* __restrict__ chunk_begin, const int64_t* __restrict__ chunk_end,
+                                                           float* __restrict__ partials, int64_t ld_part) {
+    using S = Slab<XT, G>;
+    constexpr int NG = S::NG, VW = S::VW, Q = S::Q;
+    constexpr int BINS = SPMM_LONG_ROW + 2;                // lengths 0 .. SPMM_LONG_ROW, and above
+    __shared__ union {
+        float4 red[256 * VW / 4];
+        struct {
+            int64_t begin[SLAB_ROWS];
+            uint32_t len[SLAB_ROWS], bin[BINS], wave_sum[4];
+            uint8_t row[SLAB_ROWS];
+        } o;
+    } sh;
+    const int tid = threadIdx.x;
+    const uint32_t slab = blockIdx.x / slab_blocks, block = blockIdx.x - slab * slab_blocks;
+    const S s(X, x_bytes, ldx, slab, ep.F);
+    float acc[VW];
+#pragma unroll
+    for (int q = 0; q < VW; ++q) acc[q] = 0.f;
+    uint32_t off[Q];
+    int32_t ix[Q];
+    if ((int)block < n_chunks) {
+        const int64_t cb = chunk_begin[block];
+        const uint32_t len = (uint32_t)(chunk_end[block] - cb), per = (len + 256 / G - 1) / (256 / G);
+        const uint32_t run = (uint32_t)(tid / G) * per, end = run + per < len ? run + per : len;
+        for (uint32_t k = 0; k < per; k += SLAB_BATCH) {
+            s.fetch(idx, cb, run + k, end, ix);
+            s.place(ix, run + k, end, off);
+            s.gather(off, (int)(per - k), acc);
+        }
+#pragma unroll
+        for (int q = 0; q < VW; q += 4) sh.red[tid * (VW / 4) + q / 4] = make_float4(acc[q], acc[q + 1], acc[q + 2], acc[q + 3]);
+        __syncthreads();
+        if (tid < G * (VW / 4) && (int)slab * S::COLS + 4 * tid < ep.F) {
+            float4 sum = sh.red[tid];
+            for (int g = 1; g < 256 / G; ++g) add4(sum, sh.red[g * (G * VW / 4) + tid]);
+            *reinterpret_cast<float4*>(partials + (int64_t)block * ld_part + (int)slab * S::COLS + 4 * tid) = sum;
+        }
+        return;
+    }
+    const int64_t row0 = (int64_t)((int)block - n_chunks) * SLAB_ROWS;
+    if (tid < BINS) sh.o.bin[tid] = 0;
+    __syncthreads();
+    int64_t b = 0, len = 0;
+    bool mine = row0 + tid < n_rows;
+    if (mine) {
+        b = ptr[row0 + tid];
+        len = ptr[row0 + tid + 1] - b;
+        mine = len <= long_thr;
+    }
+    const int at_bin = BINS - 1 - (int)(len < BINS - 1 ? len : BINS - 1);
+    const uint32_t rank = mine ? atomicAdd(&sh.o.bin[at_bin], 1u) : 0u;
+    __syncthreads();
+    uint32_t rows;
+    const uint32_t first = block_scan<4>(tid < BINS ? sh.o.bin[tid] : 0u, sh.o.wave_sum, rows);
+    if (tid < BINS) sh.o.bin[tid] = first;
+    __syncthreads();
+    if (mine) {
+        const uint32_t at = sh.o.bin[at_bin] + rank;
+        sh.o.begin[at] = b;
+        sh.o.len[at] = (uint32_t)len;
+        sh.o.row[at] = (uint8_t)tid;
+    }
+    __syncthreads();
+    struct Rows { int64_t begin; uint32_t len, most; int row; };      // a group's row, and the longest of the wavefront's
+    const int gi = (tid & 63) / G;
+    auto take = [&](uint32_t q) {
+        const uint32_t at = NG * q + gi;
+        const bool on = at < rows;
+        Rows r{on ? sh.o.begin[at] : 0, on ? sh.o.len[at] : 0u, 0u, on ? (int)sh.o.row[at] : -1};
+        r.most = (uint32_t)__builtin_amdgcn_readlane((int)r.len, 0);
+#pragma unroll
+        for (int g = 1; g < NG; ++g) {                     // (lengths beyond the last bin are in no order)
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)r.len, G * g);
+            r.most = o > r.most ? o : r.most;
+        }
+        return r;
+    };
+    // (a conditional load: a row without edges may begin past the last index)
+    auto fetch = [&](const Rows& r, uint32_t k) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (k + q * G + s.t < r.len) ix[q] = idx[r.begin + k + q * G + s.t];
+    };
+    uint32_t q4 = (uint32_t)tid >> 6, k = 0;
+    if (NG * q4 >= rows) return;
+    Rows cur = take(q4);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) ix[q] = 0;
+    fetch(cur, 0);
+    for (;;) {
+        s.place(ix, k, cur.len, off);
+        const bool last = k + SLAB_BATCH >= cur.most;
+        Rows nxt = cur;
+        uint32_t nk = k + SLAB_BATCH;
+        if (last) {
+            q4 += 4;
+            nk = 0;
+            nxt = take(q4);                                // (none: of no length)
+        }
+        fetch(nxt, nk);
+        if (cur.most > k) s.gather(off, (int)(cur.most - k), acc);
+        if (last) {
+            if (cur.row >= 0) {
+#pragma unroll
+                for (int q = 0; q < VW; q += 4)
+                    if (s.col + q < ep.F)
+                        finish_row<XT>(ep, row0 + cur.row, (int64_t)cur.len, s.col + q, make_float4(acc[q], acc[q + 1], acc[q + 2], acc[q + 3]), X, ldx);
+            }
+#pragma unroll
+            for (int q = 0; q < VW; ++q) acc[q] = 0.f;
+            if (NG * q4 >= rows) return;
+        }
+        cur = nxt;
+        k = nk;
+    }
+}
+template <typename XT, int G> constexpr int SLAB_WGS = sizeof(XT) == 2 || G == 4 ? 5 : 6;       // (more registers spill)
+template <typename XT, int G>
+__global__ __launch_bounds__(256, (SLAB_WGS<XT, G>)) void spmm_slab_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, int64_t n_rows,
+                                                                int64_t long_thr, const XT* __restrict__ X, int64_t ldx, uint32_t x_bytes,
+                                                                SpmmEpilogue ep, uint32_t slab_blocks, int n_chunks,
+                                                                const int64_t* __restrict__ chunk_begin, const int64_t* __restrict__ chunk_end,
+                                                                float* __restrict__ partials, int64_t ld_part) {
+    spmm_slab_rows_kernel_body<XT, G>(gridDim.x, ptr, idx, n_rows, long_thr, X, ldx, x_bytes, ep, slab_blocks, n_chunks, chunk_begin, chunk_end, partials, ld_part);
+}
+template <typename XT, int G> struct spmm_slab_rows_kernel_op {
+    static constexpr int THREADS = 256, WGS = SLAB_WGS<XT, G>;
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { spmm_slab_rows_kernel_body<XT, G>(gx, a...); }
+};
+
+// The tasks of the sliced schedule, one a wavefront: its groups take equal runs of the task's edges, two batches at a time, whose indices are
+// asked for while the two before them are gathered.  (A wavefront that walks several tasks, consecutive or strided, with the next task's
+// indices on their way, is slower the more it has: the wavefronts drift apart and the L2 holds more of X's slices at a time.)
+template <typename XT, int G>
+__global__ __launch_bounds__(256, 6) void spmm_slab_tasks_kernel(const SliceTask* __restrict__ tasks, int64_t n_tasks,
+                                                                 const int32_t* __restrict__ idx, int F, const XT* __restrict__ X, int64_t ldx,
+                                                                 uint32_t x_bytes, float* __restrict__ partials, int64_t ld_part,
+                                                                 uint32_t slab_blocks) {
+    using S = Slab<XT, G>;
+    constexpr int NG = S::NG, VW = S::VW, Q = S::Q;
+    const uint32_t slab = blockIdx.x / slab_blocks;
+    const int64_t p = (int64_t)(blockIdx.x - slab * slab_blocks) * 4 + (threadIdx.x >> 6);
+    if (p >= n_tasks) return;                              // uniform over the wavefront
+    const S s(X, x_bytes, ldx, slab, F);
+    const int gi = (threadIdx.x & 63) / G;
+    const SliceTask tk = tasks[p];
+    const uint32_t per = (tk.len + NG - 1) / NG;
+    const uint32_t run = gi * per, end = run + per < tk.len ? run + per : tk.len;      // the group's edges of the task
+    int32_t i0[Q], i1[Q];
+    s.fetch(idx, tk.begin, run, end, i0);
+    s.fetch(idx, tk.begin, run + SLAB_BATCH, end, i1);
+    float acc[VW];
+#pragma unroll
+    for (int q = 0; q < VW; ++q) acc[q] = 0.f;
+    for (uint32_t k = 0;;) {
+        uint32_t o0[Q], o1[Q];
+        s.place(i0, run + k, end, o0);
+        s.place(i1, run + k + SLAB_BATCH, end, o1);
+        const bool more = k + 2 * SLAB_BATCH < per;
+        if (more) {
+            s.fetch(idx, tk.begin, run + k + 2 * SLAB_BATCH, end, i0);
+            s.fetch(idx, tk.begin, run + k + 3 * SLAB_BATCH, end, i1);
+        }
+        s.gather(o0, (int)(per - k), acc);
+        if (per > k + SLAB_BATCH) s.gather(o1, (int)(per - k - SLAB_BATCH), acc);
+        if (!more) break;
+        k += 2 * SLAB_BATCH;
+    }
+#pragma unroll
+    for (int o = G; o < 64; o <<= 1)
+#pragma unroll
+        for (int q = 0; q < VW; ++q) acc[q] += __shfl_xor(acc[q], o, 64);
+    if (gi == 0 && s.col < F) s.store(partials + (int64_t)tk.id * ld_part, acc);
+}
+
 // Rows of fewer than four columns without room for one vector: one wavefront per row,
 // one lane per column (handles rows of any length itself).
 template <typename XT>
@@ -675,7 +938,38 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
     const int64_t thr = split ? (int64_t)SPMM_LONG_ROW : INT64_MAX;
     const int n_chunks = split && !sliced ? lr->n_chunks : 0;
     const int64_t ld_part = round_up(a.F, 4);
-    if (sliced) {                                          // the long rows' tasks, slice by slice
+    bool tasks_done = false, rows_done = false;
+    constexpr int VW = 16 / (int)sizeof(XT), LANES = G * NJ * 4 / VW;      // lanes of a whole row, 16 bytes each
+    if constexpr (LANES >= 4) {
+        constexpr int SG = LANES < 16 ? LANES : 16;
+        const int64_t slabs = cdiv(a.F, SG * VW);
+        const int64_t x_rows = a.n_src > 0 ? a.n_src : a.n_rows;
+        const int64_t x_bytes = ((x_rows - 1) * a.ldx + round_up(a.F, VW)) * (int64_t)sizeof(XT);
+        const bool units = VW == 4 || (a.F % VW == 0 && a.ldx % VW == 0 && (uintptr_t)a.X % 16 == 0);
+        // several slabs: of whole lines, and at most a quarter of them without columns (20 edges a row, 3e5 rows, fp32, us of rows / slabs:
+        // F = 96 260/225, 160 412/364, 224 612/494, but 72 260/274 and lines cut by slabs: 112 308/312, 120 352/378, 172 530/573)
+        const bool whole = slabs == 1 || ((a.ldx * (int64_t)sizeof(XT)) % 128 == 0 && (uintptr_t)a.X % 128 == 0 && slabs * SG * VW * 3 <= (int64_t)a.F * 4);
+        // (rows of few edges with more than Y to read or write beside them are done a whole row at a time: 3.25 edges, F = 256, mask and
+        // addend: 255 us, in slabs 278; without them 190 and 187)
+        const bool sums = slabs == 1 || a.nnz >= 8 * a.n_rows || (!a.mask && !a.addend && !a.residual && !a.Y2);
+        if (!a.val && !a.colscale && !ep.tight && !a.n_rows_dev && units && whole && sums && x_bytes < (int64_t)SLAB_X_BYTES) {
+            const int64_t task_blocks = sliced ? cdiv(lr->n_tasks, 4) : 0, row_blocks = n_chunks + cdiv(a.n_rows, SLAB_ROWS);
+            if (sliced && slabs * task_blocks < ((int64_t)1 << 24)) {          // (fewer than 2^32 work-items)
+                GRP_PLAIN_LAUNCH((spmm_slab_tasks_kernel<XT, SG>), dim3((unsigned)(slabs * task_blocks)), dim3(256), 0, st, (const SliceTask*)lr->tasks,
+                                 lr->n_tasks, a.idx, a.F, (const XT*)a.X, a.ldx, (uint32_t)x_bytes, a.partials, ld_part, (uint32_t)task_blocks);
+                tasks_done = true;
+            }
+            // SLAB_MANY rows: below, the workgroups of SLAB_ROWS rows leave the GPU idle (1.5e4 .. 1e5 rows, 15 edges a row: 33 against 18 us at
+            // F = 64 and 2e4 rows, 64 and 50 at 4e4, 65 and 64 at 1e5, 81 and 83 at 1.5e5)
+            if (a.n_rows >= SLAB_MANY && slabs * row_blocks < ((int64_t)1 << 24)) {
+                launch(spmm_slab_rows_kernel<XT, SG>, spmm_slab_rows_kernel_op<XT, SG>(), dim3((unsigned)(slabs * row_blocks)), st, a.ptr, a.idx,
+                       a.n_rows, thr, (const XT*)a.X, a.ldx, (uint32_t)x_bytes, ep, (uint32_t)row_blocks, n_chunks,
+                       n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
+                rows_done = true;
+            }
+        }
+    }
+    if (sliced && !tasks_done) {                           // the long rows' tasks, slice by slice
         // at most 2^19 workgroups of four wavefronts: a wavefront that walks a dozen consecutive tasks keeps its
         // pipeline of index and record prefetches full (2^21 / 2^19 / 2^17 workgroups on the 2^32-edge share: bf16
         // launch 44.3 / 42.9 / 42.4 ms, fp32 F = 16 launch 34.7 / 34.7 / 35.6 ms)
@@ -686,7 +980,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         {
             const int64_t pitch_bytes = a.ldx * (int64_t)sizeof(XT);
             const int64_t x_rows = a.n_src > 0 ? a.n_src : a.n_rows;
-            if (!a.val && !a.colscale && pitch_bytes > 0 && (pitch_bytes & (pitch_bytes - 1)) == 0 &&
+            if (LANES < 4 && !a.val && !a.colscale && pitch_bytes > 0 && (pitch_bytes & (pitch_bytes - 1)) == 0 &&
                 x_rows * pitch_bytes <= ((int64_t)1 << 32)) {
                 row_shift = 0;
                 while (((int64_t)1 << row_shift) < pitch_bytes) ++row_shift;
@@ -704,16 +998,16 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
                 if (a.val && a.colscale) go(spmm_tasks_kernel<XT, G / 2, 1, 8, true, true>);
                 else if (a.val) go(spmm_tasks_kernel<XT, G / 2, 1, 8, true, false>);
                 else if (a.colscale) go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, true>);
-                else if (row_shift >= 0) go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false, true>);
-                else go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false>);
+                                else go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false>);
             }
         }
         if (!wide) {
             if (a.val && a.colscale) go(spmm_tasks_kernel<XT, G, NJ, 4, true, true>);
             else if (a.val) go(spmm_tasks_kernel<XT, G, NJ, 4, true, false>);
             else if (a.colscale) go(spmm_tasks_kernel<XT, G, NJ, 4, false, true>);
-            else if (row_shift >= 0) go(spmm_tasks_kernel<XT, G, NJ, 4, false, false, true>);
-            else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
+            else if (row_shift >= 0) {
+                if constexpr (LANES < 4) go(spmm_tasks_kernel<XT, G, NJ, 4, false, false, true>);
+            } else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
         }
     }
     auto rows = [&](auto kernel, auto op, int lanes) {     // lanes: of a row
@@ -725,10 +1019,9 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
                          (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr,
                          a.partials, ld_part);
     };
-    bool rows_done = false;
     if constexpr (std::is_same<XT, __hip_bfloat16>::value && G >= 2 && NJ == 1) {
         // bf16 rows of whole 16-byte units: eight columns per lane, half the lanes per row (twice the rows per wavefront)
-        if (a.F % 8 == 0 && a.ldx % 8 == 0 && ((uintptr_t)a.X % 16) == 0 && !a.self_term) {
+        if (!rows_done && a.F % 8 == 0 && a.ldx % 8 == 0 && ((uintptr_t)a.X % 16) == 0 && !a.self_term) {
             constexpr int GW = G / 2, S = SPMM_GROUPS(GW);
             if (S > 1 && spmm_share(a.n_rows, a.nnz, n_chunks, GW, S)) {
                 if (a.val) rows_val(spmm_rows_kernel<XT, GW, S, 2, true, true>, GW * S);
