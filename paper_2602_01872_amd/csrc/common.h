@@ -397,9 +397,6 @@ grp_status launch_colsum(const float* A, int64_t M, int32_t N, int64_t lda, floa
 // Same with every row multiplied by rowmul[m] first (rowmul may be null).
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul,
                                 float* out, void* scratch, hipStream_t st);
-// inv_in = 1/max(d_in,1); r = 1/sqrt(max(d_in+sl,1)); s = 1/sqrt(max(d_out+sl,1)); rinv = 1/r.
-grp_status launch_degree_scales(const int32_t* d_in, const int32_t* d_out, int64_t n, int sl,
-                                float* inv_in, float* r, float* s, float* rinv, hipStream_t st);
 // Weight re-packing jobs of one step (at most four per layer), run by a single launch.
 struct PackJob {
     const float* in;
@@ -444,7 +441,6 @@ grp_status launch_scale_rows(const float* X, int64_t ldx, const float* rowscale,
 grp_status launch_pad_rows(const float* X, int64_t ldx, int64_t n, int32_t F, float* Y, int64_t ldy, hipStream_t st);
 // out[i] = in[i] * s
 grp_status launch_scale_copy(const float* in, float s, float* out, int64_t n, hipStream_t st);
-grp_status launch_pack_weights(const PackJobs& jobs, hipStream_t st);
 
 // Graph attention model (full-graph mode): workspace size and the whole train step.
 size_t gat_step_workspace_bytes(const grp_partition_t* part, const grp_model_desc* m);
@@ -459,21 +455,39 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
 size_t stats_workspace_bytes(int64_t n);
 // nnz_used = nnz_const + the sum of the n_parts device counters nnz_parts[i][0]; or, when the device counter
 // *bad_seeds is set and positive, minus that count (the record of a step whose seed list was invalid).
-grp_status launch_stats(int64_t n_loss, const int32_t* loss_nodes /*null = 0..n-1 by mask*/,
-                        const uint8_t* mask, const int32_t* d_local, const int64_t* d_global,
-                        const int32_t* sampled_count /*null = full graph*/, int64_t nnz_const,
-                        const int64_t* const* nnz_parts /*HOST array of device pointers*/, int n_parts,
-                        void* scratch, grp_step_stats* out, hipStream_t st,
-                        const double* w_local = nullptr, const double* w_global = nullptr /*weight masses: full graph*/,
-                        const int64_t* bad_seeds = nullptr);
-grp_status launch_softmax_xent(int64_t n_rows, int32_t C, const float* Z, int64_t ldz,
-                               const int32_t* labels, const int32_t* node_of_row /*null = row*/,
-                               const uint8_t* mask, int32_t node_level,
-                               const int32_t* d_local, const int64_t* d_global,
+struct StatsIn {
+    int64_t n_loss = 0;
+    const int32_t* nodes = nullptr;                    // null: 0 .. n_loss - 1 by mask
+    const uint8_t* mask = nullptr;
+    const int32_t* d_local = nullptr;
+    const int64_t* d_global = nullptr;
+    const int32_t* sampled_count = nullptr;            // null: full graph
+    int64_t nnz_const = 0;
+    const int64_t* const* nnz_parts = nullptr;         // HOST array of device pointers
+    int n_parts = 0;
+    void* scratch = nullptr;                           // stats_workspace_bytes
+    const double *w_local = nullptr, *w_global = nullptr;      // weight masses: full graph
+    const int64_t* bad_seeds = nullptr;
+};
+// What a step does before its first layer, in one launch: the statistics' partial sums, the degree scales (inv_in = 1/max(d_in,1);
+// r = 1/sqrt(max(d_in+sl,1)); s = 1/sqrt(max(d_out+sl,1)); rinv = 1/r; n = 0: none) and the re-packed weights (may be none).
+struct DegreeScales {
+    const int32_t *d_in = nullptr, *d_out = nullptr;
+    int64_t n = 0;
+    int sl = 0;
+    float *inv_in = nullptr, *r = nullptr, *s = nullptr, *rinv = nullptr;      // each may be null
+};
+struct StepPrelude {
+    StatsIn stats;
+    DegreeScales degrees;
+    PackJobs pack;
+};
+grp_status launch_prelude(const StepPrelude& pre, hipStream_t st);
+// Reads the statistics' partial sums that launch_prelude left in in.scratch, writes the whole record.
+grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int64_t ldz,
+                               const int32_t* labels, int32_t node_level,
                                const float* rowscale /*null; multiplies dZ rows*/,
-                               float* dZ, int64_t lddz, void* scratch,
-                               grp_step_stats* stats /*reads S, writes loss*/, hipStream_t st,
-                               const double* w_local = nullptr, const double* w_global = nullptr);
+                               float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st);
 // inv[v] = mass[v] > 0 ? 1 / mass[v] : 0
 grp_status launch_inverse_mass(const double* mass, int64_t n, float* inv, hipStream_t st);
 

@@ -41,8 +41,8 @@ grp_status launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
 // All weight re-packing jobs of a step in one launch: job j owns the flat element range
 // [begin_j, begin_{j+1}) of the grid and is either a zero-padded copy or a zero-padded transpose.
 template <int MOST>
-__device__ __forceinline__ void pack_weights_kernel_body(unsigned gx, const PackJobsOf<MOST>& jobs) {
-    const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_weights_block(uint32_t block, const PackJobsOf<MOST>& jobs) {
+    const int64_t e0 = (int64_t)block * 256 + threadIdx.x;
     if (e0 >= jobs.begin[jobs.n]) return;
     int j = 0;
     while (e0 >= jobs.begin[j + 1]) ++j;
@@ -58,16 +58,6 @@ __device__ __forceinline__ void pack_weights_kernel_body(unsigned gx, const Pack
         J.out[(int64_t)r * J.ld_out + c] = (r < J.rows && c < J.cols) ? J.in[(int64_t)r * J.cols + c] * J.scale : 0.f;
     }
 }
-template <int MOST>
-__global__ __launch_bounds__(256) void pack_weights_kernel(PackJobsOf<MOST> jobs) {
-    pack_weights_kernel_body<MOST>(gridDim.x, jobs);
-}
-template <int MOST>
-struct pack_weights_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { pack_weights_kernel_body<MOST>(gx, a...); }
-};
-
 void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, bool transpose, int32_t out_rows_pad,
                    float* out, int64_t ld_out, float scale) {
     PackJob& J = jobs.job[jobs.n];
@@ -78,24 +68,6 @@ void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, 
     const int64_t width = round_up(transpose ? rows : cols, 4);
     jobs.begin[jobs.n + 1] = jobs.begin[jobs.n] + (int64_t)out_rows_pad * width;
     ++jobs.n;
-}
-
-grp_status launch_pack_weights(const PackJobs& jobs, hipStream_t st) {
-    if (jobs.n == 0 || jobs.begin[jobs.n] == 0) return GRP_OK;
-    ProfScope ps("pack_weights", st);
-    const dim3 grid((unsigned)cdiv(jobs.begin[jobs.n], 256));
-    constexpr int FEW = 12;                            // three layers: arguments of several steps fit one launch
-    if (jobs.n <= FEW) {
-        PackJobsOf<FEW> few;
-        few.n = jobs.n;
-        for (int j = 0; j < jobs.n; ++j) few.job[j] = jobs.job[j];
-        for (int j = 0; j <= jobs.n; ++j) few.begin[j] = jobs.begin[j];
-        launch(pack_weights_kernel<FEW>, pack_weights_kernel_op<FEW>(), grid, st, few);
-    } else {
-        GRP_PLAIN_LAUNCH(pack_weights_kernel<4 * GRP_MAX_LAYERS>, grid, dim3(256), 0, st, jobs);
-    }
-    GRP_LAUNCH_CHECK();
-    return GRP_OK;
 }
 
 // ------------------------------------------------------------------ dropout
@@ -422,39 +394,16 @@ grp_status launch_colsum(const float* A, int64_t M, int32_t N, int64_t lda, floa
 // ------------------------------------------------------------------ degree scales
 // inv_in[v] = 1/max(d_in,1); r[v] = 1/sqrt(max(d_in+sl,1)); s[v] = 1/sqrt(max(d_out+sl,1));
 // rinv[v] = sqrt(max(d_in+sl,1)).  Null outputs are skipped.
-__device__ __forceinline__ void degree_scales_kernel_body(unsigned gx, const int32_t* __restrict__ d_in,
-                                                            const int32_t* __restrict__ d_out, int64_t n, int sl,
-                                                            float* __restrict__ inv_in, float* __restrict__ r,
-                                                            float* __restrict__ s, float* __restrict__ rinv) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= n) return;
-    const int di = d_in[v], dout = d_out[v];
-    if (inv_in) inv_in[v] = 1.0f / (float)(di > 1 ? di : 1);
+__device__ __forceinline__ void degree_scales_block(uint32_t block, const DegreeScales& d) {
+    const int64_t v = (int64_t)block * 256 + threadIdx.x;
+    if (v >= d.n) return;
+    const int di = d.d_in[v], dout = d.d_out[v], sl = d.sl;
+    if (d.inv_in) d.inv_in[v] = 1.0f / (float)(di > 1 ? di : 1);
     const float a = (float)(di + sl > 1 ? di + sl : 1), b = (float)(dout + sl > 1 ? dout + sl : 1);
-    if (r) r[v] = 1.0f / sqrtf(a);
-    if (rinv) rinv[v] = sqrtf(a);
-    if (s) s[v] = 1.0f / sqrtf(b);
+    if (d.r) d.r[v] = 1.0f / sqrtf(a);
+    if (d.rinv) d.rinv[v] = sqrtf(a);
+    if (d.s) d.s[v] = 1.0f / sqrtf(b);
 }
-__global__ __launch_bounds__(256) void degree_scales_kernel(const int32_t* __restrict__ d_in,
-                                                            const int32_t* __restrict__ d_out, int64_t n, int sl,
-                                                            float* __restrict__ inv_in, float* __restrict__ r,
-                                                            float* __restrict__ s, float* __restrict__ rinv) {
-    degree_scales_kernel_body(gridDim.x, d_in, d_out, n, sl, inv_in, r, s, rinv);
-}
-struct degree_scales_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { degree_scales_kernel_body(gx, a...); }
-};
-
-grp_status launch_degree_scales(const int32_t* d_in, const int32_t* d_out, int64_t n, int sl, float* inv_in, float* r,
-                                float* s, float* rinv, hipStream_t st) {
-    if (n == 0) return GRP_OK;
-    ProfScope ps("degree_scales", st);
-    launch(degree_scales_kernel, degree_scales_kernel_op(), dim3((unsigned)cdiv(n, 256)), st, d_in, d_out, n, sl, inv_in, r, s, rinv);
-    GRP_LAUNCH_CHECK();
-    return GRP_OK;
-}
-
 // ------------------------------------------------------------------ coverage statistics
 // At most this many partial results; fewer where the rows do not fill them: the one workgroup that adds them up waits for each
 // (2500 rows: the four kernels of statistics and loss 20 -> 12 us).
@@ -466,7 +415,10 @@ struct StatsPartial {
     int64_t s, r_int;
 };
 
-size_t stats_workspace_bytes(int64_t) { return (size_t)STATS_BLOCKS * sizeof(StatsPartial) + STATS_BLOCKS * sizeof(double); }
+// (the partial sums, their counts of loss rows once more side by side, the partial losses)
+size_t stats_workspace_bytes(int64_t) { return (size_t)STATS_BLOCKS * (sizeof(StatsPartial) + sizeof(int64_t) + sizeof(double)); }
+static int64_t* stats_rows(void* scratch) { return (int64_t*)((char*)scratch + (size_t)STATS_BLOCKS * sizeof(StatsPartial)); }
+static double* stats_loss(void* scratch) { return (double*)(stats_rows(scratch) + STATS_BLOCKS); }
 
 __device__ __forceinline__ double degree_ratio(int64_t dl, int64_t dg) { return dg > 0 ? (double)dl / (double)dg : 1.0; }
 
@@ -484,25 +436,33 @@ __device__ __forceinline__ double coverage_ratio(const CoverageIn& c, int64_t v)
 }
 
 // Rows are loss candidates: node = nodes ? nodes[i] : i; kept if !mask || mask[node].
-__device__ __forceinline__ void stats_partial_kernel_body(unsigned gx, int64_t n_rows, const int32_t* __restrict__ nodes,
-                                                            const uint8_t* __restrict__ mask, CoverageIn cv,
-                                                            const int32_t* __restrict__ sampled,
-                                                            StatsPartial* __restrict__ part) {
+struct StatsArgs {
+    int64_t n_rows;
+    const int32_t* nodes;
+    const uint8_t* mask;
+    CoverageIn cv;
+    const int32_t* sampled;
+    StatsPartial* part;
+    int64_t* part_rows;
+    uint32_t blocks;
+};
+__device__ __forceinline__ void stats_partial_block(uint32_t block, const StatsArgs& a) {
+    const CoverageIn& cv = a.cv;
     __shared__ double smd[4];
     __shared__ int64_t smi[4];
     double ratio = 0.0, rd = 0.0;
     int64_t s = 0, ri = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_rows; i += (int64_t)gx * 256) {
-        const int64_t v = nodes ? nodes[i] : i;
-        if (mask && !mask[v]) continue;
+    for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < a.n_rows; i += (int64_t)a.blocks * 256) {
+        const int64_t v = a.nodes ? a.nodes[i] : i;
+        if (a.mask && !a.mask[v]) continue;
         const int64_t dl = cv.d_local[v], dg = cv.d_global[v];
         s += 1;
         ratio += coverage_ratio(cv, v);
         if (cv.w_local) {         // full graph, weight masses: missing mass in units of the mean local edge weight
             const double wl = cv.w_local[v];
             rd += dl > 0 ? (cv.w_global[v] - wl) * (double)dl / wl : (double)dg;
-        } else if (sampled) {
-            if (dl > 0) rd += (double)(dg - dl) * (double)sampled[i] / (double)dl;
+        } else if (a.sampled) {
+            if (dl > 0) rd += (double)(dg - dl) * (double)a.sampled[i] / (double)dl;
         } else {
             ri += dg - dl;
         }
@@ -511,80 +471,109 @@ __device__ __forceinline__ void stats_partial_kernel_body(unsigned gx, int64_t n
     rd = block_sum<double>(rd, smd);
     s = block_sum<int64_t>(s, smi);
     ri = block_sum<int64_t>(ri, smi);
-    if (threadIdx.x == 0) part[blockIdx.x] = StatsPartial{ratio, rd, s, ri};
+    if (threadIdx.x == 0) {
+        a.part[block] = StatsPartial{ratio, rd, s, ri};
+        a.part_rows[block] = s;
+    }
 }
-__global__ __launch_bounds__(256) void stats_partial_kernel(int64_t n_rows, const int32_t* __restrict__ nodes,
-                                                            const uint8_t* __restrict__ mask, CoverageIn cv,
-                                                            const int32_t* __restrict__ sampled,
-                                                            StatsPartial* __restrict__ part) {
-    stats_partial_kernel_body(gridDim.x, n_rows, nodes, mask, cv, sampled, part);
+
+// A step's first launch: statistics, degree scales and weights are independent, and a launch costs as much as any of them does on a small
+// partition (10 000 nodes in four partitions: an iteration of 28 launches 148 us, of 25 132 us;
+// the other launch it lost is that of the statistics' end, which the record's kernel does with the loss).
+template <int MOST>
+__device__ __forceinline__ void prelude_kernel_body(unsigned gx, const StatsArgs& stats, const DegreeScales& degrees, uint32_t degree_blocks,
+                                                    const PackJobsOf<MOST>& pack) {
+    uint32_t block = blockIdx.x;
+    if (block < stats.blocks) return stats_partial_block(block, stats);
+    block -= stats.blocks;
+    if (block < degree_blocks) return degree_scales_block(block, degrees);
+    pack_weights_block<MOST>(block - degree_blocks, pack);
 }
-struct stats_partial_kernel_op {
+template <int MOST>
+__global__ __launch_bounds__(256) void prelude_kernel(StatsArgs stats, DegreeScales degrees, uint32_t degree_blocks, PackJobsOf<MOST> pack) {
+    prelude_kernel_body<MOST>(gridDim.x, stats, degrees, degree_blocks, pack);
+}
+template <int MOST>
+struct prelude_kernel_op {
     static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { stats_partial_kernel_body(gx, a...); }
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { prelude_kernel_body<MOST>(gx, a...); }
 };
 
+grp_status launch_prelude(const StepPrelude& pre, hipStream_t st) {
+    const StatsIn& in = pre.stats;
+    if (in.w_local && in.sampled_count) return fail(GRP_EUNSUPPORTED, "coverage statistics: weight masses in mini-batch mode");
+    ProfScope ps("step_prelude", st);
+    const StatsArgs a{in.n_loss, in.nodes, in.mask, CoverageIn{in.d_local, in.d_global, in.w_local, in.w_global}, in.sampled_count,
+                      (StatsPartial*)in.scratch, stats_rows(in.scratch), (uint32_t)stats_blocks(in.n_loss, 256)};
+    const uint32_t degree_blocks = (uint32_t)cdiv(pre.degrees.n, 256);
+    const dim3 grid((unsigned)(a.blocks + degree_blocks + cdiv(pre.pack.begin[pre.pack.n], 256)));
+    constexpr int FEW = 12;                            // three layers: arguments of several steps fit one launch
+    if (pre.pack.n <= FEW) {
+        PackJobsOf<FEW> few;
+        few.n = pre.pack.n;
+        for (int j = 0; j < few.n; ++j) few.job[j] = pre.pack.job[j];
+        for (int j = 0; j <= few.n; ++j) few.begin[j] = pre.pack.begin[j];
+        launch(prelude_kernel<FEW>, prelude_kernel_op<FEW>(), grid, st, a, pre.degrees, degree_blocks, few);
+    } else {
+        GRP_PLAIN_LAUNCH(prelude_kernel<4 * GRP_MAX_LAYERS>, grid, dim3(256), 0, st, a, pre.degrees, degree_blocks, pre.pack);
+    }
+    GRP_LAUNCH_CHECK();
+    return GRP_OK;
+}
+
+// The number of loss rows, in every thread (LDS: sm).
+__device__ __forceinline__ int64_t loss_rows(const int64_t* __restrict__ part_rows, int blocks, int64_t* sm /*[4]*/) {
+    int64_t s = 0;
+    for (int b = threadIdx.x; b < blocks; b += 256) s += part_rows[b];
+    return block_sum<int64_t>(s, sm);
+}
 struct NnzParts {
     const int64_t* p[GRP_MAX_LAYERS];
     int n;
     const int64_t* bad_seeds;      // null, or the number of seeds that were outside the partition
 };
 
-__device__ __forceinline__ void stats_final_kernel_body(unsigned gx, const StatsPartial* __restrict__ part, int blocks,
-                                                          int full_graph, int64_t nnz_const, const NnzParts& np,
-                                                          grp_step_stats* __restrict__ out) {
+// The step's record, by one workgroup.
+struct RecordArgs {
+    const StatsPartial* part;
+    int blocks, full_graph;
+    int64_t nnz_const;
+    NnzParts np;
+    const double* loss_part;
+    int loss_blocks;
+    grp_step_stats* out;
+};
+__device__ __forceinline__ void record_kernel_body(unsigned gx, const RecordArgs& a) {
     __shared__ double smd[4];
     __shared__ int64_t smi[4];
-    double ratio = 0.0, rd = 0.0;
+    double ratio = 0.0, rd = 0.0, loss = 0.0;
     int64_t s = 0, ri = 0;
-    for (int b = threadIdx.x; b < blocks; b += 256) {
-        ratio += part[b].ratio; rd += part[b].r_dbl; s += part[b].s; ri += part[b].r_int;
+    for (int b = threadIdx.x; b < a.blocks; b += 256) {
+        ratio += a.part[b].ratio; rd += a.part[b].r_dbl; s += a.part[b].s; ri += a.part[b].r_int;
     }
+    for (int b = threadIdx.x; b < a.loss_blocks; b += 256) loss += a.loss_part[b];
     ratio = block_sum<double>(ratio, smd);
     rd = block_sum<double>(rd, smd);
+    loss = block_sum<double>(loss, smd);
     s = block_sum<int64_t>(s, smi);
     ri = block_sum<int64_t>(ri, smi);
     if (threadIdx.x == 0) {
-        out->loss = 0.0;
+        grp_step_stats* const out = a.out;
+        out->loss = s > 0 ? loss / (double)s : 0.0;
         out->sum_ratio = ratio;
-        out->R = full_graph ? (double)ri : rd;
+        out->R = a.full_graph ? (double)ri : rd;
         out->S = s;
-        int64_t nnz_used = nnz_const;
-        for (int i = 0; i < np.n; ++i) nnz_used += np.p[i][0];
-        if (np.bad_seeds && *np.bad_seeds > 0) nnz_used = -*np.bad_seeds;
+        int64_t nnz_used = a.nnz_const;
+        for (int i = 0; i < a.np.n; ++i) nnz_used += a.np.p[i][0];
+        if (a.np.bad_seeds && *a.np.bad_seeds > 0) nnz_used = -*a.np.bad_seeds;
         out->nnz_used = nnz_used;
     }
 }
-__global__ __launch_bounds__(256) void stats_final_kernel(const StatsPartial* __restrict__ part, int blocks,
-                                                          int full_graph, int64_t nnz_const, NnzParts np,
-                                                          grp_step_stats* __restrict__ out) {
-    stats_final_kernel_body(gridDim.x, part, blocks, full_graph, nnz_const, np, out);
-}
-struct stats_final_kernel_op {
+__global__ __launch_bounds__(256) void record_kernel(RecordArgs a) { record_kernel_body(gridDim.x, a); }
+struct record_kernel_op {
     static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { stats_final_kernel_body(gx, a...); }
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { record_kernel_body(gx, a...); }
 };
-
-grp_status launch_stats(int64_t n_rows, const int32_t* nodes, const uint8_t* mask, const int32_t* d_local,
-                        const int64_t* d_global, const int32_t* sampled_count, int64_t nnz_const,
-                        const int64_t* const* nnz_parts, int n_parts, void* scratch, grp_step_stats* out, hipStream_t st,
-                        const double* w_local, const double* w_global, const int64_t* bad_seeds) {
-    NnzParts np;
-    np.n = n_parts;
-    np.bad_seeds = bad_seeds;
-    for (int i = 0; i < GRP_MAX_LAYERS; ++i) np.p[i] = i < n_parts ? nnz_parts[i] : nullptr;
-    ProfScope ps("coverage_stats", st);
-    StatsPartial* part = (StatsPartial*)scratch;
-    if (w_local && sampled_count) return fail(GRP_EUNSUPPORTED, "coverage statistics: weight masses in mini-batch mode");
-    const CoverageIn cv{d_local, d_global, w_local, w_global};
-    const int blocks = stats_blocks(n_rows, 256);
-    launch(stats_partial_kernel, stats_partial_kernel_op(), dim3((unsigned)blocks), st, n_rows, nodes, mask, cv, sampled_count, part);
-    GRP_LAUNCH_CHECK();
-    launch(stats_final_kernel, stats_final_kernel_op(), dim3(1), st, (const StatsPartial*)part, blocks, (sampled_count || w_local) ? 0 : 1, nnz_const,
-           np, out);
-    GRP_LAUNCH_CHECK();
-    return GRP_OK;
-}
 
 // ------------------------------------------------------------------ softmax cross-entropy
 // 16 lanes per row; dZ[row,:] = w (softmax(z) - onehot(y)) / |S| for loss rows, 0 otherwise
@@ -596,11 +585,12 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(int64_t n_rows, int C
                                                            CoverageIn cv,
                                                            const float* __restrict__ rowscale,
                                                            float* __restrict__ dZ, int64_t lddz, int c_store,
-                                                           const grp_step_stats* __restrict__ stats,
+                                                           const int64_t* __restrict__ part_rows, int stats_blocks,
                                                            double* __restrict__ loss_part) {
     __shared__ double smd[4];
     const int t = threadIdx.x & 15;
-    const int64_t S = stats->S;
+    __shared__ int64_t smi[4];
+    const int64_t S = loss_rows(part_rows, stats_blocks, smi);
     const float inv_s = S > 0 ? 1.0f / (float)S : 0.f;
     double loss = 0.0;
     for (int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); row < n_rows; row += (int64_t)gridDim.x * 16) {
@@ -645,11 +635,12 @@ __device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_
                                                                CoverageIn cv,
                                                                const float* __restrict__ rowscale,
                                                                float* __restrict__ dZ, int64_t lddz, int c_store,
-                                                               const grp_step_stats* __restrict__ stats,
+                                                               const int64_t* __restrict__ part_rows, int stats_blocks,
                                                                double* __restrict__ loss_part) {
     __shared__ double smd[4];
     const int t = threadIdx.x & 15;
-    const int64_t S = stats->S;
+    __shared__ int64_t smi[4];
+    const int64_t S = loss_rows(part_rows, stats_blocks, smi);
     const float inv_s = S > 0 ? 1.0f / (float)S : 0.f;
     const int64_t stride = (int64_t)gx * 16;
     double loss = 0.0;
@@ -710,9 +701,9 @@ __global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, i
                                                                CoverageIn cv,
                                                                const float* __restrict__ rowscale,
                                                                float* __restrict__ dZ, int64_t lddz, int c_store,
-                                                               const grp_step_stats* __restrict__ stats,
+                                                               const int64_t* __restrict__ part_rows, int stats_blocks,
                                                                double* __restrict__ loss_part) {
-    softmax_xent_reg_kernel_body<NV>(gridDim.x, n_rows, C, Z, ldz, labels, nodes, mask, node_level, cv, rowscale, dZ, lddz, c_store, stats, loss_part);
+    softmax_xent_reg_kernel_body<NV>(gridDim.x, n_rows, C, Z, ldz, labels, nodes, mask, node_level, cv, rowscale, dZ, lddz, c_store, part_rows, stats_blocks, loss_part);
 }
 template <int NV>
 struct softmax_xent_reg_kernel_op {
@@ -720,36 +711,18 @@ struct softmax_xent_reg_kernel_op {
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { softmax_xent_reg_kernel_body<NV>(gx, a...); }
 };
 
-__device__ __forceinline__ void loss_final_kernel_body(unsigned gx, const double* __restrict__ part, int blocks,
-                                                         grp_step_stats* __restrict__ stats) {
-    __shared__ double smd[4];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < blocks; b += 256) s += part[b];
-    s = block_sum<double>(s, smd);
-    if (threadIdx.x == 0) stats->loss = stats->S > 0 ? s / (double)stats->S : 0.0;
-}
-__global__ __launch_bounds__(256) void loss_final_kernel(const double* __restrict__ part, int blocks,
-                                                         grp_step_stats* __restrict__ stats) {
-    loss_final_kernel_body(gridDim.x, part, blocks, stats);
-}
-struct loss_final_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { loss_final_kernel_body(gx, a...); }
-};
-
-grp_status launch_softmax_xent(int64_t n_rows, int32_t C, const float* Z, int64_t ldz, const int32_t* labels,
-                               const int32_t* node_of_row, const uint8_t* mask, int32_t node_level,
-                               const int32_t* d_local, const int64_t* d_global, const float* rowscale, float* dZ,
-                               int64_t lddz, void* scratch, grp_step_stats* stats, hipStream_t st,
-                               const double* w_local, const double* w_global) {
+grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int32_t node_level,
+                               const float* rowscale, float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st) {
+    const int64_t n_rows = in.n_loss;
     ProfScope ps("softmax_xent", st, 0.0, 8.0 * n_rows * C);
-    const CoverageIn cv{d_local, d_global, w_local, w_global};
-    double* loss_part = (double*)((char*)scratch + (size_t)STATS_BLOCKS * sizeof(StatsPartial));
+    const CoverageIn cv{in.d_local, in.d_global, in.w_local, in.w_global};
+    double* const loss_part = stats_loss(in.scratch);
+    const int counted = stats_blocks(in.n_loss, 256);
     int c_store = (int)round_up(C, 4);
     if (c_store > lddz) c_store = (int)lddz;
 #define GRP_SOFTMAX_ARGS                                                                                     \
-    n_rows, C, Z, ldz, labels, node_of_row, mask, node_level, cv, rowscale, dZ, lddz, c_store,               \
-        (const grp_step_stats*)stats, loss_part
+    n_rows, C, Z, ldz, labels, in.nodes, in.mask, node_level, cv, rowscale, dZ, lddz, c_store,               \
+        (const int64_t*)stats_rows(in.scratch), counted, loss_part
     const int blocks = stats_blocks(n_rows, 16);
     auto go = [&](auto kernel, auto op) { launch(kernel, op, dim3((unsigned)blocks), st, GRP_SOFTMAX_ARGS); };
     if (c_store <= 16) go(softmax_xent_reg_kernel<1>, softmax_xent_reg_kernel_op<1>());
@@ -760,7 +733,11 @@ grp_status launch_softmax_xent(int64_t n_rows, int32_t C, const float* Z, int64_
     else GRP_PLAIN_LAUNCH(softmax_xent_kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS);
 #undef GRP_SOFTMAX_ARGS
     GRP_LAUNCH_CHECK();
-    launch(loss_final_kernel, loss_final_kernel_op(), dim3(1), st, (const double*)loss_part, blocks, stats);
+    RecordArgs r{(const StatsPartial*)in.scratch, counted, (in.sampled_count || in.w_local) ? 0 : 1, in.nnz_const, {}, loss_part, blocks, stats};
+    r.np.n = in.n_parts;
+    r.np.bad_seeds = in.bad_seeds;
+    for (int i = 0; i < GRP_MAX_LAYERS; ++i) r.np.p[i] = i < in.n_parts ? in.nnz_parts[i] : nullptr;
+    launch(record_kernel, record_kernel_op(), dim3(1), st, r);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }

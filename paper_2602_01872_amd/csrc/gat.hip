@@ -566,13 +566,15 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
     GatPlan p = gat_plan(g, m, ws, ws_bytes);
     const int64_t n = g->n;
     const int k = m->n_layers;
-    GRP_TRY(launch_stats(n, nullptr, mask, g->d_local_in, g->d_global_in, nullptr, g->nnz, nullptr, 0, p.stats_ws, stats, st));
+    StepPrelude pre;
+    StatsIn& si = pre.stats;
+    si.n_loss = n; si.mask = mask; si.d_local = g->d_local_in; si.d_global = g->d_global_in; si.nnz_const = g->nnz; si.scratch = p.stats_ws;
+    GRP_TRY(launch_prelude(pre, st));
     if (n == 0) {                                       // nothing to train on: zero gradient
         int64_t P = 0;
         for (int l = 0; l < k; ++l) P += (int64_t)m->dims[l] * m->dims[l + 1] + 3 * m->dims[l + 1];
         GRP_TRY(launch_fill_zero(grad, (size_t)P * sizeof(float), st));      // a kernel, so the step can be captured in a graph
-        return launch_softmax_xent(0, m->dims[k], nullptr, 4, labels, nullptr, mask, o->estimator == GRP_EST_NODE_LEVEL,
-                                   g->d_local_in, g->d_global_in, nullptr, p.dZa, 4, p.stats_ws, stats, st);
+        return launch_softmax_xent(si, m->dims[k], nullptr, 4, labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, p.dZa, 4, stats, st);
     }
     const DropoutPlan drop = dropout_plan(o);
     // ---------------- packed weights
@@ -614,8 +616,7 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
     const int C = m->dims[k];
     float* dZ = p.dZa;
     float* dZ_other = p.dZb;
-    GRP_TRY(launch_softmax_xent(n, C, p.L[k - 1].Hout, ldp4(C), labels, nullptr, mask, o->estimator == GRP_EST_NODE_LEVEL,
-                                g->d_local_in, g->d_global_in, nullptr, dZ, ldp4(C), p.stats_ws, stats, st));
+    GRP_TRY(launch_softmax_xent(si, C, p.L[k - 1].Hout, ldp4(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp4(C), stats, st));
     // ---------------- backward
     for (int l = k - 1; l >= 0; --l) {
         const GatLayer& L = p.L[l];

@@ -215,9 +215,8 @@ static void set_mean(SpmmArgs& s, const Block& B) {
 
 // bwd_scale multiplies the weights of the products that carry a gradient back through a layer
 // output: 1 / (1 - rate) with dropout (the kept elements were scaled by it), else 1.
-static grp_status prep_weights(const grp_model_desc* m, const float* theta, StepPlan& p, float bwd_scale, hipStream_t st) {
+static void weight_jobs(const grp_model_desc* m, const float* theta, StepPlan& p, float bwd_scale, PackJobs& jobs) {
     const bool sage = m->arch == GRP_ARCH_SAGE_MEAN;
-    PackJobs jobs;
     for (int l = 0; l < m->n_layers; ++l) {
         const LayerBufs& L = p.L[l];
         const int fin = m->dims[l], fout = m->dims[l + 1];
@@ -230,16 +229,16 @@ static grp_status prep_weights(const grp_model_desc* m, const float* theta, Step
             if (sage) pack_jobs_add(jobs, theta + L.off_wn, fin, fout, false, (int)ldp(fin), L.Wp_n, L.ldwp, bwd_scale);
         }
     }
-    return launch_pack_weights(jobs, st);
 }
 
 static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, const grp_step_opts* o, const Block* blk,
-                            const void* X, const int32_t* labels, const uint8_t* mask, const int32_t* loss_nodes,
+                            const void* X, const int32_t* labels, StepPrelude& pre,
                             const float* theta, StepPlan& p, hipStream_t st, float* grad, grp_step_stats* stats,
                             hipEvent_t transposed_ready = nullptr) {
     const int k = m->n_layers;
     const DropoutPlan drop = dropout_plan(o);
-    GRP_TRY(prep_weights(m, theta, p, drop.scale, st));
+    weight_jobs(m, theta, p, drop.scale, pre.pack);
+    GRP_TRY(launch_prelude(pre, st));
 
     // ---------------- forward
     const void* H = X;
@@ -300,12 +299,9 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
 
     // ---------------- loss
     const int C = m->dims[k];
-    const int64_t n_loss_rows = blk[k - 1].n_dst;
     float* dZ = p.dZa;
     float* dZ_other = p.dZb;
-    GRP_TRY(launch_softmax_xent(n_loss_rows, C, p.L[k - 1].H_out, ldp(C), labels, loss_nodes, mask,
-                                o->estimator == GRP_EST_NODE_LEVEL, g->d_local_in, g->d_global_in, nullptr, dZ, ldp(C),
-                                p.stats_ws, stats, st, g->w_local_in, g->w_global_in));
+    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp(C), stats, st));
 
     // ---------------- backward
     if (transposed_ready) GRP_HIP(hipStreamWaitEvent(st, transposed_ready, 0));   // the blocks' transposed structures
@@ -390,13 +386,14 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
 //             db = 1^T diag(1/r) dZ';  dT = diag(s) (Adj^T dZ' + sl dZ');  dW = H^T dT;
 //             G_in = dT W^T (+ G on a residual layer)
 static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, const grp_step_opts* o, const void* X,
-                           const int32_t* labels, const uint8_t* mask, const float* theta, StepPlan& p, hipStream_t st,
+                           const int32_t* labels, StepPrelude& pre, const float* theta, StepPlan& p, hipStream_t st,
                            float* grad, grp_step_stats* stats) {
     const int k = m->n_layers;
     const int64_t n = g->n;
     const int sl = m->gcn_self_loops ? 1 : 0;
-    GRP_TRY(launch_degree_scales(g->d_local_in, g->d_local_out, n, sl, nullptr, p.gr, p.gs, p.grinv, st));
-    GRP_TRY(prep_weights(m, theta, p, 1.f, st));
+    pre.degrees = DegreeScales{g->d_local_in, g->d_local_out, n, sl, nullptr, p.gr, p.gs, p.grinv};
+    weight_jobs(m, theta, p, 1.f, pre.pack);
+    GRP_TRY(launch_prelude(pre, st));
     // With dropout the gradient that reaches a hidden activation is also multiplied by 1 / (1 - rate);
     // the residual path bypasses it, so the factor rides on the row scale of the masked output.
     const DropoutPlan drop = dropout_plan(o);
@@ -440,8 +437,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
     float* dZ_other = p.dZb;
     float* G = p.Ga;            // dL/dH' of the current layer (residual models only)
     float* G_other = p.Gb;
-    GRP_TRY(launch_softmax_xent(n, C, p.L[k - 1].H_out, ldp(C), labels, nullptr, mask, o->estimator == GRP_EST_NODE_LEVEL,
-                                g->d_local_in, g->d_global_in, p.gr, dZ, ldp(C), p.stats_ws, stats, st));
+    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, p.gr, dZ, ldp(C), stats, st));
 
     for (int l = k - 1; l >= 0; --l) {
         const LayerBufs& L = p.L[l];
@@ -627,26 +623,24 @@ extern "C" grp_status grp_train_step(const grp_partition_t* part, const grp_mode
     const int k = model->n_layers;
     const int64_t n = part->n;
 
-    if (model->arch != GRP_ARCH_SAGE_MEAN) {
-        GRP_TRY(launch_stats(n, nullptr, train_mask, part->d_local_in, part->d_global_in, nullptr, part->nnz, nullptr, 0,
-                             p.stats_ws, stats_out, st));
-        return gcn_step(part, model, opts, features, labels, train_mask, weights, p, st, grad_out, stats_out);
-    }
+    StepPrelude pre;
+    StatsIn& si = pre.stats;
+    si.n_loss = n; si.mask = train_mask; si.d_local = part->d_local_in; si.d_global = part->d_global_in; si.nnz_const = part->nnz;
+    si.scratch = p.stats_ws;
+    if (model->arch != GRP_ARCH_SAGE_MEAN) return gcn_step(part, model, opts, features, labels, pre, weights, p, st, grad_out, stats_out);
+    si.w_local = part->w_local_in; si.w_global = part->w_global_in;
 
     Block blocks[GRP_MAX_LAYERS];
     if (opts->full_graph) {
         if (part->csr_w) GRP_TRY(launch_inverse_mass(part->w_local_in, n, p.inv_in, st));
-        else GRP_TRY(launch_degree_scales(part->d_local_in, part->d_local_out, n, 0, p.inv_in, nullptr, nullptr, nullptr, st));
+        else pre.degrees = DegreeScales{part->d_local_in, part->d_local_out, n, 0, p.inv_in};
         for (int l = 0; l < k; ++l) {
             Block& B = blocks[l];
             B.n_dst = B.n_in = n; B.nnz = part->nnz; B.ptr = part->rowptr; B.idx = part->col;
             B.ptrT = part->colptr; B.idxT = part->row; B.long_fwd = &part->csr_long; B.long_bwd = &part->csc_long;
             B.inv_in = p.inv_in; B.val = part->csr_w; B.valT = part->csc_w;
         }
-        GRP_TRY(launch_stats(n, nullptr, train_mask, part->d_local_in, part->d_global_in, nullptr, part->nnz, nullptr, 0,
-                             p.stats_ws, stats_out, st, part->w_local_in, part->w_global_in));
-        return sage_step(part, model, opts, blocks, features, labels, train_mask, nullptr, weights, p, st, grad_out,
-                         stats_out);
+        return sage_step(part, model, opts, blocks, features, labels, pre, weights, p, st, grad_out, stats_out);
     }
 
     // mini-batch: isolated sampling, then the same layers over the sampled blocks
@@ -657,9 +651,8 @@ extern "C" grp_status grp_train_step(const grp_partition_t* part, const grp_mode
     hipEvent_t transposed_ready = nullptr;
     GRP_TRY(sample_blocks(part, opts, k, p.sampler_ws, p.sampler_bytes, blocks, long_bwd, nnz_parts, &seed_counts, &bad_seeds,
                           st, &transposed_ready));
-    const int32_t* const seeds = blocks[k - 1].dst_nodes;     // the range-checked copy of the caller's list
-    GRP_TRY(launch_stats(opts->n_seeds, seeds, nullptr, part->d_local_in, part->d_global_in, seed_counts, 0, nnz_parts, k,
-                         p.stats_ws, stats_out, st, nullptr, nullptr, bad_seeds));
-    return sage_step(part, model, opts, blocks, features, labels, nullptr, seeds, weights, p, st, grad_out, stats_out,
-                     transposed_ready);
+    si.n_loss = opts->n_seeds; si.mask = nullptr; si.sampled_count = seed_counts; si.nnz_const = 0;
+    si.nodes = blocks[k - 1].dst_nodes;                       // the range-checked copy of the caller's list
+    si.nnz_parts = nnz_parts; si.n_parts = k; si.bad_seeds = bad_seeds;
+    return sage_step(part, model, opts, blocks, features, labels, pre, weights, p, st, grad_out, stats_out, transposed_ready);
 }
