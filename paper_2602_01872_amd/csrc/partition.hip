@@ -1564,6 +1564,108 @@ __global__ __launch_bounds__(256) void seed_keys_kernel(const int32_t* __restric
     keys[pos[v]] = mixM(h ^ (uint64_t)l2g[v]);           // slots ascend with the local id: the stable sort keeps ties in that order
     ids[pos[v]] = (int32_t)v;
 }
+
+// The same order for up to SEEDS_MOST nodes: the keys are as good as uniform, so their top bits deal them to buckets of 128 on average
+// (if every node trains), and a workgroup ranks a bucket's keys against each other in LDS.  Three launches and one wait instead of
+// eleven and two (a radix sort passes over all 8 bytes of the key however few there are).  Buckets beyond SEEDS_BUCKET keys (nodes that
+// share a global id) are left to the sort.  A call, us, sort / buckets: 2500 nodes, half of them trained on 68/43; 1.5e5, 4 % 83/44, all
+// 130/94; 5e5, 10 % 101/66; 2^19, all 219/159; but 1e6, all 259/288 (256 keys a bucket, each compared with each): the line is at 2^19.
+// (Buckets of 64: 51 and 84 us at 1.5e5; of 256: 42 and 113.)
+constexpr int64_t SEEDS_MOST = (int64_t)1 << 19;
+constexpr int SEEDS_BUCKET = 2048;
+constexpr int SEEDS_BITS = 12;           // 4096 buckets at most
+struct SeedJob {
+    const uint8_t* mask;
+    const int64_t* l2g;
+    int64_t n;
+    uint64_t h;
+    int bits;
+    uint32_t *count, *taken;             // [2^bits] keys of a bucket, places given out in it
+    uint64_t* keys;
+    int32_t* ids;
+    int32_t* out;
+    int32_t* totals;                     // keys, keys of the largest bucket
+};
+__device__ __forceinline__ uint32_t seed_bucket(uint64_t key, int bits) { return bits ? (uint32_t)(key >> (64 - bits)) : 0u; }
+__global__ __launch_bounds__(256) void seed_count_kernel(SeedJob j) {
+    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v < j.n && (!j.mask || j.mask[v])) atomicAdd(&j.count[seed_bucket(mixM(j.h ^ (uint64_t)j.l2g[v]), j.bits)], 1u);
+}
+__global__ __launch_bounds__(256) void seed_place_kernel(SeedJob j) {
+    __shared__ uint32_t at[1 << SEEDS_BITS];
+    __shared__ uint32_t wave_sum[4];
+    const int buckets = 1 << j.bits, tid = threadIdx.x;
+    uint32_t before = 0, largest = 0;
+    for (int b0 = 0; b0 < buckets; b0 += 256) {
+        const uint32_t c = b0 + tid < buckets ? j.count[b0 + tid] : 0u;
+        uint32_t all;
+        const uint32_t first = block_scan<4>(c, wave_sum, all);
+        if (b0 + tid < buckets) at[b0 + tid] = before + first;
+        before += all;
+        largest = c > largest ? c : largest;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        if (tid == 0) j.totals[0] = (int32_t)before;
+        atomicMax(&j.totals[1], (int32_t)largest);
+    }
+    const int64_t v = (int64_t)blockIdx.x * 256 + tid;
+    if (v >= j.n || (j.mask && !j.mask[v])) return;
+    const uint64_t key = mixM(j.h ^ (uint64_t)j.l2g[v]);
+    const uint32_t b = seed_bucket(key, j.bits), to = at[b] + atomicAdd(&j.taken[b], 1u);
+    j.keys[to] = key;
+    j.ids[to] = (int32_t)v;
+}
+__global__ __launch_bounds__(256) void seed_rank_kernel(SeedJob j) {
+    __shared__ uint64_t key_s[SEEDS_BUCKET];
+    __shared__ int32_t id_s[SEEDS_BUCKET];
+    __shared__ uint32_t sums[4];
+    const int b = blockIdx.x, tid = threadIdx.x, m = (int)j.count[b];
+    uint32_t before = 0;
+    for (int q = tid; q < b; q += 256) before += j.count[q];
+    uint32_t base;
+    block_scan<4>(before, sums, base);
+    if (m > SEEDS_BUCKET) return;
+    for (int i = tid; i < m; i += 256) {
+        key_s[i] = j.keys[base + i];
+        id_s[i] = j.ids[base + i];
+    }
+    __syncthreads();
+    for (int i = tid; i < m; i += 256) {
+        const uint64_t key = key_s[i];
+        const int32_t id = id_s[i];
+        int rank = 0;
+        for (int q = 0; q < m; ++q) rank += key_s[q] < key || (key_s[q] == key && id_s[q] < id) ? 1 : 0;
+        j.out[base + rank] = id;
+    }
+}
+
+// done: false if a bucket was too large (seeds_out is then unfinished).
+static grp_status seeds_by_buckets(const grp_partition_t* part, const uint8_t* mask, uint64_t h, hipStream_t st, int32_t* seeds_out,
+                                   int64_t* n_seeds_out, bool* done) {
+    const int64_t n = part->n;
+    int bits = 0;
+    while (bits < SEEDS_BITS && ((int64_t)128 << bits) < n) ++bits;
+    const size_t buckets = (size_t)1 << bits;
+    DevBuf keys, ids, counts;
+    GRP_TRY(keys.alloc((size_t)n * sizeof(uint64_t)));
+    GRP_TRY(ids.alloc((size_t)n * sizeof(int32_t)));
+    const size_t words = 2 * buckets + 2;
+    GRP_TRY(counts.alloc(words * sizeof(uint32_t)));
+    uint32_t* const c = counts.as<uint32_t>();
+    GRP_TRY(launch_fill_zero(c, words * sizeof(uint32_t), st));
+    const SeedJob j{mask, part->l2g, n, h, bits, c, c + buckets, keys.as<uint64_t>(), ids.as<int32_t>(), seeds_out, (int32_t*)(c + 2 * buckets)};
+    hipLaunchKernelGGL(seed_count_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, j);
+    hipLaunchKernelGGL(seed_place_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, j);
+    hipLaunchKernelGGL(seed_rank_kernel, dim3((unsigned)buckets), dim3(256), 0, st, j);
+    GRP_LAUNCH_CHECK();
+    int32_t totals[2] = {0, 0};
+    GRP_HIP(hipMemcpyAsync(totals, j.totals, sizeof totals, hipMemcpyDeviceToHost, st));
+    GRP_HIP(hipStreamSynchronize(st));                   // (the temporaries are released on return)
+    *done = totals[1] <= SEEDS_BUCKET;
+    if (*done) *n_seeds_out = totals[0];
+    return GRP_OK;
+}
 }  // namespace grp
 
 extern "C" grp_status grp_epoch_seeds(const grp_partition_t* part, const uint8_t* train_mask, uint64_t sampler_seed,
@@ -1575,6 +1677,12 @@ extern "C" grp_status grp_epoch_seeds(const grp_partition_t* part, const uint8_t
     if (n == 0) return GRP_OK;
     if (!seeds_out) return fail(GRP_EINVAL, "grp_epoch_seeds: null output");
     hipStream_t st = (hipStream_t)stream;
+    const uint64_t h = mixM(mixM(sampler_seed) ^ epoch);
+    if (n <= SEEDS_MOST) {
+        bool done = false;
+        GRP_TRY(seeds_by_buckets(part, train_mask, h, st, seeds_out, n_seeds_out, &done));
+        if (done) return GRP_OK;
+    }
     DevBuf flag, pos, keys, keys_alt, ids, tmp;
     GRP_TRY(flag.alloc(((size_t)n + 1) * sizeof(int32_t)));
     GRP_TRY(pos.alloc(((size_t)n + 1) * sizeof(int32_t)));
@@ -1590,7 +1698,7 @@ extern "C" grp_status grp_epoch_seeds(const grp_partition_t* part, const uint8_t
     GRP_LAUNCH_CHECK();
     GRP_TRY(exclusive_scan_i32(tmp.p, scan_bytes, flag.as<int32_t>(), pos.as<int32_t>(), n + 1, st));
     hipLaunchKernelGGL(seed_keys_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, (const int32_t*)flag.as<int32_t>(),
-                       (const int32_t*)pos.as<int32_t>(), part->l2g, n, mixM(mixM(sampler_seed) ^ epoch), keys.as<uint64_t>(),
+                       (const int32_t*)pos.as<int32_t>(), part->l2g, n, h, keys.as<uint64_t>(),
                        ids.as<int32_t>());
     GRP_LAUNCH_CHECK();
     int32_t total = 0;
