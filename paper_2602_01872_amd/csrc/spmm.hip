@@ -631,8 +631,9 @@ __global__ __launch_bounds__(256) void spmm_combine_tasks_kernel(const int32_t* 
 //   bf16: 2^20 rows, 25 edges: F = 32 405 -> 271, 64 600 -> 368, 128 882 -> 679, 256 1467 -> 1289;  3e5 rows, 20 edges: F = 64 165 -> 100
 // (Slabs of 32 columns for wide rows: 79 million lines, but 2350 us: a quarter of the bytes in flight for each index fetched.)
 constexpr int SLAB_BATCH = 16;
-constexpr uint32_t SLAB_NOWHERE = 0xFFFF0000u;             // (a column's bytes may be added to it)
-constexpr uint32_t SLAB_X_BYTES = 0xFFFF0000u;             // X ends before
+// (offsets are from a slab's first column: 2^22 rows of 1 KB, 4 GiB, leave room above the last row's)
+constexpr uint32_t SLAB_NOWHERE = 0xFFFFFE00u;             // (a lane's bytes within the slab, at most 240, are added to it)
+constexpr uint32_t SLAB_X_BYTES = 0xFFFFFE00u;             // a slab of X ends here at most
 
 template <int G, int N> __device__ __forceinline__ uint32_t group_lane(uint32_t v) {      // lane N of the G lanes around this one
     static_assert(G == 4 || G == 8 || G == 16, "a quad, half a DPP row, a DPP row");
@@ -650,11 +651,11 @@ template <typename XT, int G> struct Slab {
     uint32_t pitch, colx;
     int t, col;                                            // lane of the group, its first column
     __device__ __forceinline__ Slab(const XT* X, uint32_t x_bytes, int64_t ldx, uint32_t slab, int F) {
-        x = __builtin_amdgcn_make_buffer_rsrc(const_cast<XT*>(X), 0, (int)x_bytes, 0x00020000);
+        x = __builtin_amdgcn_make_buffer_rsrc(const_cast<XT*>(X) + (int64_t)slab * COLS, 0, (int)x_bytes, 0x00020000);
         pitch = (uint32_t)ldx * (uint32_t)sizeof(XT);
         t = (int)threadIdx.x % G;
         col = (int)slab * COLS + VW * t;
-        colx = (uint32_t)(col < F ? col : (int)slab * COLS) * (uint32_t)sizeof(XT);      // (a lane without columns reads what its first one does)
+        colx = col < F ? 16u * (uint32_t)t : 0u;           // (a lane without columns reads what its first one does)
     }
     template <int N0, int... U> __device__ __forceinline__ void step(const uint32_t (&off)[Q], float (&acc)[VW], std::integer_sequence<int, U...>) const {
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -944,7 +945,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         constexpr int SG = LANES < 16 ? LANES : 16;
         const int64_t slabs = cdiv(a.F, SG * VW);
         const int64_t x_rows = a.n_src > 0 ? a.n_src : a.n_rows;
-        const int64_t x_bytes = ((x_rows - 1) * a.ldx + round_up(a.F, VW)) * (int64_t)sizeof(XT);
+        const int64_t x_bytes = ((x_rows - 1) * a.ldx + std::min<int64_t>(round_up(a.F, VW), SG * VW)) * (int64_t)sizeof(XT);      // of a slab
         const bool units = VW == 4 || (a.F % VW == 0 && a.ldx % VW == 0 && (uintptr_t)a.X % 16 == 0);
         // several slabs: of whole lines, and at most a quarter of them without columns (20 edges a row, 3e5 rows, fp32, us of rows / slabs:
         // F = 96 260/225, 160 412/364, 224 612/494, but 72 260/274 and lines cut by slabs: 112 308/312, 120 352/378, 172 530/573)
@@ -952,7 +953,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         // (rows of few edges with more than Y to read or write beside them are done a whole row at a time: 3.25 edges, F = 256, mask and
         // addend: 255 us, in slabs 278; without them 190 and 187)
         const bool sums = slabs == 1 || a.nnz >= 8 * a.n_rows || (!a.mask && !a.addend && !a.residual && !a.Y2);
-        if (!a.val && !a.colscale && !ep.tight && !a.n_rows_dev && units && whole && sums && x_bytes < (int64_t)SLAB_X_BYTES) {
+        if (!a.val && !a.colscale && !ep.tight && !a.n_rows_dev && units && whole && sums && x_bytes <= (int64_t)SLAB_X_BYTES) {
             const int64_t task_blocks = sliced ? cdiv(lr->n_tasks, 4) : 0, row_blocks = n_chunks + cdiv(a.n_rows, SLAB_ROWS);
             if (sliced && slabs * task_blocks < ((int64_t)1 << 24)) {          // (fewer than 2^32 work-items)
                 GRP_PLAIN_LAUNCH((spmm_slab_tasks_kernel<XT, SG>), dim3((unsigned)(slabs * task_blocks)), dim3(256), 0, st, (const SliceTask*)lr->tasks,
