@@ -81,3 +81,22 @@ def test_rows_longer_than_any_bin_without_a_split(lib):
     part = g.grp_partition_from_local_coo(src.to(DEV), dst.to(DEV), n)
     _check(g, part, src.to(DEV), dst.to(DEV), n, 64, torch.float32, 64)
     _check(g, part, src.to(DEV), dst.to(DEV), n, 16, torch.float32, 16)
+
+
+@pytest.mark.parametrize("n", [1 << 22, (1 << 22) + 1])
+def test_operand_of_four_gib(lib, n):
+    """X of exactly 4 GiB, the most that 32-bit offsets from a slab's first column reach, and of one row more; the last rows are
+    neighbours of short rows and of a long one, whose edges go by the sliced schedule."""
+    g = lib
+    gen = torch.Generator().manual_seed(n)
+    src = torch.cat([torch.randint(n, (200_000,), generator=gen), torch.arange(n - 4000, n), torch.arange(n - 64, n)])
+    dst = torch.cat([torch.randint(n, (200_000,), generator=gen), torch.full((4000,), 5), torch.arange(n - 64, n).flip(0)])
+    src, dst = src.to(DEV), dst.to(DEV)
+    g.grp_set_slice_policy(1, 1)
+    try:
+        part = g.grp_partition_from_local_coo(src, dst, n)
+    finally:
+        g.grp_set_slice_policy()
+    _check(g, part, src, dst, n, 256, torch.float32, 256)
+    part.destroy()
+    torch.cuda.empty_cache()
