@@ -976,12 +976,14 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         // launch 44.3 / 42.9 / 42.4 ms, fp32 F = 16 launch 34.7 / 34.7 / 35.6 ms)
         const int64_t per_wave = cdiv(lr->n_tasks, (int64_t)4 << 19);
         const dim3 tgrid((unsigned)cdiv(lr->n_tasks, 4 * per_wave));
-        // plain sums over rows that start at multiples of a power of two inside less than 4 GiB: 32-bit addressing
+        // Plain sums over rows that start at multiples of a power of two inside less than 4 GiB: 32-bit addressing; not for the one or two
+        // lanes of a bf16 row of 8 or 16 columns (2^20 rows, 1e8 edges, forward and transposed, us with / without: 1711 / 1346 at 8,
+        // 1578 / 1577 at 16; no difference for fp32 of 72 columns).
         int row_shift = -1;
         {
             const int64_t pitch_bytes = a.ldx * (int64_t)sizeof(XT);
             const int64_t x_rows = a.n_src > 0 ? a.n_src : a.n_rows;
-            if (LANES < 4 && !a.val && !a.colscale && pitch_bytes > 0 && (pitch_bytes & (pitch_bytes - 1)) == 0 &&
+            if (!a.val && !a.colscale && pitch_bytes > 0 && (pitch_bytes & (pitch_bytes - 1)) == 0 &&
                 x_rows * pitch_bytes <= ((int64_t)1 << 32)) {
                 row_shift = 0;
                 while (((int64_t)1 << row_shift) < pitch_bytes) ++row_shift;
@@ -999,16 +1001,17 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
                 if (a.val && a.colscale) go(spmm_tasks_kernel<XT, G / 2, 1, 8, true, true>);
                 else if (a.val) go(spmm_tasks_kernel<XT, G / 2, 1, 8, true, false>);
                 else if (a.colscale) go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, true>);
-                                else go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false>);
+                else if (LANES >= 4 && row_shift >= 0) {
+                    if constexpr (LANES >= 4) go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false, true>);
+                } else go(spmm_tasks_kernel<XT, G / 2, 1, 8, false, false>);
             }
         }
         if (!wide) {
             if (a.val && a.colscale) go(spmm_tasks_kernel<XT, G, NJ, 4, true, true>);
             else if (a.val) go(spmm_tasks_kernel<XT, G, NJ, 4, true, false>);
             else if (a.colscale) go(spmm_tasks_kernel<XT, G, NJ, 4, false, true>);
-            else if (row_shift >= 0) {
-                if constexpr (LANES < 4) go(spmm_tasks_kernel<XT, G, NJ, 4, false, false, true>);
-            } else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
+            else if (row_shift >= 0) go(spmm_tasks_kernel<XT, G, NJ, 4, false, false, true>);
+            else go(spmm_tasks_kernel<XT, G, NJ, 4, false, false>);
         }
     }
     auto rows = [&](auto kernel, auto op, int lanes) {     // lanes: of a row
