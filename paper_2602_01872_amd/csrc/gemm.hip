@@ -1085,6 +1085,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------- TN
 constexpr int TN_IDLE = 128;                  // a launch of fewer workgroups leaves half the chip idle
 constexpr int TN_MAX_SPLITS = 256;
+constexpr int64_t TN_STREAM_ROWS = (int64_t)1 << 23;
 constexpr int N_CU = 256;                     // a product is cut into one full round of resident workgroups (768 slices at two per CU: 6-8 % slower)
 
 struct TnPlan {
@@ -1103,7 +1104,7 @@ static TnPlan tn_plan(int64_t M, int K, int N, int products = 1) {
     // slices of 1.7e7 rows an accumulator is rounded 2000 times), and the partial tiles cost nothing beside 10^7 rows (bf16 K = 64,
     // N = 128 over 1.7e7 rows 2.34 ms in one round of workgroups, 2.38 in four; K = 128, N = 16 1.95 and 1.94; at 3e5 rows four times the
     // slices cost 4 %).
-    const bool stream = M >= ((int64_t)1 << 23);
+    const bool stream = M >= TN_STREAM_ROWS;
     const int target = N_CU * tn_wgs(p.bk_tile * p.bn_tile / 4096);      // (tiles of 32 x 32 per wavefront)
     int64_t s = (stream ? 4 * target : target) / (p.tiles_k * p.tiles_n * products);
     // A lone workgroup spends over a microsecond on 32 rows: slices of 128, of fewer where that leaves most of the chip idle (with the
@@ -1121,14 +1122,30 @@ static TnPlan tn_plan(int64_t M, int K, int N, int products = 1) {
     return p;
 }
 
+// The most slices of any product of at most M rows.  The slices of a plan do not grow with its rows alone: rows_min doubles where they
+// leave the chip less idle, and the rounding of a chunk drops slices (6000 rows at K = N = 128, two products: 94; 10 584 rows: 83).  A scratch
+// array sized for an upper bound of the rows has to do for every launch below it.
+static int64_t tn_most_splits(int64_t M, int K, int N, int products) {
+    const TnPlan p = tn_plan(M, K, N, products);           // (tiles: the same for every M)
+    const int64_t tiles = (int64_t)p.tiles_k * p.tiles_n * products;
+    const bool stream = M >= TN_STREAM_ROWS;
+    const int64_t target = N_CU * tn_wgs(p.bk_tile * p.bn_tile / 4096);
+    int64_t s = cdiv(M, 128);
+    for (int rows_min = 64; rows_min >= 32; rows_min /= 2)     // slices so short are made up to this many rows
+        s = std::max(s, cdiv(std::min(M, 2 * rows_min * (TN_IDLE / tiles)), rows_min));
+    s = std::min({s, (stream ? 4 * target : target) / tiles, (int64_t)(stream ? 8 : 1) * TN_MAX_SPLITS});
+    return std::max<int64_t>(s, 1);
+}
+
+// (does not shrink as M grows)
 size_t gemm_tn_workspace_bytes(int64_t M, int32_t K, int32_t N) {
     // room for one product, or for two from one launch: (2K + 1) rows of N, or (K + 1) rows of 2N
     size_t need = 0;
     for (int products = 1; products <= 2; ++products) {
-        const TnPlan p = tn_plan(M, K, N, products);
-        if (p.splits <= 1) continue;
+        const int64_t splits = tn_most_splits(M, K, N, products);
+        if (splits <= 1) continue;
         const size_t rows_n = products == 1 ? (size_t)(K + 1) * N : std::max((size_t)(2 * (size_t)K + 1) * N, (size_t)(K + 1) * 2 * N);
-        need = std::max(need, (size_t)p.splits * rows_n * sizeof(float));
+        need = std::max(need, (size_t)splits * rows_n * sizeof(float));
     }
     return need;
 }
