@@ -585,13 +585,15 @@ struct transpose_sort_kernel_op {
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { transpose_sort_kernel_body<MOST>(gx, a...); }
 };
 
+// A list of sources names every node once, but for the seeds: those that had to be replaced, and those that the caller repeated, stand in
+// it as often as in the seed list.  So it may hold n_seeds - 1 more than the partition has nodes.
 void sampler_bounds(int64_t n, int64_t n_seeds, const int32_t* fanouts, int k, SamplerBounds* out) {
     int64_t nd = n_seeds;
     for (int l = k - 1; l >= 0; --l) {
         out->dst[l] = nd;
         out->nnz[l] = nd * fanouts[l];
         int64_t ns = nd + out->nnz[l];
-        if (ns > n) ns = n;
+        if (ns > n + n_seeds - 1) ns = n + n_seeds - 1;
         out->src[l] = ns;
         nd = ns;
     }
