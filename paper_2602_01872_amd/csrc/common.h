@@ -107,6 +107,7 @@ struct LaunchRecord {
 struct LaunchRecorder {
     std::vector<LaunchRecord> list;
     bool unsupported = false;                      // a launch that cannot be merged was asked for (and not made)
+    int steps = 1;                                 // that may share a launch
 };
 extern thread_local LaunchRecorder* g_recorder;    // null: launches are made at once
 

@@ -41,11 +41,17 @@ constexpr int SAMPLE_MAX_FANOUT = 64;         // one lane of a wavefront per cho
 // edges, newly reached nodes.
 enum { SZ_DST = 0, SZ_SRC = 1, SZ_NNZ = 2, SZ_NEW = 3, SZ_PER_LAYER = 4 };
 
-// ---- prefix sums across the workgroups of one launch.  A workgroup posts the sum of its part, then adds up what those before it have
+// ---- prefix sums across the workgroups of one launch (the decoupled look-back of Merrill and Garland, "Single-pass parallel prefix scan
+// with decoupled look-back", 2016).  A workgroup posts the sum of its part, then adds up what those before it have
 // posted, 64 at a time, until it meets one that has posted its whole prefix, and posts its own.  Flag and value share a 64-bit word,
-// cleared before the launch.  Workgroups wait for lower-numbered ones only, and there are at most PARTS of them, which the chip
-// holds many times over: launches that run side by side cannot keep each other's waiting.
-constexpr int PARTS = 128;
+// cleared before the launch.
+// Every wait ends: workgroups wait for lower-numbered ones of their launch only, which each XCD starts first, so a launch on its own
+// cannot stall.  Launches side by side could, if those of others filled an XCD while they wait for parts that have no place there.  So a
+// launch, whatever its layers and merged steps, has at most WAITING workgroups that wait, 48 on an XCD; an XCD holds at
+// least 192 of them (six a CU: these kernels take at most 80 vector registers and next to no LDS), so that three of the four launches that four
+// hardware queues run at a time leave room for the fourth.
+constexpr int PARTS = 128;               // of one prefix sum
+constexpr int WAITING = 384;             // of all prefix sums of a launch (256: an epoch in four merged lanes 1 % slower)
 constexpr unsigned long long POSTED_SUM = 1ull << 62, POSTED_PREFIX = 2ull << 62, POSTED_VALUE = (1ull << 62) - 1;
 
 // The sum before part `part`, for the lanes of one wavefront; `own`: this part's sum.
@@ -75,12 +81,14 @@ __device__ __forceinline__ unsigned long long look_back(unsigned long long* __re
 constexpr int CS_THREADS = 256;
 constexpr int CS_PER = 4;
 constexpr int CS_ROUND = CS_THREADS * CS_PER;                // rows of a part, taken that many at a time
-// Rounds of a part and number of parts for `items` rows.
+// Rounds of a part and number of parts (workgroups) for `items` rows; sums: that share the launch (merged steps times the layers of one: 8
+// times 15 are 120, fewer than WAITING).
 struct ScanPlan { int rounds, parts; };
-static ScanPlan scan_plan(int64_t items, int64_t round) {
-    const int64_t rounds = cdiv(items, round * PARTS);
+ScanPlan look_back_plan(int64_t items, int64_t round, int sums) {
+    const int64_t parts = std::max(1, std::min(PARTS, WAITING / sums)), rounds = cdiv(items, round * parts);
     return {(int)rounds, (int)cdiv(items, round * rounds)};
 }
+static int steps_of_launch() { return g_recorder ? g_recorder->steps : 1; }
 
 // Rows of a layer, counted: the number of edges row i keeps (CSR pointer ptr[0 .. bound], the rows between the real count and the bound
 // empty), 1 / max(that, 1) and, above the input layer, its place at the head of the block's source list.  The seeds' layer reads
@@ -700,7 +708,7 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         const int64_t dst_bound = bd.dst[l];
         const int f = o->fanouts[l];
         const bool top = l == k - 1;
-        const ScanPlan cp = scan_plan(dst_bound + 1, CS_ROUND);
+        const ScanPlan cp = look_back_plan(dst_bound + 1, CS_ROUND, steps_of_launch());
         const CountJob count{part->rowptr, dst_nodes, top ? o->seeds : nullptr, n, (int64_t)o->n_seeds, D, dst_bound, f, cp.rounds, cp.parts, L.posted,
                              L.ptr, L.cnt32, L.inv_in, top && l > 0 ? s.mark : nullptr, L.src_nodes, (unsigned long long*)s.bad};
         launch(count_rows_kernel, count_rows_kernel_op(), dim3((unsigned)(cp.parts + (relabel.ptr ? cdiv(relabel.dst_bound, 4) : 0))), st, count, relabel);
@@ -766,12 +774,12 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
         }
         // new source nodes in ascending local id
         const int64_t src_bound = bd.src[l];
-        const ScanPlan wp = scan_plan(s.n_words, WD_ROUND);
+        const ScanPlan wp = look_back_plan(s.n_words, WD_ROUND, steps_of_launch());
         launch(number_new_kernel, number_new_kernel_op(), dim3((unsigned)wp.parts), st, s.n_words, wp.rounds, L.posted + PARTS, s.bits, D,
                            s.sizes + SZ_PER_LAYER * (l - 1) + SZ_DST, s.mark, L.src_nodes);
         GRP_LAUNCH_CHECK();
         relabel = RelabelJob{L.ptr, D, dst_bound, L.idx_local, s.mark, L.idx_blk, L.arrival, L.count_t};
-        const ScanPlan tp = scan_plan(src_bound + 1, CS_ROUND);
+        const ScanPlan tp = look_back_plan(src_bound + 1, CS_ROUND, (k - 1) * steps_of_launch());
         jobs.d[l - 1] = TransposeJob{D, L.ptr, L.idx_blk, L.arrival, L.count_t, src_bound, L.ptrT, L.loose, L.idxT, tp.rounds, tp.parts,
                                      L.posted + 2 * PARTS, L.lr_row, L.lr_first, L.lr_cb, L.lr_ce, L.lr_cap_long, L.lr_cap_chunks};
         LongRows& lr = long_bwd_store[l];

@@ -528,6 +528,7 @@ extern "C" grp_status grp_train_steps(int32_t count, const grp_partition_t* cons
             for (int p = 0; p < count && merge; ++p) {
                 grp_step_opts o = opts[p];
                 o.flags |= GRP_STEP_ONE_STREAM;
+                steps[(size_t)p].steps = std::min(count, MANY_MOST);
                 Recording r(&steps[(size_t)p]);
                 GRP_TRY(step(p, o));
                 merge = !steps[(size_t)p].unsupported;

@@ -61,6 +61,21 @@ def test_minibatch_steps(fanouts, batches, dropout):
     _compare(g, parts, model, opts, xs, ys, None, theta.to(DEV), P)
 
 
+def test_minibatch_steps_whose_prefix_sums_take_several_rounds():
+    """Eight merged steps share a launch's waiting workgroups: blocks of up to 1.8e5 places are summed in fewer, longer parts."""
+    import paper_2602_01872_amd as g
+    n, fanouts, dims = 200_000, (15, 10, 5), [16, 16, 16, 6]
+    model = g.model_desc(g.ARCH_SAGE_MEAN, dims)
+    s, d = _graph(n, 20 * n, 90)
+    part = g.grp_partition_from_local_coo(s, d, n)
+    x, y, theta = make_inputs(n, dims, "sage", 8)
+    opts = []
+    for i in range(8):
+        seeds = torch.randperm(n, generator=torch.Generator().manual_seed(i))[:1024 - i].to(torch.int32).to(DEV)
+        opts.append(g.step_opts(estimator=g.EST_NONE, full_graph=False, seeds=seeds, fanouts=fanouts, sampler_seed=4, batch_id=i))
+    _compare(g, [part] * 8, model, opts, [x.to(DEV)] * 8, [y.to(DEV)] * 8, None, theta.to(DEV), g.grp_param_count(model))
+
+
 def _compare(g, parts, model, opts, xs, ys, masks, theta, P):
     K = len(parts)
     size = max(g.grp_step_workspace_bytes(p, model, o) for p, o in zip(parts, opts))
