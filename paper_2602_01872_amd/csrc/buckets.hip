@@ -6,8 +6,14 @@
 // row within the bucket, other end), and a workgroup per bucket sorts its keys in LDS and writes the pointers, the degrees and
 // the indices.  Equal keys are indistinguishable, so the arrays are unique, whatever order the keys arrived in.
 //
-// What skewed graphs ask for: a bucket of more keys than LDS holds is sorted a range of rows at a time; a single row of more keys
-// (a hub) is left to jobs over ranges of the other end's ids.
+// What skewed graphs ask for: a bucket of a few more keys than LDS holds is sorted a range of rows at a time, one of many more puts them in
+// order of their rows in memory and leaves the sorting to jobs, of a range of rows each or, where a single row has more keys than LDS holds
+// (a hub), of a range of the other end's ids.  One workgroup orders a bucket, and every job of a hub reads all its keys: where either would
+// take longer than a device-wide sort, the build is refused and goes there (bucket_build).
+// Builds, ms, of graphs numbered so that heavy rows are neighbours (buckets / every range and hub reading its whole bucket again /
+// radix sorts): R-MAT by degree, 3e5 nodes 3e6 edges 0.61 / 8.0 / 6.9, 2e6 3e7 3.0 / 203 / 57; all edges to 1000 nodes numbered first, 2e6 3e7
+// 2.8 / 1133 / 52, 300 of 6e5 3.9e6 0.82 / 187 / 15.8; to one node, 1e6 2e7 3.6 / 72 / 20.  (The sorts took their time over the
+// pointers of empty rows: csr_rows_kernel.)
 #include "common.h"
 
 namespace grp {
@@ -26,7 +32,9 @@ constexpr int BK_SUBS = (1 << BK_ROW_BITS) + 2 * BK_CAP / BK_SUB;
 constexpr int HUB_SPAN = 8192;                  // ids that are counted at a time where a hub's keys crowd: 32 KB of LDS
 constexpr int HUB_PART = 2048;                  // keys of a hub's job, if they are spread evenly: many short jobs, each of which reads all keys,
 constexpr int HUB_LONG = 1 << 18;               // or, of a hub of more than this, BK_AIM keys
-constexpr int HUB_GROUPS = 512;
+constexpr int JOB_GROUPS = 512;
+constexpr int BK_ALONE = 2 * BK_CAP;            // keys that a bucket's workgroup sorts itself, reading them again for every range of rows
+constexpr int JOB_KEYS = BK_CAP / 2;            // a range of rows: those that begin within so many keys, but for one of more keys at its end
 
 // Fewest buckets of at most BK_AIM keys on average (more where there would be too many of them), 2048 rows and 32 bits of key.  Builds from
 // n nodes and E local edges of a skewed graph, destroy included (us; radix sorts of 64-bit keys -> buckets): 1e3, 4e3 180 -> 110;
@@ -44,29 +52,38 @@ bool bucket_plan(int64_t n, int64_t nnz, BucketPlan* p) {
 }
 
 struct BucketScratch {
+    unsigned long long* totals;      // [5] sums: longs, edges of the CSR, of the CSC; keys that the hubs' jobs read (cleared)
     uint32_t* count;                 // [2 B] keys of the buckets (cleared)
-    uint32_t* n_jobs;                // [1] (cleared, after the counts)
+    uint32_t* n_jobs;                // [1] (cleared)
     uint32_t* start;                 // [2 (B + 1)] first key of each bucket
     uint32_t* cursor;                // [2 B]
     unsigned long long* longs;       // [2 B] long rows << 32 | their chunks
     unsigned long long* edges;       // [2 B] edges of the long rows
-    unsigned long long* totals;      // [4] the sums: longs, edges of the CSR, of the CSC
-    uint4* jobs;                     // [2 (nnz / HUB_PART + nnz / BK_CAP)] of hubs: direction << 31 | first id, id after the last, first key, keys
+    uint4* jobs;                     // direction << 31 | JOB_ROWS or first id, id after the last, first key, keys
+    uint32_t bucket_most;            // keys of a bucket, and keys that the hubs' jobs read, beyond which the build is refused
+    unsigned long long hubs_most;
     size_t bytes, clear_bytes;
 };
+constexpr unsigned long long REFUSED_AT_ONCE = 1ull << 62;       // in totals[4], before the keys are moved
+constexpr uint32_t JOB_ROWS = 1u << 30;          // the job's keys are those of whole rows
 static BucketScratch carve_scratch(const BucketPlan& p, int64_t nnz, void* base) {
     BucketScratch s;
     Bump b(base, 0);
     const size_t B = (size_t)p.n_buckets;
-    s.count = b.take<uint32_t>(2 * B + 1);
+    s.totals = b.take<unsigned long long>(5 + B + 1);
+    s.count = (uint32_t*)(s.totals + 5);
     s.n_jobs = s.count + 2 * B;
-    s.clear_bytes = (2 * B + 1) * sizeof(uint32_t);
+    s.clear_bytes = 5 * sizeof(unsigned long long) + (2 * B + 1) * sizeof(uint32_t);
     s.start = b.take<uint32_t>(2 * (B + 1));
     s.cursor = b.take<uint32_t>(2 * B);
     s.longs = b.take<unsigned long long>(2 * B);
     s.edges = b.take<unsigned long long>(2 * B);
-    s.totals = b.take<unsigned long long>(4);
-    s.jobs = b.take<uint4>(2 * (size_t)(nnz / HUB_PART + nnz / BK_CAP) + 1);
+    // a direction's jobs: ranges of rows, at most one more per crowded bucket than whole JOB_KEYS; rows of more than JOB_KEYS keys; parts of hubs
+    s.jobs = b.take<uint4>(2 * (size_t)(2 * (nnz / JOB_KEYS) + nnz / HUB_PART + 2 * (nnz / BK_CAP)) + 1);
+    // One workgroup reads a bucket's keys twice, some five a nanosecond each time, and the hubs' jobs read 128 times the edges in about
+    // as long as the sorts take (30 hubs of 1e6 keys: 6.7 ms by jobs, 4.0 refused; of 1e5: 0.62 by jobs, 1.3 by sorts).
+    s.bucket_most = (uint32_t)std::max<int64_t>((int64_t)1 << 20, nnz / 16);
+    s.hubs_most = 128ull * (unsigned long long)nnz;
     s.bytes = b.total();
     return s;
 }
@@ -88,26 +105,28 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_count_kernel(const uint64_t
         if (hist[i]) atomicAdd(&count[i], hist[i]);
 }
 
-__global__ __launch_bounds__(BK_THREADS) void bucket_start_kernel(const uint32_t* __restrict__ count, int B, uint32_t* __restrict__ start,
-                                                                  uint32_t* __restrict__ cursor) {
+__global__ __launch_bounds__(BK_THREADS) void bucket_start_kernel(BucketScratch s, int B) {
     __shared__ uint32_t wave_sum[BK_WAVES];
     constexpr int PER = BK_MAX / BK_THREADS;
     for (int dir = 0; dir < 2; ++dir) {
         uint32_t c[PER], sum = 0, total;
+        bool too_many = false;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int b = PER * threadIdx.x + i;
-            c[i] = b < B ? count[dir * B + b] : 0u;
+            c[i] = b < B ? s.count[dir * B + b] : 0u;
             sum += c[i];
+            too_many = too_many || c[i] > s.bucket_most;
         }
+        if (too_many) s.totals[4] = REFUSED_AT_ONCE;
         uint32_t at = block_scan<BK_WAVES>(sum, wave_sum, total);
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int b = PER * threadIdx.x + i;
-            if (b < B) start[dir * (B + 1) + b] = cursor[dir * B + b] = at;
+            if (b < B) s.start[dir * (B + 1) + b] = s.cursor[dir * B + b] = at;
             at += c[i];
         }
-        if (threadIdx.x == 0) start[dir * (B + 1) + B] = total;
+        if (threadIdx.x == 0) s.start[dir * (B + 1) + B] = total;
     }
 }
 
@@ -117,9 +136,11 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_start_kernel(const uint32_t
 constexpr int SC_PER = 16;                                 // (16 bits hold a place in a tile, and a bucket of either direction)
 constexpr int SC_TILE = BK_THREADS * SC_PER;
 __global__ __launch_bounds__(BK_THREADS) void bucket_scatter_kernel(const uint64_t* __restrict__ keys, int64_t nnz, BucketPlan p, int per,
-                                                                    uint32_t* __restrict__ cursor, uint32_t* __restrict__ packed) {
+                                                                    const unsigned long long* __restrict__ refused, uint32_t* __restrict__ cursor,
+                                                                    uint32_t* __restrict__ packed) {
     extern __shared__ uint32_t lds[];                      // [2 B] counts, then where a bucket's keys go; [tile] keys; [2 B] places; [tile] buckets
     __shared__ uint32_t wave_sum[BK_WAVES];
+    if (*refused) return;
     const int B = p.n_buckets, tile = per * BK_THREADS;
     uint32_t* const to = lds;
     uint32_t* const buf = lds + 2 * B;
@@ -211,6 +232,20 @@ template <typename F> __device__ __forceinline__ void each_key(const uint32_t* _
     }
 }
 
+// counter[row] += 1 for every lane that is on; returns what the counter held, as if the lanes came one after another.  The lanes that have
+// the first one's row are counted with one addition (a hub's keys come 64 at a time).
+__device__ __forceinline__ uint32_t count_row(bool on, uint32_t row, uint32_t* counter) {
+    const unsigned long long who = __ballot(on);
+    if (!who) return 0u;
+    const bool same = on && row == (uint32_t)__builtin_amdgcn_readlane((int)row, __ffsll(who) - 1);
+    const unsigned long long group = __ballot(same);
+    const int lane = threadIdx.x & 63, lead = __ffsll(group) - 1;
+    uint32_t at = 0u;
+    if (on && (!same || lane == lead)) at = atomicAdd(&counter[row], same ? (uint32_t)__popcll(group) : 1u);
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)at, lead);
+    return same ? first + (uint32_t)__popcll(group & ((1ull << lane) - 1ull)) : at;
+}
+
 struct BucketOut {
     int64_t* ptr[2];
     int32_t* idx[2];
@@ -287,9 +322,9 @@ __device__ __forceinline__ void radix_sort(uint32_t (&k)[BK_PER], int per, int b
 // One workgroup per bucket.  The keys of a row of d are dealt to the next power of two above d / BK_SUB equal ranges of the other
 // end's ids, counted in LDS; each then finds its place among the few of its range by comparing.  Where a range is crowded (a graph
 // whose numbering has locality) the rows are sorted digit by digit instead.  (3.9e6 edges of 6e5 nodes, both directions, digits
-// alone 250 us, this way 160.)
+// alone 250 us, this way 160.)  A bucket of more than BK_CAP keys: see the top of the file.
 __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t* __restrict__ packed, int64_t nnz, int64_t n, BucketPlan p,
-                                                                 BucketScratch s, BucketOut out, uint32_t* __restrict__ hub_keys) {
+                                                                 BucketScratch s, BucketOut out, uint32_t* __restrict__ by_row) {
     __shared__ uint32_t buf[BK_CAP];
     __shared__ uint32_t off[(1 << BK_ROW_BITS) + 1];       // first key of each row of the bucket
     __shared__ uint32_t sub_of[1 << BK_ROW_BITS];          // a row's first range << 5 | how far an id is shifted to its range
@@ -303,6 +338,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
     const int B = p.n_buckets, dir = (int)blockIdx.x >= B, b = (int)blockIdx.x - dir * B;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t lo = s.start[dir * (B + 1) + b], count = s.start[dir * (B + 1) + b + 1] - lo;
+    if (s.totals[4] == REFUSED_AT_ONCE) return;
     const uint32_t* const in = packed + dir * nnz + lo;
     const int64_t first = (int64_t)b << p.row_bits;
     const int rows = (int)(first + (1 << p.row_bits) <= n ? (int64_t)1 << p.row_bits : n - first);
@@ -327,8 +363,10 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
         for (int i = 0; i < BK_PER; ++i)
             if (on(i, count, per)) atomicAdd(&off[k[i] >> p.id_bits], 1u);
     } else {
+        const bool heavy = count > (uint32_t)BK_ALONE;
         each_key(in, count, [&](bool mine, uint32_t key) {
-            if (mine) atomicAdd(&off[key >> p.id_bits], 1u);
+            if (heavy) (void)count_row(mine, key >> p.id_bits, off);
+            else if (mine) atomicAdd(&off[key >> p.id_bits], 1u);
         });
     }
     __syncthreads();
@@ -361,6 +399,62 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
     __syncthreads();
     if (tid == 0) { s.longs[dir * B + b] = stat[0]; s.edges[dir * B + b] = stat[1]; }
 
+    uint32_t* const to = by_row + dir * nnz + lo;
+    if (count > (uint32_t)BK_ALONE) {
+        for (int i = tid; i < rows; i += BK_THREADS) sub_of[i] = 0u;       // the rows' keys placed so far
+        __syncthreads();
+        each_key(in, count, [&](bool mine, uint32_t key) {
+            const uint32_t r = key >> p.id_bits, at = count_row(mine, r, sub_of);
+            if (mine) to[off[r] + at] = key;
+        });
+        // Ranges of rows: the rows that begin among the same JOB_KEYS keys, but for a row of more than JOB_KEYS, which is the last of them and a
+        // job, or several, of its own.  So a range has at most 2 JOB_KEYS = BK_CAP keys.  A thread looks at two rows, each of which
+        // may be the first of a range, and heavy.
+        uint32_t begin[2], end[2], parts[2], jobs = 0, total;
+        unsigned long long reads = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = 2 * tid + q;
+            begin[q] = end[q] = parts[q] = 0u;
+            if (r >= rows) continue;
+            const uint32_t at = off[r], m = off[r + 1] - at, window = at / JOB_KEYS;
+            if (m > (uint32_t)BK_CAP) {
+                const uint32_t aim = m <= (uint32_t)HUB_LONG ? HUB_PART : BK_AIM;
+                parts[q] = (m + aim - 1) / aim;
+                reads += (unsigned long long)parts[q] * m;
+            } else if (m > (uint32_t)JOB_KEYS) {
+                parts[q] = 1u;
+            }
+            if (r == 0 || off[r - 1] / JOB_KEYS != window) {
+                int x = r, y = rows;                       // x begins in this window, y (or the end) does not
+                while (y - x > 1) {
+                    const int mid = (x + y) >> 1;
+                    if (off[mid] / JOB_KEYS == window) x = mid; else y = mid;
+                }
+                begin[q] = at;
+                end[q] = off[x + 1] - off[x] > (uint32_t)JOB_KEYS ? off[x] : off[x + 1];
+            }
+            jobs += parts[q] + (end[q] > begin[q] ? 1u : 0u);
+        }
+        const uint32_t mine = block_scan<BK_WAVES>(jobs, wave_sum, total);
+        if (tid == 0) fill = atomicAdd(s.n_jobs, total);
+        if (reads) atomicAdd(&s.totals[4], reads);
+        __syncthreads();
+        uint4* job = s.jobs + fill + mine;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = 2 * tid + q;
+            if (end[q] > begin[q]) *job++ = make_uint4((uint32_t)dir << 31 | JOB_ROWS, 0u, lo + begin[q], end[q] - begin[q]);
+            if (parts[q] == 0) continue;
+            const uint32_t at = off[r], m = off[r + 1] - at;
+            if (m <= (uint32_t)BK_CAP) *job++ = make_uint4((uint32_t)dir << 31 | JOB_ROWS, 0u, lo + at, m);
+            else
+                for (uint32_t x = 0; x < parts[q]; ++x)
+                    *job++ = make_uint4((uint32_t)dir << 31 | (uint32_t)(n * x / parts[q]), (uint32_t)(n * (x + 1) / parts[q]), lo + at, m);
+        }
+        return;
+    }
+
     for (int ra = 0; ra < rows;) {                         // (all of it uniform) the next rows that fit
         const uint32_t base = off[ra];
         int rb = rows;
@@ -377,7 +471,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
         const uint32_t m = off[rb] - base;
         if (m == 0) { ra = rb; continue; }                 // empty rows, before a hub or at the end
         const int per = (int)((m + BK_THREADS - 1) / BK_THREADS);
-        if (!whole) {                            // those rows' keys among the bucket's
+        if (!whole) {                                      // those rows' keys among the bucket's
             if (tid == 0) fill = 0u;
             __syncthreads();
             each_key(in, count, [&](bool on, uint32_t key) {
@@ -390,24 +484,23 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
                 if (lane == lead) at = atomicAdd(&fill, (uint32_t)__popcll(who));
                 at = __shfl(at, lead, 64) + __popcll(who & ((1ull << lane) - 1ull));
                 if (mine) {
-                    if (hub) hub_keys[dir * nnz + lo + base + at] = key & id_mask;
+                    if (hub) to[base + at] = key;
                     else buf[at] = key;
                 }
             });
             __syncthreads();
             if (hub) {
-                const uint32_t aim = m <= (uint32_t)HUB_LONG ? HUB_PART : BK_AIM, parts = (m + aim - 1) / aim;
+                const uint32_t parts = (m + HUB_PART - 1) / HUB_PART;      // (at most BK_ALONE keys: no strain on hubs_most)
                 if (tid == 0) fill = atomicAdd(s.n_jobs, parts);
                 __syncthreads();
-                const uint32_t at = fill;
                 for (uint32_t q = tid; q < parts; q += BK_THREADS)
-                    s.jobs[at + q] = make_uint4((uint32_t)dir << 31 | (uint32_t)(n * q / parts), (uint32_t)(n * (q + 1) / parts), lo + base, m);
+                    s.jobs[fill + q] = make_uint4((uint32_t)dir << 31 | (uint32_t)(n * q / parts), (uint32_t)(n * (q + 1) / parts), lo + base, m);
                 __syncthreads();
                 ra = rb;
                 continue;
             }
+            fetch(buf, m, per);
         }
-        if (!whole) fetch(buf, m, per);
         uint32_t n_sub;
         {
             uint32_t lg[2], parts = 0;
@@ -484,11 +577,11 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
     }
 }
 
-// The first HUB_GROUPS workgroups take the hubs' jobs (a chain of several memory latencies, so they start first): the keys of a hub that
-// lie in one range of ids are sorted in LDS or, where they do not fit, counted id by id, HUB_SPAN ids at a time.  The others
-// list their bucket's long rows and their chunks, in row order (as long_rows_emit_kernel does).
+// The first JOB_GROUPS workgroups take the jobs of crowded buckets (a chain of several memory latencies, so they start first): a range of
+// rows is sorted in LDS; so are the keys of a hub that lie in one range of ids or, where they do not fit, they are counted id by id,
+// HUB_SPAN ids at a time.  The others list their bucket's long rows and their chunks, in row order (as long_rows_emit_kernel does).
 __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, int64_t n, BucketPlan p, BucketScratch s, BucketOut out,
-                                                                   const uint32_t* __restrict__ hub_keys) {
+                                                                   const uint32_t* __restrict__ by_row) {
     static_assert(HUB_SPAN == BK_CAP, "one array for both");
     __shared__ uint32_t buf[BK_CAP];
     __shared__ RadixLds radix;
@@ -496,8 +589,9 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, 
     __shared__ unsigned long long wave_sum64[BK_WAVES];
     __shared__ uint32_t wave_sum[BK_WAVES];
     const int B = p.n_buckets, tid = threadIdx.x;
-    if ((int)blockIdx.x >= HUB_GROUPS) {
-        const int at_b = (int)blockIdx.x - HUB_GROUPS, dir = at_b >= B, b = at_b - dir * B;
+    if (s.totals[4] > s.hubs_most) return;                 // refused
+    if ((int)blockIdx.x >= JOB_GROUPS) {
+        const int at_b = (int)blockIdx.x - JOB_GROUPS, dir = at_b >= B, b = at_b - dir * B;
         if (!out.long_row[dir]) {
             if (b == 0 && tid < 2) s.totals[2 * dir + tid] = 0ull;
             return;
@@ -551,29 +645,33 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, 
         }
         return;
     }
-    const uint32_t jobs = *s.n_jobs;
+    const uint32_t jobs = *s.n_jobs, id_mask = p.id_bits == 32 ? ~0u : (1u << p.id_bits) - 1u;
     const int lane = tid & 63, wave = tid >> 6;
-    for (uint32_t job = blockIdx.x; job < jobs; job += HUB_GROUPS) {
+    for (uint32_t job = blockIdx.x; job < jobs; job += JOB_GROUPS) {
         const uint4 h = s.jobs[job];
         const int dir = (int)(h.x >> 31);
-        const uint32_t id0 = h.x & 0x7FFFFFFFu, id1 = h.y;
-        const uint32_t* const in = hub_keys + dir * nnz + h.z;
-        uint32_t below = 0, all_below;
-        if (tid == 0) fill = 0u;
-        __syncthreads();
-        each_key(in, h.w, [&](bool on, uint32_t id) {
-            below += on && id < id0 ? 1u : 0u;
-            const bool mine = on && id >= id0 && id < id1;
-            const unsigned long long who = __ballot(mine);
-            if (!who) return;
-            const int lead = __ffsll(who) - 1;
-            uint32_t at = 0;
-            if (lane == lead) at = atomicAdd(&fill, (uint32_t)__popcll(who));
-            at = __shfl(at, lead, 64) + __popcll(who & ((1ull << lane) - 1ull));
-            if (mine && at < (uint32_t)BK_CAP) buf[at] = id;
-        });
-        (void)block_scan<BK_WAVES>(below, wave_sum, all_below);
-        const uint32_t m = fill;                           // (block_scan's barriers are between)
+        const bool whole_rows = (h.x & JOB_ROWS) != 0;
+        const uint32_t id0 = h.x & (JOB_ROWS - 1u), id1 = h.y;
+        const uint32_t* const in = by_row + dir * nnz + h.z;
+        uint32_t m = h.w, below = 0, all_below = 0;
+        if (!whole_rows) {
+            if (tid == 0) fill = 0u;
+            __syncthreads();
+            each_key(in, h.w, [&](bool on, uint32_t key) {
+                const uint32_t id = key & id_mask;
+                below += on && id < id0 ? 1u : 0u;
+                const bool mine = on && id >= id0 && id < id1;
+                const unsigned long long who = __ballot(mine);
+                if (!who) return;
+                const int lead = __ffsll(who) - 1;
+                uint32_t at = 0;
+                if (lane == lead) at = atomicAdd(&fill, (uint32_t)__popcll(who));
+                at = __shfl(at, lead, 64) + __popcll(who & ((1ull << lane) - 1ull));
+                if (mine && at < (uint32_t)BK_CAP) buf[at] = id;
+            });
+            (void)block_scan<BK_WAVES>(below, wave_sum, all_below);
+            m = fill;                                      // (block_scan's barriers are between)
+        }
         int32_t* o = out.idx[dir] + h.z + all_below;
         if (m <= (uint32_t)BK_CAP) {
             uint32_t k[BK_PER];
@@ -581,10 +679,10 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, 
 #pragma unroll
             for (int i = 0; i < BK_PER; ++i) {
                 const uint32_t at = (uint32_t)((wave * per + i) * 64 + lane);
-                k[i] = i < per && at < m ? buf[at] : ~0u;
+                k[i] = i < per && at < m ? (whole_rows ? in[at] : buf[at]) : ~0u;
             }
-            radix_sort(k, per, p.id_bits, buf, radix);
-            for (uint32_t i = tid; i < m; i += BK_THREADS) o[i] = (int32_t)buf[i];
+            radix_sort(k, per, whole_rows ? p.row_bits + p.id_bits : p.id_bits, buf, radix);
+            for (uint32_t i = tid; i < m; i += BK_THREADS) o[i] = (int32_t)(buf[i] & id_mask);
             __syncthreads();
             continue;
         }
@@ -594,7 +692,8 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, 
             __syncthreads();
             for (int i = tid; i < HUB_SPAN; i += BK_THREADS) buf[i] = 0u;
             __syncthreads();
-            each_key(in, h.w, [&](bool on, uint32_t id) {
+            each_key(in, h.w, [&](bool on, uint32_t key) {
+                const uint32_t id = key & id_mask;
                 if (on && id >= a && id < z) atomicAdd(&buf[id - a], 1u);
             });
             __syncthreads();
@@ -609,34 +708,56 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_finish_kernel(int64_t nnz, 
     }
 }
 
+// The 64-bit keys again, from the CSR's packed ones.
+__global__ __launch_bounds__(256) void bucket_unpack_kernel(const uint32_t* __restrict__ packed, int64_t nnz, BucketPlan p,
+                                                            const uint32_t* __restrict__ start /*[B + 1]*/, uint64_t* __restrict__ keys) {
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= nnz) return;
+    int x = 0, y = p.n_buckets;                            // start[x] <= e < start[y]
+    while (y - x > 1) {
+        const int mid = (x + y) >> 1;
+        if ((int64_t)start[mid] <= e) x = mid; else y = mid;
+    }
+    const uint32_t k = packed[e], id_mask = p.id_bits == 32 ? ~0u : (1u << p.id_bits) - 1u;
+    keys[e] = (uint64_t)(((uint32_t)x << p.row_bits) + (k >> p.id_bits)) << 32 | (uint64_t)(k & id_mask);
+}
+
 // keys: nnz of them, clobbered; packed: scratch of the same size; scratch: bucket_scratch_bytes.  Fills the handle's CSR, CSC and
 // degrees and the lists of its long rows (arrays of the worst case's size, or null where no row can be long); waits for the lists'
-// lengths.  long_edges: the edges of each direction's long rows.
+// lengths.  long_edges: the edges of each direction's long rows.  *done = false: the build was refused, keys holds them again.
 grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys, uint64_t* packed, void* scratch, int64_t (&long_edges)[2],
-                        hipStream_t st) {
+                        bool* done, hipStream_t st) {
     const int64_t n = h->n, nnz = h->nnz;
     const BucketScratch s = carve_scratch(p, nnz, scratch);
     const BucketOut out{{h->rowptr, h->colptr}, {h->col, h->row}, {h->d_local_in, h->d_local_out},
                         {h->csr_long.long_row, h->csc_long.long_row}, {h->csr_long.long_first, h->csc_long.long_first},
                         {h->csr_long.chunk_begin, h->csc_long.chunk_begin}, {h->csr_long.chunk_end, h->csc_long.chunk_end}};
     const size_t hist_bytes = 2 * (size_t)p.n_buckets * sizeof(uint32_t);
-    GRP_TRY(launch_fill_zero(s.count, s.clear_bytes, st));
+    GRP_TRY(launch_fill_zero(s.totals, s.clear_bytes, st));
     const int64_t count_groups = cdiv(nnz, 8 * BK_THREADS);
     hipLaunchKernelGGL(bucket_count_kernel, dim3((unsigned)(count_groups < 512 ? count_groups : 512)), dim3(BK_THREADS), hist_bytes, st, keys, nnz,
                        p, s.count);
-    hipLaunchKernelGGL(bucket_start_kernel, dim3(1), dim3(BK_THREADS), 0, st, s.count, p.n_buckets, s.start, s.cursor);
+    hipLaunchKernelGGL(bucket_start_kernel, dim3(1), dim3(BK_THREADS), 0, st, s, p.n_buckets);
     // Long tiles make long runs in the buckets, short ones more workgroups.
     const int per = (int)(nnz >= (int64_t)256 * SC_TILE ? SC_PER : nnz <= (int64_t)256 * 4 * BK_THREADS ? 4 : cdiv(nnz, 256 * BK_THREADS));
     const size_t scatter_bytes = hist_bytes / 2 * 3 + (size_t)per * BK_THREADS * 6;
     hipLaunchKernelGGL(bucket_scatter_kernel, dim3((unsigned)cdiv(nnz, per * BK_THREADS)), dim3(BK_THREADS), scatter_bytes, st, keys, nnz, p, per,
-                       s.cursor, (uint32_t*)packed);
+                       (const unsigned long long*)(s.totals + 4), s.cursor, (uint32_t*)packed);
     GRP_LAUNCH_CHECK();
     hipLaunchKernelGGL(bucket_sort_kernel, dim3(2 * p.n_buckets), dim3(BK_THREADS), 0, st, (const uint32_t*)packed, nnz, n, p, s, out, (uint32_t*)keys);
-    hipLaunchKernelGGL(bucket_finish_kernel, dim3(2 * p.n_buckets + HUB_GROUPS), dim3(BK_THREADS), 0, st, nnz, n, p, s, out, (const uint32_t*)keys);
+    hipLaunchKernelGGL(bucket_finish_kernel, dim3(2 * p.n_buckets + JOB_GROUPS), dim3(BK_THREADS), 0, st, nnz, n, p, s, out, (const uint32_t*)keys);
     GRP_LAUNCH_CHECK();
-    unsigned long long totals[4];
+    unsigned long long totals[5];
     GRP_HIP(hipMemcpyAsync(totals, s.totals, sizeof totals, hipMemcpyDeviceToHost, st));
     GRP_HIP(hipStreamSynchronize(st));
+    *done = totals[4] <= s.hubs_most;
+    if (!*done) {
+        if (totals[4] == REFUSED_AT_ONCE) return GRP_OK;   // (keys are untouched)
+        hipLaunchKernelGGL(bucket_unpack_kernel, dim3((unsigned)cdiv(nnz, 256)), dim3(256), 0, st, (const uint32_t*)packed, nnz, p, (const uint32_t*)s.start,
+                           keys);
+        GRP_LAUNCH_CHECK();
+        return GRP_OK;
+    }
     LongRows* const lr[2] = {&h->csr_long, &h->csc_long};
     for (int d = 0; d < 2; ++d) {
         lr[d]->n_long = (int32_t)(totals[2 * d] >> 32);

@@ -564,7 +564,8 @@ __global__ __launch_bounds__(256) void local_keys_kernel(const int64_t* __restri
     }
 }
 
-// From sorted keys: idx[i] = low half; ptr[r] = first position whose high half is >= r.  SWAPPED: the halves change places.
+// From sorted keys: idx[i] = low half; ptr[r] = first position whose high half is >= r (null: left to csr_rows_kernel).  SWAPPED: the
+// halves change places.
 template <bool SWAPPED>
 __global__ __launch_bounds__(256) void csr_from_keys_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int64_t n,
                                                             int64_t* __restrict__ ptr, int32_t* __restrict__ idx) {
@@ -572,9 +573,24 @@ __global__ __launch_bounds__(256) void csr_from_keys_kernel(const uint64_t* __re
         auto row = [&](int64_t k) { return (int64_t)(SWAPPED ? keys[k] & 0xFFFFFFFFull : keys[k] >> 32); };
         const int64_t hi = i < nnz ? row(i) : n;
         const int64_t prev = i > 0 ? row(i - 1) : -1;
-        for (int64_t r = prev + 1; r <= hi; ++r) ptr[r] = i;
+        if (ptr)
+            for (int64_t r = prev + 1; r <= hi; ++r) ptr[r] = i;
         if (i < nnz) idx[i] = (int32_t)(SWAPPED ? keys[i] >> 32 : keys[i] & 0xFFFFFFFFull);
     }
+}
+
+// The pointers alone, a search for each: where most rows are empty, one key after another would have a thread write all the pointers of
+// a gap (2e6 rows of which 1000 have the 3e7 edges: 50 ms).
+template <bool SWAPPED>
+__global__ __launch_bounds__(256) void csr_rows_kernel(const uint64_t* __restrict__ keys, int64_t nnz, int64_t n, int64_t* __restrict__ ptr) {
+    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (r > n) return;
+    int64_t lo = 0, hi = nnz;                            // first position whose row is >= r
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)(SWAPPED ? keys[mid] & 0xFFFFFFFFull : keys[mid] >> 32) < r) lo = mid + 1; else hi = mid;
+    }
+    ptr[r] = lo;
 }
 
 __global__ __launch_bounds__(256) void degree_from_ptr_kernel(const int64_t* __restrict__ ptr, int64_t n,
@@ -788,12 +804,15 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
     }
     (void)carve_csr_csc(h, vals != nullptr, cap_long, cap_chunks, h->slab, h->slab_bytes);
     BucketPlan plan;
+    bool uneven = false;                                 // few rows hold most edges
     if (!vals && bucket_plan(n, nnz, &plan)) {
         DevBuf scratch;
         int64_t long_edges[2];
+        bool done = false;
         GRP_TRY(scratch.alloc(bucket_scratch_bytes(plan, nnz)));
-        GRP_TRY(bucket_build(h, plan, keys, keys_alt, scratch.p, long_edges, st));
-        return build_slice_tasks(h, long_edges, st);
+        GRP_TRY(bucket_build(h, plan, keys, keys_alt, scratch.p, long_edges, &done, st));
+        if (done) return build_slice_tasks(h, long_edges, st);
+        uneven = true;
     }
     const unsigned id_bits = bits_for(n > 1 ? n : 2);
     // one scratch allocation: the sorts' temporary storage, later the long-row pass's prefix sums
@@ -812,7 +831,8 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
         GRP_HIP(sort_bits(tmp.p, sort_bytes, keys, keys_alt, vals, vals_alt, nnz, 0u, 32u + id_bits, st));
         if (vals) GRP_HIP(hipMemcpyAsync(h->csr_w, vals_alt, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
     }
-    hipLaunchKernelGGL(csr_from_keys_kernel<false>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys_alt, nnz, n, h->rowptr, h->col);
+    if (uneven) hipLaunchKernelGGL(csr_rows_kernel<false>, dim3((unsigned)cdiv(n + 1, 256)), dim3(256), 0, st, (const uint64_t*)keys_alt, nnz, n, h->rowptr);
+    hipLaunchKernelGGL(csr_from_keys_kernel<false>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys_alt, nnz, n, uneven ? nullptr : h->rowptr, h->col);
     GRP_LAUNCH_CHECK();
     // The transpose: the keys are in order of (destination, source), so that a stable sort by source alone gives the order of
     // (source, destination): half the digits.
@@ -820,7 +840,8 @@ static grp_status build_csr_csc(grp_partition_t* h, uint64_t* keys, uint64_t* ke
         GRP_HIP(sort_bits(tmp.p, sort_bytes, keys_alt, keys, vals_alt, vals, nnz, 0u, id_bits, st));
         if (vals) GRP_HIP(hipMemcpyAsync(h->csc_w, vals, (size_t)nnz * sizeof(float), hipMemcpyDeviceToDevice, st));
     }
-    hipLaunchKernelGGL(csr_from_keys_kernel<true>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys, nnz, n, h->colptr, h->row);
+    if (uneven) hipLaunchKernelGGL(csr_rows_kernel<true>, dim3((unsigned)cdiv(n + 1, 256)), dim3(256), 0, st, (const uint64_t*)keys, nnz, n, h->colptr);
+    hipLaunchKernelGGL(csr_from_keys_kernel<true>, dim3(grid_for(nnz + 1)), dim3(256), 0, st, keys, nnz, n, uneven ? nullptr : h->colptr, h->row);
     GRP_LAUNCH_CHECK();
     if (n > 0) {
         hipLaunchKernelGGL(degree_from_ptr_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, h->rowptr, n, h->d_local_in);

@@ -67,3 +67,64 @@ def test_hash_split_bit_exact(N, K):
         assert part.n == want["n"]
         for k in KEYS:
             assert np.array_equal(part.array(k), want[k]), k
+
+
+def _degrees(kind):
+    W, C = 4096, 8192                       # keys by which a crowded bucket's rows are dealt to jobs; keys a workgroup sorts
+    return {"edges of a job": [W - 1, 1, W, 0, W + 1, 3, C - 1, C, 0, C + 1, 2, W, W, W],
+            "hub first and last": [C + 1, 5, 5, 0, 3 * C],
+            "one after another": [W] * 9 + [W + 1] * 5,
+            "a hub of one sort": [C + 1],
+            "long hub": [(1 << 18) + 1, 7, 1 << 18],
+            "few ranges": [C - 1, 2, C - 9], "few ranges, a hub": [7, 2 * C - 9], "jobs at once": [W, W, W, W, 1],
+            "too long for a workgroup": [(1 << 20) + 1, 40],
+            "too much for the hubs' jobs": [1_000_000, 1_000_000, 1_000_000, 40]}[kind]
+
+
+@pytest.mark.parametrize("spread", [1, 300])                # rows beside each other, in a bucket each
+@pytest.mark.parametrize("kind", ["edges of a job", "hub first and last", "one after another", "a hub of one sort", "long hub", "few ranges", "few ranges, a hub", "jobs at once",
+                                  "too long for a workgroup", "too much for the hubs' jobs"])
+def test_crowded_buckets_bit_exact(kind, spread):
+    import paper_2602_01872_amd as g
+    deg = _degrees(kind)
+    n, E = 70_000, sum(deg) + 4000
+    print(f"[case] crowded buckets {kind} spread={spread} E={E}", flush=True)
+    rng = np.random.default_rng(E)
+    rows = 100 + spread * np.arange(len(deg))
+    a = rng.permutation(np.concatenate([np.repeat(rows, deg), rng.integers(0, n, 4000)]))
+    b = np.where(rng.random(E) < 0.1, rng.integers(5, 12, E), rng.integers(0, n, E))      # (some ids of a row many times over)
+    for s, d in ((a, b), (b, a)):
+        want = ograph.local_graph_from_edges(s, d, n)
+        part = g.grp_partition_from_local_coo(torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV), n)
+        for k in KEYS:
+            assert np.array_equal(part.array(k), want[k]), k
+        x = torch.arange(4 * n, device=DEV).remainder_(3).float().view(n, 4)
+        sd, dd = torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV)
+        for transposed, (u, v) in ((False, (sd, dd)), (True, (dd, sd))):       # (sums below 2^24: exact)
+            y = torch.empty(n, 4, device=DEV)
+            g.grp_spmm(part, transposed, g.SCALE_NONE, False, 4, x, 4, g.DTYPE_FP32, y, 4)
+            assert torch.equal(y, torch.zeros(n, 4, device=DEV).index_add_(0, v, x[u])), transposed
+
+
+def test_heavy_rows_beside_each_other_cost_no_more_than_scattered_ones():
+    """150 popular nodes, numbered first: once read again for every one of them, 85 ms against 0.34 scattered."""
+    import paper_2602_01872_amd as g
+    n, E, popular = 300_000, 3_000_000, 150
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    s = popular + torch.randint(n - popular, (E,), generator=gen, device=DEV)
+    d = torch.randint(popular, (E,), generator=gen, device=DEV)
+    perm = torch.randperm(n, generator=gen, device=DEV)
+
+    def best(s, d):
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.grp_partition_from_local_coo(s, d, n).destroy()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    keep = g.grp_partition_from_local_coo(s[:4], d[:4], n)
+    assert best(s, d) < 20 * best(perm[s], perm[d])
+    keep.destroy()
