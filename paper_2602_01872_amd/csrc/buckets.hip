@@ -43,12 +43,13 @@ bool bucket_plan(int64_t n, int64_t nnz, BucketPlan* p) {
     if (n < 1 || nnz < 1 || n > ((int64_t)1 << 22) || nnz > ((int64_t)1 << 26)) return false;
     p->id_bits = 1;
     while (((int64_t)1 << p->id_bits) < n) ++p->id_bits;
-    int r = BK_ROW_BITS;
+    const int most = std::min(BK_ROW_BITS, 32 - p->id_bits);       // (2^22 nodes: 10, and as many buckets as there may be)
+    int r = most;
     while (r > 0 && (nnz << r) > n * BK_AIM) --r;
-    while (r < BK_ROW_BITS && ((n - 1) >> r) >= BK_MAX) ++r;
+    while (r < most && ((n - 1) >> r) >= BK_MAX) ++r;
     p->row_bits = r;
     p->n_buckets = (int)(((n - 1) >> r) + 1);
-    return p->n_buckets <= BK_MAX && r + p->id_bits <= 32;
+    return p->n_buckets <= BK_MAX;
 }
 
 struct BucketScratch {

@@ -33,6 +33,7 @@ def _edges(kind, n, E, rng):
     ("uniform", 1, 1), ("uniform", 1, 9000), ("uniform", 2, 4097), ("uniform", 63, 128), ("uniform", 2049, 8192),
     ("uniform", 5000, 60001), ("hub", 40001, 60000), ("hub", 16385, 8193 * 2), ("same", 3, 20000), ("crowded", 2000, 27000),
     ("near", 3001, 400000), ("near hub", 65537, 150000), ("last", 70000, 300000), ("uniform", 1 << 22, 5000), ("uniform", (1 << 22) + 1, 5000), ("hub", 300000, 9000000),
+    ("uniform", 1 << 22, 9_000_000),       # as many buckets as there may be, keys of 32 bits, the longest tiles of the scatter
 ])
 def test_local_edges_bit_exact(kind, n, E):
     import paper_2602_01872_amd as g
