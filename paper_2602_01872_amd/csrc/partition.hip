@@ -4,8 +4,8 @@
 // endpoints it owns, renumbers nodes by ascending global id and stores the edge multiset
 // twice in canonical order: CSR by destination (sources ascending) and CSC by source
 // (destinations ascending).  Canonical order comes from a sort of the 64-bit keys (row << 32 | column): by buckets of rows
-// (buckets.hip), or a device-wide radix sort where weights travel with the keys or there are more than 2^22 nodes or 2^26
-// edges.  Equal keys are indistinguishable, so the arrays are unique and can
+// (buckets.hip), or a device-wide radix sort where weights travel with the keys, there are more than 2^22 nodes or 2^26
+// edges, or a few rows hold most of them.  Equal keys are indistinguishable, so the arrays are unique and can
 // be compared bit for bit.  Everything is integer work: counters use integer atomics only.
 //
 // The device-wide radix sort and prefix sum are rocPRIM's; the hashing, filtering,
@@ -240,13 +240,19 @@ __device__ __forceinline__ void dg_table_add(int32_t* slot_key, uint32_t* slot_c
     atomicAdd(&dg[r], 1ull);
 }
 
+// KEYS: the keys of the kept edges too, into a buffer of `cap` of them (as edge_scan_keys_kernel does).  counters: [1] += bad ids,
+// and += kept edges to [2], the slot cursor, or else [0].
+template <bool KEYS>
 __global__ __launch_bounds__(256) void edge_scan_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
                                                         int64_t E, int64_t N, NodeSet own,
                                                         unsigned long long* __restrict__ dg,
-                                                        unsigned long long* __restrict__ counters /*[0]=kept,[1]=bad*/) {
+                                                        unsigned long long* __restrict__ counters,
+                                                        uint64_t* __restrict__ keys, unsigned long long cap) {
     const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
     __shared__ int32_t slot_key[DG_SLOTS];
     __shared__ uint32_t slot_count[DG_SLOTS];
+    __shared__ uint32_t wave_sum[4];
+    __shared__ unsigned long long tile_base;
     for (int i = threadIdx.x; i < DG_SLOTS; i += 256) { slot_key[i] = -1; slot_count[i] = 0u; }
     __syncthreads();
     unsigned long long kept = 0, bad = 0;
@@ -261,20 +267,44 @@ __global__ __launch_bounds__(256) void edge_scan_kernel(const int64_t* __restric
             load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
             load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);     // -2: past the end, neither counted nor an error
         }
-        bool mine[PER];
+        // Eight edges' lookups are requested together, in two stages; a lane that has no need of one reads word 0 (one line for all of
+        // them).
+        uint2 wv[PER], wu[PER];
+        uint32_t has = 0, both = 0;                      // bit i: the destination, and also the source, of edge i is in the set
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int64_t u = us[i], v = vs[i];
-            mine[i] = false;
-            if (v == -2) continue;
-            if (u < 0 || v < 0 || u >= N || v >= N) { bad++; continue; }
-            mine[i] = set_has(own, v);
+            const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
+            bad += !ok && vs[i] != -2;
+            if (!ok) us[i] = vs[i] = 0;
+            wv[i] = own.words[vs[i] >> 5];
+            has |= (ok ? 1u : 0u) << i;
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            if (!mine[i]) continue;
-            dg_table_add(slot_key, slot_count, dg, set_rank(own, vs[i]));
-            if (set_has(own, us[i])) kept++;
+            if (!word_has(wv[i], vs[i])) has &= ~(1u << i);
+            wu[i] = own.words[(has >> i) & 1u ? us[i] >> 5 : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (!((has >> i) & 1u)) continue;
+            dg_table_add(slot_key, slot_count, dg, word_rank(wv[i], vs[i]));
+            if (word_has(wu[i], us[i])) both |= 1u << i;
+        }
+        if (KEYS) {
+            uint32_t total;
+            const uint32_t before = block_scan<4>((uint32_t)__popc(both), wave_sum, total);
+            if (threadIdx.x == 0) tile_base = total ? atomicAdd(&counters[2], (unsigned long long)total) : 0ull;
+            __syncthreads();
+            unsigned long long slot = tile_base + before;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (!((both >> i) & 1u)) continue;
+                if (slot < cap) keys[slot] = ((uint64_t)(uint32_t)word_rank(wv[i], vs[i]) << 32) | (uint64_t)(uint32_t)word_rank(wu[i], us[i]);
+                ++slot;
+            }
+            // (tile_base is written anew behind the next tile's barriers, which every thread reaches with its base read)
+        } else {
+            kept += (unsigned long long)__popc(both);
         }
     }
     __syncthreads();
@@ -932,10 +962,11 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
     const unsigned scan_grid = grid_for(E) < (unsigned)EDGE_SCAN_GRID ? grid_for(E) : (unsigned)EDGE_SCAN_GRID;
     // Unweighted: one pass writes the keys too, into a buffer sized for twice the expected E / K^2 kept edges, and the local ids of twice
     // the expected E / K edges that end in the partition.  Ids beyond 32 bits and more ranges of local ids than that pass
-    // orders take two passes and an addition per edge instead.
+    // orders are counted through a table in LDS instead (a build from 62e6 edges, one of 2 parts of 1e7 nodes: 4.5 ms; with a second pass
+    // over the edges for the keys 5.4).
     const int64_t spans = cdiv(n > 0 ? n : 1, (int64_t)1 << SPAN_BITS), scan_tiles = cdiv(E, SCAN_TILE);
-    const bool one_pass = !weighted && N < ((int64_t)1 << 31) && spans <= SPANS_MAX;
-    int64_t cap = one_pass ? 2 * (E / K / K) + (1 << 20) : 0, id_cap = one_pass ? 2 * (E / K) + (1 << 20) : 0;
+    const bool ranged = !weighted && N < ((int64_t)1 << 31) && spans <= SPANS_MAX;
+    int64_t cap = weighted ? 0 : 2 * (E / K / K) + (1 << 20), id_cap = ranged ? 2 * (E / K) + (1 << 20) : 0;
     if (cap > E) cap = E;
     if (id_cap > E) id_cap = E;
     if (id_cap > (int64_t)0xFFFFFFF0) id_cap = 0xFFFFFFF0;
@@ -943,12 +974,17 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
     size_t key_pitch = (((size_t)(cap > 0 ? cap : 1) * sizeof(uint64_t)) + 255) & ~(size_t)255;
     const size_t id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
     if (!weighted) GRP_TRY(keybuf.alloc(2 * key_pitch));
-    if (one_pass && E > 0) GRP_TRY(idbuf.alloc(id_pitch + (size_t)scan_tiles * (size_t)(spans + 1) * sizeof(uint32_t)));
+    if (ranged && E > 0) GRP_TRY(idbuf.alloc(id_pitch + (size_t)scan_tiles * (size_t)(spans + 1) * sizeof(uint32_t)));
     if (E > 0) {
-        if (!one_pass) {
+        if (weighted) {
             ProfScope ps("partition_edge_scan", st, 0.0, 16.0 * (double)E);
-            hipLaunchKernelGGL(edge_scan_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
-                               (unsigned long long*)h->d_global_in, t.counters);
+            hipLaunchKernelGGL(edge_scan_kernel<false>, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
+                               (unsigned long long*)h->d_global_in, t.counters, (uint64_t*)nullptr, 0ull);
+            GRP_LAUNCH_CHECK();
+        } else if (!ranged) {
+            ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
+            hipLaunchKernelGGL(edge_scan_kernel<true>, dim3(scan_grid), dim3(256), 0, st, src, dst, E, N, own,
+                               (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(), (unsigned long long)cap);
             GRP_LAUNCH_CHECK();
         } else {
             ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
@@ -969,7 +1005,7 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
     }
     if (host_counters[1] != 0)
         return fail(GRP_ERANGE, "%llu edges have an endpoint outside [0, %lld)", host_counters[1], (long long)N);
-    const int64_t nnz = (int64_t)(one_pass ? host_counters[2] : host_counters[0]);
+    const int64_t nnz = (int64_t)(weighted ? host_counters[0] : host_counters[2]);
     h->nnz = nnz;
     if (weighted) return weighted_build(src, dst, w, E, own, st, h);
     DevBuf exact;                                        // only if the first buffer was too small

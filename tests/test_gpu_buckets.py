@@ -70,6 +70,34 @@ def test_hash_split_bit_exact(N, K):
             assert np.array_equal(part.array(k), want[k]), k
 
 
+@pytest.mark.parametrize("inside", [False, True])            # every edge within the part: more keys than one pass has room for
+def test_hash_split_of_many_nodes_reads_the_edges_once(inside):
+    """Parts of more than 2^22 nodes count their in-degrees another way, in the pass that writes the keys all the same."""
+    import paper_2602_01872_amd as g
+    N, K, E = 9_000_000, 2, 3_000_001
+    print(f"[case] hash N={N} K={K} inside={inside}", flush=True)
+    rng = np.random.default_rng(8)
+    s, d = rng.integers(0, N, E), rng.integers(0, N, E)
+    d[: E // 3] = 77                                        # a hub
+    if inside:
+        owner = torch.empty(N, dtype=torch.int32, device=DEV)
+        g.grp_node_owners(N, K, 5, owner)
+        own = torch.nonzero(owner == 1).flatten().cpu().numpy()
+        assert len(own) > 1 << 22
+        s, d = own[s % len(own)], own[d % len(own)]
+    want = ograph.partition(s, d, N, K, 5, 1)
+    g.grp_profile_enable(1)
+    try:
+        part = g.grp_partition(torch.from_numpy(s).to(DEV), torch.from_numpy(d).to(DEV), N, K, 5, 1)
+        torch.cuda.synchronize()
+        passes = [k for k in g.grp_profile_report() if k.startswith("partition_edge")]
+    finally:
+        g.grp_profile_enable(0)
+    assert passes == ["partition_edge_scan_keys"] + ["partition_edge_keys"] * inside
+    for k in KEYS:
+        assert np.array_equal(part.array(k), want[k]), k
+
+
 def _degrees(kind):
     W, C = 4096, 8192                       # keys by which a crowded bucket's rows are dealt to jobs; keys a workgroup sorts
     return {"edges of a job": [W - 1, 1, W, 0, W + 1, 3, C - 1, C, 0, C + 1, 2, W, W, W],
