@@ -352,8 +352,11 @@ grp_status grp_train_step(const grp_partition_t* part, const grp_model_desc* mod
  * for bit, but the steps' launches are merged where they are the same kernel (small partitions and mini-batches are bound by their
  * number).  HOST arrays of `count` device pointers each: features, labels, train_masks (the array or any entry may be
  * null), workspaces (workspace_bytes each), grads_out and stats_out must not overlap; opts: HOST array of `count` options.
- * Steps that cannot be merged (attention models, weighted partitions, partitions with the sliced schedule, wide products over many
- * rows, profiling switched on) run one after another.  Capturable like grp_train_step.  Errors: as there; of
+ * Attention models, full-graph steps of a partition with the sliced schedule, products over so many rows that their weights are split
+ * beforehand, two entries with one workspace, and any steps while profiling is on run one after another, as that many calls.  Of the others each
+ * step makes by itself: the scaled weights of a GCN with dropout, the loss of more than 192 classes, the first launch and the transposed
+ * blocks of deep models (more than 12 packed weights: four each for a hidden GraphSAGE layer; more than four layers of blocks), the sums of
+ * weighted edges and of rows narrower than a vector, products and column sums of operands that rule out 16-byte loads.  Capturable like grp_train_step.  Errors: as there; of
  * merged steps none has been started when an argument of any is refused. */
 grp_status grp_train_steps(int32_t count, const grp_partition_t* const* parts, const grp_model_desc* model,
                            const grp_step_opts* opts, const void* const* features,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <vector>
 #include <hip/hip_bf16.h>
 
@@ -100,13 +101,14 @@ template <class Op, class P> __global__ __launch_bounds__(Op::THREADS, Op::WGS) 
 }
 
 struct LaunchRecord {
-    void (*go)(const LaunchRecord* const* recs, int count, hipStream_t st);     // launches `count` records of this kind (the same go)
+    void (*go)(const LaunchRecord* const* recs, int count, hipStream_t st) = nullptr;     // launches `count` records of this kind (the same go)
     dim3 grid;
     std::vector<unsigned char> args;               // a Pack
+    std::function<void()> alone;                   // a launch that is not merged (go: null)
 };
 struct LaunchRecorder {
     std::vector<LaunchRecord> list;
-    bool unsupported = false;                      // a launch that cannot be merged was asked for (and not made)
+    bool refused = false;                          // a launch that no merged step has was asked for (and not made)
     int steps = 1;                                 // that may share a launch
 };
 extern thread_local LaunchRecorder* g_recorder;    // null: launches are made at once
@@ -143,13 +145,22 @@ template <class Op, class... P, class... A> void launch(void (*kernel)(P...), Op
     r.grid = grid;
     r.args.assign((const unsigned char*)&p, (const unsigned char*)&p + sizeof p);
 }
-// In front of a launch that has no Op: false if it must not be made, because launches are being recorded (the steps are then made one by
-// one).
+// The same of a kernel without an Op, which steps that are otherwise merged launch one by one: what few models or odd sizes run.
+template <class... P, class... A> void launch_alone(void (*kernel)(P...), dim3 grid, dim3 block, unsigned lds, hipStream_t st, A... a) {
+    if (!g_recorder) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, P(a)...);
+        return;
+    }
+    g_recorder->list.emplace_back();
+    g_recorder->list.back().alone = [=] { hipLaunchKernelGGL(kernel, grid, block, lds, st, P(a)...); };
+}
+// In front of a launch that is large by itself: false if it must not be made, because launches are being recorded (such steps are made one
+// by one: their launches do not bound them, and side by side they would take the caches from each other).
 inline bool may_launch() {
-    if (g_recorder) g_recorder->unsupported = true;
+    if (g_recorder) g_recorder->refused = true;
     return !g_recorder;
 }
-#define GRP_PLAIN_LAUNCH(...) do { if (grp::may_launch()) hipLaunchKernelGGL(__VA_ARGS__); } while (0)
+#define GRP_LARGE_LAUNCH(...) do { if (grp::may_launch()) hipLaunchKernelGGL(__VA_ARGS__); } while (0)
 
 }  // namespace grp
 

@@ -233,14 +233,14 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const float* __restrict__
 
 grp_status launch_pad_rows(const float* X, int64_t ldx, int64_t n, int32_t F, float* Y, int64_t ldy, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    GRP_PLAIN_LAUNCH(pad_rows_kernel, dim3((unsigned)cdiv(n * ldy, 256)), dim3(256), 0, st, X, ldx, n, (int)F, Y, ldy);
+    launch_alone(pad_rows_kernel, dim3((unsigned)cdiv(n * ldy, 256)), dim3(256), 0, st, X, ldx, n, (int)F, Y, ldy);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
 
 grp_status launch_scale_copy(const float* in, float s, float* out, int64_t n, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    GRP_PLAIN_LAUNCH(scale_copy_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, in, s, out, n);
+    launch_alone(scale_copy_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, in, s, out, n);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -379,7 +379,7 @@ grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t ld
     if (vec)
         launch(colsum_partial_vec_kernel, colsum_partial_vec_kernel_op(), dim3((unsigned)blocks), st, A, M, N, lda, rowmul, (float*)scratch);
     else
-        GRP_PLAIN_LAUNCH(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
+        launch_alone(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
                            (float*)scratch);
     GRP_LAUNCH_CHECK();
     launch(colsum_final_kernel, colsum_final_kernel_op(), dim3((unsigned)cdiv(N, 8)), st, (const float*)scratch, blocks, N, out);
@@ -515,7 +515,7 @@ grp_status launch_prelude(const StepPrelude& pre, hipStream_t st) {
         for (int j = 0; j <= few.n; ++j) few.begin[j] = pre.pack.begin[j];
         launch(prelude_kernel<FEW>, prelude_kernel_op<FEW>(), grid, st, a, pre.degrees, degree_blocks, few);
     } else {
-        GRP_PLAIN_LAUNCH(prelude_kernel<4 * GRP_MAX_LAYERS>, grid, dim3(256), 0, st, a, pre.degrees, degree_blocks, pre.pack);
+        launch_alone(prelude_kernel<4 * GRP_MAX_LAYERS>, grid, dim3(256), 0, st, a, pre.degrees, degree_blocks, pre.pack);
     }
     GRP_LAUNCH_CHECK();
     return GRP_OK;
@@ -730,7 +730,7 @@ grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int
     else if (c_store <= 64) go(softmax_xent_reg_kernel<4>, softmax_xent_reg_kernel_op<4>());
     else if (c_store <= 128) go(softmax_xent_reg_kernel<8>, softmax_xent_reg_kernel_op<8>());
     else if (c_store <= 192) go(softmax_xent_reg_kernel<12>, softmax_xent_reg_kernel_op<12>());       // (1024 rows of 172 columns: 11 -> 5.5 us)
-    else GRP_PLAIN_LAUNCH(softmax_xent_kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS);
+    else launch_alone(softmax_xent_kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS);
 #undef GRP_SOFTMAX_ARGS
     GRP_LAUNCH_CHECK();
     RecordArgs r{(const StatsPartial*)in.scratch, counted, (in.sampled_count || in.w_local) ? 0 : 1, in.nnz_const, {}, loss_part, blocks, stats};
@@ -750,7 +750,7 @@ __global__ __launch_bounds__(256) void inverse_mass_kernel(const double* __restr
 
 grp_status launch_inverse_mass(const double* mass, int64_t n, float* inv, hipStream_t st) {
     if (n <= 0) return GRP_OK;
-    GRP_PLAIN_LAUNCH(inverse_mass_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, mass, n, inv);
+    launch_alone(inverse_mass_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, mass, n, inv);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }

@@ -997,12 +997,12 @@ static void nn_pick(const GemmNNArgs& a, hipStream_t st) {
     const int64_t slabs = round_up(cdiv(a.M, 128), NXCD);
     if (n_eff > 64) {
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, 128));
-        if (short_k) GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 16, 2>), dim3(blocks), dim3(256), 0, st, a);
-        else GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 32, 1>), dim3(blocks), dim3(256), 0, st, a);
+        if (short_k) launch_alone((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 16, 2>), dim3(blocks), dim3(256), 0, st, a);
+        else launch_alone((gemm_nn_kernel<AT, VEC, 2, 2, 2, 2, 32, 1>), dim3(blocks), dim3(256), 0, st, a);
     } else if (n_eff > 32) {
-        GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 4, 1, 1, 2, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
+        launch_alone((gemm_nn_kernel<AT, VEC, 4, 1, 1, 2, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
     } else {
-        GRP_PLAIN_LAUNCH((gemm_nn_kernel<AT, VEC, 4, 1, 1, 1, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
+        launch_alone((gemm_nn_kernel<AT, VEC, 4, 1, 1, 1, 32, 1>), dim3((unsigned)slabs), dim3(256), 0, st, a);
     }
 }
 
@@ -1046,13 +1046,13 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, p.tile_n));
         const bool pre = p.pre;
         if (pre)
-            GRP_PLAIN_LAUNCH(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
+            GRP_LARGE_LAUNCH(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
                                a.ldbt2, a.K2, a.N, p.n_all, a.planes);
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
         constexpr bool P_ = TM_ == 2 && TN_ >= 4;                                                                          \
-        if (P_ && pre && irreg) GRP_PLAIN_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
-        else if (P_ && pre) GRP_PLAIN_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        if (P_ && pre && irreg) GRP_LARGE_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (P_ && pre) GRP_LARGE_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
         else if (irreg) launch(gemm_nt_kernel<AT, TM_, TN_, true>, gemm_nt_kernel_op<AT, TM_, TN_, true>(), dim3(blocks), st, t);       \
         else launch(gemm_nt_kernel<AT, TM_, TN_, false>, gemm_nt_kernel_op<AT, TM_, TN_, false>(), dim3(blocks), st, t);                 \
     } while (0)
@@ -1578,7 +1578,7 @@ static void tn_pick(const GemmTNArgs& a, const TnPlan& p, int dual, float* out, 
             launch(gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>, gemm_tn_kernel_op<AT, VEC, GATHER, WM_, WN_, TM_, TN_>(), grid, st, a, \
                    p.tiles_k, p.tiles_n, dual, p.splits, p.chunk, out, out2, out_ld, stride, cs_out, stride);           \
         else                                                                                                           \
-            GRP_PLAIN_LAUNCH((gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>), grid, dim3(256), 0, st, a, p.tiles_k, \
+            launch_alone((gemm_tn_kernel<AT, VEC, GATHER, WM_, WN_, TM_, TN_>), grid, dim3(256), 0, st, a, p.tiles_k, \
                              p.tiles_n, dual, p.splits, p.chunk, out, out2, out_ld, stride, cs_out, stride);            \
     } while (0)
     if (p.bk_tile == 64 && p.bn_tile == 128) GRP_TN_LAUNCH(2, 2, 1, 2);

@@ -736,9 +736,9 @@ grp_status sample_blocks(const grp_partition_t* part, const grp_step_opts* o, in
                 launch(transpose_sort_kernel<FEW>, transpose_sort_kernel_op<FEW>(), dim3((unsigned)src_groups, (unsigned)(k - 1)), bst, few);
             } else {
                 constexpr int ALL = GRP_MAX_LAYERS - 1;
-                GRP_PLAIN_LAUNCH(transpose_rows_kernel<ALL>, dim3((unsigned)parts, (unsigned)(k - 1)), dim3(CS_THREADS), 0, bst, jobs);
-                GRP_PLAIN_LAUNCH(transpose_scatter_kernel<ALL>, dim3((unsigned)dst_groups, (unsigned)(k - 1)), dim3(256), 0, bst, jobs);
-                GRP_PLAIN_LAUNCH(transpose_sort_kernel<ALL>, dim3((unsigned)src_groups, (unsigned)(k - 1)), dim3(TS_THREADS), 0, bst, jobs);
+                launch_alone(transpose_rows_kernel<ALL>, dim3((unsigned)parts, (unsigned)(k - 1)), dim3(CS_THREADS), 0, bst, jobs);
+                launch_alone(transpose_scatter_kernel<ALL>, dim3((unsigned)dst_groups, (unsigned)(k - 1)), dim3(256), 0, bst, jobs);
+                launch_alone(transpose_sort_kernel<ALL>, dim3((unsigned)src_groups, (unsigned)(k - 1)), dim3(TS_THREADS), 0, bst, jobs);
             }
             GRP_LAUNCH_CHECK();
             if (lane) {

@@ -956,7 +956,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         if (!a.val && !a.colscale && !ep.tight && !a.n_rows_dev && units && whole && sums && x_bytes <= (int64_t)SLAB_X_BYTES) {
             const int64_t task_blocks = sliced ? cdiv(lr->n_tasks, 4) : 0, row_blocks = n_chunks + cdiv(a.n_rows, SLAB_ROWS);
             if (sliced && slabs * task_blocks < ((int64_t)1 << 24)) {          // (fewer than 2^32 work-items)
-                GRP_PLAIN_LAUNCH((spmm_slab_tasks_kernel<XT, SG>), dim3((unsigned)(slabs * task_blocks)), dim3(256), 0, st, (const SliceTask*)lr->tasks,
+                GRP_LARGE_LAUNCH((spmm_slab_tasks_kernel<XT, SG>), dim3((unsigned)(slabs * task_blocks)), dim3(256), 0, st, (const SliceTask*)lr->tasks,
                                  lr->n_tasks, a.idx, a.F, (const XT*)a.X, a.ldx, (uint32_t)x_bytes, a.partials, ld_part, (uint32_t)task_blocks);
                 tasks_done = true;
             }
@@ -990,7 +990,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             }
         }
         auto go = [&](auto kernel) {
-            GRP_PLAIN_LAUNCH(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F, ep.last_x,
+            GRP_LARGE_LAUNCH(kernel, tgrid, dim3(256), 0, st, (const SliceTask*)lr->tasks, lr->n_tasks, per_wave, a.idx, a.val, a.F, ep.last_x,
                                (const XT*)a.X, a.ldx, a.colscale, a.partials, ld_part, row_shift);
         };
         // bf16 rows of whole 16-byte units: eight elements per lane, half the lanes per row
@@ -1019,7 +1019,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
                a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);
     };
     auto rows_val = [&](auto kernel, int lanes) {          // with edge values
-        GRP_PLAIN_LAUNCH(kernel, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows, thr,
+        launch_alone(kernel, dim3((unsigned)(n_chunks + cdiv(a.n_rows, 256 / lanes))), dim3(256), 0, st, a.ptr, a.idx, a.val, a.n_rows, thr,
                          (const XT*)a.X, a.ldx, a.colscale, ep, n_chunks, n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr,
                          a.partials, ld_part);
     };
@@ -1044,7 +1044,7 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
         else rows(spmm_rows_kernel<XT, G, 1, NJ, false>, spmm_rows_kernel_op<XT, G, 1, NJ, false>(), G);
     }
     if (sliced) {
-        GRP_PLAIN_LAUNCH((spmm_combine_tasks_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, 4)), dim3(256), 0, st,
+        GRP_LARGE_LAUNCH((spmm_combine_tasks_kernel<XT, G, NJ>), dim3((unsigned)cdiv(lr->n_long, 4)), dim3(256), 0, st,
                            lr->long_row, (const int64_t*)lr->row_task, lr->n_long, a.ptr, (const float*)a.partials, ld_part,
                            (const XT*)a.X, a.ldx, ep);
     } else if (split) {
@@ -1123,11 +1123,11 @@ grp_status launch_spmm(const SpmmArgs& a, hipStream_t st) {
             return fail(GRP_EUNSUPPORTED, "spmm: this epilogue needs 16-byte friendly operands");
         const int64_t blocks = cdiv(a.n_rows, 4);
         if (a.x_bf16)
-            GRP_PLAIN_LAUNCH((spmm_rows_scalar_kernel<__hip_bfloat16>), dim3((unsigned)blocks), dim3(256), 0, st,
+            launch_alone((spmm_rows_scalar_kernel<__hip_bfloat16>), dim3((unsigned)blocks), dim3(256), 0, st,
                                a.ptr, a.idx, a.n_rows, a.F, (const __hip_bfloat16*)a.X, a.ldx, a.scale,
                                a.self_term, a.colscale, a.addend, a.ld_add, a.bias, a.relu, a.Y, a.ldy, a.val, a.rowscale, a.n_rows_dev);
         else
-            GRP_PLAIN_LAUNCH((spmm_rows_scalar_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, st, a.ptr,
+            launch_alone((spmm_rows_scalar_kernel<float>), dim3((unsigned)blocks), dim3(256), 0, st, a.ptr,
                                a.idx, a.n_rows, a.F, (const float*)a.X, a.ldx, a.scale, a.self_term, a.colscale, a.addend,
                                a.ld_add, a.bias, a.relu, a.Y, a.ldy, a.val, a.rowscale, a.n_rows_dev);
     }

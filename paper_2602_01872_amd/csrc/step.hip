@@ -478,6 +478,7 @@ thread_local LaunchRecorder* g_recorder = nullptr;
 
 // The launches of several steps, each step's in its own order: what stands at the front of a step is launched together with every other
 // front of the same kernel, the step with the most launches left first (so that steps that differ by a launch or two fall in again).
+// Launches that are not merged are made in their step's turn.
 static void launch_merged(const std::vector<LaunchRecorder>& steps, hipStream_t st) {
     std::vector<size_t> at(steps.size(), 0);
     std::vector<const LaunchRecord*> recs;
@@ -489,8 +490,14 @@ static void launch_merged(const std::vector<LaunchRecorder>& steps, hipStream_t 
                 lead = p;
             }
         if (left == 0) return;
-        const auto go = steps[lead].list[at[lead]].go;
-        const unsigned layers = steps[lead].list[at[lead]].grid.y;
+        const LaunchRecord& front = steps[lead].list[at[lead]];
+        if (!front.go) {
+            front.alone();
+            ++at[lead];
+            continue;
+        }
+        const auto go = front.go;
+        const unsigned layers = front.grid.y;
         recs.clear();
         for (size_t p = 0; p < steps.size(); ++p)
             if (at[p] < steps[p].list.size() && steps[p].list[at[p]].go == go && steps[p].list[at[p]].grid.y == layers)
@@ -520,8 +527,11 @@ extern "C" grp_status grp_train_steps(int32_t count, const grp_partition_t* cons
     };
     // (an attention model's launches are not recorded, nor are any while they are timed one by one)
     bool merge = count > 1 && model->arch != GRP_ARCH_GAT && !prof_enabled() && !g_recorder;
-    for (int p = 0; p < count && merge; ++p)
+    for (int p = 0; p < count && merge; ++p) {
+        // (sums over sources in slices are large launches: no need to record the step to find that out)
+        if (parts[p] && opts[p].full_graph) merge = parts[p]->csr_long.n_tasks == 0 && parts[p]->csc_long.n_tasks == 0;
         for (int q = 0; q < p; ++q) merge = merge && workspaces[p] != workspaces[q];
+    }
     if (merge) {
         try {
             std::vector<LaunchRecorder> steps((size_t)count);
@@ -531,7 +541,7 @@ extern "C" grp_status grp_train_steps(int32_t count, const grp_partition_t* cons
                 steps[(size_t)p].steps = std::min(count, MANY_MOST);
                 Recording r(&steps[(size_t)p]);
                 GRP_TRY(step(p, o));
-                merge = !steps[(size_t)p].unsupported;
+                merge = !steps[(size_t)p].refused;
             }
             if (merge) {
                 launch_merged(steps, (hipStream_t)stream);

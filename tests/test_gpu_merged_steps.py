@@ -1,5 +1,8 @@
 """Steps whose launches are merged give the bits that the same steps give one after another: partitions of very different sizes (other tiles, more
-or fewer launches: long rows, slices of the sums), more steps than one launch takes, steps that cannot be merged."""
+or fewer launches: long rows, slices of the sums), more steps than one launch takes, steps with launches that are not merged, steps that are
+made one by one.  What is merged is seen by the number of launches."""
+import ctypes
+
 import pytest
 import torch
 
@@ -17,10 +20,12 @@ def _graph(n, E, seed):
 
 @pytest.mark.parametrize("arch,dims,sizes,dropout", [
     ("gcn", [64, 64, 8], [(2500, 6000), (2400, 40000), (1, 0), (9000, 20000)], 0.0),
-    ("gcn", [17, 33, 5], [(300, 900)] * 11, 0.25),
+    ("gcn", [17, 33, 5], [(300, 900)] * 11, 0.25),                 # two launches of eight and three; scaled weights
     ("gcn_res", [32, 32, 32, 6], [(700, 5000), (4100, 9000)], 0.5),
-    ("sage", [30, 100, 70, 200], [(5000, 60000), (64, 100), (40000, 90000)], 0.5),
-    ("gat", [12, 16, 4], [(500, 3000), (600, 3000)], 0.0),
+    ("sage", [30, 100, 70, 200], [(5000, 60000), (64, 100), (40000, 90000)], 0.5),      # more classes than a row's lanes hold
+    ("sage", [24, 16, 16, 16, 16, 8], [(800, 4000)] * 3, 0.5),     # more weights than a merged launch's arguments hold
+    ("sage", [30, 3, 2], [(800, 4000)] * 3, 0.0),                  # rows narrower than a vector
+    ("gat", [12, 16, 4], [(500, 3000), (600, 3000)], 0.0),         # (one by one)
 ])
 def test_full_graph_steps(arch, dims, sizes, dropout):
     import paper_2602_01872_amd as g
@@ -74,6 +79,45 @@ def test_minibatch_steps_whose_prefix_sums_take_several_rounds():
         seeds = torch.randperm(n, generator=torch.Generator().manual_seed(i))[:1024 - i].to(torch.int32).to(DEV)
         opts.append(g.step_opts(estimator=g.EST_NONE, full_graph=False, seeds=seeds, fanouts=fanouts, sampler_seed=4, batch_id=i))
     _compare(g, [part] * 8, model, opts, [x.to(DEV)] * 8, [y.to(DEV)] * 8, None, theta.to(DEV), g.grp_param_count(model))
+
+
+def _launches(g, steps):
+    """Kernels that ``steps()`` launches: the nodes of a graph that it is captured in."""
+    steps()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        steps()
+    count = ctypes.c_size_t(0)
+    assert g.binding.load().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+# alone: launches that each step makes by itself
+@pytest.mark.parametrize("arch,dims,dropout,weighted,alone", [
+    ("gcn", [32, 32, 6], 0.0, False, 0), ("gcn", [32, 32, 6], 0.5, False, 1), ("gcn_res", [32, 32, 32, 6], 0.5, False, 1),
+    ("sage", [32, 32, 32, 32, 32, 6], 0.5, False, 1), ("sage", [32, 32, 200], 0.0, False, 1), ("sage", [32, 32, 6], 0.0, True, 4),
+])
+def test_launches_of_merged_steps(arch, dims, dropout, weighted, alone):
+    import paper_2602_01872_amd as g
+    print(f"[case] launches {arch} {dims} dropout={dropout} weighted={weighted}", flush=True)
+    K, n = 8, 2000
+    code = {"sage": g.ARCH_SAGE_MEAN, "gcn": g.ARCH_GCN, "gcn_res": g.ARCH_GCN_RESIDUAL}[arch]
+    model = g.model_desc(code, dims)
+    s, d = _graph(n, 12 * n, 3)
+    part = g.grp_partition_weighted(s, d, torch.rand(12 * n, device=DEV) + 0.5, n, 1, 0, 0) if weighted else g.grp_partition_from_local_coo(s, d, n)
+    x, y, theta = (t.to(DEV) for t in make_inputs(n, dims, arch, 7))
+    opts = g.step_opts(full_graph=True, dropout_rate=dropout, dropout_seed=3)
+    P = g.grp_param_count(model)
+    size = g.grp_step_workspace_bytes(part, model, opts)
+    ws = [torch.empty(size, dtype=torch.uint8, device=DEV) for _ in range(K)]
+    grads, stats = list(torch.empty(K, P, device=DEV)), g.new_stats(K)
+    recs = [stats[i * g.STATS_BYTES:(i + 1) * g.STATS_BYTES] for i in range(K)]
+    one = _launches(g, lambda: g.grp_train_step(part, model, opts, x, y, None, theta, ws[0], grads[0], recs[0]))
+    many = _launches(g, lambda: g.grp_train_steps([part] * K, model, [opts] * K, [x] * K, [y] * K, None, theta, ws, grads, recs))
+    print(f"{one} launches of one step, {many} of {K}", flush=True)
+    # what does not fit the arguments of one launch takes two or three
+    assert one + (K - 1) * alone <= many <= 2 * one + (K - 1) * alone
 
 
 def _compare(g, parts, model, opts, xs, ys, masks, theta, P):
