@@ -120,6 +120,20 @@ def test_launches_of_merged_steps(arch, dims, dropout, weighted, alone):
     assert one + (K - 1) * alone <= many <= 2 * one + (K - 1) * alone
 
 
+def test_trainer_keeps_one_workspace_for_steps_that_are_not_merged():
+    import paper_2602_01872_amd as g
+    n = 300
+    s, d = _graph(n, 900, 5)
+    for arch, code, held in (("gat", g.ARCH_GAT, 1), ("gcn", g.ARCH_GCN, 3)):
+        dims = [12, 16, 4]
+        x, y, theta = (t.to(DEV) for t in make_inputs(n, dims, arch, 7))
+        parts = [g.grp_partition_from_local_coo(s, d, n) for _ in range(3)]
+        tr = g.PhaseParallelTrainer(parts, g.model_desc(code, dims), [x] * 3, [y] * 3, [None] * 3, theta, g.EST_NONE, 3)
+        assert len(tr.ws) == held
+        tr.run_phase([0, 1, 2])
+    torch.cuda.synchronize()
+
+
 def _compare(g, parts, model, opts, xs, ys, masks, theta, P):
     K = len(parts)
     size = max(g.grp_step_workspace_bytes(p, model, o) for p, o in zip(parts, opts))
