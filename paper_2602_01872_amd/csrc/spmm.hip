@@ -630,6 +630,9 @@ __global__ __launch_bounds__(256) void spmm_combine_tasks_kernel(const int32_t* 
 //   73, 64 196 -> 165, 256 682 -> 553
 //   bf16: 2^20 rows, 25 edges: F = 32 405 -> 271, 64 600 -> 368, 128 882 -> 679, 256 1467 -> 1289;  3e5 rows, 20 edges: F = 64 165 -> 100
 // (Slabs of 32 columns for wide rows: 79 million lines, but 2350 us: a quarter of the bytes in flight for each index fetched.)
+// Narrow rows are added up by batches (BY_BATCH).  R-MAT graphs, both directions, us, a chain per row / by batches: 1.5e5 rows, 3 edges: F = 16
+// 49.5/44.3, F = 32 53.7/52.1, bf16 F = 64 76.8/71.1;  5e5 rows, 8 edges: 117/112, 133/133, 188/183 (all loads of a step are asked for before the
+// first is waited for: with the additions among them F = 32 took 66 us).
 constexpr int SLAB_BATCH = 16;
 // (offsets are from a slab's first column: 2^22 rows of 1 KB, 4 GiB, leave room above the last row's)
 constexpr uint32_t SLAB_NOWHERE = 0xFFFFFE00u;             // (a lane's bytes within the slab, at most 240, are added to it)
@@ -657,28 +660,52 @@ template <typename XT, int G> struct Slab {
         col = (int)slab * COLS + VW * t;
         colx = col < F ? 16u * (uint32_t)t : 0u;           // (a lane without columns reads what its first one does)
     }
+    // Narrow rows are added up by batches: four rows first, those sums in turn, a batch's sum to acc.  So a row of 100 edges has the rounding
+    // errors of four chains of 25 (the sums of narrow rows in the general kernel; one chain has 1.8 to 3 times as much).
+    static constexpr bool BY_BATCH = G < 16;
+    // acc (+)= the rows of the edges N0, N0 + 1, ... of a batch (by batches: = with the first of them).
     template <int N0, int... U> __device__ __forceinline__ void step(const uint32_t (&off)[Q], float (&acc)[VW], std::integer_sequence<int, U...>) const {
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        u32x4 v[sizeof...(U)];
+        constexpr int N = (int)sizeof...(U);
+        static_assert(N % 4 == 0, "four at a time");
+        u32x4 v[N];
         ((v[U] = __builtin_amdgcn_raw_buffer_load_b128(x, (int)(group_lane<G, (N0 + U) % G>(off[(N0 + U) / G]) + colx), 0, 0)), ...);
+        __builtin_amdgcn_sched_barrier(0);                 // all of them in flight before the first is waited for
+        auto column = [&](int u, int c) {                  // of edge u: column c of the lane's
+            if constexpr (sizeof(XT) == 4) return __uint_as_float(v[u][c]);
+            else return __uint_as_float(c % 2 ? v[u][c / 2] & 0xFFFF0000u : v[u][c / 2] << 16);
+        };
+        if constexpr (BY_BATCH) {
 #pragma unroll
-        for (int u = 0; u < (int)sizeof...(U); ++u)
+            for (int u = 0; u < N; u += 4)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if constexpr (sizeof(XT) == 4) {
-                    acc[q] += __uint_as_float(v[u][q]);
-                } else {
-                    acc[2 * q] += __uint_as_float(v[u][q] << 16);
-                    acc[2 * q + 1] += __uint_as_float(v[u][q] & 0xFFFF0000u);
+                for (int c = 0; c < VW; ++c) {
+                    const float four = (column(u, c) + column(u + 1, c)) + (column(u + 2, c) + column(u + 3, c));
+                    acc[c] = N0 + u ? acc[c] + four : four;
                 }
-            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+#pragma unroll
+                for (int c = 0; c < VW; ++c) acc[c] += column(u, c);
+        }
+    }
+    template <int N0> __device__ __forceinline__ void steps(const uint32_t (&off)[Q], int cnt, float (&acc)[VW]) const {
+        if (cnt > N0 + 4) step<N0>(off, acc, std::make_integer_sequence<int, 8>());
+        else step<N0>(off, acc, std::make_integer_sequence<int, 4>());
     }
     // The first cnt edges of a batch (cnt: the same in every group; a group with fewer has offsets nowhere).
     __device__ __forceinline__ void gather(const uint32_t (&off)[Q], int cnt, float (&acc)[VW]) const {
-        if (cnt > 4) step<0>(off, acc, std::make_integer_sequence<int, 8>());
-        else step<0>(off, acc, std::make_integer_sequence<int, 4>());
-        if (cnt > 12) step<8>(off, acc, std::make_integer_sequence<int, 8>());
-        else if (cnt > 8) step<8>(off, acc, std::make_integer_sequence<int, 4>());
+        if constexpr (BY_BATCH) {
+            float sum[VW];
+            steps<0>(off, cnt, sum);
+            if (cnt > 8) steps<8>(off, cnt, sum);
+#pragma unroll
+            for (int c = 0; c < VW; ++c) acc[c] += sum[c];
+        } else {
+            steps<0>(off, cnt, acc);
+            if (cnt > 8) steps<8>(off, cnt, acc);
+        }
     }
     // Indices of the edges k .. k + SLAB_BATCH - 1 of a run that ends at `end` (edge `some` exists and is read where there are none), and
     // the offsets of their rows.
@@ -823,7 +850,7 @@ __device__ __forceinline__ void spmm_slab_rows_kernel_body(unsigned gx, const in
         k = nk;
     }
 }
-template <typename XT, int G> constexpr int SLAB_WGS = sizeof(XT) == 2 || G == 4 ? 5 : 6;       // (more registers spill)
+template <typename XT, int G> constexpr int SLAB_WGS = sizeof(XT) == 2 || G < 16 ? 5 : 6;       // (more registers spill)
 template <typename XT, int G>
 __global__ __launch_bounds__(256, (SLAB_WGS<XT, G>)) void spmm_slab_rows_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx, int64_t n_rows,
                                                                 int64_t long_thr, const XT* __restrict__ X, int64_t ldx, uint32_t x_bytes,

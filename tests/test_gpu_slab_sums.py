@@ -100,3 +100,24 @@ def test_operand_of_four_gib(lib, n):
     _check(g, part, src, dst, n, 256, torch.float32, 256)
     part.destroy()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("F,bf16", [(16, False), (32, False), (32, True), (64, True)])
+def test_sums_are_as_accurate_as_four_chains(F, bf16):
+    """Narrow rows of 100 edges: the rounding errors are those of chains of a quarter of a row at most (one chain has 1.8 to 3 times as much)."""
+    import paper_2602_01872_amd as g
+    print(f"[case] accuracy of slab sums F={F} bf16={bf16}", flush=True)
+    n, deg = 1 << 17, 100
+    gen = torch.Generator(device=DEV).manual_seed(F)
+    s, d = torch.randint(n, (n * deg,), generator=gen, device=DEV), torch.arange(n, device=DEV).repeat_interleave(deg)
+    part = g.grp_partition_from_local_coo(s, d, n)
+    col = torch.from_numpy(part.array("col")).to(DEV).long().view(n, deg)
+    for x in (torch.randn(n, F, generator=gen, device=DEV), torch.rand(n, F, generator=gen, device=DEV) + 0.1):
+        x = x.to(torch.bfloat16) if bf16 else x
+        y, want, chain = torch.empty(n, F, device=DEV), torch.zeros(n, F, dtype=torch.float64, device=DEV), torch.zeros(4, n, F, device=DEV)
+        g.grp_spmm(part, False, g.SCALE_NONE, False, F, x, F, g.DTYPE_BF16 if bf16 else g.DTYPE_FP32, y, F)
+        for e in range(deg):
+            want += x[col[:, e]].double()
+            chain[e % 4] += x[col[:, e]].float()
+        four = (chain[0] + chain[1]) + (chain[2] + chain[3])
+        assert float((y - want).norm()) <= 1.1 * float((four - want).norm())
