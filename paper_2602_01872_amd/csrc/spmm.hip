@@ -989,7 +989,14 @@ static void launch_one(const SpmmArgs& a, const SpmmEpilogue& ep, hipStream_t st
             }
             // SLAB_MANY rows: below, the workgroups of SLAB_ROWS rows leave the GPU idle (1.5e4 .. 1e5 rows, 15 edges a row: 33 against 18 us at
             // F = 64 and 2e4 rows, 64 and 50 at 4e4, 65 and 64 at 1e5, 81 and 83 at 1.5e5)
-            if (a.n_rows >= SLAB_MANY && slabs * row_blocks < ((int64_t)1 << 24)) {
+            // Dealing rows by length pays where their lengths differ (long rows, as far as the host knows them, hold a sixteenth of the edges)
+            // or where they are long; short rows of like lengths are done faster a whole row at a time, but for those of four lanes.  Rows / slabs,
+            // both directions, 3e5 rows, us.  Skewed (R-MAT), 5 edges a row: F = 32 130/78, 128 233/208, 256 445/434; uniform: F = 32 74/79, 64
+            // 128/141, 256 484/551, 12 edges: 145/150, 273/286, 1095/1120, 40 edges (2.6e5 rows, one direction): 175/159, 366/366; F = 16: 3 edges
+            // 60/47, 5 edges 66/66, 8 edges 83/91; bf16, F = 128: 174/188, 12 edges 298/325, 40 edges 384/384.
+            const bool uneven = split && 16 * ((int64_t)lr->n_long * SPMM_LONG_ROW + (int64_t)(lr->n_chunks - lr->n_long) * SPMM_CHUNK) >= a.nnz;
+            const bool deal = uneven || a.nnz >= 32 * a.n_rows || (SG == 4 && a.nnz <= 5 * a.n_rows);
+            if (deal && a.n_rows >= SLAB_MANY && slabs * row_blocks < ((int64_t)1 << 24)) {
                 launch(spmm_slab_rows_kernel<XT, SG>, spmm_slab_rows_kernel_op<XT, SG>(), dim3((unsigned)(slabs * row_blocks)), st, a.ptr, a.idx,
                        a.n_rows, thr, (const XT*)a.X, a.ldx, (uint32_t)x_bytes, ep, (uint32_t)row_blocks, n_chunks,
                        n_chunks ? lr->chunk_begin : nullptr, n_chunks ? lr->chunk_end : nullptr, a.partials, ld_part);

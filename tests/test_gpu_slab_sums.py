@@ -102,6 +102,36 @@ def test_operand_of_four_gib(lib, n):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("n", [1 << 22, (1 << 22) + 1])
+def test_short_rows_over_an_operand_of_four_gib(lib, n):
+    """The same sizes with rows so unequal (a long row of a tenth of the edges) that the short ones go by slabs, and by the general kernel a
+    row above."""
+    g = lib
+    gen = torch.Generator().manual_seed(n)
+    src = torch.cat([torch.randint(n, (100_000,), generator=gen), torch.arange(n - 12_000, n), torch.arange(n - 64, n)])
+    dst = torch.cat([torch.randint(n, (100_000,), generator=gen), torch.full((12_000,), 5), torch.arange(n - 64, n).flip(0)])
+    src, dst = src.to(DEV), dst.to(DEV)
+    part = g.grp_partition_from_local_coo(src, dst, n)
+    _check(g, part, src, dst, n, 256, torch.float32, 256)
+    part.destroy()
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("deg", [0, 3, 6, 31, 32])
+def test_rows_of_like_lengths(lib, deg):
+    """Both sides of the rule that leaves short rows of like lengths to the general kernel, and rows that are all empty but one."""
+    g = lib
+    n = MANY + 3
+    gen = torch.Generator().manual_seed(deg)
+    dst = torch.arange(n).repeat_interleave(deg) if deg else torch.full((9,), n - 1)
+    src = torch.randint(n, (dst.numel(),), generator=gen)
+    src, dst = src.to(DEV), dst.to(DEV)
+    part = g.grp_partition_from_local_coo(src, dst, n)
+    for dtype, F in ((torch.float32, 16), (torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 32), (torch.bfloat16, 64)):
+        _check(g, part, src, dst, n, F, dtype, F)
+    part.destroy()
+
+
 @pytest.mark.parametrize("F,bf16", [(16, False), (32, False), (32, True), (64, True)])
 def test_sums_are_as_accurate_as_four_chains(F, bf16):
     """Narrow rows of 100 edges: the rounding errors are those of chains of a quarter of a row at most (one chain has 1.8 to 3 times as much)."""
