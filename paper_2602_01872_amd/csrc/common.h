@@ -292,8 +292,8 @@ static inline int64_t round_up(int64_t a, int64_t b) { return cdiv(a, b) * b; }
 struct SpmmArgs {
     const int64_t* ptr = nullptr;   // [n_rows+1]
     const int32_t* idx = nullptr;   // [nnz]
-    int64_t nnz = 0;                // only used for the profiler's byte count
-    int64_t n_src = 0;              // rows of X (0 = n_rows); profiler only
+    int64_t nnz = 0;                // (with n_rows, what chooses between kernels)
+    int64_t n_src = 0;              // rows of X, above every idx (0 = n_rows): some kernels read rows beyond it as zeros
     int64_t n_rows = 0;
     int32_t F = 0;
     const void* X = nullptr;

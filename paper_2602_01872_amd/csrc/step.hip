@@ -1,8 +1,7 @@
 // One isolated train step on one partition: (sampling,) forward, loss, backward, coverage
 // statistics.  Host-side orchestration of the kernels in sampler.hip / spmm.hip / gemm.hip /
 // elementwise.hip on one stream, with every intermediate carved out of the caller's
-// workspace (no allocation; full-graph mode never synchronises the stream, mini-batch mode
-// does once per layer above the input layer to learn the sampled block sizes).
+// workspace (no allocation and no synchronisation: the sizes of sampled blocks stay on the device).
 //
 // Every layer is a bipartite block (common.h): in full-graph mode all layers share the
 // partition's CSR/CSC, in mini-batch mode each layer has its sampled block.  Per GraphSAGE
