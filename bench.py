@@ -368,18 +368,18 @@ def run_evidence_workload(args, g, synth, torch, dev):
             torch.cuda.synchronize()
             return tr, first, (time.perf_counter() - t0) / epochs
         tr, first, dt_one = timed_epochs(1)
-        tr, first, dt_threads = timed_epochs(4)              # four host threads, each with its stream and workspace
+        tr, first, dt_lanes = timed_epochs(4)                # the steps of four partitions in merged launches
         losses_eager = tr.losses()
-        tr, first, dt = timed_epochs(8, graphs=True)         # one host thread replaying captured steps on eight streams
+        tr, first, dt = timed_epochs(8, graphs=True)         # of all eight, captured
         assert tr.losses() == losses_eager, "the captured steps must reproduce the uncaptured ones bit for bit"
         used = sum(int(g.read_stats(h)["nnz_used"].sum()) for h in tr.history[first:]) / epochs
         out.update(metric="sampled edges/s over one mini-batch epoch of all 8 partitions (fwd+bwd, aggregate, Adam)",
                    unit="edges/s", value=used / dt, ms_per_step=dt * 1e3, dtype="f32", steps=epochs,
                    config={"workload": f"c2-minibatch-epoch: SAGE-mean-3 {dims}, fanouts (15,10,5), 1024 seeds per batch, "
                                        f"8 partitions of the R-MAT 2.4M-node / 62M-edge graph, {sum(tr.n_train)} training nodes",
-                           "ms_per_epoch": dt * 1e3, "launch": "captured steps (HIP graphs) replayed on 8 streams by one host thread",
-                           "ms_per_epoch_uncaptured_one_host_thread": dt_one * 1e3,
-                           "ms_per_epoch_uncaptured_four_host_threads": dt_threads * 1e3,
+                           "ms_per_epoch": dt * 1e3, "launch": "the steps of 8 partitions in merged launches, captured in one HIP graph",
+                           "ms_per_epoch_uncaptured_one_lane": dt_one * 1e3,
+                           "ms_per_epoch_uncaptured_four_lanes": dt_lanes * 1e3,
                            "iterations_per_epoch": tr.iters,
                            "train_steps_per_epoch": tr.iters * K_PARTS, "sampled_edges_per_epoch": used,
                            "losses_first_last": [tr.losses()[0], tr.losses()[-1]]},
@@ -545,7 +545,7 @@ def run_evidence_workload(args, g, synth, torch, dev):
     dt, dt_med = _timed_steps(torch, fn, args.warmup, args.steps)
     dt_eager = dt
     if wl == "c3-step":
-        # a chain of ~65 small launches: the host's launch cost bounds the uncaptured step, so the step is also
+        # a chain of 36 small launches: the host's launch cost bounds the uncaptured step, so the step is also
         # captured once in a HIP graph and the replays are timed (the same work: nothing in the graph depends on
         # the captured batch; a trainer rewrites the seed buffer and the device-resident batch id between replays)
         side = torch.cuda.Stream()

@@ -134,6 +134,28 @@ def test_trainer_keeps_one_workspace_for_steps_that_are_not_merged():
     torch.cuda.synchronize()
 
 
+def test_epochs_of_very_unequal_partitions():
+    """Partitions run out of seeds one after another, so most groups have a short batch or none among them: merged and captured as one by one."""
+    import paper_2602_01872_amd as g
+    K, n, dims = 5, 1500, [12, 16, 16, 4]
+    s, d = _graph(n, 9 * n, 6)
+    part = g.grp_partition_from_local_coo(s, d, n)
+    x, y, theta = (t.to(DEV) for t in make_inputs(n, dims, "sage", 7))
+    masks = [(torch.arange(n, device=DEV) < count).to(torch.uint8) for count in (37, 1000, 64, 0, 500)]
+    model = g.model_desc(g.ARCH_SAGE_MEAN, dims)
+    runs = []
+    for lanes, graphs in ((1, False), (4, False), (4, True), (5, True)):
+        tr = g.MiniBatchTrainer([part] * K, model, [x] * K, [y] * K, masks, theta, g.EST_SHRINKAGE, K, 64, (4, 3, 5), 21,
+                                g.optimizer_desc(g.OPT_ADAM, lr=0.003), dropout_rate=0.3, dropout_seed=2, lanes=lanes, graphs=graphs)
+        for _ in range(2):
+            tr.run_epoch()
+        torch.cuda.synchronize()
+        runs.append((tr.theta.clone(), tr.losses()))
+    assert len(runs[0][1]) == 2 * 16
+    for theta_, losses in runs[1:]:
+        assert torch.equal(theta_, runs[0][0]) and losses == runs[0][1]
+
+
 def _compare(g, parts, model, opts, xs, ys, masks, theta, P):
     K = len(parts)
     size = max(g.grp_step_workspace_bytes(p, model, o) for p, o in zip(parts, opts))

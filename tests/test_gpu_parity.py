@@ -937,10 +937,9 @@ def test_minibatch_phase_parallel_loop_matches_oracle(g, M):
 
 @pytest.mark.gpu
 def test_minibatch_steps_driven_by_several_host_threads_give_the_same_bits(g):
-    """The steps of a phase on three host threads, each with its stream and workspace (one thread takes two
-    of the four steps), and as captured graphs replayed on three streams by one thread: same theta and losses
-    as the one-thread loop, bit for bit."""
-    _note("mini-batch loop on several host threads")
+    """Three of the four steps of a phase in merged launches, each with its workspace, and then the fourth; the same as captured
+    graphs: same theta and losses as one step after another, bit for bit."""
+    _note("mini-batch loop in several lanes")
     N, E, K, M = 2000, 24000, 4, 4
     s, d = synth.rmat_graph(11, E, seed=81, n_nodes=N)
     dims = [12, 24, 24, 4]
@@ -955,8 +954,8 @@ def test_minibatch_steps_driven_by_several_host_threads_give_the_same_bits(g):
     model = g.model_desc(g.ARCH_SAGE_MEAN, dims)
     runs = []
     for lanes, graphs in ((1, False), (3, False), (3, True)):
-        # graphs: every partition's full-batch step is captured once and replayed with the seeds and the batch
-        # id rewritten in device memory (the batches shorter than 100 seeds run uncaptured)
+        # graphs: a group's full-batch steps are captured once and replayed with the seeds and the batch
+        # id rewritten in device memory (groups with a batch shorter than 100 seeds run uncaptured)
         tr = g.MiniBatchTrainer(parts, model, xs, ys, masks, theta0.to(DEV), g.EST_SHRINKAGE, M, 100, (4, 3, 5), 21,
                                 g.optimizer_desc(g.OPT_ADAM, lr=0.003), dropout_rate=0.3, dropout_seed=2, lanes=lanes,
                                 graphs=graphs)
