@@ -402,13 +402,12 @@ struct GemmTNArgs {
 };
 grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st);
 
-// out[N] = column sums of A[M x N]; scratch holds the per-block partials.
+// out[N] = column sums of A[M x N], every row multiplied by rowmul[m] first (may be null); scratch holds the per-block partials.
 size_t colsum_workspace_bytes(int64_t M, int32_t N);
-grp_status launch_colsum(const float* A, int64_t M, int32_t N, int64_t lda, float* out,
-                         void* scratch, hipStream_t st);
-// Same with every row multiplied by rowmul[m] first (rowmul may be null).
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul,
                                 float* out, void* scratch, hipStream_t st);
+// out[N] = sums over the rows of part[blocks x N].
+void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st);
 // Weight re-packing jobs of one step (at most four per layer), run by a single launch.
 struct PackJob {
     const float* in;

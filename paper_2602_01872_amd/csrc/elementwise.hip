@@ -371,6 +371,10 @@ struct colsum_partial_vec_kernel_op {
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { colsum_partial_vec_kernel_body(gx, a...); }
 };
 
+void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st) {
+    launch(colsum_final_kernel, colsum_final_kernel_op(), dim3((unsigned)cdiv(N, 8)), st, part, blocks, N, out);
+}
+
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul, float* out,
                                 void* scratch, hipStream_t st) {
     const int64_t blocks = cdiv(M > 0 ? M : 1, COLSUM_ROWS);
@@ -382,13 +386,9 @@ grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t ld
         launch_alone(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
                            (float*)scratch);
     GRP_LAUNCH_CHECK();
-    launch(colsum_final_kernel, colsum_final_kernel_op(), dim3((unsigned)cdiv(N, 8)), st, (const float*)scratch, blocks, N, out);
+    launch_colsum_final((const float*)scratch, blocks, N, out, st);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
-}
-
-grp_status launch_colsum(const float* A, int64_t M, int32_t N, int64_t lda, float* out, void* scratch, hipStream_t st) {
-    return launch_colsum_scaled(A, M, N, lda, nullptr, out, scratch, st);
 }
 
 // ------------------------------------------------------------------ degree scales

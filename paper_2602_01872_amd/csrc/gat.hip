@@ -41,6 +41,20 @@ __device__ __forceinline__ float group_max(float x) {
     for (int o = G / 2; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, G));
     return x;
 }
+// A group's number in the workgroup, and what its lane k holds.  A group of a whole wavefront has both in scalar registers: a row's
+// bounds, its scalars and the addresses of the rows it gathers take no vector registers then, of which the walks have few
+// to spare (3e5 rows of 256 columns, 3.25 edges a row, us of FWD / DST / SRC: 291/229/315, registers 54/62/68 -> 276/225/282, 36/54/52).
+template <int G>
+__device__ __forceinline__ int group_id() {
+    const int g = (int)threadIdx.x / G;
+    return G == 64 ? __builtin_amdgcn_readfirstlane(g) : g;
+}
+template <int G>
+__device__ __forceinline__ int held_by(int x, int k) {
+    return G == 64 ? __builtin_amdgcn_readlane(x, k) : __shfl(x, k, G);
+}
+template <int G>
+__device__ __forceinline__ float held_by(float x, int k) { return __int_as_float(held_by<G>(__float_as_int(x), k)); }
 __device__ __forceinline__ float dot4(const float4& a, const float4& b) {
     return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
 }
@@ -55,15 +69,18 @@ __global__ __launch_bounds__(256) void gat_extract_pq_kernel(const float* __rest
 
 // Row statistics of the attention softmax: rowstat[v] = (m_v, Z_v) = (max_u e_uv, sum_u exp(e_uv - m_v)),
 // self term included.  Scalars only (p and q sit in L2).  The first n_long workgroups each take one
-// row longer than long_thr edges with all 256 threads (partial results combined through LDS in a
-// fixed order); the others give 16 lanes to a row and skip the long ones.
-__global__ __launch_bounds__(256) void gat_stats_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
+// row longer than long_thr edges with all their threads (partial results combined through LDS in a
+// fixed order): the launch lasts as long as the longest row, a chain of gathers.  The others give G lanes to a row and skip the long ones.
+// G: 4 up to 16 edges a row on average (four gathers a lane), else 16.
+constexpr int GAT_STATS_THREADS = 1024;
+template <int G>
+__global__ __launch_bounds__(GAT_STATS_THREADS) void gat_stats_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ idx,
                                                         int64_t n, const float2* __restrict__ pq,
                                                         float2* __restrict__ rowstat, const int32_t* __restrict__ long_row,
                                                         int n_long, int64_t long_thr) {
-    constexpr int G = 16;
+    constexpr int T = GAT_STATS_THREADS, WAVES = T / 64;
     if ((int)blockIdx.x < n_long) {
-        __shared__ float red[4];
+        __shared__ float red[WAVES];
         const int64_t v = long_row[blockIdx.x];
         const int64_t b = ptr[v], e = ptr[v + 1];
         const float2 pqv = pq[v];
@@ -71,28 +88,34 @@ __global__ __launch_bounds__(256) void gat_stats_kernel(const int64_t* __restric
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         auto score = [&](int64_t k) { return k < e ? leaky(pq[idx[k]].x + pqv.y) : -INFINITY; };
         float mx = es;
-        for (int64_t k = b + tid; k < e; k += 4 * 256) {
-            const float s0 = score(k), s1 = score(k + 256), s2 = score(k + 512), s3 = score(k + 768);
+        for (int64_t k = b + tid; k < e; k += 4 * T) {
+            const float s0 = score(k), s1 = score(k + T), s2 = score(k + 2 * T), s3 = score(k + 3 * T);
             mx = fmaxf(fmaxf(mx, fmaxf(s0, s1)), fmaxf(s2, s3));
         }
         mx = group_max<64>(mx);
         if (lane == 0) red[wave] = mx;
         __syncthreads();
-        mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) mx = fmaxf(mx, red[w]);
         __syncthreads();
         float sum = 0.f;
-        for (int64_t k = b + tid; k < e; k += 4 * 256) {
-            const float s0 = score(k), s1 = score(k + 256), s2 = score(k + 512), s3 = score(k + 768);
+        for (int64_t k = b + tid; k < e; k += 4 * T) {
+            const float s0 = score(k), s1 = score(k + T), s2 = score(k + 2 * T), s3 = score(k + 3 * T);
             sum += __expf(s0 - mx); sum += __expf(s1 - mx); sum += __expf(s2 - mx); sum += __expf(s3 - mx);
         }
         sum = group_sum<64>(sum);
         if (lane == 0) red[wave] = sum;
         __syncthreads();
-        if (tid == 0) rowstat[v] = make_float2(mx, ((red[0] + red[1]) + (red[2] + red[3])) + __expf(es - mx));
+        if (tid == 0) {
+            float all = 0.f;
+#pragma unroll
+            for (int w = 0; w < WAVES; w += 4) all += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
+            rowstat[v] = make_float2(mx, all + __expf(es - mx));
+        }
         return;
     }
     const int t = threadIdx.x % G;
-    const int64_t v = ((int64_t)blockIdx.x - n_long) * (256 / G) + threadIdx.x / G;
+    const int64_t v = ((int64_t)blockIdx.x - n_long) * (T / G) + threadIdx.x / G;
     if (v >= n) return;               // whole groups leave together
     const int64_t b = ptr[v], e = ptr[v + 1];
     if (e - b > long_thr) return;     // done by one of the first workgroups
@@ -100,16 +123,17 @@ __global__ __launch_bounds__(256) void gat_stats_kernel(const int64_t* __restric
     const float es = leaky(pqv.x + pqv.y);
     // four independent index -> score gathers per lane and trip
     auto score = [&](int64_t k) { return k < e ? leaky(pq[idx[k]].x + pqv.y) : -INFINITY; };
-    float mx = es;
-    for (int64_t k = b + t; k < e; k += 4 * G) {
+    const float f0 = score(b + t), f1 = score(b + t + G), f2 = score(b + t + 2 * G), f3 = score(b + t + 3 * G);      // the first trip's are kept
+    float mx = fmaxf(fmaxf(fmaxf(es, f0), fmaxf(f1, f2)), f3);
+    for (int64_t k = b + 4 * G + t; k < e; k += 4 * G) {
         const float s0 = score(k), s1 = score(k + G), s2 = score(k + 2 * G), s3 = score(k + 3 * G);
         mx = fmaxf(fmaxf(mx, fmaxf(s0, s1)), fmaxf(s2, s3));
     }
     mx = group_max<G>(mx);
-    float sum = 0.f;
-    for (int64_t k = b + t; k < e; k += 4 * G) {
+    float sum = (__expf(f0 - mx) + __expf(f1 - mx)) + (__expf(f2 - mx) + __expf(f3 - mx));
+    for (int64_t k = b + 4 * G + t; k < e; k += 4 * G) {
         const float s0 = score(k), s1 = score(k + G), s2 = score(k + 2 * G), s3 = score(k + 3 * G);
-        sum += __expf(s0 - mx); sum += __expf(s1 - mx); sum += __expf(s2 - mx); sum += __expf(s3 - mx);
+        sum += (__expf(s0 - mx) + __expf(s1 - mx)) + (__expf(s2 - mx) + __expf(s3 - mx));
     }
     sum = group_sum<G>(sum) + __expf(es - mx);
     if (t == 0) rowstat[v] = make_float2(mx, sum);
@@ -119,7 +143,7 @@ __global__ __launch_bounds__(256) void gat_stats_kernel(const int64_t* __restric
 // FWD and DST, of the CSC for SRC) and accumulates a feature row `acc` and a scalar `scal`:
 //   FWD  acc += alpha_uv T[u,:]                                           (row v, edges u -> v)
 //   DST  scal += alpha_uv (dOut_v . T[u,:] - c_v) LeakyReLU'(pre_uv)      (row v; acc unused)
-//        (the slope LeakyReLU' here less that of the self edge: see gat_walk_edges)
+//        (the slope LeakyReLU' here less that of the self edge, so that only some of the edges are looked at: see gat_walk_edges)
 //   SRC  acc += alpha_uv dOut[v,:];  scal += alpha_uv (T_u . dOut[v,:] - c_v) LeakyReLU'(pre_uv)   (row u, edges u -> v)
 // Short rows are walked by one group of G lanes.  Rows longer than `long_thr` edges use the
 // partition's split schedule: the first workgroups of the launch each walk one chunk (their
@@ -140,8 +164,9 @@ struct GatWalk {
     float* Hout;      int64_t ldh;       // FWD: output; DST: the layer's stored output
     float hout_scale;                    // DST: out_v = hout_scale * Hout[v,:] where dOut is non-zero (undoes dropout)
     const float* dOut; int64_t ldd;
-    float* cvec;                         // DST: written; SRC: read
-    float2* dqs;                         // DST: written (dq, self-term score gradient); SRC: read
+    float4* dst;                         // (q_v, m_v, 1 / Z_v, c_v), what an edge needs of its destination: DST: written; SRC: read
+    float* dq;                           // without the self edge's term.  DST: written; SRC: read
+    float* colsum;                       // DST: [workgroups of rows x F] partial column sums of dOut
     float* dTx;                          // SRC: output rows [dT | 0 | dp | dq | 0 0]
     int64_t long_thr;
     int n_chunks;
@@ -153,25 +178,28 @@ struct GatWalk {
 template <int G, int NJ>
 struct GatRow {                          // per-row constants held by every lane of the group
     float4 vec[NJ];                      // DST: dOut[v,:]; SRC: T[u,:]
-    float q, mx, inv, c, p;
+    float p;
+    float q, mx, inv, c;                 // (SRC: not held)
 };
 
 template <int PASS, int G, int NJ>
-__device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t, const bool (&live)[NJ], GatRow<G, NJ>& R,
-                                              float& dself) {
-    const float2 pqr = A.pq[r];
-    R.p = pqr.x; R.q = pqr.y;
-    R.mx = 0.f; R.inv = 0.f; R.c = 0.f;
-    if (PASS != GAT_SRC) {
-        const float2 st = A.rowstat[r];
-        R.mx = st.x; R.inv = 1.f / st.y;
+__device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t, const bool (&live)[NJ], GatRow<G, NJ>& R) {
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    R.p = A.pq[r].x;
+    if (PASS == GAT_SRC) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) R.vec[j] = live[j] ? ld4(A.Tx + r * A.ldx + 4 * (t + G * j)) : zero;
+        return;
     }
-    dself = 0.f;
+    const float2 st = A.rowstat[r];
+    R.q = A.pq[r].y;
+    R.mx = st.x; R.inv = 1.f / st.y;
+    R.c = 0.f;
     if (PASS == GAT_DST) {
-        float cpart = 0.f, spart = 0.f;
+        float cpart = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            R.vec[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            R.vec[j] = zero;
             if (!live[j]) continue;
             const int col = 4 * (t + G * j);
             R.vec[j] = ld4(A.dOut + r * A.ldd + col);
@@ -182,48 +210,67 @@ __device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t
             const float hs = A.hout_scale;
             cpart += R.vec[j].x * (h.x * hs - bb[0]) + R.vec[j].y * (h.y * hs - bb[1]) + R.vec[j].z * (h.z * hs - bb[2]) +
                      R.vec[j].w * (h.w * hs - bb[3]);
-            spart += dot4(R.vec[j], ld4(A.Tx + r * A.ldx + col));
         }
         R.c = group_sum<G>(cpart);        // c_v = dOut_v . (out_v - b) = sum_u alpha_uv (dOut_v . t_u)
-        dself = group_sum<G>(spart);      // dOut_v . t_v
-    }
-    if (PASS == GAT_SRC) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            R.vec[j] = live[j] ? ld4(A.Tx + r * A.ldx + 4 * (t + G * j)) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 }
 
 template <int PASS, int G, int NJ>
-__device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G, NJ>& R, int64_t b, int64_t e, int t,
+__device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G, NJ>& R, int64_t b, int64_t e, int first, int t,
                                                const bool (&live)[NJ], float4 (&acc)[NJ], float& scal) {
     // DST adds up alpha_uv (dOut_v . t_u - c_v) LeakyReLU'(pre_uv) over a row.  Without the last factor that sum is zero, so the
     // self edge's slope is taken off every factor: what is left are the edges on the other side of the kink, instead of
-    // terms of both signs that cancel to rounding noise (the self edge itself then adds nothing).
+    // terms of both signs that cancel to rounding noise (the self edge itself then adds nothing).  The others add nothing and their rows
+    // of T are not fetched (but where c_v is not finite: 0 times that is not zero).  3e5 rows of 256 columns, 3.25
+    // skewed edges a row, the bias gradient's column sums included: 308 + 45 -> 225 us.
     const float slope0 = PASS == GAT_DST ? leaky_d(R.p + R.q) : 0.f;
     for (int64_t base = b; base < e; base += G) {
         const int cnt = (int)(e - base < G ? e - base : G);
         int mine = 0;
-        float mya = 0.f, mw = 0.f, mc = R.c;              // alpha, alpha * LeakyReLU', c of the edge's destination
+        float mya = 0.f, mw = 0.f, mc = PASS == GAT_SRC ? 0.f : R.c;              // alpha, alpha * LeakyReLU', c of the edge's destination
         if (t < cnt) {
-            mine = A.idx[base + t];
+            mine = PASS == GAT_DST && base == b ? first : A.idx[base + t];      // (asked for before the row itself)
             float pre, mx, inv;
             if (PASS == GAT_SRC) {
-                const float2 sv = A.rowstat[mine];
-                pre = R.p + A.pq[mine].y; mx = sv.x; inv = 1.f / sv.y;
-                mc = A.cvec[mine];
+                const float4 to = A.dst[mine];
+                pre = R.p + to.x; mx = to.y; inv = to.z; mc = to.w;
             } else {
                 pre = A.pq[mine].x + R.q; mx = R.mx; inv = R.inv;
             }
             mya = __expf(leaky(pre) - mx) * inv;
             mw = mya * (leaky_d(pre) - slope0);
         }
+        if constexpr (PASS == GAT_DST) {
+            const bool all = !(fabsf(R.c) < INFINITY);
+            unsigned long long who = __ballot(t < cnt && (all || mw != 0.f));      // (NaN is not 0)
+            if (G < 64) who = (who >> ((threadIdx.x & 63) / G * G)) & ((1ull << (G & 63)) - 1ull);
+            while (who) {                                  // the edges that are walked, two at a time
+                const int k0 = __ffsll(who) - 1;
+                who &= who - 1;
+                const bool two = who != 0;
+                const int k1 = two ? __ffsll(who) - 1 : k0;
+                who &= who - 1;
+                const int64_t c0 = held_by<G>(mine, k0), c1 = held_by<G>(mine, k1);
+                float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    if (!live[j]) continue;
+                    const float4 v0 = ld4(A.Tx + c0 * A.ldx + 4 * (t + G * j)), v1 = ld4(A.Tx + c1 * A.ldx + 4 * (t + G * j));
+                    d0 += dot4(R.vec[j], v0); d1 += dot4(R.vec[j], v1);
+                }
+                d0 = group_sum<G>(d0); d1 = group_sum<G>(d1);
+                scal += held_by<G>(mw, k0) * (d0 - R.c);
+                const float w1 = held_by<G>(mw, k1);
+                if (two) scal += w1 * (d1 - R.c);
+            }
+            continue;
+        }
         for (int k = 0; k < cnt; k += 4) {
             const bool p1 = k + 1 < cnt, p2 = k + 2 < cnt, p3 = k + 3 < cnt;
             const int k1 = p1 ? k + 1 : k, k2 = p2 ? k + 2 : k, k3 = p3 ? k + 3 : k;
-            const int64_t c0 = __shfl(mine, k, G), c1 = __shfl(mine, k1, G), c2 = __shfl(mine, k2, G), c3 = __shfl(mine, k3, G);
-            const float a0 = __shfl(mya, k, G), a1 = p1 ? __shfl(mya, k1, G) : 0.f;
-            const float a2 = p2 ? __shfl(mya, k2, G) : 0.f, a3 = p3 ? __shfl(mya, k3, G) : 0.f;
+            const int64_t c0 = held_by<G>(mine, k), c1 = held_by<G>(mine, k1), c2 = held_by<G>(mine, k2), c3 = held_by<G>(mine, k3);
+            const float a0 = held_by<G>(mya, k), a1 = p1 ? held_by<G>(mya, k1) : 0.f;
+            const float a2 = p2 ? held_by<G>(mya, k2) : 0.f, a3 = p3 ? held_by<G>(mya, k3) : 0.f;
             float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
             const float* base_ptr = PASS == GAT_SRC ? A.dOut : A.Tx;
             const int64_t ld = PASS == GAT_SRC ? A.ldd : A.ldx;
@@ -233,7 +280,7 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
                 const int col = 4 * (t + G * j);
                 const float4 v0 = ld4(base_ptr + c0 * ld + col), v1 = ld4(base_ptr + c1 * ld + col);
                 const float4 v2 = ld4(base_ptr + c2 * ld + col), v3 = ld4(base_ptr + c3 * ld + col);
-                if (PASS != GAT_DST) {
+                {
                     acc[j].x += a0 * v0.x; acc[j].y += a0 * v0.y; acc[j].z += a0 * v0.z; acc[j].w += a0 * v0.w;
                     acc[j].x += a1 * v1.x; acc[j].y += a1 * v1.y; acc[j].z += a1 * v1.z; acc[j].w += a1 * v1.w;
                     acc[j].x += a2 * v2.x; acc[j].y += a2 * v2.y; acc[j].z += a2 * v2.z; acc[j].w += a2 * v2.w;
@@ -245,9 +292,9 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
             }
             if (PASS != GAT_FWD) {
                 d0 = group_sum<G>(d0); d1 = group_sum<G>(d1); d2 = group_sum<G>(d2); d3 = group_sum<G>(d3);
-                scal += __shfl(mw, k, G) * (d0 - __shfl(mc, k, G));
-                const float w1 = __shfl(mw, k1, G), w2 = __shfl(mw, k2, G), w3 = __shfl(mw, k3, G);
-                const float e1 = __shfl(mc, k1, G), e2 = __shfl(mc, k2, G), e3 = __shfl(mc, k3, G);
+                scal += held_by<G>(mw, k) * (d0 - held_by<G>(mc, k));
+                const float w1 = held_by<G>(mw, k1), w2 = held_by<G>(mw, k2), w3 = held_by<G>(mw, k3);
+                const float e1 = held_by<G>(mc, k1), e2 = held_by<G>(mc, k2), e3 = held_by<G>(mc, k3);
                 if (p1) scal += w1 * (d1 - e1);
                 if (p2) scal += w2 * (d2 - e2);
                 if (p3) scal += w3 * (d3 - e3);
@@ -259,7 +306,7 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
 // Adds the self term and writes the row's results.
 template <int PASS, int G, int NJ>
 __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G, NJ>& R, int64_t r, int t,
-                                               const bool (&live)[NJ], float4 (&acc)[NJ], float scal, float dself) {
+                                               const bool (&live)[NJ], float4 (&acc)[NJ], float scal) {
     if (PASS == GAT_FWD) {
         const float as = __expf(leaky(R.p + R.q) - R.mx) * R.inv;
 #pragma unroll
@@ -280,28 +327,29 @@ __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G,
             *reinterpret_cast<float4*>(A.Hout + r * A.ldh + col) = make_float4(o[0], o[1], o[2], o[3]);
         }
     } else if (PASS == GAT_DST) {
-        const float pre_s = R.p + R.q;
-        const float ds_self = __expf(leaky(pre_s) - R.mx) * R.inv * (dself - R.c) * leaky_d(pre_s);
         if (t == 0) {
-            A.cvec[r] = R.c;
-            A.dqs[r] = make_float2(scal, ds_self);
+            A.dst[r] = make_float4(R.q, R.mx, R.inv, R.c);
+            A.dq[r] = scal;
         }
     } else {
-        const float2 st = A.rowstat[r], dq = A.dqs[r];
-        const float as = __expf(leaky(R.p + R.q) - st.x) / st.y;
+        const float4 to = A.dst[r];
+        const float pre = R.p + to.x, as = __expf(leaky(pre) - to.y) * to.z;
+        float own = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             if (!live[j]) continue;
             const int col = 4 * (t + G * j);
             const float4 d = ld4(A.dOut + r * A.ldd + col);
+            own += dot4(R.vec[j], d);
             float o[4] = {acc[j].x + as * d.x, acc[j].y + as * d.y, acc[j].z + as * d.z, acc[j].w + as * d.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 if (col + q >= A.F) o[q] = 0.f;
             *reinterpret_cast<float4*>(A.dTx + r * A.ldx + col) = make_float4(o[0], o[1], o[2], o[3]);
         }
+        own = as * (group_sum<G>(own) - to.w) * leaky_d(pre);      // the self edge's score gradient
         if (t == 0)
-            *reinterpret_cast<float4*>(A.dTx + r * A.ldx + ((A.F + 3) & ~3)) = make_float4(scal + dq.y, dq.x, 0.f, 0.f);
+            *reinterpret_cast<float4*>(A.dTx + r * A.ldx + ((A.F + 3) & ~3)) = make_float4(scal + own, A.dq[r], 0.f, 0.f);
     }
 }
 
@@ -311,7 +359,7 @@ __global__ __launch_bounds__(256) void gat_walk_kernel(GatWalk A) {
     constexpr int W = 4 * G * NJ;                 // padded row width held by a group
     __shared__ __attribute__((aligned(16))) float red[ROWS * (W + 4)];
     __shared__ int64_t chunk_row;
-    const int t = threadIdx.x % G, gi = threadIdx.x / G;
+    const int t = threadIdx.x % G, gi = group_id<G>();
     bool live[NJ];
     float4 acc[NJ];
 #pragma unroll
@@ -320,7 +368,7 @@ __global__ __launch_bounds__(256) void gat_walk_kernel(GatWalk A) {
         acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     GatRow<G, NJ> R;
-    float scal = 0.f, dself = 0.f;
+    float scal = 0.f;
     if ((int)blockIdx.x < A.n_chunks) {           // uniform per workgroup: one chunk of a long row
         const int64_t cb = A.chunk_begin[blockIdx.x], ce = A.chunk_end[blockIdx.x];
         if (threadIdx.x == 0) {                   // the row that owns edge cb: last r with ptr[r] <= cb
@@ -333,12 +381,13 @@ __global__ __launch_bounds__(256) void gat_walk_kernel(GatWalk A) {
         }
         __syncthreads();
         const int64_t r = chunk_row;
-        gat_row_setup<PASS, G, NJ>(A, r, t, live, R, dself);
         const int64_t per = (ce - cb + ROWS - 1) / ROWS;
         int64_t b = cb + gi * per, e = b + per;
         if (b > ce) b = ce;
         if (e > ce) e = ce;
-        gat_walk_edges<PASS, G, NJ>(A, R, b, e, t, live, acc, scal);
+        const int first = PASS == GAT_DST && b + t < e ? A.idx[b + t] : 0;
+        gat_row_setup<PASS, G, NJ>(A, r, t, live, R);
+        gat_walk_edges<PASS, G, NJ>(A, R, b, e, first, t, live, acc, scal);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) *reinterpret_cast<float4*>(&red[gi * (W + 4) + 4 * (t + G * j)]) = acc[j];
         if (t == 0) red[gi * (W + 4) + W] = scal;
@@ -354,21 +403,53 @@ __global__ __launch_bounds__(256) void gat_walk_kernel(GatWalk A) {
         }
         return;
     }
-    const int64_t r = (int64_t)(blockIdx.x - A.n_chunks) * ROWS + gi;
-    if (r >= A.n) return;                         // whole groups leave together
-    const int64_t b = A.ptr[r], e = A.ptr[r + 1];
-    if (e - b > A.long_thr) return;               // walked in chunks above, finished by the combine kernel
-    gat_row_setup<PASS, G, NJ>(A, r, t, live, R, dself);
-    gat_walk_edges<PASS, G, NJ>(A, R, b, e, t, live, acc, scal);
-    gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal, dself);
+    if constexpr (PASS == GAT_DST) {
+        // several rows a group: its column sums of dOut, which it reads anyway, stay in registers until the last
+        const int block = (int)blockIdx.x - A.n_chunks, blocks = (int)gridDim.x - A.n_chunks;
+        float4 csum[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) csum[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // (Asking for the next row while the edges of one are walked took 14 more registers and 46 us more.)
+        for (int64_t r = (int64_t)block * ROWS + gi; r < A.n; r += (int64_t)blocks * ROWS) {
+            const int64_t b = A.ptr[r], e = A.ptr[r + 1];
+            const int first = b + t < e ? A.idx[b + t] : 0;
+            gat_row_setup<PASS, G, NJ>(A, r, t, live, R);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) { csum[j].x += R.vec[j].x; csum[j].y += R.vec[j].y; csum[j].z += R.vec[j].z; csum[j].w += R.vec[j].w; }
+            if (e - b > A.long_thr) continue;     // walked in chunks above, finished by the combine kernel
+            scal = 0.f;
+            gat_walk_edges<PASS, G, NJ>(A, R, b, e, first, t, live, acc, scal);
+            gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) *reinterpret_cast<float4*>(&red[gi * (W + 4) + 4 * (t + G * j)]) = csum[j];
+        __syncthreads();
+        for (int c = threadIdx.x; c < A.F; c += 256) {
+            float sum = 0.f;
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q) sum += red[q * (W + 4) + c];
+            A.colsum[(int64_t)block * A.F + c] = sum;
+        }
+    } else {
+        const int64_t r = (int64_t)(blockIdx.x - A.n_chunks) * ROWS + gi;
+        if (r >= A.n) return;                         // whole groups leave together
+        const int64_t b = A.ptr[r], e = A.ptr[r + 1];
+        if (e - b > A.long_thr) return;               // walked in chunks above, finished by the combine kernel
+        gat_row_setup<PASS, G, NJ>(A, r, t, live, R);
+        gat_walk_edges<PASS, G, NJ>(A, R, b, e, 0, t, live, acc, scal);
+        gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal);
+    }
 }
+
+// Workgroups of rows of a DST walk: as many as run at a time (each leaves a partial row of column sums).
+constexpr int GAT_DST_BLOCKS = 2048;
 
 template <int PASS, int G, int NJ>
 __global__ __launch_bounds__(256) void gat_combine_kernel(GatWalk A, const int32_t* __restrict__ long_row,
                                                           const int32_t* __restrict__ long_first, int n_long) {
     constexpr int ROWS = 256 / G;
     const int t = threadIdx.x % G;
-    const int j0 = blockIdx.x * ROWS + threadIdx.x / G;
+    const int j0 = blockIdx.x * ROWS + group_id<G>();
     if (j0 >= n_long) return;
     const int64_t r = long_row[j0];
     const int c0 = long_first[j0], c1 = long_first[j0 + 1];
@@ -380,8 +461,8 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(GatWalk A, const int32
         acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     GatRow<G, NJ> R;
-    float scal = 0.f, dself = 0.f;
-    gat_row_setup<PASS, G, NJ>(A, r, t, live, R, dself);
+    float scal = 0.f;
+    gat_row_setup<PASS, G, NJ>(A, r, t, live, R);
     const int fpad = (A.F + 3) & ~3;
     for (int c = c0; c < c1; ++c) {
         const float* prow = A.partials + (int64_t)c * A.ld_part;
@@ -393,30 +474,40 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(GatWalk A, const int32
         }
         scal += prow[fpad];
     }
-    gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal, dself);
+    gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal);
 }
 
 // Packed weights of one layer: Wp[Fin x ldx] = wp_scale [W | 0 | W a_src | W a_dst | 0 0] (rows of the
 // product dT_ext -> dH; wp_scale = 1 / (1 - rate) when the layer's input went through dropout) and the
 // unscaled transpose Wt[ldx x ld(Fin)] (rows of the product H -> T_ext).
+// The first workgroups multiply W by the attention vectors, a row a wavefront (one thread a row: 15 us at 256 x 256).
 __global__ __launch_bounds__(256) void gat_pack_kernel(const float* __restrict__ W, const float* __restrict__ a_s,
                                                        const float* __restrict__ a_d, int fin, int fout, int fin_pad, int ldx,
                                                        float wp_scale, float* __restrict__ Wp, float* __restrict__ Wt) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int cp = (fout + 3) & ~3, score_blocks = (fin_pad + 3) / 4;
+    auto put = [&](int i, int c, float val) {
+        if (i < fin) Wp[(int64_t)i * ldx + c] = val * wp_scale;
+        Wt[(int64_t)c * fin_pad + i] = val;
+    };
+    if ((int)blockIdx.x < score_blocks) {
+        const int i = 4 * blockIdx.x + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+        if (i >= fin_pad) return;
+        float s = 0.f, d = 0.f;
+        for (int j = lane; i < fin && j < fout; j += 64) {
+            const float w = W[(int64_t)i * fout + j];
+            s = fmaf(w, a_s[j], s);
+            d = fmaf(w, a_d[j], d);
+        }
+        s = group_sum<64>(s);
+        d = group_sum<64>(d);
+        if (lane < 2) put(i, cp + lane, lane ? d : s);
+        return;
+    }
+    const int64_t e = (int64_t)(blockIdx.x - score_blocks) * 256 + threadIdx.x;
     if (e >= (int64_t)fin_pad * ldx) return;
     const int i = (int)(e / ldx), c = (int)(e % ldx);
-    const int cp = (fout + 3) & ~3;
-    float val = 0.f;
-    if (i < fin) {
-        if (c < fout) {
-            val = W[(int64_t)i * fout + c];
-        } else if (c == cp || c == cp + 1) {
-            const float* a = c == cp ? a_s : a_d;
-            for (int j = 0; j < fout; ++j) val = fmaf(W[(int64_t)i * fout + j], a[j], val);
-        }
-        Wp[(int64_t)i * ldx + c] = val * wp_scale;
-    }
-    Wt[(int64_t)c * fin_pad + i] = val;
+    if (c == cp || c == cp + 1) return;
+    put(i, c, i < fin && c < fout ? W[(int64_t)i * fout + c] : 0.f);
 }
 
 // Gradients of W, a_src, a_dst from dWx = H^T dT_ext [Fin x ldx]:
@@ -458,9 +549,9 @@ struct GatLayer {
 
 struct GatPlan {
     std::vector<GatLayer> L;
-    float *dZa, *dZb, *dTx, *cvec, *dWx, *partials;
-    float2* dqs;
-    void *tn_ws, *colsum_ws, *stats_ws;
+    float *dZa, *dZb, *dTx, *dq, *dWx, *partials, *colsum;
+    float4* dst;
+    void *tn_ws, *stats_ws;
     size_t tn_ws_bytes, total;
     unsigned char* planes = nullptr;   // the weights of the product at hand, split (GemmNNArgs::planes)
     size_t planes_bytes = 0;
@@ -475,7 +566,7 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
     const int k = m->n_layers;
     p.L.resize(k);
     int64_t off = 0, ldmax = 4, ldxmax = 8, wxmax = 1;
-    size_t tn_bytes = 0, cs_bytes = 0, pl_bytes = 0;
+    size_t tn_bytes = 0, pl_bytes = 0;
     for (int l = 0; l < k; ++l) {
         GatLayer& L = p.L[l];
         L.fin = m->dims[l]; L.fout = m->dims[l + 1];
@@ -495,21 +586,19 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
         if ((int64_t)L.fin * L.ldx > wxmax) wxmax = (int64_t)L.fin * L.ldx;
         const size_t t = gemm_tn_workspace_bytes(n, L.fin, (int32_t)L.ldx);
         if (t > tn_bytes) tn_bytes = t;
-        const size_t c = colsum_workspace_bytes(n, L.fout);
-        if (c > cs_bytes) cs_bytes = c;
         pl_bytes = std::max({pl_bytes, gemm_planes_bytes(n, (int32_t)L.ldx, L.fin), gemm_planes_bytes(n, L.fin, (int32_t)L.ldx)});
     }
     p.dZa = b.take<float>((size_t)n * ldmax);
     p.dZb = b.take<float>((size_t)n * ldmax);
     p.dTx = b.take<float>((size_t)n * ldxmax);
-    p.cvec = b.take<float>((size_t)n);
-    p.dqs = b.take<float2>((size_t)n);
+    p.dst = b.take<float4>((size_t)n);
+    p.dq = b.take<float>((size_t)n);
     p.dWx = b.take<float>((size_t)wxmax);
     const int64_t chunks_cap = part->csr_long.n_chunks > part->csc_long.n_chunks ? part->csr_long.n_chunks : part->csc_long.n_chunks;
     p.partials = b.take<float>((size_t)chunks_cap * ldxmax);
     p.tn_ws = b.take<char>(tn_bytes);
     p.tn_ws_bytes = tn_bytes;
-    p.colsum_ws = b.take<char>(cs_bytes);
+    p.colsum = b.take<float>((size_t)GAT_DST_BLOCKS * ldxmax);
     if (pl_bytes > 0) p.planes = b.take<unsigned char>(pl_bytes);
     p.planes_bytes = pl_bytes;
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
@@ -529,16 +618,18 @@ void gat_step_activation(const grp_partition_t* part, const grp_model_desc* m, v
 }
 
 template <int PASS, int G, int NJ>
-static void gat_walk_one(const GatWalk& A, const LongRows* lr, hipStream_t st) {
+static void gat_walk_one(const GatWalk& A, const LongRows* lr, float* dbias, hipStream_t st) {
     constexpr int ROWS = 256 / G;
-    hipLaunchKernelGGL((gat_walk_kernel<PASS, G, NJ>), dim3((unsigned)(A.n_chunks + cdiv(A.n, ROWS))), dim3(256), 0, st, A);
+    const int64_t blocks = PASS == GAT_DST ? std::min<int64_t>(cdiv(A.n, ROWS), GAT_DST_BLOCKS) : cdiv(A.n, ROWS);
+    hipLaunchKernelGGL((gat_walk_kernel<PASS, G, NJ>), dim3((unsigned)(A.n_chunks + blocks)), dim3(256), 0, st, A);
+    if (PASS == GAT_DST) launch_colsum_final(A.colsum, blocks, A.F, dbias, st);
     if (A.n_chunks > 0)
         hipLaunchKernelGGL((gat_combine_kernel<PASS, G, NJ>), dim3((unsigned)cdiv(lr->n_long, ROWS)), dim3(256), 0, st, A,
                            (const int32_t*)lr->long_row, (const int32_t*)lr->long_first, lr->n_long);
 }
 
 template <int PASS>
-static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials, hipStream_t st) {
+static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials, hipStream_t st, float* dbias = nullptr /*DST: column sums of dOut*/) {
     const bool split = lr && lr->n_long > 0;
     A.long_thr = split ? (int64_t)SPMM_LONG_ROW : INT64_MAX;
     A.n_chunks = split ? lr->n_chunks : 0;
@@ -547,15 +638,15 @@ static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials
     A.partials = partials;
     A.ld_part = round_up(A.F, 4) + 4;
     const int f4 = (A.F + 3) / 4;
-    if (f4 <= 1) gat_walk_one<PASS, 1, 1>(A, lr, st);
-    else if (f4 <= 2) gat_walk_one<PASS, 2, 1>(A, lr, st);
-    else if (f4 <= 4) gat_walk_one<PASS, 4, 1>(A, lr, st);
-    else if (f4 <= 8) gat_walk_one<PASS, 8, 1>(A, lr, st);
-    else if (f4 <= 16) gat_walk_one<PASS, 16, 1>(A, lr, st);
-    else if (f4 <= 32) gat_walk_one<PASS, 32, 1>(A, lr, st);
-    else if (f4 <= 64) gat_walk_one<PASS, 64, 1>(A, lr, st);
-    else if (f4 <= 128) gat_walk_one<PASS, 64, 2>(A, lr, st);
-    else gat_walk_one<PASS, 64, 4>(A, lr, st);
+    if (f4 <= 1) gat_walk_one<PASS, 1, 1>(A, lr, dbias, st);
+    else if (f4 <= 2) gat_walk_one<PASS, 2, 1>(A, lr, dbias, st);
+    else if (f4 <= 4) gat_walk_one<PASS, 4, 1>(A, lr, dbias, st);
+    else if (f4 <= 8) gat_walk_one<PASS, 8, 1>(A, lr, dbias, st);
+    else if (f4 <= 16) gat_walk_one<PASS, 16, 1>(A, lr, dbias, st);
+    else if (f4 <= 32) gat_walk_one<PASS, 32, 1>(A, lr, dbias, st);
+    else if (f4 <= 64) gat_walk_one<PASS, 64, 1>(A, lr, dbias, st);
+    else if (f4 <= 128) gat_walk_one<PASS, 64, 2>(A, lr, dbias, st);
+    else gat_walk_one<PASS, 64, 4>(A, lr, dbias, st);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -581,7 +672,7 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
     for (int l = 0; l < k; ++l) {
         const GatLayer& L = p.L[l];
         ProfScope ps("gat_pack_weights", st);
-        hipLaunchKernelGGL(gat_pack_kernel, dim3((unsigned)cdiv((int64_t)L.ldin_pad * L.ldx, 256)), dim3(256), 0, st,
+        hipLaunchKernelGGL(gat_pack_kernel, dim3((unsigned)(cdiv(L.ldin_pad, 4) + cdiv((int64_t)L.ldin_pad * L.ldx, 256))), dim3(256), 0, st,
                            theta + L.off_w, theta + L.off_as, theta + L.off_ad, L.fin, L.fout, (int)L.ldin_pad, (int)L.ldx,
                            l > 0 ? drop.scale : 1.f, L.Wp, L.Wt);
         GRP_LAUNCH_CHECK();
@@ -600,9 +691,10 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
         {
             ProfScope ps("gat_forward", st, 2.0 * g->nnz * L.fout, 4.0 * g->nnz + 8.0 * L.fout * n);
             hipLaunchKernelGGL(gat_extract_pq_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, L.Tx, L.ldx, (int)L.ldh, n, L.pq);
-            hipLaunchKernelGGL(gat_stats_kernel, dim3((unsigned)(cdiv(n, 16) + g->csr_long.n_long)), dim3(256), 0, st,
-                               g->rowptr, g->col, n, (const float2*)L.pq, L.rowstat, g->csr_long.long_row,
-                               g->csr_long.n_long, (int64_t)SPMM_LONG_ROW);
+            const bool few = g->nnz <= 16 * n;
+            const dim3 grid((unsigned)(cdiv(n, GAT_STATS_THREADS / (few ? 4 : 16)) + g->csr_long.n_long));
+            hipLaunchKernelGGL(few ? gat_stats_kernel<4> : gat_stats_kernel<16>, grid, dim3(GAT_STATS_THREADS), 0, st, g->rowptr, g->col, n,
+                               (const float2*)L.pq, L.rowstat, g->csr_long.long_row, g->csr_long.n_long, (int64_t)SPMM_LONG_ROW);
             GRP_LAUNCH_CHECK();
             GatWalk A{};
             A.ptr = g->rowptr; A.idx = g->col; A.n = n; A.F = L.fout; A.Tx = L.Tx; A.ldx = L.ldx; A.pq = L.pq;
@@ -623,15 +715,14 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
         const void* Hin = l == 0 ? X : (const void*)p.L[l - 1].Hout;
         const int64_t ldin = l == 0 ? m->dims[0] : p.L[l - 1].ldh;
         const int in_bf16 = l == 0 && m->feat_dtype == GRP_DTYPE_BF16;
-        GRP_TRY(launch_colsum(dZ, n, L.fout, L.ldh, grad + L.off_b, p.colsum_ws, st));
         {
             ProfScope ps("gat_backward", st, 6.0 * g->nnz * L.fout, 8.0 * g->nnz + 16.0 * L.fout * n);
             GatWalk A{};
             A.ptr = g->rowptr; A.idx = g->col; A.n = n; A.F = L.fout; A.Tx = L.Tx; A.ldx = L.ldx; A.pq = L.pq;
             A.rowstat = L.rowstat; A.bias = theta + L.off_b; A.Hout = L.Hout; A.ldh = L.ldh; A.dOut = dZ; A.ldd = L.ldh;
-            A.cvec = p.cvec; A.dqs = p.dqs; A.dTx = p.dTx;
+            A.dst = p.dst; A.dq = p.dq; A.dTx = p.dTx; A.colsum = p.colsum;
             A.hout_scale = (drop.on && l < k - 1) ? 1.0f - o->dropout_rate : 1.f;
-            GRP_TRY(launch_gat_walk<GAT_DST>(A, &g->csr_long, p.partials, st));
+            GRP_TRY(launch_gat_walk<GAT_DST>(A, &g->csr_long, p.partials, st, grad + L.off_b));
             A.ptr = g->colptr; A.idx = g->row;
             GRP_TRY(launch_gat_walk<GAT_SRC>(A, &g->csc_long, p.partials, st));
         }

@@ -99,3 +99,27 @@ def test_gat_unsupported_and_degenerate(g):
         g.grp_step_workspace_bytes(part, model, mb)
     assert ei.value.status == g.EUNSUPPORTED
     part.destroy()
+
+
+@pytest.mark.parametrize("degree,dims", [(4, [20, 160, 5]), (20, [12, 40, 3])])
+def test_gat_more_rows_than_one_round_of_workgroups(g, degree, dims):
+    """The backward walk over destinations deals its rows to at most 2048 workgroups, of 4 rows at 160 columns and of 16 at 40; the
+    statistics take 4 lanes a row up to 16 edges on average, 16 lanes above."""
+    n = 12_000 if dims[1] > 64 else 40_000
+    print(f"[case] gat rows={n} degree={degree} dims={dims}", flush=True)
+    s, d = synth.rmat_graph(16, degree * n, seed=61)
+    s, d = s % n, d % n
+    op = ograph.partition(s.numpy(), d.numpy(), n, 1, 3, 0)
+    part = g.grp_partition(s.to(DEV), d.to(DEV), n, 1, 3, 0)
+    assert part.n == n and int(op["d_local_in"].max()) > 512
+    x, y = synth.normal_matrix(n, dims[0], 62), synth.labels(n, dims[-1], 63)
+    theta = synth.model_weights("gat", dims, 65)
+    model, opts = g.model_desc(g.ARCH_GAT, dims), g.step_opts(estimator=g.EST_NONE, full_graph=True)
+    ws = torch.empty(g.grp_step_workspace_bytes(part, model, opts), dtype=torch.uint8, device=DEV)
+    grad, stats = torch.full((g.grp_param_count(model),), float("nan"), device=DEV), g.new_stats(1)
+    g.grp_train_step(part, model, opts, x.to(DEV), y.to(DEV), None, theta.to(DEV), ws, grad, stats)
+
+    def oracle_fn(relu_flip=None, near_kink=None):
+        return ostep.train_step(op, "gat", dims, theta.double().numpy(), x.double().numpy(), y.numpy(), None, relu_flip=relu_flip, near_kink=near_kink)
+    assert_step_grads_close(grad.cpu().numpy(), oracle_fn, "gat", dims, TOL_FP32)
+    part.destroy()
