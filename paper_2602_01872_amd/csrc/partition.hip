@@ -34,12 +34,15 @@ struct OwnerTest {
     uint64_t seed, inv, limit;
     uint32_t part;
     int rot;
-    __device__ __forceinline__ bool operator()(int64_t v) const {
-        const uint64_t z = splitmix64_output(seed, (uint64_t)v);
+    // POW2: K = 2^rot, whose remainder is the low bits
+    template <bool POW2 = false> __device__ __forceinline__ bool owns(uint64_t v) const {
+        const uint64_t z = splitmix64_output(seed, v);
+        if (POW2) return ((uint32_t)z & ((1u << rot) - 1u)) == part;
         uint64_t q = (z - part) * inv;
         q = (q >> rot) | (q << ((64 - rot) & 63));
         return z >= part && q <= limit;
     }
+    __device__ __forceinline__ bool operator()(int64_t v) const { return owns((uint64_t)v); }
 };
 static OwnerTest owner_test(uint64_t seed, uint32_t K, uint32_t part) {
     OwnerTest t{seed, 1, ~0ull / K, part, 0};
@@ -403,34 +406,42 @@ __global__ __launch_bounds__(256) void edge_keys_kernel(const int64_t* __restric
 // edge_keys_kernel with a buffer of the exact size; local ids past id_cap are counted here, one by one.
 // What sets the time is what is asked of the L2 beside the edges: a membership lookup per edge (a bitmap larger than the L1: a line
 // each) and, worst, the in-degrees' additions, scattered words that are a request each even after a table in LDS (62e6
-// edges, an eighth of the nodes: 547 us with either of a lookup and a computed membership).  So membership is computed (about
-// 290 cycles a wavefront), and a tile's ids leave in ranges of SPAN ids, as neighbouring words; counting a range takes LDS only.
-// (286 us, and 49 for the counts; the read alone would take 190.)
+// edges, an eighth of the nodes: 547 us with either of a lookup and a computed membership).  So membership is computed, and a tile's ids
+// leave in ranges of SPAN ids, as neighbouring words; counting a range takes LDS only.  Then it is the vector instructions (89 an edge and
+// wavefront, 11 of them at a quarter of the rate, beside a read that alone would take 190 us): so remainders of a power of
+// two are the low bits, bounds are checked on the halves of the ids, and the edges whose destination is owned are lined up in LDS before they
+// are looked up, ranked and counted, instead of all eight of a lane's in turn with most lanes idle.  (62e6 edges, 8 parts: 286 -> 250 us.)
 constexpr int SPAN_BITS = 14;            // 64 KB of counters
 constexpr int SPANS_MAX = 256;           // ranges: partitions of up to 2^22 nodes
 constexpr int SCAN_THREADS = 512;
 constexpr int SCAN_PER = 8;              // edges per thread and tile: their loads are in flight together
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_PER;
-constexpr int SCAN_GRID = 2048;
-__global__ __launch_bounds__(SCAN_THREADS) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, int64_t E,
-                                                                      int64_t N, NodeSet own, OwnerTest owned, int spans,
+constexpr int SCAN_GRID = 1536;          // two rounds of three workgroups a CU
+template <bool POW2>
+__global__ __launch_bounds__(SCAN_THREADS, 6) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, int64_t E,
+                                                                      uint32_t N, NodeSet own, OwnerTest owned, int spans,
                                                                       unsigned long long* __restrict__ dg, unsigned long long* __restrict__ counters,
                                                                       uint64_t* __restrict__ keys, unsigned long long cap,
                                                                       uint32_t* __restrict__ ids, unsigned long long id_cap,
                                                                       uint32_t* __restrict__ heads /*[tiles][spans + 1]*/) {
-    __shared__ uint32_t buf[SCAN_TILE];
+    __shared__ union {
+        uint2 line[SCAN_TILE];                               // (source, destination) of the edges in question, 64 * SCAN_PER places a wavefront
+        uint32_t buf[SCAN_TILE];
+    } sh;
+    uint32_t* const buf = sh.buf;
     __shared__ uint32_t first[SPANS_MAX + 1];
     __shared__ uint32_t kept, id_total;
     __shared__ unsigned long long base[2];
     const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
     const int tid = threadIdx.x, lane = tid & 63;
+    uint2* const line = sh.line + (tid >> 6) * (64 * SCAN_PER);
     unsigned long long bad = 0;
     const int64_t n_tiles = (E + SCAN_TILE - 1) / SCAN_TILE;
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         for (int i = tid; i < spans; i += SCAN_THREADS) first[i] = 0u;
         if (tid == 0) kept = 0u;
         const int64_t e0 = tile * SCAN_TILE + 2 * tid;
-        uint32_t u[SCAN_PER], v[SCAN_PER], has = 0;          // bit i: the destination of edge i is owned
+        uint32_t here = 0;                                   // edges of the wavefront whose destination is owned
         {
             int64_t us[SCAN_PER], vs[SCAN_PER];
             if (vec && (tile + 1) * SCAN_TILE <= E) {        // (uniform)
@@ -449,36 +460,46 @@ __global__ __launch_bounds__(SCAN_THREADS) void edge_scan_keys_kernel(const int6
                     load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);      // -2: past the end, neither counted nor an error
                 }
             }
+            bool odd = false;                                // an id out of range, or no edge
 #pragma unroll
             for (int i = 0; i < SCAN_PER; ++i) {
-                const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-                bad += !ok && vs[i] != -2;
-                u[i] = ok ? (uint32_t)us[i] : 0u;
-                v[i] = ok ? (uint32_t)vs[i] : 0u;
-                has |= (ok && owned(v[i]) ? 1u : 0u) << i;
+                const uint32_t u = (uint32_t)us[i], v = (uint32_t)vs[i], high = (uint32_t)(us[i] >> 32) | (uint32_t)(vs[i] >> 32);
+                const bool ok = high == 0u && (u > v ? u : v) < N;
+                odd = odd || !ok;
+                const unsigned long long in = __ballot(ok && owned.template owns<POW2>(v));
+                if ((in >> lane) & 1ull) line[__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, here))] = make_uint2(u, v);
+                here += (uint32_t)__popcll(in);
+                __builtin_amdgcn_sched_barrier(0);           // (an edge at a time: registers)
+            }
+            if (__any(odd)) {                                // (read again: registers)
+                for (int i = 0; i < SCAN_PER; i += 2)
+                    for (int64_t e = e0 + (int64_t)i * SCAN_THREADS, z = e + 2; e < z; ++e)
+                        bad += e < E && !(src[e] >= 0 && dst[e] >= 0 && src[e] < (int64_t)N && dst[e] < (int64_t)N);
             }
         }
-        // The lookups of eight edges are requested together, in two stages; a lane that has no need of one reads word 0 (one line for all
-        // of them).
-        uint2 wv[SCAN_PER], wu[SCAN_PER];
+        here = (uint32_t)__builtin_amdgcn_readfirstlane((int)here);
+        __builtin_amdgcn_wave_barrier();                     // (a wavefront's accesses to LDS are made in order)
+        uint32_t u[SCAN_PER], v[SCAN_PER], at[SCAN_PER];      // local ids of edge 64 i + lane of them (NOT_KEPT: a source that is not owned)
+        constexpr uint32_t NOT_KEPT = ~0u;
+        auto on = [&](int i) { return (uint32_t)(64 * i + lane) < here; };
 #pragma unroll
-        for (int i = 0; i < SCAN_PER; ++i) {
-            const bool in = (has >> i) & 1u;
-            wv[i] = own.words[in ? v[i] >> 5 : 0u];
-            wu[i] = own.words[in ? u[i] >> 5 : 0u];
+        for (int i = 0; i < SCAN_PER; i += 2) {
+            if (64u * i >= here) break;                      // (uniform, here and below)
+            const uint2 a = line[on(i) ? 64 * i + lane : 0], b = line[on(i + 1) ? 64 * (i + 1) + lane : 0];
+            const uint2 av = own.words[a.y >> 5], au = own.words[a.x >> 5], bv = own.words[b.y >> 5], bu = own.words[b.x >> 5];
+            v[i] = (uint32_t)word_rank(av, a.y);
+            u[i] = word_has(au, a.x) ? (uint32_t)word_rank(au, a.x) : NOT_KEPT;
+            v[i + 1] = (uint32_t)word_rank(bv, b.y);
+            u[i + 1] = word_has(bu, b.x) ? (uint32_t)word_rank(bu, b.x) : NOT_KEPT;
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();                                     // the counters are clear
-        uint32_t at[SCAN_PER];
+        __syncthreads();                                     // the counters are clear; the line has been read
 #pragma unroll
         for (int i = 0; i < SCAN_PER; ++i) {
-            if (!((has >> i) & 1u)) continue;
-            v[i] = (uint32_t)word_rank(wv[i], v[i]);
+            if (64u * i >= here) break;
+            if (!on(i)) continue;
             at[i] = atomicAdd(&first[v[i] >> SPAN_BITS], 1u);
-            if (word_has(wu[i], u[i])) {
-                u[i] = (uint32_t)word_rank(wu[i], u[i]);
-                has |= (1u << SCAN_PER) << i;                // kept
-                at[i] |= atomicAdd(&kept, 1u) << 16;
-            }
+            if (u[i] != NOT_KEPT) at[i] |= atomicAdd(&kept, 1u) << 16;
         }
         __syncthreads();
         if (tid < 64) {                                      // the ranges' places in the tile, and the tile's in the arrays
@@ -519,8 +540,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void edge_scan_keys_kernel(const int6
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < SCAN_PER; ++i) {
-            if ((has >> i) & 1u) buf[first[v[i] >> SPAN_BITS] + (at[i] & 0xFFFFu)] = v[i];
-            if ((has >> (SCAN_PER + i)) & 1u) {
+            if (64u * i >= here) break;
+            if (on(i)) buf[first[v[i] >> SPAN_BITS] + (at[i] & 0xFFFFu)] = v[i];
+            if (on(i) && u[i] != NOT_KEPT) {
                 const unsigned long long slot = base[1] + (at[i] >> 16);
                 if (slot < cap) keys[slot] = ((uint64_t)v[i] << 32) | (uint64_t)u[i];
             }
@@ -989,10 +1011,10 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
         } else {
             ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
             uint32_t* const heads = (uint32_t*)((char*)idbuf.p + id_pitch);
-            hipLaunchKernelGGL(edge_scan_keys_kernel, dim3((unsigned)(scan_tiles < SCAN_GRID ? scan_tiles : SCAN_GRID)), dim3(SCAN_THREADS), 0, st, src,
-                               dst, E, N, own, owned, (int)spans, (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(),
+            hipLaunchKernelGGL((K & (K - 1)) == 0 ? edge_scan_keys_kernel<true> : edge_scan_keys_kernel<false>,
+                               dim3((unsigned)(scan_tiles < SCAN_GRID ? scan_tiles : SCAN_GRID)), dim3(SCAN_THREADS), 0, st, src, dst, E, (uint32_t)N, own, owned, (int)spans, (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(),
                                (unsigned long long)cap, idbuf.as<uint32_t>(), (unsigned long long)id_cap, heads);
-            int64_t parts = cdiv(256, spans);            // a workgroup per CU, a tile at least for each of its wavefronts
+                        int64_t parts = cdiv(256, spans);            // a workgroup per CU, a tile at least for each of its wavefronts
             if (parts > cdiv(scan_tiles, 16)) parts = cdiv(scan_tiles, 16);
             int at_once = 64;
             while (at_once > 1 && parts * 16 * at_once > scan_tiles) at_once /= 2;
