@@ -9,10 +9,12 @@
 // in it are written as keys (source << 32 | destination), sorted (rocPRIM radix sort) and unpacked
 // into their final places in `row`, with `colptr` found by binary search in the sorted keys.  Equal keys
 // are indistinguishable, so the result is the canonical CSC whatever order the keys were emitted in.
+// (Where all edges may be held at once and sizes allow, they are sorted in buckets: buckets.hip.)
 // A share of 2^32 edges therefore needs its 36 GB of indices plus a few GB of temporaries, where sorting
 // an edge list of the same share would hold the list, two key buffers and the sort's scratch at once.
 #include "common.h"
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -25,64 +27,79 @@ constexpr int AD_TILE = 4096;        // edges per workgroup tile of the emit pas
 constexpr int AD_PER = AD_TILE / 256;
 constexpr int AD_WIN = 2048;         // row pointers of a tile kept in LDS (more rows: search in global memory)
 
+// Adds a workgroup's counts to two counters: one atomic each (37,500 wavefronts' took 455 us on one address).
+__device__ __forceinline__ void add_counts(unsigned long long a, unsigned long long b, unsigned long long* to_a, unsigned long long* to_b) {
+    __shared__ unsigned long long part[2][16];
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_down(a, o, 64);
+        b += __shfl_down(b, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) { part[0][threadIdx.x >> 6] = a; part[1][threadIdx.x >> 6] = b; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (unsigned w = 1; w < blockDim.x / 64; ++w) { a += part[0][w]; b += part[1][w]; }
+    if (a) atomicAdd(to_a, a);
+    if (b) atomicAdd(to_b, b);
+}
+
 // counters: [0] malformed row pointers, [1] column indices outside [0, n), [2] positions e > 0 with
 // col[e] < col[e-1], [3] non-empty rows that start at such a position (rows are ascending iff [2] == [3])
 __global__ __launch_bounds__(256) void adopt_check_ptr_kernel(const int64_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                               int64_t n, int64_t nnz,
                                                               unsigned long long* __restrict__ counters) {
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    bool bad = false, starts_low = false;
-    if (r <= n) {
+    unsigned long long low = 0, bads = 0;
+    for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r <= n; r += (int64_t)gridDim.x * 256) {
         const int64_t b = ptr[r];
-        bad = b < 0 || b > nnz || (r == 0 && b != 0) || (r == n && b != nnz);
+        bool bad = b < 0 || b > nnz || (r == 0 && b != 0) || (r == n && b != nnz);
         if (r < n) {
             const int64_t e = ptr[r + 1];
             if (e < b) bad = true;
-            starts_low = !bad && e <= nnz && e > b && b > 0 && col[b] < col[b - 1];
+            if (!bad && e <= nnz && e > b && b > 0 && col[b] < col[b - 1]) ++low;
         }
+        bads += bad;
     }
-    // nearly every row of a real graph starts below the end of the row before it: one atomic per wavefront,
-    // not per row (16 M atomics on one address took 106 ms on a 2^24-node share)
-    const unsigned long long low = __ballot(starts_low), bads = __ballot(bad);
-    if ((threadIdx.x & 63) == 0) {
-        if (low) atomicAdd(&counters[3], (unsigned long long)__popcll(low));
-        if (bads) atomicAdd(&counters[0], (unsigned long long)__popcll(bads));
-    }
+    add_counts(bads, low, &counters[0], &counters[3]);
 }
 
-// Range check, order check and the histogram of the sources over bins of 2^shift ids.
-__global__ __launch_bounds__(256) void adopt_check_col_kernel(const int32_t* __restrict__ col, int64_t nnz, int64_t n,
-                                                              int shift, unsigned long long* __restrict__ counters,
-                                                              unsigned long long* __restrict__ hist) {
+// Range check, order check and the histogram of the sources over bins of 2^shift ids.  A workgroup takes runs of `run` consecutive
+// edges, at most 2^20, so that a bin counter in LDS cannot overflow; a launch has AD_CHECK_GRID of them or more, where there are that many
+// times AD_BINS edges (in runs of 2^20, 2e7 edges kept 20 workgroups busy: 1693 us, now 33).
+constexpr int AD_CHECK_GRID = 512;
+__global__ __launch_bounds__(1024) void adopt_check_col_kernel(const int32_t* __restrict__ col, int64_t nnz, int64_t n, int64_t run,
+                                                               int shift, unsigned long long* __restrict__ counters,
+                                                               unsigned long long* __restrict__ hist) {
     __shared__ unsigned int bins[AD_BINS];
-    for (int i = threadIdx.x; i < AD_BINS; i += 256) bins[i] = 0u;
+    for (int i = threadIdx.x; i < AD_BINS; i += 1024) bins[i] = 0u;
     __syncthreads();
     unsigned long long bad = 0, desc = 0;
-    // a workgroup takes runs of 2^20 consecutive edges, so that a bin counter in LDS cannot overflow
-    const int64_t run = (int64_t)1 << 20;
+    constexpr int U = 8;                                   // edges in flight per thread
     for (int64_t r0 = (int64_t)blockIdx.x * run; r0 < nnz; r0 += (int64_t)gridDim.x * run) {
         const int64_t r1 = r0 + run < nnz ? r0 + run : nnz;
-        for (int64_t e = r0 + threadIdx.x; e < r1; e += 256) {
-            const int32_t c = col[e];
-            if (c < 0 || (int64_t)c >= n) { ++bad; continue; }
-            if (e > 0 && c < col[e - 1]) ++desc;
-            atomicAdd(&bins[c >> shift], 1u);
+        for (int64_t e0 = r0; e0 < r1; e0 += U * 1024) {
+            int32_t c[U], before[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int64_t e = e0 + u * 1024 + threadIdx.x;
+                e = e < r1 ? e : r1 - 1;
+                c[u] = col[e];
+                before[u] = col[e > 0 ? e - 1 : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (e0 + u * 1024 + threadIdx.x >= r1) continue;
+                if (c[u] < 0 || (int64_t)c[u] >= n) { ++bad; continue; }
+                desc += c[u] < before[u];                  // (edge 0 is its own predecessor)
+                atomicAdd(&bins[c[u] >> shift], 1u);
+            }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < AD_BINS; i += 256) {
+        for (int i = threadIdx.x; i < AD_BINS; i += 1024) {
             if (bins[i]) atomicAdd(&hist[i], (unsigned long long)bins[i]);
             bins[i] = 0u;
         }
         __syncthreads();
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        bad += __shfl_down(bad, o, 64);
-        desc += __shfl_down(desc, o, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        if (bad) atomicAdd(&counters[1], bad);
-        if (desc) atomicAdd(&counters[2], desc);
-    }
+    add_counts(bad, desc, &counters[1], &counters[2]);
 }
 
 // The row that holds edge e: the largest r in [lo, hi] with ptr[r] <= e (ptr[lo] <= e < ptr[hi + 1]).
@@ -260,16 +277,16 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
     unsigned long long* cursor = counters + 4;
     unsigned long long* hist = counters + 8;
     GRP_TRY(launch_fill_zero(small.p, (8 + AD_BINS) * sizeof(unsigned long long), st));
-    hipLaunchKernelGGL(adopt_check_ptr_kernel, dim3((unsigned)cdiv(n + 1, 256)), dim3(256), 0, st, rowptr, col, n, nnz, counters);
+    hipLaunchKernelGGL(adopt_check_ptr_kernel, dim3((unsigned)std::min<int64_t>(cdiv(n + 1, 256), 1024)), dim3(256), 0, st, rowptr, col, n, nnz, counters);
     GRP_LAUNCH_CHECK();
     unsigned long long host[8 + AD_BINS];
     GRP_HIP(hipMemcpyAsync(host, counters, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     GRP_HIP(hipStreamSynchronize(st));
     if (host[0]) return fail(GRP_EINVAL, "grp_partition_from_csr: %llu row pointers are not a non-decreasing sequence from 0 to nnz", host[0]);
     if (nnz > 0) {
-        const int64_t runs = cdiv(nnz, (int64_t)1 << 20);
-        hipLaunchKernelGGL(adopt_check_col_kernel, dim3((unsigned)(runs < 2048 ? runs : 2048)), dim3(256), 0, st, col, nnz, n,
-                           shift, counters, hist);
+        const int64_t run = std::min<int64_t>(std::max<int64_t>(round_up(cdiv(nnz, AD_CHECK_GRID), AD_BINS), AD_BINS), (int64_t)1 << 20);
+        hipLaunchKernelGGL(adopt_check_col_kernel, dim3((unsigned)std::min<int64_t>(cdiv(nnz, run), 2048)), dim3(1024), 0, st, col, nnz, n, run, shift,
+                           counters, hist);
         GRP_LAUNCH_CHECK();
     }
     GRP_HIP(hipMemcpyAsync(host, counters, sizeof host, hipMemcpyDeviceToHost, st));
@@ -279,14 +296,30 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
         return fail(GRP_EINVAL, "grp_partition_from_csr: the column indices of a row must be ascending (%llu descents inside rows)",
                     host[2] - host[3]);
 
-    // ---- the transpose, one range of sources at a time
-    if (nnz > 0) {
+    // ---- the transpose: in buckets where all edges may be held at once and the sizes allow, or one range of sources at a time
+    const int64_t hold = slice_edges > 0 ? slice_edges : ((int64_t)1 << 28);
+    const int64_t n_tiles = cdiv(nnz, AD_TILE);
+    const unsigned emit_grid = (unsigned)(n_tiles < 4096 ? n_tiles : 4096);
+    int64_t long_edges[2] = {-1, -1};
+    bool done = false;
+    BucketPlan plan;
+    if (nnz <= hold && bucket_plan(n, nnz, &plan)) {
+        Owned keys, packed, scratch;
+        GRP_TRY(keys.alloc((size_t)nnz * sizeof(uint64_t)));
+        GRP_TRY(packed.alloc((size_t)nnz * sizeof(uint64_t)));
+        GRP_TRY(scratch.alloc(bucket_scratch_bytes(plan, nnz)));
+        GRP_TRY(launch_fill_zero(cursor, 4 * sizeof(unsigned long long), st));
+        hipLaunchKernelGGL(adopt_slice_keys_kernel, dim3(emit_grid), dim3(256), 0, st, rowptr, col, n, nnz, 0, (int32_t)n, (uint64_t*)keys.p,
+                           (unsigned long long)nnz, cursor);
+        GRP_LAUNCH_CHECK();
+        GRP_TRY(bucket_build(h, plan, (uint64_t*)keys.p, (uint64_t*)packed.p, scratch.p, long_edges, &done, st, true));
+    }
+    if (nnz > 0 && !done) {
         const unsigned long long* hb = host + 8;
         const int64_t n_bins = ((n - 1) >> shift) + 1;
         unsigned long long biggest = 0;
         for (int64_t b = 0; b < n_bins; ++b) biggest = hb[b] > biggest ? hb[b] : biggest;
-        int64_t cap = slice_edges > 0 ? slice_edges : ((int64_t)1 << 28);
-        if (cap > nnz) cap = nnz;
+        int64_t cap = hold < nnz ? hold : nnz;
         if ((unsigned long long)cap < biggest) cap = (int64_t)biggest;      // a bin is never cut
         const unsigned end_bit = 64;
         size_t sort_bytes = 0;
@@ -295,8 +328,6 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
         GRP_TRY(keys.alloc((size_t)cap * sizeof(uint64_t)));
         GRP_TRY(sorted.alloc((size_t)cap * sizeof(uint64_t)));
         GRP_TRY(tmp.alloc(sort_bytes));
-        const int64_t n_tiles = cdiv(nnz, AD_TILE);
-        const unsigned emit_grid = (unsigned)(n_tiles < 4096 ? n_tiles : 4096);
         int64_t at = 0;
         for (int64_t b0 = 0; b0 < n_bins;) {
             int64_t b1 = b0;
@@ -334,7 +365,7 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
         }
         GRP_HIP(hipStreamSynchronize(st));                 // the temporaries are freed on return
         if (at != nnz) return fail(GRP_EHIP, "grp_partition_from_csr: transposed %lld of %lld edges", (long long)at, (long long)nnz);
-    } else if (n > 0) {
+    } else if (n > 0 && !done) {
         GRP_TRY(launch_fill_zero(h->colptr, (size_t)(n + 1) * sizeof(int64_t), st));
     }
     if (n > 0) {
@@ -352,10 +383,10 @@ static grp_status adopt_impl(grp_partition_t* h, const int64_t* rowptr, const in
         int64_t* scanned = (int64_t*)tmp.p;
         void* scan_tmp = (char*)tmp.p + scanned_bytes;
         GRP_TRY(long_rows_of(h->rowptr, n, &h->csr_long, cap_long, cap_chunks, scanned, scan_tmp, scan_bytes, st));
-        GRP_TRY(long_rows_of(h->colptr, n, &h->csc_long, cap_long, cap_chunks, scanned, scan_tmp, scan_bytes, st));
+        if (!done) GRP_TRY(long_rows_of(h->colptr, n, &h->csc_long, cap_long, cap_chunks, scanned, scan_tmp, scan_bytes, st));
     }
     GRP_HIP(hipStreamSynchronize(st));
-    return build_slice_tasks(h, {-1, -1}, st);
+    return build_slice_tasks(h, long_edges, st);
 }
 
 }  // namespace grp

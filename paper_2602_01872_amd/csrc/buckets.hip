@@ -90,7 +90,7 @@ static BucketScratch carve_scratch(const BucketPlan& p, int64_t nnz, void* base)
 }
 size_t bucket_scratch_bytes(const BucketPlan& p, int64_t nnz) { return carve_scratch(p, nnz, nullptr).bytes; }
 
-__global__ __launch_bounds__(BK_THREADS) void bucket_count_kernel(const uint64_t* __restrict__ keys, int64_t nnz, BucketPlan p,
+__global__ __launch_bounds__(BK_THREADS) void bucket_count_kernel(const uint64_t* __restrict__ keys, int64_t nnz, BucketPlan p, int dirs,
                                                                   uint32_t* __restrict__ count) {
     extern __shared__ uint32_t hist[];                     // [2 B]
     const int B = p.n_buckets;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_count_kernel(const uint64_t
     for (int64_t e = (int64_t)blockIdx.x * BK_THREADS + threadIdx.x; e < nnz; e += (int64_t)gridDim.x * BK_THREADS) {
         const uint64_t k = keys[e];
         atomicAdd(&hist[(uint32_t)(k >> 32) >> p.row_bits], 1u);
-        atomicAdd(&hist[B + ((uint32_t)k >> p.row_bits)], 1u);
+        if (dirs > 1) atomicAdd(&hist[B + ((uint32_t)k >> p.row_bits)], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * B; i += BK_THREADS)
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_start_kernel(BucketScratch 
 // 2 x 1170 buckets 89 us, this way 29).  packed: nnz keys of each direction.
 constexpr int SC_PER = 16;                                 // (16 bits hold a place in a tile, and a bucket of either direction)
 constexpr int SC_TILE = BK_THREADS * SC_PER;
-__global__ __launch_bounds__(BK_THREADS) void bucket_scatter_kernel(const uint64_t* __restrict__ keys, int64_t nnz, BucketPlan p, int per,
+__global__ __launch_bounds__(BK_THREADS) void bucket_scatter_kernel(const uint64_t* __restrict__ keys, int64_t nnz, BucketPlan p, int dirs, int per,
                                                                     const unsigned long long* __restrict__ refused, uint32_t* __restrict__ cursor,
                                                                     uint32_t* __restrict__ packed) {
     extern __shared__ uint32_t lds[];                      // [2 B] counts, then where a bucket's keys go; [tile] keys; [2 B] places; [tile] buckets
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_scatter_kernel(const uint64
     for (int i = 0; i < SC_PER; ++i) {
         if (!on(i)) continue;
         at[i] = atomicAdd(&to[v[i] >> p.row_bits], 1u);
-        at[i] |= atomicAdd(&to[B + (u[i] >> p.row_bits)], 1u) << 16;
+        if (dirs > 1) at[i] |= atomicAdd(&to[B + (u[i] >> p.row_bits)], 1u) << 16;
     }
     __syncthreads();
     {   // reservations (neighbouring lanes ask for neighbouring cursors: a line of them is one request), and places of both directions
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_scatter_kernel(const uint64
     }
     __syncthreads();
     const uint32_t low = (1u << p.row_bits) - 1u;
-    for (int dir = 0; dir < 2; ++dir) {
+    for (int dir = 0; dir < dirs; ++dir) {
 #pragma unroll
         for (int i = 0; i < SC_PER; ++i) {
             if (!on(i)) continue;
@@ -726,27 +726,30 @@ __global__ __launch_bounds__(256) void bucket_unpack_kernel(const uint32_t* __re
 // keys: nnz of them, clobbered; packed: scratch of the same size; scratch: bucket_scratch_bytes.  Fills the handle's CSR, CSC and
 // degrees and the lists of its long rows (arrays of the worst case's size, or null where no row can be long); waits for the lists'
 // lengths.  long_edges: the edges of each direction's long rows.  *done = false: the build was refused, keys holds them again.
+// csc_alone: the keys are source << 32 | destination, and the CSC is all that is filled (as the first direction of what is below).
 grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys, uint64_t* packed, void* scratch, int64_t (&long_edges)[2],
-                        bool* done, hipStream_t st) {
+                        bool* done, hipStream_t st, bool csc_alone) {
     const int64_t n = h->n, nnz = h->nnz;
     const BucketScratch s = carve_scratch(p, nnz, scratch);
-    const BucketOut out{{h->rowptr, h->colptr}, {h->col, h->row}, {h->d_local_in, h->d_local_out},
-                        {h->csr_long.long_row, h->csc_long.long_row}, {h->csr_long.long_first, h->csc_long.long_first},
-                        {h->csr_long.chunk_begin, h->csc_long.chunk_begin}, {h->csr_long.chunk_end, h->csc_long.chunk_end}};
+    const int dirs = csc_alone ? 1 : 2;
+    LongRows* const lr[2] = {csc_alone ? &h->csc_long : &h->csr_long, &h->csc_long};
+    const BucketOut out{{csc_alone ? h->colptr : h->rowptr, h->colptr}, {csc_alone ? h->row : h->col, h->row},
+                        {csc_alone ? h->d_local_out : h->d_local_in, h->d_local_out}, {lr[0]->long_row, lr[1]->long_row},
+                        {lr[0]->long_first, lr[1]->long_first}, {lr[0]->chunk_begin, lr[1]->chunk_begin}, {lr[0]->chunk_end, lr[1]->chunk_end}};
     const size_t hist_bytes = 2 * (size_t)p.n_buckets * sizeof(uint32_t);
     GRP_TRY(launch_fill_zero(s.totals, s.clear_bytes, st));
     const int64_t count_groups = cdiv(nnz, 8 * BK_THREADS);
     hipLaunchKernelGGL(bucket_count_kernel, dim3((unsigned)(count_groups < 512 ? count_groups : 512)), dim3(BK_THREADS), hist_bytes, st, keys, nnz,
-                       p, s.count);
+                       p, dirs, s.count);
     hipLaunchKernelGGL(bucket_start_kernel, dim3(1), dim3(BK_THREADS), 0, st, s, p.n_buckets);
     // Long tiles make long runs in the buckets, short ones more workgroups.
     const int per = (int)(nnz >= (int64_t)256 * SC_TILE ? SC_PER : nnz <= (int64_t)256 * 4 * BK_THREADS ? 4 : cdiv(nnz, 256 * BK_THREADS));
     const size_t scatter_bytes = hist_bytes / 2 * 3 + (size_t)per * BK_THREADS * 6;
-    hipLaunchKernelGGL(bucket_scatter_kernel, dim3((unsigned)cdiv(nnz, per * BK_THREADS)), dim3(BK_THREADS), scatter_bytes, st, keys, nnz, p, per,
+    hipLaunchKernelGGL(bucket_scatter_kernel, dim3((unsigned)cdiv(nnz, per * BK_THREADS)), dim3(BK_THREADS), scatter_bytes, st, keys, nnz, p, dirs, per,
                        (const unsigned long long*)(s.totals + 4), s.cursor, (uint32_t*)packed);
     GRP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3(2 * p.n_buckets), dim3(BK_THREADS), 0, st, (const uint32_t*)packed, nnz, n, p, s, out, (uint32_t*)keys);
-    hipLaunchKernelGGL(bucket_finish_kernel, dim3(2 * p.n_buckets + JOB_GROUPS), dim3(BK_THREADS), 0, st, nnz, n, p, s, out, (const uint32_t*)keys);
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3(dirs * p.n_buckets), dim3(BK_THREADS), 0, st, (const uint32_t*)packed, nnz, n, p, s, out, (uint32_t*)keys);
+    hipLaunchKernelGGL(bucket_finish_kernel, dim3(dirs * p.n_buckets + JOB_GROUPS), dim3(BK_THREADS), 0, st, nnz, n, p, s, out, (const uint32_t*)keys);
     GRP_LAUNCH_CHECK();
     unsigned long long totals[5];
     GRP_HIP(hipMemcpyAsync(totals, s.totals, sizeof totals, hipMemcpyDeviceToHost, st));
@@ -759,11 +762,10 @@ grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys,
         GRP_LAUNCH_CHECK();
         return GRP_OK;
     }
-    LongRows* const lr[2] = {&h->csr_long, &h->csc_long};
-    for (int d = 0; d < 2; ++d) {
+    for (int d = 0; d < dirs; ++d) {
         lr[d]->n_long = (int32_t)(totals[2 * d] >> 32);
         lr[d]->n_chunks = (int32_t)(totals[2 * d] & 0xFFFFFFFFull);
-        long_edges[d] = (int64_t)totals[2 * d + 1];
+        long_edges[csc_alone ? 1 : d] = (int64_t)totals[2 * d + 1];
     }
     return GRP_OK;
 }

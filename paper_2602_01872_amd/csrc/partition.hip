@@ -52,11 +52,6 @@ static OwnerTest owner_test(uint64_t seed, uint32_t K, uint32_t part) {
     return t;
 }
 
-__global__ __launch_bounds__(256) void owner_flag_kernel(int64_t N, OwnerTest owned, int32_t* __restrict__ flag) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N) flag[v] = owned(v) ? 1 : 0;
-}
-
 // owner[v] for every node and (optionally) the number of nodes per partition.
 __global__ __launch_bounds__(256) void node_owners_kernel(int64_t N, uint32_t K, uint64_t seed, int32_t* __restrict__ owner,
                                                           unsigned long long* __restrict__ hist) {
@@ -332,13 +327,12 @@ struct SetSelect {                        // both endpoints in the node set
         return true;
     }
 };
-struct ArraySelect {                      // per-node flag and position arrays
-    const int32_t* flag;
-    const int64_t* pos;
-    int dst_only;                         // keep every edge whose destination is flagged (halo partitions), whatever its source
+struct HaloSelect {                       // destination in `inner`, a part of the set; its source then is in the set
+    NodeSet own;
+    const uint32_t* inner;
     __device__ __forceinline__ bool operator()(int64_t u, int64_t v, uint64_t& key) const {
-        if (!flag[v] || !(dst_only || flag[u])) return false;
-        key = ((uint64_t)pos[v] << 32) | (uint64_t)pos[u];
+        if (!((inner[v >> 5] >> (v & 31)) & 1u)) return false;
+        key = ((uint64_t)(uint32_t)set_rank(own, v) << 32) | (uint64_t)(uint32_t)set_rank(own, u);
         return true;
     }
 };
@@ -416,10 +410,25 @@ constexpr int SPANS_MAX = 256;           // ranges: partitions of up to 2^22 nod
 constexpr int SCAN_THREADS = 512;
 constexpr int SCAN_PER = 8;              // edges per thread and tile: their loads are in flight together
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_PER;
-constexpr int SCAN_GRID = 1536;          // two rounds of three workgroups a CU
-template <bool POW2>
-__global__ __launch_bounds__(SCAN_THREADS, 6) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, int64_t E,
-                                                                      uint32_t N, NodeSet own, OwnerTest owned, int spans,
+constexpr int SCAN_GRID = 1536;
+// Which edges are looked at (by their destination: its in-degree counts) and which of them are kept.
+template <bool POW2> struct OwnedEdges {   // destination owned, which is computed; source owned too
+    OwnerTest owned;
+    static constexpr bool LOOKUP = false;
+    static constexpr int WAVES = 5;          // a SIMD's (4: 492 us, 6: 500, some registers spilled)
+};
+struct HaloEdges {                         // destination in the set; destination in the set as it was before the last hop (its sources then are)
+    const uint32_t* inner;
+    static constexpr bool LOOKUP = true;
+    static constexpr int WAVES = 4;          // (2e7 edges, 2.4e6 nodes, one hop: a build 807 us; 3: 847, 5: 1232, spilled)
+};
+template <bool POW2> __device__ __forceinline__ bool select_counted(const OwnedEdges<POW2>& s, uint32_t v) { return s.owned.template owns<POW2>(v); }
+__device__ __forceinline__ bool select_counted(const HaloEdges&, uint32_t) { return true; }
+template <bool POW2> __device__ __forceinline__ uint32_t select_inner(const OwnedEdges<POW2>&, uint32_t) { return 0u; }
+__device__ __forceinline__ uint32_t select_inner(const HaloEdges& s, uint32_t word) { return s.inner[word]; }
+template <typename Select>
+__global__ __launch_bounds__(SCAN_THREADS, Select::WAVES) void edge_scan_keys_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst, int64_t E,
+                                                                      uint32_t N, NodeSet own, Select select, int spans,
                                                                       unsigned long long* __restrict__ dg, unsigned long long* __restrict__ counters,
                                                                       uint64_t* __restrict__ keys, unsigned long long cap,
                                                                       uint32_t* __restrict__ ids, unsigned long long id_cap,
@@ -461,12 +470,27 @@ __global__ __launch_bounds__(SCAN_THREADS, 6) void edge_scan_keys_kernel(const i
                 }
             }
             bool odd = false;                                // an id out of range, or no edge
+            auto in_range = [&](int i) {
+                const uint32_t u = (uint32_t)us[i], v = (uint32_t)vs[i], high = (uint32_t)(us[i] >> 32) | (uint32_t)(vs[i] >> 32);
+                return high == 0u && (u > v ? u : v) < N;
+            };
+            uint2 of_v[Select::LOOKUP ? SCAN_PER : 1];       // LOOKUP: the lookups of all destinations at once, here
+            uint32_t inner[Select::LOOKUP ? SCAN_PER : 1];
+#pragma unroll
+            for (int i = 0; Select::LOOKUP && i < SCAN_PER; ++i) {
+                const uint32_t word = in_range(i) ? (uint32_t)vs[i] >> 5 : 0u;
+                of_v[i] = own.words[word];
+                inner[i] = select_inner(select, word);
+            }
 #pragma unroll
             for (int i = 0; i < SCAN_PER; ++i) {
-                const uint32_t u = (uint32_t)us[i], v = (uint32_t)vs[i], high = (uint32_t)(us[i] >> 32) | (uint32_t)(vs[i] >> 32);
-                const bool ok = high == 0u && (u > v ? u : v) < N;
+                const uint32_t u = (uint32_t)us[i];
+                uint32_t v = (uint32_t)vs[i];
+                const bool ok = in_range(i);
                 odd = odd || !ok;
-                const unsigned long long in = __ballot(ok && owned.template owns<POW2>(v));
+                const unsigned long long in = __ballot(ok && (Select::LOOKUP ? word_has(of_v[Select::LOOKUP ? i : 0], v) : select_counted(select, v)));
+                if (Select::LOOKUP)                          // in line: the destination's local id, and at the top whether the edge is kept
+                    v = (uint32_t)word_rank(of_v[Select::LOOKUP ? i : 0], v) | ((inner[Select::LOOKUP ? i : 0] >> (v & 31u)) & 1u) << 31;
                 if ((in >> lane) & 1ull) line[__builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, here))] = make_uint2(u, v);
                 here += (uint32_t)__popcll(in);
                 __builtin_amdgcn_sched_barrier(0);           // (an edge at a time: registers)
@@ -486,6 +510,15 @@ __global__ __launch_bounds__(SCAN_THREADS, 6) void edge_scan_keys_kernel(const i
         for (int i = 0; i < SCAN_PER; i += 2) {
             if (64u * i >= here) break;                      // (uniform, here and below)
             const uint2 a = line[on(i) ? 64 * i + lane : 0], b = line[on(i + 1) ? 64 * (i + 1) + lane : 0];
+            if constexpr (Select::LOOKUP) {
+                const bool ka = a.y >> 31, kb = b.y >> 31;
+                const uint2 au = own.words[ka ? a.x >> 5 : 0u], bu = own.words[kb ? b.x >> 5 : 0u];
+                v[i] = a.y & ~(1u << 31);
+                u[i] = ka ? (uint32_t)word_rank(au, a.x) : NOT_KEPT;
+                v[i + 1] = b.y & ~(1u << 31);
+                u[i + 1] = kb ? (uint32_t)word_rank(bu, b.x) : NOT_KEPT;
+                continue;
+            }
             const uint2 av = own.words[a.y >> 5], au = own.words[a.x >> 5], bv = own.words[b.y >> 5], bu = own.words[b.x >> 5];
             v[i] = (uint32_t)word_rank(av, a.y);
             u[i] = word_has(au, a.x) ? (uint32_t)word_rank(au, a.x) : NOT_KEPT;
@@ -599,6 +632,23 @@ __global__ __launch_bounds__(1024) void rank_count_kernel(const uint32_t* __rest
     const int64_t id0 = (int64_t)blockIdx.x << SPAN_BITS;
     for (int i = tid; i < (1 << SPAN_BITS); i += 1024)
         if (count[i] && id0 + i < n) atomicAdd(&dg[id0 + i], (unsigned long long)count[i]);
+}
+
+template <typename Select>
+static grp_status launch_scan_keys(const Select& select, const int64_t* src, const int64_t* dst, int64_t E, int64_t N, NodeSet own, int64_t n, int64_t spans,
+                                   unsigned long long* dg, unsigned long long* counters, uint64_t* keys, int64_t cap, uint32_t* ids, int64_t id_cap,
+                                   uint32_t* heads, hipStream_t st) {
+    const int64_t tiles = cdiv(E, SCAN_TILE);
+    hipLaunchKernelGGL(edge_scan_keys_kernel<Select>, dim3((unsigned)(tiles < SCAN_GRID ? tiles : SCAN_GRID)), dim3(SCAN_THREADS), 0, st, src, dst, E, (uint32_t)N,
+                       own, select, (int)spans, dg, counters, keys, (unsigned long long)cap, ids, (unsigned long long)id_cap, heads);
+    int64_t parts = cdiv(256, spans);                        // a workgroup per CU, a tile at least for each of its wavefronts
+    if (parts > cdiv(tiles, 16)) parts = cdiv(tiles, 16);
+    int at_once = 64;
+    while (at_once > 1 && parts * 16 * at_once > tiles) at_once /= 2;
+    hipLaunchKernelGGL(rank_count_kernel, dim3((unsigned)spans, (unsigned)parts), dim3(1024), 0, st, (const uint32_t*)ids, (const uint32_t*)heads, tiles, (int)spans,
+                       at_once, n, dg);
+    GRP_LAUNCH_CHECK();
+    return GRP_OK;
 }
 
 // Local edge list: range check + keys in place order.
@@ -737,7 +787,8 @@ static unsigned grid_for(int64_t work) {
 
 struct DevBuf {
     void* p = nullptr;
-    ~DevBuf() { if (p) pool_free(p); }
+    ~DevBuf() { free(); }
+    void free() { if (p) pool_free(p); p = nullptr; }    // (nothing on the device may still use it)
     grp_status alloc(size_t bytes) {
         if (pool_alloc(&p, bytes ? bytes : 4) != hipSuccess) {
             p = nullptr;
@@ -936,6 +987,7 @@ struct SetScratch {
         return GRP_OK;
     }
 };
+static grp_status count_node_set(int64_t N, const SetScratch& t, int64_t* n, hipStream_t st);      // the rest, from bits
 // bits and before of the nodes that member(v) holds for, and their number n (waits for it).
 template <typename Member>
 static grp_status build_node_set(int64_t N, Member member, const SetScratch& t, int64_t* n, hipStream_t st) {
@@ -943,6 +995,9 @@ static grp_status build_node_set(int64_t N, Member member, const SetScratch& t, 
     if (N <= 0) return GRP_OK;
     hipLaunchKernelGGL(node_bits_kernel<Member>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words, member, t.bits);
     GRP_LAUNCH_CHECK();
+    return count_node_set(N, t, n, st);
+}
+static grp_status count_node_set(int64_t N, const SetScratch& t, int64_t* n, hipStream_t st) {
     GRP_TRY(exclusive_scan_popcount(t.scan, t.scan_bytes, t.bits, t.before, t.n_words + 1, st));
     if (N >= ((int64_t)1 << 31)) {       // more than 32 bits may be needed to see that there are too many
         hipLaunchKernelGGL(count_bits_kernel, dim3(4096), dim3(256), 0, st, (const uint32_t*)t.bits, t.n_words, t.counters + 3);
@@ -1011,16 +1066,11 @@ static grp_status partition_impl(const int64_t* src, const int64_t* dst, int64_t
         } else {
             ProfScope ps("partition_edge_scan_keys", st, 0.0, 16.0 * (double)E);
             uint32_t* const heads = (uint32_t*)((char*)idbuf.p + id_pitch);
-            hipLaunchKernelGGL((K & (K - 1)) == 0 ? edge_scan_keys_kernel<true> : edge_scan_keys_kernel<false>,
-                               dim3((unsigned)(scan_tiles < SCAN_GRID ? scan_tiles : SCAN_GRID)), dim3(SCAN_THREADS), 0, st, src, dst, E, (uint32_t)N, own, owned, (int)spans, (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(),
-                               (unsigned long long)cap, idbuf.as<uint32_t>(), (unsigned long long)id_cap, heads);
-                        int64_t parts = cdiv(256, spans);            // a workgroup per CU, a tile at least for each of its wavefronts
-            if (parts > cdiv(scan_tiles, 16)) parts = cdiv(scan_tiles, 16);
-            int at_once = 64;
-            while (at_once > 1 && parts * 16 * at_once > scan_tiles) at_once /= 2;
-            hipLaunchKernelGGL(rank_count_kernel, dim3((unsigned)spans, (unsigned)parts), dim3(1024), 0, st, (const uint32_t*)idbuf.as<uint32_t>(),
-                               (const uint32_t*)heads, scan_tiles, (int)spans, at_once, n, (unsigned long long*)h->d_global_in);
-            GRP_LAUNCH_CHECK();
+            auto go = [&](auto select) {
+                return launch_scan_keys(select, src, dst, E, N, own, n, spans, (unsigned long long*)h->d_global_in, t.counters, keybuf.as<uint64_t>(), cap,
+                                        idbuf.as<uint32_t>(), id_cap, heads, st);
+            };
+            GRP_TRY((K & (K - 1)) == 0 ? go(OwnedEdges<true>{owned}) : go(OwnedEdges<false>{owned}));
         }
         GRP_HIP(hipMemcpyAsync(host_counters, t.counters, sizeof host_counters, hipMemcpyDeviceToHost, st));
         GRP_HIP(hipStreamSynchronize(st));
@@ -1142,20 +1192,48 @@ static grp_status weighted_build(const int64_t* src, const int64_t* dst, const f
     return GRP_OK;
 }
 
+// The sources of edges whose destination is in `inner` are flagged.  (Memberships come from a bitmap in the L2, a flag is a byte: every
+// writer stores the same value.  A bitmap of the new members would take an atomic each: 2e7 edges, 2.4e6 nodes 536 us, words of flags for both
+// 228, this way 137.)
 __global__ __launch_bounds__(256) void halo_grow_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
-                                                        int64_t E, int64_t N, const int32_t* __restrict__ inner,
-                                                        int32_t* __restrict__ member, unsigned long long* __restrict__ bad) {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < E; e += (int64_t)gridDim.x * 256) {
-        const int64_t u = src[e], v = dst[e];
-        if (u < 0 || v < 0 || u >= N || v >= N) { atomicAdd(bad, 1ull); continue; }
-        if (inner[v]) member[u] = 1;              // every writer stores the same value
+                                                        int64_t E, int64_t N, const uint32_t* __restrict__ inner,
+                                                        uint8_t* __restrict__ flag, unsigned long long* __restrict__ bad) {
+    const bool vec = (((uintptr_t)src | (uintptr_t)dst) & 15) == 0;
+    constexpr int PER = 8;
+    unsigned long long odd = 0;
+    for (int64_t t0 = (int64_t)blockIdx.x * (256 * PER); t0 < E; t0 += (int64_t)gridDim.x * (256 * PER)) {
+        int64_t us[PER], vs[PER];
+#pragma unroll
+        for (int i = 0; i < PER; i += 2) {
+            const int64_t e = t0 + (int64_t)i * 256 + 2 * threadIdx.x;
+            load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
+            load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);      // -2: past the end
+        }
+        uint32_t in[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
+            odd += !ok && vs[i] != -2;
+            in[i] = inner[ok ? vs[i] >> 5 : 0];
+            if (!ok) in[i] = 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if ((in[i] >> (vs[i] & 31)) & 1u) flag[us[i]] = 1;
     }
+    for (int o = 32; o > 0; o >>= 1) odd += __shfl_down(odd, o, 64);
+    if ((threadIdx.x & 63) == 0 && odd) atomicAdd(bad, odd);
 }
+struct GrownMember {
+    const uint32_t* inner;
+    const uint8_t* flag;
+    __device__ __forceinline__ bool operator()(int64_t v) const { return ((inner[v >> 5] >> (v & 31)) & 1u) || flag[v]; }
+};
 
-// Global in-degree of the members and the number of kept edges (destination in `inner`).
+// Global in-degree of the members and the number of kept edges (destination in `inner`): partitions of more nodes than
+// edge_scan_keys_kernel orders.
 __global__ __launch_bounds__(256) void halo_scan_kernel(const int64_t* __restrict__ src, const int64_t* __restrict__ dst,
-                                                        int64_t E, const int32_t* __restrict__ member,
-                                                        const int32_t* __restrict__ inner, const int64_t* __restrict__ pos,
+                                                        int64_t E, NodeSet own, const uint32_t* __restrict__ inner,
                                                         unsigned long long* __restrict__ dg,
                                                         unsigned long long* __restrict__ kept_out) {
     __shared__ int32_t slot_key[DG_SLOTS];               // in-degree counts go through an LDS table (see edge_scan_kernel)
@@ -1165,8 +1243,8 @@ __global__ __launch_bounds__(256) void halo_scan_kernel(const int64_t* __restric
     unsigned long long kept = 0;
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < E; e += (int64_t)gridDim.x * 256) {
         const int64_t v = dst[e];
-        if (member[v]) dg_table_add(slot_key, slot_count, dg, (int32_t)pos[v]);
-        if (inner[v]) kept++;
+        if (set_has(own, v)) dg_table_add(slot_key, slot_count, dg, set_rank(own, v));
+        kept += (inner[v >> 5] >> (v & 31)) & 1u;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < DG_SLOTS; i += 256)
@@ -1175,54 +1253,42 @@ __global__ __launch_bounds__(256) void halo_scan_kernel(const int64_t* __restric
     if ((threadIdx.x & 63) == 0 && kept) atomicAdd(kept_out, kept);
 }
 
-__global__ __launch_bounds__(256) void halo_nodes_kernel(int64_t N, const int32_t* __restrict__ member,
-                                                         const int32_t* __restrict__ owned, const int64_t* __restrict__ pos,
-                                                         int64_t* __restrict__ l2g, uint8_t* __restrict__ owned_mask) {
+__global__ __launch_bounds__(256) void halo_owned_kernel(int64_t N, NodeSet own, const uint32_t* __restrict__ owned, uint8_t* __restrict__ owned_mask) {
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v < N && member[v]) {
-        l2g[pos[v]] = v;
-        owned_mask[pos[v]] = owned[v] ? 1 : 0;
-    }
+    if (v < N && set_has(own, v)) owned_mask[set_rank(own, v)] = (uint8_t)((owned[v >> 5] >> (v & 31)) & 1u);
 }
 
 static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, int64_t E, int64_t N, int32_t K, uint64_t seed,
                                       int32_t part_id, int32_t hops, hipStream_t st, grp_partition_t* h) {
-    DevBuf owned, member, inner, pos, counters, scan_tmp;
-    GRP_TRY(owned.alloc((size_t)N * sizeof(int32_t)));
-    GRP_TRY(member.alloc((size_t)N * sizeof(int32_t)));
-    GRP_TRY(inner.alloc((size_t)N * sizeof(int32_t)));
-    GRP_TRY(pos.alloc((size_t)N * sizeof(int64_t)));
-    GRP_TRY(counters.alloc(3 * sizeof(unsigned long long)));          // [0] kept, [1] bad ids, [2] key cursor
-    GRP_HIP(hipMemsetAsync(counters.p, 0, 3 * sizeof(unsigned long long), st));
+    SetScratch t;                                        // the members; counters: [0] kept, [1] bad ids, [2] key cursor, [3] ids
+    DevBuf slab, bits;
+    GRP_TRY(t.alloc(N, slab));
+    GRP_TRY(bits.alloc(2 * ((size_t)t.n_words + 1) * sizeof(uint32_t) + (size_t)t.n_words * 32));
+    uint32_t* const owned = bits.as<uint32_t>();
+    uint32_t* const inner = owned + t.n_words + 1;       // the members before the last hop
+    uint8_t* const flag = (uint8_t*)(inner + t.n_words + 1);
+    const size_t bits_bytes = ((size_t)t.n_words + 1) * sizeof(uint32_t);
+    GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
     int64_t n = 0;
     if (N > 0) {
-        hipLaunchKernelGGL(owner_flag_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, owner_test(seed, (uint32_t)K, (uint32_t)part_id),
-                           owned.as<int32_t>());
+        const OwnerTest test = owner_test(seed, (uint32_t)K, (uint32_t)part_id);
+        hipLaunchKernelGGL(node_bits_kernel<OwnerTest>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words, test, owned);
         GRP_LAUNCH_CHECK();
-        GRP_HIP(hipMemcpyAsync(member.p, owned.p, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+        GRP_HIP(hipMemcpyAsync(t.bits, owned, bits_bytes, hipMemcpyDeviceToDevice, st));
+        GRP_HIP(hipMemsetAsync(flag, 0, (size_t)t.n_words * 32, st));
         for (int hop = 0; hop < hops; ++hop) {
-            GRP_HIP(hipMemcpyAsync(inner.p, member.p, (size_t)N * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
+            GRP_HIP(hipMemcpyAsync(inner, t.bits, bits_bytes, hipMemcpyDeviceToDevice, st));
             if (E > 0) {
-                hipLaunchKernelGGL(halo_grow_kernel, dim3(grid_for(E)), dim3(256), 0, st, src, dst, E, N, inner.as<int32_t>(),
-                                   member.as<int32_t>(), counters.as<unsigned long long>() + 1);
+                hipLaunchKernelGGL(halo_grow_kernel, dim3(grid_for(cdiv(E, 8))), dim3(256), 0, st, src, dst, E, N, (const uint32_t*)inner, flag, t.counters + 1);
+                hipLaunchKernelGGL(node_bits_kernel<GrownMember>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words,
+                                   GrownMember{inner, flag}, t.bits);
                 GRP_LAUNCH_CHECK();
             }
         }
-        size_t bytes = 0;
-        GRP_HIP(rocprim::exclusive_scan(nullptr, bytes, member.as<int32_t>(), pos.as<int64_t>(), (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-        GRP_TRY(scan_tmp.alloc(bytes));
-        GRP_HIP(rocprim::exclusive_scan(scan_tmp.p, bytes, member.as<int32_t>(), pos.as<int64_t>(), (int64_t)0, (size_t)N,
-                                        rocprim::plus<int64_t>(), st));
-        int64_t last_pos = 0;
-        int32_t last_flag = 0;
         unsigned long long nbad = 0;
-        GRP_HIP(hipMemcpyAsync(&last_pos, pos.as<int64_t>() + (N - 1), sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipMemcpyAsync(&last_flag, member.as<int32_t>() + (N - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipMemcpyAsync(&nbad, counters.as<unsigned long long>() + 1, sizeof nbad, hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipStreamSynchronize(st));
+        GRP_HIP(hipMemcpyAsync(&nbad, t.counters + 1, sizeof nbad, hipMemcpyDeviceToHost, st));
+        GRP_TRY(count_node_set(N, t, &n, st));           // (waits)
         if (nbad) return fail(GRP_ERANGE, "edges have an endpoint outside [0, %lld)", (long long)N);
-        n = last_pos + last_flag;
     }
     if (n >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "partition has %lld >= 2^31 local nodes", (long long)n);
     h->n = n;
@@ -1230,32 +1296,49 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     GRP_TRY(halloc(&h->d_global_in, n));
     GRP_TRY(halloc(&h->base_mask, n));
     GRP_HIP(hipMemsetAsync(h->d_global_in, 0, (size_t)(n > 0 ? n : 1) * sizeof(int64_t), st));
-    unsigned long long kept = 0;
+    GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
+    const NodeSet own{t.words};
     if (N > 0) {
-        hipLaunchKernelGGL(halo_nodes_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, member.as<int32_t>(),
-                           owned.as<int32_t>(), pos.as<int64_t>(), h->l2g, h->base_mask);
+        hipLaunchKernelGGL(set_nodes_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, (const uint32_t*)t.bits, (const int32_t*)t.before,
+                           t.words, h->l2g);
+        hipLaunchKernelGGL(halo_owned_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, own, (const uint32_t*)owned, h->base_mask);
         GRP_LAUNCH_CHECK();
     }
-    if (E > 0) {
+    // As a hash build (partition_impl): one pass writes the keys too, into a buffer for twice the expected edges of a single hop.
+    const int64_t spans = cdiv(n > 0 ? n : 1, (int64_t)1 << SPAN_BITS);
+    const bool ranged = N < ((int64_t)1 << 31) && spans <= SPANS_MAX && E > 0;
+    const HaloEdges select{inner};
+    unsigned long long host[3] = {0, 0, 0};
+    DevBuf keys, keys_alt, idbuf;
+    int64_t cap = 0;
+    if (ranged) {
+        cap = std::min<int64_t>(E, hops == 1 ? 2 * (E / K) + (1 << 20) : (int64_t)1 << 28);
+        const int64_t id_cap = std::min<int64_t>(E, (int64_t)1 << 30);
+        const size_t id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
+        GRP_TRY(keys.alloc((size_t)cap * sizeof(uint64_t)));
+        GRP_TRY(idbuf.alloc(id_pitch + (size_t)cdiv(E, SCAN_TILE) * (size_t)(spans + 1) * sizeof(uint32_t)));
+        GRP_TRY(launch_scan_keys(select, src, dst, E, N, own, n, spans, (unsigned long long*)h->d_global_in, t.counters, keys.as<uint64_t>(), cap,
+                                 idbuf.as<uint32_t>(), id_cap, (uint32_t*)((char*)idbuf.p + id_pitch), st));
+    } else if (E > 0) {
         const unsigned scan_grid = grid_for(E) < (unsigned)EDGE_SCAN_GRID ? grid_for(E) : (unsigned)EDGE_SCAN_GRID;
-        hipLaunchKernelGGL(halo_scan_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, member.as<int32_t>(),
-                           inner.as<int32_t>(), pos.as<int64_t>(), (unsigned long long*)h->d_global_in,
-                           counters.as<unsigned long long>());
+        hipLaunchKernelGGL(halo_scan_kernel, dim3(scan_grid), dim3(256), 0, st, src, dst, E, own, (const uint32_t*)inner,
+                           (unsigned long long*)h->d_global_in, t.counters);
         GRP_LAUNCH_CHECK();
-        GRP_HIP(hipMemcpyAsync(&kept, counters.p, sizeof kept, hipMemcpyDeviceToHost, st));
-        GRP_HIP(hipStreamSynchronize(st));
     }
-    const int64_t nnz = (int64_t)kept;
+    GRP_HIP(hipMemcpyAsync(host, t.counters, sizeof host, hipMemcpyDeviceToHost, st));
+    GRP_HIP(hipStreamSynchronize(st));
+    const int64_t nnz = (int64_t)(ranged ? host[2] : host[0]);
     h->nnz = nnz;
-    DevBuf keys, keys_alt;
-    GRP_TRY(keys.alloc((size_t)nnz * sizeof(uint64_t)));
-    GRP_TRY(keys_alt.alloc((size_t)nnz * sizeof(uint64_t)));
-    if (nnz > 0) {
-        hipLaunchKernelGGL(edge_keys_kernel<ArraySelect>, dim3(grid_for(E)), dim3(256), 0, st, src, dst, E,
-                           ArraySelect{inner.as<int32_t>(), pos.as<int64_t>(), 1}, counters.as<unsigned long long>() + 2,
+    if (nnz > cap) {                                     // not written yet, or not all of them
+        keys.free();
+        GRP_TRY(keys.alloc((size_t)nnz * sizeof(uint64_t)));
+        GRP_HIP(hipMemsetAsync(t.counters + 2, 0, sizeof(unsigned long long), st));
+        hipLaunchKernelGGL(edge_keys_kernel<HaloSelect>, dim3(grid_for(E)), dim3(256), 0, st, src, dst, E, HaloSelect{own, inner}, t.counters + 2,
                            keys.as<uint64_t>());
         GRP_LAUNCH_CHECK();
     }
+    idbuf.free();
+    GRP_TRY(keys_alt.alloc((size_t)nnz * sizeof(uint64_t)));
     return build_csr_csc(h, keys.as<uint64_t>(), keys_alt.as<uint64_t>(), st);
 }
 

@@ -49,11 +49,16 @@ def _assert_equal(part, want):
     ("rmat", 1 << 13, 400000, 1),           # the bound is raised to the largest bin: a slice per bin
     ("rmat", 300000, 50000, 9000),          # far more rows than edges: tiles whose row window exceeds LDS
     ("uniform", 3, 5000, 100),              # three nodes, long duplicate runs
+    ("rmat", 1 << 13, 400000, 0),           # all edges at once: buckets, some of them crowded
+    ("rmat", 300000, 50000, 0),             # far more rows than keys
+    ("one source", 2000, 1100000, 0),       # a bucket of more keys than one workgroup takes: refused, and sorted instead
 ])
 def test_from_csr_bit_exact(g, kind, n, E, slice_edges):
     _note(f"from_csr {kind} n={n} E={E} slice_edges={slice_edges}")
     if kind == "uniform":
         s, d = synth.uniform_graph(n, E, seed=31)
+    elif kind == "one source":
+        s, d = torch.full((E,), 5, dtype=torch.int64), torch.arange(E) % n
     else:
         s, d = synth.rmat_graph(max(2, (n - 1).bit_length()), E, seed=32, n_nodes=n)
     want = ograph.local_graph_from_edges(s.numpy(), d.numpy(), n)

@@ -23,7 +23,9 @@ def g():
 
 @pytest.mark.parametrize("kind,N,E,K,hops", [("uniform", 5000, 30000, 4, 1), ("uniform", 5000, 30000, 4, 2),
                                               ("rmat", 1 << 13, 100000, 8, 1), ("rmat", 1 << 13, 100000, 8, 3),
-                                              ("uniform", 400, 0, 2, 1)])
+                                              ("uniform", 400, 0, 2, 1),
+                                              # two ranges of local ids to count in-degrees by; a last tile of edges that is not whole
+                                              ("uniform", 30000, 200001, 3, 1), ("uniform", 30000, 60000, 2, 2)])
 def test_partition_halo_bit_exact(g, kind, N, E, K, hops):
     print(f"[case] halo partition {kind} N={N} E={E} K={K} hops={hops}", flush=True)
     if E == 0:
