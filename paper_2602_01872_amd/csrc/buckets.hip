@@ -326,11 +326,11 @@ __device__ __forceinline__ void radix_sort(uint32_t (&k)[BK_PER], int per, int b
 // alone 250 us, this way 160.)  A bucket of more than BK_CAP keys: see the top of the file.
 __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t* __restrict__ packed, int64_t nnz, int64_t n, BucketPlan p,
                                                                  BucketScratch s, BucketOut out, uint32_t* __restrict__ by_row) {
-    __shared__ uint32_t buf[BK_CAP];
+    __shared__ __attribute__((aligned(16))) uint32_t buf[BK_CAP];
     __shared__ uint32_t off[(1 << BK_ROW_BITS) + 1];       // first key of each row of the bucket
     __shared__ uint32_t sub_of[1 << BK_ROW_BITS];          // a row's first range << 5 | how far an id is shifted to its range
-    __shared__ union {
-        uint32_t sub[BK_SUBS + 1];                         // keys of each range, then where they begin
+    __shared__ union __attribute__((aligned(16))) {
+        uint32_t sub[BK_SUBS + 4];                         // keys of each range, then where they begin
         RadixLds radix;
     } u;
     __shared__ uint32_t wave_sum[BK_WAVES];
@@ -371,11 +371,29 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
         });
     }
     __syncthreads();
-    {   // pointers, degrees, and what the schedule of the long rows needs
-        uint32_t c[2], total;
+    auto ranges_log = [&](uint32_t d) {                    // a row of d keys has 2^this ranges
+        const uint32_t lg = d <= (uint32_t)BK_SUB ? 0u : 32u - __clz((d - 1u) / BK_SUB);
+        return lg > (uint32_t)p.id_bits ? (uint32_t)p.id_bits : lg;
+    };
+    uint32_t n_sub = 0;
+    {   // pointers, degrees, and what the schedule of the long rows needs; the ranges too where the bucket is sorted whole (one sum over both)
+        static_assert(BK_CAP < 1 << 16 && BK_SUBS < 1 << 16, "16 bits each");
+        uint32_t c[2], lg[2], total;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) c[q] = 2 * tid + q < rows ? off[2 * tid + q] : 0u;
-        uint32_t at = block_scan<BK_WAVES>(c[0] + c[1], wave_sum, total);
+        for (int q = 0; q < 2; ++q) {
+            c[q] = 2 * tid + q < rows ? off[2 * tid + q] : 0u;
+            lg[q] = ranges_log(c[q]);
+        }
+        const uint32_t parts0 = whole && c[0] ? 1u << lg[0] : 0u, parts1 = whole && c[1] ? 1u << lg[1] : 0u;
+        uint32_t at = block_scan<BK_WAVES>(c[0] + c[1] + (parts0 + parts1) * 65536u, wave_sum, total);
+        if (whole) {
+            n_sub = total >> 16;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * tid + q < rows) sub_of[2 * tid + q] = ((at >> 16) + (q ? parts0 : 0u)) << 5 | ((uint32_t)p.id_bits - lg[q]);
+            for (uint32_t i = 4 * tid; i < n_sub; i += 4 * BK_THREADS) *reinterpret_cast<uint4*>(&u.sub[i]) = make_uint4(0u, 0u, 0u, 0u);
+            at &= 0xFFFFu;
+        }
         unsigned long long longs = 0, edges = 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
@@ -502,15 +520,13 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
             }
             fetch(buf, m, per);
         }
-        uint32_t n_sub;
-        {
+        if (!whole) {
             uint32_t lg[2], parts = 0;
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int r = 2 * tid + q;
                 const uint32_t d = r >= ra && r < rb ? off[r + 1] - off[r] : 0u;
-                lg[q] = d <= (uint32_t)BK_SUB ? 0u : 32u - __clz((d - 1u) / BK_SUB);
-                if (lg[q] > (uint32_t)p.id_bits) lg[q] = (uint32_t)p.id_bits;
+                lg[q] = ranges_log(d);
                 parts += d ? 1u << lg[q] : 0u;
             }
             uint32_t at = block_scan<BK_WAVES>(parts, wave_sum, n_sub);
@@ -523,8 +539,8 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
                 }
             }
             for (uint32_t i = tid; i < n_sub; i += BK_THREADS) u.sub[i] = 0u;
+            __syncthreads();
         }
-        __syncthreads();
         auto range = [&](uint32_t key) {
             const uint32_t x = sub_of[key >> p.id_bits];
             return (x >> 5) + ((key & id_mask) >> (x & 31u));
@@ -534,43 +550,38 @@ __global__ __launch_bounds__(BK_THREADS) void bucket_sort_kernel(const uint32_t*
         for (int i = 0; i < BK_PER; ++i)
             if (on(i, m, per)) arrived[i] = atomicAdd(&u.sub[range(k[i])], 1u);
         __syncthreads();
-        constexpr int SUB_PER = (BK_SUBS + BK_THREADS - 1) / BK_THREADS;
-        uint32_t c[SUB_PER], sum = 0, most = 0, total;
-#pragma unroll
-        for (int q = 0; q < SUB_PER; ++q) {
-            const uint32_t i = SUB_PER * tid + q;
-            c[q] = i < n_sub ? u.sub[i] : 0u;
-            sum += c[q];
-            most = c[q] > most ? c[q] : most;
-        }
+        static_assert(BK_SUBS == 4 * BK_THREADS, "four ranges a thread: one access of LDS");
+        uint4 c = *reinterpret_cast<const uint4*>(&u.sub[4 * tid]);
+        c.x = 4 * tid < n_sub ? c.x : 0u; c.y = 4 * tid + 1 < n_sub ? c.y : 0u;
+        c.z = 4 * tid + 2 < n_sub ? c.z : 0u; c.w = 4 * tid + 3 < n_sub ? c.w : 0u;
+        const uint32_t most = max(max(c.x, c.y), max(c.z, c.w));
+        uint32_t total;
         const bool crowded = __syncthreads_or(most > (uint32_t)BK_SUB_MAX) != 0;
         if (crowded) {
             radix_sort(k, per, p.row_bits + p.id_bits, buf, u.radix);
             for (uint32_t i = tid; i < m; i += BK_THREADS) out.idx[dir][lo + base + i] = (int32_t)(buf[i] & id_mask);
         } else {
-            uint32_t at = block_scan<BK_WAVES>(sum, wave_sum, total);
-#pragma unroll
-            for (int q = 0; q < SUB_PER; ++q) {
-                const uint32_t i = SUB_PER * tid + q;
-                if (i <= n_sub) u.sub[i] = at;
-                at += c[q];
-            }
+            const uint32_t at = block_scan<BK_WAVES>((c.x + c.y) + (c.z + c.w), wave_sum, total);
+            *reinterpret_cast<uint4*>(&u.sub[4 * tid]) = make_uint4(at, at + c.x, at + c.x + c.y, at + c.x + c.y + c.z);
+            if (tid == BK_THREADS - 1) u.sub[BK_SUBS] = m;
+            if (tid < 3 && m + tid < (uint32_t)BK_CAP) buf[m + tid] = ~0u;       // (the last four that are read together)
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < BK_PER; ++i)
                 if (on(i, m, per)) buf[u.sub[range(k[i])] + arrived[i]] = k[i];
             __syncthreads();
+            // A key's place: behind the smaller ones, and behind its equals that stand before it.  Four keys at a time, whole aligned groups: what
+            // stands before the range is smaller, what stands behind it larger.
             for (uint32_t i = tid; i < m; i += BK_THREADS) {
-                const uint32_t key = buf[i], g = range(key), b0 = u.sub[g], b1 = u.sub[g + 1];
-                uint32_t rank = 0;
-                for (uint32_t j = b0; j < b1; j += 4) {    // (four reads in flight)
-                    uint32_t other[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) other[q] = buf[j + q < b1 ? j + q : i];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) rank += j + q < b1 && (other[q] < key || (other[q] == key && j + q < i)) ? 1u : 0u;
+                const uint32_t key = buf[i], g = range(key), j0 = u.sub[g] & ~3u, j1 = u.sub[g + 1];
+                uint32_t at_key = j0;
+#pragma unroll 1
+                for (uint32_t j = j0; j < j1; j += 4) {
+                    const uint4 o = *reinterpret_cast<const uint4*>(&buf[j]);
+                    at_key += (o.x < key || (o.x == key && j < i)) + (o.y < key || (o.y == key && j + 1 < i)) +
+                              (o.z < key || (o.z == key && j + 2 < i)) + (o.w < key || (o.w == key && j + 3 < i));
                 }
-                out.idx[dir][lo + base + b0 + rank] = (int32_t)(key & id_mask);
+                out.idx[dir][lo + base + at_key] = (int32_t)(key & id_mask);
             }
         }
         __syncthreads();                                   // buf is filled anew
