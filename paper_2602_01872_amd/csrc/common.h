@@ -365,7 +365,11 @@ struct GemmNNArgs {
     int64_t ldbt = 0;
     const float* Bt2 = nullptr;     // same for the second product
     int64_t ldbt2 = 0;
-    unsigned char* planes = nullptr;  // scratch of gemm_planes_bytes for B split once per launch (null: split in the kernel)
+    // Bt and Bt2 as planes that exist already (bt_planes_at), of ready_rows rows each, or null: then, if set, `planes` is scratch of
+    // gemm_planes_bytes for them to be made once per launch.  (Set by the launch too: what the kernel reads.)
+    const unsigned char *ready = nullptr, *ready2 = nullptr;
+    int32_t ready_rows = 0;
+    unsigned char* planes = nullptr;
     size_t planes_bytes = 0;
     // Row counts known on the device only: when set, M (and a_valid_rows) above are upper bounds that
     // size the launch, and the kernels read the real values here.
@@ -408,25 +412,51 @@ grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t ld
                                 float* out, void* scratch, hipStream_t st);
 // out[N] = sums over the rows of part[blocks x N].
 void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st);
-// Weight re-packing jobs of one step (at most four per layer), run by a single launch.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+// a, b -> packed pairs hi, mid, lo with a = hi.x + mid.x + lo.x exactly.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
+    const floatx2 r = {a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u)};
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+    const float la = r.x - __uint_as_float(mid << 16), lb = r.y - __uint_as_float(mid & 0xFFFF0000u);
+    lo = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+}
+// An operand B of an NT product as its kernels read it: split into three bf16 planes (fp32 = hi + mid + lo, exactly), in tiles of 32 k.
+// Tile kt, plane p and row n have 64 bytes at ((kt * 3 + p) * rows + n) * 64, in four places of eight k: place q ^ ((n >> 1) & 3) holds the k
+// 4 q .. 4 q + 3 and 16 + 4 q .. 16 + 4 q + 3.  Rows and k that do not exist are zero, up to bt_plane_rows rows (what tiles of any
+// width read) and whole tiles.
+inline int32_t bt_plane_rows(int64_t n) { return (int32_t)std::max(round_up(n, 128), round_up(n, 96)); }
+inline size_t bt_planes_bytes(int64_t k, int32_t rows) { return (size_t)cdiv(k, 32) * 3 * rows * 64; }
+__host__ __device__ inline int64_t bt_planes_at(int k, int n, int plane, int rows) {      // the byte of element (n, k)
+    const int kt = k >> 5, k32 = k & 31;
+    return ((int64_t)(kt * 3 + plane) * rows + n) * 64 + 16 * (((k32 & 15) >> 2) ^ ((n >> 1) & 3)) + 2 * ((k32 & 3) + (k32 >> 4) * 4);
+}
+// Weight re-packing jobs of one step (at most four per layer), run by a single launch: a matrix of the parameters, or its transpose,
+// times a scale, zero-padded, as fp32 and as planes.
 struct PackJob {
-    const float* in;
-    float* out;
-    int32_t rows, cols;      // shape of `in` (dense, pitch cols)
-    int32_t transpose;       // 0: out = in;  1: out = in^T
-    int64_t ld_out;
+    uint32_t in;             // element of the parameters
+    uint32_t out, planes;    // units of 16 bytes of the workspace (planes 0: none)
     float scale;             // every element is multiplied by this
+    uint16_t rows, cols;     // as written
+    uint16_t out_rows;       // fp32 rows written (zeros from `rows` on)
+    uint16_t ld4;            // their pitch in 16 bytes
+    uint16_t row0, plane_rows;     // the planes' row of the first row; their rows in all
+    uint16_t dom_rows;       // rows that this job writes to either
+    uint16_t transpose;      // the matrix is stored as [cols x rows]
 };
 template <int MOST> struct PackJobsOf {
+    const float* theta = nullptr;
+    char* base = nullptr;    // the workspace
     int32_t n = 0;
+    uint32_t begin[MOST + 1] = {0};      // pairs of elements
     PackJob job[MOST];
-    int64_t begin[MOST + 1] = {0};
 };
 using PackJobs = PackJobsOf<4 * GRP_MAX_LAYERS>;
-// Appends a job: the output is written with its columns zero-padded to a multiple of 4 and its
-// rows zero-padded to out_rows_pad.
+// Appends a job for the matrix in[rows x cols], or its transpose.  out: round_up(width, 4) columns and at least out_rows_pad rows.  planes
+// (may be null): from row plane_row0 on, up to plane_rows if last, else as many rows as out has.
 void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, bool transpose, int32_t out_rows_pad,
-                   float* out, int64_t ld_out, float scale = 1.f);
+                   float* out, int64_t ld_out, unsigned char* planes, int32_t plane_row0, int32_t plane_rows, bool last, float scale = 1.f);
 
 // Inverted dropout of a layer's output (rows = local nodes, F columns), in place:
 //   keep(v, f) = (mix(key + (l2g[node(v)] * F + f + 1) * GAMMA) >> 40) >= thresh;  a' = keep ? a * scale : 0.

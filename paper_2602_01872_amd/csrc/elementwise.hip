@@ -38,35 +38,43 @@ grp_status launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
     return GRP_OK;
 }
 
-// All weight re-packing jobs of a step in one launch: job j owns the flat element range
-// [begin_j, begin_{j+1}) of the grid and is either a zero-padded copy or a zero-padded transpose.
+// All weight re-packing jobs of a step in one launch: job j owns the pairs of elements [begin_j, begin_{j+1}) of the grid.
 template <int MOST>
 __device__ __forceinline__ void pack_weights_block(uint32_t block, const PackJobsOf<MOST>& jobs) {
-    const int64_t e0 = (int64_t)block * 256 + threadIdx.x;
+    const uint32_t e0 = block * 256 + threadIdx.x;
     if (e0 >= jobs.begin[jobs.n]) return;
     int j = 0;
     while (e0 >= jobs.begin[j + 1]) ++j;
     const PackJob& J = jobs.job[j];
-    const int64_t e = e0 - jobs.begin[j];
-    if (J.transpose) {        // out[cols x rows] = in[rows x cols]^T; pad columns and rows [cols, out_rows_pad) are zero
-        const int width = (J.rows + 3) & ~3;
-        const int r = (int)(e / width), c = (int)(e % width);
-        J.out[(int64_t)r * J.ld_out + c] = (r < J.cols && c < J.rows) ? J.in[(int64_t)c * J.cols + r] * J.scale : 0.f;
-    } else {                  // out[rows x cols] = in; pad columns and rows [rows, out_rows_pad) are zero
-        const int width = (J.cols + 3) & ~3;
-        const int r = (int)(e / width), c = (int)(e % width);
-        J.out[(int64_t)r * J.ld_out + c] = (r < J.rows && c < J.cols) ? J.in[(int64_t)r * J.cols + c] * J.scale : 0.f;
+    const uint32_t pairs = (uint32_t)(J.planes ? (J.cols + 31) / 32 * 16 : (J.cols + 3) / 4 * 2), e = e0 - jobs.begin[j];      // of a row
+    const int r = (int)(e / pairs), c = 2 * (int)(e % pairs);
+    const float* const in = jobs.theta + J.in;
+    auto at = [&](int k) { return r < J.rows && k < J.cols ? in[J.transpose ? (int64_t)k * J.rows + r : (int64_t)r * J.cols + k] * J.scale : 0.f; };
+    const float v0 = at(c), v1 = at(c + 1);
+    if (r < J.out_rows && c < 4 * ((J.cols + 3) / 4)) *reinterpret_cast<float2*>(jobs.base + 16 * ((int64_t)J.out + (int64_t)r * J.ld4) + 4 * c) = make_float2(v0, v1);
+    if (J.planes) {
+        uint32_t part[3];
+        split2(v0, v1, part[0], part[1], part[2]);
+        char* const planes = jobs.base + 16 * (int64_t)J.planes;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint32_t*>(planes + bt_planes_at(c, r + J.row0, p, J.plane_rows)) = part[p];
     }
 }
 void pack_jobs_add(PackJobs& jobs, const float* in, int32_t rows, int32_t cols, bool transpose, int32_t out_rows_pad,
-                   float* out, int64_t ld_out, float scale) {
+                   float* out, int64_t ld_out, unsigned char* planes, int32_t plane_row0, int32_t plane_rows, bool last, float scale) {
     PackJob& J = jobs.job[jobs.n];
-    J.in = in; J.out = out; J.rows = rows; J.cols = cols; J.transpose = transpose ? 1 : 0; J.ld_out = ld_out;
+    J.in = (uint32_t)(in - jobs.theta);
+    J.out = (uint32_t)(((char*)out - jobs.base) / 16);
+    J.planes = planes ? (uint32_t)(((char*)planes - jobs.base) / 16) : 0u;
     J.scale = scale;
-    const int32_t out_rows = transpose ? cols : rows;
-    if (out_rows_pad < out_rows) out_rows_pad = out_rows;
-    const int64_t width = round_up(transpose ? rows : cols, 4);
-    jobs.begin[jobs.n + 1] = jobs.begin[jobs.n] + (int64_t)out_rows_pad * width;
+    J.rows = (uint16_t)(transpose ? cols : rows); J.cols = (uint16_t)(transpose ? rows : cols);
+    J.out_rows = (uint16_t)std::max<int32_t>(out_rows_pad, J.rows);
+    J.ld4 = (uint16_t)(ld_out / 4);
+    J.row0 = (uint16_t)plane_row0; J.plane_rows = (uint16_t)plane_rows;
+    J.dom_rows = planes && last ? (uint16_t)(plane_rows - plane_row0) : J.out_rows;
+    J.transpose = transpose ? 1 : 0;
+    const uint32_t pairs = planes ? (uint32_t)round_up(J.cols, 32) / 2 : (uint32_t)round_up(J.cols, 4) / 2;
+    jobs.begin[jobs.n + 1] = jobs.begin[jobs.n] + J.dom_rows * pairs;
     ++jobs.n;
 }
 
@@ -510,7 +518,7 @@ grp_status launch_prelude(const StepPrelude& pre, hipStream_t st) {
     constexpr int FEW = 12;                            // three layers: arguments of several steps fit one launch
     if (pre.pack.n <= FEW) {
         PackJobsOf<FEW> few;
-        few.n = pre.pack.n;
+        few.n = pre.pack.n; few.theta = pre.pack.theta; few.base = pre.pack.base;
         for (int j = 0; j < few.n; ++j) few.job[j] = pre.pack.job[j];
         for (int j = 0; j <= few.n; ++j) few.begin[j] = pre.pack.begin[j];
         launch(prelude_kernel<FEW>, prelude_kernel_op<FEW>(), grid, st, a, pre.degrees, degree_blocks, few);

@@ -45,7 +45,7 @@ constexpr int BK = 32;      // k-tile depth
 // 338 with two; TN with two 32 x 32 tiles per wavefront: K = 256, N = 47 129 and 112 us, with four: 1127 and 323).
 constexpr int nt_wgs(int TN, bool pre) { return TN >= 8 && !pre ? 2 : 3; }
 constexpr int tn_wgs(int tiles) { return tiles > 1 ? 2 : 3; }
-constexpr int NT_PRE_SLABS = 512;      // products over fewer slabs of 128 rows split B in the kernel (a launch for the planes costs 3 us)
+constexpr int NT_PRE_SLABS = 512;      // products over fewer slabs of 128 rows whose B is not ready split it in the kernel (a launch for the planes costs 3 us)
 constexpr int NXCD = 8;     // L2 domains; consecutive workgroup ids go round them
 
 template <typename T> __device__ __forceinline__ float to_f(T v);
@@ -93,18 +93,8 @@ __device__ __forceinline__ int64_t lmin(int64_t a, int64_t b) { return a < b ? a
 
 // ------------------------------------------------------------------------------- fp32 as three bf16 planes
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// a, b -> packed pairs hi, mid, lo with a = hi.x + mid.x + lo.x exactly.
-__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
-    const floatx2 r = {a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u)};
-    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
-    const float la = r.x - __uint_as_float(mid << 16), lb = r.y - __uint_as_float(mid & 0xFFFF0000u);
-    lo = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
-}
 __device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& mid, uint4& lo) {
     split2(v[0], v[1], hi.x, mid.x, lo.x);
     split2(v[2], v[3], hi.y, mid.y, lo.y);
@@ -482,12 +472,13 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(GemmNNArgs g) {
 // an operand are clamped to its last row (their products are not stored); only the last, ragged k-tile of a product
 // is masked.
 // IRREG selects the variant with gathered (a_rows), limited (a_valid_rows) or tightly packed (a_tight) A rows.
-// PRE: B comes as planes (g.planes, split_b_kernel below) whose 1 KB runs are copied from memory to LDS without passing
+// PRE: B comes as planes (g.ready: of a step's weights by the launch that re-packs them, else split_b_kernel below) whose 1 KB runs are copied from memory to LDS without passing
 // through registers.  The loop is bound by issue: matrix and vector instructions of a SIMD's wavefronts add up (N = 512, K = 256: per
 // k-tile 128 of the former of 16 cycles and 350 of the latter of 4, 2048 + 1400 cycles; 3360 measured), and the split of B, which
 // every slab of 128 rows does again otherwise, would add to the latter and to the registers.  With and without, in us: the four 128-wide
 // products of a SAGE step on 3e5 rows 1652 and 1997, those of a residual GCN-8 step on 2^20 rows 14.1 and 16.5 ms, a bf16 one over
-// 8.4e6 rows (K = 64 + 64) 2.74 and 3.30 ms.
+// 8.4e6 rows (K = 64 + 64) 2.74 and 3.30 ms.  Products of few rows, whose every workgroup would split all of B for 64 rows: K = 256 + 256, N = 172 ..
+// 256 over 1e3 .. 1e4 rows 15.0 -> 13.2, gathered bf16 K = 128 + 128 over 2e4 37 -> 35, K = 130 over 1e5 a ragged step 612 -> 594.
 // One element of the product, added up in plain fp32 along k (up to the first NaN: a diverged step has them everywhere).
 template <typename AT>
 __device__ __forceinline__ float nt_plain(const GemmNNArgs& g, int64_t m, int n) {
@@ -589,12 +580,12 @@ __device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
     const int swave = __builtin_amdgcn_readfirstlane(wave);
     auto copy_b = [&](int kt) {
         constexpr int RUNS = 3 * BN / 16, PER_PLANE = BN / 16;
-        const int64_t n_all = (int64_t)n_tiles * BN;
+        const unsigned char* const tile = (kt < nk1 ? g.ready : g.ready2) + (int64_t)(kt < nk1 ? kt : kt - nk1) * 3 * g.ready_rows * 64;
 #pragma unroll
         for (int r = 0; r < (RUNS + 3) / 4; ++r) {
             const int c = swave + 4 * r;
             if (RUNS % 4 != 0 && c >= RUNS) break;
-            const unsigned char* const from = g.planes + (((int64_t)kt * 3 + c / PER_PLANE) * n_all + n0 + 16 * (c % PER_PLANE)) * 64;
+            const unsigned char* const from = tile + ((int64_t)(c / PER_PLANE) * g.ready_rows + n0 + 16 * (c % PER_PLANE)) * 64;
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                          :: "s"(lds_at + (kt & 1) * 3 * PLANE + c * 1024), "v"(lane * 16), "s"(from) : "memory", "m0");
         }
@@ -927,8 +918,7 @@ struct gemm_nt_kernel_op {
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { gemm_nt_kernel_body<AT, TM, TN, IRREG, PRE>(gx, a...); }
 };
 
-// The operand(s) B of a product as the planes that the PRE kernels copy: tile kt of 32 k (those of the second product follow the
-// first's), plane, row n < n_all, 64 bytes laid out as the kernel's LDS rows are.  Rows and k that do not exist are zero.
+// Bt as planes (bt_planes_at).
 __global__ __launch_bounds__(256) void split_b_kernel(const float* __restrict__ Bt, int64_t ldbt, int K, const float* __restrict__ Bt2,
                                                       int64_t ldbt2, int K2, int N, int n_all, unsigned char* __restrict__ planes) {
     const int e = blockIdx.x * 256 + threadIdx.x;
@@ -946,9 +936,8 @@ __global__ __launch_bounds__(256) void split_b_kernel(const float* __restrict__ 
     }
     uint4 part[3];
     split8(v, part[0], part[1], part[2]);
-    unsigned char* const out = planes + ((int64_t)kt * 3 * n_all + n) * 64 + 16 * (q ^ ((n >> 1) & 3));
 #pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(out + (int64_t)p * n_all * 64) = part[p];
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(planes + bt_planes_at(kt * BK + 4 * q, n, p, n_all)) = part[p];
 }
 
 size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K) {
@@ -961,7 +950,8 @@ struct NtPlan {
     int tile_m, tile_n;
     int n_all;               // columns that the tiles cover
     size_t planes_need;
-    bool pre;                // B is split once, into a.planes
+    bool pre;                // B is read as planes: a.ready, or made once in a.planes
+    bool large;              // launched by itself
 };
 static NtPlan nt_plan(const GemmNNArgs& a, int n_eff) {
     NtPlan p;
@@ -984,7 +974,8 @@ static NtPlan nt_plan(const GemmNNArgs& a, int n_eff) {
     // Both k tilings and the padding fit what gemm_planes_bytes reserved for this N and K + K2.
     p.n_all = (int)cdiv(n_eff, p.tile_n) * p.tile_n;
     p.planes_need = (size_t)(cdiv(a.K, BK) + cdiv(a.K2, BK)) * 3 * p.n_all * 64;
-    p.pre = p.tile_m == 128 && p.tile_n >= 64 && a.planes && cdiv(m_plan, 128) >= NT_PRE_SLABS && p.planes_need <= a.planes_bytes;
+    p.large = cdiv(m_plan, 128) >= NT_PRE_SLABS;
+    p.pre = a.ready || (p.tile_m == 128 && p.tile_n >= 64 && a.planes && p.large && p.planes_need <= a.planes_bytes);
     return p;
 }
 
@@ -1044,17 +1035,23 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         const bool irreg = t.a_tight || a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
         const int64_t slabs = round_up(cdiv(a.M, p.tile_m), NXCD);
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, p.tile_n));
-        const bool pre = p.pre;
-        if (pre)
+        if (p.pre && !a.ready) {
             GRP_LARGE_LAUNCH(split_b_kernel, dim3((unsigned)cdiv((int64_t)p.planes_need / 48, 256)), dim3(256), 0, st, a.Bt, a.ldbt, a.K, a.Bt2,
                                a.ldbt2, a.K2, a.N, p.n_all, a.planes);
+            t.ready = a.planes;
+            t.ready2 = a.planes + (int64_t)cdiv(a.K, BK) * 3 * p.n_all * 64;
+            t.ready_rows = p.n_all;
+        }
+        // (the products of a step have their planes ready: only those launches are merged)
+#define GRP_NT_LAUNCH3(AT, TM_, TN_, IRR)                                                                                  \
+    do {                                                                                                                   \
+        if (p.pre && p.large) GRP_LARGE_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, IRR, true>), dim3(blocks), dim3(256), 0, st, t); \
+        else if (p.pre) launch(gemm_nt_kernel<AT, TM_, TN_, IRR, true>, gemm_nt_kernel_op<AT, TM_, TN_, IRR, true>(), dim3(blocks), st, t); \
+        else launch_alone((gemm_nt_kernel<AT, TM_, TN_, IRR, false>), dim3(blocks), dim3(256), 0, st, t);                    \
+    } while (0)
 #define GRP_NT_LAUNCH2(AT, TM_, TN_)                                                                                       \
     do {                                                                                                                   \
-        constexpr bool P_ = TM_ == 2 && TN_ >= 4;                                                                          \
-        if (P_ && pre && irreg) GRP_LARGE_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, true, P_>), dim3(blocks), dim3(256), 0, st, t); \
-        else if (P_ && pre) GRP_LARGE_LAUNCH((gemm_nt_kernel<AT, TM_, TN_, false, P_>), dim3(blocks), dim3(256), 0, st, t); \
-        else if (irreg) launch(gemm_nt_kernel<AT, TM_, TN_, true>, gemm_nt_kernel_op<AT, TM_, TN_, true>(), dim3(blocks), st, t);       \
-        else launch(gemm_nt_kernel<AT, TM_, TN_, false>, gemm_nt_kernel_op<AT, TM_, TN_, false>(), dim3(blocks), st, t);                 \
+        if (irreg) GRP_NT_LAUNCH3(AT, TM_, TN_, true); else GRP_NT_LAUNCH3(AT, TM_, TN_, false);                           \
     } while (0)
 #define GRP_NT_LAUNCH(TM_, TN_)                                                                                            \
     do {                                                                                                                   \
@@ -1065,6 +1062,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         else if (p.tile_n == 96) GRP_NT_LAUNCH(2, 6);
         else if (p.tile_n == 64) GRP_NT_LAUNCH(2, 4);
         else GRP_NT_LAUNCH(2, 2);
+#undef GRP_NT_LAUNCH3
 #undef GRP_NT_LAUNCH2
 #undef GRP_NT_LAUNCH
         GRP_LAUNCH_CHECK();

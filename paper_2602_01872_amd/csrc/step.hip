@@ -28,6 +28,10 @@ struct LayerBufs {
     float* Act = nullptr;    // [rows x ld(Fout)] ReLU(z) of a residual layer (its derivative mask)
     int64_t off_ws = 0, off_wn = 0, off_b = 0;
     int64_t ldwp = 0, ldwt = 0;   // pitches of Wp_* / Wt_* (SAGE keeps [W_neigh | W_self] side by side)
+    // Their planes (bt_planes_at), as the layer's products read them: of one stack (t_stack, p_stack: _n holds both), or of each alone.
+    unsigned char *Pt_s = nullptr, *Pt_n = nullptr, *Pp_s = nullptr, *Pp_n = nullptr;
+    int32_t t_rows = 0, p_rows = 0;
+    bool t_stack = false, p_stack = false;
     bool agg_first = false;
     bool skip = false;       // residual GCN: H_out = H_in + ReLU(z)
 };
@@ -41,8 +45,7 @@ struct StepPlan {
     void *tn_ws = nullptr, *colsum_ws = nullptr, *stats_ws = nullptr, *sampler_ws = nullptr;
     float* partials = nullptr;   // partial rows of the split long rows (SpMM)
     size_t tn_ws_bytes = 0, sampler_bytes = 0;
-    unsigned char* planes = nullptr;   // the weights of the product at hand, split (GemmNNArgs::planes)
-    size_t planes_bytes = 0;
+    char* base = nullptr;        // the workspace
     size_t total = 0;
 };
 
@@ -82,6 +85,42 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
     // partial rows of the split long rows: one per task of the sliced schedule, else one per chunk
     auto slots = [](const LongRows& lr) { return lr.n_tasks > 0 ? lr.n_tasks : (int64_t)lr.n_chunks; };
     int64_t chunks_cap = slots(part->csr_long) > slots(part->csc_long) ? slots(part->csr_long) : slots(part->csc_long);
+    // the weights first: what the re-packing launch writes lies within reach of 32-bit units of 16 bytes, behind one that is never written
+    p.base = (char*)ws;
+    (void)b.take<float>(4);
+    p.L.resize(k);
+    int64_t off = 0;
+    for (int l = 0; l < k; ++l) {
+        LayerBufs& L = p.L[l];
+        const int fin = m->dims[l], fout = m->dims[l + 1];
+        L.off_ws = off; off += (int64_t)fin * fout;
+        if (sage) { L.off_wn = off; off += (int64_t)fin * fout; }
+        L.off_b = off; off += fout;
+        L.agg_first = sage && (fin <= fout || (mb && l == 0));
+        L.ldwp = ldp(fout);
+        L.ldwt = ldp(fin);
+        if (sage) {
+            // W_neigh stacked on top of W_self (row offset rounded up to 4, pad rows zero), so that
+            // one product can span both: [.. | ..] = X [Wn | Ws] reads the stack as one Bt.
+            float* wp = b.take<float>((size_t)2 * ldp(fin) * L.ldwp);
+            float* wt = b.take<float>((size_t)2 * ldp(fout) * L.ldwt);
+            L.Wp_n = wp; L.Wp_s = measure_only(wp) ? nullptr : wp + ldp(fin) * L.ldwp;
+            L.Wt_n = wt; L.Wt_s = measure_only(wt) ? nullptr : wt + ldp(fout) * L.ldwt;
+            L.t_stack = !L.agg_first && !mb;
+            L.p_stack = L.agg_first;
+        } else {
+            L.Wp_s = b.take<float>((size_t)ldp(fin) * ldp(fout));
+            L.Wt_s = b.take<float>((size_t)ldp(fout) * ldp(fin));
+        }
+        L.t_rows = bt_plane_rows(L.t_stack ? 2 * ldp(fout) : ldp(fout));
+        L.p_rows = bt_plane_rows(L.p_stack ? 2 * ldp(fin) : ldp(fin));
+        if (sage) L.Pt_n = b.take<unsigned char>(bt_planes_bytes(fin, L.t_rows));
+        if (!L.t_stack) L.Pt_s = b.take<unsigned char>(bt_planes_bytes(fin, L.t_rows));
+        if (l > 0) {
+            if (sage) L.Pp_n = b.take<unsigned char>(bt_planes_bytes(fout, L.p_rows));
+            if (!L.p_stack) L.Pp_s = b.take<unsigned char>(bt_planes_bytes(fout, L.p_rows));
+        }
+    }
     if (mb) {
         sampler_bounds(n, o->n_seeds, o->fanouts, k, &bd);
         p.sampler_bytes = sampler_workspace_bytes(n, bd, k);
@@ -92,9 +131,8 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
             if (c > chunks_cap) chunks_cap = c;
         }
     }
-    p.L.resize(k);
-    int64_t off = 0, fmax = 0, max_rows = 1;
-    size_t tn_bytes = 0, cs_bytes = 0, pl_bytes = 0;
+    int64_t fmax = 0, max_rows = 1;
+    size_t tn_bytes = 0, cs_bytes = 0;
     for (int l = 0; l < k; ++l) {
         LayerBufs& L = p.L[l];
         const int fin = m->dims[l], fout = m->dims[l + 1];
@@ -102,27 +140,8 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         const int64_t rows_in = mb ? (l == 0 ? bd.dst[0] : bd.src[l]) : n;
         if (rows > max_rows) max_rows = rows;
         if (rows_in > max_rows) max_rows = rows_in;
-        L.off_ws = off; off += (int64_t)fin * fout;
-        if (sage) { L.off_wn = off; off += (int64_t)fin * fout; }
-        L.off_b = off; off += fout;
-        L.agg_first = sage && (fin <= fout || (mb && l == 0));
         L.skip = m->arch == GRP_ARCH_GCN_RESIDUAL && fin == fout && l < k - 1;
-        if (sage) {
-            // W_neigh stacked on top of W_self (row offset rounded up to 4, pad rows zero), so that
-            // one product can span both: [.. | ..] = X [Wn | Ws] reads the stack as one Bt.
-            L.ldwp = ldp(fout);
-            L.ldwt = ldp(fin);
-            float* wp = b.take<float>((size_t)2 * ldp(fin) * L.ldwp);
-            float* wt = b.take<float>((size_t)2 * ldp(fout) * L.ldwt);
-            L.Wp_n = wp; L.Wp_s = measure_only(wp) ? nullptr : wp + ldp(fin) * L.ldwp;
-            L.Wt_n = wt; L.Wt_s = measure_only(wt) ? nullptr : wt + ldp(fout) * L.ldwt;
-            if (L.agg_first) L.M = b.take<float>((size_t)rows * ldp(fin));
-        } else {
-            L.ldwp = ldp(fout);
-            L.ldwt = ldp(fin);
-            L.Wp_s = b.take<float>((size_t)ldp(fin) * ldp(fout));
-            L.Wt_s = b.take<float>((size_t)ldp(fout) * ldp(fin));
-        }
+        if (L.agg_first) L.M = b.take<float>((size_t)rows * ldp(fin));
         L.H_out = b.take<float>((size_t)rows * ldp(fout));
         if (L.skip) L.Act = b.take<float>((size_t)rows * ldp(fout));
         if (ldp(fout) > fmax) fmax = ldp(fout);
@@ -131,9 +150,6 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         if (t > tn_bytes) tn_bytes = t;
         const size_t c = colsum_workspace_bytes(rows, fout);
         if (c > cs_bytes) cs_bytes = c;
-        const int32_t w = (int32_t)std::max(ldp(fin), ldp(fout));      // one operand of a product may be two matrices side by side
-        const int64_t m_rows = std::max(rows, rows_in);
-        pl_bytes = std::max({pl_bytes, gemm_planes_bytes(m_rows, 2 * w, w), gemm_planes_bytes(m_rows, w, 2 * w)});
     }
     if (!mb) p.inv_in = b.take<float>((size_t)n);
     if (!sage) {
@@ -154,8 +170,6 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
     p.tn_ws = b.take<char>(tn_bytes);
     p.tn_ws_bytes = tn_bytes;
     p.colsum_ws = b.take<char>(cs_bytes);
-    if (pl_bytes > 0) p.planes = b.take<unsigned char>(pl_bytes);
-    p.planes_bytes = pl_bytes;
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
     {
         int64_t fsp = 0;                                   // the widest aggregation of the step
@@ -216,16 +230,20 @@ static void set_mean(SpmmArgs& s, const Block& B) {
 // output: 1 / (1 - rate) with dropout (the kept elements were scaled by it), else 1.
 static void weight_jobs(const grp_model_desc* m, const float* theta, StepPlan& p, float bwd_scale, PackJobs& jobs) {
     const bool sage = m->arch == GRP_ARCH_SAGE_MEAN;
+    jobs.theta = theta;
+    jobs.base = p.base;
     for (int l = 0; l < m->n_layers; ++l) {
         const LayerBufs& L = p.L[l];
         const int fin = m->dims[l], fout = m->dims[l + 1];
         // the products read their weights transposed: forward uses W^T (rows = outputs), the
         // backward pass to the layer below uses W itself (rows = inputs)
-        pack_jobs_add(jobs, theta + L.off_ws, fin, fout, true, (int)ldp(fout), L.Wt_s, L.ldwt);
-        if (sage) pack_jobs_add(jobs, theta + L.off_wn, fin, fout, true, (int)ldp(fout), L.Wt_n, L.ldwt);
+        const int lo = (int)ldp(fout), li = (int)ldp(fin);
+        if (sage) pack_jobs_add(jobs, theta + L.off_wn, fin, fout, true, lo, L.Wt_n, L.ldwt, L.Pt_n, 0, L.t_rows, !L.t_stack);
+        pack_jobs_add(jobs, theta + L.off_ws, fin, fout, true, lo, L.Wt_s, L.ldwt, L.t_stack ? L.Pt_n : L.Pt_s, L.t_stack ? lo : 0, L.t_rows, true);
         if (l > 0) {
-            pack_jobs_add(jobs, theta + L.off_ws, fin, fout, false, (int)ldp(fin), L.Wp_s, L.ldwp, bwd_scale);
-            if (sage) pack_jobs_add(jobs, theta + L.off_wn, fin, fout, false, (int)ldp(fin), L.Wp_n, L.ldwp, bwd_scale);
+            if (sage) pack_jobs_add(jobs, theta + L.off_wn, fin, fout, false, li, L.Wp_n, L.ldwp, L.Pp_n, 0, L.p_rows, !L.p_stack, bwd_scale);
+            pack_jobs_add(jobs, theta + L.off_ws, fin, fout, false, li, L.Wp_s, L.ldwp, L.p_stack ? L.Pp_n : L.Pp_s, L.p_stack ? li : 0, L.p_rows, true,
+                          bwd_scale);
         }
     }
 }
@@ -255,10 +273,10 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             s.F = fin; s.X = H; s.ldx = ldh; s.x_bf16 = h_bf16; set_mean(s, B); s.Y = L.M; s.ldy = ldp(fin);
             GRP_TRY(launch_spmm(s, st));
             GemmNNArgs a;
-            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
             a.a_rows = B.self_rows; a.Bt = L.Wt_s; a.ldbt = L.ldwt;
             a.K2 = fin; a.A2 = L.M; a.lda2 = ldp(fin); a.Bt2 = L.Wt_n; a.ldbt2 = L.ldwt;
+            a.ready = L.Pt_s; a.ready2 = L.Pt_n; a.ready_rows = L.t_rows;
             a.bias = theta + L.off_b; a.relu = relu; a.C = L.H_out; a.ldc = ldp(fout); a.zero_pad_to = (int)ldp(fout);
             GRP_TRY(launch_gemm_nn(a, st));
         } else if (B.n_in == B.n_dst && !B.self_rows && !B.n_dst_dev) {
@@ -266,8 +284,8 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             // H' = ReLU(mean-aggregate(T) + Z0)
             const int64_t w2 = 2 * ldp(fout);
             GemmNNArgs a;
-            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_dst; a.N = (int)(ldp(fout) + fout); a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
+            a.ready = L.Pt_n; a.ready_rows = L.t_rows;
             a.Bt = L.Wt_n; a.ldbt = L.ldwt; a.bias = theta + L.off_b; a.bias_col0 = (int)ldp(fout); a.bias_n = fout;
             a.C = p.tmpA; a.ldc = w2; a.zero_pad_to = (int)w2;
             GRP_TRY(launch_gemm_nn(a, st));
@@ -278,12 +296,11 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             GRP_TRY(launch_spmm(s, st));
         } else {
             GemmNNArgs a;      // T = H Wn over every input row, Z0 = H_self Ws + b
-            a.planes = p.planes; a.planes_bytes = p.planes_bytes;
             a.M = B.n_in; a.M_dev = B.n_in_dev; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16;
-            a.Bt = L.Wt_n; a.ldbt = L.ldwt;
+            a.Bt = L.Wt_n; a.ldbt = L.ldwt; a.ready = L.Pt_n; a.ready_rows = L.t_rows;
             a.C = p.tmpA; a.ldc = ldp(fout); a.zero_pad_to = (int)ldp(fout);
             GRP_TRY(launch_gemm_nn(a, st));
-            a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.a_rows = B.self_rows; a.Bt = L.Wt_s; a.bias = theta + L.off_b; a.C = L.H_out;
+            a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.a_rows = B.self_rows; a.Bt = L.Wt_s; a.ready = L.Pt_s; a.bias = theta + L.off_b; a.C = L.H_out;
             GRP_TRY(launch_gemm_nn(a, st));
             SpmmArgs s;
             fill_spmm(s, B, false, p.partials);
@@ -330,8 +347,8 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
                 const int64_t w2 = 2 * ldp(fin);
                 if (B.n_dst > 0) {
                     GemmNNArgs a;
-                    a.planes = p.planes; a.planes_bytes = p.planes_bytes;
                     a.M = B.n_dst; a.M_dev = B.n_dst_dev; a.N = (int)(ldp(fin) + fin); a.K = fout; a.A = dZ; a.lda = ldp(fout);
+                    a.ready = L.Pp_n; a.ready_rows = L.p_rows;
                     a.Bt = L.Wp_n; a.ldbt = L.ldwp; a.rowscale = B.inv_in; a.rowscale_cols = (int)ldp(fin);
                     a.C = p.tmpA; a.ldc = w2; a.zero_pad_to = (int)w2;
                     GRP_TRY(launch_gemm_nn(a, st));
@@ -364,10 +381,9 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
             GRP_TRY(launch_gemm_tn(t, st));
             if (l > 0 && B.n_in > 0) {
                 GemmNNArgs c;      // dZ_prev = mask * ([dZ Ws^T ; 0] + dT Wn^T)
-                c.planes = p.planes; c.planes_bytes = p.planes_bytes;
                 c.M = B.n_in; c.M_dev = B.n_in_dev; c.N = fin; c.K = fout; c.A = dZ; c.lda = ldp(fout);
                 c.a_valid_rows = B.n_dst; c.a_valid_rows_dev = B.n_dst_dev;
-                c.Bt = L.Wp_s; c.ldbt = L.ldwp;
+                c.Bt = L.Wp_s; c.ldbt = L.ldwp; c.ready = L.Pp_s; c.ready2 = L.Pp_n; c.ready_rows = L.p_rows;
                 c.K2 = fout; c.A2 = p.tmpA; c.lda2 = ldp(fout); c.Bt2 = L.Wp_n; c.ldbt2 = L.ldwp;
                 c.mask = p.L[l - 1].H_out; c.ld_mask = ldp(fin);
                 c.C = dZ_other; c.ldc = ldp(fin); c.zero_pad_to = (int)ldp(fin);
@@ -415,8 +431,8 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
             ldh = ldp(fin);
         }
         GemmNNArgs a;
-        a.planes = p.planes; a.planes_bytes = p.planes_bytes;
         a.M = n; a.N = fout; a.K = fin; a.A = H; a.lda = ldh; a.a_bf16 = h_bf16; a.Bt = L.Wt_s; a.ldbt = L.ldwt;
+        a.ready = L.Pt_s; a.ready_rows = L.t_rows;
         a.rowscale = p.gs; a.C = p.tmpA; a.ldc = ldp(fout); a.zero_pad_to = (int)ldp(fout);
         GRP_TRY(launch_gemm_nn(a, st));
         SpmmArgs s;
@@ -456,8 +472,8 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         if (l > 0 && n > 0) {
             const LayerBufs& Lp = p.L[l - 1];
             GemmNNArgs c;      // G_in = dT W^T (+ G);  dZ'_prev = diag(r) (A_prev > 0) G_in
-            c.planes = p.planes; c.planes_bytes = p.planes_bytes;
             c.M = n; c.N = fin; c.K = fout; c.A = p.tmpA; c.lda = ldp(fout); c.Bt = L.Wp_s; c.ldbt = L.ldwp;
+            c.ready = L.Pp_s; c.ready_rows = L.p_rows;
             if (L.skip) { c.addend = G; c.ld_add = ldp(fout); }
             if (Lp.skip) { c.C_raw = G_other; c.ld_raw = ldp(fin); }
             c.rowscale = gr_bwd; c.mask = Lp.skip ? Lp.Act : Lp.H_out; c.ld_mask = ldp(fin);

@@ -64,3 +64,24 @@ def test_minibatch_step_on_a_used_workspace(g, fill):
     torch.cuda.synchronize()
     for grad, stats in out[1:]:
         assert torch.equal(grad, out[0][0]) and torch.equal(stats, out[0][1])
+
+
+@pytest.mark.parametrize("arch,N,dims", [
+    ("sage", 700, [33, 31, 65, 97]), ("sage", 26_000, [129, 95, 33, 32]), ("gcn", 26_000, [31, 129, 97, 63]), ("gcn", 700, [127, 64, 1, 3])])
+def test_weights_at_tile_edges_on_a_used_workspace(g, arch, N, dims):
+    """The products read the weights from tiles of 32 k by up to 128 rows that the step writes itself: one column past a tile and one short
+    of it, side by side and alone, 64-row and 128-row products; what the workspace held before (NaN) must not show."""
+    seed = 11
+    s, d = synth.uniform_graph(N, 2 * N, seed=seed)
+    part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, seed, 0)
+    op = ograph.partition(s.numpy(), d.numpy(), N, 1, seed, 0)
+    x, y, theta = synth.normal_matrix(N, dims[0], seed), synth.labels(N, dims[-1], seed), synth.model_weights(arch, dims, seed)
+    model, opts = g.model_desc(g.ARCH_SAGE_MEAN if arch == "sage" else g.ARCH_GCN, dims), g.step_opts(full_graph=True)
+    ws = torch.full((g.grp_step_workspace_bytes(part, model, opts),), 255, dtype=torch.uint8, device=DEV)
+    grad, stats = torch.full((g.grp_param_count(model),), float("nan"), device=DEV), g.new_stats(1)
+    g.grp_train_step(part, model, opts, x.to(DEV), y.to(DEV), None, theta.to(DEV), ws, grad, stats)
+    torch.cuda.synchronize()
+
+    def oracle(**kw):
+        return ostep.train_step(op, arch, dims, theta.double().numpy(), x.double().numpy(), y.numpy(), **kw)
+    assert_step_grads_close(grad.cpu().numpy(), oracle, arch, dims, TOL_FP32)
