@@ -379,6 +379,67 @@ struct GemmNNArgs {
 size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K);      // K: of both products together
 grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st);
 
+// Partial statistics of a step's loss rows.
+struct StatsPartial {
+    double ratio, r_dbl;
+    int64_t s, r_int;
+};
+
+struct NnzParts {
+    const int64_t* p[GRP_MAX_LAYERS];
+    int n;
+    const int64_t* bad_seeds;      // null, or the number of seeds that were outside the partition
+};
+
+// What a step's record is made of.
+struct RecordArgs {
+    const StatsPartial* part;
+    int blocks, full_graph;
+    int64_t nnz_const;
+    NnzParts np;
+    const double* loss_part;
+    int loss_blocks;
+    grp_step_stats* out;
+};
+
+// Sums over partial results that nothing but a step's gradient waits for, done by its last launch together with its record
+// (a mini-batch step of three layers makes 32 launches; 36 with a launch for each).
+enum SumKind : uint8_t { SUM_TN, SUM_TN_4WAY, SUM_TN_VEC, SUM_COLUMNS };
+constexpr int64_t sum_block(SumKind kind) { return kind == SUM_TN ? 256 : kind == SUM_COLUMNS ? 8 : 64; }      // elements of a workgroup
+constexpr uint32_t NO_SUM = ~0u;
+struct SumJob {
+    uint32_t part;                   // units of 16 bytes of the workspace
+    uint32_t C, C2, colsum;          // elements of the gradient (NO_SUM: none)
+    uint32_t begin;                  // its first workgroup
+    int32_t count;                   // partial results
+    uint16_t K, N;
+    uint8_t dual, kind;
+};
+template <int MOST> struct StepSumsOf {
+    const char* base = nullptr;      // the workspace
+    float* grad = nullptr;
+    RecordArgs record = {};
+    uint32_t record_blocks = 0;      // 1: there is a record to be made
+    int32_t n = 0;
+    SumJob job[MOST];
+};
+constexpr int STEP_SUMS = 3 * GRP_MAX_LAYERS;
+struct StepSums : StepSumsOf<STEP_SUMS> {
+    uint32_t blocks = 0;
+    double bytes = 0.0;
+    StepSums(const void* workspace, float* gradient) { base = (const char*)workspace; grad = gradient; }
+    // elements: that the sums give
+    void add(SumKind kind, const void* part, int32_t count, int32_t K, int32_t N, int dual, const float* C, const float* C2, const float* colsum,
+             int64_t elements) {
+        auto at = [&](const float* p) { return p ? (uint32_t)(p - grad) : NO_SUM; };
+        job[n++] = SumJob{(uint32_t)(((const char*)part - base) / 16), at(C), at(C2), at(colsum), blocks, count, (uint16_t)K, (uint16_t)N, (uint8_t)dual,
+                          (uint8_t)kind};
+        blocks += (uint32_t)cdiv(elements, sum_block(kind));
+        bytes += 4.0 * (double)elements * (count + 1.0);
+    }
+};
+grp_status launch_step_sums(const StepSums& s, hipStream_t st);
+
 // C[K x N] = A[M x K]^T B[M x N], fixed-order split over M.
 size_t gemm_tn_workspace_bytes(int64_t M, int32_t K, int32_t N);
 struct GemmTNArgs {
@@ -403,13 +464,14 @@ struct GemmTNArgs {
     float* C2 = nullptr;             // pitch ldc
     const int64_t* M_dev = nullptr;  // when set: the real number of rows (on the device); M above is an upper bound
     int32_t a_tight = 0, b_tight = 0;    // set by the launch: rows of A / B end at their last column or are not 16-byte friendly
+    StepSums* sums = nullptr;        // when set (and ldc = N): the sum over the slices is left to it, the workspace is in use until then
 };
 grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st);
 
 // out[N] = column sums of A[M x N], every row multiplied by rowmul[m] first (may be null); scratch holds the per-block partials.
 size_t colsum_workspace_bytes(int64_t M, int32_t N);
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul,
-                                float* out, void* scratch, hipStream_t st);
+                                float* out, void* scratch, hipStream_t st, StepSums* sums = nullptr /*as of GemmTNArgs*/);
 // out[N] = sums over the rows of part[blocks x N].
 void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st);
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -528,7 +590,8 @@ grp_status launch_prelude(const StepPrelude& pre, hipStream_t st);
 grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int64_t ldz,
                                const int32_t* labels, int32_t node_level,
                                const float* rowscale /*null; multiplies dZ rows*/,
-                               float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st);
+                               float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st,
+                               StepSums* sums = nullptr /*when set: the record is left to it*/);
 // inv[v] = mass[v] > 0 ? 1 / mass[v] : 0
 grp_status launch_inverse_mass(const double* mass, int64_t n, float* inv, hipStream_t st);
 

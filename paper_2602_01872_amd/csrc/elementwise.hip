@@ -5,6 +5,7 @@
 // All reductions are two-stage with a fixed block count and a fixed tree, so results are
 // bit-reproducible (no floating-point atomics).
 #include "common.h"
+#include "step_sums.h"
 
 #include <algorithm>
 
@@ -288,42 +289,10 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
     }
 }
 
-// out[c] = sum_b part[b][c]: 8 columns per workgroup, 32 lanes per column take the blocks
-// b = j, j + 32, ... and are added in lane order.
-__device__ __forceinline__ void colsum_final_kernel_body(unsigned gx, const float* __restrict__ part, int64_t blocks, int N,
-                                                           float* __restrict__ out) {
-    __shared__ float red[32][8];
-    const int cl = threadIdx.x & 7, j = threadIdx.x >> 3;
-    const int c = blockIdx.x * 8 + cl;
-    float s = 0.f;
-    if (c < N) {
-        int64_t b = j;
-        for (; b + 7 * 32 < blocks; b += 8 * 32) {      // eight loads in flight, added in the same order (eight sums over 4096 blocks in the residual step: 59.46 -> 59.22 ms)
-            float v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = part[(b + 32 * q) * N + c];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) s += v[q];
-        }
-        for (; b < blocks; b += 32) s += part[b * N + c];
-    }
-    red[j][cl] = s;
-    __syncthreads();
-    if (j == 0 && c < N) {
-        float t = 0.f;
-#pragma unroll
-        for (int q = 0; q < 32; ++q) t += red[q][cl];
-        out[c] = t;
-    }
-}
 __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, int64_t blocks, int N,
                                                            float* __restrict__ out) {
-    colsum_final_kernel_body(gridDim.x, part, blocks, N, out);
+    colsum_final_block(blockIdx.x, part, blocks, N, out);
 }
-struct colsum_final_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { colsum_final_kernel_body(gx, a...); }
-};
 
 // Same partial sums with 16-byte loads: thread t owns the float4 column t % C4 and the rows
 // t / C4, t / C4 + R, ... of the block's slab (R = 256 / C4 row lanes); the row lanes are then
@@ -380,11 +349,11 @@ struct colsum_partial_vec_kernel_op {
 };
 
 void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st) {
-    launch(colsum_final_kernel, colsum_final_kernel_op(), dim3((unsigned)cdiv(N, 8)), st, part, blocks, N, out);
+    launch_alone(colsum_final_kernel, dim3((unsigned)cdiv(N, 8)), dim3(256), 0, st, part, blocks, N, out);
 }
 
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul, float* out,
-                                void* scratch, hipStream_t st) {
+                                void* scratch, hipStream_t st, StepSums* sums) {
     const int64_t blocks = cdiv(M > 0 ? M : 1, COLSUM_ROWS);
     ProfScope ps("colsum", st, 0.0, 4.0 * M * N);
     const bool vec = N <= 1024 && lda % 4 == 0 && lda >= round_up(N, 4) && (uintptr_t)A % 16 == 0;
@@ -394,6 +363,10 @@ grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t ld
         launch_alone(colsum_partial_kernel, dim3((unsigned)blocks), dim3(256), 0, st, A, M, N, lda, rowmul,
                            (float*)scratch);
     GRP_LAUNCH_CHECK();
+    if (sums) {
+        sums->add(SUM_COLUMNS, scratch, (int32_t)blocks, 0, N, 0, out, nullptr, nullptr, N);
+        return GRP_OK;
+    }
     launch_colsum_final((const float*)scratch, blocks, N, out, st);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
@@ -417,11 +390,6 @@ __device__ __forceinline__ void degree_scales_block(uint32_t block, const Degree
 // (2500 rows: the four kernels of statistics and loss 20 -> 12 us).
 constexpr int STATS_BLOCKS = 2048;
 static int stats_blocks(int64_t rows, int per_block) { return (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows, per_block), 1), STATS_BLOCKS); }
-
-struct StatsPartial {
-    double ratio, r_dbl;
-    int64_t s, r_int;
-};
 
 // (the partial sums, their counts of loss rows once more side by side, the partial losses)
 size_t stats_workspace_bytes(int64_t) { return (size_t)STATS_BLOCKS * (sizeof(StatsPartial) + sizeof(int64_t) + sizeof(double)); }
@@ -535,23 +503,8 @@ __device__ __forceinline__ int64_t loss_rows(const int64_t* __restrict__ part_ro
     for (int b = threadIdx.x; b < blocks; b += 256) s += part_rows[b];
     return block_sum<int64_t>(s, sm);
 }
-struct NnzParts {
-    const int64_t* p[GRP_MAX_LAYERS];
-    int n;
-    const int64_t* bad_seeds;      // null, or the number of seeds that were outside the partition
-};
-
 // The step's record, by one workgroup.
-struct RecordArgs {
-    const StatsPartial* part;
-    int blocks, full_graph;
-    int64_t nnz_const;
-    NnzParts np;
-    const double* loss_part;
-    int loss_blocks;
-    grp_step_stats* out;
-};
-__device__ __forceinline__ void record_kernel_body(unsigned gx, const RecordArgs& a) {
+__device__ __forceinline__ void record_block(const RecordArgs& a) {
     __shared__ double smd[4];
     __shared__ int64_t smi[4];
     double ratio = 0.0, rd = 0.0, loss = 0.0;
@@ -577,11 +530,55 @@ __device__ __forceinline__ void record_kernel_body(unsigned gx, const RecordArgs
         out->nnz_used = nnz_used;
     }
 }
-__global__ __launch_bounds__(256) void record_kernel(RecordArgs a) { record_kernel_body(gridDim.x, a); }
-struct record_kernel_op {
+__global__ __launch_bounds__(256) void record_kernel(RecordArgs a) { record_block(a); }
+
+// A step's last launch: its record and every sum over partial results that only its gradient waits for.  They are independent, and a launch
+// costs more than any of them on a small partition or batch.
+template <int MOST>
+__device__ __forceinline__ void step_sums_kernel_body(unsigned gx, const StepSumsOf<MOST>& s) {
+    uint32_t block = blockIdx.x;
+    if (block < s.record_blocks) return record_block(s.record);
+    block -= s.record_blocks;
+    int j = 0;
+    while (j + 1 < s.n && block >= s.job[j + 1].begin) ++j;
+    const SumJob& k = s.job[j];
+    block -= k.begin;
+    const float* const part = reinterpret_cast<const float*>(s.base + (uint64_t)k.part * 16);
+    auto out = [&](uint32_t at) { return at == NO_SUM ? nullptr : s.grad + at; };
+    if (k.kind == SUM_COLUMNS) return colsum_final_block(block, part, k.count, k.N, s.grad + k.C);
+    const int64_t products = (int64_t)k.K * k.N * (k.dual ? 2 : 1), row = (int64_t)k.N * (k.dual == 2 ? 2 : 1);
+    const int64_t stride = products + row, total = products + (k.colsum == NO_SUM ? 0 : k.N);
+    if (k.kind == SUM_TN_VEC) tn_reduce_vec_block(block, part, k.count, k.K, k.N, stride, out(k.C), k.N, out(k.colsum), k.dual, out(k.C2), total);
+    else if (k.kind == SUM_TN_4WAY) tn_reduce_4way_block(block, part, k.count, k.K, k.N, stride, out(k.C), k.N, out(k.colsum), k.dual, out(k.C2), total);
+    else tn_reduce_block(block, part, k.count, k.K, k.N, stride, out(k.C), k.N, out(k.colsum), k.dual, out(k.C2), total);
+}
+template <int MOST>
+__global__ __launch_bounds__(256) void step_sums_kernel(StepSumsOf<MOST> s) {
+    step_sums_kernel_body<MOST>(gridDim.x, s);
+}
+template <int MOST>
+struct step_sums_kernel_op {
     static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { record_kernel_body(gx, a...); }
+    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { step_sums_kernel_body<MOST>(gx, a...); }
 };
+
+grp_status launch_step_sums(const StepSums& s, hipStream_t st) {
+    if (s.record_blocks + s.blocks == 0) return GRP_OK;
+    ProfScope ps("step_sums", st, 0.0, s.bytes);
+    const dim3 grid(s.record_blocks + s.blocks);
+    constexpr int FEW = 6;                             // three layers: arguments of eight steps fit one launch
+    static_assert(many_of<Pack<StepSumsOf<FEW>>>() == MANY_MOST, "of as many steps as other launches hold");
+    if (s.n <= FEW) {
+        StepSumsOf<FEW> few;
+        few.base = s.base; few.grad = s.grad; few.record = s.record; few.record_blocks = s.record_blocks; few.n = s.n;
+        for (int j = 0; j < s.n; ++j) few.job[j] = s.job[j];
+        launch(step_sums_kernel<FEW>, step_sums_kernel_op<FEW>(), grid, st, few);
+    } else {
+        launch_alone(step_sums_kernel<STEP_SUMS>, grid, dim3(256), 0, st, (const StepSumsOf<STEP_SUMS>&)s);
+    }
+    GRP_LAUNCH_CHECK();
+    return GRP_OK;
+}
 
 // ------------------------------------------------------------------ softmax cross-entropy
 // 16 lanes per row; dZ[row,:] = w (softmax(z) - onehot(y)) / |S| for loss rows, 0 otherwise
@@ -720,7 +717,7 @@ struct softmax_xent_reg_kernel_op {
 };
 
 grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int32_t node_level,
-                               const float* rowscale, float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st) {
+                               const float* rowscale, float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st, StepSums* sums) {
     const int64_t n_rows = in.n_loss;
     ProfScope ps("softmax_xent", st, 0.0, 8.0 * n_rows * C);
     const CoverageIn cv{in.d_local, in.d_global, in.w_local, in.w_global};
@@ -745,7 +742,12 @@ grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int
     r.np.n = in.n_parts;
     r.np.bad_seeds = in.bad_seeds;
     for (int i = 0; i < GRP_MAX_LAYERS; ++i) r.np.p[i] = i < in.n_parts ? in.nnz_parts[i] : nullptr;
-    launch(record_kernel, record_kernel_op(), dim3(1), st, r);
+    if (sums) {
+        sums->record = r;
+        sums->record_blocks = 1;
+        return GRP_OK;
+    }
+    launch_alone(record_kernel, dim3(1), dim3(256), 0, st, r);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }

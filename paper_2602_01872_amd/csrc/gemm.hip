@@ -30,6 +30,7 @@
 // operand instead of branching.  The layouts are described at the kernels.  Products whose operands are not 16-byte
 // friendly, or whose B is not given transposed, take gemm_nn_kernel, which uses the fp32 instructions.
 #include "common.h"
+#include "step_sums.h"
 
 #include <algorithm>
 
@@ -1422,148 +1423,21 @@ struct gemm_tn_kernel_op {
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { gemm_tn_kernel_body<AT, VEC, GATHER, WM, WN, TM, TN>(gx, a...); }
 };
 
-// Where element (row, col) of the reduced partials goes: rows [0, K) x cols [0, N) -> C; with two
-// products the second one's rows [K, 2K) (dual = 1) or columns [N, 2N) (dual = 2) -> C2; the last row
-// holds the column sums of B (its first N columns).
-__device__ __forceinline__ void tn_store(int64_t e, float val, int K, int N, int dual, float* __restrict__ C,
-                                         float* __restrict__ C2, int64_t ldc, float* __restrict__ colsum_out) {
-    const int width = dual == 2 ? 2 * N : N;
-    const int64_t row = e / width;
-    const int col = (int)(e % width);
-    const int krows = dual == 1 ? 2 * K : K;
-    if (row >= krows) {
-        if (colsum_out && col < N) colsum_out[col] = val;
-    } else if (dual == 1 && row >= K) {
-        C2[(row - K) * ldc + col] = val;
-    } else if (dual == 2 && col >= N) {
-        C2[row * ldc + (col - N)] = val;
-    } else {
-        C[row * ldc + col] = val;
-    }
+__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ part, int splits, int K, int N, int64_t part_stride,
+                                                        float* __restrict__ C, int64_t ldc, float* __restrict__ colsum_out, int dual,
+                                                        float* __restrict__ C2, int64_t total) {
+    tn_reduce_block(blockIdx.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
 }
-
-// C[e] = sum_p part[p][e], p ascending.  Four partial tiles are requested before the first is
-// added (the adds stay in split order, so the result is the plain sequential sum).
-__device__ __forceinline__ void tn_reduce_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
-                                                        int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                        float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                        int64_t total) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= total) return;                           // total = (rows of products + the column-sum row) x width
-    const float* p0 = part + e;
-    float s = 0.f;
-    int p = 0;
-    for (; p + 4 <= splits; p += 4) {
-        const float a = p0[(int64_t)p * part_stride], b = p0[(int64_t)(p + 1) * part_stride];
-        const float c = p0[(int64_t)(p + 2) * part_stride], d = p0[(int64_t)(p + 3) * part_stride];
-        s += a; s += b; s += c; s += d;
-    }
-    for (; p < splits; ++p) s += p0[(int64_t)p * part_stride];
-    tn_store(e, s, K, N, dual, C, C2, ldc, colsum_out);
+__global__ __launch_bounds__(256) void tn_reduce_vec_kernel(const float* __restrict__ part, int splits, int K, int N, int64_t part_stride,
+                                                            float* __restrict__ C, int64_t ldc, float* __restrict__ colsum_out, int dual,
+                                                            float* __restrict__ C2, int64_t total) {
+    tn_reduce_vec_block(blockIdx.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
 }
-__global__ __launch_bounds__(256) void tn_reduce_kernel(const float* __restrict__ part, int splits, int K, int N,
-                                                        int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                        float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                        int64_t total) {
-    tn_reduce_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
+__global__ __launch_bounds__(256) void tn_reduce_4way_kernel(const float* __restrict__ part, int splits, int K, int N, int64_t part_stride,
+                                                             float* __restrict__ C, int64_t ldc, float* __restrict__ colsum_out, int dual,
+                                                             float* __restrict__ C2, int64_t total) {
+    tn_reduce_4way_block(blockIdx.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
 }
-struct tn_reduce_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_kernel_body(gx, a...); }
-};
-
-// The same sum for partials whose stride allows 16-byte loads: a workgroup owns 64 elements,
-// 16 groups of threads each add a contiguous range of splits in ascending order, and the 16
-// group sums are then added in ascending order: a fixed association, so still deterministic.
-__device__ __forceinline__ void tn_reduce_vec_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
-                                                            int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                            float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                            int64_t total) {           // total: a multiple of 4
-    __shared__ float4 red[16][16];
-    const int c = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const int64_t e = ((int64_t)blockIdx.x * 16 + c) * 4;
-    const int per = (splits + 15) / 16;
-    const int p_begin = grp * per, p_end = p_begin + per < splits ? p_begin + per : splits;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (e < total) {
-        const float* p0 = part + e;
-        int p = p_begin;
-        for (; p + 4 <= p_end; p += 4) {
-            const float4 a = *reinterpret_cast<const float4*>(p0 + (int64_t)p * part_stride);
-            const float4 b = *reinterpret_cast<const float4*>(p0 + (int64_t)(p + 1) * part_stride);
-            const float4 c4 = *reinterpret_cast<const float4*>(p0 + (int64_t)(p + 2) * part_stride);
-            const float4 d = *reinterpret_cast<const float4*>(p0 + (int64_t)(p + 3) * part_stride);
-            s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-            s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w;
-            s.x += c4.x; s.y += c4.y; s.z += c4.z; s.w += c4.w;
-            s.x += d.x; s.y += d.y; s.z += d.z; s.w += d.w;
-        }
-        for (; p < p_end; ++p) {
-            const float4 a = *reinterpret_cast<const float4*>(p0 + (int64_t)p * part_stride);
-            s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-        }
-    }
-    red[grp][c] = s;
-    __syncthreads();
-    if (grp == 0 && e < total) {
-        float4 t = red[0][c];
-        for (int u = 1; u < 16; ++u) { const float4 v = red[u][c]; t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w; }
-        const float tv[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) tn_store(e + q, tv[q], K, N, dual, C, C2, ldc, colsum_out);
-    }
-}
-__global__ __launch_bounds__(256) void tn_reduce_vec_kernel(const float* __restrict__ part, int splits, int K, int N,
-                                                            int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                            float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                            int64_t total) {
-    tn_reduce_vec_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
-}
-struct tn_reduce_vec_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_vec_kernel_body(gx, a...); }
-};
-
-// Scalar variant of the same scheme for strides that rule out 16-byte loads: a workgroup owns
-// 64 elements, 4 groups of threads each add a contiguous quarter of the splits in ascending
-// order, the 4 group sums are added in ascending order.
-__device__ __forceinline__ void tn_reduce_4way_kernel_body(unsigned gx, const float* __restrict__ part, int splits, int K, int N,
-                                                             int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                             float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                             int64_t total) {
-    __shared__ float red[4][64];
-    const int c = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const int64_t e = (int64_t)blockIdx.x * 64 + c;
-    const int per = (splits + 3) / 4;
-    const int p_begin = grp * per, p_end = p_begin + per < splits ? p_begin + per : splits;
-    float s = 0.f;
-    if (e < total) {
-        const float* p0 = part + e;
-        int p = p_begin;
-        for (; p + 4 <= p_end; p += 4) {
-            const float a = p0[(int64_t)p * part_stride], b = p0[(int64_t)(p + 1) * part_stride];
-            const float c2 = p0[(int64_t)(p + 2) * part_stride], d = p0[(int64_t)(p + 3) * part_stride];
-            s += a; s += b; s += c2; s += d;
-        }
-        for (; p < p_end; ++p) s += p0[(int64_t)p * part_stride];
-    }
-    red[grp][c] = s;
-    __syncthreads();
-    if (grp == 0 && e < total) {
-        const float t = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
-        tn_store(e, t, K, N, dual, C, C2, ldc, colsum_out);
-    }
-}
-__global__ __launch_bounds__(256) void tn_reduce_4way_kernel(const float* __restrict__ part, int splits, int K, int N,
-                                                             int64_t part_stride, float* __restrict__ C, int64_t ldc,
-                                                             float* __restrict__ colsum_out, int dual, float* __restrict__ C2,
-                                                             int64_t total) {
-    tn_reduce_4way_kernel_body(gridDim.x, part, splits, K, N, part_stride, C, ldc, colsum_out, dual, C2, total);
-}
-struct tn_reduce_4way_kernel_op {
-    static constexpr int THREADS = 256, WGS = 1;
-    template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { tn_reduce_4way_kernel_body(gx, a...); }
-};
 
 template <typename AT, bool VEC, bool GATHER>
 static void tn_pick(const GemmTNArgs& a, const TnPlan& p, int dual, float* out, float* out2, int64_t out_ld, int64_t stride,
@@ -1638,18 +1512,20 @@ grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st) {
     }
     if (p.splits > 1) {
         const int64_t total = krows * width + (a.colsum_out ? a.N : 0);
-        ProfScope ps("gemm_tn_reduce", st, 0.0, 4.0 * total * (p.splits + 1.0));
-        const float* part = (const float*)a.workspace;
-        if (stride % 4 == 0 && total % 4 == 0 && (uintptr_t)a.workspace % 16 == 0 && p.splits >= 16) {
-            launch(tn_reduce_vec_kernel, tn_reduce_vec_kernel_op(), dim3((unsigned)cdiv(total, 64)), st, part, p.splits, a.K,
-                               a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
-        } else if (p.splits >= 16) {
-            launch(tn_reduce_4way_kernel, tn_reduce_4way_kernel_op(), dim3((unsigned)cdiv(total, 64)), st, part, p.splits, a.K,
-                               a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
-        } else {
-            launch(tn_reduce_kernel, tn_reduce_kernel_op(), dim3((unsigned)cdiv(total, 256)), st, part, p.splits, a.K,
-                               a.N, stride, a.C, a.ldc, a.colsum_out, dual, a.C2, total);
+        const SumKind kind = stride % 4 == 0 && total % 4 == 0 && (uintptr_t)a.workspace % 16 == 0 && p.splits >= 16 ? SUM_TN_VEC
+                             : p.splits >= 16 ? SUM_TN_4WAY : SUM_TN;
+        if (a.sums && a.ldc == a.N) {                      // left to the step's last launch
+            a.sums->add(kind, a.workspace, p.splits, a.K, a.N, dual, a.C, a.C2, a.colsum_out, total);
+            return GRP_OK;
         }
+        ProfScope ps("gemm_tn_reduce", st, 0.0, 4.0 * total * (p.splits + 1.0));
+        auto go = [&](auto kernel) {
+            launch_alone(kernel, dim3((unsigned)cdiv(total, sum_block(kind))), dim3(256), 0, st, (const float*)a.workspace, p.splits, a.K, a.N, stride,
+                         a.C, a.ldc, a.colsum_out, dual, a.C2, total);
+        };
+        if (kind == SUM_TN_VEC) go(tn_reduce_vec_kernel);
+        else if (kind == SUM_TN_4WAY) go(tn_reduce_4way_kernel);
+        else go(tn_reduce_kernel);
         GRP_LAUNCH_CHECK();
     }
     return GRP_OK;

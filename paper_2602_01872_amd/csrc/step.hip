@@ -31,6 +31,9 @@ struct LayerBufs {
     // Their planes (bt_planes_at), as the layer's products read them: of one stack (t_stack, p_stack: _n holds both), or of each alone.
     unsigned char *Pt_s = nullptr, *Pt_n = nullptr, *Pp_s = nullptr, *Pp_n = nullptr;
     int32_t t_rows = 0, p_rows = 0;
+    // Partial results of the layer's transposed products (tn_ws2: of a second one) and column sums: in use until the step's last launch.
+    void *tn_ws = nullptr, *tn_ws2 = nullptr, *colsum_ws = nullptr;
+    size_t tn_ws_bytes = 0;
     bool t_stack = false, p_stack = false;
     bool agg_first = false;
     bool skip = false;       // residual GCN: H_out = H_in + ReLU(z)
@@ -42,9 +45,9 @@ struct StepPlan {
     float* Xpad = nullptr;       // residual first layer: zero-padded copy of features whose rows are not 16-byte friendly
     float* gr_drop = nullptr;    // gr / (1 - dropout rate): the row scale of the backward pass through a dropped layer
     float *tmpA = nullptr, *tmpB = nullptr, *dZa = nullptr, *dZb = nullptr, *Ga = nullptr, *Gb = nullptr;
-    void *tn_ws = nullptr, *colsum_ws = nullptr, *stats_ws = nullptr, *sampler_ws = nullptr;
+    void *stats_ws = nullptr, *sampler_ws = nullptr;
     float* partials = nullptr;   // partial rows of the split long rows (SpMM)
-    size_t tn_ws_bytes = 0, sampler_bytes = 0;
+    size_t sampler_bytes = 0;
     char* base = nullptr;        // the workspace
     size_t total = 0;
 };
@@ -121,8 +124,18 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
             if (!L.p_stack) L.Pp_s = b.take<unsigned char>(bt_planes_bytes(fout, L.p_rows));
         }
     }
+    if (mb) sampler_bounds(n, o->n_seeds, o->fanouts, k, &bd);
+    // the rows of a layer's outputs and inputs (of a sampled first layer: only those that are gathered)
+    auto rows_of = [&](int l) { return mb ? bd.dst[l] : n; };
+    auto rows_in_of = [&](int l) { return mb ? (l == 0 ? bd.dst[0] : bd.src[l]) : n; };
+    for (int l = 0; l < k; ++l) {              // (what the last launch adds up: within the same reach)
+        LayerBufs& L = p.L[l];
+        L.tn_ws_bytes = gemm_tn_workspace_bytes(std::max(rows_of(l), rows_in_of(l)), m->dims[l], m->dims[l + 1]);
+        L.tn_ws = b.take<char>(L.tn_ws_bytes);
+        if (mb && !L.agg_first) L.tn_ws2 = b.take<char>(L.tn_ws_bytes);
+        if (!sage) L.colsum_ws = b.take<char>(colsum_workspace_bytes(rows_of(l), m->dims[l + 1]));
+    }
     if (mb) {
-        sampler_bounds(n, o->n_seeds, o->fanouts, k, &bd);
         p.sampler_bytes = sampler_workspace_bytes(n, bd, k);
         p.sampler_ws = b.take<char>(p.sampler_bytes);
         chunks_cap = 0;
@@ -132,12 +145,10 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         }
     }
     int64_t fmax = 0, max_rows = 1;
-    size_t tn_bytes = 0, cs_bytes = 0;
     for (int l = 0; l < k; ++l) {
         LayerBufs& L = p.L[l];
         const int fin = m->dims[l], fout = m->dims[l + 1];
-        const int64_t rows = mb ? bd.dst[l] : n;
-        const int64_t rows_in = mb ? (l == 0 ? bd.dst[0] : bd.src[l]) : n;
+        const int64_t rows = rows_of(l), rows_in = rows_in_of(l);
         if (rows > max_rows) max_rows = rows;
         if (rows_in > max_rows) max_rows = rows_in;
         L.skip = m->arch == GRP_ARCH_GCN_RESIDUAL && fin == fout && l < k - 1;
@@ -146,10 +157,6 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         if (L.skip) L.Act = b.take<float>((size_t)rows * ldp(fout));
         if (ldp(fout) > fmax) fmax = ldp(fout);
         if (l > 0 && ldp(fin) > fmax) fmax = ldp(fin);
-        const size_t t = gemm_tn_workspace_bytes(rows_in > rows ? rows_in : rows, fin, fout);
-        if (t > tn_bytes) tn_bytes = t;
-        const size_t c = colsum_workspace_bytes(rows, fout);
-        if (c > cs_bytes) cs_bytes = c;
     }
     if (!mb) p.inv_in = b.take<float>((size_t)n);
     if (!sage) {
@@ -167,9 +174,6 @@ static StepPlan make_plan(const grp_partition_t* part, const grp_model_desc* m, 
         p.Ga = b.take<float>((size_t)max_rows * fmax);
         p.Gb = b.take<float>((size_t)max_rows * fmax);
     }
-    p.tn_ws = b.take<char>(tn_bytes);
-    p.tn_ws_bytes = tn_bytes;
-    p.colsum_ws = b.take<char>(cs_bytes);
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
     {
         int64_t fsp = 0;                                   // the widest aggregation of the step
@@ -254,6 +258,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
                             hipEvent_t transposed_ready = nullptr) {
     const int k = m->n_layers;
     const DropoutPlan drop = dropout_plan(o);
+    StepSums sums(p.base, grad);
     weight_jobs(m, theta, p, drop.scale, pre.pack);
     GRP_TRY(launch_prelude(pre, st));
 
@@ -317,7 +322,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
     const int C = m->dims[k];
     float* dZ = p.dZa;
     float* dZ_other = p.dZb;
-    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp(C), stats, st));
+    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp(C), stats, st, &sums));
 
     // ---------------- backward
     if (transposed_ready) GRP_HIP(hipStreamWaitEvent(st, transposed_ready, 0));   // the blocks' transposed structures
@@ -330,7 +335,8 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
         const int in_bf16 = l == 0 && m->feat_dtype == GRP_DTYPE_BF16;
         GemmTNArgs t;      // dW_self = H_self^T dZ, and db = 1^T dZ from the same pass over dZ
         t.M = B.n_dst; t.M_dev = B.n_dst_dev; t.K = fin; t.N = fout; t.A = Hin; t.lda = ldin; t.a_bf16 = in_bf16; t.a_rows = B.self_rows;
-        t.B = dZ; t.ldb = ldp(fout); t.C = grad + L.off_ws; t.ldc = fout; t.workspace = p.tn_ws; t.workspace_bytes = p.tn_ws_bytes;
+        t.B = dZ; t.ldb = ldp(fout); t.C = grad + L.off_ws; t.ldc = fout; t.workspace = L.tn_ws; t.workspace_bytes = L.tn_ws_bytes;
+        t.sums = &sums;
         t.colsum_out = grad + L.off_b;
         // the same rows of the input feed both weight gradients of a transform-first layer
         const bool shared_rows = !L.agg_first && B.n_in == B.n_dst && !B.self_rows && !B.n_dst_dev;
@@ -376,6 +382,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
                 t.B2 = p.tmpA; t.ldb2 = ldp(fout); t.C2 = grad + L.off_wn;
             } else {
                 t.colsum_out = nullptr;
+                t.workspace = L.tn_ws2;
                 t.M = B.n_in; t.M_dev = B.n_in_dev; t.a_rows = nullptr; t.B = p.tmpA; t.C = grad + L.off_wn;
             }
             GRP_TRY(launch_gemm_tn(t, st));
@@ -392,7 +399,7 @@ static grp_status sage_step(const grp_partition_t* g, const grp_model_desc* m, c
         }
         float* sw = dZ; dZ = dZ_other; dZ_other = sw;
     }
-    return GRP_OK;
+    return launch_step_sums(sums, st);
 }
 
 // GCN / residual GCN, full-graph mode.
@@ -406,6 +413,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
     const int k = m->n_layers;
     const int64_t n = g->n;
     const int sl = m->gcn_self_loops ? 1 : 0;
+    StepSums sums(p.base, grad);
     pre.degrees = DegreeScales{g->d_local_in, g->d_local_out, n, sl, nullptr, p.gr, p.gs, p.grinv};
     weight_jobs(m, theta, p, 1.f, pre.pack);
     GRP_TRY(launch_prelude(pre, st));
@@ -452,7 +460,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
     float* dZ_other = p.dZb;
     float* G = p.Ga;            // dL/dH' of the current layer (residual models only)
     float* G_other = p.Gb;
-    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, p.gr, dZ, ldp(C), stats, st));
+    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, p.gr, dZ, ldp(C), stats, st, &sums));
 
     for (int l = k - 1; l >= 0; --l) {
         const LayerBufs& L = p.L[l];
@@ -460,14 +468,15 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         const void* Hin = l == 0 ? X : (const void*)p.L[l - 1].H_out;
         const int64_t ldin = l == 0 ? m->dims[0] : ldp(fin);
         const int in_bf16 = l == 0 && m->feat_dtype == GRP_DTYPE_BF16;
-        GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, p.colsum_ws, st));
+        GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, L.colsum_ws, st, &sums));
         SpmmArgs s;
         fill_spmm(s, B, true, p.partials);
         s.F = fout; s.X = dZ; s.ldx = ldp(fout); s.scale = GRP_SCALE_RSQRT; s.self_term = sl; s.Y = p.tmpA; s.ldy = ldp(fout);
         GRP_TRY(launch_spmm(s, st));
         GemmTNArgs t;
         t.M = n; t.K = fin; t.N = fout; t.A = Hin; t.lda = ldin; t.a_bf16 = in_bf16; t.B = p.tmpA; t.ldb = ldp(fout);
-        t.C = grad + L.off_ws; t.ldc = fout; t.workspace = p.tn_ws; t.workspace_bytes = p.tn_ws_bytes;
+        t.C = grad + L.off_ws; t.ldc = fout; t.workspace = L.tn_ws; t.workspace_bytes = L.tn_ws_bytes;
+        t.sums = &sums;
         GRP_TRY(launch_gemm_tn(t, st));
         if (l > 0 && n > 0) {
             const LayerBufs& Lp = p.L[l - 1];
@@ -483,7 +492,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         }
         float* sw = dZ; dZ = dZ_other; dZ_other = sw;
     }
-    return GRP_OK;
+    return launch_step_sums(sums, st);
 }
 
 }  // namespace grp

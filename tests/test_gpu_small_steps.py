@@ -85,3 +85,30 @@ def test_weights_at_tile_edges_on_a_used_workspace(g, arch, N, dims):
     def oracle(**kw):
         return ostep.train_step(op, arch, dims, theta.double().numpy(), x.double().numpy(), y.numpy(), **kw)
     assert_step_grads_close(grad.cpu().numpy(), oracle, arch, dims, TOL_FP32)
+
+
+@pytest.mark.parametrize("arch,N,dims", [
+    ("gcn", 300, [7, 5, 6, 9, 3]), ("gcn", 900, [33, 64, 31, 32, 16]), ("gcn", 5000, [64, 128, 8, 130, 41, 5]), ("sage", 5000, [12] * 8 + [3])])
+def test_sums_that_a_deep_step_leaves_to_its_end(g, arch, N, dims):
+    """Every layer's products and column sums leave partial results to the step's last launch: more of them than three layers have, of few and
+    of many slices, in vectors and not; one step alone and two that share their launches, on workspaces that held NaN."""
+    seed = 13
+    s, d = synth.rmat_graph(13, 6 * N, seed=seed, n_nodes=N)
+    part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, seed, 0)
+    op = ograph.partition(s.numpy(), d.numpy(), N, 1, seed, 0)
+    x, y, theta = synth.normal_matrix(N, dims[0], seed), synth.labels(N, dims[-1], seed), synth.model_weights(arch, dims, seed)
+    model, opts = g.model_desc(g.ARCH_SAGE_MEAN if arch == "sage" else g.ARCH_GCN, dims), g.step_opts(full_graph=True)
+    bytes_, P = g.grp_step_workspace_bytes(part, model, opts), g.grp_param_count(model)
+    xd, yd, td, out = x.to(DEV), y.to(DEV), theta.to(DEV), []
+    for count in (1, 2):
+        ws = [torch.full((bytes_,), 255, dtype=torch.uint8, device=DEV) for _ in range(count)]
+        grads, stats = [torch.full((P,), float("nan"), device=DEV) for _ in range(count)], [g.new_stats(1) for _ in range(count)]
+        g.grp_train_steps([part] * count, model, [opts] * count, [xd] * count, [yd] * count, None, td, ws, grads, stats)
+        out += list(zip(grads, stats))
+    torch.cuda.synchronize()
+    for grad, stat in out[1:]:
+        assert torch.equal(grad, out[0][0]) and torch.equal(stat, out[0][1])
+
+    def oracle(**kw):
+        return ostep.train_step(op, arch, dims, theta.double().numpy(), x.double().numpy(), y.numpy(), **kw)
+    assert_step_grads_close(out[0][0].cpu().numpy(), oracle, arch, dims, TOL_FP32)
