@@ -328,6 +328,8 @@ struct SpmmArgs {
 grp_status launch_spmm(const SpmmArgs& a, hipStream_t st);
 size_t spmm_partials_bytes(const LongRows* lr, int32_t F);
 
+struct StepSums;
+
 // C[M x N] = epilogue(A[M x K] B[K x N] + A2[M x K2] B2[K2 x N])
 // epilogue: (+ bias[N]) (+ addend[M x N]) (* rowscale[M]) (ReLU) (* (mask[M x N] > 0))
 struct GemmNNArgs {
@@ -375,6 +377,11 @@ struct GemmNNArgs {
     // size the launch, and the kernels read the real values here.
     const int64_t* M_dev = nullptr;
     const int64_t* a_valid_rows_dev = nullptr;
+    // When set: also the column sums of C, row m times col_mul[m], to col_out[N] through `sums`, by way of col_part (a row of N floats for
+    // every 64 rows of C).  For fp32 A of whole 16-byte units, all rows valid, and ready planes.
+    StepSums* sums = nullptr;
+    float *col_part = nullptr, *col_out = nullptr;
+    const float* col_mul = nullptr;
 };
 size_t gemm_planes_bytes(int64_t M, int32_t N, int32_t K);      // K: of both products together
 grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st);
@@ -469,6 +476,7 @@ struct GemmTNArgs {
 grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st);
 
 // out[N] = column sums of A[M x N], every row multiplied by rowmul[m] first (may be null); scratch holds the per-block partials.
+// (room also for the partial sums that softmax_xent and a product that makes C[M x N] leave)
 size_t colsum_workspace_bytes(int64_t M, int32_t N);
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul,
                                 float* out, void* scratch, hipStream_t st, StepSums* sums = nullptr /*as of GemmTNArgs*/);
@@ -591,7 +599,10 @@ grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int
                                const int32_t* labels, int32_t node_level,
                                const float* rowscale /*null; multiplies dZ rows*/,
                                float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st,
-                               StepSums* sums = nullptr /*when set: the record is left to it*/);
+                               StepSums* sums = nullptr /*when set: the record is left to it*/,
+                               float* col_part = nullptr /*colsum_workspace_bytes; when set: and the column sums of dZ before rowscale*/,
+                               float* col_out = nullptr);
+constexpr int XENT_COLS_MOST = 192;       // classes up to which it makes them
 // inv[v] = mass[v] > 0 ? 1 / mass[v] : 0
 grp_status launch_inverse_mass(const double* mass, int64_t n, float* inv, hipStream_t st);
 

@@ -274,7 +274,13 @@ __device__ __forceinline__ T block_sum(T v, T* sm /*[4]*/) {
 // ------------------------------------------------------------------ column sums
 constexpr int COLSUM_ROWS = 256;     // rows per block
 
-size_t colsum_workspace_bytes(int64_t M, int32_t N) { return (size_t)cdiv(M > 0 ? M : 1, COLSUM_ROWS) * N * sizeof(float); }
+// At most this many partial results of the statistics and of the loss; fewer where the rows do not fill them: the one workgroup that adds them
+// up waits for each (2500 rows: the four kernels of statistics and loss 20 -> 12 us).
+constexpr int STATS_BLOCKS = 2048;
+static int stats_blocks(int64_t rows, int per_block) { return (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows, per_block), 1), STATS_BLOCKS); }
+size_t colsum_workspace_bytes(int64_t M, int32_t N) {
+    return (size_t)std::max<int64_t>(cdiv(M > 0 ? M : 1, 64), stats_blocks(M, 16)) * N * sizeof(float);
+}
 
 // part[b][c] = sum over the block's rows of A[m][c] * (rowmul ? rowmul[m] : 1)
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __restrict__ A, int64_t M, int N, int64_t lda,
@@ -386,11 +392,6 @@ __device__ __forceinline__ void degree_scales_block(uint32_t block, const Degree
     if (d.s) d.s[v] = 1.0f / sqrtf(b);
 }
 // ------------------------------------------------------------------ coverage statistics
-// At most this many partial results; fewer where the rows do not fill them: the one workgroup that adds them up waits for each
-// (2500 rows: the four kernels of statistics and loss 20 -> 12 us).
-constexpr int STATS_BLOCKS = 2048;
-static int stats_blocks(int64_t rows, int per_block) { return (int)std::min<int64_t>(std::max<int64_t>(cdiv(rows, per_block), 1), STATS_BLOCKS); }
-
 // (the partial sums, their counts of loss rows once more side by side, the partial losses)
 size_t stats_workspace_bytes(int64_t) { return (size_t)STATS_BLOCKS * (sizeof(StatsPartial) + sizeof(int64_t) + sizeof(double)); }
 static int64_t* stats_rows(void* scratch) { return (int64_t*)((char*)scratch + (size_t)STATS_BLOCKS * sizeof(StatsPartial)); }
@@ -641,7 +642,7 @@ __device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_
                                                                const float* __restrict__ rowscale,
                                                                float* __restrict__ dZ, int64_t lddz, int c_store,
                                                                const int64_t* __restrict__ part_rows, int stats_blocks,
-                                                               double* __restrict__ loss_part) {
+                                                               double* __restrict__ loss_part, float* __restrict__ col_part) {
     __shared__ double smd[4];
     const int t = threadIdx.x & 15;
     __shared__ int64_t smi[4];
@@ -649,6 +650,9 @@ __device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_
     const float inv_s = S > 0 ? 1.0f / (float)S : 0.f;
     const int64_t stride = (int64_t)gx * 16;
     double loss = 0.0;
+    float cols[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) cols[q] = 0.f;
     int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     float cur[NV], nxt[NV];
     auto load = [&](int64_t r, float (&v)[NV]) {
@@ -677,13 +681,15 @@ __device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_
             const int y = labels[v];
             float w = 1.f;
             if (node_level) w = (float)coverage_ratio(cv, v);
-            const float k = w * inv_s * (rowscale ? rowscale[v] : 1.f), inv_sum = 1.0f / sum;
+            const float k1 = w * inv_s, k = k1 * (rowscale ? rowscale[v] : 1.f), inv_sum = 1.0f / sum;
             float zy = 0.f;                           // the label's logit sits in lane y%16, slot y/16
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
                 const int c = t + 16 * q;
                 if (c == y) zy = cur[q];
-                if (c < c_store) dZ[row * lddz + c] = c < C ? (e[q] * inv_sum - (c == y ? 1.f : 0.f)) * k : 0.f;
+                const float d = e[q] * inv_sum - (c == y ? 1.f : 0.f);
+                if (c < c_store) dZ[row * lddz + c] = c < C ? d * k : 0.f;
+                cols[q] = fmaf(d, k1, cols[q]);
             }
             zy = __shfl(zy, y & 15, 16);
             if (t == 0) loss += (double)w * (double)(logf(sum) + mx - zy);
@@ -697,6 +703,17 @@ __device__ __forceinline__ void softmax_xent_reg_kernel_body(unsigned gx, int64_
     }
     loss = block_sum<double>(loss, smd);
     if (threadIdx.x == 0) loss_part[blockIdx.x] = loss;
+    if (!col_part) return;
+    __shared__ float red[16][16 * NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) red[threadIdx.x >> 4][t + 16 * q] = cols[q];
+    __syncthreads();
+    for (int c = threadIdx.x; c < C; c += 256) {
+        float s = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s += red[r][c];
+        col_part[(int64_t)blockIdx.x * C + c] = s;
+    }
 }
 template <int NV>
 __global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, int C, const float* __restrict__ Z,
@@ -707,8 +724,8 @@ __global__ __launch_bounds__(256) void softmax_xent_reg_kernel(int64_t n_rows, i
                                                                const float* __restrict__ rowscale,
                                                                float* __restrict__ dZ, int64_t lddz, int c_store,
                                                                const int64_t* __restrict__ part_rows, int stats_blocks,
-                                                               double* __restrict__ loss_part) {
-    softmax_xent_reg_kernel_body<NV>(gridDim.x, n_rows, C, Z, ldz, labels, nodes, mask, node_level, cv, rowscale, dZ, lddz, c_store, part_rows, stats_blocks, loss_part);
+                                                               double* __restrict__ loss_part, float* __restrict__ col_part) {
+    softmax_xent_reg_kernel_body<NV>(gridDim.x, n_rows, C, Z, ldz, labels, nodes, mask, node_level, cv, rowscale, dZ, lddz, c_store, part_rows, stats_blocks, loss_part, col_part);
 }
 template <int NV>
 struct softmax_xent_reg_kernel_op {
@@ -717,7 +734,8 @@ struct softmax_xent_reg_kernel_op {
 };
 
 grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int64_t ldz, const int32_t* labels, int32_t node_level,
-                               const float* rowscale, float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st, StepSums* sums) {
+                               const float* rowscale, float* dZ, int64_t lddz, grp_step_stats* stats, hipStream_t st, StepSums* sums,
+                               float* col_part, float* col_out) {
     const int64_t n_rows = in.n_loss;
     ProfScope ps("softmax_xent", st, 0.0, 8.0 * n_rows * C);
     const CoverageIn cv{in.d_local, in.d_global, in.w_local, in.w_global};
@@ -729,15 +747,16 @@ grp_status launch_softmax_xent(const StatsIn& in, int32_t C, const float* Z, int
     n_rows, C, Z, ldz, labels, in.nodes, in.mask, node_level, cv, rowscale, dZ, lddz, c_store,               \
         (const int64_t*)stats_rows(in.scratch), counted, loss_part
     const int blocks = stats_blocks(n_rows, 16);
-    auto go = [&](auto kernel, auto op) { launch(kernel, op, dim3((unsigned)blocks), st, GRP_SOFTMAX_ARGS); };
+    auto go = [&](auto kernel, auto op) { launch(kernel, op, dim3((unsigned)blocks), st, GRP_SOFTMAX_ARGS, col_part); };
     if (c_store <= 16) go(softmax_xent_reg_kernel<1>, softmax_xent_reg_kernel_op<1>());
     else if (c_store <= 32) go(softmax_xent_reg_kernel<2>, softmax_xent_reg_kernel_op<2>());
     else if (c_store <= 64) go(softmax_xent_reg_kernel<4>, softmax_xent_reg_kernel_op<4>());
     else if (c_store <= 128) go(softmax_xent_reg_kernel<8>, softmax_xent_reg_kernel_op<8>());
-    else if (c_store <= 192) go(softmax_xent_reg_kernel<12>, softmax_xent_reg_kernel_op<12>());       // (1024 rows of 172 columns: 11 -> 5.5 us)
+    else if (c_store <= XENT_COLS_MOST) go(softmax_xent_reg_kernel<12>, softmax_xent_reg_kernel_op<12>());       // (1024 rows of 172 columns: 11 -> 5.5 us)
     else launch_alone(softmax_xent_kernel, dim3((unsigned)blocks), dim3(256), 0, st, GRP_SOFTMAX_ARGS);
 #undef GRP_SOFTMAX_ARGS
     GRP_LAUNCH_CHECK();
+    if (col_part) sums->add(SUM_COLUMNS, col_part, blocks, 0, C, 0, col_out, nullptr, nullptr, C);
     RecordArgs r{(const StatsPartial*)in.scratch, counted, (in.sampled_count || in.w_local) ? 0 : 1, in.nnz_const, {}, loss_part, blocks, stats};
     r.np.n = in.n_parts;
     r.np.bad_seeds = in.bad_seeds;

@@ -44,7 +44,8 @@ constexpr int BK = 32;      // k-tile depth
 // Resident workgroups per CU that the kernels are built for: three of 168 registers, but two where the partial sums of a tile would
 // not fit beside the rest and were spilled (NT, 128 columns with B split in the kernel: K = N = 256 over 3e5 rows 380 us with three,
 // 338 with two; TN with two 32 x 32 tiles per wavefront: K = 256, N = 47 129 and 112 us, with four: 1127 and 323).
-constexpr int nt_wgs(int TN, bool pre) { return TN >= 8 && !pre ? 2 : 3; }
+// Four of 128 where 64 columns of an fp32 product take hardly more (130 if left alone).
+constexpr int nt_wgs(int TN, bool pre, bool lean = false) { return TN >= 8 && !pre ? 2 : TN == 4 && pre && lean ? 4 : 3; }
 constexpr int tn_wgs(int tiles) { return tiles > 1 ? 2 : 3; }
 constexpr int NT_PRE_SLABS = 512;      // products over fewer slabs of 128 rows whose B is not ready split it in the kernel (a launch for the planes costs 3 us)
 constexpr int NXCD = 8;     // L2 domains; consecutive workgroup ids go round them
@@ -836,11 +837,18 @@ __device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
     const bool rs_in = g.rowscale && n0 + BN <= rs_cols;
     const bool rs_out = !g.rowscale || n0 >= rs_cols;
     const bool lean = vec && n0 + BN <= g.N && (bias_in || bias_out) && (rs_in || rs_out);
+    constexpr bool COLS = PRE && !IRREG && !A_BF16;
+    const bool cols = COLS && g.col_part;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int lr = wave * 16 * TM + 16 * i + li;
-        if (lr >= rows_here) continue;
+        if (lr >= rows_here) {
+#pragma unroll
+            for (int j = 0; COLS && j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            continue;
+        }
         const int64_t m = m0 + lr;
+        const float cm = cols ? g.col_mul[m] : 0.f;
         const int nl = n0 + 4 * lq;
         const float rs = g.rowscale ? g.rowscale[m] : 1.f;
         float* const Cr = g.C + m * g.ldc + nl;
@@ -870,6 +878,7 @@ __device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
                 v.x = mv[j].x > 0.f ? v.x : 0.f; v.y = mv[j].y > 0.f ? v.y : 0.f;
                 v.z = mv[j].z > 0.f ? v.z : 0.f; v.w = mv[j].w > 0.f ? v.w : 0.f;
                 *reinterpret_cast<float4*>(Cr + 16 * j) = v;
+                if (COLS) acc[i][j] = floatx4{v.x * cm, v.y * cm, v.z * cm, v.w * cm};
             }
             continue;
         }
@@ -893,6 +902,7 @@ __device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
                     raw[q] = 0.f;
                 }
                 v[q] = t;
+                if (COLS) acc[i][j][q] = t * cm;
             }
             if (vec) {
                 if (nb >= n_store) continue;
@@ -908,14 +918,40 @@ __device__ __forceinline__ void gemm_nt_kernel_body(unsigned gx, GemmNNArgs g) {
             }
         }
     }
+    // Column sums: over the 16 rows of the lanes' DPP row, then over the wavefronts.  (A pass of its own over C took 199 us over 2^20 rows of
+    // 256, and a launch of 4.6 where the rows are few.)
+    if constexpr (COLS) {
+        if (!cols) return;
+        __syncthreads();                              // everybody is done with the tiles of B
+        float* const red = reinterpret_cast<float*>(lds);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            float4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float x = acc[0][j][q];
+#pragma unroll
+                for (int i = 1; i < TM; ++i) x += acc[i][j][q];
+                auto turn = [](float y, auto ctrl) { return y + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), decltype(ctrl)::value, 0xF, 0xF, false)); };
+                x = turn(x, std::integral_constant<int, 0x128>());      // row_ror 8, 4, 2, 1
+                x = turn(x, std::integral_constant<int, 0x124>());
+                x = turn(x, std::integral_constant<int, 0x122>());
+                x = turn(x, std::integral_constant<int, 0x121>());
+                (q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w) = x;
+            }
+            if (li == 0) *reinterpret_cast<float4*>(red + wave * BN + 16 * j + 4 * lq) = v;
+        }
+        __syncthreads();
+        if (tid < BN && n0 + tid < g.N) g.col_part[slab * g.N + n0 + tid] = (red[tid] + red[BN + tid]) + (red[2 * BN + tid] + red[3 * BN + tid]);
+    }
 }
 template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
-__global__ __launch_bounds__(256, nt_wgs(TN, PRE)) void gemm_nt_kernel(GemmNNArgs g) {
+__global__ __launch_bounds__(256, nt_wgs(TN, PRE, !IRREG && sizeof(AT) == 4)) void gemm_nt_kernel(GemmNNArgs g) {
     gemm_nt_kernel_body<AT, TM, TN, IRREG, PRE>(gridDim.x, g);
 }
 template <typename AT, int TM, int TN, bool IRREG, bool PRE = false>
 struct gemm_nt_kernel_op {
-    static constexpr int THREADS = 256, WGS = nt_wgs(TN, PRE);
+    static constexpr int THREADS = 256, WGS = nt_wgs(TN, PRE, !IRREG && sizeof(AT) == 4);
     template <class... A> static __device__ __forceinline__ void run(unsigned gx, const A&... a) { gemm_nt_kernel_body<AT, TM, TN, IRREG, PRE>(gx, a...); }
 };
 
@@ -1027,6 +1063,7 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
                  ok ? p.tile_n : n_eff > 64 ? 128 : n_eff > 32 ? 64 : 32, ok && p.pre ? "_planes" : "");
         ProfScope ps(pname, st, nn_flops, nn_bytes);
         if (!ok) {                                       // slow, always-safe kernel
+            if (a.col_part) return fail(GRP_EUNSUPPORTED, "gemm_nn: column sums of such a product");
             if (a.a_bf16) nn_pick<__hip_bfloat16, false>(a, st); else nn_pick<float, false>(a, st);
             GRP_LAUNCH_CHECK();
             return GRP_OK;
@@ -1034,6 +1071,10 @@ grp_status launch_gemm_nn(const GemmNNArgs& a, hipStream_t st) {
         GemmNNArgs t = a;
         t.a_tight = veca ? 0 : 1;
         const bool irreg = t.a_tight || a.a_rows != nullptr || a.a_valid_rows_dev != nullptr || (a.a_valid_rows > 0 && a.a_valid_rows < a.M);
+        if (a.col_part) {
+            if (irreg || a.a_bf16 || !p.pre || a.M_dev) return fail(GRP_EUNSUPPORTED, "gemm_nn: column sums of such a product");
+            a.sums->add(SUM_COLUMNS, a.col_part, (int32_t)cdiv(a.M, p.tile_m), 0, a.N, 0, a.col_out, nullptr, nullptr, a.N);
+        }
         const int64_t slabs = round_up(cdiv(a.M, p.tile_m), NXCD);
         const unsigned blocks = (unsigned)(slabs * cdiv(n_eff, p.tile_n));
         if (p.pre && !a.ready) {

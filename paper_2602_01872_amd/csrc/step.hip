@@ -460,7 +460,10 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
     float* dZ_other = p.dZb;
     float* G = p.Ga;            // dL/dH' of the current layer (residual models only)
     float* G_other = p.Gb;
-    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, p.gr, dZ, ldp(C), stats, st, &sums));
+    // db of the last layer comes from the loss, of the others from the product that makes their dZ'
+    const bool xent_cols = n > 0 && ldp(C) <= XENT_COLS_MOST;
+    GRP_TRY(launch_softmax_xent(pre.stats, C, p.L[k - 1].H_out, ldp(C), labels, o->estimator == GRP_EST_NODE_LEVEL, p.gr, dZ, ldp(C), stats, st, &sums,
+                                xent_cols ? (float*)p.L[k - 1].colsum_ws : nullptr, grad + p.L[k - 1].off_b));
 
     for (int l = k - 1; l >= 0; --l) {
         const LayerBufs& L = p.L[l];
@@ -468,7 +471,8 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         const void* Hin = l == 0 ? X : (const void*)p.L[l - 1].H_out;
         const int64_t ldin = l == 0 ? m->dims[0] : ldp(fin);
         const int in_bf16 = l == 0 && m->feat_dtype == GRP_DTYPE_BF16;
-        GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, L.colsum_ws, st, &sums));
+        if (n == 0 || (l == k - 1 && !xent_cols))
+            GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, L.colsum_ws, st, &sums));
         SpmmArgs s;
         fill_spmm(s, B, true, p.partials);
         s.F = fout; s.X = dZ; s.ldx = ldp(fout); s.scale = GRP_SCALE_RSQRT; s.self_term = sl; s.Y = p.tmpA; s.ldy = ldp(fout);
@@ -487,6 +491,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
             if (Lp.skip) { c.C_raw = G_other; c.ld_raw = ldp(fin); }
             c.rowscale = gr_bwd; c.mask = Lp.skip ? Lp.Act : Lp.H_out; c.ld_mask = ldp(fin);
             c.C = dZ_other; c.ldc = ldp(fin); c.zero_pad_to = (int)ldp(fin);
+            c.sums = &sums; c.col_part = (float*)Lp.colsum_ws; c.col_out = grad + Lp.off_b; c.col_mul = p.grinv;
             GRP_TRY(launch_gemm_nn(c, st));
             float* sg = G; G = G_other; G_other = sg;
         }

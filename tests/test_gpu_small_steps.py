@@ -88,10 +88,12 @@ def test_weights_at_tile_edges_on_a_used_workspace(g, arch, N, dims):
 
 
 @pytest.mark.parametrize("arch,N,dims", [
-    ("gcn", 300, [7, 5, 6, 9, 3]), ("gcn", 900, [33, 64, 31, 32, 16]), ("gcn", 5000, [64, 128, 8, 130, 41, 5]), ("sage", 5000, [12] * 8 + [3])])
+    ("gcn", 300, [7, 5, 6, 9, 3]), ("gcn", 900, [33, 64, 31, 32, 16]), ("gcn", 5000, [64, 128, 8, 130, 41, 5]), ("sage", 5000, [12] * 8 + [3]),
+    ("gcn", 50_001, [20, 130, 96, 61, 33, 7]), ("gcn", 700, [16, 20, 193])])
 def test_sums_that_a_deep_step_leaves_to_its_end(g, arch, N, dims):
     """Every layer's products and column sums leave partial results to the step's last launch: more of them than three layers have, of few and
-    of many slices, in vectors and not; one step alone and two that share their launches, on workspaces that held NaN."""
+    of many slices, in vectors and not, column sums from the loss (up to 192 classes) and from products of 64 and of
+    128 rows; one step alone and two that share their launches, on workspaces that held NaN."""
     seed = 13
     s, d = synth.rmat_graph(13, 6 * N, seed=seed, n_nodes=N)
     part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, seed, 0)
