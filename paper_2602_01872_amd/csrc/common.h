@@ -276,6 +276,28 @@ template <int WAVES, typename T> __device__ __forceinline__ T block_scan(T v, T*
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
+// add(load(c), true) for c in [c0, c1), in this order, eight loads in flight, four at the end: a place past the end is loaded from the last
+// one again and handed over with false.  (Loaded one by one, the longest row's partial rows were what the launches that combine them waited for:
+// 3e5 rows of 256, sums 9.1 -> 5.5 us, attention 10.1 -> 5.6; 1e5 rows of 75 7.1 -> 4.9.)
+template <class Load, class Add> __device__ __forceinline__ void in_order(int c0, int c1, Load load, Add add) {
+    typedef decltype(load(0)) T;
+    int c = c0;
+    for (; c + 8 <= c1; c += 8) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = load(c + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(v[u], true);
+    }
+    for (; c < c1; c += 4) {
+        T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = load(imin(c + u, c1 - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add(v[u], c + u < c1);
+    }
+}
+
 // 16 and 8 bytes at any element boundary: global loads of these need no alignment beyond the element's
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));

@@ -464,16 +464,25 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(GatWalk A, const int32
     float scal = 0.f;
     gat_row_setup<PASS, G, NJ>(A, r, t, live, R);
     const int fpad = (A.F + 3) & ~3;
-    for (int c = c0; c < c1; ++c) {
-        const float* prow = A.partials + (int64_t)c * A.ld_part;
+    struct Part { float4 v[NJ]; float s; };
+    in_order(c0, c1,
+             [&](int c) {
+                 const float* prow = A.partials + (int64_t)c * A.ld_part;
+                 Part p;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            if (!live[j]) continue;
-            const float4 v = ld4(prow + 4 * (t + G * j));
-            acc[j].x += v.x; acc[j].y += v.y; acc[j].z += v.z; acc[j].w += v.w;
-        }
-        scal += prow[fpad];
-    }
+                 for (int j = 0; j < NJ; ++j) p.v[j] = ld4(prow + (live[j] ? 4 * (t + G * j) : 0));
+                 p.s = prow[fpad];
+                 return p;
+             },
+             [&](const Part& p, bool on) {
+#pragma unroll
+                 for (int j = 0; j < NJ; ++j) {
+                     const bool is = on && live[j];
+                     acc[j].x += is ? p.v[j].x : 0.f; acc[j].y += is ? p.v[j].y : 0.f;
+                     acc[j].z += is ? p.v[j].z : 0.f; acc[j].w += is ? p.v[j].w : 0.f;
+                 }
+                 scal += on ? p.s : 0.f;
+             });
     gat_row_finish<PASS, G, NJ>(A, R, r, t, live, acc, scal);
 }
 

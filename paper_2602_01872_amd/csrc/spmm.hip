@@ -362,7 +362,8 @@ __device__ __forceinline__ void spmm_combine_kernel_body(unsigned gx, const int3
         const int col = 4 * (t + G * j);
         if (col >= ep.F) continue;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int c = c0; c < c1; ++c) add4(acc, *reinterpret_cast<const float4*>(partials + (int64_t)c * ld_part + col));
+        in_order(c0, c1, [&](int c) { return *reinterpret_cast<const float4*>(partials + (int64_t)c * ld_part + col); },
+                 [&](const float4& v, bool on) { add4(acc, on ? v : make_float4(0.f, 0.f, 0.f, 0.f)); });
         finish_row<XT>(ep, i, deg, col, acc, X, ldx);
     }
 }
