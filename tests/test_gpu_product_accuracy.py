@@ -116,3 +116,20 @@ def test_errors_have_no_sign(g, way, M, K, N):
     n = got.numel()
     size = math.sqrt(total / n)
     assert abs(float(err)) / n <= 5 * math.sqrt(float(squares) / n / n) + U / 2000 * size
+
+
+@pytest.mark.parametrize("M,K,N", [(1, 65, 65), (33, 66, 96), (700, 128, 95), (5_000, 75, 130), (5_000, 130, 192), (3_000, 257, 161), (100_003, 75, 185), (31, 100, 288)])
+@pytest.mark.parametrize("bf16,pad", [(False, 0), (False, 1), (True, 0)])
+def test_tiles_of_96_columns(g, M, K, N, bf16, pad):
+    """Widths whose tiles of 96 columns leave fewer of them empty than tiles of 128, packed and with room at the rows' ends.  Every element is a
+    sum in which at most M / 32 + 40 roundings follow one another (a k-tile's five, the tiles', the slices')."""
+    A, B = values("normal", M, K, 11), values("normal", M, N, 12)
+    if bf16:
+        A = A.bfloat16()
+    a, b = (torch.full((M, w + 7 * pad), float("nan"), device=DEV, dtype=t.dtype) for t, w in ((A, K), (B, N)))
+    a[:, :K], b[:, :N] = A, B
+    got = torch.full((K, N), float("nan"), device=DEV)
+    ws = torch.empty(max(16, g.grp_gemm_tn_workspace_bytes(M, K, N)), dtype=torch.uint8, device=DEV)
+    g.grp_gemm_tn(M, K, N, a, a.shape[1], g.DTYPE_BF16 if bf16 else g.DTYPE_FP32, b, b.shape[1], got, N, ws)
+    want, size = A.double().T @ B.double(), A.double().abs().T @ B.double().abs()
+    assert bool(((got.double() - want).abs() <= (M / 32 + 40) * U * size).all())
