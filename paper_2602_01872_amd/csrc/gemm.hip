@@ -1138,9 +1138,14 @@ static TnPlan tn_plan(int64_t M, int K, int N, int products = 1) {
     TnPlan p;
     p.bn_tile = N > 64 ? 128 : (N > 32 ? 64 : 32);
     p.bk_tile = (K <= 64 && p.bn_tile >= 64) ? 64 : 128;      // a short K fills a 64-row tile
-    // 96 columns where fewer of the tiles' columns lie beyond N then (1e5 rows, K = 75 / 256, us, tiles of 128 and 96 columns: N = 72 47/39 and 64/55,
-    // 130 62/53 and 107/89, 280 84/70 and 231/201; 3e3 rows, K = 75: 14.2/12.6, 15.5/13.6, 18.0/15.2).
-    if (N > 64 && p.bk_tile == 128 && round_up(N, 96) < round_up(N, 128)) p.bn_tile = 96;
+    // 96 columns, or 96 rows, where fewer of the tiles' elements lie beyond the product then (1e5 rows, K = 75 / 256, us, tiles of 128 and 96 columns:
+    // N = 72 47/39 and 64/55, 130 62/53 and 107/89, 280 84/70 and 231/201; 3e3 rows, K = 75: 14.2/12.6, 15.5/13.6, 18.0/15.2.
+    // K = 72 / 280, N = 256: 63/54 and 231/199; 3e3 rows: 16.4/15.5, 22.8/21.2).
+    if (N > 64 && p.bk_tile == 128) {
+        const int64_t n128 = round_up(N, 128), n96 = round_up(N, 96), k128 = round_up(K, 128), k96 = round_up(K, 96);
+        if (n96 * k128 < n128 * k128 && n96 * k128 <= n128 * k96) p.bn_tile = 96;
+        else if (k96 < k128) p.bk_tile = 96;
+    }
     p.tiles_k = (int)cdiv(K, p.bk_tile);
     p.tiles_n = (int)cdiv(N, p.bn_tile);
     // Products over very many rows are cut into up to eight times the slices: the chains of partial sums get that much shorter (at 256
@@ -1198,7 +1203,7 @@ size_t gemm_tn_workspace_bytes(int64_t M, int32_t K, int32_t N) {
 // The matrix instruction wants eight consecutive k per lane, and k is the node dimension here: a staging thread loads
 // four columns of eight consecutive rows, which in its registers are four runs of eight k values.  Column 4*g + q of a
 // tile W columns wide is kept in tile row q*(W/4) + g, so that the lanes of a wavefront (consecutive g) write consecutive
-// rows.  The first threads stage A, the next ones B.  LDS rows hold 32 k values (64 bytes, 4 places of 16); the eight k
+// rows.  The first threads stage A, the next ones B (or the other way round).  LDS rows hold 32 k values (64 bytes, 4 places of 16); the eight k
 // from 8*c of a row sit at place c ^ tn_turn(row).
 // Whole 32-row steps load as they are; columns past K or N are read from clamped
 // addresses and never masked, since they only reach output rows / columns that are not stored.
@@ -1227,7 +1232,8 @@ __device__ __forceinline__ void gemm_tn_kernel_body(unsigned gx, GemmTNArgs g, i
     constexpr int PLANE_A = BKA * 64, PLANE_B = BN * 64;
     constexpr int QA = BKA / 4, QB = BN / 4;               // column groups of a tile
     constexpr int TA = QA * (BK / 8), TB = QB * (BK / 8);  // staging threads of each operand
-    static_assert(TA % 64 == 0 && TA + TB <= 256 && QA % 8 == 0 && QB % 8 == 0, "an operand is staged by whole wavefronts");
+    constexpr int A0 = TA % 64 == 0 ? 0 : TB, B0 = A0 ? 0 : TA;      // their first threads
+    static_assert((A0 ? TB : TA) % 64 == 0 && TA + TB <= 256 && QA % 8 == 0 && QB % 8 == 0, "an operand is staged by whole wavefronts");
     __shared__ __attribute__((aligned(16))) unsigned char lds[3 * (PLANE_A + PLANE_B)];
     unsigned char* const As = lds;
     unsigned char* const Bs = lds + 3 * PLANE_A;
@@ -1251,9 +1257,9 @@ __device__ __forceinline__ void gemm_tn_kernel_body(unsigned gx, GemmTNArgs g, i
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int wm = wave / WN, wn = wave % WN;
-    const bool is_a = tid < TA, is_b = !is_a && tid < TA + TB;
+    const bool is_a = tid >= A0 && tid < A0 + TA, is_b = tid >= B0 && tid < B0 + TB;
     const int q_n = is_a ? QA : QB;                        // the operand this thread stages:
-    const int lt = is_a ? tid : tid - TA;
+    const int lt = tid - (is_a ? A0 : B0);
     const int grp = lt % q_n, mb = lt / q_n;               // four columns from 4 * grp, eight rows from 8 * mb
     const void* const op = is_a ? (a2 ? (const void*)g.A2 : g.A) : (const void*)(b2 ? g.B2 : g.B);
     const int64_t ld = is_a ? (a2 ? g.lda2 : g.lda) : (b2 ? g.ldb2 : g.ldb);
@@ -1499,6 +1505,7 @@ static void tn_pick(const GemmTNArgs& a, const TnPlan& p, int dual, float* out, 
     } while (0)
     if (p.bk_tile == 64 && p.bn_tile == 128) GRP_TN_LAUNCH(2, 2, 1, 2);
     else if (p.bk_tile == 64) GRP_TN_LAUNCH(2, 2, 1, 1);
+    else if (p.bk_tile == 96) GRP_TN_LAUNCH(1, 4, 3, 1);
     else if (p.bn_tile == 128) GRP_TN_LAUNCH(2, 2, 2, 2);
     else if (p.bn_tile == 96) GRP_TN_LAUNCH(4, 1, 1, 3);
     else if (p.bn_tile == 64) GRP_TN_LAUNCH(4, 1, 1, 2);

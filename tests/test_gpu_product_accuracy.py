@@ -118,10 +118,11 @@ def test_errors_have_no_sign(g, way, M, K, N):
     assert abs(float(err)) / n <= 5 * math.sqrt(float(squares) / n / n) + U / 2000 * size
 
 
-@pytest.mark.parametrize("M,K,N", [(1, 65, 65), (33, 66, 96), (700, 128, 95), (5_000, 75, 130), (5_000, 130, 192), (3_000, 257, 161), (100_003, 75, 185), (31, 100, 288)])
+@pytest.mark.parametrize("M,K,N", [(1, 65, 65), (33, 66, 96), (700, 128, 95), (5_000, 75, 130), (5_000, 130, 192), (3_000, 257, 161), (100_003, 75, 185), (31, 100, 288),
+                                   (1, 65, 200), (33, 96, 100), (5_000, 66, 128), (700, 190, 256), (100_003, 81, 255), (3_000, 257, 97)])
 @pytest.mark.parametrize("bf16,pad", [(False, 0), (False, 1), (True, 0)])
-def test_tiles_of_96_columns(g, M, K, N, bf16, pad):
-    """Widths whose tiles of 96 columns leave fewer of them empty than tiles of 128, packed and with room at the rows' ends.  Every element is a
+def test_tiles_of_96(g, M, K, N, bf16, pad):
+    """Shapes whose tiles of 96 columns, or of 96 rows, leave less of them empty than tiles of 128, packed and with room at the rows' ends.  Every element is a
     sum in which at most M / 32 + 40 roundings follow one another (a k-tile's five, the tiles', the slices')."""
     A, B = values("normal", M, K, 11), values("normal", M, N, 12)
     if bf16:
