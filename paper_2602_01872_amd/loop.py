@@ -17,7 +17,10 @@ from .controller import Controller
 # its own, so this also bounds the memory).  Eight steps one by one / merged by two / four / eight, us, workspace of one step:
 #   GraphSAGE 100-256-256-47   26 MiB 1661/917/526/355   117 MiB 2703/1927/1552/1389   369 MiB 5750/4873/4485/4332   706 MiB 8827/8842/8832/8828
 #   GCN 64-128-16               5 MiB 959/527/303/185     70 MiB 1409/885/605/498      136 MiB 1771/1188/980/915     498 MiB 3917/3458/3370/3182
+# (measured on workspaces that held one layer's partial sums at a time; every further layer's, at most 512 tiles of 64 KiB and their column
+# sums, come on top)
 MERGE_WORKSPACE_BYTES = 512 << 20
+MERGE_LAYER_BYTES = 34 << 20
 MERGE_STEPS = 8
 
 
@@ -58,7 +61,8 @@ class PhaseParallelTrainer:
         ws_bytes = max(g.grp_step_workspace_bytes(p, model, self.opts) for p in parts)
         n_lanes = max(1, min(int(streams), max_active))
         self.side = [torch.cuda.Stream(device=dev) for _ in range(n_lanes)] if n_lanes > 1 else []
-        if not self.side and ws_bytes <= MERGE_WORKSPACE_BYTES and model.arch != g.ARCH_GAT:      # (an attention model's steps are not merged)
+        merge_bytes = MERGE_WORKSPACE_BYTES + MERGE_LAYER_BYTES * (model.n_layers - 1)
+        if not self.side and ws_bytes <= merge_bytes and model.arch != g.ARCH_GAT:      # (an attention model's steps are not merged)
             n_lanes = min(MERGE_STEPS, max_active)
         self.ws = [torch.empty(ws_bytes, dtype=torch.uint8, device=dev) for _ in range(n_lanes)]
         self.step_count = 0
