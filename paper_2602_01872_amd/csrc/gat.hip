@@ -521,10 +521,11 @@ __global__ __launch_bounds__(256) void gat_pack_kernel(const float* __restrict__
 
 // Gradients of W, a_src, a_dst from dWx = H^T dT_ext [Fin x ldx]:
 //   dW = dWx[:, :F] + dWx[:, cp] a_src^T + dWx[:, cp+1] a_dst^T,  da_src = W^T dWx[:, cp],  da_dst = W^T dWx[:, cp+1].
-__global__ __launch_bounds__(256) void gat_param_grad_kernel(const float* __restrict__ dWx, int ldx, const float* __restrict__ W,
+// (The bias gradient comes along from where the step's sums left it.)
+__global__ __launch_bounds__(256) void gat_param_grad_kernel(const float* __restrict__ dWx, const float* __restrict__ dbias, int ldx, const float* __restrict__ W,
                                                              const float* __restrict__ a_s, const float* __restrict__ a_d,
                                                              int fin, int fout, float* __restrict__ gW,
-                                                             float* __restrict__ ga_s, float* __restrict__ ga_d) {
+                                                             float* __restrict__ ga_s, float* __restrict__ ga_d, float* __restrict__ gb) {
     // workgroup j < fout: column j of dW and the two attention-vector gradients of index j
     __shared__ float sm[8];
     const int cp = (fout + 3) & ~3;
@@ -544,6 +545,7 @@ __global__ __launch_bounds__(256) void gat_param_grad_kernel(const float* __rest
     if (threadIdx.x == 0) {
         ga_s[j] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
         ga_d[j] = (sm[4] + sm[5]) + (sm[6] + sm[7]);
+        gb[j] = dbias[j];
     }
 }
 
@@ -554,14 +556,19 @@ struct GatLayer {
     int64_t off_w, off_as, off_ad, off_b;
     float *Wp, *Wt, *Tx, *Hout;
     float2 *pq, *rowstat;
+    // what the step's sums (StepSums) read and write
+    float *dWx, *dbias, *colsum;
+    void* tn_ws;
+    size_t tn_ws_bytes;
 };
 
 struct GatPlan {
     std::vector<GatLayer> L;
-    float *dZa, *dZb, *dTx, *dq, *dWx, *partials, *colsum;
+    float *dZa, *dZb, *dTx, *dq, *partials;
+    char* base;
     float4* dst;
-    void *tn_ws, *stats_ws;
-    size_t tn_ws_bytes, total;
+    void* stats_ws;
+    size_t total;
     unsigned char* planes = nullptr;   // the weights of the product at hand, split (GemmNNArgs::planes)
     size_t planes_bytes = 0;
 };
@@ -574,12 +581,21 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
     const int64_t n = part->n;
     const int k = m->n_layers;
     p.L.resize(k);
-    int64_t off = 0, ldmax = 4, ldxmax = 8, wxmax = 1;
-    size_t tn_bytes = 0, pl_bytes = 0;
-    for (int l = 0; l < k; ++l) {
+    int64_t off = 0, ldmax = 4, ldxmax = 8;
+    size_t pl_bytes = 0;
+    p.base = (char*)ws;
+    for (int l = 0; l < k; ++l) {          // first: within reach of 32-bit numbers of floats
         GatLayer& L = p.L[l];
         L.fin = m->dims[l]; L.fout = m->dims[l + 1];
         L.ldh = ldp4(L.fout); L.ldx = L.ldh + 4; L.ldin_pad = ldp4(L.fin);
+        L.dWx = b.take<float>((size_t)L.fin * L.ldx);
+        L.dbias = b.take<float>((size_t)L.fout);
+        L.colsum = b.take<float>((size_t)GAT_DST_BLOCKS * L.ldx);
+        L.tn_ws_bytes = gemm_tn_workspace_bytes(n, L.fin, (int32_t)L.ldx);
+        L.tn_ws = b.take<char>(L.tn_ws_bytes);
+    }
+    for (int l = 0; l < k; ++l) {
+        GatLayer& L = p.L[l];
         L.off_w = off; off += (int64_t)L.fin * L.fout;
         L.off_as = off; off += L.fout;
         L.off_ad = off; off += L.fout;
@@ -592,9 +608,6 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
         L.rowstat = b.take<float2>((size_t)n);
         if (L.ldh > ldmax) ldmax = L.ldh;
         if (L.ldx > ldxmax) ldxmax = L.ldx;
-        if ((int64_t)L.fin * L.ldx > wxmax) wxmax = (int64_t)L.fin * L.ldx;
-        const size_t t = gemm_tn_workspace_bytes(n, L.fin, (int32_t)L.ldx);
-        if (t > tn_bytes) tn_bytes = t;
         pl_bytes = std::max({pl_bytes, gemm_planes_bytes(n, (int32_t)L.ldx, L.fin), gemm_planes_bytes(n, L.fin, (int32_t)L.ldx)});
     }
     p.dZa = b.take<float>((size_t)n * ldmax);
@@ -602,12 +615,8 @@ static GatPlan gat_plan(const grp_partition_t* part, const grp_model_desc* m, vo
     p.dTx = b.take<float>((size_t)n * ldxmax);
     p.dst = b.take<float4>((size_t)n);
     p.dq = b.take<float>((size_t)n);
-    p.dWx = b.take<float>((size_t)wxmax);
     const int64_t chunks_cap = part->csr_long.n_chunks > part->csc_long.n_chunks ? part->csr_long.n_chunks : part->csc_long.n_chunks;
     p.partials = b.take<float>((size_t)chunks_cap * ldxmax);
-    p.tn_ws = b.take<char>(tn_bytes);
-    p.tn_ws_bytes = tn_bytes;
-    p.colsum = b.take<float>((size_t)GAT_DST_BLOCKS * ldxmax);
     if (pl_bytes > 0) p.planes = b.take<unsigned char>(pl_bytes);
     p.planes_bytes = pl_bytes;
     p.stats_ws = b.take<char>(stats_workspace_bytes(n));
@@ -627,18 +636,18 @@ void gat_step_activation(const grp_partition_t* part, const grp_model_desc* m, v
 }
 
 template <int PASS, int G, int NJ>
-static void gat_walk_one(const GatWalk& A, const LongRows* lr, float* dbias, hipStream_t st) {
+static void gat_walk_one(const GatWalk& A, const LongRows* lr, StepSums* sums, float* dbias, hipStream_t st) {
     constexpr int ROWS = 256 / G;
     const int64_t blocks = PASS == GAT_DST ? std::min<int64_t>(cdiv(A.n, ROWS), GAT_DST_BLOCKS) : cdiv(A.n, ROWS);
     hipLaunchKernelGGL((gat_walk_kernel<PASS, G, NJ>), dim3((unsigned)(A.n_chunks + blocks)), dim3(256), 0, st, A);
-    if (PASS == GAT_DST) launch_colsum_final(A.colsum, blocks, A.F, dbias, st);
+    if (PASS == GAT_DST) sums->add(SUM_COLUMNS, A.colsum, (int32_t)blocks, 0, A.F, 0, dbias, nullptr, nullptr, A.F);
     if (A.n_chunks > 0)
         hipLaunchKernelGGL((gat_combine_kernel<PASS, G, NJ>), dim3((unsigned)cdiv(lr->n_long, ROWS)), dim3(256), 0, st, A,
                            (const int32_t*)lr->long_row, (const int32_t*)lr->long_first, lr->n_long);
 }
 
 template <int PASS>
-static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials, hipStream_t st, float* dbias = nullptr /*DST: column sums of dOut*/) {
+static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials, hipStream_t st, StepSums* sums = nullptr, float* dbias = nullptr /*DST: column sums of dOut*/) {
     const bool split = lr && lr->n_long > 0;
     A.long_thr = split ? (int64_t)SPMM_LONG_ROW : INT64_MAX;
     A.n_chunks = split ? lr->n_chunks : 0;
@@ -647,15 +656,15 @@ static grp_status launch_gat_walk(GatWalk A, const LongRows* lr, float* partials
     A.partials = partials;
     A.ld_part = round_up(A.F, 4) + 4;
     const int f4 = (A.F + 3) / 4;
-    if (f4 <= 1) gat_walk_one<PASS, 1, 1>(A, lr, dbias, st);
-    else if (f4 <= 2) gat_walk_one<PASS, 2, 1>(A, lr, dbias, st);
-    else if (f4 <= 4) gat_walk_one<PASS, 4, 1>(A, lr, dbias, st);
-    else if (f4 <= 8) gat_walk_one<PASS, 8, 1>(A, lr, dbias, st);
-    else if (f4 <= 16) gat_walk_one<PASS, 16, 1>(A, lr, dbias, st);
-    else if (f4 <= 32) gat_walk_one<PASS, 32, 1>(A, lr, dbias, st);
-    else if (f4 <= 64) gat_walk_one<PASS, 64, 1>(A, lr, dbias, st);
-    else if (f4 <= 128) gat_walk_one<PASS, 64, 2>(A, lr, dbias, st);
-    else gat_walk_one<PASS, 64, 4>(A, lr, dbias, st);
+    if (f4 <= 1) gat_walk_one<PASS, 1, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 2) gat_walk_one<PASS, 2, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 4) gat_walk_one<PASS, 4, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 8) gat_walk_one<PASS, 8, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 16) gat_walk_one<PASS, 16, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 32) gat_walk_one<PASS, 32, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 64) gat_walk_one<PASS, 64, 1>(A, lr, sums, dbias, st);
+    else if (f4 <= 128) gat_walk_one<PASS, 64, 2>(A, lr, sums, dbias, st);
+    else gat_walk_one<PASS, 64, 4>(A, lr, sums, dbias, st);
     GRP_LAUNCH_CHECK();
     return GRP_OK;
 }
@@ -717,7 +726,8 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
     const int C = m->dims[k];
     float* dZ = p.dZa;
     float* dZ_other = p.dZb;
-    GRP_TRY(launch_softmax_xent(si, C, p.L[k - 1].Hout, ldp4(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp4(C), stats, st));
+    StepSums sums(p.base, (float*)p.base);
+    GRP_TRY(launch_softmax_xent(si, C, p.L[k - 1].Hout, ldp4(C), labels, o->estimator == GRP_EST_NODE_LEVEL, nullptr, dZ, ldp4(C), stats, st, &sums));
     // ---------------- backward
     for (int l = k - 1; l >= 0; --l) {
         const GatLayer& L = p.L[l];
@@ -729,23 +739,16 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
             GatWalk A{};
             A.ptr = g->rowptr; A.idx = g->col; A.n = n; A.F = L.fout; A.Tx = L.Tx; A.ldx = L.ldx; A.pq = L.pq;
             A.rowstat = L.rowstat; A.bias = theta + L.off_b; A.Hout = L.Hout; A.ldh = L.ldh; A.dOut = dZ; A.ldd = L.ldh;
-            A.dst = p.dst; A.dq = p.dq; A.dTx = p.dTx; A.colsum = p.colsum;
+            A.dst = p.dst; A.dq = p.dq; A.dTx = p.dTx; A.colsum = L.colsum;
             A.hout_scale = (drop.on && l < k - 1) ? 1.0f - o->dropout_rate : 1.f;
-            GRP_TRY(launch_gat_walk<GAT_DST>(A, &g->csr_long, p.partials, st, grad + L.off_b));
+            GRP_TRY(launch_gat_walk<GAT_DST>(A, &g->csr_long, p.partials, st, &sums, L.dbias));
             A.ptr = g->colptr; A.idx = g->row;
             GRP_TRY(launch_gat_walk<GAT_SRC>(A, &g->csc_long, p.partials, st));
         }
         GemmTNArgs t;          // dW_ext = H_in^T dT_ext
         t.M = n; t.K = L.fin; t.N = (int)L.ldx; t.A = Hin; t.lda = ldin; t.a_bf16 = in_bf16; t.B = p.dTx; t.ldb = L.ldx;
-        t.C = p.dWx; t.ldc = L.ldx; t.workspace = p.tn_ws; t.workspace_bytes = p.tn_ws_bytes;
+        t.C = L.dWx; t.ldc = L.ldx; t.workspace = L.tn_ws; t.workspace_bytes = L.tn_ws_bytes; t.sums = &sums;
         GRP_TRY(launch_gemm_tn(t, st));
-        {
-            ProfScope ps("gat_param_grad", st);
-            hipLaunchKernelGGL(gat_param_grad_kernel, dim3((unsigned)L.fout), dim3(256), 0, st, (const float*)p.dWx,
-                               (int)L.ldx, theta + L.off_w, theta + L.off_as, theta + L.off_ad, L.fin, L.fout,
-                               grad + L.off_w, grad + L.off_as, grad + L.off_ad);
-            GRP_LAUNCH_CHECK();
-        }
         if (l > 0) {
             GemmNNArgs c;      // dZ_prev = (H_in > 0) * (dT_ext W_ext^T)
             c.planes = p.planes; c.planes_bytes = p.planes_bytes;
@@ -755,6 +758,14 @@ grp_status gat_step(const grp_partition_t* g, const grp_model_desc* m, const grp
             GRP_TRY(launch_gemm_nn(c, st));
         }
         float* sw = dZ; dZ = dZ_other; dZ_other = sw;
+    }
+    GRP_TRY(launch_step_sums(sums, st));
+    for (const GatLayer& L : p.L) {
+        ProfScope ps("gat_param_grad", st);
+        hipLaunchKernelGGL(gat_param_grad_kernel, dim3((unsigned)L.fout), dim3(256), 0, st, (const float*)L.dWx, (const float*)L.dbias,
+                               (int)L.ldx, theta + L.off_w, theta + L.off_as, theta + L.off_ad, L.fin, L.fout,
+                               grad + L.off_w, grad + L.off_as, grad + L.off_ad, grad + L.off_b);
+        GRP_LAUNCH_CHECK();
     }
     return GRP_OK;
 }
