@@ -497,13 +497,12 @@ struct GemmTNArgs {
 };
 grp_status launch_gemm_tn(const GemmTNArgs& a, hipStream_t st);
 
-// out[N] = column sums of A[M x N], every row multiplied by rowmul[m] first (may be null); scratch holds the per-block partials.
+// out[N] = column sums of A[M x N], every row multiplied by rowmul[m] first (may be null); scratch holds the per-block
+// partials until sums has added them up.
 // (room also for the partial sums that softmax_xent and a product that makes C[M x N] leave)
 size_t colsum_workspace_bytes(int64_t M, int32_t N);
 grp_status launch_colsum_scaled(const float* A, int64_t M, int32_t N, int64_t lda, const float* rowmul,
-                                float* out, void* scratch, hipStream_t st, StepSums* sums = nullptr /*as of GemmTNArgs*/);
-// out[N] = sums over the rows of part[blocks x N].
-void launch_colsum_final(const float* part, int64_t blocks, int32_t N, float* out, hipStream_t st);
+                                float* out, void* scratch, StepSums& sums, hipStream_t st);
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 // a, b -> packed pairs hi, mid, lo with a = hi.x + mid.x + lo.x exactly.

@@ -472,7 +472,7 @@ static grp_status gcn_step(const grp_partition_t* g, const grp_model_desc* m, co
         const int64_t ldin = l == 0 ? m->dims[0] : ldp(fin);
         const int in_bf16 = l == 0 && m->feat_dtype == GRP_DTYPE_BF16;
         if (n == 0 || (l == k - 1 && !xent_cols))
-            GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, L.colsum_ws, st, &sums));
+            GRP_TRY(launch_colsum_scaled(dZ, n, fout, ldp(fout), p.grinv, grad + L.off_b, L.colsum_ws, sums, st));
         SpmmArgs s;
         fill_spmm(s, B, true, p.partials);
         s.F = fout; s.X = dZ; s.ldx = ldp(fout); s.scale = GRP_SCALE_RSQRT; s.self_term = sl; s.Y = p.tmpA; s.ldy = ldp(fout);

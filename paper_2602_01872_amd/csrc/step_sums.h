@@ -1,5 +1,5 @@
-// Sums over partial results, a workgroup at a time: of the transposed products' slices and of column sums.  Kernels of one kind are
-// built from them, and the launch that ends a step (step_sums_kernel), which does all that its products and column sums left.
+// Sums over partial results, a workgroup at a time: of the transposed products' slices and of column sums.  The kernel of a lone
+// product is built from them, and the launch that ends a step (step_sums_kernel), which does all that its products and column sums left.
 #pragma once
 #include "common.h"
 
