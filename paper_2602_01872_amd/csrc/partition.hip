@@ -1207,13 +1207,14 @@ __global__ __launch_bounds__(256) void halo_grow_kernel(const int64_t* __restric
         for (int i = 0; i < PER; i += 2) {
             const int64_t e = t0 + (int64_t)i * 256 + 2 * threadIdx.x;
             load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-            load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);      // -2: past the end
+            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // -1: past the end (or an edge's: what is past the end is told by its place)
         }
         uint32_t in[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
+            const int64_t e = t0 + (int64_t)(i & ~1) * 256 + 2 * threadIdx.x + (i & 1);
             const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-            odd += !ok && vs[i] != -2;
+            odd += !ok && e < E;
             in[i] = inner[ok ? vs[i] >> 5 : 0];
             if (!ok) in[i] = 0u;
         }
@@ -1327,6 +1328,7 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     }
     GRP_HIP(hipMemcpyAsync(host, t.counters, sizeof host, hipMemcpyDeviceToHost, st));
     GRP_HIP(hipStreamSynchronize(st));
+    if (host[1]) return fail(GRP_ERANGE, "%llu edges have an endpoint outside [0, %lld)", host[1], (long long)N);      // (edges of no nodes: not seen above)
     const int64_t nnz = (int64_t)(ranged ? host[2] : host[0]);
     h->nnz = nnz;
     if (nnz > cap) {                                     // not written yet, or not all of them

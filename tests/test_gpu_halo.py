@@ -51,6 +51,33 @@ def test_partition_halo_bit_exact(g, kind, N, E, K, hops):
         assert ei.value.status == g.ERANGE
 
 
+@pytest.mark.parametrize("value", [-1, -2, 5000, -(1 << 40)])
+@pytest.mark.parametrize("end", ["src", "dst"])
+def test_halo_ids_out_of_range(g, end, value):
+    """One id outside [0, N), at either end of an edge, in a whole tile of edges, in the tail and last of all: refused, whatever its value."""
+    N, E, K = 5000, 30001, 4
+    s, d = synth.uniform_graph(N, E, seed=61)
+    for at in (5, E - 40, E - 1):
+        bad = {"src": s.clone(), "dst": d.clone()}
+        bad[end][at] = value
+        for hops in (1, 2):
+            print(f"[case] halo bad {end} {value} at {at} hops={hops}", flush=True)
+            with pytest.raises(g.GrappaError) as ei:
+                g.grp_partition_halo(bad["src"].to(DEV), bad["dst"].to(DEV), N, K, 7, 0, hops)
+            assert ei.value.status == g.ERANGE
+
+
+def test_halo_of_no_nodes(g):
+    """Without nodes every edge's ends are out of range."""
+    none, some = torch.zeros(0, dtype=torch.int64, device=DEV), torch.zeros(3, dtype=torch.int64, device=DEV)
+    part = g.grp_partition_halo(none, none, 0, 2, 7, 0, 1)
+    assert part.n == part.nnz == 0
+    part.destroy()
+    with pytest.raises(g.GrappaError) as ei:
+        g.grp_partition_halo(some, some, 0, 2, 7, 0, 1)
+    assert ei.value.status == g.ERANGE
+
+
 @pytest.mark.parametrize("arch,dims", [("sage", [12, 16, 5]), ("gat", [12, 16, 5])])
 def test_train_step_on_a_k_hop_halo_partition(g, arch, dims):
     print(f"[case] halo train step {arch} {dims}", flush=True)
