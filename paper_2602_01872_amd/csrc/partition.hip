@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void edge_scan_kernel(const int64_t* __restric
         for (int i = 0; i < PER; i += 2) {               // a thread takes pairs of consecutive edges
             const int64_t e = e0 + (int64_t)i * 256;
             load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-            load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);     // -2: past the end, neither counted nor an error
+            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);     // past the end: neither counted nor, by its place, an error
         }
         // Eight edges' lookups are requested together, in two stages; a lane that has no need of one reads word 0 (one line for all of
         // them).
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void edge_scan_kernel(const int64_t* __restric
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-            bad += !ok && vs[i] != -2;
+            bad += !ok && (i & ~1) * 256 + (i & 1) < E - e0;
             if (!ok) us[i] = vs[i] = 0;
             wv[i] = own.words[vs[i] >> 5];
             has |= (ok ? 1u : 0u) << i;
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(SCAN_THREADS, Select::WAVES) void edge_scan_keys_ke
                 for (int i = 0; i < SCAN_PER; i += 2) {
                     const int64_t e = e0 + (int64_t)i * SCAN_THREADS;
                     load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-                    load_edge_pair(dst, e, E, vec, -2, vs[i], vs[i + 1]);      // -2: past the end, neither counted nor an error
+                    load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // past the end: neither counted nor, by its place, an error
                 }
             }
             bool odd = false;                                // an id out of range, or no edge

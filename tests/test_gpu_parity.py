@@ -95,6 +95,24 @@ def test_partition_edge_cases_and_errors(g):
         assert ei.value.status == g.EINVAL
 
 
+@pytest.mark.parametrize("value", [-1, -2, None])
+@pytest.mark.parametrize("way", ["ranges", "table", "weighted"])      # of counting in-degrees: up to 2^22 local nodes, above, with weights
+def test_partition_ids_out_of_range(g, way, value):
+    """One id outside [0, N), at either end of an edge, in a whole tile of edges, in the tail and last of all: refused, whatever its value."""
+    N, E = ((1 << 22) + 1 if way == "table" else 5000), 30001
+    s, d = synth.uniform_graph(N, E, seed=17)
+    w = torch.ones(E, device=DEV)
+    for end in (0, 1):
+        for at in (5, E - 40, E - 1):
+            ends = [s.clone(), d.clone()]
+            ends[end][at] = N if value is None else value
+            _note(f"partition {way} end {end} at {at} is {int(ends[end][at])}")
+            a, b = (t.to(DEV) for t in ends)
+            with pytest.raises(g.GrappaError) as ei:
+                g.grp_partition_weighted(a, b, w, N, 1, 7, 0) if way == "weighted" else g.grp_partition(a, b, N, 1, 7, 0)
+            assert ei.value.status == g.ERANGE
+
+
 def test_partition_from_local_coo(g):
     _note("partition_from_local_coo")
     n, E = 3000, 40000
