@@ -158,7 +158,7 @@ struct GatWalk {
     int F;
     const float* Tx;  int64_t ldx;
     const float2* pq;
-    const float2* rowstat;
+    float2* rowstat;                     // (m_v, Z_v); FWD: Z_v negated where out_v is not finite before the ReLU, which hides it; DST: read
     const float* bias;
     int relu;
     float* Hout;      int64_t ldh;       // FWD: output; DST: the layer's stored output
@@ -180,6 +180,7 @@ struct GatRow {                          // per-row constants held by every lane
     float4 vec[NJ];                      // DST: dOut[v,:]; SRC: T[u,:]
     float p;
     float q, mx, inv, c;                 // (SRC: not held)
+    bool all;                            // DST: edges that add zero are walked too
 };
 
 template <int PASS, int G, int NJ>
@@ -193,7 +194,7 @@ __device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t
     }
     const float2 st = A.rowstat[r];
     R.q = A.pq[r].y;
-    R.mx = st.x; R.inv = 1.f / st.y;
+    R.mx = st.x; R.inv = 1.f / fabsf(st.y);
     R.c = 0.f;
     if (PASS == GAT_DST) {
         float cpart = 0.f;
@@ -212,6 +213,7 @@ __device__ __forceinline__ void gat_row_setup(const GatWalk& A, int64_t r, int t
                      R.vec[j].w * (h.w * hs - bb[3]);
         }
         R.c = group_sum<G>(cpart);        // c_v = dOut_v . (out_v - b) = sum_u alpha_uv (dOut_v . t_u)
+        R.all = st.y < 0.f || !(fabsf(R.c) < INFINITY);
     }
 }
 
@@ -221,7 +223,8 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
     // DST adds up alpha_uv (dOut_v . t_u - c_v) LeakyReLU'(pre_uv) over a row.  Without the last factor that sum is zero, so the
     // self edge's slope is taken off every factor: what is left are the edges on the other side of the kink, instead of
     // terms of both signs that cancel to rounding noise (the self edge itself then adds nothing).  The others add nothing and their rows
-    // of T are not fetched (but where c_v is not finite: 0 times that is not zero).  3e5 rows of 256 columns, 3.25
+    // of T are not fetched, but where c_v or one of the t_u is not finite: 0 times that is not zero.  (Where both are, a product dOut_v . t_u that
+    // overflows counts only for the edges across the kink.)  3e5 rows of 256 columns, 3.25
     // skewed edges a row, the bias gradient's column sums included: 308 + 45 -> 225 us.
     const float slope0 = PASS == GAT_DST ? leaky_d(R.p + R.q) : 0.f;
     for (int64_t base = b; base < e; base += G) {
@@ -241,8 +244,7 @@ __device__ __forceinline__ void gat_walk_edges(const GatWalk& A, const GatRow<G,
             mw = mya * (leaky_d(pre) - slope0);
         }
         if constexpr (PASS == GAT_DST) {
-            const bool all = !(fabsf(R.c) < INFINITY);
-            unsigned long long who = __ballot(t < cnt && (all || mw != 0.f));      // (NaN is not 0)
+            unsigned long long who = __ballot(t < cnt && (R.all || mw != 0.f));      // (NaN is not 0)
             if (G < 64) who = (who >> ((threadIdx.x & 63) / G * G)) & ((1ull << (G & 63)) - 1ull);
             while (who) {                                  // the edges that are walked, two at a time
                 const int k0 = __ffsll(who) - 1;
@@ -309,6 +311,7 @@ __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G,
                                                const bool (&live)[NJ], float4 (&acc)[NJ], float scal) {
     if (PASS == GAT_FWD) {
         const float as = __expf(leaky(R.p + R.q) - R.mx) * R.inv;
+        bool odd = false;                 // one of the t_u is not finite (a weight of zero does not hide it)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             if (!live[j]) continue;
@@ -317,6 +320,7 @@ __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G,
             float o[4] = {acc[j].x + as * tv.x, acc[j].y + as * tv.y, acc[j].z + as * tv.z, acc[j].w + as * tv.w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
+                odd = odd || !(fabsf(o[q]) < INFINITY);
                 if (col + q < A.F) {
                     o[q] += A.bias[col + q];
                     if (A.relu) o[q] = o[q] > 0.f ? o[q] : 0.f;
@@ -326,6 +330,7 @@ __device__ __forceinline__ void gat_row_finish(const GatWalk& A, const GatRow<G,
             }
             *reinterpret_cast<float4*>(A.Hout + r * A.ldh + col) = make_float4(o[0], o[1], o[2], o[3]);
         }
+        if (odd) A.rowstat[r].y = -fabsf(A.rowstat[r].y);      // (every lane that sees one writes the same)
     } else if (PASS == GAT_DST) {
         if (t == 0) {
             A.dst[r] = make_float4(R.q, R.mx, R.inv, R.c);

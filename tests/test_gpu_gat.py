@@ -123,3 +123,48 @@ def test_gat_more_rows_than_one_round_of_workgroups(g, degree, dims):
         return ostep.train_step(op, "gat", dims, theta.double().numpy(), x.double().numpy(), y.numpy(), None, relu_flip=relu_flip, near_kink=near_kink)
     assert_step_grads_close(grad.cpu().numpy(), oracle_fn, "gat", dims, TOL_FP32)
     part.destroy()
+
+
+@pytest.mark.parametrize("hidden", [3, 16, 128, 256, 300])
+def test_gat_rows_of_t_that_overflowed(g, hidden):
+    """A hidden layer's t_u that overflowed to -inf in one column is hidden from its destinations' outputs by the ReLU, but not from their score
+    gradients: dq_v has 0 * inf there, so that da_dst is NaN although no edge adds anything else to it.  Every gradient is finite or NaN as
+    single-precision autograd of the same formulas says."""
+    N, dims = 900, [4, hidden, 3]
+    print(f"[case] gat overflow dims={dims}", flush=True)
+    s, d = synth.uniform_graph(N, 4 * N, seed=71)
+    s, d = torch.cat([s, torch.arange(N)]), torch.cat([d, torch.full((N,), 7)])      # node 7: a row in chunks
+    x, y, theta = synth.normal_matrix(N, dims[0], 72), synth.labels(N, dims[-1], 73), synth.model_weights("gat", dims, 74)
+    x = x.abs()
+    x[:, 0] = 0.0
+    x[5, 0] = 4.0
+    at_w1 = dims[0] * hidden + 3 * hidden                # W, a_src, a_dst, bias of the first layer
+    theta[:at_w1] = theta[:at_w1].abs()                  # every score of it is positive: no edge is across the kink from its self edge
+    theta[0] = -3e38                                     # times 4: t_5 overflows in column 0, which neither score reads
+    theta[dims[0] * hidden] = theta[dims[0] * hidden + hidden] = 0.0
+    part = g.grp_partition(s.to(DEV), d.to(DEV), N, 1, 3, 0)
+    model, opts = g.model_desc(g.ARCH_GAT, dims), g.step_opts(estimator=g.EST_NONE, full_graph=True)
+    ws = torch.empty(g.grp_step_workspace_bytes(part, model, opts), dtype=torch.uint8, device=DEV)
+    grad, stats = torch.full((g.grp_param_count(model),), 1e9, device=DEV), g.new_stats(1)
+    g.grp_train_step(part, model, opts, x.to(DEV), y.to(DEV), None, theta.to(DEV), ws, grad, stats)
+    got = grad.cpu()
+
+    th = theta.clone().requires_grad_()
+    u, v = torch.cat([s, torch.arange(N)]), torch.cat([d, torch.arange(N)])
+    h, at = x, 0
+    for fin, fout in zip(dims[:-1], dims[1:]):
+        W, a_s, a_d, b = th[at:at + (fin + 3) * fout].split([fin * fout, fout, fout, fout])
+        W = W.view(fin, fout)
+        e = torch.nn.functional.leaky_relu((h @ (W @ a_s))[u] + (h @ (W @ a_d))[v], 0.2)
+        w = torch.exp(e - torch.zeros(N).scatter_reduce(0, v, e, "amax", include_self=False)[v].detach())
+        alpha = w / torch.zeros(N).index_add(0, v, w)[v]
+        h = torch.zeros(N, fout).index_add(0, v, alpha[:, None] * (h @ W)[u]) + b
+        at += (fin + 3) * fout
+        if at == at_w1:
+            h = torch.relu(h)
+    torch.nn.functional.cross_entropy(h, y.long()).backward()
+    da_dst = slice(dims[0] * hidden + hidden, dims[0] * hidden + 2 * hidden)
+    assert bool(th.grad[da_dst].isnan().all()) and bool(th.grad[at_w1:].isfinite().all())
+    assert torch.equal(got.isfinite(), th.grad.isfinite())
+    assert rel_err(got[at_w1:].numpy(), th.grad[at_w1:].numpy()) < TOL_FP32
+    part.destroy()
