@@ -1271,6 +1271,8 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     const size_t bits_bytes = ((size_t)t.n_words + 1) * sizeof(uint32_t);
     GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
     int64_t n = 0;
+    // destinations of kept edges: of one hop about a K-th of the nodes; counted, which costs some 6 us, where all edges would be much room
+    int64_t n_inner = hops == 1 ? cdiv(N, K) : N;
     if (N > 0) {
         const OwnerTest test = owner_test(seed, (uint32_t)K, (uint32_t)part_id);
         hipLaunchKernelGGL(node_bits_kernel<OwnerTest>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words, test, owned);
@@ -1286,10 +1288,17 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
                 GRP_LAUNCH_CHECK();
             }
         }
-        unsigned long long nbad = 0;
-        GRP_HIP(hipMemcpyAsync(&nbad, t.counters + 1, sizeof nbad, hipMemcpyDeviceToHost, st));
+        const bool counted = hops > 1 && E > (1 << 22);
+        if (counted) {
+            hipLaunchKernelGGL(count_bits_kernel, dim3((unsigned)std::min<int64_t>(cdiv(t.n_words, 256), 4096)), dim3(256), 0, st, (const uint32_t*)inner,
+                               t.n_words, t.counters + 2);
+            GRP_LAUNCH_CHECK();
+        }
+        unsigned long long grown[2] = {0, 0};
+        GRP_HIP(hipMemcpyAsync(grown, t.counters + 1, sizeof grown, hipMemcpyDeviceToHost, st));
         GRP_TRY(count_node_set(N, t, &n, st));           // (waits)
-        if (nbad) return fail(GRP_ERANGE, "edges have an endpoint outside [0, %lld)", (long long)N);
+        if (counted) n_inner = (int64_t)grown[1];
+        if (grown[0]) return fail(GRP_ERANGE, "edges have an endpoint outside [0, %lld)", (long long)N);
     }
     if (n >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "partition has %lld >= 2^31 local nodes", (long long)n);
     h->n = n;
@@ -1305,19 +1314,26 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
         hipLaunchKernelGGL(halo_owned_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, own, (const uint32_t*)owned, h->base_mask);
         GRP_LAUNCH_CHECK();
     }
-    // As a hash build (partition_impl): one pass writes the keys too, into a buffer for twice the expected edges of a single hop.
+    // As a hash build (partition_impl): one pass writes the keys too, into a buffer for twice the edges that as many destinations have
+    // on average, and the local ids of as many.  Where that room is not to be had, edges and in-degrees are counted first
+    // (which needs no room but the keys' in the end).
     const int64_t spans = cdiv(n > 0 ? n : 1, (int64_t)1 << SPAN_BITS);
-    const bool ranged = N < ((int64_t)1 << 31) && spans <= SPANS_MAX && E > 0;
+    bool ranged = N < ((int64_t)1 << 31) && spans <= SPANS_MAX && E > 0;
     const HaloEdges select{inner};
     unsigned long long host[3] = {0, 0, 0};
     DevBuf keys, keys_alt, idbuf;
-    int64_t cap = 0;
+    int64_t cap = 0, id_cap = 0;
+    size_t id_pitch = 0;
     if (ranged) {
-        cap = std::min<int64_t>(E, hops == 1 ? 2 * (E / K) + (1 << 20) : (int64_t)1 << 28);
-        const int64_t id_cap = std::min<int64_t>(E, (int64_t)1 << 30);
-        const size_t id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
-        GRP_TRY(keys.alloc((size_t)cap * sizeof(uint64_t)));
-        GRP_TRY(idbuf.alloc(id_pitch + (size_t)cdiv(E, SCAN_TILE) * (size_t)(spans + 1) * sizeof(uint32_t)));
+        auto room = [&](int64_t nodes) { return std::min<int64_t>(E, (int64_t)(2.0 * (double)E * (double)nodes / (double)std::max<int64_t>(N, 1)) + (1 << 20)); };
+        cap = room(n_inner);
+        id_cap = std::min<int64_t>(room(n), (int64_t)1 << 30);
+        id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
+        ranged = keys.alloc((size_t)cap * sizeof(uint64_t)) == GRP_OK &&
+                 idbuf.alloc(id_pitch + (size_t)cdiv(E, SCAN_TILE) * (size_t)(spans + 1) * sizeof(uint32_t)) == GRP_OK;
+        if (!ranged) { keys.free(); idbuf.free(); cap = 0; }
+    }
+    if (ranged) {
         GRP_TRY(launch_scan_keys(select, src, dst, E, N, own, n, spans, (unsigned long long*)h->d_global_in, t.counters, keys.as<uint64_t>(), cap,
                                  idbuf.as<uint32_t>(), id_cap, (uint32_t*)((char*)idbuf.p + id_pitch), st));
     } else if (E > 0) {
@@ -1331,16 +1347,17 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     if (host[1]) return fail(GRP_ERANGE, "%llu edges have an endpoint outside [0, %lld)", host[1], (long long)N);      // (edges of no nodes: not seen above)
     const int64_t nnz = (int64_t)(ranged ? host[2] : host[0]);
     h->nnz = nnz;
-    if (nnz > cap) {                                     // not written yet, or not all of them
+    idbuf.free();
+    // not written yet, or not all of them, or in a buffer with more to spare than there is for the other
+    if (nnz > cap || keys_alt.alloc((size_t)nnz * sizeof(uint64_t)) != GRP_OK) {
         keys.free();
         GRP_TRY(keys.alloc((size_t)nnz * sizeof(uint64_t)));
+        GRP_TRY(keys_alt.alloc((size_t)nnz * sizeof(uint64_t)));
         GRP_HIP(hipMemsetAsync(t.counters + 2, 0, sizeof(unsigned long long), st));
         hipLaunchKernelGGL(edge_keys_kernel<HaloSelect>, dim3(grid_for(E)), dim3(256), 0, st, src, dst, E, HaloSelect{own, inner}, t.counters + 2,
                            keys.as<uint64_t>());
         GRP_LAUNCH_CHECK();
     }
-    idbuf.free();
-    GRP_TRY(keys_alt.alloc((size_t)nnz * sizeof(uint64_t)));
     return build_csr_csc(h, keys.as<uint64_t>(), keys_alt.as<uint64_t>(), st);
 }
 
