@@ -737,7 +737,8 @@ __global__ __launch_bounds__(256) void bucket_unpack_kernel(const uint32_t* __re
 // keys: nnz of them, clobbered; packed: scratch of the same size; scratch: bucket_scratch_bytes.  Fills the handle's CSR, CSC and
 // degrees and the lists of its long rows (arrays of the worst case's size, or null where no row can be long); waits for the lists'
 // lengths.  long_edges: the edges of each direction's long rows.  *done = false: the build was refused, keys holds them again.
-// csc_alone: the keys are source << 32 | destination, and the CSC is all that is filled (as the first direction of what is below).
+// csc_alone: the keys are source << 32 | destination, and the CSC is all that is filled (as the first direction of what is below); keys of a
+// refused build are lost (its caller makes them anew, a range at a time).
 grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys, uint64_t* packed, void* scratch, int64_t (&long_edges)[2],
                         bool* done, hipStream_t st, bool csc_alone) {
     const int64_t n = h->n, nnz = h->nnz;
@@ -767,7 +768,7 @@ grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys,
     GRP_HIP(hipStreamSynchronize(st));
     *done = totals[4] <= s.hubs_most;
     if (!*done) {
-        if (totals[4] == REFUSED_AT_ONCE) return GRP_OK;   // (keys are untouched)
+        if (csc_alone || totals[4] == REFUSED_AT_ONCE) return GRP_OK;      // (keys are untouched if refused at once)
         hipLaunchKernelGGL(bucket_unpack_kernel, dim3((unsigned)cdiv(nnz, 256)), dim3(256), 0, st, (const uint32_t*)packed, nnz, p, (const uint32_t*)s.start,
                            keys);
         GRP_LAUNCH_CHECK();

@@ -658,7 +658,7 @@ struct BucketPlan {
 bool bucket_plan(int64_t n, int64_t nnz, BucketPlan* p);      // false: sizes that are not built this way
 size_t bucket_scratch_bytes(const BucketPlan& p, int64_t nnz);
 grp_status bucket_build(grp_partition_t* h, const BucketPlan& p, uint64_t* keys, uint64_t* packed, void* scratch, int64_t (&long_edges)[2],
-                        bool* done, hipStream_t st, bool csc_alone = false);          // *done = false: refused, and the keys as they were
+                        bool* done, hipStream_t st, bool csc_alone = false);          // *done = false: refused, and the keys as they were (csc_alone: lost)
 
 // M(x): the SplitMix64 finaliser of x + 0x9E3779B97F4A7C15 (the sampler's and the seed order's hash step)
 __host__ __device__ __forceinline__ uint64_t mixM(uint64_t x) {

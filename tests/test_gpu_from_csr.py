@@ -52,6 +52,7 @@ def _assert_equal(part, want):
     ("rmat", 1 << 13, 400000, 0),           # all edges at once: buckets, some of them crowded
     ("rmat", 300000, 50000, 0),             # far more rows than keys
     ("one source", 2000, 1100000, 0),       # a bucket of more keys than one workgroup takes: refused, and sorted instead
+    ("two sources", 2000, 2000000, 0),      # no such bucket, but hubs whose jobs would read 245 times the keys: refused once the keys are moved
 ])
 def test_from_csr_bit_exact(g, kind, n, E, slice_edges):
     _note(f"from_csr {kind} n={n} E={E} slice_edges={slice_edges}")
@@ -59,6 +60,8 @@ def test_from_csr_bit_exact(g, kind, n, E, slice_edges):
         s, d = synth.uniform_graph(n, E, seed=31)
     elif kind == "one source":
         s, d = torch.full((E,), 5, dtype=torch.int64), torch.arange(E) % n
+    elif kind == "two sources":
+        s, d = 5 + 995 * (torch.arange(E) % 2), torch.arange(E) // 2 % n
     else:
         s, d = synth.rmat_graph(max(2, (n - 1).bit_length()), E, seed=32, n_nodes=n)
     want = ograph.local_graph_from_edges(s.numpy(), d.numpy(), n)
