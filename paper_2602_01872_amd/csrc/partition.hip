@@ -263,20 +263,26 @@ __global__ __launch_bounds__(256) void edge_scan_kernel(const int64_t* __restric
         for (int i = 0; i < PER; i += 2) {               // a thread takes pairs of consecutive edges
             const int64_t e = e0 + (int64_t)i * 256;
             load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);     // past the end: neither counted nor, by its place, an error
+            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);     // past the end: out of range, and looked at again below
         }
         // Eight edges' lookups are requested together, in two stages; a lane that has no need of one reads word 0 (one line for all of
         // them).
         uint2 wv[PER], wu[PER];
+        bool odd = false;                                // an id out of range, or no edge
         uint32_t has = 0, both = 0;                      // bit i: the destination, and also the source, of edge i is in the set
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-            bad += !ok && (i & ~1) * 256 + (i & 1) < E - e0;
+            odd = odd || !ok;
             if (!ok) us[i] = vs[i] = 0;
             wv[i] = own.words[vs[i] >> 5];
             has |= (ok ? 1u : 0u) << i;
         }
+        if (__any(odd))                                  // (read again, by place, as an id may have any value; counted with the others 595 -> 628 us, 62e6 edges)
+            for (int i = 0; i < PER; ++i) {
+                const int64_t e = e0 + (i & ~1) * 256 + (i & 1);
+                bad += e < E && !(src[e] >= 0 && dst[e] >= 0 && src[e] < N && dst[e] < N);
+            }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             if (!word_has(wv[i], vs[i])) has &= ~(1u << i);
@@ -466,7 +472,7 @@ __global__ __launch_bounds__(SCAN_THREADS, Select::WAVES) void edge_scan_keys_ke
                 for (int i = 0; i < SCAN_PER; i += 2) {
                     const int64_t e = e0 + (int64_t)i * SCAN_THREADS;
                     load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-                    load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // past the end: neither counted nor, by its place, an error
+                    load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // past the end: out of range, and looked at again below
                 }
             }
             bool odd = false;                                // an id out of range, or no edge
@@ -1207,14 +1213,16 @@ __global__ __launch_bounds__(256) void halo_grow_kernel(const int64_t* __restric
         for (int i = 0; i < PER; i += 2) {
             const int64_t e = t0 + (int64_t)i * 256 + 2 * threadIdx.x;
             load_edge_pair(src, e, E, vec, 0, us[i], us[i + 1]);
-            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // -1: past the end (or an edge's: what is past the end is told by its place)
+            load_edge_pair(dst, e, E, vec, -1, vs[i], vs[i + 1]);      // past the end: out of range, but no error
         }
+        if (t0 + 256 * PER > E)                              // (uniform; by its place: an edge's id may have any value)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) odd -= t0 + (i & ~1) * 256 + 2 * threadIdx.x + (i & 1) >= E;
         uint32_t in[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int64_t e = t0 + (int64_t)(i & ~1) * 256 + 2 * threadIdx.x + (i & 1);
             const bool ok = us[i] >= 0 && vs[i] >= 0 && us[i] < N && vs[i] < N;
-            odd += !ok && e < E;
+            odd += !ok;
             in[i] = inner[ok ? vs[i] >> 5 : 0];
             if (!ok) in[i] = 0u;
         }
