@@ -1279,8 +1279,6 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     const size_t bits_bytes = ((size_t)t.n_words + 1) * sizeof(uint32_t);
     GRP_HIP(hipMemsetAsync(t.counters, 0, 4 * sizeof(unsigned long long), st));
     int64_t n = 0;
-    // destinations of kept edges: of one hop about a K-th of the nodes; counted, which costs some 6 us, where all edges would be much room
-    int64_t n_inner = hops == 1 ? cdiv(N, K) : N;
     if (N > 0) {
         const OwnerTest test = owner_test(seed, (uint32_t)K, (uint32_t)part_id);
         hipLaunchKernelGGL(node_bits_kernel<OwnerTest>, dim3((unsigned)cdiv((t.n_words + 1) * 32, 256)), dim3(256), 0, st, N, t.n_words, test, owned);
@@ -1296,17 +1294,10 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
                 GRP_LAUNCH_CHECK();
             }
         }
-        const bool counted = hops > 1 && E > (1 << 22);
-        if (counted) {
-            hipLaunchKernelGGL(count_bits_kernel, dim3((unsigned)std::min<int64_t>(cdiv(t.n_words, 256), 4096)), dim3(256), 0, st, (const uint32_t*)inner,
-                               t.n_words, t.counters + 2);
-            GRP_LAUNCH_CHECK();
-        }
-        unsigned long long grown[2] = {0, 0};
-        GRP_HIP(hipMemcpyAsync(grown, t.counters + 1, sizeof grown, hipMemcpyDeviceToHost, st));
+        unsigned long long nbad = 0;
+        GRP_HIP(hipMemcpyAsync(&nbad, t.counters + 1, sizeof nbad, hipMemcpyDeviceToHost, st));
         GRP_TRY(count_node_set(N, t, &n, st));           // (waits)
-        if (counted) n_inner = (int64_t)grown[1];
-        if (grown[0]) return fail(GRP_ERANGE, "edges have an endpoint outside [0, %lld)", (long long)N);
+        if (nbad) return fail(GRP_ERANGE, "edges have an endpoint outside [0, %lld)", (long long)N);
     }
     if (n >= ((int64_t)1 << 31)) return fail(GRP_ERANGE, "partition has %lld >= 2^31 local nodes", (long long)n);
     h->n = n;
@@ -1322,9 +1313,10 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
         hipLaunchKernelGGL(halo_owned_kernel, dim3((unsigned)cdiv(N, 256)), dim3(256), 0, st, N, own, (const uint32_t*)owned, h->base_mask);
         GRP_LAUNCH_CHECK();
     }
-    // As a hash build (partition_impl): one pass writes the keys too, into a buffer for twice the edges that as many destinations have
-    // on average, and the local ids of as many.  Where that room is not to be had, edges and in-degrees are counted first
-    // (which needs no room but the keys' in the end).
+    // As a hash build (partition_impl): one pass writes the keys too.  Room for twice the expected edges of a single hop, whose destinations are a
+    // random part of the nodes; for all edges, up to 2^28, of several, and for the local ids of all, up to 2^30: halo nodes are those with
+    // many edges (62e6 of a skewed graph, ids of the nodes' share of them: the rest, counted one by one, took the pass from 657 to 1037 us).  Where
+    // that room is not to be had, edges and in-degrees are counted first, which needs none.
     const int64_t spans = cdiv(n > 0 ? n : 1, (int64_t)1 << SPAN_BITS);
     bool ranged = N < ((int64_t)1 << 31) && spans <= SPANS_MAX && E > 0;
     const HaloEdges select{inner};
@@ -1333,9 +1325,8 @@ static grp_status halo_partition_impl(const int64_t* src, const int64_t* dst, in
     int64_t cap = 0, id_cap = 0;
     size_t id_pitch = 0;
     if (ranged) {
-        auto room = [&](int64_t nodes) { return std::min<int64_t>(E, (int64_t)(2.0 * (double)E * (double)nodes / (double)std::max<int64_t>(N, 1)) + (1 << 20)); };
-        cap = room(n_inner);
-        id_cap = std::min<int64_t>(room(n), (int64_t)1 << 30);
+        cap = std::min<int64_t>(E, hops == 1 ? 2 * (E / K) + (1 << 20) : (int64_t)1 << 28);
+        id_cap = std::min<int64_t>(E, (int64_t)1 << 30);
         id_pitch = (((size_t)id_cap * sizeof(uint32_t)) + 255) & ~(size_t)255;
         ranged = keys.alloc((size_t)cap * sizeof(uint64_t)) == GRP_OK &&
                  idbuf.alloc(id_pitch + (size_t)cdiv(E, SCAN_TILE) * (size_t)(spans + 1) * sizeof(uint32_t)) == GRP_OK;
