@@ -545,7 +545,7 @@ def run_evidence_workload(args, g, synth, torch, dev):
     dt, dt_med = _timed_steps(torch, fn, args.warmup, args.steps)
     dt_eager = dt
     if wl == "c3-step":
-        # a chain of 36 small launches: the host's launch cost bounds the uncaptured step, so the step is also
+        # a chain of 32 small launches: the host's launch cost bounds the uncaptured step, so the step is also
         # captured once in a HIP graph and the replays are timed (the same work: nothing in the graph depends on
         # the captured batch; a trainer rewrites the seed buffer and the device-resident batch id between replays)
         side = torch.cuda.Stream()

@@ -441,8 +441,7 @@ __device__ __forceinline__ void stats_partial_block(uint32_t block, const StatsA
 }
 
 // A step's first launch: statistics, degree scales and weights are independent, and a launch costs as much as any of them does on a small
-// partition (10 000 nodes in four partitions: an iteration of 28 launches 148 us, of 25 132 us;
-// the other launch it lost is that of the statistics' end, which the record's kernel does with the loss).
+// partition.  (The end of the statistics is done with the loss's, by the workgroup that makes the record: step_sums_kernel.)
 template <int MOST>
 __device__ __forceinline__ void prelude_kernel_body(unsigned gx, const StatsArgs& stats, const DegreeScales& degrees, uint32_t degree_blocks,
                                                     const PackJobsOf<MOST>& pack) {
@@ -517,7 +516,7 @@ __device__ __forceinline__ void record_block(const RecordArgs& a) {
         out->nnz_used = nnz_used;
     }
 }
-__global__ __launch_bounds__(256) void record_kernel(RecordArgs a) { record_block(a); }
+__global__ __launch_bounds__(256) void record_kernel(RecordArgs a) { record_block(a); }      // (an attention step without nodes: it has no sums)
 
 // A step's last launch: its record and every sum over partial results that only its gradient waits for.  They are independent, and a launch
 // costs more than any of them on a small partition or batch (a GCN of two layers on four partitions of 2500 rows: five launches of 2.5 to 5 us

@@ -12,9 +12,9 @@
 // follow from dW_ext = H^T dT_ext by the chain rule of the two extra columns.
 //
 // No per-edge state is kept: alpha_uv is recomputed from four per-node scalars (p_u, q_v, the
-// row maximum m_v and the row sum Z_v), so the reverse pass can walk the CSC (rows = sources,
-// for dT and dp) and the CSR (rows = destinations, for dq) independently, each row summing in
-// its stored edge order: no floating-point atomics, bit-reproducible.
+// row maximum m_v and the row sum Z_v).  The reverse pass walks the CSR (rows = destinations, for dq
+// and what an edge needs of its destination) and then, with that, the CSC (rows = sources, for dT and dp),
+// each row summing in its stored edge order: no floating-point atomics, bit-reproducible.
 //
 // Mapping as in the SpMM: a group of G lanes owns a row, lane t owns columns 4*(t + G*j); rows
 // longer than SPMM_LONG_ROW edges are walked in the partition's chunks by whole workgroups.

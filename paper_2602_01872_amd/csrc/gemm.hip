@@ -44,7 +44,8 @@ constexpr int BK = 32;      // k-tile depth
 // Resident workgroups per CU that the kernels are built for: three of 168 registers, but two where the partial sums of a tile would
 // not fit beside the rest and were spilled (NT, 128 columns with B split in the kernel: K = N = 256 over 3e5 rows 380 us with three,
 // 338 with two; TN with two 32 x 32 tiles per wavefront: K = 256, N = 47 129 and 112 us, with four: 1127 and 323).
-// Four of 128 where 64 columns of an fp32 product take hardly more (130 if left alone).
+// Four of 128 where 64 columns of an fp32 product take hardly more (130 if left alone): steps on graphs of few edges, us with three and four: GCN 128-48-40
+// over 1e5 rows 199 and 195, SAGE 100-64-64-47 over 3e5 910 and 903, GCN 256-64-64 over 2^20 2019 and 2014; 2e4 rows and fewer the same.
 constexpr int nt_wgs(int TN, bool pre, bool lean = false) { return TN >= 8 && !pre ? 2 : TN == 4 && pre && lean ? 4 : 3; }
 constexpr int tn_wgs(int tiles) { return tiles > 1 ? 2 : 3; }
 constexpr int NT_PRE_SLABS = 512;      // products over fewer slabs of 128 rows whose B is not ready split it in the kernel (a launch for the planes costs 3 us)
@@ -1233,6 +1234,8 @@ __device__ __forceinline__ void gemm_tn_kernel_body(unsigned gx, GemmTNArgs g, i
     constexpr int QA = BKA / 4, QB = BN / 4;               // column groups of a tile
     constexpr int TA = QA * (BK / 8), TB = QB * (BK / 8);  // staging threads of each operand
     constexpr int A0 = TA % 64 == 0 ? 0 : TB, B0 = A0 ? 0 : TA;      // their first threads
+    // (Written for either order, the narrowest bf16 tiles have 81 to 85 registers in their 40 bytes of scratch where 13 were: 3e5 rows, K = N = 64
+    // 63.5 -> 50.8 us, K = 256, N = 32 83.2 -> 58.2, 3e3 rows 10.2 -> 9.9.)
     static_assert((A0 ? TB : TA) % 64 == 0 && TA + TB <= 256 && QA % 8 == 0 && QB % 8 == 0, "an operand is staged by whole wavefronts");
     __shared__ __attribute__((aligned(16))) unsigned char lds[3 * (PLANE_A + PLANE_B)];
     unsigned char* const As = lds;

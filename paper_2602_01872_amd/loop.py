@@ -14,11 +14,15 @@ from .controller import Controller
 
 
 # Full-graph steps are merged, at most MERGE_STEPS at a time, while a step's workspace is at most this large (each merged step needs one of
-# its own, so this also bounds the memory).  Eight steps one by one / merged by two / four / eight, us, workspace of one step:
-#   GraphSAGE 100-256-256-47   26 MiB 1661/917/526/355   117 MiB 2703/1927/1552/1389   369 MiB 5750/4873/4485/4332   706 MiB 8827/8842/8832/8828
-#   GCN 64-128-16               5 MiB 959/527/303/185     70 MiB 1409/885/605/498      136 MiB 1771/1188/980/915     498 MiB 3917/3458/3370/3182
-# (measured on workspaces that held one layer's partial sums at a time; every further layer's, at most 512 tiles of 64 KiB and their column
-# sums, come on top)
+# its own, so this also bounds the memory).  A workspace holds the partial sums of every layer, at most 512 tiles of 64 KiB and their column
+# sums, whatever the number of rows: a further layer counts for them, as it does not make the launches longer.  Eight steps on R-MAT graphs of
+# 10 edges a row, one by one / merged by two / four / eight, us, workspace of one step:
+#   GraphSAGE 100-256-256-47     60 MiB 1496/919/654/529       164 MiB 2524/2056/1773/1675   409 MiB 5581/4912/4569/4366   543 MiB 7307/6512/6148/5987
+#     eight layers, 256 wide    178 MiB 5043/3503/2692/2214    455 MiB 9020/7500/6692/6349   683 MiB 14129/12509/11602/11225
+#   GCN 64-128-16                14 MiB 676/385/225/148        142 MiB 1654/1267/1085/1032
+#     eight layers, 64 wide      27 MiB 2214/1428/947/706      184 MiB 6292/4398/3477/3057
+# From 2^16 rows on products are large launches, and a step that makes them is not merged (744 MiB of three layers 9580/9599/9601/9593); what the
+# limit keeps from it is wide models of many layers, for their memory's sake (eight layers on uniform graphs, 973 MiB 20101/18916/18149/17702).
 MERGE_WORKSPACE_BYTES = 512 << 20
 MERGE_LAYER_BYTES = 34 << 20
 MERGE_STEPS = 8
